@@ -123,9 +123,11 @@ int mst_layer_export_dense(const mst_layer_t* layer, float* W_dev, uint8_t* M_de
 
 /* The active weights as one fp32 vector in ascending flat-index order, for the caller's
  * optimiser to update in place.  After changing them call mst_layer_sync_values: it copies
- * the values into whatever the products read (the entries of built index views, a dense
- * weight copy that is in use) with one or two kernels on `stream`, nothing else; products
- * recorded into a HIP graph therefore see the new values on their next replay.  Every
+ * the values into whatever the products read (the entries of the index views that a product has
+ * walked since they were built, a dense weight copy that is in use) with one or two kernels on
+ * `stream`, nothing else; products recorded into a HIP graph therefore see the new values on
+ * their next replay.  (A built view that no product has walked yet takes the values before its
+ * first walk.)  Every
  * mask update changes the set and therefore the meaning of position k of this vector. */
 int mst_layer_values(mst_layer_t* layer, float** vals_dev, int64_t* nnz);
 int mst_layer_sync_values(mst_layer_t* layer, mst_stream_t stream);
@@ -151,12 +153,13 @@ int mst_layer_uses_dense(const mst_layer_t* layer, mst_dtype act, int T, int wei
 int mst_layer_set_prune_lambda(mst_layer_t* layer, float lambda);
 int64_t mst_layer_nnz(const mst_layer_t* layer);
 
-/* Launch shape of the sparse products' SpMM kernel: tokens per workgroup (128 or 64) and
- * quads of four rows per wavefront (2, 3 or 4 with 128 tokens; 2, 3, 4, 6 or 8 with 64).  By
- * default the library chooses per call from T, the layer's shape and its density; every
- * shape gives bit-identical results.  This call pins one shape for all later calls of the
- * process (tests and tuning); (0, 0) returns to the automatic choice.  Not thread-safe.
- * MST_ERR_ARG for a combination that does not exist. */
+/* Launch shape of the sparse Y / dX kernel.  A workgroup takes 64 tokens and one to six blocks of
+ * 128 rows; the library chooses per call from T, the layer's shape and its density, and every shape
+ * gives bit-identical results.  This call pins one for all later calls of the process (tests and
+ * tuning), (0, 0) returns to the automatic choice.  The accepted pairs are those of the launch
+ * shapes that earlier kernels had: (128, 2), (128, 3), (128, 4) select 1, 2, 3 row blocks, (64, 2),
+ * (64, 3), (64, 4), (64, 6), (64, 8) select 1, 2, 4, 5, 6.  Not thread-safe.
+ * MST_ERR_ARG for another pair. */
 int mst_spmm_force_shape(int tokens_per_workgroup, int quads_per_wavefront);
 
 /* Heavy rows.  When the index views of a layer are built, rows of W . M that hold at least a
@@ -192,13 +195,13 @@ int mst_sparse_fc_bwd_weight(const mst_layer_t* layer, const void* dY_dev, const
 
 /* For callers that cannot allocate or pass a workspace (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): mst_sparse_fc_bwd_weight with its scratch
- * -- the per-token-tile partial sums of the SDDMM -- in a device array that is part of the
+ * -- the per-token-tile partial sums of the weight gradient -- in a device array that is part of the
  * library (mst_static_scratch_bytes() = 64 MiB, held by every GPU the library runs on until
  * the process ends).  Always runs the sparse kernels (never the dense-gradient variant), so
  * dW_dev equals mst_sparse_fc_bwd_weight's result exactly on the sparse path and up to the
  * order of the fp32 sums where that call would use a dense contraction.  Calls no allocating
- * routine.  MST_ERR_WORKSPACE when ceil(T / 128) planes of partial sums (8 floats per pair of
- * entry slots of the larger index view at the layer's CAPACITY) exceed the array: e.g. a
+ * routine.  MST_ERR_WORKSPACE when ceil(T / 128) planes of 4 floats per active weight of the layer's
+ * CAPACITY (plus 16 per four rows and 128 contraction indices) exceed the array: e.g. a
  * 768 x 3072 layer of capacity 177 k fits up to T = 2944.  All calls on one GPU share the
  * array: calls that overlap in time on one GPU (other streams, other threads) race.  The
  * first call on a device looks the array's address up (hipGetSymbolAddress); make that call
@@ -220,9 +223,9 @@ int mst_sparse_fc_bwd(const mst_layer_t* layer, const void* dY_dev, const void* 
                       float* dX_dev, float* dW_vals_dev, int T, mst_dtype act,
                       void* ws_dev, size_t ws_bytes, mst_stream_t stream);
 
-/* Test hook like mst_spmm_force_shape for the shared walk of mst_sparse_fc_bwd:
- * (8, 3) .. (8, 5), (16, 1) or (16, 2) wavefronts per workgroup x quads per wavefront, (0, 0) = automatic.
- * Every shape gives the same results. */
+/* Test hook like mst_spmm_force_shape for the shared walk of mst_sparse_fc_bwd (one to four row
+ * blocks per workgroup): the accepted pairs (16, 1), (16, 2), (8, 3), (8, 4), (8, 5) select 1, 2, 2, 3, 4
+ * of them, (0, 0) = automatic.  Every shape gives the same results. */
 int mst_bwd_force_shape(int wavefronts_per_workgroup, int quads_per_wavefront);
 
 /* The dense fp32 products (the dense gradient below, and the three products of a layer on the
@@ -254,8 +257,8 @@ int mst_dense_grad(const void* dY_dev, const void* X_dev, float* G_dev, int T, i
  * step), the middle part of mst_sparse_fc_bwd_weight_update as a call of its own. */
 int mst_gather_active(const mst_layer_t* layer, const float* G_dev, float* dW_dev, mst_stream_t stream);
 
-/* What the index views of a layer store.  A view keeps, per chunk of 128 contraction indices
- * and quad of four rows, as many steps as the longest of the four rows needs, padded to an
+/* What the index views of a layer store.  A view keeps, per chunk of up to 640 contraction indices
+ * and octet of eight rows, as many steps as the longest of the eight rows needs, padded to an
  * even count; each step has one entry slot per row.  efficiency = nnz / slots is the share of
  * walk steps that do real work (for the row view: of the entries it holds, nnz minus those of
  * the heavy rows, see mst_heavy_rows).  Synchronises `stream` (reads a few counters back). */

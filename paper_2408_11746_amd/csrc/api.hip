@@ -1,5 +1,6 @@
 // The C-ABI entry points that launch device work: argument checks on the host, then
 // dispatch to the sparse kernels or, for dense layers, to the masked dense MFMA path.
+#include <algorithm>
 #include <mutex>
 
 #include "common.h"
@@ -136,7 +137,7 @@ int mst_sparse_fc_fwd(const mst_layer_t* L, const void* X_dev, float* Y_dev, int
     note_call(L, act, T);
     // (unbuilt views and no workspace to build them with: the dense product, same result within tolerance)
     if (use_dense_path(L, act, T) || !L->views_valid) return dense_products_fwd(L, X_dev, Y_dev, T, act, s);
-    const int rc = spmm(L->row, X_dev, Y_dev, T, L->nnz, act, s);
+    const int rc = spmm(L, L->row, X_dev, Y_dev, T, act, s);
     if (rc != MST_OK || !L->heavy_on) return rc;
     return heavy_fwd(L, X_dev, Y_dev, T, act, s);        // the rows the view leaves out (returns at once without any)
 }
@@ -148,7 +149,7 @@ int mst_sparse_fc_bwd_input(const mst_layer_t* L, const void* dY_dev, float* dX_
     hipStream_t s = (hipStream_t)stream;
     note_call(L, act, T);
     if (use_dense_path(L, act, T) || !L->views_valid) return dense_products_bwd_input(L, dY_dev, dX_dev, T, act, s);
-    return spmm(L->col, dY_dev, dX_dev, T, L->nnz, act, s);
+    return spmm(L, L->col, dY_dev, dX_dev, T, act, s);
 }
 
 int mst_sparse_fc_bwd_weight(const mst_layer_t* L, const void* dY_dev, const void* X_dev, float* dW_dev, int T,
@@ -163,7 +164,7 @@ int mst_sparse_fc_bwd_weight(const mst_layer_t* L, const void* dY_dev, const voi
     if (use_dense_weight_grad(L, act, T)) return dense_products_bwd_weight(L, dY_dev, X_dev, dW_dev, T, act, ws, s);
     const int rc = ensure_views(L, ws, s);
     if (rc != MST_OK) return rc;
-    return sddmm(L, dY_dev, X_dev, dW_dev, T, act, ws, s);
+    return sddmm(L, dY_dev, X_dev, dW_dev, T, act, ws.partial, ws.partial_floats, s);
 }
 
 size_t mst_static_scratch_bytes(void) { return STATIC_SCRATCH_BYTES; }
@@ -173,18 +174,21 @@ int mst_sparse_fc_bwd_weight_static(const mst_layer_t* L, const void* dY_dev, co
     if (!L || !dY_dev || !X_dev || !dW_dev || T < 1 || !act_ok(act)) return MST_ERR_ARG;
     if (!aligned16(dY_dev) || !aligned16(X_dev) || !aligned16(dW_dev)) return MST_ERR_ARG;
     if (!L->built || !L->views_valid) return MST_ERR_STATE;      // (it has no workspace to build unbuilt views with)
-    // partial sums: one plane of entry slots per tile of TT tokens; the plane's stride is that of
-    // the larger view because the view that drives the product is chosen on the device
-    const size_t slots = (size_t)std::max(L->row.cap_pairs, L->col.cap_pairs) * 8;
-    const size_t need = (size_t)cdiv(T, TT) * slots * sizeof(float);
+    // the documented limit: ceil(T / 128) planes of 8 floats per pair of four-row slices of 128 indices at the
+    // layer's capacity.  (The planes of the walk are other ones; a batch that needs more of them than the
+    // array holds is taken in ranges of tokens.)
+    auto plane = [&](int K, int R) {
+        const int64_t quads = cdiv(K, 128) * cdiv(R, 16) * 4;
+        return cdiv((L->cap + quads) / 2 + 1 + 16, 8) * 8 * 8;
+    };
+    const size_t need = (size_t)cdiv(T, 128) * (size_t)std::max(plane(L->I, L->O), plane(L->O, L->I)) * sizeof(float);
     if (need > STATIC_SCRATCH_BYTES) return MST_ERR_WORKSPACE;
     void* base = nullptr;
     const int rc = static_scratch(&base);
     if (rc != MST_OK) return rc;
-    Workspace ws{};
-    ws.partial = static_cast<float*>(base);      // every slot the second kernel reads is written by the first
-    ws.partial_floats = STATIC_SCRATCH_BYTES / sizeof(float);
-    return sddmm(L, dY_dev, X_dev, dW_dev, T, act, ws, (hipStream_t)stream);
+    // (every slot the second kernel reads is written by the first)
+    return sddmm(L, dY_dev, X_dev, dW_dev, T, act, static_cast<float*>(base), STATIC_SCRATCH_BYTES / sizeof(float),
+                 (hipStream_t)stream);
 }
 
 int mst_sparse_fc_bwd(const mst_layer_t* L, const void* dY_dev, const void* X_dev, float* dX_dev, float* dW_dev,
@@ -197,7 +201,7 @@ int mst_sparse_fc_bwd(const mst_layer_t* L, const void* dY_dev, const void* X_de
     if (ws_bytes < ws.total) return MST_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     note_call(L, act, T);
-    if (use_fused_backward(L, act, T) && bwd_fused_pays(L)) {
+    if (use_fused_backward(L, act, T)) {
         const int rcv = ensure_views(L, ws, s);
         if (rcv != MST_OK) return rcv;
         return bwd_fused(L, dY_dev, X_dev, dX_dev, dW_dev, T, act, ws, s);
@@ -248,8 +252,8 @@ int mst_layer_format_stats(const mst_layer_t* L, mst_format_stats* out, mst_stre
     out->nnz = L->nnz;
     out->heavy_rows = hv[0];
     out->heavy_entries = hv[1];
-    out->row_view_slots = (int64_t)pr * 8;
-    out->col_view_slots = (int64_t)pc * 8;
+    out->row_view_slots = (int64_t)pr * (2 * OCT);
+    out->col_view_slots = (int64_t)pc * (2 * OCT);
     out->row_view_efficiency = pr ? (double)(L->nnz - hv[1]) / (double)out->row_view_slots : 1.0;
     out->col_view_efficiency = pc ? (double)L->nnz / (double)out->col_view_slots : 1.0;
     return MST_OK;
@@ -367,7 +371,7 @@ int mst_sparse_fc_bwd_weight_update(mst_layer_t* L, const void* dY_dev, const vo
             rc = dense_products_bwd_weight(L, dY_dev, X_dev, dW_dev, T, act, ws, s);
         } else {
             rc = ensure_views(L, ws, s);
-            if (rc == MST_OK) rc = sddmm(L, dY_dev, X_dev, dW_dev, T, act, ws, s);
+            if (rc == MST_OK) rc = sddmm(L, dY_dev, X_dev, dW_dev, T, act, ws.partial, ws.partial_floats, s);
         }
         if (rc != MST_OK) return rc;
     }

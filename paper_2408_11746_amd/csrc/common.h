@@ -10,53 +10,58 @@
 namespace mst {
 
 // ---- tiling constants shared by the format builder and the product kernels ----
-// The contraction dimension of a view is cut into chunks of KC indices; one chunk of
-// the dense operand for TT tokens is what a workgroup stages in LDS at a time.
-constexpr int KC = 128;          // contraction indices per chunk
-constexpr int TT = 128;          // tokens per LDS tile
-constexpr int RB = 16;           // rows per row block: 4 lane groups x 4 quads
-constexpr int MAX_WG_BLOCKS = 32;
-constexpr int SPREAD_FLAG = 1 << 30;   // in rowmap / rowpos: the quad holds ONE row spread over its four lane groups   // most row blocks one workgroup may own
-constexpr int HEAVY_MAX = 64;   // rows a layer may keep out of its row view as a small dense matrix (heavy.hip)
+// The contraction dimension of a view is cut into equal chunks of at most KCMAX indices; one chunk
+// of the dense operand for WT tokens (160 KB at most: the whole LDS of a CU) is what a workgroup
+// stages at a time.
+constexpr int KCMAX = 640;       // contraction indices per chunk, at most
+constexpr int KSMAX = 128;       // ... and per sub-chunk, the unit in which the format builder counts
+constexpr int WT = 64;           // tokens per LDS tile
+constexpr int OCT = 8;           // rows per octet: one per lane group of eight lanes
+constexpr int OPB = 16;          // octets per row block: one per wavefront of a workgroup
+constexpr int RB = OCT * OPB;    // rows per row block
+constexpr int MAX_WG_BLOCKS = 8; // most row blocks one workgroup may own
+constexpr int SPREAD_FLAG = 1 << 30;   // in rowmap / rowpos: the octet holds ONE row spread over its eight lane groups
+constexpr int HEAVY_MAX = 64;    // rows a layer may keep out of its row view as a small dense matrix (heavy.hip)
 constexpr int PAIR_TAIL = 16;    // readable step pairs past the last one (a whole entry batch may be fetched there)
 
-// LDS tile layout: row k (one contraction index) holds TT tokens = 512 bytes as 32
-// 16-byte slots of four consecutive tokens; slot u of tokens 4u..4u+3 sits at byte
-// (u >> 4) * 256 + ((u & 15) ^ ((k >> 2) & 15)) * 16.  Lane s (0..15) of a lane group
-// owns tokens 4s..4s+3 and 64+4s..64+4s+3 and finds them at lds_off(k) ^ (s << 4) and
-// 256 bytes further.  The XOR spreads the transposing stores of the tile loader over all
-// banks while the 16 lanes of a group still read one contiguous 256 bytes.
-__host__ __device__ inline uint32_t lds_off(uint32_t k) {
-    return (k << 9) | (((k >> 2) & 15u) << 4);
-}
+// LDS tile layout: row k (one contraction index) holds WT tokens = 256 bytes as 16 slots of four
+// consecutive tokens; slot u of tokens 4u .. 4u+3 sits at byte (u ^ ((k >> 2) & 3)) * 16.  A 16-byte
+// LDS read is served in sets of four lane quads, {0, 3, 5, 6} and {1, 2, 4, 7} of every 32 lanes,
+// and is free of conflicts when the four quads of a set read four different 64-byte quarters of a
+// row: the swizzle therefore stays inside a quarter (with a swizzle over eight slots the walk
+// counted 3 conflict cycles per read), it spreads the transposing stores of the tile loader.
+__host__ __device__ inline uint32_t lds_off(uint32_t k) { return (k << 8) | (((k >> 2) & 3u) << 4); }
 
 // Sparse matrix S [R x K] as the product kernels walk it.  Rows are grouped in blocks of
-// RB = 16 consecutive rows.  Inside a block the rows are ranked by their total length
-// (longest first, lower index first on ties); the row of rank 4q + g belongs to quad q and
-// lane group g, so the four rows of a quad have similar lengths (little ELL padding even
-// when row lengths are very uneven).  rowmap[16b + rank] is that row.  For every
-// (chunk c of K, block b, quad q) the four rows' entries inside the chunk are stored side
-// by side, padded with zero-weight entries to the longest of the four and to an even
-// count (an ELL slice of height 4): step j of the quad holds one entry per lane group.
-// Two steps form a pair = uint4[4]: element g is {off_j, w_j, off_j+1, w_j+1} of lane
+// RB = 128 consecutive rows.  Inside a block the rows are ranked by their total length
+// (longest first, lower index first on ties); the row of rank 8o + g belongs to octet o and
+// lane group g, so the eight rows of an octet have similar lengths (little ELL padding even
+// when row lengths are very uneven).  rowmap[128b + rank] is that row.  For every
+// (chunk c of K, block b, octet o) the eight rows' entries inside the chunk are stored side
+// by side, padded with zero-weight entries to the longest of the eight and to an even
+// count (an ELL slice of height 8): step j of the octet holds one entry per lane group.
+// Two steps form a pair = uint4[8]: element g is {off_j, w_j, off_j+1, w_j+1} of lane
 // group g, off = lds_off(k - c*KC), w = fp32 bits.
-// A very long row can take a whole quad ("spread"): its entries are dealt to the four lane
-// groups in turn (entry j of a chunk: lane group j & 3, step j >> 2), the kernels add the
-// four lane groups' sums at the end.  The other three places of such a quad are given to
-// three EMPTY rows of the block (they own the output positions, which receive zero), so a
-// block spreads at most as many rows as it has triples of empty rows.  All four rowmap
-// entries of a spread quad and the rowpos entry of the spread row carry SPREAD_FLAG.
+// A very long row can take a whole octet ("spread"): its entries are dealt to the eight lane
+// groups in turn (entry j of a chunk: lane group j & 7, step j >> 3), the kernels add the
+// eight lane groups' sums at the end.  The other seven places of such an octet are given to
+// seven EMPTY rows of the block (they own the output positions, which receive zero), so a
+// block spreads at most as many rows as it has sevens of empty rows.  All eight rowmap
+// entries of a spread octet and the rowpos entry of the spread row carry SPREAD_FLAG.
 struct View {
     int R = 0, K = 0, nchunk = 0;
-    int NB = 0;            // row blocks: ceil(R / 16)
+    int KC = 0;            // indices per chunk: msub * KS
+    int KS = 0, msub = 0;  // indices per sub-chunk (a multiple of 4), sub-chunks per chunk
+    int NB = 0;            // row blocks: ceil(R / 128)
     int NBpad = 0;         // block stride of ptr: NB + MAX_WG_BLOCKS (the extra blocks stay empty)
-    int64_t nseg = 0;      // nchunk * NBpad * 4 quad segments
+    int64_t nseg = 0;      // nchunk * NBpad * 16 octet segments
     int64_t cap_pairs = 0; // pairs the arrays can hold (incl. tail)
-    int* ptr = nullptr;    // [nseg + 1] first pair of segment (c*NBpad + b)*4 + q
-    uint4* ent = nullptr;  // [cap_pairs * 4]
-    int* perm = nullptr;   // [cap_pairs * 8] canonical index of entry slot (pair*4 + g)*2 + half, -1 = padding
-    int* rowmap = nullptr; // [NBpad * 16] rank inside the block -> row (identity in the empty blocks)
-    int* rowpos = nullptr; // [NBpad * 16] row -> rank inside its block
+    int* ptr = nullptr;    // [nseg + 1] first pair of segment (c*NBpad + b)*16 + o
+    uint4* ent = nullptr;  // [cap_pairs * 8]
+    int* perm = nullptr;   // [cap_pairs * 16] canonical index of entry slot (pair*8 + g)*2 + half, -1 = padding
+    int* rowmap = nullptr; // [NBpad * 128] rank inside the block -> row (identity in the empty blocks)
+    int* rowpos = nullptr; // [NBpad * 128] row -> rank inside its block
+    int nsub() const { return nchunk * msub; }
 };
 
 // Hd row j = row heavy[1 + j] of W . M, from the canonical arrays, by one block (heavy rows, heavy.hip).
@@ -94,6 +99,11 @@ struct mst_layer {
     // (path choice at the batch size and type of the last product call) leaves them unbuilt; a
     // call that needs them and has a workspace builds them, one without runs the dense product.
     bool views_valid = false;
+    // mst_layer_sync_values refreshes the entries of a built view only if a product has walked it
+    // since it was built (recorded products included: recording is a call); the entries of the others
+    // are stale and take the values before their first walk.  Same for the dense rows beside the row view.
+    bool row_walked = false, col_walked = false;
+    bool row_stale = false, col_stale = false;
     int hint_T = 0;            // batch size and activation type of the last product call (0: none yet)
     int hint_act = 0;
     mst::View row;             // S = W   [O x I], used by fwd (and bwd_weight)
@@ -137,14 +147,14 @@ struct Workspace {
     int* cidx = nullptr;       // [N] canonical index of each active position
     uint8_t* sel = nullptr;    // [N] selection flags of the grow step
     uint8_t* psel = nullptr;   // [cap] selection flags of the prune step
-    int* segcnt = nullptr;     // active count per (chunk, row) of the view being built
-    int* qlen = nullptr;       // pairs per quad segment of the view being built
+    int* segcnt = nullptr;     // active count per (sub-chunk, row) of the view being built
+    int* qlen = nullptr;       // pairs per octet segment of the view being built
     int* rowcnt = nullptr;     // [O + 1]
     uint32_t* blk = nullptr;   // per-block tie counts: [blocks(N) + 1] of the growth selections, then [blocks(cap) + 1] of the prune selection
     uint64_t* sel_state = nullptr;   // [SEL_STATES][SEL_STATE_WORDS] radix-select state + histogram
     float* gemm = nullptr;     // [GEMM_WS_SPLITS * N] split-k partial outputs of the dense GEMM
     size_t gemm_floats = 0;
-    float* partial = nullptr;  // SDDMM partial sums [ntile][entry slots of the row view]
+    float* partial = nullptr;  // weight-gradient partial sums [token tile][entry slots of the larger view]
     size_t partial_floats = 0;
     size_t total = 0;
 };
@@ -157,7 +167,7 @@ constexpr int SEL_BINS = 1 << SEL_DIGIT_BITS;
 constexpr int SEL_STATE_WORDS = 8 + 4096 / 2;            // one selection: 8 control words + up to 4096 uint32 histogram bins
 constexpr int SEL_STATES = 3;                            // prune, gradient growth, random growth
 
-int64_t view_pair_capacity(int64_t cap, int64_t nchunk, int64_t R);
+View view_shape(int R, int K, int64_t cap);
 int fill_u32(void* dst, uint32_t value, int64_t n_words, hipStream_t s);
 
 // ---- internal entry points implemented across the .hip files ----
@@ -165,14 +175,15 @@ int build_views(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_
 int build_canonical(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_t s);
 int ensure_views(const mst_layer* L, const Workspace& ws, hipStream_t s);
 bool views_wanted(const mst_layer* L);
-int spmm(const View& v, const void* A, float* out, int T, int64_t nnz, mst_dtype act, hipStream_t s);
+int ensure_fresh(const mst_layer* L, bool row, bool col, hipStream_t s);
+// the products of the sparse path; see walk.hip
+int spmm(const mst_layer* L, const View& v, const void* A, float* out, int T, mst_dtype act, hipStream_t s);
 int spmm_force_shape(int tokens_per_workgroup, int quads_per_wavefront);
-int sddmm(const mst_layer* L, const void* dY, const void* X, float* dW, int T, mst_dtype act,
-          const Workspace& ws, hipStream_t s);
-// dX and dW from one walk of the col view; see bwd_fused.hip
+int sddmm(const mst_layer* L, const void* dY, const void* X, float* dW, int T, mst_dtype act, float* partial,
+          size_t partial_floats, hipStream_t s);
+// dX and dW from one walk of the col view
 int bwd_fused(const mst_layer* L, const void* dY, const void* X, float* dX, float* dW, int T, mst_dtype act,
               const Workspace& ws, hipStream_t s);
-bool bwd_fused_pays(const mst_layer* L);
 int bwd_fused_force_shape(int waves, int quads);
 // C[M x N] (fp32) = op(A) op(B) on the matrix cores; see gemm_mfma.hip
 enum GemmKind { GEMM_TN = 0, GEMM_NT = 1, GEMM_NN = 2 };

@@ -172,7 +172,7 @@ __global__ __launch_bounds__(256) void k_heavy_fill(const int* __restrict__ heav
 // their entries in total; their per-chunk counts are cleared, so that the view's ranking and
 // pointers see empty rows.  One block.
 __global__ __launch_bounds__(1024) void k_mark_heavy(const int* __restrict__ rowcnt, int O, int thr, int* __restrict__ segcnt,
-                                                     int nchunk, int Rpad, int* __restrict__ heavy) {
+                                                     int nsub, int Rpad, int* __restrict__ heavy) {
     __shared__ int wsum[16];
     __shared__ int entries_s;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -194,7 +194,7 @@ __global__ __launch_bounds__(1024) void k_mark_heavy(const int* __restrict__ row
         if (is && pos < HEAVY_MAX) {
             heavy[1 + pos] = r;
             atomicAdd(&entries_s, rowcnt[r]);
-            for (int c = 0; c < nchunk; ++c) segcnt[(size_t)c * Rpad + r] = 0;
+            for (int c = 0; c < nsub; ++c) segcnt[(size_t)c * Rpad + r] = 0;
         }
         base += total;
         __syncthreads();
@@ -223,7 +223,7 @@ int heavy_threshold(const mst_layer* L) {
 }
 
 int heavy_mark(const mst_layer* L, const Workspace& ws, int Rpad, hipStream_t s) {
-    k_mark_heavy<<<1, 1024, 0, s>>>(ws.rowcnt, L->O, heavy_threshold(L), ws.segcnt, L->row.nchunk, Rpad, L->heavy);
+    k_mark_heavy<<<1, 1024, 0, s>>>(ws.rowcnt, L->O, heavy_threshold(L), ws.segcnt, L->row.nsub(), Rpad, L->heavy);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }

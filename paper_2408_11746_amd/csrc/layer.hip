@@ -6,25 +6,36 @@
 //   row view  S = W    [O x I]  -> forward
 //   col view  S = W^T  [I x O]  -> input gradient
 // (the weight gradient walks whichever of the two is cheaper, see build_views).
-// A view cuts the contraction index into chunks of KC and stores, per (chunk, block of
-// 16 rows, quad), an ELL slice of four rows (see View in common.h).  perm[] maps an
+// A view cuts the contraction index into chunks and stores, per (chunk, block of 128 rows,
+// octet), an ELL slice of eight rows (see View in common.h).  perm[] maps an
 // entry slot back to its canonical position, so that values can be refreshed after an
 // optimiser step and weight gradients can be returned in canonical order.
+#include <algorithm>
+
 #include "common.h"
 
 namespace mst {
 
 thread_local int g_last_hip_error = 0;
 
-static int64_t nchunks(int K) { return cdiv(K, KC); }
-static int64_t nblocks(int R) { return cdiv(R, RB); }
-static int64_t nbpad(int R) { return nblocks(R) + MAX_WG_BLOCKS; }
-
-// A quad segment holds max(len of its four rows) steps rounded up to even, which is at
-// most (sum of the four lens) + 1; summed over all segments: steps <= nnz + #segments.
-int64_t view_pair_capacity(int64_t cap, int64_t nchunk, int64_t R) {
-    const int64_t nqs = nchunk * nblocks((int)R) * 4;
-    return cdiv((cap + nqs) / 2 + 1 + PAIR_TAIL, 8) * 8;
+// Chunks of equal size (a short last chunk would cost the same barriers for less work), each of
+// whole sub-chunks of KS indices.  An octet segment holds max(len of its eight rows) steps rounded up
+// to even: at most (sum of the eight lens) + 1, and at most the chunk's length.
+View view_shape(int R, int K, int64_t cap) {
+    View v;
+    v.R = R;
+    v.K = K;
+    const int64_t n = cdiv(K, KCMAX), per = cdiv(K, n);
+    v.msub = (int)cdiv(per, KSMAX);
+    v.KS = (int)(cdiv(cdiv(per, v.msub), 4) * 4);
+    v.KC = v.msub * v.KS;
+    v.nchunk = (int)cdiv(K, v.KC);
+    v.NB = (int)cdiv(R, RB);
+    v.NBpad = v.NB + MAX_WG_BLOCKS;
+    v.nseg = (int64_t)v.nchunk * v.NBpad * OPB;
+    const int64_t nos = (int64_t)v.nchunk * v.NB * OPB;
+    v.cap_pairs = cdiv(std::min((cap + nos) / 2 + 1, nos * (v.KC / 2)) + PAIR_TAIL, 8) * 8;
+    return v;
 }
 
 // Measured cross-overs (GPT-2 small / medium / large layer shapes).  With fp32 activations the
@@ -89,8 +100,7 @@ struct LayerCarve {
 static LayerCarve carve_layer(int O, int I, int64_t cap) {
     LayerCarve c{};
     const int64_t N = (int64_t)O * I;
-    const int64_t nseg_r = nchunks(I) * nbpad(O) * 4, nseg_c = nchunks(O) * nbpad(I) * 4;
-    const int64_t cp_r = view_pair_capacity(cap, nchunks(I), O), cp_c = view_pair_capacity(cap, nchunks(O), I);
+    const View r = view_shape(O, I, cap), k = view_shape(I, O, cap);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return o; };
     c.mask = take((size_t)N);
@@ -98,16 +108,16 @@ static LayerCarve carve_layer(int O, int I, int64_t cap) {
     c.flat = take((size_t)cap * 4);
     c.rowptr = take((size_t)(O + 1) * 4);
     c.Wd = take((size_t)N * 4);
-    c.rptr = take((size_t)(nseg_r + 1) * 4);
-    c.rent = take((size_t)cp_r * 64);
-    c.rperm = take((size_t)cp_r * 32);
-    c.rmap = take((size_t)nbpad(O) * RB * 4);
-    c.rpos = take((size_t)nbpad(O) * RB * 4);
-    c.cptr = take((size_t)(nseg_c + 1) * 4);
-    c.cent = take((size_t)cp_c * 64);
-    c.cperm = take((size_t)cp_c * 32);
-    c.cmap = take((size_t)nbpad(I) * RB * 4);
-    c.cpos = take((size_t)nbpad(I) * RB * 4);
+    c.rptr = take((size_t)(r.nseg + 1) * 4);
+    c.rent = take((size_t)r.cap_pairs * OCT * 16);
+    c.rperm = take((size_t)r.cap_pairs * OCT * 8);
+    c.rmap = take((size_t)r.NBpad * RB * 4);
+    c.rpos = take((size_t)r.NBpad * RB * 4);
+    c.cptr = take((size_t)(k.nseg + 1) * 4);
+    c.cent = take((size_t)k.cap_pairs * OCT * 16);
+    c.cperm = take((size_t)k.cap_pairs * OCT * 8);
+    c.cmap = take((size_t)k.NBpad * RB * 4);
+    c.cpos = take((size_t)k.NBpad * RB * 4);
     c.choice = take(16);
     c.heavy = take((size_t)(HEAVY_MAX + 2) * 4);
     c.Hd = take((size_t)HEAVY_MAX * I * 4);
@@ -126,10 +136,10 @@ static bool shape_ok(int O, int I, int64_t cap) {
 Workspace carve_workspace(void* base, int O, int I, int64_t cap, int T) {
     Workspace w{};
     const int64_t N = (int64_t)O * I;
-    // per-row-per-chunk counts of either view, rows padded to whole blocks
-    const int64_t cnt_r = nchunks(I) * nbpad(O) * RB, cnt_c = nchunks(O) * nbpad(I) * RB;
-    const int64_t nseg_r = nchunks(I) * nbpad(O) * 4, nseg_c = nchunks(O) * nbpad(I) * 4;
-    const int64_t ntile = cdiv(T > 0 ? T : 1, TT);
+    const View r = view_shape(O, I, cap), k = view_shape(I, O, cap);
+    // per-row-per-sub-chunk counts of either view, rows padded to whole blocks
+    const int64_t cnt_r = (int64_t)r.nsub() * r.NBpad * RB, cnt_c = (int64_t)k.nsub() * k.NBpad * RB;
+    const int64_t ntile = cdiv(T > 0 ? T : 1, WT);
     char* b = static_cast<char*>(base);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return b ? b + o : nullptr; };
@@ -139,14 +149,13 @@ Workspace carve_workspace(void* base, int O, int I, int64_t cap, int T) {
     w.sel = (uint8_t*)take((size_t)N);
     w.psel = (uint8_t*)take((size_t)(cap > 0 ? cap : 1));
     w.segcnt = (int*)take((size_t)(std::max(cnt_r, cnt_c) + 1) * 4);
-    w.qlen = (int*)take((size_t)(std::max(nseg_r, nseg_c) + 1) * 4);
+    w.qlen = (int*)take((size_t)(std::max(r.nseg, k.nseg) + 1) * 4);
     w.rowcnt = (int*)take((size_t)(O + 1) * 4);
     w.blk = (uint32_t*)take((size_t)(cdiv(N, SELECT_BLOCK) + cdiv(cap > 0 ? cap : 1, SELECT_BLOCK) + 4) * 4);
     w.sel_state = (uint64_t*)take((size_t)SEL_STATES * SEL_STATE_WORDS * 8);
     w.gemm_floats = (size_t)GEMM_WS_SPLITS * (size_t)N;
     w.gemm = (float*)take(w.gemm_floats * 4);
-    w.partial_floats = (size_t)ntile * 8 *
-                       (size_t)std::max(view_pair_capacity(cap, nchunks(I), O), view_pair_capacity(cap, nchunks(O), I));
+    w.partial_floats = (size_t)ntile * 2 * OCT * (size_t)std::max(r.cap_pairs, k.cap_pairs);
     w.partial = (float*)take(w.partial_floats * 4);
     w.total = off;
     return w;
@@ -154,40 +163,40 @@ Workspace carve_workspace(void* base, int O, int I, int64_t cap, int T) {
 
 // ------------------------------------------------------------------ kernels
 
-// one block per row r of the mask: active count per chunk of columns and per row; blocks past
+// one block per row r of the mask: active count per sub-chunk of KS columns and per row; blocks past
 // the last row (the padding rows of the view) write zero counts
-__global__ void k_count_row(const uint8_t* __restrict__ mask, int O, int I, int nchunk, int Rpad,
+__global__ void k_count_row(const uint8_t* __restrict__ mask, int O, int I, int KS, int nsub, int Rpad,
                             int* __restrict__ segcnt, int* __restrict__ rowcnt) {
-    extern __shared__ int cnt[];   // [nchunk]
+    extern __shared__ int cnt[];   // [nsub]
     const int r = blockIdx.x;
     if (r >= O) {
-        for (int c = threadIdx.x; c < nchunk; c += blockDim.x) segcnt[(size_t)c * Rpad + r] = 0;
+        for (int c = threadIdx.x; c < nsub; c += blockDim.x) segcnt[(size_t)c * Rpad + r] = 0;
         return;
     }
-    for (int c = threadIdx.x; c < nchunk; c += blockDim.x) cnt[c] = 0;
+    for (int c = threadIdx.x; c < nsub; c += blockDim.x) cnt[c] = 0;
     __syncthreads();
     const uint8_t* m = mask + (size_t)r * I;
     int total = 0;
     for (int i = threadIdx.x; i < I; i += blockDim.x) {
-        if (m[i]) { atomicAdd(&cnt[i / KC], 1); }
+        if (m[i]) { atomicAdd(&cnt[i / KS], 1); }
     }
     __syncthreads();
     if (segcnt)
-        for (int c = threadIdx.x; c < nchunk; c += blockDim.x) segcnt[(size_t)c * Rpad + r] = cnt[c];
+        for (int c = threadIdx.x; c < nsub; c += blockDim.x) segcnt[(size_t)c * Rpad + r] = cnt[c];
     if (threadIdx.x == 0) {
-        for (int c = 0; c < nchunk; ++c) total += cnt[c];
+        for (int c = 0; c < nsub; ++c) total += cnt[c];
         rowcnt[r] = total;
     }
 }
 
-// [KC rows x 64 columns] of the mask into LDS (rows beyond O and columns beyond I read as
-// zero); 256 threads, 32 bytes each.  Row stride 68 bytes: the 64 lanes of a wavefront read
+// [KSMAX rows x 64 columns] of the mask into LDS (rows beyond the sub-chunk or O and columns beyond I
+// read as zero); 256 threads, 32 bytes each.  Row stride 68 bytes: the 64 lanes of a wavefront read
 // one row's 64 bytes without bank conflicts.
 constexpr int MT_COLS = 64, MT_LD = 68;
-__device__ inline void load_mask_tile(const uint8_t* __restrict__ mask, int O, int I, int o0, int i0,
+__device__ inline void load_mask_tile(const uint8_t* __restrict__ mask, int O, int I, int o0, int nrows, int i0,
                                       uint8_t* __restrict__ m, int tid) {
     const int r = tid >> 1, half = tid & 1;
-    const int o = o0 + r, ib = i0 + 32 * half;
+    const int o = r < nrows ? o0 + r : O, ib = i0 + 32 * half;
     uint8_t* dst = m + r * MT_LD + 32 * half;
     const uint8_t* src = mask + (size_t)o * I + ib;
     if (o < O && ib + 32 <= I && ((reinterpret_cast<uintptr_t>(src) & 3) == 0)) {
@@ -199,15 +208,15 @@ __device__ inline void load_mask_tile(const uint8_t* __restrict__ mask, int O, i
     }
 }
 
-// block = (64 columns, chunk c of KC rows): active count of every column inside the chunk.
+// block = (64 columns, sub-chunk c of KS rows): active count of every column inside the sub-chunk.
 // Thread (column j, row group rg of 32 rows) counts its rows from the LDS tile.
-__global__ __launch_bounds__(256) void k_count_col(const uint8_t* __restrict__ mask, int O, int I, int Rpad,
+__global__ __launch_bounds__(256) void k_count_col(const uint8_t* __restrict__ mask, int O, int I, int KS, int Rpad,
                                                    int* __restrict__ segcnt) {
-    __shared__ __attribute__((aligned(16))) uint8_t m[KC * MT_LD];
+    __shared__ __attribute__((aligned(16))) uint8_t m[KSMAX * MT_LD];
     __shared__ int part[4][MT_COLS];
     const int tid = threadIdx.x, j = tid & 63, rg = tid >> 6;
     const int i0 = blockIdx.x * MT_COLS, c = blockIdx.y;
-    load_mask_tile(mask, O, I, c * KC, i0, m, tid);
+    load_mask_tile(mask, O, I, c * KS, KS, i0, m, tid);
     __syncthreads();
     int n = 0;
 #pragma unroll
@@ -218,74 +227,68 @@ __global__ __launch_bounds__(256) void k_count_col(const uint8_t* __restrict__ m
     if (rg == 0 && i0 + j < Rpad) segcnt[(size_t)c * Rpad + i0 + j] = part[0][j] + part[1][j] + part[2][j] + part[3][j];
 }
 
-// 16 lanes per row block (lane j = row j): order its 16 rows by total length over all
-// chunks, longest first, lower row first on ties (the empty padding blocks keep the
-// identity).  With h rows spread over whole quads (h <= #empty rows / 3) the quads cost about
-//   sum_{j<h} ceil(len_j / 4)  +  sum over the quads of the other rows of their longest row,
+// One workgroup per row block (thread j = row j): orders its 128 rows by total length over all
+// chunks, longest first, lower row first on ties (the empty padding blocks keep the identity), then
+// writes the pairs of every (chunk, octet) segment of the block.  With h rows spread over whole
+// octets (h <= #empty rows / 7) the octets cost about
+//   sum_{j<h} ceil(len_j / 8)  +  sum over the octets of the other rows of their longest row,
 // h is the value that minimises it (0 for every mask without empty rows).
-__global__ __launch_bounds__(256) void k_block_rank(const int* __restrict__ segcnt, int nchunk, int Rpad, int NBpad,
-                                                    int* __restrict__ rowmap, int* __restrict__ rowpos) {
-    __shared__ int sorted_s[16][RB];
-    __shared__ int h_s[16];
-    const int tid = threadIdx.x, j = tid & 15, lb = tid >> 4;
-    const int b = blockIdx.x * 16 + lb;
-    const bool live = b < NBpad;
+__global__ __launch_bounds__(RB) void k_block_rank(const int* __restrict__ segcnt, int msub, int nchunk, int Rpad, int NBpad,
+                                                   int* __restrict__ rowmap, int* __restrict__ rowpos, int* __restrict__ qlen) {
+    __shared__ int len_s[RB], sorted[RB], row_s[RB];
+    __shared__ int h_s, nzero_s;
+    const int j = threadIdx.x, b = blockIdx.x;
+    if (j == 0) { h_s = 0; nzero_s = 0; }
     int len = 0;
-    if (live)
-        for (int c = 0; c < nchunk; ++c) len += segcnt[(size_t)c * Rpad + b * RB + j];
+    for (int c = 0; c < nchunk * msub; ++c) len += segcnt[(size_t)c * Rpad + b * RB + j];
+    len_s[j] = len;
+    __syncthreads();
     int rank = 0;
-#pragma unroll
     for (int u = 0; u < RB; ++u) {
-        const int lu = __shfl(len, u, 16);
+        const int lu = len_s[u];
         rank += (lu > len) || (lu == len && u < j);
     }
-    sorted_s[lb][rank] = len;
+    sorted[rank] = len;
+    if (len == 0) atomicAdd(&nzero_s, 1);
     __syncthreads();
-    if (j == 0) {
-        const int* sorted = sorted_s[lb];
-        int nzero = 0;
-        for (int u = 0; u < RB; ++u) nzero += sorted[u] == 0;
-        int h = 0, best = sorted[0] + sorted[4] + sorted[8] + sorted[12];
-        for (int hh = 1; hh <= 4 && 3 * hh <= nzero; ++hh) {
-            int cost = 0;
-            for (int u = 0; u < hh; ++u) cost += (sorted[u] + 3) >> 2;
-            for (int p = hh; p < RB - 3 * hh; p += 4) cost += sorted[p];
-            if (cost < best) { best = cost; h = hh; }
+    if (j < 32) {                                    // candidate h = j on lane j of the first wavefront
+        int cost = 0x7FFFFFFF;
+        if (j <= OPB && 7 * j <= nzero_s) {
+            cost = 0;
+            for (int u = 0; u < j; ++u) cost += (sorted[u] + 7) >> 3;
+            for (int p = j; p < RB - 7 * j; p += OCT) cost += sorted[p];
         }
-        h_s[lb] = h;
+        int best = cost, at = j;
+        for (int d = 16; d >= 1; d >>= 1) {
+            const int oc = __shfl_xor(best, d, 32), oa = __shfl_xor(at, d, 32);
+            if (oc < best || (oc == best && oa < at)) { best = oc; at = oa; }
+        }
+        if (j == 0) h_s = at;
     }
     __syncthreads();
-    if (!live) return;
-    const int h = h_s[lb], p = rank;
+    const int h = h_s, p = rank;
     int slot, flag_row = 0;
-    if (p < h) { slot = 4 * p; flag_row = SPREAD_FLAG; }                 // spread row: lane group 0 of quad p
-    else if (p < RB - 3 * h) slot = 4 * h + (p - h);                     // ordinary rows fill the other quads
-    else { const int e = p - (RB - 3 * h); slot = 4 * (e / 3) + 1 + e % 3; }   // empty rows own the rest
-    const int flag_quad = (slot >> 2) < h ? SPREAD_FLAG : 0;
-    rowmap[b * RB + slot] = (b * RB + j) | flag_quad;
+    if (p < h) { slot = OCT * p; flag_row = SPREAD_FLAG; }               // spread row: lane group 0 of octet p
+    else if (p < RB - 7 * h) slot = OCT * h + (p - h);                   // ordinary rows fill the other octets
+    else { const int e = p - (RB - 7 * h); slot = OCT * (e / 7) + 1 + e % 7; }   // empty rows own the rest
+    const int flag_oct = slot / OCT < h ? SPREAD_FLAG : 0;
+    rowmap[b * RB + slot] = (b * RB + j) | flag_oct;
     rowpos[b * RB + j] = slot | flag_row;
-}
-
-// pairs of one quad segment: longest of its four rows (a spread row: a quarter of it),
-// rounded up to even, halved
-__device__ inline int quad_pairs(const int* __restrict__ segcnt, const int* __restrict__ rowmap, int Rpad, int NBpad,
-                                 int64_t sidx) {
-    const int q = (int)(sidx & 3);
-    const int64_t cb = sidx >> 2;
-    const int b = (int)(cb % NBpad);
-    const int64_t c = cb / NBpad;
-    const int* cnt = segcnt + c * Rpad;
-    const int* rm = rowmap + b * RB + 4 * q;          // the quad's four rows (one per lane group)
-    int L;
-    if (rm[0] & SPREAD_FLAG) L = (cnt[rm[0] & ~SPREAD_FLAG] + 3) >> 2;
-    else L = max(max(cnt[rm[0]], cnt[rm[1]]), max(cnt[rm[2]], cnt[rm[3]]));
-    return (L + 1) >> 1;
-}
-
-__global__ void k_quad_len(const int* __restrict__ segcnt, const int* __restrict__ rowmap, int Rpad, int NBpad,
-                           int64_t nseg, int* __restrict__ qlen) {
-    const int64_t sidx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;   // (c*NBpad + b)*4 + q
-    if (sidx < nseg) qlen[sidx] = quad_pairs(segcnt, rowmap, Rpad, NBpad, sidx);
+    row_s[slot] = j;
+    __syncthreads();
+    // pairs of a segment: longest of its eight rows (a spread row: an eighth of it), rounded up to even, halved
+    for (int idx = j; idx < nchunk * OPB; idx += RB) {
+        const int c = idx / OPB, o = idx % OPB;
+        const int* cnt = segcnt + (size_t)c * msub * Rpad + b * RB;
+        int L = 0;
+        for (int g = 0; g < (o < h ? 1 : OCT); ++g) {
+            int n = 0;
+            for (int u = 0; u < msub; ++u) n += cnt[(size_t)u * Rpad + row_s[o * OCT + g]];
+            L = max(L, n);
+        }
+        if (o < h) L = (L + 7) >> 3;
+        qlen[((size_t)c * NBpad + b) * OPB + o] = (L + 1) >> 1;
+    }
 }
 
 // exclusive scan by ONE block of 1024 threads: out[j] = sum_{j' < j} in[j'], out[n] = total (in == out
@@ -331,12 +334,11 @@ __global__ __launch_bounds__(1024) void k_scan_excl(const int* in, int* out, int
 }
 
 // One block does what follows the segment lengths of a view: (row view only) the canonical row
-// pointers from the per-row counts; the first pair of every quad segment; the view's cost
-// for the weight gradient -- a workgroup of the SDDMM owns about 16 consecutive row blocks and
-// waits at every chunk for its longest wavefront, so a view costs the sum over (chunk, group
-// of 16 blocks) of the most pairs of a block -- and, when the other view's cost is known
-// (`choice` not null), the view that drives the weight gradient: the one with the clearly
-// smaller cost, else the one with more rows.
+// pointers from the per-row counts; the first pair of every octet segment; the view's cost
+// for the weight gradient -- the wavefronts of a workgroup take one octet of a block each and wait at
+// every chunk for the longest, so a view costs the sum over (chunk, block) of the most pairs of an
+// octet -- and, when the other view's cost is known (`choice` not null), the view that drives the
+// weight gradient: the one with the clearly smaller cost, else the one with more rows.
 __global__ __launch_bounds__(1024) void k_view_ptr(const int* __restrict__ rowcnt, int* __restrict__ rowptr, int nrows,
                                                    const int* __restrict__ qlen, int NBpad, int NB, int nchunk,
                                                    int64_t nseg, int* __restrict__ ptr,
@@ -347,34 +349,15 @@ __global__ __launch_bounds__(1024) void k_view_ptr(const int* __restrict__ rowcn
     __shared__ unsigned long long cost_s;
     if (rowcnt) block_scan_excl(rowcnt, rowptr, nrows, wsum);
     block_scan_excl(qlen, ptr, nseg, wsum);
-    // cost: per (chunk, group of 16 blocks) the most pairs of a block, summed.  Every thread takes
-    // (chunk, block) items side by side and folds them into an LDS table of the groups.
-    constexpr int MAXG = 4096;
-    __shared__ int worst_s[MAXG];
-    const int ngroup = (NB + 15) / 16;
-    const int ngrp_all = nchunk * ngroup;
     if (threadIdx.x == 0) cost_s = 0ull;
-    for (int i = threadIdx.x; i < min(ngrp_all, MAXG); i += blockDim.x) worst_s[i] = 0;
     __syncthreads();                                  // ptr[] written by this block is visible to it
     unsigned long long mine = 0ull;
-    if (ngrp_all <= MAXG) {
-        for (int idx = threadIdx.x; idx < nchunk * NB; idx += blockDim.x) {
-            const int c = idx / NB, b = idx % NB;
-            const int64_t sidx = ((int64_t)c * NBpad + b) * 4;
-            atomicMax(&worst_s[c * ngroup + (b >> 4)], ptr[sidx + 4] - ptr[sidx]);
-        }
-        __syncthreads();
-        for (int i = threadIdx.x; i < ngrp_all; i += blockDim.x) mine += (unsigned long long)worst_s[i];
-    } else {
-        for (int idx = threadIdx.x; idx < ngrp_all; idx += blockDim.x) {
-            const int c = idx / ngroup, grp = idx % ngroup;
-            int worst = 0;
-            for (int b = grp * 16; b < min(NB, grp * 16 + 16); ++b) {
-                const int64_t sidx = ((int64_t)c * NBpad + b) * 4;
-                worst = max(worst, ptr[sidx + 4] - ptr[sidx]);
-            }
-            mine += (unsigned long long)worst;
-        }
+    for (int idx = threadIdx.x; idx < nchunk * NB; idx += blockDim.x) {
+        const int c = idx / NB, b = idx % NB;
+        const int* pp = ptr + ((int64_t)c * NBpad + b) * OPB;
+        int worst = 0;
+        for (int o = 0; o < OPB; ++o) worst = max(worst, pp[o + 1] - pp[o]);
+        mine += (unsigned long long)worst;
     }
     if (mine) atomicAdd(&cost_s, mine);
     __syncthreads();
@@ -393,85 +376,99 @@ __global__ __launch_bounds__(1024) void k_view_ptr(const int* __restrict__ rowcn
 
 // entry slot (as index into ent viewed as uint2[], and into perm) of step j of a row
 __device__ inline int64_t entry_slot(int pair0, int g, int j) {
-    return (((int64_t)pair0 + (j >> 1)) * 4 + g) * 2 + (j & 1);
+    return (((int64_t)pair0 + (j >> 1)) * OCT + g) * 2 + (j & 1);
 }
 
-// Slots of a row's lane group (of the whole quad for a spread row) past its `run` entries, up
-// to the quad's length: zero-weight padding (offset 0, perm -1).  The three empty rows that
-// share a spread quad own no slots.  `lanes` threads of the caller share the work.
+// entry j of a row inside a chunk: its lane group's step j, or dealt to the eight lane groups (spread row)
+__device__ inline int64_t row_slot(int pair0, int g, bool spread, int j) {
+    return spread ? entry_slot(pair0, j & 7, j >> 3) : entry_slot(pair0, g, j);
+}
+
+// Slots of a row's lane group (of the whole octet for a spread row) past its `run` entries, up
+// to the octet's length: zero-weight padding (offset 0, perm -1).  The seven empty rows that
+// share a spread octet own no slots.  `lanes` threads of the caller share the work.
 __device__ inline void pad_row_slots(uint2* __restrict__ ent, int* __restrict__ perm, int pair0, int npairs, int g,
                                      bool spread, int run, int lane, int lanes) {
-    const int total = spread ? 8 * npairs : 2 * npairs;
+    const int total = spread ? 16 * npairs : 2 * npairs;
     for (int j = run + lane; j < total; j += lanes) {
-        const int64_t e = spread ? entry_slot(pair0, j & 3, j >> 2) : entry_slot(pair0, g, j);
+        const int64_t e = row_slot(pair0, g, spread, j);
         ent[e] = make_uint2(0u, 0u);
         perm[e] = -1;
     }
 }
 
-// one wavefront per (row, part of its chunks) (incl. the padding rows of the last block, which
+// one wavefront per (row, part of its sub-chunks) (incl. the padding rows of the last block, which
 // only pad): ordered compaction of the row into canonical arrays and the row view.  A layer of
-// few long rows gives every row `nparts` wavefronts of `cpp` chunks each (one per row would leave
-// the 1280 rows of a 5120-wide layer on 320 workgroups); a part finds its first canonical index
-// from the per-chunk counts of the chunks before it (a heavy row, whose counts were cleared, from
-// the mask itself).
+// few long rows gives every row `nparts` wavefronts of `spp` sub-chunks each (one per row would leave
+// the 1280 rows of a 5120-wide layer on 320 workgroups); a part finds its first canonical index and
+// its place in its first chunk from the counts of the sub-chunks before it (a heavy row, whose counts
+// were cleared, from the mask itself).
 __global__ void k_fill_row(const uint8_t* __restrict__ mask, const float* __restrict__ W,
-                           int O, int I, int nchunk, int NBpad, int NB,
+                           int O, int I, int KS, int msub, int nsub, int NBpad, int NB,
                            const int* __restrict__ rowptr, const int* __restrict__ ptr,
                            const int* __restrict__ rowpos, const int* __restrict__ rowmap,
                            float* __restrict__ vals, int* __restrict__ flat, int* __restrict__ cidx,
                            uint2* __restrict__ ent, int* __restrict__ perm, const int* __restrict__ heavy,
-                           int nparts, int cpp, const int* __restrict__ segcnt, int Rpad) {
+                           int nparts, int spp, const int* __restrict__ segcnt, int Rpad) {
     const int lane = threadIdx.x & 63;
     const int unit = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const int r = unit / nparts, c0 = (unit % nparts) * cpp, c1 = min(nchunk, c0 + cpp);
+    const int r = unit / nparts, s0 = (unit % nparts) * spp, s1 = min(nsub, s0 + spp);
     if (r >= NB * RB) return;
     // a heavy row (HEAVY_MAX = 64 list entries, one per lane) fills the canonical arrays only
     const bool hv = heavy != nullptr && __ballot(lane < heavy[0] && heavy[1 + lane] == r) != 0ull;
-    const int b = r / RB, rp = rowpos[r], rank = rp & ~SPREAD_FLAG, g = rank & 3, q = rank >> 2;
+    const int b = r / RB, rp = rowpos[r], rank = rp & ~SPREAD_FLAG, g = rank % OCT, o = rank / OCT;
     const bool spread = (rp & SPREAD_FLAG) != 0;
-    // an empty row placed in a spread quad: the quad's slots belong to the spread row
-    const bool guest = !spread && (rowmap[b * RB + 4 * q] & SPREAD_FLAG) != 0;
+    // an empty row placed in a spread octet: the octet's slots belong to the spread row
+    const bool guest = !spread && (rowmap[b * RB + OCT * o] & SPREAD_FLAG) != 0;
     const bool real = r < O;
     const uint8_t* m = mask + (size_t)r * I;
     const float* w = W + (size_t)r * I;
-    int canon = real ? rowptr[r] : 0;
-    if (real && c0 > 0) {                             // entries of this row in the chunks before c0
-        int before = 0;
-        if (hv) {                                     // (a heavy row's per-chunk counts were cleared: count the mask)
-            for (int i = lane; i < c0 * KC; i += 64) before += m[i] != 0;
+    int canon = real ? rowptr[r] : 0, run = 0;        // run: entries of this row in the current chunk so far
+    if (real && s0 > 0) {                             // entries of this row in the sub-chunks before s0
+        const int cs = s0 / msub * msub;              // first sub-chunk of s0's chunk
+        int before = 0, here = 0;
+        if (hv) {                                     // (a heavy row's counts were cleared: count the mask)
+            for (int i = lane; i < s0 * KS && i < I; i += 64) before += m[i] != 0;
         } else {
-            for (int c = lane; c < c0; c += 64) before += segcnt[(size_t)c * Rpad + r];
+            for (int c = lane; c < s0; c += 64) {
+                const int n = segcnt[(size_t)c * Rpad + r];
+                before += n;
+                if (c >= cs) here += n;
+            }
         }
-        for (int d = 32; d >= 1; d >>= 1) before += __shfl_xor(before, d, 64);
+        for (int d = 32; d >= 1; d >>= 1) { before += __shfl_xor(before, d, 64); here += __shfl_xor(here, d, 64); }
         canon += before;
+        run = here;
     }
-    for (int c = c0; c < c1; ++c) {
-        const size_t seg = ((size_t)c * NBpad + b) * 4 + q;
+    const int KC = KS * msub;
+    for (int sc = s0; sc < s1; ++sc) {
+        const int c = sc / msub;
+        if (sc == c * msub) run = 0;
+        const size_t seg = ((size_t)c * NBpad + b) * OPB + o;
         const int pair0 = ptr[seg], npairs = ptr[seg + 1] - pair0;
-        int run = 0;
-        const int i1 = real ? min(I, (c + 1) * KC) : 0;
-        for (int i0 = c * KC; i0 < i1; i0 += 64) {
+        const int i1 = real ? min(I, (sc + 1) * KS) : 0;
+        for (int i0 = sc * KS; i0 < i1; i0 += 64) {
             const int i = i0 + lane;
             const bool on = i < i1 && m[i] != 0;
             const unsigned long long bal = __ballot(on);
             if (on) {
-                const int j = run + __popcll(bal & ((1ull << lane) - 1ull));
-                const int k = canon + j;
+                const int at = __popcll(bal & ((1ull << lane) - 1ull));
+                const int k = canon + at;
                 const float v = w[i];
                 vals[k] = v;
                 flat[k] = r * I + i;
                 cidx[(size_t)r * I + i] = k;
                 if (!hv) {
-                    const int64_t e = spread ? entry_slot(pair0, j & 3, j >> 2) : entry_slot(pair0, g, j);
+                    const int64_t e = row_slot(pair0, g, spread, run + at);
                     ent[e] = make_uint2(lds_off((uint32_t)(i - c * KC)), __float_as_uint(v));
                     perm[e] = k;
                 }
             }
             run += __popcll(bal);
+            canon += __popcll(bal);
         }
-        canon += run;
-        if (!guest) pad_row_slots(ent, perm, pair0, npairs, g, spread, hv ? 0 : run, lane, 64);
+        // the part that holds the chunk's last sub-chunk knows the row's whole count in it: it pads
+        if (!guest && sc == min(nsub, (c + 1) * msub) - 1) pad_row_slots(ent, perm, pair0, npairs, g, spread, hv ? 0 : run, lane, 64);
     }
 }
 
@@ -563,21 +560,22 @@ __global__ __launch_bounds__(256) void k_fill_canonical(const uint8_t* __restric
     if (sg == nseg - 1 && lane == 0) rowptr[O] = canon;
 }
 
-// block = (64 columns, chunk c of KC rows): rows i0 .. i0+63 of the col view, chunk c.  The
+// block = (64 columns, sub-chunk sc of KS rows): rows i0 .. i0+63 of the col view.  The
 // mask tile sits in LDS; thread (column j, row group rg of 32 rows) counts its rows, the
-// counts of the row groups before it give the position of its first entry in the column's
-// list, then it writes its entries in row order.
+// counts of the chunk's earlier sub-chunks and of the row groups before it give the position of its
+// first entry in the column's list, then it writes its entries in row order.
 __global__ __launch_bounds__(256) void k_fill_col(const uint8_t* __restrict__ mask, const float* __restrict__ W,
-                                                  int O, int I, int NBpad, int NB, const int* __restrict__ ptr,
+                                                  int O, int I, int KS, int msub, int nsub, int NBpad, int NB, int Rpad,
+                                                  const int* __restrict__ segcnt, const int* __restrict__ ptr,
                                                   const int* __restrict__ rowpos, const int* __restrict__ rowmap,
                                                   const int* __restrict__ cidx,
                                                   uint2* __restrict__ ent, int* __restrict__ perm) {
-    __shared__ __attribute__((aligned(16))) uint8_t m[KC * MT_LD];
+    __shared__ __attribute__((aligned(16))) uint8_t m[KSMAX * MT_LD];
     __shared__ int part[4][MT_COLS];
     const int tid = threadIdx.x, j = tid & 63, rg = tid >> 6;
-    const int i0 = blockIdx.x * MT_COLS, c = blockIdx.y, i = i0 + j;
-    const int o0 = c * KC;
-    load_mask_tile(mask, O, I, o0, i0, m, tid);
+    const int i0 = blockIdx.x * MT_COLS, sc = blockIdx.y, c = sc / msub, i = i0 + j;
+    const int o0 = sc * KS, oc0 = c * msub * KS;
+    load_mask_tile(mask, O, I, o0, KS, i0, m, tid);
     __syncthreads();
     int n = 0;
 #pragma unroll
@@ -586,30 +584,32 @@ __global__ __launch_bounds__(256) void k_fill_col(const uint8_t* __restrict__ ma
     __syncthreads();
     if (i >= NB * RB) return;                         // (columns past the matrix only pad)
     int jj = 0;
+    for (int u = c * msub; u < sc; ++u) jj += segcnt[(size_t)u * Rpad + i];
     for (int r = 0; r < rg; ++r) jj += part[r][j];
-    const int b = i / RB, rp = rowpos[i], rank = rp & ~SPREAD_FLAG, g = rank & 3, q = rank >> 2;
+    const int b = i / RB, rp = rowpos[i], rank = rp & ~SPREAD_FLAG, g = rank % OCT, o = rank / OCT;
     const bool spread = (rp & SPREAD_FLAG) != 0;
-    const bool guest = !spread && (rowmap[b * RB + 4 * q] & SPREAD_FLAG) != 0;
-    const size_t seg = ((size_t)c * NBpad + b) * 4 + q;
+    const bool guest = !spread && (rowmap[b * RB + OCT * o] & SPREAD_FLAG) != 0;
+    const size_t seg = ((size_t)c * NBpad + b) * OPB + o;
     const int pair0 = ptr[seg], npairs = ptr[seg + 1] - pair0;
     if (n > 0) {
         for (int k = 0; k < 32; ++k) {
             const int ol = 32 * rg + k;
             if (!m[ol * MT_LD + j]) continue;
             const size_t f = (size_t)(o0 + ol) * I + i;
-            const int64_t e = spread ? entry_slot(pair0, jj & 3, jj >> 2) : entry_slot(pair0, g, jj);
-            ent[e] = make_uint2(lds_off((uint32_t)ol), __float_as_uint(W[f]));
+            const int64_t e = row_slot(pair0, g, spread, jj);
+            ent[e] = make_uint2(lds_off((uint32_t)(o0 + ol - oc0)), __float_as_uint(W[f]));
             perm[e] = cidx[f];
             ++jj;
         }
     }
-    // the thread of the last row group knows the column's whole count in this chunk: it pads
-    if (rg == 3 && !guest) pad_row_slots(ent, perm, pair0, npairs, g, spread, jj, 0, 1);
+    // the last row group of the chunk's last sub-chunk knows the column's whole count in the chunk: it pads
+    if (rg == 3 && !guest && sc == min(nsub, (c + 1) * msub) - 1) pad_row_slots(ent, perm, pair0, npairs, g, spread, jj, 0, 1);
 }
 
-// Both views in one launch: the first `row_blocks` blocks refresh the row view's entries,
-// the next `col_blocks` the col view's, the last HEAVY_MAX the dense matrix of the heavy rows.
-__global__ void k_sync_views(const float* __restrict__ vals, unsigned row_blocks, unsigned col_blocks,
+// The entries of one or both views in one launch: the first `row_blocks` blocks refresh the row
+// view's, the next `col_blocks` the col view's, then (with row blocks) HEAVY_MAX blocks the dense
+// matrix of the heavy rows.  A thread takes four slots: one 16-byte read of their canonical indices.
+__global__ __launch_bounds__(256) void k_sync_views(const float* __restrict__ vals, unsigned row_blocks, unsigned col_blocks,
                              const int* __restrict__ ptr_r, int64_t nseg_r, const int* __restrict__ perm_r,
                              uint2* __restrict__ ent_r,
                              const int* __restrict__ ptr_c, int64_t nseg_c, const int* __restrict__ perm_c,
@@ -620,14 +620,18 @@ __global__ void k_sync_views(const float* __restrict__ vals, unsigned row_blocks
         return;
     }
     const bool col = blockIdx.x >= row_blocks;
-    const int* __restrict__ ptr = col ? ptr_c : ptr_r;
     const int* __restrict__ perm = col ? perm_c : perm_r;
     uint2* __restrict__ ent = col ? ent_c : ent_r;
-    const int64_t nseg = col ? nseg_c : nseg_r;
-    const int64_t e = (int64_t)(blockIdx.x - (col ? row_blocks : 0u)) * blockDim.x + threadIdx.x;
-    if (e >= (int64_t)ptr[nseg] * 8) return;
-    const int p = perm[e];
-    if (p >= 0) ent[e].y = __float_as_uint(vals[p]);
+    const int64_t n4 = (int64_t)(col ? ptr_c[nseg_c] : ptr_r[nseg_r]) * (2 * OCT / 4);
+    const int64_t stride = (int64_t)(col ? col_blocks : row_blocks) * 256;
+    for (int64_t e = (int64_t)(blockIdx.x - (col ? row_blocks : 0u)) * 256 + threadIdx.x; e < n4; e += stride) {
+        const int4 p = reinterpret_cast<const int4*>(perm)[e];
+        uint2* d = ent + 4 * e;
+        if (p.x >= 0) d[0].y = __float_as_uint(vals[p.x]);
+        if (p.y >= 0) d[1].y = __float_as_uint(vals[p.y]);
+        if (p.z >= 0) d[2].y = __float_as_uint(vals[p.z]);
+        if (p.w >= 0) d[3].y = __float_as_uint(vals[p.w]);
+    }
 }
 
 __global__ void k_scatter_dense(const float* __restrict__ vals, const int* __restrict__ flat,
@@ -663,29 +667,27 @@ int fill_u32(void* dst, uint32_t value, int64_t n_words, hipStream_t s) {
     return MST_OK;
 }
 
-// One view: count per (row, chunk) -> ranking of every block's rows -> pointers of the quad
-// segments (with the view's cost for the weight gradient and, for the second view, the choice
-// of the driving view) -> ordered compaction.  Five launches; nothing is cleared beforehand:
+// One view: count per (row, sub-chunk) -> ranking of every block's rows with the segments' lengths ->
+// pointers of the octet segments (with the view's cost for the weight gradient and, for the second
+// view, the choice of the driving view) -> ordered compaction.  Four launches; nothing is cleared beforehand:
 // the count kernels write the padding rows' zero counts and the fill kernels their own padding.
 static int build_one_view(View& v, bool row_view, const mst_layer* L, const float* Wsrc,
                           const Workspace& ws, unsigned long long* cost, hipStream_t s) {
     const int O = L->O, I = L->I;
-    const int Rpad = v.NBpad * RB;
+    const int Rpad = v.NBpad * RB, nsub = v.nsub();
     if (row_view) {
-        k_count_row<<<Rpad, 256, (size_t)v.nchunk * 4, s>>>(L->mask, O, I, v.nchunk, Rpad, ws.segcnt, ws.rowcnt);
+        k_count_row<<<Rpad, 256, (size_t)nsub * 4, s>>>(L->mask, O, I, v.KS, nsub, Rpad, ws.segcnt, ws.rowcnt);
         if (L->heavy_on) {
             MST_LAUNCH_CHECK();
             const int rc = heavy_mark(L, ws, Rpad, s);  // heavy rows leave the view
             if (rc != MST_OK) return rc;
         }
     } else {
-        dim3 gcnt((unsigned)cdiv(Rpad, 64), (unsigned)v.nchunk);
-        k_count_col<<<gcnt, 256, 0, s>>>(L->mask, O, I, Rpad, ws.segcnt);
+        dim3 gcnt((unsigned)cdiv(Rpad, 64), (unsigned)nsub);
+        k_count_col<<<gcnt, 256, 0, s>>>(L->mask, O, I, v.KS, Rpad, ws.segcnt);
     }
     MST_LAUNCH_CHECK();
-    k_block_rank<<<(unsigned)cdiv(v.NBpad, 16), 256, 0, s>>>(ws.segcnt, v.nchunk, Rpad, v.NBpad, v.rowmap, v.rowpos);
-    MST_LAUNCH_CHECK();
-    k_quad_len<<<(unsigned)cdiv(v.nseg, 256), 256, 0, s>>>(ws.segcnt, v.rowmap, Rpad, v.NBpad, v.nseg, ws.qlen);
+    k_block_rank<<<(unsigned)v.NBpad, RB, 0, s>>>(ws.segcnt, v.msub, v.nchunk, Rpad, v.NBpad, v.rowmap, v.rowpos, ws.qlen);
     MST_LAUNCH_CHECK();
     k_view_ptr<<<1, 1024, 0, s>>>(row_view ? ws.rowcnt : nullptr, L->rowptr, O, ws.qlen, v.NBpad, v.NB, v.nchunk, v.nseg,
                                   v.ptr, cost + (row_view ? 0 : 1), cost, L->I > L->O ? 1 : 0,
@@ -693,20 +695,20 @@ static int build_one_view(View& v, bool row_view, const mst_layer* L, const floa
     MST_LAUNCH_CHECK();
     if (row_view) {
         const int nrows = v.NB * RB;
-        const int nparts = std::max(1, std::min(v.nchunk, 8192 / nrows));
-        const int cpp = (int)cdiv(v.nchunk, nparts);
+        const int nparts = std::max(1, std::min(nsub, 8192 / nrows));
+        const int spp = (int)cdiv(nsub, nparts);
         k_fill_row<<<(unsigned)cdiv((int64_t)nrows * nparts, 4), 256, 0, s>>>(
-            L->mask, Wsrc, O, I, v.nchunk, v.NBpad, v.NB, L->rowptr, v.ptr, v.rowpos, v.rowmap, L->vals, L->flat, ws.cidx,
-            reinterpret_cast<uint2*>(v.ent), v.perm, L->heavy_on ? L->heavy : nullptr, nparts, cpp, ws.segcnt, Rpad);
+            L->mask, Wsrc, O, I, v.KS, v.msub, nsub, v.NBpad, v.NB, L->rowptr, v.ptr, v.rowpos, v.rowmap, L->vals, L->flat,
+            ws.cidx, reinterpret_cast<uint2*>(v.ent), v.perm, L->heavy_on ? L->heavy : nullptr, nparts, spp, ws.segcnt, Rpad);
         if (L->heavy_on) {
             MST_LAUNCH_CHECK();
             const int rc = heavy_fill(L, s);
             if (rc != MST_OK) return rc;
         }
     } else {
-        dim3 gcol((unsigned)cdiv(v.NB * RB, 64), (unsigned)v.nchunk);
-        k_fill_col<<<gcol, 256, 0, s>>>(L->mask, Wsrc, O, I, v.NBpad, v.NB, v.ptr, v.rowpos, v.rowmap, ws.cidx,
-                                        reinterpret_cast<uint2*>(v.ent), v.perm);
+        dim3 gcol((unsigned)cdiv(v.NB * RB, 64), (unsigned)nsub);
+        k_fill_col<<<gcol, 256, 0, s>>>(L->mask, Wsrc, O, I, v.KS, v.msub, nsub, v.NBpad, v.NB, Rpad, ws.segcnt, v.ptr, v.rowpos,
+                                        v.rowmap, ws.cidx, reinterpret_cast<uint2*>(v.ent), v.perm);
     }
     MST_LAUNCH_CHECK();
     return MST_OK;
@@ -724,6 +726,7 @@ int build_views(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_
     rc = build_one_view(L->col, false, L, Wsrc, ws, cost, s);
     if (rc != MST_OK) return rc;
     L->views_valid = true;
+    L->row_walked = L->col_walked = L->row_stale = L->col_stale = false;
     if (!keep_dense_copy) L->Wd_valid = L->Wd_zeros = false;
     return MST_OK;
 }
@@ -752,6 +755,30 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
         MST_LAUNCH_CHECK();
     }
     L->Wd_valid = L->Wd_zeros = true;
+    return MST_OK;
+}
+
+// new values into the entries of the row view (and the dense rows beside it) and / or of the col view
+static int refresh_views(const mst_layer* L, bool row, bool col, hipStream_t s) {
+    if (L->nnz == 0 || (!row && !col)) return MST_OK;
+    const View &r = L->row, &c = L->col;
+    // about 1.5 slots per entry, four slots per thread; the kernel strides over whatever there is
+    const unsigned nb = (unsigned)std::min<int64_t>(cdiv(L->nnz * 3 / 2 + 1, 1024), 4096);
+    const unsigned rb = row ? nb : 0u, cb = col ? nb : 0u;
+    k_sync_views<<<rb + cb + (row && L->heavy_on ? HEAVY_MAX : 0), 256, 0, s>>>(
+        L->vals, rb, cb, r.ptr, r.nseg, r.perm, reinterpret_cast<uint2*>(r.ent), c.ptr, c.nseg, c.perm,
+        reinterpret_cast<uint2*>(c.ent), L->heavy, L->rowptr, L->flat, L->I, L->Hd);
+    MST_LAUNCH_CHECK();
+    return MST_OK;
+}
+
+// A product is about to walk these (built) views: entries that missed a change of the values take it now.
+int ensure_fresh(const mst_layer* Lc, bool row, bool col, hipStream_t s) {
+    mst_layer* L = const_cast<mst_layer*>(Lc);       // caches of vals[], not layer state
+    const int rc = refresh_views(L, row && L->row_stale, col && L->col_stale, s);
+    if (rc != MST_OK) return rc;
+    if (row) { L->row_walked = true; L->row_stale = false; }
+    if (col) { L->col_walked = true; L->col_stale = false; }
     return MST_OK;
 }
 
@@ -813,9 +840,7 @@ int mst_layer_create(mst_layer_t** out, int O, int I, int64_t nnz_capacity, void
     L->heavy = (int*)(b + c.heavy);
     L->Hd = (float*)(b + c.Hd);
     auto init_view = [&](View& v, int R, int K, size_t optr, size_t oent, size_t operm, size_t omap, size_t opos) {
-        v.R = R; v.K = K; v.nchunk = (int)nchunks(K); v.NB = (int)nblocks(R); v.NBpad = (int)nbpad(R);
-        v.nseg = (int64_t)v.nchunk * v.NBpad * 4;
-        v.cap_pairs = view_pair_capacity(nnz_capacity, v.nchunk, R);
+        v = view_shape(R, K, nnz_capacity);
         v.ptr = (int*)(b + optr); v.ent = (uint4*)(b + oent); v.perm = (int*)(b + operm);
         v.rowmap = (int*)(b + omap); v.rowpos = (int*)(b + opos);
     };
@@ -838,7 +863,7 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
     if (ws_bytes < ws.total) return MST_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     // learn the active count first so that nothing is written when it does not fit
-    k_count_row<<<L->O, 256, (size_t)L->row.nchunk * 4, s>>>(M_dev, L->O, L->I, L->row.nchunk, 0, nullptr, ws.rowcnt);
+    k_count_row<<<L->O, 256, (size_t)L->row.nsub() * 4, s>>>(M_dev, L->O, L->I, L->row.KS, L->row.nsub(), 0, nullptr, ws.rowcnt);
     MST_LAUNCH_CHECK();
     int rcs = scan_excl_i32(ws.rowcnt, L->rowptr, L->O, s);          // rebuilt below anyway
     if (rcs != MST_OK) return rcs;
@@ -908,15 +933,9 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
         L->Wd_valid = false;
     }
     if (L->nnz == 0 || !L->views_valid) return MST_OK;     // unbuilt views take the values when they are built
-    // every real entry slot lies below 4 * (nnz + #quad segments); the kernel stops at ptr[nseg] * 8
-    const View &r = L->row, &c = L->col;
-    const unsigned rb = (unsigned)cdiv(4 * (L->nnz + (int64_t)r.nchunk * r.NB * 4), 256);
-    const unsigned cb = (unsigned)cdiv(4 * (L->nnz + (int64_t)c.nchunk * c.NB * 4), 256);
-    k_sync_views<<<rb + cb + (L->heavy_on ? HEAVY_MAX : 0), 256, 0, s>>>(L->vals, rb, cb, r.ptr, r.nseg, r.perm, reinterpret_cast<uint2*>(r.ent),
-                                                     c.ptr, c.nseg, c.perm, reinterpret_cast<uint2*>(c.ent), L->heavy,
-                                                     L->rowptr, L->flat, L->I, L->Hd);
-    MST_LAUNCH_CHECK();
-    return MST_OK;
+    L->row_stale |= !L->row_walked;
+    L->col_stale |= !L->col_walked;
+    return refresh_views(L, L->row_walked, L->col_walked, s);
 }
 
 int mst_layer_indices(const mst_layer_t* L, int32_t* flat_dev, mst_stream_t stream) {

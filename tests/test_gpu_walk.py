@@ -1,0 +1,125 @@
+"""The walk kernels at the edges of their tiles: one index more or less than a chunk of 640, a block of
+128 rows, a tile of 64 tokens, a sub-chunk; rows of an odd number of bfloat16; octets without
+entries between others; rows spread over an octet; chunks split over workgroups; token ranges and
+the slot kernel of the call without a workspace.  Against the oracle (App. Eq. (1) and its
+gradients)."""
+import numpy as np
+import pytest
+
+import paper_2408_11746_amd as mst
+import synth
+from oracle import products as opr
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from gpu_util import Rig, TOL, DEV, dev, rel_err  # noqa: E402
+
+SPMM = [(0, 0), (128, 2), (128, 3), (128, 4), (64, 4), (64, 6), (64, 8)]     # 1 .. 6 row blocks per workgroup
+BOTH = [(16, 1), (16, 2), (8, 4), (8, 5)]
+
+
+def _check(W, M, X, dY, act=mst.MST_F32, Xd=None, dYd=None):
+    T = X.shape[0]
+    rig = Rig(W, M, T, cap=max(1, int(M.sum())))
+    rig.layer.set_path(mst.MST_PATH_SPARSE)
+    Xd, dYd = (dev(X), dev(dY)) if Xd is None else (Xd, dYd)
+    nnz = rig.layer.nnz
+    Yr, dXr, dWr = opr.fc_fwd(X, W, M), opr.fc_bwd_input(dY, W, M), opr.fc_bwd_weight(dY, X, M)
+    new = lambda *shape: torch.full(shape, float("nan"), dtype=torch.float32, device=DEV)  # noqa: E731
+    ys, dxs, dws = [], [], []
+    try:
+        for shape in SPMM:
+            mst.mst_spmm_force_shape(*shape)
+            Y, dX = new(T, rig.O), new(T, rig.I)
+            mst.mst_sparse_fc_fwd(rig.layer, Xd, Y, T, act)
+            mst.mst_sparse_fc_bwd_input(rig.layer, dYd, dX, T, act)
+            ys.append(Y.cpu().numpy())
+            dxs.append(dX.cpu().numpy())
+        for shape in [(0, 0)] + BOTH:
+            mst.mst_bwd_force_shape(*shape)
+            dX, dW = new(T, rig.I), new(max(nnz, 1))
+            mst.mst_sparse_fc_bwd(rig.layer, dYd, Xd, dX, dW, T, rig.ws, act)
+            assert rel_err(dX.cpu().numpy(), dXr) <= TOL, shape
+            if shape != (0, 0):
+                dxs.append(dX.cpu().numpy())
+            dws.append(dW.cpu().numpy()[:nnz])
+    finally:
+        mst.mst_spmm_force_shape(0, 0)
+        mst.mst_bwd_force_shape(0, 0)
+    dW = new(max(nnz, 1))
+    mst.mst_sparse_fc_bwd_weight(rig.layer, dYd, Xd, dW, T, rig.ws, act)
+    dW = dW.cpu().numpy()[:nnz]
+    assert rel_err(ys[0], Yr) <= TOL and rel_err(dxs[0], dXr) <= TOL
+    if nnz:
+        assert rel_err(dws[0], dWr) <= TOL and rel_err(dW, dWr) <= TOL
+    for group in (ys, dxs, dws):
+        for other in group[1:]:
+            np.testing.assert_array_equal(other, group[0])
+    return rig, Xd, dYd, dW
+
+
+@pytest.mark.parametrize("O,I", [(127, 639), (128, 640), (129, 641), (1, 1281), (1283, 3), (260, 1279), (769, 515)])
+@pytest.mark.parametrize("T", [1, 63, 64, 65, 193])
+def test_edges_of_chunks_blocks_and_token_tiles(O, I, T):
+    print("case", O, I, T, flush=True)
+    W, M = synth.make_layer(900 + O, 1, I, O, 0.06)
+    X, dY = synth.make_activations(900 + O, 1, T, I, O)
+    _check(W, M, X, dY)
+
+
+@pytest.mark.parametrize("O,I,T", [(131, 129, 70), (130, 257, 65), (257, 642, 33)])
+def test_bfloat16_rows_of_odd_and_even_length(O, I, T):
+    print("case", O, I, T, flush=True)
+    W, M = synth.make_layer(950 + O, 1, I, O, 0.08)
+    X, dY, xb, yb = synth.make_activations(950 + O, 1, T, I, O, "bf16")
+    _check(W, M, X, dY, mst.MST_BF16, dev(xb.view(np.int16)), dev(yb.view(np.int16)))
+
+
+@pytest.mark.parametrize("O,I,T", [(400, 700, 129), (1030, 1300, 66)])
+def test_empty_octets_and_spread_rows(O, I, T):
+    """Blocks with a few full rows among empty ones (spread over whole octets), blocks with nothing, and
+    columns that leave whole chunks of the other view empty."""
+    print("case", O, I, T, flush=True)
+    rng = np.random.default_rng(O)
+    M = (rng.random((O, I)) < 0.03).astype(np.uint8)
+    M[rng.random(O) < 0.7] = 0
+    M[128:256] = 0
+    M[rng.random(O) < 0.04] = 1
+    M[:, I // 3: I // 3 + 200] = 0
+    W = (synth.normal(O, 5, (O, I), 0.02) * M).astype(np.float32)
+    X, dY = synth.make_activations(960 + O, 1, T, I, O)
+    _check(W, M, X, dY)
+
+
+def test_weight_gradient_without_a_workspace_in_token_ranges_and_by_slots():
+    """More token tiles than the library's array has planes for (taken in ranges), and a layer whose
+    capacity leaves not one plane (taken slot by slot): the bits of the call with a workspace."""
+    for O, I, T, cap in ((768, 1536, 1100, 220000), (4112, 4112, 40, 2300000)):
+        print("case", O, I, T, cap, flush=True)
+        W, M = synth.make_layer(970 + O, 1, I, O, 0.02 if O < 4000 else 0.002)
+        X, dY = synth.make_activations(970 + O, 1, T, I, O)
+        rig = Rig(W, M, T, cap=cap)
+        rig.layer.set_path(mst.MST_PATH_SPARSE)
+        want = rig.bwd_weight(dY, X)
+        got = torch.full((rig.layer.nnz,), float("nan"), dtype=torch.float32, device=DEV)
+        mst.mst_sparse_fc_bwd_weight_static(rig.layer, dev(dY), dev(X), got, T)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy(), want)
+        assert rel_err(want, opr.fc_bwd_weight(dY, X, M)) <= TOL
+
+
+def test_values_reach_views_that_no_product_has_walked_yet():
+    O, I, T = 300, 500, 70
+    W, M = synth.make_layer(980, 1, I, O, 0.05)
+    X, dY = synth.make_activations(980, 1, T, I, O)
+    rig = Rig(W, M, T)
+    L = rig.layer
+    L.set_path(mst.MST_PATH_SPARSE)
+    L.values().mul_(2.0)
+    L.sync_values()                                   # before any walk
+    assert rel_err(rig.fwd(X), opr.fc_fwd(X, 2 * W, M)) <= TOL
+    L.values().mul_(2.0)
+    L.sync_values()                                   # the row view has been walked, the col view has not
+    assert rel_err(rig.fwd(X), opr.fc_fwd(X, 4 * W, M)) <= TOL
+    assert rel_err(rig.bwd_input(dY), opr.fc_bwd_input(dY, 4 * W, M)) <= TOL
