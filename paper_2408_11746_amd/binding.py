@@ -312,7 +312,7 @@ def mst_heavy_rows(on: int = 1):
 
 
 def mst_gemm_force_fp32_mfma(on):
-    """False / 0: automatic; True / 1: plain fp32 MFMA kernel; 128 or 256: split kernel with that tile."""
+    """False / 0: automatic; True / 1: full-precision kernel; 128 or 256: split kernel with that tile."""
     _check("mst_gemm_force_fp32_mfma", lib().mst_gemm_force_fp32_mfma(int(on)))
 
 

@@ -131,6 +131,18 @@ extern thread_local int g_last_hip_error;
 
 #define MST_LAUNCH_CHECK() MST_HIP(hipGetLastError())
 
+// More than 64 KB of LDS has to be asked for, once per kernel and device (`done`: a bit per device; two
+// threads that meet here repeat the call).
+inline int allow_lds(const void* kernel, int bytes, uint64_t& done) {
+    int dev = 0;
+    MST_HIP(hipGetDevice(&dev));
+    const uint64_t bit = 1ull << (dev & 63);
+    if (__atomic_load_n(&done, __ATOMIC_RELAXED) & bit) return MST_OK;
+    MST_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+    __atomic_fetch_or(&done, bit, __ATOMIC_RELAXED);
+    return MST_OK;
+}
+
 inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -189,6 +201,11 @@ int bwd_fused_force_shape(int waves, int quads);
 enum GemmKind { GEMM_TN = 0, GEMM_NT = 1, GEMM_NN = 2 };
 int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_dtype b_dt, float* C,
               int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed = nullptr);
+// the same at full fp32 precision for any shape (B fp32); see gemm_exact.hip
+int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,
+               float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed);
+int gemm_exact_tile(int tile);
+int sum_split_planes(const float* part, int64_t stride, int nsplit, float* C, int64_t n, hipStream_t s);
 int gemm_force_fp32_mfma(int on);
 int gemm_last_tile();
 int mask_update_device(mst_layer* L, const float* G, const mst_update_stats& st, uint64_t seed,

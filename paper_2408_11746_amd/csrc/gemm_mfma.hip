@@ -1,5 +1,5 @@
-// Dense fp32-accumulating GEMMs on the CDNA matrix cores: v_mfma_f32_32x32x2f32 for fp32
-// operands, v_mfma_f32_32x32x16_bf16 when both operands are bfloat16.
+// Dense fp32-accumulating GEMMs of whole tiles on the CDNA matrix cores (v_mfma_f32_32x32x16_bf16; any
+// other shape: gemm_exact.hip, except the bfloat16 dense gradient, which is here for every shape).
 //
 // Used where a dense contraction really is the work: the dense weight gradient
 // G = dY^T X that scores gradient-based growth (Algorithm 1, ArgTopK of |grad|; the dense
@@ -7,12 +7,8 @@
 // density is high (start of warm-up / end of restoration, Sec. 3.1).
 //
 // C[M x N] = sum_k A'[k][m] B'[k][n].  Each operand is given either k-major (element
-// (k, m) at src[k*ld + m]) or m-major (src[m*ld + k]); both are staged k-major in LDS.
-// Workgroup tile 128 x 128 x 16, four wavefronts of 64 x 64 (2 x 2 MFMA tiles each).
-// Optional split of the k range over blockIdx.x (fastest index: consecutive workgroups go
-// to the 8 XCDs in turn, so an XCD's L2 mostly sees one k range of the operands instead of
-// all of them) into separate partial outputs that a
-// second kernel adds in a fixed order.
+// (k, m) at src[k*ld + m]) or m-major (src[m*ld + k]).  The k range may be split over workgroups
+// into separate partial outputs that a second kernel adds in a fixed order.
 #include <type_traits>
 #include "common.h"
 #include "split_bf16.h"
@@ -20,164 +16,6 @@
 namespace mst {
 
 constexpr int BM = 128, BN = 128;      // bf16 kernel tile
-constexpr int BK = 16;                 // k per LDS tile of the fp32 kernel
-
-template <typename TIn>
-__device__ inline float to_f32(TIn v);
-template <>
-__device__ inline float to_f32<float>(float v) { return v; }
-template <>
-__device__ inline float to_f32<uint16_t>(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
-
-// four consecutive source elements; the 16-byte path needs all four in range and aligned
-template <typename TIn>
-__device__ inline void load4(const TIn* __restrict__ p, int n_valid, bool vec, float* v);
-template <>
-__device__ inline void load4<float>(const float* __restrict__ p, int n_valid, bool vec, float* v) {
-    if (vec && n_valid >= 4) {
-        const float4 q = *reinterpret_cast<const float4*>(p);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = j < n_valid ? p[j] : 0.f;
-}
-template <>
-__device__ inline void load4<uint16_t>(const uint16_t* __restrict__ p, int n_valid, bool vec, float* v) {
-    if (vec && n_valid >= 4) {
-        const uint2 q = *reinterpret_cast<const uint2*>(p);
-        v[0] = __uint_as_float(q.x << 16); v[1] = __uint_as_float(q.x & 0xFFFF0000u);
-        v[2] = __uint_as_float(q.y << 16); v[3] = __uint_as_float(q.y & 0xFFFF0000u);
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = j < n_valid ? to_f32<uint16_t>(p[j]) : 0.f;
-}
-
-// One operand tile [BK x W] (k-major in LDS, row stride W + 4) handled by NT threads:
-// IPT items of four elements per thread.
-template <int W, int NT> struct TileShape {
-    static constexpr int LD = W + 4;
-    static constexpr int IPT = BK * W / 4 / NT;
-    static_assert(BK * W / 4 % NT == 0, "tile does not divide over the threads");
-};
-
-template <typename TIn, bool KMAJOR, int W, int NT>
-__device__ inline void fetch_tile(const TIn* __restrict__ src, int64_t ld, int k0, int m0, int Kdim, int Mdim,
-                                  int tid, bool vec, float (&v)[4 * TileShape<W, NT>::IPT]) {
-    constexpr int IPT = TileShape<W, NT>::IPT;
-#pragma unroll
-    for (int it = 0; it < IPT; ++it) {
-        const int idx = it * NT + tid;
-        if (KMAJOR) {            // item = (k, group of 4 m): a wavefront reads whole rows
-            const int k = k0 + idx / (W / 4), m = m0 + ((idx % (W / 4)) << 2);
-            const int nv = (k < Kdim) ? max(0, min(4, Mdim - m)) : 0;
-            if (nv > 0) load4<TIn>(src + (int64_t)k * ld + m, nv, vec, &v[it * 4]);
-            else { v[it * 4] = v[it * 4 + 1] = v[it * 4 + 2] = v[it * 4 + 3] = 0.f; }
-        } else {                 // item = (m, group of 4 k)
-            const int m = m0 + idx / (BK / 4), k = k0 + ((idx % (BK / 4)) << 2);
-            const int nv = (m < Mdim) ? max(0, min(4, Kdim - k)) : 0;
-            if (nv > 0) load4<TIn>(src + (int64_t)m * ld + k, nv, vec, &v[it * 4]);
-            else { v[it * 4] = v[it * 4 + 1] = v[it * 4 + 2] = v[it * 4 + 3] = 0.f; }
-        }
-    }
-}
-
-template <bool KMAJOR, int W, int NT>
-__device__ inline void stage_tile(float* lds, int tid, const float (&v)[4 * TileShape<W, NT>::IPT]) {
-    constexpr int IPT = TileShape<W, NT>::IPT, LD = TileShape<W, NT>::LD;
-#pragma unroll
-    for (int it = 0; it < IPT; ++it) {
-        const int idx = it * NT + tid;
-        if (KMAJOR) {
-            const int k = idx / (W / 4), m = (idx % (W / 4)) << 2;
-            *reinterpret_cast<float4*>(lds + k * LD + m) =
-                make_float4(v[it * 4 + 0], v[it * 4 + 1], v[it * 4 + 2], v[it * 4 + 3]);
-        } else {
-            const int m = idx / (BK / 4), k = (idx % (BK / 4)) << 2;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) lds[(k + j) * LD + m] = v[it * 4 + j];
-        }
-    }
-}
-
-// TM x 128 workgroup tile, TM / 64 x 2 wavefronts of 64 x 64 each
-template <typename TA, bool A_KMAJOR, typename TB, bool B_KMAJOR, int TM>
-__global__ __launch_bounds__(TM * 2) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_gemm(const TA* __restrict__ A, int64_t lda,
-                                                 const TB* __restrict__ B, int64_t ldb,
-                                                 float* __restrict__ C, int M, int N, int Kdim, int k_per_split,
-                                                 int64_t split_stride, int vec_a, int vec_b) {
-    constexpr int NT = TM * 2, TNW = 128;
-    typedef TileShape<TM, NT> SA;
-    typedef TileShape<TNW, NT> SB;
-    __shared__ float As[2][BK * SA::LD];
-    __shared__ float Bs[2][BK * SB::LD];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
-    const int m0 = blockIdx.z * TM, n0 = blockIdx.y * TNW;
-    const int kbeg = blockIdx.x * k_per_split;
-    const int kend = min(Kdim, kbeg + k_per_split);
-    float* Cz = C + (int64_t)blockIdx.x * split_stride;
-
-    floatx16 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    // Two LDS buffers, one barrier per step: while buffer b is multiplied, the registers
-    // (tile s + 1, fetched during step s - 1) go to buffer b ^ 1 and tile s + 2 is fetched.
-    float ra[4 * SA::IPT], rb[4 * SB::IPT];
-    fetch_tile<TA, A_KMAJOR, TM, NT>(A, lda, kbeg, m0, kend, M, tid, vec_a != 0, ra);
-    fetch_tile<TB, B_KMAJOR, TNW, NT>(B, ldb, kbeg, n0, kend, N, tid, vec_b != 0, rb);
-    stage_tile<A_KMAJOR, TM, NT>(As[0], tid, ra);
-    stage_tile<B_KMAJOR, TNW, NT>(Bs[0], tid, rb);
-    if (kbeg + BK < kend) {
-        fetch_tile<TA, A_KMAJOR, TM, NT>(A, lda, kbeg + BK, m0, kend, M, tid, vec_a != 0, ra);
-        fetch_tile<TB, B_KMAJOR, TNW, NT>(B, ldb, kbeg + BK, n0, kend, N, tid, vec_b != 0, rb);
-    }
-    __syncthreads();
-    const int lk = lane >> 5, lm = lane & 31;
-    int buf = 0;
-    for (int k0 = kbeg; k0 < kend; k0 += BK, buf ^= 1) {
-        const float* as = As[buf];
-        const float* bs = Bs[buf];
-        if (k0 + BK < kend) {                  // the next tile goes to the other buffer ...
-            stage_tile<A_KMAJOR, TM, NT>(As[buf ^ 1], tid, ra);
-            stage_tile<B_KMAJOR, TNW, NT>(Bs[buf ^ 1], tid, rb);
-            if (k0 + 2 * BK < kend) {          // ... and the one after it starts to travel
-                fetch_tile<TA, A_KMAJOR, TM, NT>(A, lda, k0 + 2 * BK, m0, kend, M, tid, vec_a != 0, ra);
-                fetch_tile<TB, B_KMAJOR, TNW, NT>(B, ldb, k0 + 2 * BK, n0, kend, N, tid, vec_b != 0, rb);
-            }
-        }
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += 2) {
-            const float a0 = as[(kk + lk) * SA::LD + wm + lm];
-            const float a1 = as[(kk + lk) * SA::LD + wm + 32 + lm];
-            const float b0 = bs[(kk + lk) * SB::LD + wn + lm];
-            const float b1 = bs[(kk + lk) * SB::LD + wn + 32 + lm];
-            acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b0, acc[0][0], 0, 0, 0);
-            acc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0, b1, acc[0][1], 0, 0, 0);
-            acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b0, acc[1][0], 0, 0, 0);
-            acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1, b1, acc[1][1], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-
-    // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int m = m0 + wm + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
-                const int n = n0 + wn + j * 32 + lm;
-                if (m < M && n < N) Cz[(int64_t)m * N + n] = acc[i][j][v];
-            }
-}
 
 // ---- bf16 x bf16 -> fp32, both operands k-major (the dense gradient G = dY^T X with
 // bfloat16 activations).  v_mfma_f32_32x32x16_bf16 wants, per lane, 8 consecutive k of one
@@ -190,28 +28,34 @@ __global__ __launch_bounds__(TM * 2) __attribute__((amdgpu_waves_per_eu(4, 4))) 
 constexpr int BKH = 64;            // k per LDS tile
 
 
-// thread -> patch: 16 patches along m x 8 along k, for the A tile (tid < 128) or the B tile
-__device__ inline void fetch_patch(const uint16_t* __restrict__ src, int64_t ld, int k0, int m0, int Kdim,
-                                   int Mdim, int p, bool vec_ok, uint4 (&d)[8]) {
+// thread -> patch: 16 patches along m x 8 along k, for the A tile (tid < 128) or the B tile.  Buffer loads
+// from the tile's corner with an exact end (k rows from kend on read as zeros; what follows the end of
+// a row is the next row and lands in outputs that are not stored): dword alignment is all they need, and
+// where rows have an odd length every other row starts in the middle of a dword and is shifted into
+// place (element by element such a layer took 780 us where an aligned one takes 170).
+typedef uint32_t tn_u32x4 __attribute__((ext_vector_type(4)));
+__device__ inline void fetch_patch(const uint16_t* __restrict__ src, int64_t ld, int k0, int m0, int kend, int p, uint4 (&d)[8]) {
     const int mq = p & 15, kg = p >> 4;
-    const int m = m0 + 8 * mq;
+    const int64_t left = (int64_t)min(kend - k0, BKH) * ld - m0;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src + (int64_t)k0 * ld + m0), 0,
+                                                                        (int)((2 * left + 3) & ~3ll), 0x00020000);
+    const uint32_t pitch = 2u * (uint32_t)ld, o0 = (uint32_t)(8 * kg) * pitch + (uint32_t)(16 * mq);
+    if ((ld & 1) == 0) {
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) {
-        const int k = k0 + 8 * kg + kk;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (k < Kdim && m < Mdim) {
-            const uint16_t* q = src + (int64_t)k * ld + m;
-            if (vec_ok && m + 8 <= Mdim) {
-                v = *reinterpret_cast<const uint4*>(q);
-            } else {
-                uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (m + j < Mdim) w[j >> 1] |= (uint32_t)q[j] << (16 * (j & 1));
-                v = make_uint4(w[0], w[1], w[2], w[3]);
-            }
+        for (int kk = 0; kk < 8; ++kk) {
+            const tn_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(o0 + kk * pitch), 0, 0);
+            d[kk] = make_uint4(v.x, v.y, v.z, v.w);
         }
-        d[kk] = v;
+    } else {
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            const uint32_t o = o0 + kk * pitch, oa = o & ~3u, sh = (o & 2u) << 3;
+            const tn_u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)oa, 0, 0);
+            const uint32_t e = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(oa + 16), 0, 0);
+            // (the last dword may hold one element past the end: it would be the first one of row kend)
+            d[kk] = make_uint4((int64_t)o >= 2 * left ? 0u : __builtin_amdgcn_alignbit(w.y, w.x, sh), __builtin_amdgcn_alignbit(w.z, w.y, sh),
+                               __builtin_amdgcn_alignbit(w.w, w.z, sh), __builtin_amdgcn_alignbit(e, w.w, sh));
+        }
     }
 }
 
@@ -233,8 +77,7 @@ __device__ inline void stage_patch(char* lds, int p, const uint4 (&d)[8]) {
 __global__ __launch_bounds__(256) void k_gemm_tn_bf16(const uint16_t* __restrict__ A, int64_t lda,
                                                       const uint16_t* __restrict__ B, int64_t ldb,
                                                       float* __restrict__ C, int M, int N, int Kdim,
-                                                      int k_per_split, int64_t split_stride, int vec_a,
-                                                      int vec_b) {
+                                                      int k_per_split, int64_t split_stride) {
     __shared__ __attribute__((aligned(16))) char As[BM * 128];
     __shared__ __attribute__((aligned(16))) char Bs[BN * 128];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -248,8 +91,7 @@ __global__ __launch_bounds__(256) void k_gemm_tn_bf16(const uint16_t* __restrict
     const int p = tid & 127;
     const uint16_t* src = mine_a ? A : B;
     const int64_t ld = mine_a ? lda : ldb;
-    const int o0 = mine_a ? m0 : n0, odim = mine_a ? M : N;
-    const bool vec = mine_a ? vec_a != 0 : vec_b != 0;
+    const int o0 = mine_a ? m0 : n0;
     char* dst = mine_a ? As : Bs;
 
     floatx16 acc[2][2];
@@ -261,13 +103,13 @@ __global__ __launch_bounds__(256) void k_gemm_tn_bf16(const uint16_t* __restrict
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
     uint4 rp[8];
-    fetch_patch(src, ld, kbeg, o0, kend, odim, p, vec, rp);
+    fetch_patch(src, ld, kbeg, o0, kend, p, rp);
     const int lk = lane >> 5, lm = lane & 31;
     for (int k0 = kbeg; k0 < kend; k0 += BKH) {
         __syncthreads();
         stage_patch(dst, p, rp);
         __syncthreads();
-        if (k0 + BKH < kend) fetch_patch(src, ld, k0 + BKH, o0, kend, odim, p, vec, rp);
+        if (k0 + BKH < kend) fetch_patch(src, ld, k0 + BKH, o0, kend, p, rp);
 #pragma unroll
         for (int ks = 0; ks < BKH / 8; ks += 2) {          // 16 k per MFMA: units ks + lk
             const bf16x8 a0 = *reinterpret_cast<const bf16x8*>(As + bf_unit(wm + lm, ks + lk));
@@ -303,7 +145,7 @@ __global__ __launch_bounds__(256) void k_gemm_tn_bf16(const uint16_t* __restrict
 // (64 KB).  Either operand may be k-major (element (k, m) at src[k*ld + m]: an [8 k x 4 m]
 // patch per thread is transposed in registers) or m-major (src[m*ld + k]: eight consecutive k
 // per thread go to LDS as they are).  Only for shapes whose tiles are whole (M, N multiples
-// of 128, k ranges multiples of 64, rows 16-byte aligned); everything else takes k_gemm.
+// of 128, k ranges multiples of 64, rows 16-byte aligned).
 constexpr int SPK = 64;
 
 
@@ -1269,7 +1111,7 @@ __global__ void k_splitk_reduce4(const float* __restrict__ part, int64_t stride,
     }
     reinterpret_cast<float4*>(C)[i] = s;
 }
-static int sum_split_planes(const float* part, int64_t stride, int nsplit, float* C, int64_t n, hipStream_t s) {
+int sum_split_planes(const float* part, int64_t stride, int nsplit, float* C, int64_t n, hipStream_t s) {
     if (n % 4 == 0 && stride % 4 == 0 && aligned16(part) && aligned16(C))
         k_splitk_reduce4<<<(unsigned)cdiv(n / 4, 256), 256, 0, s>>>(part, stride, nsplit, C, n / 4);
     else
@@ -1283,12 +1125,11 @@ static int sum_split_planes(const float* part, int64_t stride, int nsplit, float
 // times.  Cost of a choice = (k steps per workgroup x step_us + wg_us) x rounds, a last
 // partial round counting `last[]` by quarters of the places it fills, plus the pass that
 // adds the partial outputs.  Constants fitted to timings of the dense gradient at GPT-2
-// small / medium / large shapes (fp32 kernel: 2.7 % rms error; bf16 kernel: 9 %).
+// small / medium / large shapes (9 % rms error).
 struct SplitModel {
     int wg_per_cu, bk;
     double step_us, wg_us, sum_us_per_float, last[3];
 };
-static const SplitModel kSplitF32 = {4, BK, 4.63, 10.7, 5e-7, {0.44, 0.63, 0.84}};
 static const SplitModel kSplitBf16 = {3, BKH, 2.08, 3.0, 1.8e-6, {0.69, 0.76, 0.86}};
 
 static int pick_nsplit(int64_t tiles, int Kdim, const SplitModel& md, int64_t max_split) {
@@ -1309,37 +1150,6 @@ static int pick_nsplit(int64_t tiles, int Kdim, const SplitModel& md, int64_t ma
         }
     }
     return best;
-}
-
-// `left_unsummed`: if not null the partial outputs of a split stay in split_ws and their number
-// is returned there (1: the result is in C); otherwise they are added into C.
-template <typename TA, bool AK, typename TB, bool BKM>
-static int launch(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int M, int N, int Kdim,
-                  float* split_ws, int64_t split_ws_floats, int* left_unsummed, hipStream_t s) {
-    // (a 256 x 128 tile was measured: a third less operand traffic per flop, no gain in time)
-    const int tm = 128;
-    const int gm = (int)cdiv(M, tm), gn = (int)cdiv(N, 128);
-    const int64_t mn = (int64_t)M * N;
-    const int nsplit0 = split_ws ? pick_nsplit((int64_t)gm * gn, Kdim, kSplitF32, split_ws_floats / mn) : 1;
-    const int kps = (int)(cdiv(cdiv(Kdim, nsplit0), BK) * BK);
-    const int nsplit = (int)cdiv(Kdim, kps);
-    dim3 grid(nsplit, gn, gm);
-    float* dst = nsplit > 1 ? split_ws : C;
-    // 16-byte loads need every row start aligned: leading dimension a multiple of 4
-    // elements (the k ranges of the splits start at multiples of BK)
-    const int vec_a = (lda % 4 == 0) ? 1 : 0, vec_b = (ldb % 4 == 0) ? 1 : 0;
-    k_gemm<TA, AK, TB, BKM, 128><<<grid, 256, 0, s>>>((const TA*)A, lda, (const TB*)B, ldb, dst, M, N, Kdim, kps, mn,
-                                                     vec_a, vec_b);
-    MST_LAUNCH_CHECK();
-    if (left_unsummed) {
-        *left_unsummed = nsplit;
-        return MST_OK;
-    }
-    if (nsplit > 1) {
-        const int rcs = sum_split_planes(split_ws, mn, nsplit, C, mn, s);
-        if (rcs != MST_OK) return rcs;
-    }
-    return MST_OK;
 }
 
 // Workgroup tile and split count of the bf16-split kernels, chosen together.  Tiles are dealt to
@@ -1390,12 +1200,14 @@ static int g_split_tile = 0;              // test hook: 0 = automatic, 128 / 256
 
 int gemm_last_tile() { return g_last_tile; }
 
-int gemm_force_fp32_mfma(int on) {       // 0 automatic, 1 fp32 MFMA kernel, 128 / 256 / 160: split kernel with that tile
+int gemm_force_fp32_mfma(int on) {       // 0 automatic; 1, 1064, 1128, 1192 the full-precision kernel; 128 / 256 / 160 / 192: split kernel with that tile
     if (on == 52 || on == -52) {                    // (the other settings stay as they are)
         g_sched52 = on > 0;
         return MST_OK;
     }
-    g_gemm_fp32_only = on == 1 ? 1 : 0;
+    const bool exact = on == 1 || on == 1064 || on == 1128 || on == 1192;
+    g_gemm_fp32_only = exact ? 1 : 0;
+    gemm_exact_tile(exact && on > 1 ? on - 1000 : 0);
     g_split_tile = (on == 128 || on == 256 || on == 160 || on == 192) ? on : 0;
     return MST_OK;
 }
@@ -1520,9 +1332,7 @@ static int launch_tn_bf16(const void* A, const void* B, float* C, int M, int N, 
     const int nsplit = (int)cdiv(Kdim, kps);
     dim3 grid(nsplit, gn, gm);
     float* dst = nsplit > 1 ? split_ws : C;
-    // 16-byte loads of 8 elements need leading dimensions that are multiples of 8 (bases are 16-byte aligned)
-    k_gemm_tn_bf16<<<grid, 256, 0, s>>>((const uint16_t*)A, M, (const uint16_t*)B, N, dst, M, N, Kdim, kps, mn,
-                                        (M % 8 == 0) ? 1 : 0, (N % 8 == 0) ? 1 : 0);
+    k_gemm_tn_bf16<<<grid, 256, 0, s>>>((const uint16_t*)A, M, (const uint16_t*)B, N, dst, M, N, Kdim, kps, mn);
     MST_LAUNCH_CHECK();
     if (left_unsummed) {
         *left_unsummed = nsplit;
@@ -1548,21 +1358,21 @@ int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_d
             if (ab) return launch_tn_bf16(A, B, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
             if (split_ok(M, N, Kdim, M, N, true))
                 return launch_split<true, true>(A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
-            return launch<float, true, float, true>(A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+            return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
         case GEMM_NT:
             if (bb) return MST_ERR_ARG;
             if (ab && a16_ok(M, N, Kdim)) return launch_a16<false>(A, Kdim, B, Kdim, C, M, N, Kdim, left_unsummed, s);
-            if (ab) return launch<uint16_t, false, float, false>(A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+            if (ab) return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
             if (split_ok(M, N, Kdim, Kdim, Kdim, false))
                 return launch_split<false, false>(A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
-            return launch<float, false, float, false>(A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+            return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
         case GEMM_NN:
             if (bb) return MST_ERR_ARG;
             if (ab && a16_ok(M, N, Kdim)) return launch_a16<true>(A, Kdim, B, N, C, M, N, Kdim, left_unsummed, s);
-            if (ab) return launch<uint16_t, false, float, true>(A, Kdim, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+            if (ab) return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
             if (split_ok(M, N, Kdim, Kdim, N, false))
                 return launch_split<false, true>(A, Kdim, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
-            return launch<float, false, float, true>(A, Kdim, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+            return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
     }
     return MST_ERR_ARG;
 }

@@ -38,22 +38,10 @@ __global__ __launch_bounds__(WALK_NT) void k_walk_dw(const WalkSide row, const W
 inline unsigned walk_lds_bytes(int KC) { return (unsigned)std::max(KC * WT * 4, 2 * STAGE_BYTES); }
 inline unsigned walk_grid(int ntile, int nslab) { return 8u * (unsigned)cdiv((int64_t)ntile * nslab, 8); }
 
-// More than 64 KB of LDS has to be asked for, once per kernel and device (`done`: a bit per device; two
-// threads that meet here repeat the call).
-static int walk_allow_lds(const void* kernel, uint64_t& done) {
-    int dev = 0;
-    MST_HIP(hipGetDevice(&dev));
-    const uint64_t bit = 1ull << (dev & 63);
-    if (__atomic_load_n(&done, __ATOMIC_RELAXED) & bit) return MST_OK;
-    MST_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, KCMAX * WT * 4));
-    __atomic_fetch_or(&done, bit, __ATOMIC_RELAXED);
-    return MST_OK;
-}
-
 template <typename TIn, int Q, bool OUT, bool DW>
 static int launch_q(const WalkSide& sd, const WalkArgs& wa, int nsplit, hipStream_t s) {
     static uint64_t done = 0;
-    const int rc = walk_allow_lds(reinterpret_cast<const void*>(&k_walk<TIn, Q, OUT, DW>), done);
+    const int rc = allow_lds(reinterpret_cast<const void*>(&k_walk<TIn, Q, OUT, DW>), KCMAX * WT * 4, done);
     if (rc != MST_OK) return rc;
     k_walk<TIn, Q, OUT, DW><<<dim3(walk_grid(wa.ntile, sd.nslab), (unsigned)nsplit), WALK_NT, walk_lds_bytes(sd.KC), s>>>(sd, wa);
     MST_LAUNCH_CHECK();
@@ -85,7 +73,7 @@ static int launch_both_any(int q, const WalkSide& sd, const WalkArgs& wa, int ns
 template <typename TIn, int Q>
 static int launch_dw_q(const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const int* choice, hipStream_t s) {
     static uint64_t done = 0;
-    const int rc = walk_allow_lds(reinterpret_cast<const void*>(&k_walk_dw<TIn, Q>), done);
+    const int rc = allow_lds(reinterpret_cast<const void*>(&k_walk_dw<TIn, Q>), KCMAX * WT * 4, done);
     if (rc != MST_OK) return rc;
     k_walk_dw<TIn, Q><<<walk_grid(wa.ntile, std::max(row.nslab, col.nslab)), WALK_NT, walk_lds_bytes(std::max(row.KC, col.KC)), s>>>(
         row, col, wa, choice);

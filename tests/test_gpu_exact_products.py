@@ -1,0 +1,69 @@
+"""The dense products of any shape at full fp32 precision (three bfloat16 parts per fp32 operand): Y, dX
+and the dense gradient of a dense layer at the edges of the 64 x 64 and 128 x 128 tiles and of the k steps
+of 32 and 64, with one group of wavefronts per tile and with three, fp32 and bfloat16 activations, and the
+bfloat16 dense gradient on rows that are no multiple of anything.  Against the oracle (App. Eq. (1) and its
+gradients) at the precision of fp32 sums, far inside what two parts per operand would reach."""
+import numpy as np
+import pytest
+
+import paper_2408_11746_amd as mst
+import synth
+from oracle import products as opr
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from gpu_util import Rig, DEV, dev, rel_err  # noqa: E402
+
+FP32 = 2e-6          # max error over max value of an fp32 sum of up to 2000 terms
+SHAPES = [(1, 1, 1), (63, 65, 127), (64, 64, 64), (129, 33, 130), (130, 257, 63), (200, 191, 321), (257, 2000, 66), (2000, 66, 129)]
+
+
+@pytest.mark.parametrize("T,I,O", SHAPES)
+@pytest.mark.parametrize("mode", [1064, 1128, 1192])
+def test_fp32_operands_of_any_shape(T, I, O, mode):
+    print("case", T, I, O, mode, flush=True)
+    X, dY = synth.make_activations(61, 2, T, I, O)
+    X = (X * np.exp2(synth.normal(61, 7, X.shape) * 3)).astype(np.float32)       # all three parts matter
+    W = synth.normal(61, 3, (O, I), 0.02)
+    M = np.ones((O, I), np.uint8)
+    rig = Rig(W, M, T, cap=O * I)
+    rig.layer.set_path(mst.MST_PATH_DENSE)
+    G = torch.full((O, I), float("nan"), dtype=torch.float32, device=DEV)
+    try:
+        mst.mst_gemm_force_fp32_mfma(mode)
+        Y, dX = rig.fwd(X), rig.bwd_input(dY)
+        mst.mst_dense_grad(dev(dY), dev(X), G, T, O, I, mst.MST_F32, rig.ws)      # with room to split the token range
+        torch.cuda.synchronize()
+        G0 = torch.full((O, I), float("nan"), dtype=torch.float32, device=DEV)
+        mst.mst_dense_grad(dev(dY), dev(X), G0, T, O, I, mst.MST_F32, None)
+        torch.cuda.synchronize()
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
+    assert rel_err(Y, opr.fc_fwd(X, W, M)) <= FP32
+    assert rel_err(dX, opr.fc_bwd_input(dY, W, M)) <= FP32
+    assert rel_err(G.cpu().numpy(), opr.dense_grad(dY, X)) <= FP32
+    assert rel_err(G0.cpu().numpy(), opr.dense_grad(dY, X)) <= FP32
+
+
+@pytest.mark.parametrize("T,I,O", SHAPES)
+@pytest.mark.parametrize("mode", [1064, 1128, 1192])
+def test_bfloat16_activations_of_any_shape(T, I, O, mode):
+    print("case", T, I, O, mode, flush=True)
+    Xf, dYf, xb, yb = synth.make_activations(62, 2, T, I, O, "bf16")
+    W = synth.normal(62, 3, (O, I), 0.02)
+    W = (W * np.exp2(synth.normal(62, 8, W.shape) * 3)).astype(np.float32)
+    M = np.ones((O, I), np.uint8)
+    rig = Rig(W, M, T, cap=O * I)
+    rig.layer.set_path(mst.MST_PATH_DENSE)
+    G = torch.full((O, I), float("nan"), dtype=torch.float32, device=DEV)
+    try:
+        mst.mst_gemm_force_fp32_mfma(mode)
+        Y, dX = rig.fwd(xb.view(np.int16), mst.MST_BF16), rig.bwd_input(yb.view(np.int16), mst.MST_BF16)
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
+    mst.mst_dense_grad(dev(yb.view(np.int16)), dev(xb.view(np.int16)), G, T, O, I, mst.MST_BF16, rig.ws)
+    torch.cuda.synchronize()
+    assert rel_err(Y, opr.fc_fwd(Xf, W, M)) <= FP32
+    assert rel_err(dX, opr.fc_bwd_input(dYf, W, M)) <= FP32
+    assert rel_err(G.cpu().numpy(), opr.dense_grad(dYf, Xf)) <= FP32
