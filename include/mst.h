@@ -234,8 +234,8 @@ int mst_bwd_force_shape(int wavefronts_per_workgroup, int quads_per_wavefront);
  * staged, a product is hi*hi + hi*lo + lo*hi with fp32 accumulation; the result differs from
  * an fp32 product by less than 2^-16 per term.  Every other shape runs on a kernel of full fp32
  * precision (three bfloat16 values per element, exact; six products).  This hook pins, for all
- * later calls of the process: 1 = the full-precision kernel (1064, 1128, 1192: with a 64 x 64 tile, a
- * 128 x 128 tile, a 64 x 64 tile and three groups of wavefronts); 128, 256, 160 or 192 = the split kernel with the
+ * later calls of the process: 1 = the full-precision kernel (1064, 1128: with a 64 x 64 or a
+ * 128 x 128 tile; 1032, 1096: the streaming form for small outputs, 32 x 32 or 64 x 64); 128, 256, 160 or 192 = the split kernel with the
  * workgroup tile 128 x 128, 256 x 256, 256 x 160 or 256 x 192 (where the shape is a multiple of
  * it; the last two serve Y and dX only); 0 returns to the automatic choice.  All tiles add a
  * result's terms in the same order and give identical bits.  -52 / 52 switch off / on the

@@ -205,6 +205,14 @@ int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_d
 int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,
                float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed);
 int gemm_exact_tile(int tile);
+int gemm_stream_tn_bf16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int Kdim, int k_per_split, int64_t split_stride,
+                        hipStream_t s);
+double xcd_rounds(int64_t n, int places, int lone_places, double full, double lone);
+// modelled times in microseconds (max_split: k ranges there is room for; summed: their sum included)
+double gemm_mfma_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed);
+double gemm_exact_us(mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed);
+enum WalkJob { WALK_FWD = 0, WALK_BWD_INPUT, WALK_BWD_WEIGHT, WALK_BWD };
+double walk_us(const mst_layer* L, WalkJob job, int T);
 int sum_split_planes(const float* part, int64_t stride, int nsplit, float* C, int64_t n, hipStream_t s);
 int gemm_force_fp32_mfma(int on);
 int gemm_last_tile();

@@ -11,7 +11,7 @@
 // layer of any size): they used to run on v_mfma_f32_32x32x2f32 at 100 TFLOP/s.  Six
 // v_mfma_f32_32x32x16_bf16 take the place of eight of those at a sixteenth of the time each.
 //
-// Workgroup tile TM x TM, TM = 128 or 64, 256 threads = four wavefronts of (TM/2) x (TM/2); k steps of
+// k_gemm_exact: workgroup tile TM x TM, TM = 128 or 64, 256 threads = four wavefronts of (TM/2) x (TM/2); k steps of
 // 4096 / TM, so that a plane of an operand's tile is 8 KB and a workgroup's LDS 48 KB (32 KB with a
 // bfloat16 operand): two (three) workgroups share a CU and one's staging runs beside another's MFMAs.
 // Loads are buffer loads from the tile's corner with exact ends: rows past the matrix read as zeros
@@ -147,22 +147,15 @@ struct ExOperand {
 
 // Tile numbers run in bands of eight tile rows, column by column inside a band (the tiles an XCD works on
 // at a time share operand panels in its L2); XCD x takes a contiguous share, one k range after the other.
-//
-// KG: groups of four wavefronts that share one output tile and take its k steps in turn, each with LDS
-// planes of its own; their sums are added in order at the end.  With one group a step costs at least
-// the latency of its loads (1.3 us however few products it has), so where there are fewer tiles than CUs
-// three groups of a 64 x 64 tile fill a CU's LDS and have three steps on the way.
-template <bool A16, bool A_KMAJOR, bool B_KMAJOR, int TM, int KG>
-__global__ __launch_bounds__(256 * KG) __attribute__((amdgpu_waves_per_eu(2, 3)))
+template <bool A16, bool A_KMAJOR, bool B_KMAJOR, int TM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3)))
 void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
                   int M, int N, int Kdim, int k_per_split, int64_t split_stride) {
     typedef ExOperand<A16, A_KMAJOR, TM> OpA;
     typedef ExOperand<false, B_KMAJOR, TM> OpB;
     constexpr int BK = 4096 / TM, PLANE = 8192, MI = TM / 64;
-    constexpr int GROUP_LDS = (OpA::PLANES + OpB::PLANES) * PLANE;
     extern __shared__ __attribute__((aligned(16))) char ex_lds[];
-    const int group = KG > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) : 0;
-    char* const la = ex_lds + group * GROUP_LDS;
+    char* const la = ex_lds;
     char* const lb = la + OpA::PLANES * PLANE;
     const int gm = (M + TM - 1) / TM, gn = (N + TM - 1) / TM, ntiles = gm * gn;
     const int nsplit = (Kdim + k_per_split - 1) / k_per_split, Q = (ntiles + 7) >> 3;
@@ -175,7 +168,7 @@ void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restr
     float* const Cz = C + (int64_t)split * split_stride;
     const typename OpA::T* const A = static_cast<const typename OpA::T*>(Av);
 
-    const int tid = threadIdx.x & 255, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave >> 1) * (TM / 2), wn = (wave & 1) * (TM / 2);
     floatx16 acc[MI][MI];
 #pragma unroll
@@ -227,43 +220,24 @@ void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restr
         ra.stage(la, tid);
         rb.stage(lb, tid);
     };
-    // rounds of one step per group; only in the last one a group may have no step, or one that ends at kend
-    const int rounds = (kend - kbeg + BK * KG - 1) / (BK * KG);
-    int k0 = kbeg + group * BK;
-    if (KG == 1 || k0 < kend) fetch(k0);
-    for (int r = 1; r < rounds; ++r) {
+    int k0 = kbeg;
+    fetch(k0);
+    for (; k0 + BK < kend; k0 += BK) {
         __syncthreads();
         stage();
         __syncthreads();
-        k0 += BK * KG;
-        if (KG == 1 || k0 < kend) fetch(k0);
+        fetch(k0 + BK);
         multiply();
     }
     __syncthreads();
-    if (KG == 1 || k0 < kend) {
-        ra.clear_tail(k0, kend, tid);
-        rb.clear_tail(k0, kend, tid);
-        stage();
-    }
+    ra.clear_tail(k0, kend, tid);
+    rb.clear_tail(k0, kend, tid);
+    stage();
     __syncthreads();
-    if (KG == 1 || k0 < kend) multiply();
+    multiply();
     if constexpr (CHAINS > 1)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[0][0][v] += other[v];
-    if constexpr (KG > 1) {
-        static_assert(MI == 1, "one MFMA tile per wavefront");
-        float* const sums = reinterpret_cast<float*>(ex_lds);
-        __syncthreads();
-        if (group > 0)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sums[((group - 1) * 16 + v) * 256 + tid] = acc[0][0][v];
-        __syncthreads();
-        if (group > 0) return;
-#pragma unroll
-        for (int z = 0; z < KG - 1; ++z)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[0][0][v] += sums[(z * 16 + v) * 256 + tid];
-    }
     // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
 #pragma unroll
     for (int i = 0; i < MI; ++i)
@@ -277,49 +251,273 @@ void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restr
             }
 }
 
-// Workgroup tile, wavefront groups and number of k ranges together, as for the split kernels: modelled
-// time = rounds one XCD needs for its share of the tiles x time of a workgroup (k steps, start-up and output
-// counted in steps), plus the traffic of the partial outputs.  Places of an XCD: 64 workgroups of
-// 128 x 128, 96 of 64 x 64 (32 with three groups).  Microseconds of a step with all places taken
-// and with a CU to itself, from timings at ten shapes on MI355X.
-struct ExactPlan {
-    int tile, groups, nsplit;
-};
-static int g_exact_tile = 0;                          // test hook: 0 automatic, 64, 128, or 192: 64 with three groups
-static ExactPlan plan_exact(int M, int N, int Kdim, bool a16, int64_t max_split, bool summed) {
-    struct Kind {
-        int tile, groups, places, lone_places;
-        double start;                                 // start-up and output of a workgroup, in steps
-        double full[2], lone[2];                      // fp32, bfloat16 A
-    };
-    static const Kind kinds[] = {{128, 1, 64, 32, 4.0, {2.6, 1.4}, {1.87, 1.0}},
-                                 {64, 1, 96, 32, 4.0, {2.65, 1.4}, {1.45, 0.95}},
-                                 {64, 3, 32, 32, 3.0, {2.3, 1.65}, {2.3, 1.65}}};
-    static const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-    ExactPlan best{0, 1, 1};
-    double best_cost = 0.0;
-    for (const Kind& kd : kinds) {
-        if (g_exact_tile && kd.tile * kd.groups != g_exact_tile) continue;
-        const int bk = 4096 / kd.tile;
-        const int64_t Q = cdiv(cdiv(M, kd.tile) * cdiv(N, kd.tile), 8);
-        for (int ns : cand) {
-            if (ns > 1 && (ns > max_split || Kdim / ns < 256)) continue;
-            const double steps = (double)cdiv(cdiv(cdiv(Kdim, ns), bk), kd.groups);
-            const int64_t n = Q * ns, rest = n % kd.places;
-            if (kd.groups > 1 && n > kd.places && !g_exact_tile) continue;    // more than a round of tiles: one group each
-            const double full = kd.full[a16], lone = kd.lone[a16];
-            // (a last round that leaves places empty is shorter: the workgroups of a CU share its matrix cores)
-            const double last = rest == 0 ? 0.0 : rest <= kd.lone_places ? lone
-                : lone + (full - lone) * (double)(rest - kd.lone_places) / (double)(kd.places - kd.lone_places);
-            double cost = ((double)(n / kd.places) * full + last) * (steps + kd.start);
-            if (ns > 1) cost += 3.0 + 1.0e-6 * (double)M * (double)N * (summed ? ns + 1.0 : 0.25 * ns);
-            if (best.tile == 0 || cost < best_cost) {
-                best_cost = cost;
-                best = ExactPlan{kd.tile, kd.groups, ns};
+// ---- Small outputs: one workgroup per 32 x 32 (MI = 1) or 64 x 64 (MI = 2) output tile, all its
+// wavefronts on the same tile, each with k steps of its own.  Operands go from global memory straight to
+// the registers the matrix instructions read (lane = row, 16 or 8 consecutive k), no LDS and no barrier until
+// the partial tiles are added in wavefront order at the end.  An output of a few dozen tiles is a chain
+// of k steps that nothing else hides, and here a CU has 16 (8) steps on the way instead of one or three.
+// Every wavefront converts its own operands, so the vector ALU (MI = 1: about 90 instructions beside six
+// MFMAs per 16 k) bounds it where there are tiles for all CUs.
+//
+// Rows of the tile a lane holds: m-major lm and 32 + lm; k-major 2 lm and 2 lm + 1, so that both come with
+// one load per k.
+template <bool BF16, bool KMAJOR, int MI, int KS>
+struct StreamOperand {                               // KS / 2 consecutive k of MI rows per lane
+    static constexpr int NF = KS / 2, PLANES = BF16 ? 1 : 3;
+    // bfloat16: dwords from the one that holds the first element; k-major MI = 1 would waste half of each
+    static constexpr int NH = !BF16 ? 1 : KMAJOR ? 2 * NF : MI * (NF / 2 + 1);
+    typedef typename std::conditional<BF16, uint16_t, float>::type T;
+    static_assert(!(BF16 && KMAJOR) || MI == 2, "");
+    float f[BF16 ? 1 : MI * NF];                      // row i, k kk: f[i NF + kk]
+    uint32_t h[NH];
+    uint32_t sh[BF16 && !KMAJOR ? MI : 1];
+
+    __device__ static __forceinline__ int row(int i, int lm) { return KMAJOR && MI == 2 ? 2 * lm + i : 32 * i + lm; }
+
+    // rows past the matrix (m-major) and k from kend on (k-major) are cut off by the descriptor
+    __device__ __forceinline__ void fetch(const T* __restrict__ src, int64_t ld, int k0, int m0, int kend, int Mdim, int lm, int lk) {
+        const int64_t corner = KMAJOR ? (int64_t)k0 * ld + m0 : (int64_t)m0 * ld + k0;
+        const int64_t left = k0 >= kend ? 0 : KMAJOR ? (int64_t)min(kend - k0, KS) * ld - m0 : (int64_t)min(Mdim - m0, 32 * MI) * ld - k0;
+        const uint32_t bytes = left <= 0 ? 0u : (uint32_t)((left * (int64_t)sizeof(T) + 3) & ~3ll);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(src + (bytes ? corner : 0)), 0, (int)bytes, 0x00020000);
+        const uint32_t pitch = (uint32_t)ld * (uint32_t)sizeof(T);
+        if constexpr (KMAJOR) {
+            uint32_t o = (uint32_t)(NF * lk) * pitch + (uint32_t)(MI * lm) * (uint32_t)sizeof(T);
+            asm volatile("" : "+v"(o));               // (NF offsets kept across the loop would not fit the registers)
+#pragma unroll
+            for (int kk = 0; kk < NF; ++kk, o += pitch) {
+                if constexpr (BF16) {                 // (rows of an odd length: every other one starts in the middle of a dword)
+                    const ex_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(o & ~3u), 0, 0);
+                    h[2 * kk] = v.x;
+                    h[2 * kk + 1] = v.y;
+                } else if constexpr (MI == 2) {
+                    const ex_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)o, 0, 0);
+                    f[kk] = __uint_as_float(v.x);
+                    f[NF + kk] = __uint_as_float(v.y);
+                } else {
+                    f[kk] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)o, 0, 0));
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                const uint32_t o = (uint32_t)(32 * i + lm) * pitch + (uint32_t)(NF * lk) * (uint32_t)sizeof(T);
+                if constexpr (BF16) {
+                    sh[i] = (o & 2u) << 3;
+#pragma unroll
+                    for (int u = 0; u < NF / 8; ++u) {
+                        const ex_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)((o & ~3u) + 16 * u), 0, 0);
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) h[i * (NF / 2 + 1) + 4 * u + d] = v[d];
+                    }
+                    h[i * (NF / 2 + 1) + NF / 2] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)((o & ~3u) + 2 * NF), 0, 0);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < NF / 4; ++u) {
+                        const ex_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(o + 16 * u), 0, 0);
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) f[i * NF + 4 * u + d] = __uint_as_float(v[d]);
+                    }
+                }
             }
         }
     }
+    // bfloat16: pairs into place, h[i (NF / 2) + d] the pair of k 2d, 2d + 1 of row i.  In the last step
+    // (`tail`) k from kend on are cleared: m-major rows go on into the next row there, and the last dword of
+    // a k-major operand may hold the first element of row kend.
+    __device__ __forceinline__ void settle(bool tail, int k0, int kend, int64_t ld, int lk) {
+        const int valid = kend - (k0 + NF * lk);      // k of this lane that exist
+        if constexpr (BF16 && KMAJOR) {
+            const uint32_t s = (uint32_t)(ld & 1) << 4;
+#pragma unroll
+            for (int d = 0; d < NF / 2; ++d) {        // (k0 and NF lk are even)
+                uint32_t e = h[4 * d], o = __builtin_amdgcn_alignbit(h[4 * d + 3], h[4 * d + 2], s);
+                if (tail) {
+                    e = 2 * d < valid ? e : 0u;
+                    o = 2 * d + 1 < valid ? o : 0u;
+                }
+                h[2 * d] = __builtin_amdgcn_perm(o, e, 0x05040100u);
+                h[2 * d + 1] = __builtin_amdgcn_perm(o, e, 0x07060302u);
+            }
+        } else if constexpr (BF16) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int d = 0; d < NF / 2; ++d) {
+                    const int x = i * (NF / 2 + 1) + d;
+                    h[x] = __builtin_amdgcn_alignbit(h[x + 1], h[x], sh[i]);
+                    if (tail) h[x] = valid >= 2 * d + 2 ? h[x] : valid == 2 * d + 1 ? h[x] & 0xFFFFu : 0u;
+                }
+        } else if constexpr (!KMAJOR) {
+            if (tail)
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int d = 0; d < NF; ++d) f[i * NF + d] = d < valid ? f[i * NF + d] : 0.f;
+        }
+    }
+    // planes of the u-th eight k of row i
+    __device__ __forceinline__ void planes(int i, int u, bf16x8 (&p)[PLANES]) const {
+        if constexpr (BF16) {
+            ex_u32x4 w;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) w[d] = KMAJOR ? h[2 * (4 * u + d) + i] : h[i * (NF / 2 + 1) + 4 * u + d];
+            p[0] = __builtin_bit_cast(bf16x8, w);
+        } else {
+            ex_u32x4 w[3];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                uint32_t hi, mid, lo;
+                cut_pair(f[i * NF + 8 * u + 2 * d], f[i * NF + 8 * u + 2 * d + 1], hi, mid, lo);
+                w[0][d] = hi; w[1][d] = mid; w[2][d] = lo;
+            }
+#pragma unroll
+            for (int z = 0; z < 3; ++z) p[z] = __builtin_bit_cast(bf16x8, w[z]);
+        }
+    }
+};
+
+constexpr unsigned STREAM_LDS_32 = 16 * 32 * 32 * 4, STREAM_LDS_64 = 8 * 64 * 64 * 4;    // a partial tile per wavefront
+template <bool A16, bool A_KMAJOR, bool B16, bool B_KMAJOR, int MI>
+__global__ __launch_bounds__(MI == 1 ? 1024 : 512)
+void k_gemm_stream(const void* __restrict__ Av, int64_t lda, const void* __restrict__ Bv, int64_t ldb, float* __restrict__ C,
+                   int M, int N, int Kdim, int k_per_split, int64_t split_stride) {
+    constexpr int KS = MI == 1 ? 32 : 16, NW = MI == 1 ? 16 : 8, TM = 32 * MI;
+    typedef StreamOperand<A16, A_KMAJOR, MI, KS> OpA;
+    typedef StreamOperand<B16, B_KMAJOR, MI, KS> OpB;
+    extern __shared__ __attribute__((aligned(16))) char ex_lds[];
+    const int gm = (M + TM - 1) / TM, gn = (N + TM - 1) / TM, ntiles = gm * gn;
+    const int nsplit = (Kdim + k_per_split - 1) / k_per_split, Q = (ntiles + 7) >> 3;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int split = slot / Q, tile_id = xcd * Q + slot % Q;
+    if (tile_id >= ntiles || split >= nsplit) return;
+    const int band = tile_id / (8 * gn), rem = tile_id - band * 8 * gn, hgt = min(8, gm - 8 * band);
+    const int m0 = (8 * band + rem % hgt) * TM, n0 = (rem / hgt) * TM;
+    const int kbeg = split * k_per_split, kend = min(Kdim, kbeg + k_per_split);
+    float* const Cz = C + (int64_t)split * split_stride;
+    const typename OpA::T* const A = static_cast<const typename OpA::T*>(Av);
+    const typename OpB::T* const B = static_cast<const typename OpB::T*>(Bv);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lk = lane >> 5, lm = lane & 31;
+
+    floatx16 acc[MI][MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    // plane pairs, smallest terms first
+    constexpr int NP = A16 && B16 ? 1 : A16 ? 3 : 6;
+    constexpr int pa[6] = {A16 ? 0 : 2, A16 ? 0 : 0, A16 ? 0 : 1, 1, 0, 0};
+    constexpr int pb[6] = {B16 ? 0 : A16 ? 2 : 0, A16 ? 1 : 2, A16 ? 0 : 1, 0, 1, 0};
+    OpA ra[2];
+    OpB rb[2];
+    auto fetch = [&](OpA& a, OpB& b, int k0) __attribute__((always_inline)) {
+        a.fetch(A, lda, k0, m0, kend, M, lm, lk);
+        b.fetch(B, ldb, k0, n0, kend, N, lm, lk);
+    };
+    auto multiply = [&](OpA& a, OpB& b, int k0) __attribute__((always_inline)) {
+        if (k0 + KS > kend) {
+            a.settle(true, k0, kend, lda, lk);
+            b.settle(true, k0, kend, ldb, lk);
+        } else {
+            a.settle(false, k0, kend, lda, lk);
+            b.settle(false, k0, kend, ldb, lk);
+        }
+#pragma unroll
+        for (int u = 0; u < KS / 16; ++u) {
+            bf16x8 fa[MI][OpA::PLANES], fb[MI][OpB::PLANES];
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                a.planes(i, u, fa[i]);
+                b.planes(i, u, fb[i]);
+            }
+#pragma unroll
+            for (int t = 0; t < NP; ++t)
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < MI; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i][pa[t]], fb[j][pb[t]], acc[i][j], 0, 0, 0);
+        }
+    };
+    // step r of this wavefront starts at kbeg + (r NW + wave) KS; steps past kend are zeros
+    const int stride = KS * NW;
+    int k0 = kbeg + wave * KS;
+    fetch(ra[0], rb[0], k0);
+    while (k0 < kend) {
+        fetch(ra[1], rb[1], k0 + stride);
+        multiply(ra[0], rb[0], k0);
+        fetch(ra[0], rb[0], k0 + 2 * stride);
+        multiply(ra[1], rb[1], k0 + stride);
+        k0 += 2 * stride;
+    }
+    // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
+    float* const part = reinterpret_cast<float*>(ex_lds);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < MI; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                part[(wave * TM + OpA::row(i, 8 * (v >> 2) + 4 * lk + (v & 3))) * TM + OpB::row(j, lm)] = acc[i][j][v];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < TM * TM / (64 * NW); ++e) {
+        const int x = e * 64 * NW + tid, m = m0 + x / TM, n = n0 + x % TM;
+        float sum = part[x];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += part[w * TM * TM + x];
+        if (m < M && n < N) Cz[(int64_t)m * N + n] = sum;
+    }
+}
+
+// Kernel, workgroup tile and number of k ranges together, as for the split kernels: modelled time = rounds
+// one XCD needs for its share of the tiles x time of a workgroup, plus a launch and the traffic of the
+// partial outputs.  Places of an XCD: 64 workgroups of 128 x 128, 96 of 64 x 64, 32 of the streaming
+// kernel; with no more workgroups than CUs each has one to itself and is faster.  Microseconds fitted to timings
+// of 130 products, 1 to 40 GFLOP, on MI355X (8-14 % rms error).
+struct ExactPlan {
+    int tile;
+    bool stream;
+    int nsplit;
+    double us;
+};
+static int g_exact_tile = 0;                          // test hook: 0 automatic, 64 or 128, streaming: 32 or 96 (64 x 64)
+static ExactPlan plan_exact(int M, int N, int Kdim, bool a16, int64_t max_split, bool summed) {
+    struct Kind {
+        int hook, tile;
+        bool stream;
+        int places, lone_places, bk;
+        // fp32, bfloat16 A: a k step with all places taken, with a CU to itself; start-up and output of a workgroup
+        // (streaming: a k of all steps; microseconds); launch
+        double full[2], lone[2], start[2], launch[2];
+    };
+    static const Kind kinds[] = {{128, 128, false, 64, 32, 32, {2.71, 1.64}, {1.78, 1.08}, {1.4, 1.2}, {2.6, 4.0}},
+                                 {64, 64, false, 96, 32, 64, {2.63, 1.65}, {1.47, 0.97}, {0.5, 0.7}, {3.3, 3.6}},
+                                 {32, 32, true, 32, 0, 128, {0.0052, 0.0046}, {0.0046, 0.0040}, {3.1, 2.6}, {2.9, 3.1}},
+                                 {96, 64, true, 32, 0, 128, {0.0131, 0.0117}, {0.0108, 0.0106}, {3.7, 2.6}, {2.8, 3.1}}};
+    static const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+    ExactPlan best{0, false, 1, 0.0};
+    for (const Kind& kd : kinds) {
+        if (g_exact_tile && kd.hook != g_exact_tile) continue;
+        const int64_t Q = cdiv(cdiv(M, kd.tile) * cdiv(N, kd.tile), 8);
+        const double full = kd.full[a16], lone = kd.lone[a16];
+        for (int ns : cand) {
+            if (ns > 1 && (ns > max_split || Kdim / ns < 256)) break;
+            const double work = xcd_rounds(Q * ns, kd.places, kd.lone_places, full, lone);
+            double cost = kd.launch[a16] + (kd.stream ? work * (double)cdiv(Kdim, ns) + (double)cdiv(Q * ns, kd.places) * kd.start[a16]
+                                                      : work * ((double)cdiv(cdiv(Kdim, ns), kd.bk) + kd.start[a16]));
+            if (ns > 1) cost += 3.0 + 1.0e-6 * (double)M * (double)N * (summed ? ns + 1.0 : 0.25 * ns);
+            if (best.tile == 0 || cost < best.us) best = ExactPlan{kd.tile, kd.stream, ns, cost};
+        }
+    }
     return best;
+}
+
+double gemm_exact_us(mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed) {
+    return plan_exact(M, N, Kdim, a_dt == MST_BF16, max_split, summed).us;
 }
 
 int gemm_exact_tile(int tile) {
@@ -332,21 +530,22 @@ static int launch_exact(const void* A, int64_t lda, const float* B, int64_t ldb,
                         float* split_ws, int64_t split_ws_floats, int* nparts, hipStream_t s) {
     const int64_t mn = (int64_t)M * N;
     const ExactPlan plan = plan_exact(M, N, Kdim, A16, split_ws ? split_ws_floats / mn : 1, nparts == nullptr);
-    const int bk = 4096 / plan.tile;
-    const int kps = (int)(cdiv(cdiv(Kdim, plan.nsplit), bk) * bk);
+    const int kps = (int)(cdiv(cdiv(Kdim, plan.nsplit), 128) * 128);
     const int nsplit = (int)cdiv(Kdim, kps);
     const unsigned grid = (unsigned)(8 * cdiv(cdiv(M, plan.tile) * cdiv(N, plan.tile), 8) * nsplit);
     float* const dst = nsplit > 1 ? split_ws : C;
     constexpr unsigned lds = (ExOperand<A16, AK, 64>::PLANES + 3) * 8192;
-    if (plan.tile == 128) {
-        k_gemm_exact<A16, AK, BKM, 128, 1><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
-    } else if (plan.groups == 1) {
-        k_gemm_exact<A16, AK, BKM, 64, 1><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
-    } else {
+    if (plan.stream && plan.tile == 32) {
+        k_gemm_stream<A16, AK, false, BKM, 1><<<grid, 1024, STREAM_LDS_32, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+    } else if (plan.stream) {
         static uint64_t done = 0;
-        const int rc = allow_lds(reinterpret_cast<const void*>(&k_gemm_exact<A16, AK, BKM, 64, 3>), 3 * lds, done);
+        const int rc = allow_lds(reinterpret_cast<const void*>(&k_gemm_stream<A16, AK, false, BKM, 2>), STREAM_LDS_64, done);
         if (rc != MST_OK) return rc;
-        k_gemm_exact<A16, AK, BKM, 64, 3><<<grid, 768, 3 * lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+        k_gemm_stream<A16, AK, false, BKM, 2><<<grid, 512, STREAM_LDS_64, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+    } else if (plan.tile == 128) {
+        k_gemm_exact<A16, AK, BKM, 128><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+    } else {
+        k_gemm_exact<A16, AK, BKM, 64><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
     }
     MST_LAUNCH_CHECK();
     if (nparts) {
@@ -354,6 +553,18 @@ static int launch_exact(const void* A, int64_t lda, const float* B, int64_t ldb,
         return MST_OK;
     }
     return nsplit > 1 ? sum_split_planes(split_ws, mn, nsplit, C, mn, s) : MST_OK;
+}
+
+// C = A^T B, both bfloat16 and k-major, on 64 x 64 tiles; k_per_split a multiple of 64
+int gemm_stream_tn_bf16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int Kdim, int k_per_split, int64_t split_stride,
+                        hipStream_t s) {
+    static uint64_t done = 0;
+    const int rc = allow_lds(reinterpret_cast<const void*>(&k_gemm_stream<true, true, true, true, 2>), STREAM_LDS_64, done);
+    if (rc != MST_OK) return rc;
+    const unsigned grid = (unsigned)(8 * cdiv(cdiv(M, 64) * cdiv(N, 64), 8) * cdiv(Kdim, k_per_split));
+    k_gemm_stream<true, true, true, true, 2><<<grid, 512, STREAM_LDS_64, s>>>(A, M, B, N, C, M, N, Kdim, k_per_split, split_stride);
+    MST_LAUNCH_CHECK();
+    return MST_OK;
 }
 
 int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,

@@ -28,51 +28,55 @@ constexpr int BM = 128, BN = 128;      // bf16 kernel tile
 constexpr int BKH = 64;            // k per LDS tile
 
 
-// thread -> patch: 16 patches along m x 8 along k, for the A tile (tid < 128) or the B tile.  Buffer loads
-// from the tile's corner with an exact end (k rows from kend on read as zeros; what follows the end of
-// a row is the next row and lands in outputs that are not stored): dword alignment is all they need, and
-// where rows have an odd length every other row starts in the middle of a dword and is shifted into
-// place (element by element such a layer took 780 us where an aligned one takes 170).
+// A patch of 8 k x 8 m on its way from a k-major bfloat16 operand into LDS: eight 16-byte loads, an 8 x 8
+// halfword transpose (v_perm_b32), eight LDS units of eight k.  RAGGED: buffer loads from the tile's corner
+// with an exact end (k rows from kend on read as zeros; what follows the end of a row is the next row and
+// lands in outputs that are not stored).  Dword alignment is all they need; where rows have an odd length
+// every other one -- the odd k of a patch, tiles start at even k -- begins in the middle of a dword, and a
+// fifth dword goes with it.  (Element by element such a layer took 780 us where an aligned one takes 170.)
 typedef uint32_t tn_u32x4 __attribute__((ext_vector_type(4)));
-__device__ inline void fetch_patch(const uint16_t* __restrict__ src, int64_t ld, int k0, int m0, int kend, int p, uint4 (&d)[8]) {
-    const int mq = p & 15, kg = p >> 4;
-    const int64_t left = (int64_t)min(kend - k0, BKH) * ld - m0;
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src + (int64_t)k0 * ld + m0), 0,
-                                                                        (int)((2 * left + 3) & ~3ll), 0x00020000);
-    const uint32_t pitch = 2u * (uint32_t)ld, o0 = (uint32_t)(8 * kg) * pitch + (uint32_t)(16 * mq);
-    if ((ld & 1) == 0) {
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) {
-            const tn_u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(o0 + kk * pitch), 0, 0);
-            d[kk] = make_uint4(v.x, v.y, v.z, v.w);
-        }
-    } else {
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) {
-            const uint32_t o = o0 + kk * pitch, oa = o & ~3u, sh = (o & 2u) << 3;
-            const tn_u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)oa, 0, 0);
-            const uint32_t e = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(oa + 16), 0, 0);
-            // (the last dword may hold one element past the end: it would be the first one of row kend)
-            d[kk] = make_uint4((int64_t)o >= 2 * left ? 0u : __builtin_amdgcn_alignbit(w.y, w.x, sh), __builtin_amdgcn_alignbit(w.z, w.y, sh),
-                               __builtin_amdgcn_alignbit(w.w, w.z, sh), __builtin_amdgcn_alignbit(e, w.w, sh));
-        }
-    }
-}
+template <bool RAGGED>
+struct TnPatch {
+    tn_u32x4 r[8];
+    uint32_t e[RAGGED ? 4 : 1];
 
-// d[kk] holds 8 m of row k0 + kk; LDS row m gets its 8 k as one 16-byte unit
-__device__ inline uint32_t half_of(const uint4& v, int r) {      // element r (0..7) of the 8 packed in v
-    const uint32_t word = (r >> 1) == 0 ? v.x : (r >> 1) == 1 ? v.y : (r >> 1) == 2 ? v.z : v.w;
-    return (r & 1) ? (word >> 16) : (word & 0xFFFFu);
-}
-__device__ inline void stage_patch(char* lds, int p, const uint4 (&d)[8]) {
-    const int mq = p & 15, kg = p >> 4;
+    // kcount: k rows of the tile; p's patch: rows 8 mq .., k 8 kg ..
+    __device__ __forceinline__ void fetch(const uint16_t* __restrict__ src, int64_t ld, int k0, int kcount, int m0, int kend, int mq, int kg) {
+        const uint32_t pitch = 2u * (uint32_t)ld, o0 = (uint32_t)(8 * kg) * pitch + (uint32_t)(16 * mq);
+        if constexpr (RAGGED) {
+            const int64_t left = (int64_t)min(kend - k0, kcount) * ld - m0;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src + (int64_t)k0 * ld + m0), 0,
+                                                                                (int)((2 * left + 3) & ~3ll), 0x00020000);
 #pragma unroll
-    for (int r = 0; r < 8; ++r) {
-        const uint4 out = make_uint4(half_of(d[0], r) | (half_of(d[1], r) << 16), half_of(d[2], r) | (half_of(d[3], r) << 16),
-                                     half_of(d[4], r) | (half_of(d[5], r) << 16), half_of(d[6], r) | (half_of(d[7], r) << 16));
-        *reinterpret_cast<uint4*>(lds + bf_unit(8 * mq + r, kg)) = out;
+            for (int kk = 0; kk < 8; ++kk) {
+                const uint32_t o = o0 + kk * pitch;
+                r[kk] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(o & ~3u), 0, 0);
+                if (kk & 1) e[kk >> 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(o & ~3u) + 16, 0, 0);
+            }
+        } else {
+            const char* const row = reinterpret_cast<const char*>(src + (int64_t)k0 * ld + m0);
+#pragma unroll
+            for (int kk = 0; kk < 8; ++kk) r[kk] = *reinterpret_cast<const tn_u32x4*>(row + (int64_t)kk * pitch + o0);
+        }
     }
-}
+    // the LDS unit of row j of the patch; valid: k of the patch that exist (the dword that holds the last
+    // element may hold one more, which would be the first one of row kend)
+    __device__ __forceinline__ tn_u32x4 unit(int j, int64_t ld, int valid) const {
+        const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u, sh = (uint32_t)(ld & 1) << 4;
+        const int w = j >> 1;
+        tn_u32x4 o;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            uint32_t odd = r[2 * d + 1][w];
+            if constexpr (RAGGED) {
+                odd = __builtin_amdgcn_alignbit(w < 3 ? r[2 * d + 1][w < 3 ? w + 1 : 0] : e[d], odd, sh);
+                if (j == 0) odd = 2 * d + 1 < valid ? odd : 0u;
+            }
+            o[d] = __builtin_amdgcn_perm(odd, r[2 * d][w], sel);
+        }
+        return o;
+    }
+};
 
 __global__ __launch_bounds__(256) void k_gemm_tn_bf16(const uint16_t* __restrict__ A, int64_t lda,
                                                       const uint16_t* __restrict__ B, int64_t ldb,
@@ -102,14 +106,17 @@ __global__ __launch_bounds__(256) void k_gemm_tn_bf16(const uint16_t* __restrict
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    uint4 rp[8];
-    fetch_patch(src, ld, kbeg, o0, kend, p, rp);
+    TnPatch<true> patch;
+    const int mq = p & 15, kg = p >> 4;
+    patch.fetch(src, ld, kbeg, BKH, o0, kend, mq, kg);
     const int lk = lane >> 5, lm = lane & 31;
     for (int k0 = kbeg; k0 < kend; k0 += BKH) {
         __syncthreads();
-        stage_patch(dst, p, rp);
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            *reinterpret_cast<tn_u32x4*>(dst + bf_unit(8 * mq + j, kg)) = patch.unit(j, ld, kend - k0 - 8 * kg);
         __syncthreads();
-        if (k0 + BKH < kend) fetch_patch(src, ld, k0 + BKH, o0, kend, p, rp);
+        if (k0 + BKH < kend) patch.fetch(src, ld, k0 + BKH, BKH, o0, kend, mq, kg);
 #pragma unroll
         for (int ks = 0; ks < BKH / 8; ks += 2) {          // 16 k per MFMA: units ks + lk
             const bf16x8 a0 = *reinterpret_cast<const bf16x8*>(As + bf_unit(wm + lm, ks + lk));
@@ -962,6 +969,7 @@ void k_gemm_split_n160(const float* __restrict__ A, int64_t lda, const float* __
 // Staging of the next tile is spread over the second half of a step's MFMAs, as there.
 // (Four wavefronts of 128 x 128 with the accumulators in the accumulation half of the
 // register file measured 15 % slower: one wavefront per SIMD leaves every wait exposed.)
+template <bool RAGGED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_tn_bf16_256(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ B, int64_t ldb,
                         float* __restrict__ C, int M, int N, int Kdim, int k_per_split, int64_t split_stride) {
@@ -969,13 +977,13 @@ void k_gemm_tn_bf16_256(const uint16_t* __restrict__ A, int64_t lda, const uint1
     __shared__ __attribute__((aligned(16))) char lds[2 * 4 * PLANE];     // [stage][A k<32, A k>=32, B k<32, B k>=32]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 128;
-    const int gn = N / BN2, ntiles = (M / BM2) * gn, nsplit = (Kdim + k_per_split - 1) / k_per_split;
+    const int gm = (M + BM2 - 1) / BM2, gn = (N + BN2 - 1) / BN2, ntiles = gm * gn, nsplit = (Kdim + k_per_split - 1) / k_per_split;
     const int Q = (ntiles + 7) >> 3;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int split = slot / Q, tile_id = xcd * Q + slot % Q;
     if (tile_id >= ntiles || split >= nsplit) return;
     int mi, ni;
-    tile_coords(tile_id, M / BM2, gn, mi, ni);
+    tile_coords(tile_id, gm, gn, mi, ni);
     const int m0 = mi * BM2, n0 = ni * BN2;
     const int kbeg = split * k_per_split;
     const int kend = min(Kdim, kbeg + k_per_split);
@@ -992,34 +1000,19 @@ void k_gemm_tn_bf16_256(const uint16_t* __restrict__ A, int64_t lda, const uint1
     // h: 0 stages A, 1 stages B; uniform per wavefront, so base and row pitch stay scalar and a
     // load's address is scalar row + per-thread 32-bit offset
     const int h = __builtin_amdgcn_readfirstlane(tid >> 8), p = tid & 255, mq = p & 31, kg = p >> 5;
-    const int64_t pitch = 2 * (h == 0 ? lda : ldb);
-    const char* const sbase = reinterpret_cast<const char*>(h == 0 ? A + m0 : B + n0);
-    const uint32_t voff = (uint32_t)(8 * kg * pitch + 16 * mq);
-    uint4 r[8];
-    auto fetch = [&](int k0) __attribute__((always_inline)) {
-        const char* row = sbase + (int64_t)k0 * pitch;
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) r[kk] = *reinterpret_cast<const uint4*>(row + kk * pitch + voff);
-    };
+    const int64_t ld = h == 0 ? lda : ldb;
+    const uint16_t* const src = h == 0 ? A : B;
+    const int o0 = h == 0 ? m0 : n0;
+    TnPatch<RAGGED> patch;
+    auto fetch = [&](int k0) __attribute__((always_inline)) { patch.fetch(src, ld, k0, KS, o0, kend, mq, kg); };
     const uint32_t wr_plane = (uint32_t)((2 * h + (kg >> 2)) * PLANE);
     uint32_t wr_unit[8];                              // row 8 mq + j, unit kg & 3
 #pragma unroll
     for (int j = 0; j < 8; ++j) wr_unit[j] = wr_plane + bf_unit32(8 * mq + j, kg & 3);
-    // row j of the patch: halfword j of the eight registers, k ascending
-    auto piece = [&](int j) __attribute__((always_inline)) -> uint4 {
-        const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
-        uint32_t o[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) {
-            const uint32_t w0 = u4_at(r[2 * d], j >> 1), w1 = u4_at(r[2 * d + 1], j >> 1);
-            o[d] = __builtin_amdgcn_perm(w1, w0, sel);
-        }
-        return make_uint4(o[0], o[1], o[2], o[3]);
-    };
     const int lk = lane >> 5, lm = lane & 31;
     // one k step (64) on LDS stage buf: four groups (k half, 16-k slice) of eight MFMAs; with STAGE
     // groups 2 and 3 each store four rows of the next tile, one row after every two MFMAs
-    auto step = [&](int buf, auto stage_c, auto fetch_c, int knext) __attribute__((always_inline)) {
+    auto step = [&](int buf, auto stage_c, auto fetch_c, int kstage) __attribute__((always_inline)) {
         constexpr bool STAGE = decltype(stage_c)::value, FETCH = decltype(fetch_c)::value;
         const char* base = lds + buf * 4 * PLANE;
         char* const wr = lds + (buf ^ 1) * 4 * PLANE;
@@ -1040,28 +1033,28 @@ void k_gemm_tn_bf16_256(const uint16_t* __restrict__ A, int64_t lda, const uint1
                     acc[e & 1][e >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[e & 1], b[e >> 1], acc[e & 1][e >> 1], 0, 0, 0);
                 if (STAGE && g >= 2) {
                     const int j = 4 * (g - 2) + c;
-                    *reinterpret_cast<uint4*>(wr + wr_unit[j]) = piece(j);
+                    *reinterpret_cast<tn_u32x4*>(wr + wr_unit[j]) = patch.unit(j, ld, kend - kstage - 8 * kg);
                 }
                 __builtin_amdgcn_sched_barrier(0x124);     // scalar work, global loads and LDS reads may still move
             }
         }
-        if (FETCH) fetch(knext);
+        if (FETCH) fetch(kstage + KS);
     };
     using std::true_type;
     using std::false_type;
 
     fetch(kbeg);
 #pragma unroll
-    for (int j = 0; j < 8; ++j) *reinterpret_cast<uint4*>(lds + wr_unit[j]) = piece(j);
+    for (int j = 0; j < 8; ++j) *reinterpret_cast<tn_u32x4*>(lds + wr_unit[j]) = patch.unit(j, ld, kend - kbeg - 8 * kg);
     if (kbeg + KS < kend) fetch(kbeg + KS);
     __syncthreads();
     int buf = 0, k0 = kbeg;
     for (; k0 + 2 * KS < kend; k0 += KS, buf ^= 1) {
-        step(buf, true_type{}, true_type{}, k0 + 2 * KS);
+        step(buf, true_type{}, true_type{}, k0 + KS);
         __syncthreads();
     }
     if (k0 + KS < kend) {
-        step(buf, true_type{}, false_type{}, 0);
+        step(buf, true_type{}, false_type{}, k0 + KS);
         __syncthreads();
         buf ^= 1;
     }
@@ -1075,7 +1068,7 @@ void k_gemm_tn_bf16_256(const uint16_t* __restrict__ A, int64_t lda, const uint1
             for (int v = 0; v < 16; ++v) {
                 const int m = m0 + wm + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
                 const int n = n0 + wn + j * 32 + lm;
-                Cz[(int64_t)m * N + n] = acc[i][j][v];
+                if (!RAGGED || (m < M && n < N)) Cz[(int64_t)m * N + n] = acc[i][j][v];
             }
 }
 
@@ -1120,33 +1113,41 @@ int sum_split_planes(const float* part, int64_t stride, int nsplit, float* C, in
     return MST_OK;
 }
 
-// Number of k ranges (blockIdx.x) a GEMM of `tiles` output tiles is split into.  A CU holds
-// `wg_per_cu` workgroups; the grid should fill 256 x wg_per_cu places a whole number of
-// times.  Cost of a choice = (k steps per workgroup x step_us + wg_us) x rounds, a last
-// partial round counting `last[]` by quarters of the places it fills, plus the pass that
-// adds the partial outputs.  Constants fitted to timings of the dense gradient at GPT-2
-// small / medium / large shapes (9 % rms error).
-struct SplitModel {
-    int wg_per_cu, bk;
-    double step_us, wg_us, sum_us_per_float, last[3];
+// A plan: workgroup tile, number of k ranges, modelled time in microseconds.
+struct SplitPlan {
+    int tile, nsplit;
+    double us;
 };
-static const SplitModel kSplitBf16 = {3, BKH, 2.08, 3.0, 1.8e-6, {0.69, 0.76, 0.86}};
+static int g_split_tile = 0;              // test hook: 0 = automatic, 128 / 256 / 160 / 192 = that workgroup tile when the shape allows it; 64: streaming bf16 TN
 
-static int pick_nsplit(int64_t tiles, int Kdim, const SplitModel& md, int64_t max_split) {
-    const int64_t places = 256 * md.wg_per_cu;
-    int best = 1;
-    double best_cost = 0.0;
-    const int64_t hi = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(16, max_split), Kdim / 256));
-    for (int ns = 1; ns <= hi; ++ns) {
-        const int64_t n = tiles * ns, full = n / places, rest = n % places;
-        const double steps = (double)cdiv(cdiv(Kdim, ns), md.bk);
-        const double frac = (double)rest / (double)places;
-        const double last = rest == 0 ? 0.0 : frac <= 0.25 ? md.last[0] : frac <= 0.5 ? md.last[1] : frac <= 0.75 ? md.last[2] : 1.0;
-        const double cost = (steps * md.step_us + md.wg_us) * ((double)full + last) +
-                            (ns > 1 ? md.sum_us_per_float * (double)ns * (double)tiles * 128.0 * 128.0 : 0.0);
-        if (best_cost == 0.0 || cost < best_cost) {
-            best_cost = cost;
-            best = ns;
+// Rounds of workgroups one XCD needs for n of them, in times of a workgroup: `full` with all places taken, `lone`
+// with a CU to itself; a last round that leaves places empty lies between.
+double xcd_rounds(int64_t n, int places, int lone_places, double full, double lone) {
+    const int64_t rest = n % places;
+    const double last = rest == 0 ? 0.0 : rest <= lone_places ? lone : lone + (full - lone) * (double)(rest - lone_places) / (double)(places - lone_places);
+    return (double)(n / places) * full + last;
+}
+
+// The bfloat16 dense gradient: the two-stage 256 x 256 kernel, the 128 x 128 one or the streaming one of
+// gemm_exact.hip (64), with the number of k ranges.  Microseconds of a 64-k step (streaming: of a k), of start-up
+// and output in steps (streaming: microseconds) and of the launch fitted to timings of 100 products on MI355X
+// (5-8 % rms error).
+static SplitPlan plan_tn_bf16(int M, int N, int Kdim, int64_t max_split, bool summed) {
+    static const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
+    SplitPlan best{0, 1, 0.0};
+    const bool pinned = g_split_tile == 64 || g_split_tile == 128 || g_split_tile == 256;
+    for (int tile : {64, 128, 256}) {
+        if (pinned && g_split_tile != tile) continue;
+        const int64_t Q = cdiv(cdiv(M, tile) * cdiv(N, tile), 8);
+        for (int ns : cand) {
+            if (ns > 1 && (ns > max_split || Kdim / ns < (tile == 128 ? 256 : 512))) break;
+            const double steps = (double)cdiv(cdiv(Kdim, ns), 64);
+            double us;
+            if (tile == 64) us = 2.6 + xcd_rounds(Q * ns, 32, 0, 0.0059, 0.0054) * 64.0 * steps + (double)cdiv(Q * ns, 32) * 3.2;
+            else if (tile == 128) us = xcd_rounds(Q * ns, 96, 32, 2.51, 1.36) * (steps + 4.0);
+            else us = 0.9 + xcd_rounds(Q * ns, 32, 31, 1.78, 1.44) * (steps + 5.1);
+            if (ns > 1) us += 2.2 + 1.2e-6 * (double)M * (double)N * (summed ? ns + 1.0 : 0.25 * ns);
+            if (best.tile == 0 || us < best.us) best = SplitPlan{tile, ns, us};
         }
     }
     return best;
@@ -1163,14 +1164,10 @@ static int pick_nsplit(int64_t tiles, int Kdim, const SplitModel& md, int64_t ma
 // tile leaves idle), start-up + output 7, 13, 7 and 7 steps.
 // The model reproduces the measured times of the GPT-2 small / large products within 15 % and
 // orders the candidates as measured.
-struct SplitPlan {
-    int tile, nsplit;
-};
 static SplitPlan plan_split(int M, int N, int Kdim, int64_t max_split, bool summed, bool allow128, bool allow256,
                             bool allow160, bool allow192) {
     static const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-    SplitPlan best{0, 1};
-    double best_cost = 0.0;
+    SplitPlan best{0, 1, 0.0};
     for (int tile : {128, 256, 160, 192}) {           // 160, 192: 256 rows x 160 / 192 columns (A m-major only)
         if (tile == 128 ? !allow128 : tile == 256 ? !allow256 : tile == 160 ? !allow160 : !allow192) continue;
         const int tm = tile == 128 ? 128 : 256, tn = tile;
@@ -1179,36 +1176,45 @@ static SplitPlan plan_split(int M, int N, int Kdim, int64_t max_split, bool summ
         if (M % tm != 0 || N % tn != 0 || Kdim % kstep != 0) continue;
         const int64_t Q = cdiv((int64_t)(M / tm) * (N / tn), 8);
         for (int ns : cand) {
-            if (ns > 1 && (ns > max_split || Kdim / ns < 512)) continue;
+            if (ns > 1 && (ns > max_split || Kdim / ns < 512)) break;
             const double steps = (double)cdiv(cdiv(Kdim, ns), kstep);
             double cost = (double)cdiv(Q * ns, places) * (steps + wg_steps) * unit_us;
             // partial outputs: written and read once each, plus the sum's write (4 B at about 4 TB/s);
             // left unsummed they are read sparsely by the caller's gather
             if (ns > 1) cost += 1.0e-6 * (double)M * (double)N * (summed ? ns + 1.0 : 0.25 * ns);
-            if (best.tile == 0 || cost < best_cost) {
-                best_cost = cost;
-                best = SplitPlan{tile, ns};
-            }
+            if (best.tile == 0 || cost < best.us) best = SplitPlan{tile, ns, cost};
         }
     }
     return best;
 }
+// Time of a plan in microseconds, for the choice between these kernels and those of gemm_exact.hip: few
+// workgroups have a CU to themselves and are faster than the constants above (which order the tiles)
+// say.  Fitted to the timings of 200 products, 1 to 40 GFLOP, on MI355X (6-11 % rms error).
+static double split_us(const SplitPlan& plan, int M, int N, int Kdim, bool summed) {
+    const int tm = plan.tile == 128 ? 128 : 256, kstep = plan.tile == 128 ? SPK : 32;
+    const int64_t n = cdiv((int64_t)(M / tm) * (N / plan.tile), 8) * plan.nsplit;
+    const double steps = (double)cdiv(cdiv(Kdim, plan.nsplit), kstep);
+    double us = 0.0;
+    if (plan.tile == 128) us = 2.1 + xcd_rounds(n, 64, 32, 3.19, 1.94) * (steps + 1.5);
+    else if (plan.tile == 256) us = 1.2 + xcd_rounds(n, 32, 31, 2.32, 1.74) * (steps + 4.9);
+    else us = (double)cdiv(n, 32) * 1.43 * (steps + (plan.tile == 160 ? 5.2 : 8.8));
+    return plan.nsplit > 1 ? us + 3.0 + 1.0e-6 * (double)M * (double)N * (summed ? plan.nsplit + 1.0 : 0.25 * plan.nsplit) : us;
+}
 static int g_gemm_fp32_only = 0;          // test hook: 1 = never use the bf16-split kernel
 static int g_last_tile = 0;               // workgroup tile of the last split-kernel launch (128 / 256 / 160), 0: another kernel
 static int g_sched52 = 1;                 // test hook: 0 = never the five-for-two schedule
-static int g_split_tile = 0;              // test hook: 0 = automatic, 128 / 256 / 160 / 192 = that workgroup tile when the shape allows it
 
 int gemm_last_tile() { return g_last_tile; }
 
-int gemm_force_fp32_mfma(int on) {       // 0 automatic; 1, 1064, 1128, 1192 the full-precision kernel; 128 / 256 / 160 / 192: split kernel with that tile
+int gemm_force_fp32_mfma(int on) {       // 0 automatic; 1, 1032, 1064, 1096, 1128 the full-precision kernels; 128 / 256 / 160 / 192: split kernel with that tile; 64: streaming bf16 TN
     if (on == 52 || on == -52) {                    // (the other settings stay as they are)
         g_sched52 = on > 0;
         return MST_OK;
     }
-    const bool exact = on == 1 || on == 1064 || on == 1128 || on == 1192;
+    const bool exact = on == 1 || on == 1032 || on == 1064 || on == 1096 || on == 1128;
     g_gemm_fp32_only = exact ? 1 : 0;
     gemm_exact_tile(exact && on > 1 ? on - 1000 : 0);
-    g_split_tile = (on == 128 || on == 256 || on == 160 || on == 192) ? on : 0;
+    g_split_tile = (on == 128 || on == 256 || on == 160 || on == 192 || on == 64) ? on : 0;
     return MST_OK;
 }
 
@@ -1218,16 +1224,26 @@ static bool split_ok(int M, int N, int Kdim, int64_t lda, int64_t ldb, bool a_km
     return (M % BM == 0 && N % BN == 0) || (!a_kmajor && M % BM2 == 0 && (N % BN3 == 0 || N % 192 == 0));
 }
 
-template <bool AK, bool BKM>
-static int launch_split(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int M, int N, int Kdim,
-                        float* split_ws, int64_t split_ws_floats, int* left_unsummed, hipStream_t s) {
-    const int64_t mn = (int64_t)M * N;
+// The split kernels' plan for an fp32 product, tile 0: the kernels of gemm_exact.hip serve it, because no
+// tile divides it or because its tiles are too few (a chain of k steps on a fraction of the CUs).
+static SplitPlan plan_fp32(GemmKind kind, int M, int N, int Kdim, int64_t max_split, bool summed) {
+    const bool ak = kind == GEMM_TN;
+    if (!split_ok(M, N, Kdim, ak ? M : Kdim, kind == GEMM_NT ? Kdim : N, ak)) return SplitPlan{0, 1, 0.0};
     const int pin = g_split_tile;
-    SplitPlan plan = plan_split(M, N, Kdim, split_ws ? split_ws_floats / mn : 1, left_unsummed == nullptr,
-                                pin == 0 || pin == 128, pin == 0 || pin == 256, !AK && (pin == 0 || pin == 160),
-                                !AK && (pin == 0 || pin == 192));
+    SplitPlan plan = plan_split(M, N, Kdim, max_split, summed, pin == 0 || pin == 128, pin == 0 || pin == 256,
+                                !ak && (pin == 0 || pin == 160), !ak && (pin == 0 || pin == 192));
     if (plan.tile == 0)                               // the pinned tile does not fit this shape: any that does
-        plan = plan_split(M, N, Kdim, split_ws ? split_ws_floats / mn : 1, left_unsummed == nullptr, true, true, !AK, !AK);
+        plan = plan_split(M, N, Kdim, max_split, summed, true, true, !ak, !ak);
+    plan.us = split_us(plan, M, N, Kdim, summed);
+    // (larger products fill the chip on either kernel, and three products per term beat six)
+    if (pin == 0 && (double)M * N * Kdim < 2.0e10 && gemm_exact_us(MST_F32, M, N, Kdim, max_split, summed) < plan.us) plan.tile = 0;
+    return plan;
+}
+
+template <bool AK, bool BKM>
+static int launch_split(const SplitPlan& plan, const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int M, int N,
+                        int Kdim, float* split_ws, int64_t split_ws_floats, int* left_unsummed, hipStream_t s) {
+    const int64_t mn = (int64_t)M * N;
     const int tile = plan.tile, nsplit0 = plan.nsplit;
     g_last_tile = tile;
     const int kstep = tile == 128 ? SPK : SPK2;
@@ -1279,6 +1295,16 @@ static int launch_split(const void* A, int64_t lda, const void* B, int64_t ldb, 
 static bool a16_ok(int M, int N, int Kdim) {
     return !g_gemm_fp32_only && g_split_tile != 128 && M % BM2 == 0 && N % BN2 == 0 && Kdim % SPK2 == 0;
 }
+static double a16_us(int M, int N, int Kdim) {
+    return 3.0 + (double)cdiv(cdiv((int64_t)(M / BM2) * (N / BN2), 8), 32) * (Kdim / 32 + 8.0) * 1.5;
+}
+// Few tiles make this kernel a chain of k steps on as many CUs; the streaming kernels are several times as
+// fast then.  (Outputs of a dozen tiles and a depth of up to 768 stay here: mst_gemm_last_tile reports the
+// tile for them, and a program may have come to rely on it.)
+static bool use_a16(int M, int N, int Kdim) {
+    return a16_ok(M, N, Kdim) && (g_split_tile == 256 || ((int64_t)M * N <= 12 * 65536 && Kdim <= 768) || (double)M * N * Kdim >= 2.0e10 ||
+                                  a16_us(M, N, Kdim) <= gemm_exact_us(MST_BF16, M, N, Kdim, 1, true));
+}
 template <bool BKM>
 static int launch_a16(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int M, int N, int Kdim,
                       int* left_unsummed, hipStream_t s) {
@@ -1290,59 +1316,29 @@ static int launch_a16(const void* A, int64_t lda, const void* B, int64_t ldb, fl
     return MST_OK;
 }
 
-static int launch_tn_bf16(const void* A, const void* B, float* C, int M, int N, int Kdim, float* split_ws,
+static int launch_tn_bf16(const void* Av, const void* Bv, float* C, int M, int N, int Kdim, float* split_ws,
                           int64_t split_ws_floats, int* left_unsummed, hipStream_t s) {
-    const int gm = (int)cdiv(M, BM), gn = (int)cdiv(N, BN);
     const int64_t mn = (int64_t)M * N;
-    if (g_split_tile != 128 && M % BM2 == 0 && N % BN2 == 0 && Kdim % 64 == 0 &&
-        (g_split_tile == 256 || (int64_t)(M / BM2) * (N / BN2) >= 8)) {
-        // whole 256 x 256 tiles: the two-stage kernel; split count from the same per-XCD round model
-        // (a 64-k step takes about 1.3 us, start-up and output of a workgroup about 16 steps)
-        static const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-        const int64_t Q = cdiv((int64_t)(M / BM2) * (N / BN2), 8), max_split = split_ws ? split_ws_floats / mn : 1;
-        int ns_best = 1;
-        double best_cost = 0.0;
-        for (int ns : cand) {
-            if (ns > 1 && (ns > max_split || Kdim / ns < 512)) continue;
-            double cost = (double)cdiv(Q * ns, 32) * ((double)cdiv(cdiv(Kdim, ns), 64) + 16.0) * 1.3;
-            if (ns > 1) cost += 1.0e-6 * (double)mn * (left_unsummed ? 0.25 * ns : ns + 1.0);
-            if (best_cost == 0.0 || cost < best_cost) {
-                best_cost = cost;
-                ns_best = ns;
-            }
-        }
-        const int kps = (int)(cdiv(cdiv(Kdim, ns_best), 64) * 64);
-        const int nsplit = (int)cdiv(Kdim, kps);
-        const unsigned grid = (unsigned)(8 * Q * nsplit);
-        float* dst = nsplit > 1 ? split_ws : C;
-        k_gemm_tn_bf16_256<<<grid, 512, 0, s>>>((const uint16_t*)A, M, (const uint16_t*)B, N, dst, M, N, Kdim, kps, mn);
-        MST_LAUNCH_CHECK();
-        if (left_unsummed) {
-            *left_unsummed = nsplit;
-            return MST_OK;
-        }
-        if (nsplit > 1) {
-            const int rcs = sum_split_planes(split_ws, mn, nsplit, C, mn, s);
-            if (rcs != MST_OK) return rcs;
-        }
-        return MST_OK;
+    const uint16_t *A = (const uint16_t*)Av, *B = (const uint16_t*)Bv;
+    const SplitPlan plan = plan_tn_bf16(M, N, Kdim, split_ws ? split_ws_floats / mn : 1, left_unsummed == nullptr);
+    const int kps = (int)(cdiv(cdiv(Kdim, plan.nsplit), BKH) * BKH), nsplit = (int)cdiv(Kdim, kps);
+    float* const dst = nsplit > 1 ? split_ws : C;
+    if (plan.tile == 64) {
+        const int rc = gemm_stream_tn_bf16(A, B, dst, M, N, Kdim, kps, mn, s);
+        if (rc != MST_OK) return rc;
+    } else if (plan.tile == 128) {
+        k_gemm_tn_bf16<<<dim3(nsplit, (unsigned)cdiv(N, BN), (unsigned)cdiv(M, BM)), 256, 0, s>>>(A, M, B, N, dst, M, N, Kdim, kps, mn);
+    } else {
+        const unsigned grid = (unsigned)(8 * cdiv(cdiv(M, BM2) * cdiv(N, BN2), 8) * nsplit);
+        if (M % BM2 == 0 && N % BN2 == 0 && Kdim % 64 == 0) k_gemm_tn_bf16_256<false><<<grid, 512, 0, s>>>(A, M, B, N, dst, M, N, Kdim, kps, mn);
+        else k_gemm_tn_bf16_256<true><<<grid, 512, 0, s>>>(A, M, B, N, dst, M, N, Kdim, kps, mn);
     }
-    const int nsplit0 = split_ws ? pick_nsplit((int64_t)gm * gn, Kdim, kSplitBf16, split_ws_floats / mn) : 1;
-    const int kps = (int)(cdiv(cdiv(Kdim, nsplit0), BKH) * BKH);
-    const int nsplit = (int)cdiv(Kdim, kps);
-    dim3 grid(nsplit, gn, gm);
-    float* dst = nsplit > 1 ? split_ws : C;
-    k_gemm_tn_bf16<<<grid, 256, 0, s>>>((const uint16_t*)A, M, (const uint16_t*)B, N, dst, M, N, Kdim, kps, mn);
     MST_LAUNCH_CHECK();
     if (left_unsummed) {
         *left_unsummed = nsplit;
         return MST_OK;
     }
-    if (nsplit > 1) {
-        const int rcs = sum_split_planes(split_ws, mn, nsplit, C, mn, s);
-        if (rcs != MST_OK) return rcs;
-    }
-    return MST_OK;
+    return nsplit > 1 ? sum_split_planes(split_ws, mn, nsplit, C, mn, s) : MST_OK;
 }
 
 // TN: C[M x N] = A^T B, A [K x M], B [K x N]          (G = dY^T X)
@@ -1352,29 +1348,32 @@ int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_d
               int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed) {
     const bool ab = a_dt == MST_BF16, bb = b_dt == MST_BF16;
     g_last_tile = 0;
-    switch (kind) {
-        case GEMM_TN:
-            if (ab != bb) return MST_ERR_ARG;
-            if (ab) return launch_tn_bf16(A, B, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
-            if (split_ok(M, N, Kdim, M, N, true))
-                return launch_split<true, true>(A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
-            return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
-        case GEMM_NT:
-            if (bb) return MST_ERR_ARG;
-            if (ab && a16_ok(M, N, Kdim)) return launch_a16<false>(A, Kdim, B, Kdim, C, M, N, Kdim, left_unsummed, s);
-            if (ab) return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
-            if (split_ok(M, N, Kdim, Kdim, Kdim, false))
-                return launch_split<false, false>(A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
-            return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
-        case GEMM_NN:
-            if (bb) return MST_ERR_ARG;
-            if (ab && a16_ok(M, N, Kdim)) return launch_a16<true>(A, Kdim, B, N, C, M, N, Kdim, left_unsummed, s);
-            if (ab) return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
-            if (split_ok(M, N, Kdim, Kdim, N, false))
-                return launch_split<false, true>(A, Kdim, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
-            return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
+    if (kind == GEMM_TN ? ab != bb : bb) return MST_ERR_ARG;
+    if (ab) {
+        if (kind == GEMM_TN) return launch_tn_bf16(A, B, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+        if (use_a16(M, N, Kdim))
+            return kind == GEMM_NT ? launch_a16<false>(A, Kdim, B, Kdim, C, M, N, Kdim, left_unsummed, s)
+                                   : launch_a16<true>(A, Kdim, B, N, C, M, N, Kdim, left_unsummed, s);
+        return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
     }
-    return MST_ERR_ARG;
+    const int64_t max_split = split_ws ? split_ws_floats / ((int64_t)M * N) : 1;
+    const SplitPlan plan = plan_fp32(kind, M, N, Kdim, max_split, left_unsummed == nullptr);
+    if (plan.tile == 0) return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
+    if (kind == GEMM_TN) return launch_split<true, true>(plan, A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+    if (kind == GEMM_NT) return launch_split<false, false>(plan, A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+    return launch_split<false, true>(plan, A, Kdim, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+}
+
+// Modelled time of a product in microseconds, as the kernel choice above would run it.
+double gemm_mfma_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed) {
+    if (a_dt == MST_BF16) {
+        if (kind == GEMM_TN) return plan_tn_bf16(M, N, Kdim, max_split, summed).us;
+        if (use_a16(M, N, Kdim)) return a16_us(M, N, Kdim);
+    } else {
+        const SplitPlan plan = plan_fp32(kind, M, N, Kdim, max_split, summed);
+        if (plan.tile != 0) return plan.us;
+    }
+    return gemm_exact_us(a_dt, M, N, Kdim, max_split, summed);
 }
 
 }  // namespace mst

@@ -1,6 +1,6 @@
 """The dense products of any shape at full fp32 precision (three bfloat16 parts per fp32 operand): Y, dX
-and the dense gradient of a dense layer at the edges of the 64 x 64 and 128 x 128 tiles and of the k steps
-of 32 and 64, with one group of wavefronts per tile and with three, fp32 and bfloat16 activations, and the
+and the dense gradient of a dense layer at the edges of the 32 x 32, 64 x 64 and 128 x 128 tiles and of the k steps
+of 16, 32 and 64, staged through LDS and streamed into registers, fp32 and bfloat16 activations, and the
 bfloat16 dense gradient on rows that are no multiple of anything.  Against the oracle (App. Eq. (1) and its
 gradients) at the precision of fp32 sums, far inside what two parts per operand would reach."""
 import numpy as np
@@ -20,7 +20,7 @@ SHAPES = [(1, 1, 1), (63, 65, 127), (64, 64, 64), (129, 33, 130), (130, 257, 63)
 
 
 @pytest.mark.parametrize("T,I,O", SHAPES)
-@pytest.mark.parametrize("mode", [1064, 1128, 1192])
+@pytest.mark.parametrize("mode", [1032, 1064, 1096, 1128])
 def test_fp32_operands_of_any_shape(T, I, O, mode):
     print("case", T, I, O, mode, flush=True)
     X, dY = synth.make_activations(61, 2, T, I, O)
@@ -47,7 +47,7 @@ def test_fp32_operands_of_any_shape(T, I, O, mode):
 
 
 @pytest.mark.parametrize("T,I,O", SHAPES)
-@pytest.mark.parametrize("mode", [1064, 1128, 1192])
+@pytest.mark.parametrize("mode", [1032, 1064, 1096, 1128])
 def test_bfloat16_activations_of_any_shape(T, I, O, mode):
     print("case", T, I, O, mode, flush=True)
     Xf, dYf, xb, yb = synth.make_activations(62, 2, T, I, O, "bf16")
@@ -56,14 +56,29 @@ def test_bfloat16_activations_of_any_shape(T, I, O, mode):
     M = np.ones((O, I), np.uint8)
     rig = Rig(W, M, T, cap=O * I)
     rig.layer.set_path(mst.MST_PATH_DENSE)
-    G = torch.full((O, I), float("nan"), dtype=torch.float32, device=DEV)
     try:
         mst.mst_gemm_force_fp32_mfma(mode)
         Y, dX = rig.fwd(xb.view(np.int16), mst.MST_BF16), rig.bwd_input(yb.view(np.int16), mst.MST_BF16)
     finally:
         mst.mst_gemm_force_fp32_mfma(0)
-    mst.mst_dense_grad(dev(yb.view(np.int16)), dev(xb.view(np.int16)), G, T, O, I, mst.MST_BF16, rig.ws)
-    torch.cuda.synchronize()
     assert rel_err(Y, opr.fc_fwd(Xf, W, M)) <= FP32
     assert rel_err(dX, opr.fc_bwd_input(dYf, W, M)) <= FP32
-    assert rel_err(G.cpu().numpy(), opr.dense_grad(dYf, Xf)) <= FP32
+
+
+@pytest.mark.parametrize("T,I,O", SHAPES + [(1027, 513, 255), (1984, 257, 320)])
+@pytest.mark.parametrize("mode", [64, 128, 256])
+def test_bfloat16_dense_gradient_of_any_shape(T, I, O, mode):
+    print("case", T, I, O, mode, flush=True)
+    Xf, dYf, xb, yb = synth.make_activations(62, 2, T, I, O, "bf16")
+    X, dY = dev(xb.view(np.int16)), dev(yb.view(np.int16))
+    ws = torch.empty(16 * O * I * 4 + 256, dtype=torch.uint8, device=DEV)
+    ref = opr.dense_grad(dYf, Xf)
+    try:
+        mst.mst_gemm_force_fp32_mfma(mode)
+        for area in (ws, None):                              # with room to split the token range, and without
+            G = torch.full((O, I), float("nan"), dtype=torch.float32, device=DEV)
+            mst.mst_dense_grad(dY, X, G, T, O, I, mst.MST_BF16, area)
+            torch.cuda.synchronize()
+            assert rel_err(G.cpu().numpy(), ref) <= FP32
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
