@@ -149,17 +149,32 @@ def _check(fn: str, code: int):
 
 def _ptr(t) -> int:
     """Device (or host) address of a torch tensor / raw int address / None."""
-    if t is None:
-        return 0
-    if isinstance(t, int):
-        return t
-    return t.data_ptr()
+    try:
+        return t.data_ptr()
+    except AttributeError:
+        return 0 if t is None else int(t)
+
+
+_current = None
+
+
+def _current_stream_function():
+    """() -> handle of the calling thread's current stream.  A small call takes 3 us on the host; through the
+    Stream object that torch.cuda.current_stream() makes, the handle alone takes another 2.7."""
+    import torch
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    torch.cuda.current_stream()                      # (initialises the device)
+    return lambda: raw(device())
 
 
 def _stream(stream) -> int:
+    global _current
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _current is None:
+            _current = _current_stream_function()
+        return _current()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -217,6 +232,7 @@ class Layer:
         h = C.c_void_p()
         _check("mst_layer_create", lib().mst_layer_create(C.byref(h), O, I, nnz_capacity, self.buf.data_ptr(), nbytes))
         self.h = h
+        self._base, self._f32 = self.buf.data_ptr(), self.buf[:nbytes & ~3].view(torch.float32)
         self._destroy = lib().mst_layer_destroy      # kept for __del__ at interpreter shutdown
 
     def close(self):
@@ -239,11 +255,10 @@ class Layer:
 
     def values(self):
         """fp32 torch view (no copy) of the active weights in ascending flat-index order."""
-        import torch
         p, n = C.c_void_p(), C.c_int64()
         _check("mst_layer_values", lib().mst_layer_values(self.h, C.byref(p), C.byref(n)))
-        off = p.value - self.buf.data_ptr()
-        return self.buf[off: off + 4 * n.value].view(torch.float32)
+        off = (p.value - self._base) >> 2
+        return self._f32[off: off + n.value]
 
     def sync_values(self, stream=None):
         _check("mst_layer_sync_values", lib().mst_layer_sync_values(self.h, _stream(stream)))

@@ -614,9 +614,16 @@ __global__ __launch_bounds__(256) void k_sync_views(const float* __restrict__ va
                              uint2* __restrict__ ent_r,
                              const int* __restrict__ ptr_c, int64_t nseg_c, const int* __restrict__ perm_c,
                              uint2* __restrict__ ent_c, const int* __restrict__ heavy, const int* __restrict__ rowptr,
-                             const int* __restrict__ flat, int I, float* __restrict__ Hd) {
+                             const int* __restrict__ flat, int I, float* __restrict__ Hd, unsigned heavy_blocks,
+                             float* __restrict__ Wd, int64_t nnz) {
     if (blockIdx.x >= row_blocks + col_blocks) {
-        heavy_fill_row((int)(blockIdx.x - row_blocks - col_blocks), heavy, rowptr, flat, vals, I, Hd);
+        const unsigned b = blockIdx.x - row_blocks - col_blocks;
+        if (b < heavy_blocks) {
+            heavy_fill_row((int)b, heavy, rowptr, flat, vals, I, Hd);
+        } else {
+            const int64_t k = (int64_t)(b - heavy_blocks) * 256 + threadIdx.x;
+            if (k < nnz) Wd[flat[k]] = vals[k];
+        }
         return;
     }
     const bool col = blockIdx.x >= row_blocks;
@@ -758,16 +765,18 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
     return MST_OK;
 }
 
-// new values into the entries of the row view (and the dense rows beside it) and / or of the col view
-static int refresh_views(const mst_layer* L, bool row, bool col, hipStream_t s) {
-    if (L->nnz == 0 || (!row && !col)) return MST_OK;
+// new values into the entries of the row view (and the dense rows beside it) and / or of the col view, and into
+// a dense copy that is zero at every inactive position: one launch
+static int refresh_views(const mst_layer* L, bool row, bool col, bool dense, hipStream_t s) {
+    if (L->nnz == 0 || (!row && !col && !dense)) return MST_OK;
     const View &r = L->row, &c = L->col;
     // about 1.5 slots per entry, four slots per thread; the kernel strides over whatever there is
     const unsigned nb = (unsigned)std::min<int64_t>(cdiv(L->nnz * 3 / 2 + 1, 1024), 4096);
     const unsigned rb = row ? nb : 0u, cb = col ? nb : 0u;
-    k_sync_views<<<rb + cb + (row && L->heavy_on ? HEAVY_MAX : 0), 256, 0, s>>>(
+    const unsigned hb = row && L->heavy_on ? HEAVY_MAX : 0u, db = dense ? (unsigned)cdiv(L->nnz, 256) : 0u;
+    k_sync_views<<<rb + cb + hb + db, 256, 0, s>>>(
         L->vals, rb, cb, r.ptr, r.nseg, r.perm, reinterpret_cast<uint2*>(r.ent), c.ptr, c.nseg, c.perm,
-        reinterpret_cast<uint2*>(c.ent), L->heavy, L->rowptr, L->flat, L->I, L->Hd);
+        reinterpret_cast<uint2*>(c.ent), L->heavy, L->rowptr, L->flat, L->I, L->Hd, hb, L->Wd, L->nnz);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
@@ -775,7 +784,7 @@ static int refresh_views(const mst_layer* L, bool row, bool col, hipStream_t s) 
 // A product is about to walk these (built) views: entries that missed a change of the values take it now.
 int ensure_fresh(const mst_layer* Lc, bool row, bool col, hipStream_t s) {
     mst_layer* L = const_cast<mst_layer*>(Lc);       // caches of vals[], not layer state
-    const int rc = refresh_views(L, row && L->row_stale, col && L->col_stale, s);
+    const int rc = refresh_views(L, row && L->row_stale, col && L->col_stale, false, s);
     if (rc != MST_OK) return rc;
     if (row) { L->row_walked = true; L->row_stale = false; }
     if (col) { L->col_walked = true; L->col_stale = false; }
@@ -925,17 +934,13 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     hipStream_t s = (hipStream_t)stream;
     // A dense copy that is in use (zero at every inactive position) takes the new values now rather
     // than at the next product, so that products recorded into a graph never see stale weights.
-    if (L->Wd_zeros && L->nnz > 0) {
-        k_scatter_dense<<<(unsigned)cdiv(L->nnz, 256), 256, 0, s>>>(L->vals, L->flat, L->nnz, L->Wd);
-        MST_LAUNCH_CHECK();
-        L->Wd_valid = true;
-    } else {
-        L->Wd_valid = false;
+    const bool dense = L->Wd_zeros && L->nnz > 0, views = L->nnz > 0 && L->views_valid;   // unbuilt views take the values when they are built
+    L->Wd_valid = dense;
+    if (views) {
+        L->row_stale |= !L->row_walked;
+        L->col_stale |= !L->col_walked;
     }
-    if (L->nnz == 0 || !L->views_valid) return MST_OK;     // unbuilt views take the values when they are built
-    L->row_stale |= !L->row_walked;
-    L->col_stale |= !L->col_walked;
-    return refresh_views(L, L->row_walked, L->col_walked, s);
+    return refresh_views(L, views && L->row_walked, views && L->col_walked, dense, s);
 }
 
 int mst_layer_indices(const mst_layer_t* L, int32_t* flat_dev, mst_stream_t stream) {
