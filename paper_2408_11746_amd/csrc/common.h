@@ -1,6 +1,7 @@
 // Internal declarations shared by the translation units of libmst_hip.so.
 #pragma once
 
+#include <atomic>
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
@@ -106,9 +107,10 @@ struct mst_layer {
     bool row_stale = false, col_stale = false;
     int hint_T = 0;            // batch size and activation type of the last product call (0: none yet)
     int hint_act = 0;
+    std::atomic<uint64_t> choice{0};   // sparse-or-dense choices at the last batch size and type (see remembered(); 0: none)
     mst::View row;             // S = W   [O x I], used by fwd (and bwd_weight)
     mst::View col;             // S = W^T [I x O], used by bwd_input
-    int* sddmm_view = nullptr; // device flag: view that drives bwd_weight (0 row, 1 col), set when the views are built
+    unsigned long long* walk_cost = nullptr;   // device: cost of the row and of the col view for bwd_weight (k_view_ptr)
     // Heavy rows (see heavy.hip): device list [0] = count, [1 + j] = row; Hd [HEAVY_MAX x I] their dense weights.
     // Both follow the views: written when they are built, Hd again whenever the values change.
     int* heavy = nullptr;

@@ -38,62 +38,71 @@ View view_shape(int R, int K, int64_t cap) {
     return v;
 }
 
-// Measured cross-overs (GPT-2 small / medium / large layer shapes).  With fp32 activations the
-// dense products run on the bf16 matrix cores (operands split hi + lo) at 250-360 TFLOP/s and
-// cost the same at every density; the sparse kernels cost about in proportion to nnz.  At
-// T >= 2048 the two meet at a density of 0.045-0.06 for Y and dX and at 0.03-0.04 for the
-// weight gradient; short batches fill the matrix cores badly and meet at about 0.15 (there the
-// one-call backward, both gradients from one walk, is also ahead of two separate products).
-// With bfloat16 activations on whole 256 x 256 tiles Y and dX take two bf16 products per term
-// (490 TFLOP/s at the GPT-2-medium shapes) and meet the sparse kernels at 0.042-0.05; other
-// shapes run on the fp32 MFMA kernel (cross-over 0.30).  The bfloat16 weight gradient has both
-// operands in bfloat16 (cross-over 0.045).
+// Sparse or dense.  The dense products cost the same at every density, the sparse ones about in proportion to
+// nnz.  Large batches on whole tiles run at rates that hardly depend on the shape, and the two meet at
+// densities that do not either (measured at GPT-2 small / medium / large layer shapes, T >= 2048): fp32 Y and
+// dX 0.065-0.085, weight gradient 0.04-0.06, both gradients from one walk against two dense products
+// 0.075-0.105; bfloat16 0.05 at T = 16384 and 0.07-0.1 at shorter batches, below 0.03, and 0.03-0.04.  Everywhere else the
+// modelled times of the two are compared up to a density of 0.30 (dense from there on): partial tiles and few workgroups move the line anywhere
+// between 0.03 and 0.3 (at 115 shapes and densities the choice is within 1 to 2 % of the better one, where a line at
+// 0.30 lost 12 to 37 %).
+static bool whole_tiles(const mst_layer* L, mst_dtype act, int T) {
+    const int tile = act == MST_BF16 ? 256 : 128;
+    return T >= 2048 && T % tile == 0 && L->O % tile == 0 && L->I % tile == 0;
+}
+static bool mostly_dense(const mst_layer* L) { return (double)L->nnz > 0.30 * (double)L->N; }
+static double dense_wgrad_us(const mst_layer* L, mst_dtype act, int T) {      // the sum of the k ranges is part of the gather
+    return 3.0 + gemm_mfma_us(GEMM_TN, act, L->O, L->I, T, GEMM_WS_SPLITS, false);
+}
+
+// The models take a microsecond of host time, so the answers for the last (T, type) are kept with the layer
+// until its active set changes: bits 0-2 known, 3-5 the answers, 6 the type, 8.. T.
+template <typename F>
+static bool remembered(const mst_layer* L, int which, mst_dtype act, int T, F&& decide) {
+    std::atomic<uint64_t>& word = const_cast<mst_layer*>(L)->choice;
+    const uint64_t key = (uint64_t)T << 8 | (uint64_t)(act == MST_BF16) << 6, w = word.load(std::memory_order_relaxed);
+    const bool mine = (w & ~(uint64_t)0x3F) == key;
+    if (mine && (w >> which & 1)) return w >> (3 + which) & 1;
+    const bool yes = decide();
+    word.store((mine ? w : key) | (uint64_t)1 << which | (uint64_t)yes << (3 + which), std::memory_order_relaxed);
+    return yes;
+}
+
 bool use_dense_path(const mst_layer* L, mst_dtype act, int T) {
     if (L->path == MST_PATH_DENSE) return true;
     if (L->path == MST_PATH_SPARSE) return false;
-    double thr;
-    if (act == MST_BF16) {
-        const bool tiles = T % 256 == 0 && L->O % 256 == 0 && L->I % 256 == 0;
-        thr = tiles && T >= 2048 ? 0.045 : 0.30;
-    } else {
-        // the split kernels need whole 128-tiles (and a depth that is a multiple of 64); other shapes
-        // run on the fp32 MFMA kernel, a third as fast
-        const bool tiles = T % 128 == 0 && L->O % 128 == 0 && L->I % 128 == 0;
-        thr = !tiles ? 0.30 : T >= 2048 ? 0.055 : 0.15;
-    }
-    return (double)L->nnz > thr * (double)L->N;
+    if (whole_tiles(L, act, T)) return (double)L->nnz > (act == MST_F32 ? 0.075 : T >= 8192 ? 0.045 : 0.065) * (double)L->N;
+    if (mostly_dense(L)) return true;
+    return remembered(L, 0, act, T, [&] {
+        return walk_us(L, WALK_FWD, T) + walk_us(L, WALK_BWD_INPUT, T) >
+               gemm_mfma_us(GEMM_NT, act, T, L->O, L->I, 1, true) + gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, 1, true);
+    });
 }
 
-// The one-call backward has a third choice, the shared walk, and it moves the cross-over: against the
-// two dense contractions it wins up to densities of 0.065-0.11 with fp32 activations (GPT-2 small /
-// large layer shapes, T >= 8192; a sparse dX beside a dense dW is never the fastest), and only up to
-// 0.03 with bfloat16 activations, whose dense weight gradient is a single bf16 product.  Elsewhere the
-// thresholds of the separate calls coincide and apply.
+// The one-call backward: one walk for both gradients, or the two dense products (a sparse dX beside a
+// dense dW is never the fastest).
 bool use_fused_backward(const mst_layer* L, mst_dtype act, int T) {
     if (L->path == MST_PATH_DENSE) return false;
     if (L->path == MST_PATH_SPARSE) return true;
-    double thr;
-    if (act == MST_BF16) {
-        const bool tiles = T % 256 == 0 && L->O % 256 == 0 && L->I % 256 == 0;
-        thr = tiles && T >= 2048 ? 0.03 : 0.30;
-    } else {
-        const bool tiles = T % 128 == 0 && L->O % 128 == 0 && L->I % 128 == 0;
-        thr = !tiles ? 0.30 : T >= 2048 ? 0.07 : 0.15;
-    }
-    return (double)L->nnz <= thr * (double)L->N;
+    if (whole_tiles(L, act, T)) return (double)L->nnz <= (act == MST_F32 ? 0.085 : 0.035) * (double)L->N;
+    if (mostly_dense(L)) return false;
+    return remembered(L, 1, act, T, [&] {
+        return walk_us(L, WALK_BWD, T) <= gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, GEMM_WS_SPLITS * L->N / ((int64_t)T * L->I), true) +
+                                              dense_wgrad_us(L, act, T);
+    });
 }
 
 bool use_dense_weight_grad(const mst_layer* L, mst_dtype act, int T) {
     if (L->path == MST_PATH_DENSE) return true;
     if (L->path == MST_PATH_SPARSE) return false;
-    const bool tiles = act == MST_BF16 || (T % 64 == 0 && L->O % 128 == 0 && L->I % 128 == 0);   // (the bf16 kernels take any shape)
-    const double thr = act == MST_BF16 ? (T >= 2048 ? 0.045 : 0.30) : !tiles ? 0.30 : T >= 2048 ? 0.035 : 0.15;
-    return (double)L->nnz > thr * (double)L->N;
+    if (whole_tiles(L, act, T)) return (double)L->nnz > (act == MST_F32 ? 0.05 : 0.03) * (double)L->N;
+    if (mostly_dense(L)) return true;
+    return remembered(L, 2, act, T, [&] { return walk_us(L, WALK_BWD_WEIGHT, T) > dense_wgrad_us(L, act, T); });
 }
 
 struct LayerCarve {
     size_t mask, vals, flat, rowptr, Wd;
-    size_t rptr, rent, rperm, rmap, rpos, cptr, cent, cperm, cmap, cpos, choice, heavy, Hd;
+    size_t rptr, rent, rperm, rmap, rpos, cptr, cent, cperm, cmap, cpos, cost, heavy, Hd;
     size_t total;
 };
 
@@ -118,7 +127,7 @@ static LayerCarve carve_layer(int O, int I, int64_t cap) {
     c.cperm = take((size_t)k.cap_pairs * OCT * 8);
     c.cmap = take((size_t)k.NBpad * RB * 4);
     c.cpos = take((size_t)k.NBpad * RB * 4);
-    c.choice = take(16);
+    c.cost = take(16);
     c.heavy = take((size_t)(HEAVY_MAX + 2) * 4);
     c.Hd = take((size_t)HEAVY_MAX * I * 4);
     c.total = off;
@@ -335,16 +344,13 @@ __global__ __launch_bounds__(1024) void k_scan_excl(const int* in, int* out, int
 
 // One block does what follows the segment lengths of a view: (row view only) the canonical row
 // pointers from the per-row counts; the first pair of every octet segment; the view's cost
-// for the weight gradient -- the wavefronts of a workgroup take one octet of a block each and wait at
-// every chunk for the longest, so a view costs the sum over (chunk, block) of the most pairs of an
-// octet -- and, when the other view's cost is known (`choice` not null), the view that drives the
-// weight gradient: the one with the clearly smaller cost, else the one with more rows.
+// for the weight gradient, which either view can drive -- the wavefronts of a workgroup take one
+// octet of a block each and wait at every chunk for the longest, so a view costs the sum over
+// (chunk, block) of the most pairs of an octet.
 __global__ __launch_bounds__(1024) void k_view_ptr(const int* __restrict__ rowcnt, int* __restrict__ rowptr, int nrows,
                                                    const int* __restrict__ qlen, int NBpad, int NB, int nchunk,
                                                    int64_t nseg, int* __restrict__ ptr,
-                                                   unsigned long long* __restrict__ cost_mine,
-                                                   const unsigned long long* __restrict__ cost_row, int prefer_col,
-                                                   int* __restrict__ choice, const int* __restrict__ heavy) {
+                                                   unsigned long long* __restrict__ cost, const int* __restrict__ heavy) {
     __shared__ int wsum[16];
     __shared__ unsigned long long cost_s;
     if (rowcnt) block_scan_excl(rowcnt, rowptr, nrows, wsum);
@@ -361,17 +367,8 @@ __global__ __launch_bounds__(1024) void k_view_ptr(const int* __restrict__ rowcn
     }
     if (mine) atomicAdd(&cost_s, mine);
     __syncthreads();
-    if (threadIdx.x == 0) {
-        // a row view that leaves heavy rows out cannot drive the weight gradient
-        *cost_mine = (heavy && heavy[0] > 0) ? (1ull << 50) : cost_s;
-        if (choice) {
-            const unsigned long long pr = *cost_row, pc = cost_s;
-            int ch = prefer_col;
-            if (prefer_col && pr * 10 < pc * 9) ch = 0;
-            if (!prefer_col && pc * 10 < pr * 9) ch = 1;
-            *choice = ch;
-        }
-    }
+    // (a row view that leaves heavy rows out cannot drive the weight gradient)
+    if (threadIdx.x == 0) *cost = (heavy && heavy[0] > 0) ? (1ull << 50) : cost_s;
 }
 
 // entry slot (as index into ent viewed as uint2[], and into perm) of step j of a row
@@ -675,11 +672,9 @@ int fill_u32(void* dst, uint32_t value, int64_t n_words, hipStream_t s) {
 }
 
 // One view: count per (row, sub-chunk) -> ranking of every block's rows with the segments' lengths ->
-// pointers of the octet segments (with the view's cost for the weight gradient and, for the second
-// view, the choice of the driving view) -> ordered compaction.  Four launches; nothing is cleared beforehand:
+// pointers of the octet segments (with the view's cost for the weight gradient) -> ordered compaction.  Four launches; nothing is cleared beforehand:
 // the count kernels write the padding rows' zero counts and the fill kernels their own padding.
-static int build_one_view(View& v, bool row_view, const mst_layer* L, const float* Wsrc,
-                          const Workspace& ws, unsigned long long* cost, hipStream_t s) {
+static int build_one_view(View& v, bool row_view, const mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_t s) {
     const int O = L->O, I = L->I;
     const int Rpad = v.NBpad * RB, nsub = v.nsub();
     if (row_view) {
@@ -697,8 +692,7 @@ static int build_one_view(View& v, bool row_view, const mst_layer* L, const floa
     k_block_rank<<<(unsigned)v.NBpad, RB, 0, s>>>(ws.segcnt, v.msub, v.nchunk, Rpad, v.NBpad, v.rowmap, v.rowpos, ws.qlen);
     MST_LAUNCH_CHECK();
     k_view_ptr<<<1, 1024, 0, s>>>(row_view ? ws.rowcnt : nullptr, L->rowptr, O, ws.qlen, v.NBpad, v.NB, v.nchunk, v.nseg,
-                                  v.ptr, cost + (row_view ? 0 : 1), cost, L->I > L->O ? 1 : 0,
-                                  row_view ? nullptr : L->sddmm_view, row_view && L->heavy_on ? L->heavy : nullptr);
+                                  v.ptr, L->walk_cost + (row_view ? 0 : 1), row_view && L->heavy_on ? L->heavy : nullptr);
     MST_LAUNCH_CHECK();
     if (row_view) {
         const int nrows = v.NB * RB;
@@ -723,14 +717,12 @@ static int build_one_view(View& v, bool row_view, const mst_layer* L, const floa
 
 // Rebuilds vals / flat / rowptr and both views from the layer's mask and a dense weight
 // array (read at the active positions only).  The col view needs the canonical indices the
-// row view pass writes to ws.cidx; its pointer kernel also names the view that drives the
-// weight gradient (either can: the product is symmetric in its dense operands).
+// row view pass writes to ws.cidx.
 int build_views(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_t s, bool keep_dense_copy) {
-    unsigned long long* cost = reinterpret_cast<unsigned long long*>(ws.sel_state);
     L->views_valid = false;
-    int rc = build_one_view(L->row, true, L, Wsrc, ws, cost, s);
+    int rc = build_one_view(L->row, true, L, Wsrc, ws, s);
     if (rc != MST_OK) return rc;
-    rc = build_one_view(L->col, false, L, Wsrc, ws, cost, s);
+    rc = build_one_view(L->col, false, L, Wsrc, ws, s);
     if (rc != MST_OK) return rc;
     L->views_valid = true;
     L->row_walked = L->col_walked = L->row_stale = L->col_stale = false;
@@ -845,7 +837,7 @@ int mst_layer_create(mst_layer_t** out, int O, int I, int64_t nnz_capacity, void
     L->flat = (int*)(b + c.flat);
     L->rowptr = (int*)(b + c.rowptr);
     L->Wd = (float*)(b + c.Wd);
-    L->sddmm_view = (int*)(b + c.choice);
+    L->walk_cost = (unsigned long long*)(b + c.cost);
     L->heavy = (int*)(b + c.heavy);
     L->Hd = (float*)(b + c.Hd);
     auto init_view = [&](View& v, int R, int K, size_t optr, size_t oent, size_t operm, size_t omap, size_t opos) {
@@ -882,6 +874,7 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
     if ((int64_t)total > L->cap) return MST_ERR_STATE;
     MST_HIP(hipMemcpyAsync(L->mask, M_dev, (size_t)L->N, hipMemcpyDeviceToDevice, s));
     L->nnz = total;
+    L->choice.store(0, std::memory_order_relaxed);
     L->built = false;                                   // a failed rebuild leaves no usable layer
     // Heavy rows (heavy.hip).  The dense pass costs a launch after every sparse forward, a read of
     // X and T scattered stores per heavy row: a layer of less than 2^20 positions does not earn

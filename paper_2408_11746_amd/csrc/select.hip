@@ -636,8 +636,10 @@ int mask_update_device(mst_layer* L, const float* G, const mst_update_stats& st,
     // are rebuilt; otherwise they go to the workspace and both index views are rebuilt from them.
     const int64_t nnz_before = L->nnz;
     L->nnz = st.nnz_after;
+    L->choice.store(0, std::memory_order_relaxed);
     const bool with_views = views_wanted(L);
     L->nnz = nnz_before;
+    L->choice.store(0, std::memory_order_relaxed);
     float* const Wnew = with_views ? ws.Wd : L->Wd;
     if (!with_views && !L->Wd_zeros && (rc = fill_u32(L->Wd, 0u, N, s)) != MST_OK) return rc;
     uint64_t* st0 = ws.sel_state;
@@ -680,6 +682,7 @@ int mask_update_device(mst_layer* L, const float* G, const mst_update_stats& st,
         MST_LAUNCH_CHECK();
     }
     L->nnz = st.nnz_after;
+    L->choice.store(0, std::memory_order_relaxed);
     if (with_views) return build_views(L, ws.Wd, ws, s);
     L->Wd_valid = L->Wd_zeros = true;
     return build_canonical(L, L->Wd, ws, s);

@@ -69,38 +69,53 @@ struct WalkArgs {
     int chunks_per_split;        // blockIdx.y takes a range of chunks
 };
 
+// Which view drives the weight gradient: each one's cost as counted when it was built (the host never
+// reads it back) times the time of a unit of it at this batch size and launch shape.
+struct WalkDrive {
+    const unsigned long long* cost;    // [2]: row view, col view
+    float row_unit, col_unit;
+};
+__device__ inline bool drive_by_col(const WalkDrive& d) {
+    typedef const __attribute__((address_space(4))) unsigned long long const_u64;
+    const const_u64* c = (const const_u64*)d.cost;
+    return (float)c[1] * d.col_unit < (float)c[0] * d.row_unit;
+}
+
 // one translation unit per activation type (walk_f32.hip, walk_bf16.hip); q = row blocks per workgroup
 int walk_out_f32(int q, const WalkSide& sd, const WalkArgs& wa, hipStream_t s);                       // q = 1 .. 6
 int walk_out_bf16(int q, const WalkSide& sd, const WalkArgs& wa, hipStream_t s);
 int walk_both_f32(int q, const WalkSide& sd, const WalkArgs& wa, int nsplit, hipStream_t s);          // q = 1 .. 4
 int walk_both_bf16(int q, const WalkSide& sd, const WalkArgs& wa, int nsplit, hipStream_t s);
-int walk_dw_f32(int q, const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const int* choice, hipStream_t s);   // q = 1 .. 6
-int walk_dw_bf16(int q, const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const int* choice, hipStream_t s);
+int walk_dw_f32(int q, const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const WalkDrive& drive, hipStream_t s);   // q = 1 .. 6
+int walk_dw_bf16(int q, const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const WalkDrive& drive, hipStream_t s);
 
-// raw buffer of `bytes` bytes from p: reads past the end give zeros (per dword) without an access
+// raw buffer of `bytes` bytes from p, rounded up to a dword: reads past the end give zeros (per dword)
+// without an access
 __device__ inline __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)((bytes + 3) & ~3u), 0x00020000);
 }
-// Four consecutive elements as fp32.  The hardware wants dword-aligned addresses: rows of bfloat16 of an
-// odd length (`even` false) are read element by element.
+// Four consecutive elements as fp32, zeros from `end` (bytes) on if the first is there.  The hardware wants
+// dword-aligned addresses: where rows of bfloat16 have an odd length (`even` false), every other row starts in
+// the middle of a dword and is shifted into place, and the last dword may hold one element past the end.
+// (Element by element such a layer's products took two to four times as long.)
 template <typename TIn>
-__device__ inline float4 buffer_quad(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off, bool even);
+__device__ inline float4 buffer_quad(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off, uint32_t end, bool even);
 template <>
-__device__ inline float4 buffer_quad<float>(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off, bool) {
+__device__ inline float4 buffer_quad<float>(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off, uint32_t, bool) {
     const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)byte_off, 0, 0);
     return make_float4(__uint_as_float(v.x), __uint_as_float(v.y), __uint_as_float(v.z), __uint_as_float(v.w));
 }
 template <>
-__device__ inline float4 buffer_quad<uint16_t>(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off, bool even) {
+__device__ inline float4 buffer_quad<uint16_t>(__amdgpu_buffer_rsrc_t rs, uint32_t byte_off, uint32_t end, bool even) {
     u32x2 u;
     if (even) {
         u = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)byte_off, 0, 0);
     } else {
-        uint32_t h[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) h[j] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)byte_off + 2 * j, 0, 0);
-        u.x = h[0] | (h[1] << 16);
-        u.y = h[2] | (h[3] << 16);
+        const uint32_t sh = (byte_off & 2u) << 3;
+        const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(byte_off & ~3u), 0, 0);
+        const uint32_t e = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(byte_off & ~3u) + 8, 0, 0);
+        u.x = byte_off < end ? __builtin_amdgcn_alignbit(w.y, w.x, sh) : 0u;
+        u.y = __builtin_amdgcn_alignbit(e, w.y, sh);
     }
     return make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
                        __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u));
@@ -209,14 +224,15 @@ __device__ __forceinline__ void walk_body(const WalkSide& sd, const WalkArgs& wa
         int tq, kq0;
         item_of(tq, kq0);
         const uint32_t ld = (uint32_t)K * (uint32_t)sizeof(TIn);
-        const __amdgpu_buffer_rsrc_t rs = buffer_of(A + (int64_t)t0 * K + c * KC, rows * ld - (uint32_t)(c * KC) * (uint32_t)sizeof(TIn));
+        const uint32_t end = rows * ld - (uint32_t)(c * KC) * (uint32_t)sizeof(TIn);
+        const __amdgpu_buffer_rsrc_t rs = buffer_of(A + (int64_t)t0 * K + c * KC, end);
         const uint32_t o0 = (uint32_t)(4 * tq) * ld + (uint32_t)(4 * kq0) * (uint32_t)sizeof(TIn);
 #pragma unroll
         for (int i = lo; i < hi; ++i) {
             // (items past the chunk: an offset past the end, zeros without an access)
             const uint32_t oi = kq0 + 64 * i < nkq ? o0 + (uint32_t)(256 * i) * (uint32_t)sizeof(TIn) : 0xC0000000u;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) st[i][r] = buffer_quad<TIn>(rs, oi + (uint32_t)r * ld, (K & 1) == 0);
+            for (int r = 0; r < 4; ++r) st[i][r] = buffer_quad<TIn>(rs, oi + (uint32_t)r * ld, end, (K & 1) == 0);
         }
     };
     auto put = [&](auto lo, auto hi) __attribute__((always_inline)) {
@@ -250,12 +266,13 @@ __device__ __forceinline__ void walk_body(const WalkSide& sd, const WalkArgs& wa
             const int row0 = (b0 + q) * RB;
             char* half = lds + (q & 1) * STAGE_BYTES;
             if (row0 < R) {
-                const __amdgpu_buffer_rsrc_t rs = buffer_of(B + (int64_t)t0 * R + row0, rows * ldb - (uint32_t)row0 * (uint32_t)sizeof(TIn));
+                const uint32_t end = rows * ldb - (uint32_t)row0 * (uint32_t)sizeof(TIn);
+                const __amdgpu_buffer_rsrc_t rs = buffer_of(B + (int64_t)t0 * R + row0, end);
 #pragma unroll
                 for (int it = 0; it < WT * RB / 4 / WALK_NT; ++it) {
                     const int item = it * WALK_NT + tid, tl = item / (RB / 4), j = item % (RB / 4);
                     *reinterpret_cast<float4*>(half + stage_unit(tl, j)) =
-                        buffer_quad<TIn>(rs, (uint32_t)tl * ldb + (uint32_t)(4 * j) * (uint32_t)sizeof(TIn), (R & 1) == 0);
+                        buffer_quad<TIn>(rs, (uint32_t)tl * ldb + (uint32_t)(4 * j) * (uint32_t)sizeof(TIn), end, (R & 1) == 0);
                 }
             }
             __syncthreads();

@@ -22,15 +22,46 @@ __device__ inline float ordered_plane_sum(float sum, const float* __restrict__ p
 }
 
 // dW[perm[e]] = sum over token tiles of partial[tile][e], tiles added in ascending order (`more`: on top of
-// what earlier token ranges left there).  choice null: the first view.
+// what earlier token ranges left there).  drive.cost null: the first view.  The blocks from reduce_blocks on add
+// the nsplit partial outputs of a walk whose chunks are split over workgroups, out[k] = sum of planes[.][k],
+// in ascending order: a launch costs 3 us, more than either sum takes at the batches that split.
+struct PlaneSum {
+    const float* planes;
+    float* out;
+    int64_t n;
+    int nsplit;
+};
+__device__ inline void sum_planes_block(const PlaneSum& ps, int64_t block) {
+    const int64_t k = 4 * (block * 256 + threadIdx.x);
+    if (k >= ps.n) return;
+    if (ps.n % 4 == 0) {
+        float4 sum = *reinterpret_cast<const float4*>(ps.planes + k);
+        for (int z = 1; z < ps.nsplit; ++z) {
+            const float4 v = *reinterpret_cast<const float4*>(ps.planes + (int64_t)z * ps.n + k);
+            sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
+        }
+        *reinterpret_cast<float4*>(ps.out + k) = sum;
+        return;
+    }
+    for (int64_t i = k; i < std::min(ps.n, k + 4); ++i) {
+        float sum = ps.planes[i];
+        for (int z = 1; z < ps.nsplit; ++z) sum += ps.planes[(int64_t)z * ps.n + i];
+        ps.out[i] = sum;
+    }
+}
 __global__ __launch_bounds__(256) void k_walk_reduce(const float* __restrict__ partial, int64_t slots_stride, int ntile, int more,
                                                      const int* __restrict__ ptr_end0, const int* __restrict__ perm0,
                                                      const int* __restrict__ ptr_end1, const int* __restrict__ perm1,
-                                                     const int* __restrict__ choice, float* __restrict__ dW) {
-    const bool c = choice && *choice != 0;
+                                                     const WalkDrive drive, float* __restrict__ dW, unsigned reduce_blocks,
+                                                     const PlaneSum ps) {
+    if (blockIdx.x >= reduce_blocks) {
+        sum_planes_block(ps, (int64_t)blockIdx.x - reduce_blocks);
+        return;
+    }
+    const bool c = drive.cost && drive_by_col(drive);
     const int64_t n = (int64_t)*(c ? ptr_end1 : ptr_end0) * (2 * OCT);
     const int* __restrict__ perm = c ? perm1 : perm0;
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)gridDim.x * 256) {
+    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (int64_t)reduce_blocks * 256) {
         const int p = perm[e];
         if (p >= 0) dW[p] = ordered_plane_sum(more ? dW[p] : 0.f, partial + e, slots_stride, ntile);
     }
@@ -48,9 +79,9 @@ template <typename TIn>
 __global__ __launch_bounds__(256) void k_dw_slots(const TIn* __restrict__ dY, const TIn* __restrict__ X, int T, int O, int I,
                                                   const int* __restrict__ ptr_end0, const int* __restrict__ perm0,
                                                   const int* __restrict__ ptr_end1, const int* __restrict__ perm1,
-                                                  const int* __restrict__ choice, const int* __restrict__ flat,
+                                                  const WalkDrive drive, const int* __restrict__ flat,
                                                   float* __restrict__ dW) {
-    const bool c = *choice != 0;
+    const bool c = drive_by_col(drive);
     const int64_t n = (int64_t)*(c ? ptr_end1 : ptr_end0) * (2 * OCT);
     const int* __restrict__ perm = c ? perm1 : perm0;
     const int s = threadIdx.x & 7;
@@ -76,26 +107,6 @@ __global__ __launch_bounds__(256) void k_dw_slots(const TIn* __restrict__ dY, co
     }
 }
 
-// out[k] = sum of the nsplit partial planes, added in ascending order (n a multiple of 4 or not)
-__global__ __launch_bounds__(256) void k_sum_planes(const float* __restrict__ planes, int64_t n, int nsplit, float* __restrict__ out) {
-    const int64_t k = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
-    if (k >= n) return;
-    if (n % 4 == 0) {
-        float4 sum = *reinterpret_cast<const float4*>(planes + k);
-        for (int z = 1; z < nsplit; ++z) {
-            const float4 v = *reinterpret_cast<const float4*>(planes + (int64_t)z * n + k);
-            sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
-        }
-        *reinterpret_cast<float4*>(out + k) = sum;
-        return;
-    }
-    for (int64_t i = k; i < std::min(n, k + 4); ++i) {
-        float sum = planes[i];
-        for (int z = 1; z < nsplit; ++z) sum += planes[(int64_t)z * n + i];
-        out[i] = sum;
-    }
-}
-
 // ---- launch shapes.  A workgroup fills a CU, so a call takes (workgroups / 256, rounded up) rounds of
 // one workgroup's time: staging per chunk, the walk in proportion to the octet steps of its blocks, and
 // per block the way in (DW) and out (OUT).  Microseconds, from timings of the kernels at four
@@ -106,28 +117,34 @@ struct WalkCost {
 };
 static const WalkCost kOut = {0.0060, 1.7}, kBoth = {0.0105, 2.9}, kDw = {0.0090, 1.2};
 
-static double walk_round(const View& v, double density, int q, int chunks, const WalkCost& wc) {
+static double octet_steps(const View& v, double density) {
     const double m = density * v.KC;                                  // entries per row and chunk
-    const double steps = m + 1.42 * std::sqrt(m) + 0.5;               // the longest of eight binomial rows, even
+    return m + 1.42 * std::sqrt(m) + 0.5;                             // the longest of eight binomial rows, even
+}
+static double walk_units(const View& v, double density) { return octet_steps(v, density) * v.nchunk * v.NB; }   // see k_view_ptr
+static double walk_round(const View& v, double density, int q, int chunks, const WalkCost& wc) {
+    const double steps = octet_steps(v, density);
     const double stage = 1.0 + 1.5 * v.KC / KCMAX;
     const double blocks = (double)v.NB / (double)cdiv(v.NB, q);       // of a slab, on average
     return 2.0 + chunks * (stage + blocks * OPB * steps * wc.step) + blocks * wc.block;
 }
 static double walk_rounds(int64_t wgs) { return (double)cdiv(wgs, 256); }
+static double shape_cost(const View& v, int T, double density, int q, const WalkCost& wc) {
+    return walk_rounds(cdiv(T, WT) * cdiv(v.NB, q)) * walk_round(v, density, q, v.nchunk, wc);
+}
+
+static double view_density(const mst_layer* L) { return (double)L->nnz / (double)L->N; }
 
 struct WalkShape {
     int q, nsplit;
+    double cost;
 };
 static WalkShape pick_shape(const View& v, int T, double density, int qmax, const WalkCost& wc, int max_split) {
     const int64_t ntile = cdiv(T, WT);
-    WalkShape best{1, 1};
-    double best_cost = 0.0;
+    WalkShape best{1, 1, 0.0};
     for (int q = 1; q <= qmax; ++q) {
-        const double cost = walk_rounds(ntile * cdiv(v.NB, q)) * walk_round(v, density, q, v.nchunk, wc);
-        if (best_cost == 0.0 || cost < best_cost) {
-            best_cost = cost;
-            best = WalkShape{q, 1};
-        }
+        const double cost = shape_cost(v, T, density, q, wc);
+        if (q == 1 || cost < best.cost) best = WalkShape{q, 1, cost};
     }
     // Short batches leave most CUs without a workgroup and every workgroup with a chain of chunks: the
     // chunks can be split over workgroups (an entry lies in one chunk, so its weight gradient needs nothing
@@ -137,10 +154,7 @@ static WalkShape pick_shape(const View& v, int T, double density, int qmax, cons
         if (cdiv(v.nchunk, cps) != ns) continue;                      // (no empty range)
         const double cost = walk_rounds(ntile * v.NB * ns) * walk_round(v, density, 1, cps, wc) + 3.0 +
                             1e-6 * (double)T * v.R * (ns + 1);
-        if (cost < best_cost) {
-            best_cost = cost;
-            best = WalkShape{1, ns};
-        }
+        if (cost < best.cost) best = WalkShape{1, ns, cost};
     }
     return best;
 }
@@ -167,6 +181,21 @@ int bwd_fused_force_shape(int waves, int quads) {
     return MST_ERR_ARG;
 }
 
+// Modelled time in microseconds of a product on the sparse path (the launch shapes' costs, scaled to timings of
+// whole calls at 115 shapes and densities: 8 % rms error, 12 % for the weight gradient alone).
+double walk_us(const mst_layer* L, WalkJob job, int T) {
+    const double d = view_density(L);
+    // the sum of the planes of partial gradients: one read of each, at about 4 TB/s
+    const double reduce = 4.0 + (double)cdiv(T, WT) * walk_units(L->col, d) * (OPB * OCT * 4) / 4.0e6;
+    switch (job) {
+        case WALK_FWD: return 0.87 * pick_shape(L->row, T, d, 6, kOut, 1).cost;
+        case WALK_BWD_INPUT: return 0.87 * pick_shape(L->col, T, d, 6, kOut, 1).cost;
+        case WALK_BWD_WEIGHT:
+            return 0.8 * (std::min(pick_shape(L->row, T, d, 6, kDw, 1).cost, pick_shape(L->col, T, d, 6, kDw, 1).cost) + reduce) + 0.8;
+        default: return 0.88 * (pick_shape(L->col, T, d, 4, kBoth, (int)std::min<int64_t>(8, L->col.nchunk)).cost + reduce);
+    }
+}
+
 static WalkSide side_of(const View& v, const void* A, const void* B, int q) {
     WalkSide s;
     s.A = A;
@@ -182,7 +211,6 @@ static WalkSide side_of(const View& v, const void* A, const void* B, int q) {
     s.nslab = (int)cdiv(v.NB, q);
     return s;
 }
-static double view_density(const mst_layer* L) { return (double)L->nnz / (double)L->N; }
 static unsigned reduce_blocks(const mst_layer* L) { return (unsigned)std::min<int64_t>(cdiv(L->nnz * 3 / 2 + 1, 256), 8192); }
 
 int spmm(const mst_layer* L, const View& v, const void* A, float* out, int T, mst_dtype act, hipStream_t s) {
@@ -200,7 +228,7 @@ int bwd_fused(const mst_layer* L, const void* dY, const void* X, float* dX, floa
     int rc = ensure_fresh(L, false, true, s);
     if (rc != MST_OK) return rc;
     const int64_t planes = (int64_t)(ws.gemm_floats / ((size_t)T * v.R));
-    const WalkShape sh = g_forced_both ? WalkShape{g_forced_both, 1}
+    const WalkShape sh = g_forced_both ? WalkShape{g_forced_both, 1, 0.0}
                                        : pick_shape(v, T, view_density(L), 4, kBoth, (int)std::min<int64_t>({8, v.nchunk, planes}));
     const WalkSide sd = side_of(v, dY, X, sh.q);
     const int64_t stride = v.cap_pairs * (2 * OCT);
@@ -208,13 +236,11 @@ int bwd_fused(const mst_layer* L, const void* dY, const void* X, float* dX, floa
     const WalkArgs wa{sh.nsplit > 1 ? ws.gemm : dX, ws.partial, stride, T, ntile, (int)cdiv(v.nchunk, sh.nsplit)};
     rc = act == MST_F32 ? walk_both_f32(sh.q, sd, wa, sh.nsplit, s) : walk_both_bf16(sh.q, sd, wa, sh.nsplit, s);
     if (rc != MST_OK) return rc;
-    if (sh.nsplit > 1) {
-        const int64_t n = (int64_t)T * v.R;
-        k_sum_planes<<<(unsigned)cdiv(n, 1024), 256, 0, s>>>(ws.gemm, n, sh.nsplit, dX);
-        MST_LAUNCH_CHECK();
-    }
-    if (L->nnz > 0) {
-        k_walk_reduce<<<reduce_blocks(L), 256, 0, s>>>(ws.partial, stride, ntile, 0, v.ptr + v.nseg, v.perm, nullptr, nullptr, nullptr, dW);
+    PlaneSum ps{};
+    if (sh.nsplit > 1) ps = PlaneSum{ws.gemm, dX, (int64_t)T * v.R, sh.nsplit};
+    const unsigned rb = L->nnz > 0 ? reduce_blocks(L) : 0u, sb = (unsigned)cdiv(ps.n, 1024);
+    if (rb + sb > 0) {
+        k_walk_reduce<<<rb + sb, 256, 0, s>>>(ws.partial, stride, ntile, 0, v.ptr + v.nseg, v.perm, nullptr, nullptr, WalkDrive{}, dW, rb, ps);
         MST_LAUNCH_CHECK();
     }
     return MST_OK;
@@ -226,35 +252,39 @@ int bwd_fused(const mst_layer* L, const void* dY, const void* X, float* dX, floa
 int sddmm(const mst_layer* L, const void* dY, const void* X, float* dW, int T, mst_dtype act, float* partial,
           size_t partial_floats, hipStream_t s) {
     if (L->nnz == 0) return MST_OK;
-    int rc = ensure_fresh(L, true, true, s);
-    if (rc != MST_OK) return rc;
-    const View &r = L->row, &c = L->col;
+    const View &r = L->row, &c = L->col;              // (the entries' values are not read: stale ones will do)
     const int64_t stride = std::max(r.cap_pairs, c.cap_pairs) * (2 * OCT);
     const int64_t fit = (int64_t)(partial_floats / (size_t)stride);
+    WalkDrive drive{L->walk_cost, 1.f, 1.f};
     if (fit < 1) {
         if (act == MST_F32)
             k_dw_slots<float><<<8192, 256, 0, s>>>((const float*)dY, (const float*)X, T, L->O, L->I, r.ptr + r.nseg, r.perm,
-                                                   c.ptr + c.nseg, c.perm, L->sddmm_view, L->flat, dW);
+                                                   c.ptr + c.nseg, c.perm, drive, L->flat, dW);
         else
             k_dw_slots<uint16_t><<<8192, 256, 0, s>>>((const uint16_t*)dY, (const uint16_t*)X, T, L->O, L->I, r.ptr + r.nseg, r.perm,
-                                                      c.ptr + c.nseg, c.perm, L->sddmm_view, L->flat, dW);
+                                                      c.ptr + c.nseg, c.perm, drive, L->flat, dW);
         MST_LAUNCH_CHECK();
         return MST_OK;
     }
     const size_t esz = act == MST_F32 ? 4 : 2;
+    int rc = MST_OK;
     for (int64_t t = 0; t < T; t += fit * WT) {
         const int n = (int)std::min<int64_t>(T - t, fit * WT), ntile = (int)cdiv(n, WT);
         const char* x = static_cast<const char*>(X) + (size_t)t * L->I * esz;
         const char* y = static_cast<const char*>(dY) + (size_t)t * L->O * esz;
-        // one number of blocks per workgroup for both views: the better one for the view with more rows
-        const View& big = r.R >= c.R ? r : c;
-        const int q = pick_shape(big, n, view_density(L), 6, kDw, 1).q;
+        // one number of blocks per workgroup for both views: the better one for the view that drives a
+        // uniform pattern (heavy rows are missing from the row view)
+        const double d = view_density(L);
+        const WalkShape best_r = pick_shape(r, n, d, 6, kDw, 1), best_c = pick_shape(c, n, d, 6, kDw, 1);
+        const int q = !L->heavy_on && best_r.cost <= best_c.cost ? best_r.q : best_c.q;
+        drive.row_unit = (float)(shape_cost(r, n, d, q, kDw) / walk_units(r, d));
+        drive.col_unit = (float)(shape_cost(c, n, d, q, kDw) / walk_units(c, d));
         const WalkSide sr = side_of(r, x, y, q), sc = side_of(c, y, x, q);
         const WalkArgs wa{nullptr, partial, stride, n, ntile, std::max(r.nchunk, c.nchunk)};
-        rc = act == MST_F32 ? walk_dw_f32(q, sr, sc, wa, L->sddmm_view, s) : walk_dw_bf16(q, sr, sc, wa, L->sddmm_view, s);
+        rc = act == MST_F32 ? walk_dw_f32(q, sr, sc, wa, drive, s) : walk_dw_bf16(q, sr, sc, wa, drive, s);
         if (rc != MST_OK) return rc;
         k_walk_reduce<<<reduce_blocks(L), 256, 0, s>>>(partial, stride, ntile, t > 0 ? 1 : 0, r.ptr + r.nseg, r.perm, c.ptr + c.nseg,
-                                                       c.perm, L->sddmm_view, dW);
+                                                       c.perm, drive, dW, reduce_blocks(L), PlaneSum{});
         MST_LAUNCH_CHECK();
     }
     return MST_OK;

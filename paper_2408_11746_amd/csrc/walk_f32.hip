@@ -7,8 +7,8 @@ int walk_out_f32(int q, const WalkSide& sd, const WalkArgs& wa, hipStream_t s) {
 int walk_both_f32(int q, const WalkSide& sd, const WalkArgs& wa, int nsplit, hipStream_t s) {
     return launch_both_any<float>(q, sd, wa, nsplit, s);
 }
-int walk_dw_f32(int q, const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const int* choice, hipStream_t s) {
-    return launch_dw_any<float>(q, row, col, wa, choice, s);
+int walk_dw_f32(int q, const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const WalkDrive& drive, hipStream_t s) {
+    return launch_dw_any<float>(q, row, col, wa, drive, s);
 }
 
 }  // namespace mst

@@ -13,13 +13,12 @@ __global__ __launch_bounds__(WALK_NT) void k_walk(const WalkSide sd, const WalkA
     walk_body<TIn, Q, OUT, DW>(sd, wa, walk_lds);
 }
 
-// The weight gradient alone: either view can drive it, which one is a device-side flag set when the
-// views were built (the host never reads it back).  The grid covers the larger of the two.
+// The weight gradient alone: either view can drive it, decided on the device (WalkDrive).  The grid covers the larger of the two.
 template <typename TIn, int Q>
 __global__ __launch_bounds__(WALK_NT) void k_walk_dw(const WalkSide row, const WalkSide col, const WalkArgs wa,
-                                                     const int* __restrict__ choice) {
+                                                     const WalkDrive drive) {
     extern __shared__ __attribute__((aligned(16))) char walk_lds[];
-    const bool c = *(const_int*)choice != 0;
+    const bool c = drive_by_col(drive);
     WalkSide sd;                                      // field by field: the arguments stay in scalar registers
     sd.A = c ? col.A : row.A;
     sd.B = c ? col.B : row.B;
@@ -71,25 +70,25 @@ static int launch_both_any(int q, const WalkSide& sd, const WalkArgs& wa, int ns
 }
 
 template <typename TIn, int Q>
-static int launch_dw_q(const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const int* choice, hipStream_t s) {
+static int launch_dw_q(const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const WalkDrive& drive, hipStream_t s) {
     static uint64_t done = 0;
     const int rc = allow_lds(reinterpret_cast<const void*>(&k_walk_dw<TIn, Q>), KCMAX * WT * 4, done);
     if (rc != MST_OK) return rc;
     k_walk_dw<TIn, Q><<<walk_grid(wa.ntile, std::max(row.nslab, col.nslab)), WALK_NT, walk_lds_bytes(std::max(row.KC, col.KC)), s>>>(
-        row, col, wa, choice);
+        row, col, wa, drive);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
 
 template <typename TIn>
-static int launch_dw_any(int q, const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const int* choice, hipStream_t s) {
+static int launch_dw_any(int q, const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const WalkDrive& drive, hipStream_t s) {
     switch (q) {
-        case 1: return launch_dw_q<TIn, 1>(row, col, wa, choice, s);
-        case 2: return launch_dw_q<TIn, 2>(row, col, wa, choice, s);
-        case 3: return launch_dw_q<TIn, 3>(row, col, wa, choice, s);
-        case 4: return launch_dw_q<TIn, 4>(row, col, wa, choice, s);
-        case 5: return launch_dw_q<TIn, 5>(row, col, wa, choice, s);
-        default: return launch_dw_q<TIn, 6>(row, col, wa, choice, s);
+        case 1: return launch_dw_q<TIn, 1>(row, col, wa, drive, s);
+        case 2: return launch_dw_q<TIn, 2>(row, col, wa, drive, s);
+        case 3: return launch_dw_q<TIn, 3>(row, col, wa, drive, s);
+        case 4: return launch_dw_q<TIn, 4>(row, col, wa, drive, s);
+        case 5: return launch_dw_q<TIn, 5>(row, col, wa, drive, s);
+        default: return launch_dw_q<TIn, 6>(row, col, wa, drive, s);
     }
 }
 
