@@ -123,11 +123,11 @@ int mst_layer_export_dense(const mst_layer_t* layer, float* W_dev, uint8_t* M_de
 
 /* The active weights as one fp32 vector in ascending flat-index order, for the caller's
  * optimiser to update in place.  After changing them call mst_layer_sync_values: it copies
- * the values into whatever the products read (the entries of the index views that a product has
- * walked since they were built, a dense weight copy that is in use) with one or two kernels on
+ * the values into whatever the products read (the entries of each index view that a product of
+ * this layer has walked so far, a dense weight copy that is in use) with one or two kernels on
  * `stream`, nothing else; products recorded into a HIP graph therefore see the new values on
- * their next replay.  (A built view that no product has walked yet takes the values before its
- * first walk.)  Every
+ * their next replay.  (A view that no product of the layer has walked yet takes the values in the
+ * call that walks it first, which waits for them once.)  Every
  * mask update changes the set and therefore the meaning of position k of this vector. */
 int mst_layer_values(mst_layer_t* layer, float** vals_dev, int64_t* nnz);
 int mst_layer_sync_values(mst_layer_t* layer, mst_stream_t stream);

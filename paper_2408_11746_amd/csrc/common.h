@@ -100,9 +100,10 @@ struct mst_layer {
     // (path choice at the batch size and type of the last product call) leaves them unbuilt; a
     // call that needs them and has a workspace builds them, one without runs the dense product.
     bool views_valid = false;
-    // mst_layer_sync_values refreshes the entries of a built view only if a product has walked it
-    // since it was built (recorded products included: recording is a call); the entries of the others
-    // are stale and take the values before their first walk.  Same for the dense rows beside the row view.
+    // mst_layer_sync_values refreshes the entries of a built view only if a product has ever walked that view
+    // of the layer (recorded products included: recording is a call, and its replays outlive rebuilt views); the
+    // entries of the others are stale and take the values before their first walk.  Same for the dense rows
+    // beside the row view.  (A layer on the dense contractions would spend 50 us a step on them.)
     bool row_walked = false, col_walked = false;
     bool row_stale = false, col_stale = false;
     int hint_T = 0;            // batch size and activation type of the last product call (0: none yet)

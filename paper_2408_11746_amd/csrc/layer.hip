@@ -725,7 +725,7 @@ int build_views(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_
     rc = build_one_view(L->col, false, L, Wsrc, ws, s);
     if (rc != MST_OK) return rc;
     L->views_valid = true;
-    L->row_walked = L->col_walked = L->row_stale = L->col_stale = false;
+    L->row_stale = L->col_stale = false;
     if (!keep_dense_copy) L->Wd_valid = L->Wd_zeros = false;
     return MST_OK;
 }
@@ -773,13 +773,25 @@ static int refresh_views(const mst_layer* L, bool row, bool col, bool dense, hip
     return MST_OK;
 }
 
-// A product is about to walk these (built) views: entries that missed a change of the values take it now.
+// A product is about to walk these (built) views: entries that missed a change of the values take it now,
+// once in a layer's life.  Products on other streams are ordered after mst_layer_sync_values, not after this
+// call, so it waits for the new entries before it says that they are there.  A recording cannot wait and runs
+// later or never: it takes the refresh with it and leaves the view stale for whoever walks it first.
 int ensure_fresh(const mst_layer* Lc, bool row, bool col, hipStream_t s) {
     mst_layer* L = const_cast<mst_layer*>(Lc);       // caches of vals[], not layer state
-    const int rc = refresh_views(L, row && L->row_stale, col && L->col_stale, false, s);
+    if (row) L->row_walked = true;
+    if (col) L->col_walked = true;
+    row = row && L->row_stale;
+    col = col && L->col_stale;
+    if (!row && !col) return MST_OK;
+    const int rc = refresh_views(L, row, col, false, s);
     if (rc != MST_OK) return rc;
-    if (row) { L->row_walked = true; L->row_stale = false; }
-    if (col) { L->col_walked = true; L->col_stale = false; }
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    MST_HIP(hipStreamIsCapturing(s, &capture));
+    if (capture != hipStreamCaptureStatusNone) return MST_OK;
+    MST_HIP(hipStreamSynchronize(s));
+    if (row) L->row_stale = false;
+    if (col) L->col_stale = false;
     return MST_OK;
 }
 
@@ -930,8 +942,8 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     const bool dense = L->Wd_zeros && L->nnz > 0, views = L->nnz > 0 && L->views_valid;   // unbuilt views take the values when they are built
     L->Wd_valid = dense;
     if (views) {
-        L->row_stale |= !L->row_walked;
-        L->col_stale |= !L->col_walked;
+        L->row_stale = !L->row_walked;
+        L->col_stale = !L->col_walked;
     }
     return refresh_views(L, views && L->row_walked, views && L->col_walked, dense, s);
 }

@@ -123,3 +123,43 @@ def test_values_reach_views_that_no_product_has_walked_yet():
     L.sync_values()                                   # the row view has been walked, the col view has not
     assert rel_err(rig.fwd(X), opr.fc_fwd(X, 4 * W, M)) <= TOL
     assert rel_err(rig.bwd_input(dY), opr.fc_bwd_input(dY, 4 * W, M)) <= TOL
+
+
+@pytest.mark.parametrize("T", [100, 384])
+def test_values_changed_before_a_views_first_walk(T):
+    """A view that nothing has walked takes changed values with its first walk: a recording that comes first must
+    not count as one, other streams see them as soon as the call is back, and a recorded walk goes on
+    seeing new values after the view was built anew."""
+    I, O = 640, 512
+    W, M = synth.make_layer(95, 1, I, O, 0.5)
+    X, _ = synth.make_activations(95, 2, T, I, O)
+    rig = Rig(W, M, T, cap=int(M.sum()))
+    L, Xd = rig.layer, dev(X)
+    new = lambda: torch.full((T, O), float("nan"), dtype=torch.float32, device=DEV)  # noqa: E731
+    ref = opr.fc_fwd(X, W, M)
+    L.set_path(mst.MST_PATH_SPARSE)
+    L.values().mul_(2.0)
+    L.sync_values()
+    torch.cuda.synchronize()
+    Yg, graph, side = new(), torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        mst.mst_sparse_fc_fwd(L, Xd, Yg, T, mst.MST_F32, side)
+    Y0, Y1 = new(), new()
+    mst.mst_sparse_fc_fwd(L, Xd, Y0, T, mst.MST_F32, torch.cuda.current_stream())
+    mst.mst_sparse_fc_fwd(L, Xd, Y1, T, mst.MST_F32, side)
+    torch.cuda.synchronize()
+    assert rel_err(Y0.cpu().numpy(), 2.0 * ref) <= TOL
+    assert torch.equal(Y0, Y1)
+    for k in range(3):                                       # replays with eager work and other values between them
+        graph.replay()
+        torch.cuda.synchronize()
+        assert rel_err(Yg.cpu().numpy(), 2.0 ** (1 + k) * ref) <= TOL
+        L.values().mul_(2.0)
+        L.sync_values()
+    W2 = (W * 16.0).astype(np.float32)
+    L.load_dense(dev(W2), dev(M.astype(np.uint8)), rig.ws)    # views built anew, walked by nothing but the graph
+    L.values().mul_(0.25)
+    L.sync_values()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert rel_err(Yg.cpu().numpy(), 4.0 * ref) <= TOL
