@@ -16,7 +16,7 @@
 // bfloat16 operand): two (three) workgroups share a CU and one's staging runs beside another's MFMAs.
 // Loads are buffer loads from the tile's corner with exact ends: rows past the matrix read as zeros
 // without an access, a 16-byte load needs dword alignment only, so no leading dimension is special.
-// What lies past the end of a row is the next row (finite); it lands in outputs that are not stored,
+// What lies past the end of a row is the next row; it lands in outputs that are not stored,
 // or, along k, is cleared in the last step.  Bound: the matrix cores (six products per term; a large
 // bf16 product runs at 1294 TFLOP/s on this card, that is 215 of these); the 128 tile pulls 1/6 of the
 // operand bytes per MFMA of a plain bf16 kernel.
@@ -48,6 +48,24 @@ __device__ inline void cut_pair(float x0, float x1, uint32_t& hi, uint32_t& mid,
     mid = __builtin_amdgcn_perm(b1, b0, UPPER);
     const float c0 = __uint_as_float(b0) - __uint_as_float(b0 & 0xFFFF0000u), c1 = __uint_as_float(b1) - __uint_as_float(b1 & 0xFFFF0000u);
     lo = __builtin_amdgcn_perm(__float_as_uint(c1), __float_as_uint(c0), UPPER);
+}
+
+// The lower parts of an infinite value are inf - inf = NaN, so a sum with an infinite operand comes out as NaN
+// where fp32 products give an infinity.  An output that is NaN is therefore formed again by fp32
+// multiply-adds, up to the first term that makes it NaN by itself; no other output pays more than a compare.
+template <typename TA, bool A_KMAJOR, typename TB, bool B_KMAJOR>
+__device__ __forceinline__ float fp32_sum(const TA* __restrict__ A, int64_t lda, const TB* __restrict__ B, int64_t ldb, int m, int n,
+                                          int kbeg, int kend) {
+    auto value = [](auto x) {
+        if constexpr (sizeof(x) == 2) return __uint_as_float((uint32_t)x << 16);
+        else return x;
+    };
+    float sum = 0.f;
+#pragma unroll 1
+    for (int k = kbeg; k < kend && sum == sum; ++k)
+        sum = fmaf(value(A[A_KMAJOR ? (int64_t)k * lda + m : (int64_t)m * lda + k]),
+                   value(B[B_KMAJOR ? (int64_t)k * ldb + n : (int64_t)n * ldb + k]), sum);
+    return sum;
 }
 
 // One operand's registers between global memory and LDS.  A thread (p = 0 .. 255) stages two pieces per
@@ -239,6 +257,7 @@ void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restr
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[0][0][v] += other[v];
     // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
+    bool nan = false;
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -248,7 +267,18 @@ void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restr
                 const int m = m0 + wm + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
                 const int n = n0 + wn + j * 32 + lm;
                 if (m < M && n < N) Cz[(int64_t)m * N + n] = acc[i][j][v];
+                nan |= acc[i][j][v] != acc[i][j][v];
             }
+    if (nan) {
+#pragma unroll 1
+        for (int x = 0; x < MI * MI * 16; ++x) {
+            const int m = m0 + wm + (x / (16 * MI)) * 32 + 8 * ((x >> 2) & 3) + 4 * lk + (x & 3);
+            const int n = n0 + wn + ((x >> 4) % MI) * 32 + lm;
+            if (m >= M || n >= N) continue;
+            float* const c = Cz + (int64_t)m * N + n;
+            if (*c != *c) *c = fp32_sum<typename OpA::T, A_KMAJOR, float, B_KMAJOR>(A, lda, B, ldb, m, n, kbeg, kend);
+        }
+    }
 }
 
 // ---- Small outputs: one workgroup per 32 x 32 (MI = 1) or 64 x 64 (MI = 2) output tile, all its
@@ -469,7 +499,11 @@ void k_gemm_stream(const void* __restrict__ Av, int64_t lda, const void* __restr
         float sum = part[x];
 #pragma unroll
         for (int w = 1; w < NW; ++w) sum += part[w * TM * TM + x];
-        if (m < M && n < N) Cz[(int64_t)m * N + n] = sum;
+        if (m < M && n < N) {
+            if constexpr (!(A16 && B16))
+                if (sum != sum) sum = fp32_sum<typename OpA::T, A_KMAJOR, typename OpB::T, B_KMAJOR>(A, lda, B, ldb, m, n, kbeg, kend);
+            Cz[(int64_t)m * N + n] = sum;
+        }
     }
 }
 

@@ -82,3 +82,32 @@ def test_bfloat16_dense_gradient_of_any_shape(T, I, O, mode):
             assert rel_err(G.cpu().numpy(), ref) <= FP32
     finally:
         mst.mst_gemm_force_fp32_mfma(0)
+
+
+@pytest.mark.parametrize("act", [mst.MST_F32, mst.MST_BF16])
+@pytest.mark.parametrize("mode", [1032, 1064, 1096, 1128])
+def test_infinite_operands_as_fp32_products_give_them(mode, act):
+    """The parts of an infinite value are NaN; the outputs are what fp32 products give: infinities, or NaN where
+    two of opposite sign or an infinity and a zero meet, and every other output as without it."""
+    T, I, O = 130, 190, 97
+    print("case", T, I, O, mode, act, flush=True)
+    X = synth.normal(63, 1, (T, I)).astype(np.float32)
+    X.view(np.uint32)[...] &= 0xFFFF0000                     # (exact in bfloat16)
+    W = synth.normal(63, 3, (O, I), 0.02).astype(np.float32)
+    X[3, 7], X[129, 189], X[40, 5], X[40, 6], X[50, 9] = np.inf, -np.inf, np.inf, -np.inf, np.nan
+    X[60, 11], W[5, 11] = np.inf, 0.0
+    W[96, 100] = -np.inf
+    rig = Rig(W, np.ones((O, I), np.uint8), T, cap=O * I)
+    rig.layer.set_path(mst.MST_PATH_DENSE)
+    try:
+        mst.mst_gemm_force_fp32_mfma(mode)
+        Y = rig.fwd(X if act == mst.MST_F32 else (X.view(np.uint32) >> 16).astype(np.int16), act)
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
+    with np.errstate(invalid="ignore"):
+        ref = X.astype(np.float64) @ W.T.astype(np.float64)
+    finite = np.isfinite(ref)
+    assert 400 < (~finite).sum() < ref.size // 10 and np.isinf(ref).any() and np.isnan(ref).any()
+    assert np.array_equal(np.isnan(Y), np.isnan(ref))
+    assert np.array_equal(Y[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32))
+    assert rel_err(Y[finite], ref[finite]) <= FP32
