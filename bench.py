@@ -428,14 +428,14 @@ def run_block(args, name, mst, synth, torch, lds_peak, with_cpu_baseline):
     # fwd / bwd_input are one SpMM launch or one masked dense product; bwd is the shared walk followed by its
     # small second kernel, or the two dense contractions
     dp, dw = dense_prod[dL.name], dense_wgrad[dL.name]
-    spmm_k = "k_spmm / k_spmm64 (launch shape chosen per call) + k_heavy_fwd after the forward (heavy rows as a dense product; returns at once without any)"
+    spmm_k = "k_walk<OUT> (launch shape chosen per call) + k_heavy_fwd after the forward (heavy rows as a dense product; returns at once without any)"
     gemm_k = "k_gemm_split256 / k_gemm_split_n160 / k_gemm_split (fp32 operands as bf16 hi + lo)" if act == "f32" else \
         "k_gemm_a16_256 (bfloat16 activations x fp32 weights as bf16 hi + lo, 2 products per term)"
     wgrad_dense_k = ("k_gemm_tn_bf16" if act == "bf16" else "k_gemm_split256<TN> / k_gemm_split<TN>") + " + k_gather_flat"
     kernel = {"fwd": gemm_k if dp else spmm_k,
               "bwd_input": gemm_k if dp else spmm_k,
-              "bwd_weight": wgrad_dense_k if dw else "k_sddmm + k_sddmm_reduce",
-              "bwd": "k_bwd_fused + k_bwd_fused_reduce" if not dense_bwd[dL.name] else
+              "bwd_weight": wgrad_dense_k if dw else "k_walk_dw + k_walk_reduce",
+              "bwd": "k_walk<OUT, DW> + k_walk_reduce" if not dense_bwd[dL.name] else
                      "%s, then %s" % (gemm_k, wgrad_dense_k)}[drow["call"]]
     if drow["path"] == "dense-mfma":
         # every leg of the call is a dense contraction: priced against the matrix cores
@@ -827,7 +827,7 @@ def run_sweep(args, mst, synth, torch, lds_peak, with_cpu_baseline):
         kernel = ("k_gemm_split256 (masked dense product, bf16 hi + lo split on v_mfma_f32_32x32x16_bf16; preceded by the "
                   "scatter of the dense weight copy after an update)")
     else:
-        kernel = "k_spmm / k_spmm64 (launch shape chosen per call)"
+        kernel = "k_walk<OUT> (launch shape chosen per call)"
     roof = roofline_of(drow, dL, "f32", kernel, "C5")
     if drow["call"] == "dense_grad" and roof["bound"] == "mfma":
         gi = layers.index(dL)
