@@ -152,7 +152,11 @@ def _ptr(t) -> int:
     try:
         return t.data_ptr()
     except AttributeError:
-        return 0 if t is None else int(t)
+        if t is None:
+            return 0
+        if isinstance(t, int):
+            return t
+        raise
 
 
 _current = None

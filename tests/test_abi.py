@@ -155,3 +155,11 @@ def test_calls_on_a_layer_that_was_never_loaded_return_state_error():
         assert L.mst_sparse_fc_fwd(h, None, fake, T, 0, None) == -1
     finally:
         L.mst_layer_destroy(h)
+
+
+def test_only_tensors_integers_and_none_are_addresses():
+    import numpy as np
+    assert binding._ptr(None) == 0 and binding._ptr(4096) == 4096
+    for value in ("4096", 4096.0, np.array([4096]), np.int64(4096), b"4096"):
+        with pytest.raises(AttributeError):
+            binding._ptr(value)
