@@ -242,6 +242,9 @@ __global__ __launch_bounds__(256) void k_count_col(const uint8_t* __restrict__ m
 // octets (h <= #empty rows / 7) the octets cost about
 //   sum_{j<h} ceil(len_j / 8)  +  sum over the octets of the other rows of their longest row,
 // h is the value that minimises it (0 for every mask without empty rows).
+// Bound by the latency of its reads of the counts (there are only as many workgroups as row blocks), so
+// all reads of a segment are issued together (with the fill of the col view in turns of four entries: update of
+// the GPT-2-small block at density 0.05, 1024 tokens, 766 -> 742 us).
 __global__ __launch_bounds__(RB) void k_block_rank(const int* __restrict__ segcnt, int msub, int nchunk, int Rpad, int NBpad,
                                                    int* __restrict__ rowmap, int* __restrict__ rowpos, int* __restrict__ qlen) {
     __shared__ int len_s[RB], sorted[RB], row_s[RB];
@@ -249,6 +252,7 @@ __global__ __launch_bounds__(RB) void k_block_rank(const int* __restrict__ segcn
     const int j = threadIdx.x, b = blockIdx.x;
     if (j == 0) { h_s = 0; nzero_s = 0; }
     int len = 0;
+#pragma unroll 8
     for (int c = 0; c < nchunk * msub; ++c) len += segcnt[(size_t)c * Rpad + b * RB + j];
     len_s[j] = len;
     __syncthreads();
@@ -289,13 +293,23 @@ __global__ __launch_bounds__(RB) void k_block_rank(const int* __restrict__ segcn
     for (int idx = j; idx < nchunk * OPB; idx += RB) {
         const int c = idx / OPB, o = idx % OPB;
         const int* cnt = segcnt + (size_t)c * msub * Rpad + b * RB;
-        int L = 0;
-        for (int g = 0; g < (o < h ? 1 : OCT); ++g) {
-            int n = 0;
-            for (int u = 0; u < msub; ++u) n += cnt[(size_t)u * Rpad + row_s[o * OCT + g]];
-            L = max(L, n);
+        int n[OCT];
+#pragma unroll
+        for (int g = 0; g < OCT; ++g) {
+            n[g] = 0;
+#pragma unroll
+            for (int u = 0; u < KCMAX / KSMAX; ++u) {
+                const int v = cnt[(size_t)min(u, msub - 1) * Rpad + row_s[o * OCT + g]];
+                n[g] += u < msub ? v : 0;
+            }
         }
-        if (o < h) L = (L + 7) >> 3;
+        int L = n[0];
+        if (o < h) {
+            L = (L + 7) >> 3;
+        } else {
+#pragma unroll
+            for (int g = 1; g < OCT; ++g) L = max(L, n[g]);
+        }
         qlen[((size_t)c * NBpad + b) * OPB + o] = (L + 1) >> 1;
     }
 }
@@ -574,10 +588,10 @@ __global__ __launch_bounds__(256) void k_fill_col(const uint8_t* __restrict__ ma
     const int o0 = sc * KS, oc0 = c * msub * KS;
     load_mask_tile(mask, O, I, o0, KS, i0, m, tid);
     __syncthreads();
-    int n = 0;
+    uint32_t bits = 0;                                // this thread's 32 rows of its column
 #pragma unroll
-    for (int k = 0; k < 32; ++k) n += m[(32 * rg + k) * MT_LD + j] != 0;
-    part[rg][j] = n;
+    for (int k = 0; k < 32; ++k) bits |= (uint32_t)(m[(32 * rg + k) * MT_LD + j] != 0) << k;
+    part[rg][j] = __popc(bits);
     __syncthreads();
     if (i >= NB * RB) return;                         // (columns past the matrix only pad)
     int jj = 0;
@@ -588,14 +602,27 @@ __global__ __launch_bounds__(256) void k_fill_col(const uint8_t* __restrict__ ma
     const bool guest = !spread && (rowmap[b * RB + OCT * o] & SPREAD_FLAG) != 0;
     const size_t seg = ((size_t)c * NBpad + b) * OPB + o;
     const int pair0 = ptr[seg], npairs = ptr[seg + 1] - pair0;
-    if (n > 0) {
-        for (int k = 0; k < 32; ++k) {
-            const int ol = 32 * rg + k;
-            if (!m[ol * MT_LD + j]) continue;
-            const size_t f = (size_t)(o0 + ol) * I + i;
+    // A wavefront's columns hold their entries in different rows: it takes as many turns as the fullest of
+    // them has entries, not one per row that any has, and four entries' reads go out together.
+    while (bits) {
+        int ol[4], ci[4];
+        float w[4];
+        bool has[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            has[q] = bits != 0;
+            ol[q] = has[q] ? 32 * rg + __ffs((int)bits) - 1 : ol[0];
+            bits &= bits - 1;
+            const size_t f = (size_t)(o0 + ol[q]) * I + i;
+            w[q] = W[f];
+            ci[q] = cidx[f];
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (!has[q]) continue;
             const int64_t e = row_slot(pair0, g, spread, jj);
-            ent[e] = make_uint2(lds_off((uint32_t)(o0 + ol - oc0)), __float_as_uint(W[f]));
-            perm[e] = cidx[f];
+            ent[e] = make_uint2(lds_off((uint32_t)(o0 + ol[q] - oc0)), __float_as_uint(w[q]));
+            perm[e] = ci[q];
             ++jj;
         }
     }
