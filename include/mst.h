@@ -127,7 +127,9 @@ int mst_layer_export_dense(const mst_layer_t* layer, float* W_dev, uint8_t* M_de
  * this layer has walked so far, a dense weight copy that is in use) with one or two kernels on
  * `stream`, nothing else; products recorded into a HIP graph therefore see the new values on
  * their next replay.  (A view that no product of the layer has walked yet takes the values in the
- * call that walks it first, which waits for them once.)  Every
+ * call that walks it first, which waits for them once.)  On a capturing stream the call records the
+ * refresh of every view that is built and of a dense copy in use, walked or not; a view that is
+ * built, or a dense copy that comes into use, after the recording is not in it.  Every
  * mask update changes the set and therefore the meaning of position k of this vector. */
 int mst_layer_values(mst_layer_t* layer, float** vals_dev, int64_t* nnz);
 int mst_layer_sync_values(mst_layer_t* layer, mst_stream_t stream);

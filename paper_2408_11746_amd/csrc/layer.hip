@@ -968,11 +968,20 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     // than at the next product, so that products recorded into a graph never see stale weights.
     const bool dense = L->Wd_zeros && L->nnz > 0, views = L->nnz > 0 && L->views_valid;   // unbuilt views take the values when they are built
     L->Wd_valid = dense;
-    if (views) {
-        L->row_stale = !L->row_walked;
-        L->col_stale = !L->col_walked;
+    bool row = views, col = views;
+    if (views && !(L->row_walked && L->col_walked)) {
+        // A recording refreshes every built view and changes no flag: its replays come at any time, between calls
+        // that walk a view for the first time, and it has not run yet.
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        MST_HIP(hipStreamIsCapturing(s, &capture));
+        if (capture == hipStreamCaptureStatusNone) {
+            row = L->row_walked;
+            col = L->col_walked;
+            L->row_stale |= !row;
+            L->col_stale |= !col;
+        }
     }
-    return refresh_views(L, views && L->row_walked, views && L->col_walked, dense, s);
+    return refresh_views(L, row, col, dense, s);
 }
 
 int mst_layer_indices(const mst_layer_t* L, int32_t* flat_dev, mst_stream_t stream) {
