@@ -123,13 +123,14 @@ int mst_layer_export_dense(const mst_layer_t* layer, float* W_dev, uint8_t* M_de
 
 /* The active weights as one fp32 vector in ascending flat-index order, for the caller's
  * optimiser to update in place.  After changing them call mst_layer_sync_values: it copies
- * the values into whatever the products read (the entries of each index view that a product of
- * this layer has walked so far, a dense weight copy that is in use) with one or two kernels on
- * `stream`, nothing else; products recorded into a HIP graph therefore see the new values on
- * their next replay.  (A view that no product of the layer has walked yet takes the values in the
- * call that walks it first, which waits for them once.)  On a capturing stream the call records the
- * refresh of every view that is built and of a dense copy in use, walked or not; a view that is
- * built, or a dense copy that comes into use, after the recording is not in it.  Every
+ * the values into whatever the products read (the entries of the index views, a dense weight copy
+ * that is in use) with one kernel on `stream`, nothing else; products recorded into a HIP graph
+ * therefore see the new values on their next replay, and no product sees values that have not been
+ * handed over.  (While a dense copy is in use, a view that no product of the layer has walked yet is
+ * left out; the call that walks it first copies the values from there and waits for that once.)  On a
+ * capturing stream the call records the refresh of every view that is built and of a dense copy in
+ * use, walked or not; a view that is built, or a dense copy that comes into use, after the recording
+ * is not in it.  Every
  * mask update changes the set and therefore the meaning of position k of this vector. */
 int mst_layer_values(mst_layer_t* layer, float** vals_dev, int64_t* nnz);
 int mst_layer_sync_values(mst_layer_t* layer, mst_stream_t stream);

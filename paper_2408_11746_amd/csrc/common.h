@@ -65,18 +65,18 @@ struct View {
     int nsub() const { return nchunk * msub; }
 };
 
-// Hd row j = row heavy[1 + j] of W . M, from the canonical arrays, by one block (heavy rows, heavy.hip).
-// Every thread of the block must call it; j at or past the count does nothing.
+// Hd row j = row heavy[1 + j] of W . M, from the canonical arrays, by one block (heavy rows, heavy.hip);
+// value(k) = the k-th active weight.  Every thread of the block must call it; j at or past the count does nothing.
+template <typename F>
 __device__ inline void heavy_fill_row(int j, const int* __restrict__ heavy, const int* __restrict__ rowptr,
-                                      const int* __restrict__ flat, const float* __restrict__ vals, int I,
-                                      float* __restrict__ Hd) {
+                                      const int* __restrict__ flat, F&& value, int I, float* __restrict__ Hd) {
     if (j >= min(heavy[0], HEAVY_MAX)) return;
     const int h = heavy[1 + j];
     float* row = Hd + (int64_t)j * I;
     for (int i = threadIdx.x; i < I; i += blockDim.x) row[i] = 0.f;
     __syncthreads();
     const int k1 = rowptr[h + 1];
-    for (int k = rowptr[h] + threadIdx.x; k < k1; k += blockDim.x) row[flat[k] - h * I] = vals[k];
+    for (int k = rowptr[h] + threadIdx.x; k < k1; k += blockDim.x) row[flat[k] - h * I] = value(k);
 }
 
 }  // namespace mst
@@ -100,12 +100,14 @@ struct mst_layer {
     // (path choice at the batch size and type of the last product call) leaves them unbuilt; a
     // call that needs them and has a workspace builds them, one without runs the dense product.
     bool views_valid = false;
-    // mst_layer_sync_values refreshes the entries of a built view only if a product has ever walked that view
-    // of the layer (recorded products included: recording is a call, and its replays outlive rebuilt views); the
-    // entries of the others are stale and take the values before their first walk.  Same for the dense rows
-    // beside the row view.  (A layer on the dense contractions would spend 50 us a step on them.)
+    // While a dense copy is in use mst_layer_sync_values refreshes the entries of a built view only if a product
+    // has ever walked that view of the layer (recorded products included: recording is a call, and its replays
+    // outlive rebuilt views); the entries of the others are stale and take the dense copy's values before their
+    // first walk.  Same for the dense rows beside the row view.  (A layer on the dense contractions would spend
+    // 50 us a step on them.)
     bool row_walked = false, col_walked = false;
     bool row_stale = false, col_stale = false;
+    int* dense_live = nullptr; // device: Wd holds the values handed over last (0: every built view holds them)
     int hint_T = 0;            // batch size and activation type of the last product call (0: none yet)
     int hint_act = 0;
     std::atomic<uint64_t> choice{0};   // sparse-or-dense choices at the last batch size and type (see remembered(); 0: none)

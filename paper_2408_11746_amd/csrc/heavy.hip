@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void k_heavy_fwd(const TA* __restrict__ X, con
 __global__ __launch_bounds__(256) void k_heavy_fill(const int* __restrict__ heavy, const int* __restrict__ rowptr,
                                                     const int* __restrict__ flat, const float* __restrict__ vals, int I,
                                                     float* __restrict__ Hd) {
-    heavy_fill_row((int)blockIdx.x, heavy, rowptr, flat, vals, I, Hd);
+    heavy_fill_row((int)blockIdx.x, heavy, rowptr, flat, [=](int k) { return vals[k]; }, I, Hd);
 }
 
 // The rows that leave the row view: rowcnt[r] >= thr, the first HEAVY_MAX of them in row order.

@@ -127,7 +127,7 @@ static LayerCarve carve_layer(int O, int I, int64_t cap) {
     c.cperm = take((size_t)k.cap_pairs * OCT * 8);
     c.cmap = take((size_t)k.NBpad * RB * 4);
     c.cpos = take((size_t)k.NBpad * RB * 4);
-    c.cost = take(16);
+    c.cost = take(16 + 4);
     c.heavy = take((size_t)(HEAVY_MAX + 2) * 4);
     c.Hd = take((size_t)HEAVY_MAX * I * 4);
     c.total = off;
@@ -364,7 +364,8 @@ __global__ __launch_bounds__(1024) void k_scan_excl(const int* in, int* out, int
 __global__ __launch_bounds__(1024) void k_view_ptr(const int* __restrict__ rowcnt, int* __restrict__ rowptr, int nrows,
                                                    const int* __restrict__ qlen, int NBpad, int NB, int nchunk,
                                                    int64_t nseg, int* __restrict__ ptr,
-                                                   unsigned long long* __restrict__ cost, const int* __restrict__ heavy) {
+                                                   unsigned long long* __restrict__ cost, const int* __restrict__ heavy,
+                                                   int* __restrict__ dense_live, int live) {
     __shared__ int wsum[16];
     __shared__ unsigned long long cost_s;
     if (rowcnt) block_scan_excl(rowcnt, rowptr, nrows, wsum);
@@ -382,7 +383,10 @@ __global__ __launch_bounds__(1024) void k_view_ptr(const int* __restrict__ rowcn
     if (mine) atomicAdd(&cost_s, mine);
     __syncthreads();
     // (a row view that leaves heavy rows out cannot drive the weight gradient)
-    if (threadIdx.x == 0) *cost = (heavy && heavy[0] > 0) ? (1ull << 50) : cost_s;
+    if (threadIdx.x == 0) {
+        *cost = (heavy && heavy[0] > 0) ? (1ull << 50) : cost_s;
+        *dense_live = live;
+    }
 }
 
 // entry slot (as index into ent viewed as uint2[], and into perm) of step j of a row
@@ -632,18 +636,27 @@ __global__ __launch_bounds__(256) void k_fill_col(const uint8_t* __restrict__ ma
 
 // The entries of one or both views in one launch: the first `row_blocks` blocks refresh the row
 // view's, the next `col_blocks` the col view's, then (with row blocks) HEAVY_MAX blocks the dense
-// matrix of the heavy rows.  A thread takes four slots: one 16-byte read of their canonical indices.
+// matrix of the heavy rows, the rest the dense copy.  A thread takes four slots: one 16-byte read of their
+// canonical indices.  LATE: a view that was left out of earlier hand-overs takes what the last one handed over,
+// which the dense copy holds; vals[] may have changed since.  Without a live dense copy nothing was left out.
+template <bool LATE>
 __global__ __launch_bounds__(256) void k_sync_views(const float* __restrict__ vals, unsigned row_blocks, unsigned col_blocks,
                              const int* __restrict__ ptr_r, int64_t nseg_r, const int* __restrict__ perm_r,
                              uint2* __restrict__ ent_r,
                              const int* __restrict__ ptr_c, int64_t nseg_c, const int* __restrict__ perm_c,
                              uint2* __restrict__ ent_c, const int* __restrict__ heavy, const int* __restrict__ rowptr,
                              const int* __restrict__ flat, int I, float* __restrict__ Hd, unsigned heavy_blocks,
-                             float* __restrict__ Wd, int64_t nnz) {
+                             float* __restrict__ Wd, int64_t nnz, int* __restrict__ dense_live) {
+    if (LATE) {
+        if (*dense_live == 0) return;
+    } else if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *dense_live = gridDim.x > row_blocks + col_blocks + heavy_blocks;
+    }
+    auto value = [&](int k) { return LATE ? Wd[flat[k]] : vals[k]; };
     if (blockIdx.x >= row_blocks + col_blocks) {
         const unsigned b = blockIdx.x - row_blocks - col_blocks;
         if (b < heavy_blocks) {
-            heavy_fill_row((int)b, heavy, rowptr, flat, vals, I, Hd);
+            heavy_fill_row((int)b, heavy, rowptr, flat, value, I, Hd);
         } else {
             const int64_t k = (int64_t)(b - heavy_blocks) * 256 + threadIdx.x;
             if (k < nnz) Wd[flat[k]] = vals[k];
@@ -658,17 +671,19 @@ __global__ __launch_bounds__(256) void k_sync_views(const float* __restrict__ va
     for (int64_t e = (int64_t)(blockIdx.x - (col ? row_blocks : 0u)) * 256 + threadIdx.x; e < n4; e += stride) {
         const int4 p = reinterpret_cast<const int4*>(perm)[e];
         uint2* d = ent + 4 * e;
-        if (p.x >= 0) d[0].y = __float_as_uint(vals[p.x]);
-        if (p.y >= 0) d[1].y = __float_as_uint(vals[p.y]);
-        if (p.z >= 0) d[2].y = __float_as_uint(vals[p.z]);
-        if (p.w >= 0) d[3].y = __float_as_uint(vals[p.w]);
+        if (p.x >= 0) d[0].y = __float_as_uint(value(p.x));
+        if (p.y >= 0) d[1].y = __float_as_uint(value(p.y));
+        if (p.z >= 0) d[2].y = __float_as_uint(value(p.z));
+        if (p.w >= 0) d[3].y = __float_as_uint(value(p.w));
     }
 }
 
+// dense_live: null where Wd is not the layer's own dense copy
 __global__ void k_scatter_dense(const float* __restrict__ vals, const int* __restrict__ flat,
-                                int64_t nnz, float* __restrict__ Wd) {
+                                int64_t nnz, float* __restrict__ Wd, int* __restrict__ dense_live) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k < nnz) Wd[flat[k]] = vals[k];
+    if (k == 0 && dense_live) *dense_live = 1;
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ dst, uint32_t value, int64_t n) {
@@ -701,7 +716,8 @@ int fill_u32(void* dst, uint32_t value, int64_t n_words, hipStream_t s) {
 // One view: count per (row, sub-chunk) -> ranking of every block's rows with the segments' lengths ->
 // pointers of the octet segments (with the view's cost for the weight gradient) -> ordered compaction.  Four launches; nothing is cleared beforehand:
 // the count kernels write the padding rows' zero counts and the fill kernels their own padding.
-static int build_one_view(View& v, bool row_view, const mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_t s) {
+static int build_one_view(View& v, bool row_view, const mst_layer* L, const float* Wsrc, const Workspace& ws, bool keep_dense_copy,
+                          hipStream_t s) {
     const int O = L->O, I = L->I;
     const int Rpad = v.NBpad * RB, nsub = v.nsub();
     if (row_view) {
@@ -719,7 +735,8 @@ static int build_one_view(View& v, bool row_view, const mst_layer* L, const floa
     k_block_rank<<<(unsigned)v.NBpad, RB, 0, s>>>(ws.segcnt, v.msub, v.nchunk, Rpad, v.NBpad, v.rowmap, v.rowpos, ws.qlen);
     MST_LAUNCH_CHECK();
     k_view_ptr<<<1, 1024, 0, s>>>(row_view ? ws.rowcnt : nullptr, L->rowptr, O, ws.qlen, v.NBpad, v.NB, v.nchunk, v.nseg,
-                                  v.ptr, L->walk_cost + (row_view ? 0 : 1), row_view && L->heavy_on ? L->heavy : nullptr);
+                                  v.ptr, L->walk_cost + (row_view ? 0 : 1), row_view && L->heavy_on ? L->heavy : nullptr,
+                                  L->dense_live, keep_dense_copy ? 1 : 0);
     MST_LAUNCH_CHECK();
     if (row_view) {
         const int nrows = v.NB * RB;
@@ -747,9 +764,9 @@ static int build_one_view(View& v, bool row_view, const mst_layer* L, const floa
 // row view pass writes to ws.cidx.
 int build_views(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_t s, bool keep_dense_copy) {
     L->views_valid = false;
-    int rc = build_one_view(L->row, true, L, Wsrc, ws, s);
+    int rc = build_one_view(L->row, true, L, Wsrc, ws, keep_dense_copy, s);
     if (rc != MST_OK) return rc;
-    rc = build_one_view(L->col, false, L, Wsrc, ws, s);
+    rc = build_one_view(L->col, false, L, Wsrc, ws, keep_dense_copy, s);
     if (rc != MST_OK) return rc;
     L->views_valid = true;
     L->row_stale = L->col_stale = false;
@@ -777,7 +794,7 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
         if (rc != MST_OK) return rc;
     }
     if (L->nnz > 0) {
-        k_scatter_dense<<<(unsigned)cdiv(L->nnz, 256), 256, 0, s>>>(L->vals, L->flat, L->nnz, L->Wd);
+        k_scatter_dense<<<(unsigned)cdiv(L->nnz, 256), 256, 0, s>>>(L->vals, L->flat, L->nnz, L->Wd, L->dense_live);
         MST_LAUNCH_CHECK();
     }
     L->Wd_valid = L->Wd_zeros = true;
@@ -785,23 +802,24 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
 }
 
 // new values into the entries of the row view (and the dense rows beside it) and / or of the col view, and into
-// a dense copy that is zero at every inactive position: one launch
-static int refresh_views(const mst_layer* L, bool row, bool col, bool dense, hipStream_t s) {
+// a dense copy that is zero at every inactive position: one launch.  late: the entries take the dense copy's values
+static int refresh_views(const mst_layer* L, bool row, bool col, bool dense, bool late, hipStream_t s) {
     if (L->nnz == 0 || (!row && !col && !dense)) return MST_OK;
     const View &r = L->row, &c = L->col;
     // about 1.5 slots per entry, four slots per thread; the kernel strides over whatever there is
     const unsigned nb = (unsigned)std::min<int64_t>(cdiv(L->nnz * 3 / 2 + 1, 1024), 4096);
     const unsigned rb = row ? nb : 0u, cb = col ? nb : 0u;
     const unsigned hb = row && L->heavy_on ? HEAVY_MAX : 0u, db = dense ? (unsigned)cdiv(L->nnz, 256) : 0u;
-    k_sync_views<<<rb + cb + hb + db, 256, 0, s>>>(
+    const auto kernel = late ? k_sync_views<true> : k_sync_views<false>;
+    kernel<<<rb + cb + hb + db, 256, 0, s>>>(
         L->vals, rb, cb, r.ptr, r.nseg, r.perm, reinterpret_cast<uint2*>(r.ent), c.ptr, c.nseg, c.perm,
-        reinterpret_cast<uint2*>(c.ent), L->heavy, L->rowptr, L->flat, L->I, L->Hd, hb, L->Wd, L->nnz);
+        reinterpret_cast<uint2*>(c.ent), L->heavy, L->rowptr, L->flat, L->I, L->Hd, hb, L->Wd, L->nnz, L->dense_live);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
 
-// A product is about to walk these (built) views: entries that missed a change of the values take it now,
-// once in a layer's life.  Products on other streams are ordered after mst_layer_sync_values, not after this
+// A product is about to walk these (built) views: entries that missed a hand-over take it now, once in a layer's
+// life.  They take what was handed over last, not what vals[] holds by now.  Products on other streams are ordered after mst_layer_sync_values, not after this
 // call, so it waits for the new entries before it says that they are there.  A recording cannot wait and runs
 // later or never: it takes the refresh with it and leaves the view stale for whoever walks it first.
 int ensure_fresh(const mst_layer* Lc, bool row, bool col, hipStream_t s) {
@@ -811,7 +829,7 @@ int ensure_fresh(const mst_layer* Lc, bool row, bool col, hipStream_t s) {
     row = row && L->row_stale;
     col = col && L->col_stale;
     if (!row && !col) return MST_OK;
-    const int rc = refresh_views(L, row, col, false, s);
+    const int rc = refresh_views(L, row, col, false, true, s);
     if (rc != MST_OK) return rc;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     MST_HIP(hipStreamIsCapturing(s, &capture));
@@ -877,6 +895,7 @@ int mst_layer_create(mst_layer_t** out, int O, int I, int64_t nnz_capacity, void
     L->rowptr = (int*)(b + c.rowptr);
     L->Wd = (float*)(b + c.Wd);
     L->walk_cost = (unsigned long long*)(b + c.cost);
+    L->dense_live = (int*)(b + c.cost + 16);
     L->heavy = (int*)(b + c.heavy);
     L->Hd = (float*)(b + c.Hd);
     auto init_view = [&](View& v, int R, int K, size_t optr, size_t oent, size_t operm, size_t omap, size_t opos) {
@@ -944,7 +963,7 @@ int mst_layer_export_dense(const mst_layer_t* L, float* W_dev, uint8_t* M_dev, m
         int rc = fill_u32(W_dev, 0u, L->N, s);
         if (rc != MST_OK) return rc;
         if (L->nnz > 0) {
-            k_scatter_dense<<<(unsigned)cdiv(L->nnz, 256), 256, 0, s>>>(L->vals, L->flat, L->nnz, W_dev);
+            k_scatter_dense<<<(unsigned)cdiv(L->nnz, 256), 256, 0, s>>>(L->vals, L->flat, L->nnz, W_dev, nullptr);
             MST_LAUNCH_CHECK();
         }
     }
@@ -969,7 +988,8 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     const bool dense = L->Wd_zeros && L->nnz > 0, views = L->nnz > 0 && L->views_valid;   // unbuilt views take the values when they are built
     L->Wd_valid = dense;
     bool row = views, col = views;
-    if (views && !(L->row_walked && L->col_walked)) {
+    if (dense && views && !(L->row_walked && L->col_walked)) {
+        // Views that nothing has walked are left out, since the dense copy holds the values for their first walk.
         // A recording refreshes every built view and changes no flag: its replays come at any time, between calls
         // that walk a view for the first time, and it has not run yet.
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -981,7 +1001,7 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
             L->col_stale |= !col;
         }
     }
-    return refresh_views(L, row, col, dense, s);
+    return refresh_views(L, row, col, dense, false, s);
 }
 
 int mst_layer_indices(const mst_layer_t* L, int32_t* flat_dev, mst_stream_t stream) {

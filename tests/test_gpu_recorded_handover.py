@@ -85,3 +85,63 @@ def test_a_recorded_handover_that_has_not_run_leaves_views_to_be_refreshed(mask)
         L.values().mul_(2.0)
         L.sync_values()
         assert rel_err(rig.fwd(X), 2.0 ** (k + 2) * Y1) <= TOL, k
+
+
+@pytest.mark.parametrize("mask", ["uniform", "powerlaw"])
+def test_a_views_first_walk_sees_what_was_handed_over(mask):
+    """Values changed after the last hand-over stay out of every product until the next one, whichever view is
+    walked, and for the first time or not."""
+    rig, X, dY, Y1, dX1 = _layer(mask)
+    L = rig.layer
+    _dense_copy_in_use(rig, X)
+    L.values().mul_(2.0)
+    L.sync_values()                                          # no view has been walked: left out
+    L.values().mul_(2.0)                                     # not handed over
+    assert rel_err(rig.fwd(X), 2.0 * Y1) <= TOL              # the dense product
+    L.set_path(mst.MST_PATH_SPARSE)
+    assert rel_err(rig.fwd(X), 2.0 * Y1) <= TOL
+    assert rel_err(rig.bwd_input(dY), 2.0 * dX1) <= TOL
+    L.sync_values()
+    assert rel_err(rig.fwd(X), 4.0 * Y1) <= TOL
+    assert rel_err(rig.bwd_input(dY), 4.0 * dX1) <= TOL
+    W, M = rig.export()
+    rig.layer.load_dense(dev(W), dev(M), rig.ws)             # no dense copy in use: every built view is refreshed
+    L.values().mul_(2.0)
+    L.sync_values()
+    L.values().mul_(2.0)
+    assert rel_err(rig.fwd(X), 8.0 * Y1) <= TOL
+    assert rel_err(rig.bwd_input(dY), 8.0 * dX1) <= TOL
+
+
+def test_a_recorded_first_walk_outlives_the_dense_copy_it_was_recorded_beside():
+    """A recording that takes the refresh of a view with it, replayed while the dense copy holds the values
+    handed over last and after the layer was loaded anew (the copy then holds old ones)."""
+    rig, X, dY, Y1, dX1 = _layer("uniform")
+    L, T = rig.layer, X.shape[0]
+    _dense_copy_in_use(rig, X)
+    L.values().mul_(2.0)
+    L.sync_values()
+    L.set_path(mst.MST_PATH_SPARSE)
+    Xd, Yg = dev(X), torch.empty((T, rig.O), dtype=torch.float32, device=DEV)
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        mst.mst_sparse_fc_fwd(L, Xd, Yg, T, mst.MST_F32, side)
+
+    def replayed():
+        graph.replay()
+        torch.cuda.synchronize()
+        return Yg.cpu().numpy()
+
+    L.values().mul_(2.0)                                     # not handed over
+    assert rel_err(replayed(), 2.0 * Y1) <= TOL
+    L.sync_values()
+    assert rel_err(replayed(), 4.0 * Y1) <= TOL
+    W, M = rig.export()
+    L.load_dense(dev(4.0 * W), dev(M), rig.ws)
+    assert rel_err(replayed(), 16.0 * Y1) <= TOL
+    L.values().mul_(2.0)
+    L.sync_values()
+    L.values().mul_(2.0)                                     # not handed over
+    assert rel_err(replayed(), 32.0 * Y1) <= TOL
+    assert rel_err(rig.fwd(X), 32.0 * Y1) <= TOL
