@@ -236,7 +236,8 @@ int mst_bwd_force_shape(int wavefronts_per_workgroup, int quads_per_wavefront);
  * operand element is split into two bfloat16 values (hi + lo, exact to 2^-17) while it is
  * staged, a product is hi*hi + hi*lo + lo*hi with fp32 accumulation; the result differs from
  * an fp32 product by less than 2^-16 per term.  Every other shape runs on a kernel of full fp32
- * precision (three bfloat16 values per element, exact; six products).  This hook pins, for all
+ * precision (three bfloat16 values per element, exact; six products, what they leave out is below
+ * 2^-24 of a term and of either sign).  This hook pins, for all
  * later calls of the process: 1 = the full-precision kernel (1064, 1128: with a 64 x 64 or a
  * 128 x 128 tile; 1032, 1096: the streaming form for small outputs, 32 x 32 or 64 x 64); 128, 256, 160 or 192 = the split kernel with the
  * workgroup tile 128 x 128, 256 x 256, 256 x 160 or 256 x 192 (where the shape is a multiple of

@@ -1,10 +1,17 @@
 // Dense products of any shape at full fp32 precision on the bf16 matrix cores.
 //
 // Every fp32 operand element is cut, while it is staged, into three bfloat16 values hi + mid + lo of
-// eight significant bits each: x = hi + mid + lo exactly (truncation: no rounding, no overflow).  A
-// product is hi.hi + hi.mid + mid.hi + mid.mid + hi.lo + lo.hi with fp32 accumulation; what is dropped
-// is below 2^-24 of it, less than the rounding of one fp32 product.  A bfloat16 operand is one
-// value, so bfloat16 x fp32 takes three products per term, all exact.
+// eight significant bits each, each the nearest to what is left: x = hi + mid + lo exactly (Henry, Tang and
+// Heinecke 2019, "Leveraging the bfloat16 Artificial Intelligence Datatype For Higher-Precision Computations"; below
+// 2^-110 the last part falls under bfloat16's smallest value).  A product is
+// hi.hi + hi.mid + mid.hi + mid.mid + hi.lo + lo.hi with fp32 accumulation; what is dropped is at most 2^-24 of it,
+// in either direction.  A bfloat16 operand is one value, so bfloat16 x fp32 takes three products per term, all exact.
+// Root mean square error of Y at 129 x 4099 -> 387 in units of 2^-24 sum |x w|, fp32 matrix instructions / 64 tile /
+// 128 tile: normal operands 0.47 / 0.29 / 0.41, all positive ones 16.0 / 8.1 / 10.0 (mean -0.2 / -0.7 / -1.4).
+// With truncated parts, which cost the same instructions, the dropped products all point to zero and are up to
+// eight times as large: 65.7 / 194 on the positive operands, nearly all of it the mean.
+// A value within 2^-9 of the largest finite one rounds to an infinity: its outputs come out as NaN and are
+// formed again (fp32_sum).
 //
 // C[M x N] = sum_k A'[k][m] B'[k][n]; each operand k-major (element (k, m) at src[k*ld + m]) or m-major
 // (src[m*ld + k]).  Serves the shapes whose tiles are not whole (an activation batch of any length, a
@@ -39,19 +46,19 @@ __device__ inline uint32_t ex_unit(int m, int u) {
     return (uint32_t)(rho * 64 + (((u ^ (rho >> 2) ^ (rho >> 4)) & 3) << 4));
 }
 
-// a pair of fp32 values as three words of two bfloat16 each
+// a pair of fp32 values as three words of two bfloat16 each.  The parts are rounded to nearest, so the lower
+// ones have either sign and half the size that truncation leaves: what the dropped products lose has no direction.
+// The third part is exact: 24 bits less 8 and a sign, twice.
 __device__ inline void cut_pair(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-    constexpr uint32_t UPPER = 0x07060302u;
-    const uint32_t a0 = __float_as_uint(x0), a1 = __float_as_uint(x1);
-    hi = __builtin_amdgcn_perm(a1, a0, UPPER);
-    const uint32_t b0 = __float_as_uint(x0 - __uint_as_float(a0 & 0xFFFF0000u)), b1 = __float_as_uint(x1 - __uint_as_float(a1 & 0xFFFF0000u));
-    mid = __builtin_amdgcn_perm(b1, b0, UPPER);
-    const float c0 = __uint_as_float(b0) - __uint_as_float(b0 & 0xFFFF0000u), c1 = __uint_as_float(b1) - __uint_as_float(b1 & 0xFFFF0000u);
-    lo = __builtin_amdgcn_perm(__float_as_uint(c1), __float_as_uint(c0), UPPER);
+    hi = cvt_pk_bf16(x0, x1);
+    const float b0 = x0 - __uint_as_float(hi << 16), b1 = x1 - __uint_as_float(hi & 0xFFFF0000u);
+    mid = cvt_pk_bf16(b0, b1);
+    lo = cvt_pk_bf16(b0 - __uint_as_float(mid << 16), b1 - __uint_as_float(mid & 0xFFFF0000u));
 }
 
-// The lower parts of an infinite value are inf - inf = NaN, so a sum with an infinite operand comes out as NaN
-// where fp32 products give an infinity.  An output that is NaN is therefore formed again by fp32
+// The lower parts of an infinite value are inf - inf = NaN (those of a finite one whose first part rounds to an
+// infinity the infinity of the other sign and NaN), so a sum with such an operand comes out as NaN where fp32
+// products give a number or an infinity.  An output that is NaN is therefore formed again by fp32
 // multiply-adds, up to the first term that makes it NaN by itself; no other output pays more than a compare.
 template <typename TA, bool A_KMAJOR, typename TB, bool B_KMAJOR>
 __device__ __forceinline__ float fp32_sum(const TA* __restrict__ A, int64_t lda, const TB* __restrict__ B, int64_t ldb, int m, int n,

@@ -111,3 +111,53 @@ def test_infinite_operands_as_fp32_products_give_them(mode, act):
     assert np.array_equal(np.isnan(Y), np.isnan(ref))
     assert np.array_equal(Y[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32))
     assert rel_err(Y[finite], ref[finite]) <= FP32
+
+
+@pytest.mark.parametrize("mode", [1032, 1064, 1096, 1128])
+def test_positive_operands_of_full_mantissas_leave_no_one_sided_error(mode):
+    """Terms of one sign and 24 significant bits: whatever a product drops must not point one way, or it adds up over
+    k.  Error in units of 2^-24 of the exact output.  Bounds: what the order of the fp32 sums leaves, about
+    sqrt(additions in a row) of random sign with a small mean from the matrix cores' alignment; measured mean 0.3 on the
+    streaming kernels (16 or 8 sums) and 1.4 through LDS (one sum), rms 1.7 and 10.  (Truncated parts: mean 0.8 and
+    194; fp32 matrix instructions: rms 16.)"""
+    T, I, O = 129, 4099, 130
+    print("case", T, I, O, mode, flush=True)
+    rng = np.random.default_rng(64)
+    X, W = (1.0 + rng.random((T, I))).astype(np.float32), (1.0 + rng.random((O, I))).astype(np.float32)
+    dY = (1.0 + rng.random((T, O))).astype(np.float32)
+    rig = Rig(W, np.ones((O, I), np.uint8), T, cap=O * I)
+    rig.layer.set_path(mst.MST_PATH_DENSE)
+    G = torch.full((O, I), float("nan"), dtype=torch.float32, device=DEV)
+    try:
+        mst.mst_gemm_force_fp32_mfma(mode)
+        Y, dX = rig.fwd(X), rig.bwd_input(dY)
+        mst.mst_dense_grad(dev(dY), dev(X), G, T, O, I, mst.MST_F32, None)
+        torch.cuda.synchronize()
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
+    X, W, dY = X.astype(np.float64), W.astype(np.float64), dY.astype(np.float64)
+    mean, rms = (0.5, 2.5) if mode in (1032, 1096) else (3.0, 16.0)
+    for name, got, ref in (("Y", Y, X @ W.T), ("dX", dX, dY @ W), ("G", G.cpu().numpy(), dY.T @ X)):
+        e = (got / ref - 1.0) * 2.0 ** 24
+        print(name, "mean %.2f rms %.2f" % (e.mean(), np.sqrt((e * e).mean())), flush=True)
+        assert abs(e.mean()) <= mean and np.sqrt((e * e).mean()) <= rms, name
+
+
+@pytest.mark.parametrize("mode", [1032, 1064, 1096, 1128])
+def test_values_next_to_the_largest_finite_one(mode):
+    """Their first part rounds to an infinity; the products are what fp32 gives."""
+    T, I, O = 65, 100, 70
+    print("case", T, I, O, mode, flush=True)
+    X = synth.normal(65, 1, (T, I)).astype(np.float32)
+    W = synth.normal(65, 3, (O, I), 0.02).astype(np.float32)
+    X[3, 7], X[64, 99] = np.finfo(np.float32).max, -np.finfo(np.float32).max
+    rig = Rig(W, np.ones((O, I), np.uint8), T, cap=O * I)
+    rig.layer.set_path(mst.MST_PATH_DENSE)
+    try:
+        mst.mst_gemm_force_fp32_mfma(mode)
+        Y = rig.fwd(X)
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
+    ref = X.astype(np.float64) @ W.T.astype(np.float64)
+    for rows in ([3, 64], [t for t in range(T) if t not in (3, 64)]):
+        assert rel_err(Y[rows], ref[rows]) <= FP32
