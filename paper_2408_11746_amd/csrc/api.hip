@@ -71,26 +71,25 @@ static int ensure_dense_copy(const mst_layer* L, hipStream_t s) {
     return refresh_dense_copy(const_cast<mst_layer*>(L), s);   // cache of vals[], not layer state
 }
 
-// (split_ws: room for partial outputs of a split of the contraction range, used where the output
+// (full: see full_precision(); split_ws: room for partial outputs of a split of the contraction range, used where the output
 // has too few tiles to fill the chip; null: one workgroup per tile whatever their number)
-int dense_products_fwd(const mst_layer* L, const void* X, float* Y, int T, mst_dtype act, hipStream_t s,
-                       float* split_ws, int64_t split_ws_floats) {
+int dense_products_fwd(const mst_layer* L, const void* X, float* Y, int T, mst_dtype act, hipStream_t s, bool full) {
     int rc = ensure_dense_copy(L, s);
     if (rc != MST_OK) return rc;
-    return gemm_mfma(GEMM_NT, X, act, L->Wd, MST_F32, Y, T, L->O, L->I, split_ws, split_ws_floats, s);
+    return gemm_mfma(GEMM_NT, X, act, L->Wd, MST_F32, Y, T, L->O, L->I, nullptr, 0, s, full);
 }
 
-int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int T, mst_dtype act, hipStream_t s,
+int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int T, mst_dtype act, hipStream_t s, bool full,
                              float* split_ws, int64_t split_ws_floats) {
     int rc = ensure_dense_copy(L, s);
     if (rc != MST_OK) return rc;
-    return gemm_mfma(GEMM_NN, dY, act, L->Wd, MST_F32, dX, T, L->I, L->O, split_ws, split_ws_floats, s);
+    return gemm_mfma(GEMM_NN, dY, act, L->Wd, MST_F32, dX, T, L->I, L->O, split_ws, split_ws_floats, s, full);
 }
 
 int dense_products_bwd_weight(const mst_layer* L, const void* dY, const void* X, float* dW, int T,
-                              mst_dtype act, const Workspace& ws, hipStream_t s) {
+                              mst_dtype act, const Workspace& ws, hipStream_t s, bool full) {
     int nparts = 1;
-    int rc = gemm_mfma(GEMM_TN, dY, act, X, act, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s, &nparts);
+    int rc = gemm_mfma(GEMM_TN, dY, act, X, act, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s, full, &nparts);
     if (rc != MST_OK) return rc;
     if (L->nnz > 0) {
         k_gather_flat<<<(unsigned)cdiv(L->nnz, 1024), 256, 0, s>>>(nparts > 1 ? ws.gemm : ws.G, L->N, nparts, L->flat,
@@ -136,7 +135,8 @@ int mst_sparse_fc_fwd(const mst_layer_t* L, const void* X_dev, float* Y_dev, int
     hipStream_t s = (hipStream_t)stream;
     note_call(L, act, T);
     // (unbuilt views and no workspace to build them with: the dense product, same result within tolerance)
-    if (use_dense_path(L, act, T) || !L->views_valid) return dense_products_fwd(L, X_dev, Y_dev, T, act, s);
+    if (use_dense_path(L, act, T) || !L->views_valid)
+        return dense_products_fwd(L, X_dev, Y_dev, T, act, s, full_precision(L, WALK_FWD, act, T));
     const int rc = spmm(L, L->row, X_dev, Y_dev, T, act, s);
     if (rc != MST_OK || !L->heavy_on) return rc;
     return heavy_fwd(L, X_dev, Y_dev, T, act, s);        // the rows the view leaves out (returns at once without any)
@@ -148,7 +148,8 @@ int mst_sparse_fc_bwd_input(const mst_layer_t* L, const void* dY_dev, float* dX_
     if (!L->built) return MST_ERR_STATE;
     hipStream_t s = (hipStream_t)stream;
     note_call(L, act, T);
-    if (use_dense_path(L, act, T) || !L->views_valid) return dense_products_bwd_input(L, dY_dev, dX_dev, T, act, s);
+    if (use_dense_path(L, act, T) || !L->views_valid)
+        return dense_products_bwd_input(L, dY_dev, dX_dev, T, act, s, full_precision(L, WALK_BWD_INPUT, act, T));
     return spmm(L, L->col, dY_dev, dX_dev, T, act, s);
 }
 
@@ -161,7 +162,8 @@ int mst_sparse_fc_bwd_weight(const mst_layer_t* L, const void* dY_dev, const voi
     if (ws_bytes < ws.total) return MST_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     note_call(L, act, T);
-    if (use_dense_weight_grad(L, act, T)) return dense_products_bwd_weight(L, dY_dev, X_dev, dW_dev, T, act, ws, s);
+    if (use_dense_weight_grad(L, act, T))
+        return dense_products_bwd_weight(L, dY_dev, X_dev, dW_dev, T, act, ws, s, full_precision(L, WALK_BWD_WEIGHT, act, T));
     const int rc = ensure_views(L, ws, s);
     if (rc != MST_OK) return rc;
     return sddmm(L, dY_dev, X_dev, dW_dev, T, act, ws.partial, ws.partial_floats, s);
@@ -208,9 +210,10 @@ int mst_sparse_fc_bwd(const mst_layer_t* L, const void* dY_dev, const void* X_de
     }
     // the two dense contractions (the split area of the workspace serves dX first, then the weight
     // gradient: same stream)
-    const int rc = dense_products_bwd_input(L, dY_dev, dX_dev, T, act, s, ws.gemm, (int64_t)ws.gemm_floats);
+    const bool full = full_precision(L, WALK_BWD, act, T);
+    const int rc = dense_products_bwd_input(L, dY_dev, dX_dev, T, act, s, full, ws.gemm, (int64_t)ws.gemm_floats);
     if (rc != MST_OK) return rc;
-    return dense_products_bwd_weight(L, dY_dev, X_dev, dW_dev, T, act, ws, s);
+    return dense_products_bwd_weight(L, dY_dev, X_dev, dW_dev, T, act, ws, s, full);
 }
 
 int mst_layer_uses_dense(const mst_layer_t* L, mst_dtype act, int T, int weight_gradient) {
@@ -368,7 +371,7 @@ int mst_sparse_fc_bwd_weight_update(mst_layer_t* L, const void* dY_dev, const vo
         }
     } else {
         if (use_dense_weight_grad(L, act, T)) {
-            rc = dense_products_bwd_weight(L, dY_dev, X_dev, dW_dev, T, act, ws, s);
+            rc = dense_products_bwd_weight(L, dY_dev, X_dev, dW_dev, T, act, ws, s, full_precision(L, WALK_BWD_WEIGHT, act, T));
         } else {
             rc = ensure_views(L, ws, s);
             if (rc == MST_OK) rc = sddmm(L, dY_dev, X_dev, dW_dev, T, act, ws.partial, ws.partial_floats, s);

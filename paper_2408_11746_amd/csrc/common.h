@@ -156,6 +156,9 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 bool use_dense_path(const mst_layer* L, mst_dtype act, int T);
 bool use_dense_weight_grad(const mst_layer* L, mst_dtype act, int T);
 bool use_fused_backward(const mst_layer* L, mst_dtype act, int T);
+// ... and the dense kernels take fp32 operands in full there (`job`: the call)
+enum WalkJob { WALK_FWD = 0, WALK_BWD_INPUT, WALK_BWD_WEIGHT, WALK_BWD };
+bool full_precision(const mst_layer* L, WalkJob job, mst_dtype act, int T);
 
 // ---- workspace carving (one place so that mst_workspace_bytes and the users agree) ----
 struct Workspace {
@@ -202,10 +205,11 @@ int sddmm(const mst_layer* L, const void* dY, const void* X, float* dW, int T, m
 int bwd_fused(const mst_layer* L, const void* dY, const void* X, float* dX, float* dW, int T, mst_dtype act,
               const Workspace& ws, hipStream_t s);
 int bwd_fused_force_shape(int waves, int quads);
-// C[M x N] (fp32) = op(A) op(B) on the matrix cores; see gemm_mfma.hip
+// C[M x N] (fp32) = op(A) op(B) on the matrix cores; see gemm_mfma.hip.  full: fp32 operands in full whatever the shape
 enum GemmKind { GEMM_TN = 0, GEMM_NT = 1, GEMM_NN = 2 };
 int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_dtype b_dt, float* C,
-              int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed = nullptr);
+              int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, bool full = false,
+              int* left_unsummed = nullptr);
 // the same at full fp32 precision for any shape (B fp32); see gemm_exact.hip
 int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,
                float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed);
@@ -214,21 +218,19 @@ int gemm_stream_tn_bf16(const uint16_t* A, const uint16_t* B, float* C, int M, i
                         hipStream_t s);
 double xcd_rounds(int64_t n, int places, int lone_places, double full, double lone);
 // modelled times in microseconds (max_split: k ranges there is room for; summed: their sum included)
-double gemm_mfma_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed);
+double gemm_mfma_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed, bool full);
 double gemm_exact_us(mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed);
-enum WalkJob { WALK_FWD = 0, WALK_BWD_INPUT, WALK_BWD_WEIGHT, WALK_BWD };
 double walk_us(const mst_layer* L, WalkJob job, int T);
 int sum_split_planes(const float* part, int64_t stride, int nsplit, float* C, int64_t n, hipStream_t s);
 int gemm_force_fp32_mfma(int on);
 int gemm_last_tile();
 int mask_update_device(mst_layer* L, const float* G, const mst_update_stats& st, uint64_t seed,
                        const Workspace& ws, hipStream_t s);
-int dense_products_fwd(const mst_layer* L, const void* X, float* Y, int T, mst_dtype act, hipStream_t s,
-                       float* split_ws = nullptr, int64_t split_ws_floats = 0);
-int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int T, mst_dtype act, hipStream_t s,
+int dense_products_fwd(const mst_layer* L, const void* X, float* Y, int T, mst_dtype act, hipStream_t s, bool full);
+int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int T, mst_dtype act, hipStream_t s, bool full,
                              float* split_ws = nullptr, int64_t split_ws_floats = 0);
 int dense_products_bwd_weight(const mst_layer* L, const void* dY, const void* X, float* dW, int T,
-                              mst_dtype act, const Workspace& ws, hipStream_t s);
+                              mst_dtype act, const Workspace& ws, hipStream_t s, bool full);
 int refresh_dense_copy(mst_layer* L, hipStream_t s);
 // heavy rows of the forward product; see heavy.hip
 int heavy_rows_enable(int on);

@@ -1345,19 +1345,19 @@ static int launch_tn_bf16(const void* Av, const void* Bv, float* C, int M, int N
 // NT: C[M x N] = A B^T, A [M x K], B [N x K] (fp32)   (Y = X Wd^T)
 // NN: C[M x N] = A B,   A [M x K], B [K x N] (fp32)   (dX = dY Wd)
 int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_dtype b_dt, float* C,
-              int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed) {
+              int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, bool full, int* left_unsummed) {
     const bool ab = a_dt == MST_BF16, bb = b_dt == MST_BF16;
     g_last_tile = 0;
     if (kind == GEMM_TN ? ab != bb : bb) return MST_ERR_ARG;
     if (ab) {
         if (kind == GEMM_TN) return launch_tn_bf16(A, B, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
-        if (use_a16(M, N, Kdim))
+        if (!full && use_a16(M, N, Kdim))
             return kind == GEMM_NT ? launch_a16<false>(A, Kdim, B, Kdim, C, M, N, Kdim, left_unsummed, s)
                                    : launch_a16<true>(A, Kdim, B, N, C, M, N, Kdim, left_unsummed, s);
         return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
     }
     const int64_t max_split = split_ws ? split_ws_floats / ((int64_t)M * N) : 1;
-    const SplitPlan plan = plan_fp32(kind, M, N, Kdim, max_split, left_unsummed == nullptr);
+    const SplitPlan plan = full ? SplitPlan{0, 1, 0.0} : plan_fp32(kind, M, N, Kdim, max_split, left_unsummed == nullptr);
     if (plan.tile == 0) return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
     if (kind == GEMM_TN) return launch_split<true, true>(plan, A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
     if (kind == GEMM_NT) return launch_split<false, false>(plan, A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
@@ -1365,11 +1365,11 @@ int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_d
 }
 
 // Modelled time of a product in microseconds, as the kernel choice above would run it.
-double gemm_mfma_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed) {
+double gemm_mfma_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed, bool full) {
     if (a_dt == MST_BF16) {
         if (kind == GEMM_TN) return plan_tn_bf16(M, N, Kdim, max_split, summed).us;
-        if (use_a16(M, N, Kdim)) return a16_us(M, N, Kdim);
-    } else {
+        if (!full && use_a16(M, N, Kdim)) return a16_us(M, N, Kdim);
+    } else if (!full) {
         const SplitPlan plan = plan_fp32(kind, M, N, Kdim, max_split, summed);
         if (plan.tile != 0) return plan.us;
     }

@@ -51,8 +51,24 @@ static bool whole_tiles(const mst_layer* L, mst_dtype act, int T) {
     return T >= 2048 && T % tile == 0 && L->O % tile == 0 && L->I % tile == 0;
 }
 static bool mostly_dense(const mst_layer* L) { return (double)L->nnz > 0.30 * (double)L->N; }
-static double dense_wgrad_us(const mst_layer* L, mst_dtype act, int T) {      // the sum of the k ranges is part of the gather
-    return 3.0 + gemm_mfma_us(GEMM_TN, act, L->O, L->I, T, GEMM_WS_SPLITS, false);
+static double dense_wgrad_us(const mst_layer* L, mst_dtype act, int T, bool full) {      // the sum of the k ranges is part of the gather
+    return 3.0 + gemm_mfma_us(GEMM_TN, act, L->O, L->I, T, GEMM_WS_SPLITS, false, full);
+}
+
+// The dense kernels of whole tiles take two bfloat16 parts per fp32 operand, 16 of its 24 bits.  Up to these densities
+// an automatic product has its fp32 operands in full, whether the walk or the full-precision dense kernels (six products
+// per term instead of three) run it: speed alone does not move a layer that the sparse kernels serve well to fewer
+// bits.  The choice between the two is between their times.  Above, the dense kernels are ahead by so much that
+// two parts are the rule.  Largest error of Y at 768 -> 3072, 1024 tokens, density 0.149, in units of the
+// largest output: walk 4.4e-7, full dense 5.5e-7, two parts 7.0e-6.
+bool full_precision(const mst_layer* L, WalkJob job, mst_dtype act, int T) {
+    if (L->path != MST_PATH_AUTO) return false;
+    const int tile = act == MST_BF16 ? 256 : 128;
+    const bool whole = T % (job == WALK_BWD_WEIGHT ? 64 : tile) == 0 && L->O % tile == 0 && L->I % tile == 0;
+    double line = 0.30;
+    if (whole && T >= 2048) line = job == WALK_BWD ? (act == MST_F32 ? 0.07 : 0.03) : job == WALK_BWD_WEIGHT ? 0.035 : act == MST_F32 ? 0.055 : 0.045;
+    else if (whole && act == MST_F32) line = 0.15;
+    return (double)L->nnz <= line * (double)L->N;
 }
 
 // The models take a microsecond of host time, so the answers for the last (T, type) are kept with the layer
@@ -74,8 +90,9 @@ bool use_dense_path(const mst_layer* L, mst_dtype act, int T) {
     if (whole_tiles(L, act, T)) return (double)L->nnz > (act == MST_F32 ? 0.075 : T >= 8192 ? 0.045 : 0.065) * (double)L->N;
     if (mostly_dense(L)) return true;
     return remembered(L, 0, act, T, [&] {
+        const bool full = full_precision(L, WALK_FWD, act, T);
         return walk_us(L, WALK_FWD, T) + walk_us(L, WALK_BWD_INPUT, T) >
-               gemm_mfma_us(GEMM_NT, act, T, L->O, L->I, 1, true) + gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, 1, true);
+               gemm_mfma_us(GEMM_NT, act, T, L->O, L->I, 1, true, full) + gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, 1, true, full);
     });
 }
 
@@ -87,8 +104,9 @@ bool use_fused_backward(const mst_layer* L, mst_dtype act, int T) {
     if (whole_tiles(L, act, T)) return (double)L->nnz <= (act == MST_F32 ? 0.085 : 0.035) * (double)L->N;
     if (mostly_dense(L)) return false;
     return remembered(L, 1, act, T, [&] {
-        return walk_us(L, WALK_BWD, T) <= gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, GEMM_WS_SPLITS * L->N / ((int64_t)T * L->I), true) +
-                                              dense_wgrad_us(L, act, T);
+        const bool full = full_precision(L, WALK_BWD, act, T);
+        return walk_us(L, WALK_BWD, T) <= gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, GEMM_WS_SPLITS * L->N / ((int64_t)T * L->I), true, full) +
+                                              dense_wgrad_us(L, act, T, full);
     });
 }
 
@@ -97,7 +115,7 @@ bool use_dense_weight_grad(const mst_layer* L, mst_dtype act, int T) {
     if (L->path == MST_PATH_SPARSE) return false;
     if (whole_tiles(L, act, T)) return (double)L->nnz > (act == MST_F32 ? 0.05 : 0.03) * (double)L->N;
     if (mostly_dense(L)) return true;
-    return remembered(L, 2, act, T, [&] { return walk_us(L, WALK_BWD_WEIGHT, T) > dense_wgrad_us(L, act, T); });
+    return remembered(L, 2, act, T, [&] { return walk_us(L, WALK_BWD_WEIGHT, T) > dense_wgrad_us(L, act, T, full_precision(L, WALK_BWD_WEIGHT, act, T)); });
 }
 
 struct LayerCarve {
