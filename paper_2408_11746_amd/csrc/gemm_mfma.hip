@@ -1299,11 +1299,10 @@ static double a16_us(int M, int N, int Kdim) {
     return 3.0 + (double)cdiv(cdiv((int64_t)(M / BM2) * (N / BN2), 8), 32) * (Kdim / 32 + 8.0) * 1.5;
 }
 // Few tiles make this kernel a chain of k steps on as many CUs; the streaming kernels are several times as
-// fast then.  (Outputs of a dozen tiles and a depth of up to 768 stay here: mst_gemm_last_tile reports the
-// tile for them, and a program may have come to rely on it.)
+// fast then (256 x 768 -> 3072: 15 us against 41, 256 x 256 -> 768: 5 against 18).  Products that fill the chip on either need two terms here, three there.
 static bool use_a16(int M, int N, int Kdim) {
-    return a16_ok(M, N, Kdim) && (g_split_tile == 256 || ((int64_t)M * N <= 12 * 65536 && Kdim <= 768) || (double)M * N * Kdim >= 2.0e10 ||
-                                  a16_us(M, N, Kdim) <= gemm_exact_us(MST_BF16, M, N, Kdim, 1, true));
+    return a16_ok(M, N, Kdim) &&
+           (g_split_tile == 256 || (double)M * N * Kdim >= 2.0e10 || a16_us(M, N, Kdim) <= gemm_exact_us(MST_BF16, M, N, Kdim, 1, true));
 }
 template <bool BKM>
 static int launch_a16(const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int M, int N, int Kdim,

@@ -405,8 +405,8 @@ def test_bf16_dense_gradient_on_both_workgroup_tiles(T, I, O):
 def test_dense_products_with_bf16_activations_on_the_256_tile(T, I, O):
     """Y and dX of a dense-path layer with bfloat16 activations on whole 256 x 256 tiles: the
     activations go to the matrix cores as they are, the fp32 weights as bf16 hi + lo (two
-    products per term).  Against the oracle on the same bfloat16 values, and against the fp32
-    MFMA kernel that serves ragged shapes (pinned by the hook)."""
+    products per term), pinned by the hook, since small outputs have faster kernels.  Against the oracle
+    on the same bfloat16 values, beside the full-precision kernels and the automatic choice."""
     print("case", T, I, O, flush=True)
     W = synth.normal(47, 3, (O, I), 0.02)
     W = (W * np.exp2(synth.normal(47, 8, W.shape) * 3)).astype(np.float32)     # weights over several orders of magnitude
@@ -426,15 +426,18 @@ def test_dense_products_with_bf16_activations_on_the_256_tile(T, I, O):
         return Y.cpu().numpy(), dX.cpu().numpy(), ty, tx
 
     try:
+        mst.mst_gemm_force_fp32_mfma(256)
         Y, dX, ty, tx = run()
         mst.mst_gemm_force_fp32_mfma(1)
         Y32, dX32, _, _ = run()
+        mst.mst_gemm_force_fp32_mfma(0)
+        Y0, dX0, _, _ = run()                        # whichever kernel the sizes pick
     finally:
         mst.mst_gemm_force_fp32_mfma(0)
     # Y is O wide with depth I, dX is I wide with depth O: whole tiles and a depth that is a multiple of 32
     assert ty == (256 if O % 256 == 0 and I % 32 == 0 else 0)
     assert tx == (256 if I % 256 == 0 and O % 32 == 0 else 0)
-    for name, got, got32, ref in (("Y", Y, Y32, opr.fc_fwd(Xf, W, M)), ("dX", dX, dX32, opr.fc_bwd_input(dYf, W, M))):
-        e, e32 = rel_err(got, ref), rel_err(got32, ref)
-        print(name, "err %.3g  fp32-mfma err %.3g" % (e, e32), flush=True)
-        assert e <= 2e-5 and e32 <= TOL
+    for name, got, got32, got0, ref in (("Y", Y, Y32, Y0, opr.fc_fwd(Xf, W, M)), ("dX", dX, dX32, dX0, opr.fc_bwd_input(dYf, W, M))):
+        e, e32, e0 = rel_err(got, ref), rel_err(got32, ref), rel_err(got0, ref)
+        print(name, "err %.3g  full-precision err %.3g  automatic err %.3g" % (e, e32, e0), flush=True)
+        assert e <= 2e-5 and e32 <= 2e-6 and e0 <= 2e-5
