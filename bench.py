@@ -319,16 +319,13 @@ def run_block(args, name, mst, synth, torch, lds_peak, with_cpu_baseline):
         L.layer.set_path({"auto": mst.MST_PATH_AUTO, "sparse": mst.MST_PATH_SPARSE, "dense": mst.MST_PATH_DENSE}[args.path])
     # which contraction serves each call (asked of the library, not re-derived here)
     dense_prod = {L.name: L.layer.uses_dense(L.act, T) for L in layers}
+    dense_dx = {L.name: L.layer.uses_dense(L.act, T, 3) for L in layers}
     dense_wgrad = {L.name: L.layer.uses_dense(L.act, T, True) for L in layers}
     dense_bwd = {L.name: L.layer.uses_dense(L.act, T, 2) for L in layers}      # the one-call backward's own rule
 
     def path_of(L, kind):
-        a, b = dense_prod[L.name], dense_wgrad[L.name]
-        if kind in ("fwd", "bwd_input"):
-            return "dense-mfma" if a else "sparse"
-        if kind == "bwd_weight":
-            return "dense-mfma" if b else "sparse"
-        return "dense-mfma" if dense_bwd[L.name] else "sparse"
+        by = {"fwd": dense_prod, "bwd_input": dense_dx, "bwd_weight": dense_wgrad, "bwd": dense_bwd}[kind]
+        return "dense-mfma" if by[L.name] else "sparse"
 
     if args.pmc_probe:
         pmc_probe_block(args, mst, torch, layers, T, stream)
@@ -433,7 +430,7 @@ def run_block(args, name, mst, synth, torch, lds_peak, with_cpu_baseline):
         "k_gemm_a16_256 (bfloat16 activations x fp32 weights as bf16 hi + lo, 2 products per term)"
     wgrad_dense_k = ("k_gemm_tn_bf16" if act == "bf16" else "k_gemm_split256<TN> / k_gemm_split<TN>") + " + k_gather_flat"
     kernel = {"fwd": gemm_k if dp else spmm_k,
-              "bwd_input": gemm_k if dp else spmm_k,
+              "bwd_input": gemm_k if dense_dx[dL.name] else spmm_k,
               "bwd_weight": wgrad_dense_k if dw else "k_walk_dw + k_walk_reduce",
               "bwd": "k_walk<OUT, DW> + k_walk_reduce" if not dense_bwd[dL.name] else
                      "%s, then %s" % (gemm_k, wgrad_dense_k)}[drow["call"]]

@@ -152,12 +152,12 @@ inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
-// true when a layer of this density should run the masked dense MFMA kernels
-bool use_dense_path(const mst_layer* L, mst_dtype act, int T);
+// true when a layer of this density should run the masked dense MFMA kernels (`job`: the product)
+enum WalkJob { WALK_FWD = 0, WALK_BWD_INPUT, WALK_BWD_WEIGHT, WALK_BWD };
+bool use_dense_path(const mst_layer* L, WalkJob job, mst_dtype act, int T);
 bool use_dense_weight_grad(const mst_layer* L, mst_dtype act, int T);
 bool use_fused_backward(const mst_layer* L, mst_dtype act, int T);
-// ... and the dense kernels take fp32 operands in full there (`job`: the call)
-enum WalkJob { WALK_FWD = 0, WALK_BWD_INPUT, WALK_BWD_WEIGHT, WALK_BWD };
+// ... and the dense kernels take fp32 operands in full there
 bool full_precision(const mst_layer* L, WalkJob job, mst_dtype act, int T);
 
 // ---- workspace carving (one place so that mst_workspace_bytes and the users agree) ----

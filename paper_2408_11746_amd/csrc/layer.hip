@@ -72,28 +72,33 @@ bool full_precision(const mst_layer* L, WalkJob job, mst_dtype act, int T) {
 }
 
 // The models take a microsecond of host time, so the answers for the last (T, type) are kept with the layer
-// until its active set changes: bits 0-2 known, 3-5 the answers, 6 the type, 8.. T.
+// until its active set changes: bits 0-3 known, 4-7 the answers (bit = WalkJob), 8 the type, 9.. T.
 template <typename F>
-static bool remembered(const mst_layer* L, int which, mst_dtype act, int T, F&& decide) {
+static bool remembered(const mst_layer* L, WalkJob job, mst_dtype act, int T, F&& decide) {
     std::atomic<uint64_t>& word = const_cast<mst_layer*>(L)->choice;
-    const uint64_t key = (uint64_t)T << 8 | (uint64_t)(act == MST_BF16) << 6, w = word.load(std::memory_order_relaxed);
-    const bool mine = (w & ~(uint64_t)0x3F) == key;
-    if (mine && (w >> which & 1)) return w >> (3 + which) & 1;
+    const uint64_t key = (uint64_t)T << 9 | (uint64_t)(act == MST_BF16) << 8, w = word.load(std::memory_order_relaxed);
+    const bool mine = (w & ~(uint64_t)0xFF) == key;
+    if (mine && (w >> job & 1)) return w >> (4 + job) & 1;
     const bool yes = decide();
-    word.store((mine ? w : key) | (uint64_t)1 << which | (uint64_t)yes << (3 + which), std::memory_order_relaxed);
+    word.store((mine ? w : key) | (uint64_t)1 << job | (uint64_t)yes << (4 + job), std::memory_order_relaxed);
     return yes;
 }
 
-bool use_dense_path(const mst_layer* L, mst_dtype act, int T) {
+static double dense_us(const mst_layer* L, WalkJob job, mst_dtype act, int T) {       // Y or dX
+    const bool full = full_precision(L, job, act, T);
+    return job == WALK_FWD ? gemm_mfma_us(GEMM_NT, act, T, L->O, L->I, 1, true, full)
+                           : gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, 1, true, full);
+}
+
+// Y and dX, each for itself (job WALK_FWD or WALK_BWD_INPUT): a layer that is wide on one side has its cross-over at
+// different densities for the two (3392 -> 448, 504 tokens, 0.09: dX 8.5 us sparse, 15.6 dense; Y 27 dense, a model's 47
+// sparse).  One answer for both cost one of them more than 15 % at a tenth of 13800 shapes, by the models.
+bool use_dense_path(const mst_layer* L, WalkJob job, mst_dtype act, int T) {
     if (L->path == MST_PATH_DENSE) return true;
     if (L->path == MST_PATH_SPARSE) return false;
     if (whole_tiles(L, act, T)) return (double)L->nnz > (act == MST_F32 ? 0.075 : T >= 8192 ? 0.045 : 0.065) * (double)L->N;
     if (mostly_dense(L)) return true;
-    return remembered(L, 0, act, T, [&] {
-        const bool full = full_precision(L, WALK_FWD, act, T);
-        return walk_us(L, WALK_FWD, T) + walk_us(L, WALK_BWD_INPUT, T) >
-               gemm_mfma_us(GEMM_NT, act, T, L->O, L->I, 1, true, full) + gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, 1, true, full);
-    });
+    return remembered(L, job, act, T, [&] { return walk_us(L, job, T) > dense_us(L, job, act, T); });
 }
 
 // The one-call backward: one walk for both gradients, or the two dense products (a sparse dX beside a
@@ -103,7 +108,7 @@ bool use_fused_backward(const mst_layer* L, mst_dtype act, int T) {
     if (L->path == MST_PATH_SPARSE) return true;
     if (whole_tiles(L, act, T)) return (double)L->nnz <= (act == MST_F32 ? 0.085 : 0.035) * (double)L->N;
     if (mostly_dense(L)) return false;
-    return remembered(L, 1, act, T, [&] {
+    return remembered(L, WALK_BWD, act, T, [&] {
         const bool full = full_precision(L, WALK_BWD, act, T);
         return walk_us(L, WALK_BWD, T) <= gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, GEMM_WS_SPLITS * L->N / ((int64_t)T * L->I), true, full) +
                                               dense_wgrad_us(L, act, T, full);
@@ -115,7 +120,7 @@ bool use_dense_weight_grad(const mst_layer* L, mst_dtype act, int T) {
     if (L->path == MST_PATH_SPARSE) return false;
     if (whole_tiles(L, act, T)) return (double)L->nnz > (act == MST_F32 ? 0.05 : 0.03) * (double)L->N;
     if (mostly_dense(L)) return true;
-    return remembered(L, 2, act, T, [&] { return walk_us(L, WALK_BWD_WEIGHT, T) > dense_wgrad_us(L, act, T, full_precision(L, WALK_BWD_WEIGHT, act, T)); });
+    return remembered(L, WALK_BWD_WEIGHT, act, T, [&] { return walk_us(L, WALK_BWD_WEIGHT, T) > dense_wgrad_us(L, act, T, full_precision(L, WALK_BWD_WEIGHT, act, T)); });
 }
 
 struct LayerCarve {
@@ -870,12 +875,19 @@ int ensure_views(const mst_layer* Lc, const Workspace& ws, hipStream_t s) {
 }
 
 // After an update: will a sparse kernel walk the views?  Judged at the batch size and type of
-// the last product call; a layer that has seen none yet, or is pinned to the sparse kernels, says yes.
+// the last product call; a layer that has seen none yet, or is pinned to the sparse kernels, says yes.  Y and dX are
+// judged together: both views are built or none, and where only one of the two gains by less than the other loses
+// the views are not worth their build.
 bool views_wanted(const mst_layer* L) {
     if (L->path == MST_PATH_SPARSE) return true;
     if (L->path == MST_PATH_DENSE) return false;
     if (L->hint_T <= 0) return true;
-    return !(use_dense_path(L, (mst_dtype)L->hint_act, L->hint_T) && use_dense_weight_grad(L, (mst_dtype)L->hint_act, L->hint_T));
+    const mst_dtype act = (mst_dtype)L->hint_act;
+    const int T = L->hint_T;
+    const bool y = use_dense_path(L, WALK_FWD, act, T), dx = use_dense_path(L, WALK_BWD_INPUT, act, T);
+    const bool both = y == dx ? y : walk_us(L, WALK_FWD, T) + walk_us(L, WALK_BWD_INPUT, T) >
+                                        dense_us(L, WALK_FWD, act, T) + dense_us(L, WALK_BWD_INPUT, act, T);
+    return !(both && use_dense_weight_grad(L, act, T));
 }
 
 }  // namespace mst
