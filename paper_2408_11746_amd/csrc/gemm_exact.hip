@@ -53,7 +53,8 @@ __device__ inline void cut_pair(float x0, float x1, uint32_t& hi, uint32_t& mid,
     hi = cvt_pk_bf16(x0, x1);
     const float b0 = x0 - __uint_as_float(hi << 16), b1 = x1 - __uint_as_float(hi & 0xFFFF0000u);
     mid = cvt_pk_bf16(b0, b1);
-    lo = cvt_pk_bf16(b0 - __uint_as_float(mid << 16), b1 - __uint_as_float(mid & 0xFFFF0000u));
+    const float c0 = b0 - __uint_as_float(mid << 16), c1 = b1 - __uint_as_float(mid & 0xFFFF0000u);
+    lo = __builtin_amdgcn_perm(__float_as_uint(c1), __float_as_uint(c0), 0x07060302u);
 }
 
 // The lower parts of an infinite value are inf - inf = NaN (those of a finite one whose first part rounds to an
