@@ -59,6 +59,7 @@ struct WalkSide {
     const int* ptr;
     const uint4* ent;
     const int* rowmap;
+    const int *perm, *rowpos;    // read for outputs that come out as NaN (OUT)
     int K, KC, R, NBpad, nchunk, nslab;
 };
 struct WalkArgs {
@@ -161,6 +162,63 @@ __device__ inline float sum8_pair(float a, float b) {
         "v_add_f32_dpp %0, %0, %0 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
         : "=&v"(r) : "v"(a), "v"(b));
     return r;
+}
+
+template <typename TIn>
+__device__ inline float element(const TIn* p);
+template <>
+__device__ inline float element<float>(const float* p) { return *p; }
+template <>
+__device__ inline float element<uint16_t>(const uint16_t* p) { return __uint_as_float((uint32_t)*p << 16); }
+
+// The arguments of k_walk, read again where they are needed: what a rare branch after the walk uses would
+// otherwise sit in scalar registers throughout it (1 % of the time of a step).
+struct WalkParams {
+    WalkSide sd;
+    WalkArgs wa;
+};
+__device__ __forceinline__ const WalkParams& walk_params() {
+    auto* p = (__attribute__((address_space(4))) const WalkParams*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const WalkParams*)p;
+}
+
+// out[t, row] over this workgroup's chunks from the row's own entries, in the order of the walk.  A padding entry
+// has weight 0 and multiplies the first index of the chunk, so an infinity (or NaN) there makes NaN of every row with
+// padding; an output that is NaN is formed again, up to the first term that makes it NaN by itself.  No other
+// output pays more than a compare.
+template <typename TIn>
+__device__ __forceinline__ float own_entries_sum(int t, int row) {
+    const WalkParams& wp = walk_params();
+    const WalkSide& sd = wp.sd;
+    const TIn* const a = static_cast<const TIn*>(sd.A) + (int64_t)t * sd.K;
+    const int c0 = (int)blockIdx.y * wp.wa.chunks_per_split, c1 = min(sd.nchunk, c0 + wp.wa.chunks_per_split);
+    const int rp = sd.rowpos[row], slot = rp & ~SPREAD_FLAG;
+    const bool spread = (rp & SPREAD_FLAG) != 0;
+    const uint2* __restrict__ ent = reinterpret_cast<const uint2*>(sd.ent);
+    float one = 0.f, two = 0.f, four = 0.f, sum = 0.f;       // a spread row: its eight lane groups' sums, added pairwise
+#pragma unroll 1
+    for (int g = spread ? 0 : slot % OCT, last = spread ? OCT - 1 : g; g <= last; ++g) {
+        sum = 0.f;
+#pragma unroll 1
+        for (int c = c0; c < c1 && sum == sum; ++c) {
+            const int* pp = sd.ptr + ((int64_t)c * sd.NBpad + row / RB) * OPB + slot / OCT;
+            const int steps = 2 * (pp[1] - pp[0]);
+#pragma unroll 1
+            for (int j = 0; j < steps && sum == sum; ++j) {
+                const int64_t e = (((int64_t)pp[0] + (j >> 1)) * OCT + g) * 2 + (j & 1);
+                if (sd.perm[e] >= 0) sum = fmaf(__uint_as_float(ent[e].y), element<TIn>(a + c * sd.KC + (ent[e].x >> 8)), sum);
+            }
+        }
+        if (!spread) break;
+        if ((g & 1) == 0) { one = sum; continue; }
+        sum = one + sum;
+        if ((g & 2) == 0) { two = sum; continue; }
+        sum = two + sum;
+        if ((g & 4) == 0) { four = sum; continue; }
+        sum = four + sum;
+    }
+    return sum;
 }
 
 // octet of block q of the slab that wavefront `wave` walks (see the head of this file)
@@ -398,6 +456,7 @@ __device__ __forceinline__ void walk_body(const WalkSide& sd, const WalkArgs& wa
         int tid_e = threadIdx.x;                              // (lane constants worked out again)
         asm volatile("" : "+v"(tid_e));
         const int g_e = (tid_e >> 3) & 7, s_e = tid_e & 7;
+        bool nan = false;
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
@@ -441,7 +500,18 @@ __device__ __forceinline__ void walk_body(const WalkSide& sd, const WalkArgs& wa
                         if (row + 1 < R) __builtin_nontemporal_store(v.y, o + 1);
                         if (row + 2 < R) __builtin_nontemporal_store(v.z, o + 2);
                     }
+                    nan |= __builtin_isunordered(v.x, v.y) | __builtin_isunordered(v.z, v.w);
                 }
+            }
+        }
+        if (nan) {                                            // (see own_entries_sum)
+#pragma unroll 1
+            for (int i = 0; i < Q * (WT * RB / WALK_NT); ++i) {
+                const int item = (i / 4) % (WT * RB / 4 / WALK_NT) * WALK_NT + tid_e, tl = item / (RB / 4);
+                const int t = t0 + tl, row = (b0 + i / (WT * RB / WALK_NT)) * RB + 4 * (item % (RB / 4)) + (i & 3);
+                if (t >= T || row >= R) continue;
+                float* o = out + (int64_t)t * R + row;
+                if (*o != *o) *o = own_entries_sum<TIn>(t, row);
             }
         }
     }

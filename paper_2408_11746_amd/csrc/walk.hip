@@ -70,12 +70,6 @@ __global__ __launch_bounds__(256) void k_walk_reduce(const float* __restrict__ p
 // The weight gradient without partial sums in memory, for a scratch area that does not hold one plane of
 // them: eight threads per entry slot, every sum in the order of the walk and of k_walk_reduce.
 template <typename TIn>
-__device__ inline float element(const TIn* p);
-template <>
-__device__ inline float element<float>(const float* p) { return *p; }
-template <>
-__device__ inline float element<uint16_t>(const uint16_t* p) { return __uint_as_float((uint32_t)*p << 16); }
-template <typename TIn>
 __global__ __launch_bounds__(256) void k_dw_slots(const TIn* __restrict__ dY, const TIn* __restrict__ X, int T, int O, int I,
                                                   const int* __restrict__ ptr_end0, const int* __restrict__ perm0,
                                                   const int* __restrict__ ptr_end1, const int* __restrict__ perm1,
@@ -203,6 +197,8 @@ static WalkSide side_of(const View& v, const void* A, const void* B, int q) {
     s.ptr = v.ptr;
     s.ent = v.ent;
     s.rowmap = v.rowmap;
+    s.perm = v.perm;
+    s.rowpos = v.rowpos;
     s.K = v.K;
     s.KC = v.KC;
     s.R = v.R;

@@ -8,9 +8,9 @@
 namespace mst {
 
 template <typename TIn, int Q, bool OUT, bool DW>
-__global__ __launch_bounds__(WALK_NT) void k_walk(const WalkSide sd, const WalkArgs wa) {
+__global__ __launch_bounds__(WALK_NT) void k_walk(const WalkParams wp) {
     extern __shared__ __attribute__((aligned(16))) char walk_lds[];
-    walk_body<TIn, Q, OUT, DW>(sd, wa, walk_lds);
+    walk_body<TIn, Q, OUT, DW>(wp.sd, wp.wa, walk_lds);
 }
 
 // The weight gradient alone: either view can drive it, decided on the device (WalkDrive).  The grid covers the larger of the two.
@@ -25,6 +25,7 @@ __global__ __launch_bounds__(WALK_NT) void k_walk_dw(const WalkSide row, const W
     sd.ptr = c ? col.ptr : row.ptr;
     sd.ent = c ? col.ent : row.ent;
     sd.rowmap = c ? col.rowmap : row.rowmap;
+    sd.perm = sd.rowpos = nullptr;                    // (no outputs of this kind)
     sd.K = c ? col.K : row.K;
     sd.KC = c ? col.KC : row.KC;
     sd.R = c ? col.R : row.R;
@@ -42,7 +43,7 @@ static int launch_q(const WalkSide& sd, const WalkArgs& wa, int nsplit, hipStrea
     static uint64_t done = 0;
     const int rc = allow_lds(reinterpret_cast<const void*>(&k_walk<TIn, Q, OUT, DW>), KCMAX * WT * 4, done);
     if (rc != MST_OK) return rc;
-    k_walk<TIn, Q, OUT, DW><<<dim3(walk_grid(wa.ntile, sd.nslab), (unsigned)nsplit), WALK_NT, walk_lds_bytes(sd.KC), s>>>(sd, wa);
+    k_walk<TIn, Q, OUT, DW><<<dim3(walk_grid(wa.ntile, sd.nslab), (unsigned)nsplit), WALK_NT, walk_lds_bytes(sd.KC), s>>>(WalkParams{sd, wa});
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
