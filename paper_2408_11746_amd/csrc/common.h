@@ -137,12 +137,16 @@ extern thread_local int g_last_hip_error;
 #define MST_LAUNCH_CHECK() MST_HIP(hipGetLastError())
 
 // More than 64 KB of LDS has to be asked for, once per kernel and device (`done`: a bit per device; two
-// threads that meet here repeat the call).
+// threads that meet here repeat the call).  The kernels that ask take the dynamic array alone, and the walk
+// reads it from LDS address 0: a kernel with static LDS in front of it is refused.
 inline int allow_lds(const void* kernel, int bytes, uint64_t& done) {
     int dev = 0;
     MST_HIP(hipGetDevice(&dev));
     const uint64_t bit = 1ull << (dev & 63);
     if (__atomic_load_n(&done, __ATOMIC_RELAXED) & bit) return MST_OK;
+    hipFuncAttributes attr;
+    MST_HIP(hipFuncGetAttributes(&attr, kernel));
+    if (attr.sharedSizeBytes != 0) return MST_ERR_STATE;
     MST_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
     __atomic_fetch_or(&done, bit, __ATOMIC_RELAXED);
     return MST_OK;

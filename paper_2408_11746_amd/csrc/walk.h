@@ -45,7 +45,7 @@ namespace mst {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;     // the tile starts at LDS address 0 (no static LDS)
+typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;     // the tile starts at LDS address 0 (allow_lds refuses a kernel with static LDS)
 typedef __attribute__((address_space(4))) const int const_int;        // read through the scalar cache
 
 constexpr int WALK_NW = OPB;                 // wavefronts per workgroup: one octet of a block each

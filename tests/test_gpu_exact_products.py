@@ -113,6 +113,46 @@ def test_infinite_operands_as_fp32_products_give_them(mode, act):
     assert rel_err(Y[finite], ref[finite]) <= FP32
 
 
+@pytest.mark.parametrize("act", [mst.MST_F32, mst.MST_BF16])
+@pytest.mark.parametrize("mode", [1032, 1064, 1096, 1128])
+def test_infinite_operands_of_the_input_gradient_and_the_dense_gradient(mode, act):
+    """The same for dX and G, whose operands lie the other way (contraction index along the columns of one or
+    both): infinities in dY, X and W at the edges of tiles and k steps."""
+    T, I, O = 130, 97, 190
+    print("case", T, I, O, mode, act, flush=True)
+    X, dY = synth.normal(67, 1, (T, I)).astype(np.float32), synth.normal(67, 2, (T, O)).astype(np.float32)
+    W = synth.normal(67, 3, (O, I), 0.02).astype(np.float32)
+    dY[3, 7], dY[129, 189], dY[40, 5], dY[40, 6], dY[50, 9] = np.inf, -np.inf, np.inf, -np.inf, np.nan
+    X[129, 96], X[64, 0], X[60, 11], dY[60, 12] = np.inf, -np.inf, np.inf, 0.0
+    W[189, 64], W[11, 5], dY[61, 11] = -np.inf, np.inf, 0.0
+    for a in (X, dY):
+        a.view(np.uint32)[...] &= 0xFFFF0000                 # (exact in bfloat16; infinities and the NaN stay what they are)
+    send = (lambda a: a) if act == mst.MST_F32 else (lambda a: (a.view(np.uint32) >> 16).astype(np.int16))
+    rig = Rig(W, np.ones((O, I), np.uint8), T, cap=O * I)
+    rig.layer.set_path(mst.MST_PATH_DENSE)
+    G = {}
+    try:
+        mst.mst_gemm_force_fp32_mfma(mode)
+        dX = rig.bwd_input(send(dY), act)
+        for area in (rig.ws, None):                          # with room to split the token range, and without
+            g = torch.full((O, I), 7.0, dtype=torch.float32, device=DEV)
+            mst.mst_dense_grad(dev(send(dY)), dev(send(X)), g, T, O, I, act, area)
+            torch.cuda.synchronize()
+            G["G with" if area is not None else "G without"] = g.cpu().numpy()
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
+    with np.errstate(invalid="ignore"):
+        refs = {"dX": dY.astype(np.float64) @ W.astype(np.float64)}
+        refs["G with"] = refs["G without"] = dY.astype(np.float64).T @ X.astype(np.float64)
+    for name, got in dict(G, dX=dX).items():
+        ref = refs[name]
+        finite = np.isfinite(ref)
+        assert 300 < (~finite).sum() < ref.size // 4 and np.isinf(ref).any() and np.isnan(ref).any(), name
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), name
+        assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32)), name
+        assert rel_err(got[finite], ref[finite]) <= FP32, name
+
+
 @pytest.mark.parametrize("mode", [1032, 1064, 1096, 1128])
 def test_positive_operands_of_full_mantissas_leave_no_one_sided_error(mode):
     """Terms of one sign and 24 significant bits: whatever a product drops must not point one way, or it adds up over

@@ -287,13 +287,12 @@ def test_gather_active_format_stats_and_lds_probe():
     nnz = int(M.sum())
     assert fs["nnz"] == nnz
     # every view stores each active weight once plus padding; padding is bounded by the format
-    # (longest of four rows per 128-index chunk, even step counts)
+    # (longest of the eight rows of an octet per chunk, even step counts)
     for v, (R, K) in (("row", (O, I)), ("col", (I, O))):
         slots = fs[v + "_view_slots"]
         assert slots >= nnz and slots % 8 == 0
         assert 0.0 < fs[v + "_view_efficiency"] <= 1.0
         assert abs(fs[v + "_view_efficiency"] - nnz / slots) < 1e-12
-    # an exact count of the row view's slots from the mask: per chunk and quad of the ranked rows
     out = torch.empty(4 * 1024, dtype=torch.float32, device=DEV)
     for width in (4, 8, 16):
         mst.mst_probe_lds_read(out, width, 10, 4)
@@ -308,7 +307,7 @@ def test_dense_products_on_the_bf16_split_kernel(T, I, O):
     """Shapes of whole tiles: the dense fp32 products (dense gradient; forward and input
     gradient of a dense layer) take the kernel that splits every fp32 operand into two
     bfloat16 values and adds three bf16 MFMA products.  Against the oracle within the fp32
-    tolerance, and against the plain fp32 MFMA kernel (pinned by the hook)."""
+    tolerance, beside the full-precision kernel (pinned by the hook)."""
     print("case", T, I, O, flush=True)
     X, dY = synth.make_activations(41, 2, T, I, O)
     # values over several orders of magnitude in every operand, so that hi + lo matters
@@ -319,7 +318,7 @@ def test_dense_products_on_the_bf16_split_kernel(T, I, O):
     Xd, dYd = dev(X), dev(dY)
     res = {}
     try:
-        for mode in (128, 256, 1):          # split kernel with either workgroup tile (where the shape allows), fp32 MFMA
+        for mode in (128, 256, 1):          # split kernel with either workgroup tile (where the shape allows), full precision
             mst.mst_gemm_force_fp32_mfma(mode)
             G = torch.full((O, I), float("nan"), dtype=torch.float32, device=DEV)
             mst.mst_dense_grad(dYd, Xd, G, T, O, I, mst.MST_F32, rig.ws)
@@ -328,13 +327,13 @@ def test_dense_products_on_the_bf16_split_kernel(T, I, O):
     finally:
         mst.mst_gemm_force_fp32_mfma(0)
     refs = (opr.dense_grad(dY, X), opr.fc_fwd(X, W, M), opr.fc_bwd_input(dY, W, M))
-    for name, got128, got256, got_f32, ref in zip(("G", "Y", "dX"), res[128], res[256], res[1], refs):
-        e0, e2, e1 = rel_err(got128, ref), rel_err(got256, ref), rel_err(got_f32, ref)
-        print(name, "split-128 err %.3g  split-256 err %.3g  fp32-mfma err %.3g" % (e0, e2, e1), flush=True)
+    for name, got128, got256, got_full, ref in zip(("G", "Y", "dX"), res[128], res[256], res[1], refs):
+        e0, e2, e1 = rel_err(got128, ref), rel_err(got256, ref), rel_err(got_full, ref)
+        print(name, "split-128 err %.3g  split-256 err %.3g  full-precision err %.3g" % (e0, e2, e1), flush=True)
         assert e0 <= TOL and e1 <= TOL and e2 <= TOL
         # hi + lo carries 16 significant bits: at most 3 * 2^-18 = 1.1e-5 of a product is lost
         assert e0 <= 2e-5 and e2 <= 2e-5
-        assert not np.array_equal(got128, got_f32) or e0 == 0.0         # the kernels really differ
+        assert not np.array_equal(got128, got_full) or e0 == 0.0         # the kernels really differ
 
 
 @pytest.mark.parametrize("T,I,O,tile", [(256, 320, 128, 160), (512, 320, 640, 160), (768, 128, 160, 160), (1024, 640, 320, 160),

@@ -13,7 +13,13 @@ from oracle import products as opr
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
-from gpu_util import Rig, TOL, DEV, dev, rel_err  # noqa: E402
+from gpu_util import Rig, DEV, dev, rel_err  # noqa: E402
+
+# max error over max value.  Sums of n <= 1300 fp32 products in a fixed order: rounding errors of random sign add up to
+# about sqrt(n) 2^-24 = 2.1e-6 of a sum of that many terms at the worst, and no output here has more than 160 (a full
+# row of the spread test: 1300 in eight lane groups, a weight gradient: 1100 tokens in tiles of 64), so 7.5e-7.  Observed 2e-7.
+TOL = 2e-6
+HEAVY = 2e-5         # Y where rows are kept out of the row view: two bfloat16 parts per operand, 3 * 2^-18 = 1.1e-5 of a product
 
 SPMM = [(0, 0), (128, 2), (128, 3), (128, 4), (64, 4), (64, 6), (64, 8)]     # 1 .. 6 row blocks per workgroup
 BOTH = [(16, 1), (16, 2), (8, 4), (8, 5)]
@@ -50,7 +56,8 @@ def _check(W, M, X, dY, act=mst.MST_F32, Xd=None, dYd=None):
     dW = new(max(nnz, 1))
     mst.mst_sparse_fc_bwd_weight(rig.layer, dYd, Xd, dW, T, rig.ws, act)
     dW = dW.cpu().numpy()[:nnz]
-    assert rel_err(ys[0], Yr) <= TOL and rel_err(dxs[0], dXr) <= TOL
+    heavy = rig.layer.format_stats()["heavy_rows"] > 0
+    assert rel_err(ys[0], Yr) <= (HEAVY if heavy else TOL) and rel_err(dxs[0], dXr) <= TOL
     if nnz:
         assert rel_err(dws[0], dWr) <= TOL and rel_err(dW, dWr) <= TOL
     for group in (ys, dxs, dws):
