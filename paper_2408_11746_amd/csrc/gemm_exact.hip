@@ -173,8 +173,10 @@ struct ExOperand {
 
 // Tile numbers run in bands of eight tile rows, column by column inside a band (the tiles an XCD works on
 // at a time share operand panels in its L2); XCD x takes a contiguous share, one k range after the other.
+// (TN has the fewest registers: left to itself the compiler takes two more than three workgroups on a CU can have; dense
+// gradient of 5001 x 1000 -> 4000 with two 220 us, with three 218.4.)
 template <bool A16, bool A_KMAJOR, bool B_KMAJOR, int TM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 3)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(A_KMAJOR ? 3 : 2, 3)))
 void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
                   int M, int N, int Kdim, int k_per_split, int64_t split_stride) {
     typedef ExOperand<A16, A_KMAJOR, TM> OpA;
