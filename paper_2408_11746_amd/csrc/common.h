@@ -20,7 +20,7 @@ constexpr int WT = 64;           // tokens per LDS tile
 constexpr int OCT = 8;           // rows per octet: one per lane group of eight lanes
 constexpr int OPB = 16;          // octets per row block: one per wavefront of a workgroup
 constexpr int RB = OCT * OPB;    // rows per row block
-constexpr int MAX_WG_BLOCKS = 8; // most row blocks one workgroup may own
+constexpr int MAX_WG_BLOCKS = 6; // most row blocks one workgroup may own (checked at every launch shape, walk_launch.h)
 constexpr int SPREAD_FLAG = 1 << 30;   // in rowmap / rowpos: the octet holds ONE row spread over its eight lane groups
 constexpr int HEAVY_MAX = 64;    // rows a layer may keep out of its row view as a small dense matrix (heavy.hip)
 constexpr int PAIR_TAIL = 16;    // readable step pairs past the last one (a whole entry batch may be fetched there)
@@ -30,7 +30,7 @@ constexpr int PAIR_TAIL = 16;    // readable step pairs past the last one (a who
 // LDS read is served in sets of four lane quads, {0, 3, 5, 6} and {1, 2, 4, 7} of every 32 lanes,
 // and is free of conflicts when the four quads of a set read four different 64-byte quarters of a
 // row: the swizzle therefore stays inside a quarter (with a swizzle over eight slots the walk
-// counted 3 conflict cycles per read), it spreads the transposing stores of the tile loader.
+// counted 3 conflict cycles per read); it spreads the transposing stores that stage the walk's tile.
 __host__ __device__ inline uint32_t lds_off(uint32_t k) { return (k << 8) | (((k >> 2) & 3u) << 4); }
 
 // Sparse matrix S [R x K] as the product kernels walk it.  Rows are grouped in blocks of

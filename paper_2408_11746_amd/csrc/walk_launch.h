@@ -40,6 +40,7 @@ inline unsigned walk_grid(int ntile, int nslab) { return 8u * (unsigned)cdiv((in
 
 template <typename TIn, int Q, bool OUT, bool DW>
 static int launch_q(const WalkSide& sd, const WalkArgs& wa, int nsplit, hipStream_t s) {
+    static_assert(Q <= MAX_WG_BLOCKS, "the last slab reads the pointers of this many blocks");
     static uint64_t done = 0;
     const int rc = allow_lds(reinterpret_cast<const void*>(&k_walk<TIn, Q, OUT, DW>), KCMAX * WT * 4, done);
     if (rc != MST_OK) return rc;
@@ -72,6 +73,7 @@ static int launch_both_any(int q, const WalkSide& sd, const WalkArgs& wa, int ns
 
 template <typename TIn, int Q>
 static int launch_dw_q(const WalkSide& row, const WalkSide& col, const WalkArgs& wa, const WalkDrive& drive, hipStream_t s) {
+    static_assert(Q <= MAX_WG_BLOCKS, "the last slab reads the pointers of this many blocks");
     static uint64_t done = 0;
     const int rc = allow_lds(reinterpret_cast<const void*>(&k_walk_dw<TIn, Q>), KCMAX * WT * 4, done);
     if (rc != MST_OK) return rc;
