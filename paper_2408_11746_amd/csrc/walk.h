@@ -26,8 +26,8 @@
 //     the steps, and there are five times fewer barriers, over slabs of up to 768 rows;
 //   - eight tokens a lane: the address, weight and row-sum instructions are shared by eight tokens;
 //   - odd lane groups read the upper token half of a row first, even ones the lower: with the swizzle
-//     of lds_off the reads are then free of bank conflicts (a third of the time before: 26 M conflict
-//     cycles instead of 1.5 M in the case above, 150 -> 135 us);
+//     of lds_off the reads are then free of bank conflicts (1.5 M conflict cycles instead of 26 M in
+//     the case above, 150 -> 135 us);
 //   - the weight goes through one v_mov_b32_dpp: a plain v_fmac_f32 issues in 3.4 clocks, one with a
 //     DPP operand in 5.2;
 //   - the wavefronts' octets are dealt in a snake over the blocks of the slab, so that the longest
