@@ -98,9 +98,7 @@ bool use_dense_path(const mst_layer* L, WalkJob job, mst_dtype act, int T) {
     if (L->path == MST_PATH_SPARSE) return false;
     if (whole_tiles(L, act, T)) return (double)L->nnz > (act == MST_F32 ? 0.075 : T >= 8192 ? 0.045 : 0.065) * (double)L->N;
     if (mostly_dense(L)) return true;
-    // (a tie goes to the walk: the models are 8 % off on average, and it reads a tenth of the bytes and needs no dense
-    // copy to be kept: 64 tokens 768 -> 3072 at 0.04, modelled 10.1 and 9.9 us, take 8.8 and 9.7)
-    return remembered(L, job, act, T, [&] { return walk_us(L, job, T) > 1.05 * dense_us(L, job, act, T); });
+    return remembered(L, job, act, T, [&] { return walk_us(L, job, T) > dense_us(L, job, act, T); });
 }
 
 // The one-call backward: one walk for both gradients, or the two dense products (a sparse dX beside a
