@@ -251,7 +251,14 @@ int sddmm(const mst_layer* L, const void* dY, const void* X, float* dW, int T, m
     const View &r = L->row, &c = L->col;              // (the entries' values are not read: stale ones will do)
     const int64_t stride = std::max(r.cap_pairs, c.cap_pairs) * (2 * OCT);
     const int64_t fit = (int64_t)(partial_floats / (size_t)stride);
-    WalkDrive drive{L->walk_cost, 1.f, 1.f};
+    // one number of blocks per workgroup for both views: the better one for the view that drives a
+    // uniform pattern (heavy rows are missing from the row view).  Judged for the whole batch: the view that
+    // drives decides the order of the sums, and `partial` decides the ranges.
+    const double d = view_density(L);
+    const WalkShape best_r = pick_shape(r, T, d, 6, kDw, 1), best_c = pick_shape(c, T, d, 6, kDw, 1);
+    const int q = !L->heavy_on && best_r.cost <= best_c.cost ? best_r.q : best_c.q;
+    const WalkDrive drive{L->walk_cost, (float)(shape_cost(r, T, d, q, kDw) / walk_units(r, d)),
+                          (float)(shape_cost(c, T, d, q, kDw) / walk_units(c, d))};
     if (fit < 1) {
         if (act == MST_F32)
             k_dw_slots<float><<<8192, 256, 0, s>>>((const float*)dY, (const float*)X, T, L->O, L->I, r.ptr + r.nseg, r.perm,
@@ -268,13 +275,6 @@ int sddmm(const mst_layer* L, const void* dY, const void* X, float* dW, int T, m
         const int n = (int)std::min<int64_t>(T - t, fit * WT), ntile = (int)cdiv(n, WT);
         const char* x = static_cast<const char*>(X) + (size_t)t * L->I * esz;
         const char* y = static_cast<const char*>(dY) + (size_t)t * L->O * esz;
-        // one number of blocks per workgroup for both views: the better one for the view that drives a
-        // uniform pattern (heavy rows are missing from the row view)
-        const double d = view_density(L);
-        const WalkShape best_r = pick_shape(r, n, d, 6, kDw, 1), best_c = pick_shape(c, n, d, 6, kDw, 1);
-        const int q = !L->heavy_on && best_r.cost <= best_c.cost ? best_r.q : best_c.q;
-        drive.row_unit = (float)(shape_cost(r, n, d, q, kDw) / walk_units(r, d));
-        drive.col_unit = (float)(shape_cost(c, n, d, q, kDw) / walk_units(c, d));
         const WalkSide sr = side_of(r, x, y, q), sc = side_of(c, y, x, q);
         const WalkArgs wa{nullptr, partial, stride, n, ntile, std::max(r.nchunk, c.nchunk)};
         rc = act == MST_F32 ? walk_dw_f32(q, sr, sc, wa, drive, s) : walk_dw_bf16(q, sr, sc, wa, drive, s);

@@ -116,6 +116,23 @@ def test_weight_gradient_without_a_workspace_in_token_ranges_and_by_slots():
         assert rel_err(want, opr.fc_bwd_weight(dY, X, M)) <= TOL
 
 
+@pytest.mark.parametrize("O,I,T,density,cap", [(1526, 2380, 1016, 0.03, 434108), (1679, 1110, 1247, 0.053, 396120),
+                                               (937, 1424, 1559, 0.0635, 169342), (3317, 5118, 117, 0.0021, 2707830)])
+def test_weight_gradient_without_a_workspace_walks_the_view_of_the_whole_batch(O, I, T, density, cap):
+    """Layers whose token ranges by themselves (or whose slots, where no plane fits) would be driven by the other
+    view than the whole batch: its lane groups add the tokens of a tile in another order."""
+    print("case", O, I, T, density, cap, flush=True)
+    W, M = synth.make_layer(975, 1, I, O, density)
+    X, dY = synth.make_activations(975, 1, T, I, O)
+    rig = Rig(W, M, T, cap=cap)
+    rig.layer.set_path(mst.MST_PATH_SPARSE)
+    want = rig.bwd_weight(dY, X)
+    got = torch.full((rig.layer.nnz,), float("nan"), dtype=torch.float32, device=DEV)
+    mst.mst_sparse_fc_bwd_weight_static(rig.layer, dev(dY), dev(X), got, T)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(got.cpu().numpy(), want)
+
+
 def test_values_reach_views_that_no_product_has_walked_yet():
     O, I, T = 300, 500, 70
     W, M = synth.make_layer(980, 1, I, O, 0.05)
