@@ -99,7 +99,10 @@ int mst_last_hip_error(void);           /* hipError_t of the last failing HIP ca
 size_t mst_layer_device_bytes(int O, int I, int64_t nnz_capacity);
 
 /* Bytes of workspace sufficient for every call below on a layer of this shape with
- * up to T tokens.  0 on invalid arguments. */
+ * up to T tokens.  0 on invalid arguments.  For long batches most of it is the weight gradient's partial
+ * sums: per 64 tokens one plane of about 8 floats per active weight of the capacity or one float per
+ * position, whichever is less (1280 -> 5120, 8192 tokens: 0.8 GB at capacity 196608, 3.4 GB at full
+ * capacity).  One workspace serves all layers used on a stream. */
 size_t mst_workspace_bytes(int O, int I, int64_t nnz_capacity, int T);
 
 /* Creates the host object over the caller's buffer (kept, not copied, never freed by
@@ -233,10 +236,13 @@ int mst_sparse_fc_bwd(const mst_layer_t* layer, const void* dY_dev, const void* 
 int mst_bwd_force_shape(int wavefronts_per_workgroup, int quads_per_wavefront);
 
 /* The dense fp32 products (the dense gradient below, and the three products of a layer on the
- * dense path) run on the bf16 matrix cores when their shapes are whole tiles: each fp32
+ * dense path) run on the bf16 matrix cores.  Shapes of whole tiles with at least 2e10 multiply-adds, and
+ * smaller ones where that is modelled to be faster: each fp32
  * operand element is split into two bfloat16 values (hi + lo, exact to 2^-17) while it is
  * staged, a product is hi*hi + hi*lo + lo*hi with fp32 accumulation; the result differs from
- * an fp32 product by less than 2^-16 per term.  Every other shape runs on a kernel of full fp32
+ * an fp32 product by less than 2^-16 per term.  (Room to split the contraction is part of the model, so for
+ * products below 2e10 multiply-adds a call with a workspace may take another kernel than one without.)
+ * Every other product runs on a kernel of full fp32
  * precision (three bfloat16 values per element, exact; six products, what they leave out is below
  * 2^-24 of a term and of either sign).  So do the products that MST_PATH_AUTO moves from the sparse
  * to the dense kernels at low densities: up to 0.15 (short batches) or 0.035 to 0.07 (from 2048 tokens
@@ -245,7 +251,7 @@ int mst_bwd_force_shape(int wavefronts_per_workgroup, int quads_per_wavefront);
  * later calls of the process: 1 = the full-precision kernel (1064, 1128: with a 64 x 64 or a
  * 128 x 128 tile; 1032, 1096: the streaming form for small outputs, 32 x 32 or 64 x 64); 128, 256, 160 or 192 = the split kernel with the
  * workgroup tile 128 x 128, 256 x 256, 256 x 160 or 256 x 192 (where the shape is a multiple of
- * it; the last two serve Y and dX only); 0 returns to the automatic choice.  All tiles add a
+ * it; the last two serve Y and dX only); 0 returns to the automatic choice.  The split kernel's tiles add a
  * result's terms in the same order and give identical bits.  -52 / 52 switch off / on the
  * schedule that gives two 256 x 256 tiles five workgroups (used where plain k ranges would
  * leave a fifth of the CUs idle; other cut points of the k range, so another order of

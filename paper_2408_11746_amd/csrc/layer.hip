@@ -43,9 +43,10 @@ View view_shape(int R, int K, int64_t cap) {
 // densities that do not either (measured at GPT-2 small / medium / large layer shapes, T >= 2048): fp32 Y and
 // dX 0.065-0.085, weight gradient 0.04-0.06, both gradients from one walk against two dense products
 // 0.075-0.105; bfloat16 0.05 at T = 16384 and 0.07-0.1 at shorter batches, below 0.03, and 0.03-0.04.  Everywhere else the
-// modelled times of the two are compared up to a density of 0.30 (dense from there on): partial tiles and few workgroups move the line anywhere
-// between 0.03 and 0.3 (at 115 shapes and densities the choice is within 1 to 2 % of the better one, where a line at
-// 0.30 lost 12 to 37 %).
+// modelled times of the two are compared up to a density of 0.30 (dense from there on): partial tiles and few workgroups move
+// the line anywhere between 0.03 and 0.3 (a line at 0.30 lost 12 to 37 %).  Of 150 products Y and dX whose modelled times are
+// within a third of each other the choice loses 1.5 % on average and 23 % at the worst; the models favour neither side, and
+// deciding ties for one of them by 5 % loses 1.6 or 2.2.
 static bool whole_tiles(const mst_layer* L, mst_dtype act, int T) {
     const int tile = act == MST_BF16 ? 256 : 128;
     return T >= 2048 && T % tile == 0 && L->O % tile == 0 && L->I % tile == 0;
