@@ -155,7 +155,8 @@ static WalkShape pick_shape(const View& v, int T, double density, int qmax, cons
 
 static int g_forced_out = 0, g_forced_both = 0;       // test hooks: row blocks per workgroup, 0 = automatic
 
-// Every accepted pair selects one of the launch shapes; all shapes add a row's entries in the same order.
+// Every accepted pair (the names of the shapes of earlier kernels, which callers may hold) selects a number of row blocks.
+// These shapes keep the chunks together and add a row's entries in the same order.
 int spmm_force_shape(int tokens, int quads) {
     static const int table[][3] = {{0, 0, 0}, {128, 2, 1}, {128, 3, 2}, {128, 4, 3}, {64, 2, 1}, {64, 3, 2}, {64, 4, 4}, {64, 6, 5}, {64, 8, 6}};
     for (const auto& e : table)
