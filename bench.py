@@ -6,7 +6,8 @@ forward product, the input gradient and the weight gradient at the active positi
 Mixed-Growing topology update (Algorithm 1: dense gradient on the matrix cores, prune / grow
 selections, rebuild of the index views) on the steps that carry one.
 
-Default run (what `python bench.py --gpus 1 --steps K --warmup W` prints as ONE JSON line):
+Default run (`python bench.py --gpus 1 --steps K --warmup W` prints ONE JSON line of a few KB; the per-call tables
+that it leaves out go to stderr, or with `--details FILE` to a file):
   * headline = the schedule sweep of the GPT-2-large block (the largest single-GPU workload):
     the layers are driven through the densities 1.0, 0.5, 0.1, 0.02, 0.1, 0.5 of the warm-up /
     ultra-sparse / restoration phases (Sec. 3.1), every step runs the products at the current
@@ -74,6 +75,8 @@ def parse():
                    help="step size of the caller-side SGD on the active weights between backward and hand-over "
                         "(without it grown weights would stay exactly 0 and magnitude pruning would degenerate "
                         "into a tie-break by index); 0 = no optimiser step")
+    p.add_argument("--details", metavar="FILE", default=None,
+                   help="where the full result goes, the per-call tables included (one JSON object); stderr without it")
     p.add_argument("--seed", type=int, default=2024)
     p.add_argument("--attention-mask", type=int, nargs=2, metavar=("L", "STRIDE"), default=None,
                    help="time the strided attention mask of Sec. 3.3 instead of a config (its own JSON line)")
@@ -1063,6 +1066,30 @@ def compact(out, name):
                 dense_grad_gemm=out["dense_grad_gemm"])
 
 
+def short(out):
+    """`out` without its per-call tables: a line that whoever keeps the end of the output has whole."""
+    line = {k: v for k, v in out.items() if k not in ("calls", "sweep", "per_config", "dense_grad_gemm")}
+    if "sweep" in out:
+        line["sweep"] = [{k: row[k] for k in ("density", "next_density", "ms_per_step_device", "eff_tflops", "path")}
+                         for row in out["sweep"]]
+    if "per_config" in out:
+        keep = ("config", "dtype", "ms_per_step", "eff_tflops", "hbm_frac", "alu_frac", "ms_per_mask_update", "slowest_call")
+        line["per_config"] = [dict({k: row[k] for k in keep},
+                                   graph_replay={k: row["graph_replay"][k] for k in ("ms_per_step", "matches_call_by_call")},
+                                   **({"sparse_pinned_ms_per_step": row["sparse_pinned"]["ms_per_step"]} if "sparse_pinned" in row else {}))
+                              for row in out["per_config"]]
+    return line
+
+
+def emit(out, details):
+    if details:
+        with open(details, "w") as f:
+            f.write(json.dumps(out) + "\n")
+    else:
+        print(json.dumps(out), file=sys.stderr, flush=True)
+    print(json.dumps(short(out)), flush=True)
+
+
 def main():
     args = parse()
     if args.gpus != 1:
@@ -1097,11 +1124,11 @@ def main():
                                                                "slowest_call", "calls")}
                 rows.append(row)
             out["per_config"] = rows
-        print(json.dumps(out))
+        emit(out, args.details)
         return
     out = run_block(args, args.config, mst, synth, torch, lds_peak, cpu)
     if out is not None:
-        print(json.dumps(out))
+        emit(out, args.details)
 
 
 if __name__ == "__main__":
