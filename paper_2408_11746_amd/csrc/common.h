@@ -171,8 +171,8 @@ struct Workspace {
     int* cidx = nullptr;       // [N] canonical index of each active position
     uint8_t* sel = nullptr;    // [N] selection flags of the grow step
     uint8_t* psel = nullptr;   // [cap] selection flags of the prune step
-    int* segcnt = nullptr;     // active count per (sub-chunk, row) of the view being built
-    int* qlen = nullptr;       // pairs per octet segment of the view being built
+    int* segcnt[2] = {nullptr, nullptr};   // active count per (sub-chunk, row) of the row view and of the col view
+    int* qlen[2] = {nullptr, nullptr};     // pairs per octet segment of either
     int* rowcnt = nullptr;     // [O + 1]
     uint32_t* blk = nullptr;   // per-block tie counts: [blocks(N) + 1] of the growth selections, then [blocks(cap) + 1] of the prune selection
     uint64_t* sel_state = nullptr;   // [SEL_STATES][SEL_STATE_WORDS] radix-select state + histogram
@@ -194,9 +194,48 @@ constexpr int SEL_STATES = 3;                            // prune, gradient grow
 View view_shape(int R, int K, int64_t cap);
 int fill_u32(void* dst, uint32_t value, int64_t n_words, hipStream_t s);
 
+// ---- several layers in one launch ----
+// The chains of small kernels of an update and of a view build take a batch of layers: one launch per link of the chain,
+// whatever the number of layers.  Consecutive blocks serve consecutive entries; an entry's parameters lie in the
+// kernel's arguments.
+constexpr int BATCH_MAX = 8;
+template <typename P>
+struct Batch {
+    int n = 0;
+    unsigned first[BATCH_MAX + 1] = {0};   // first block of every entry, then the number of blocks
+    P p[BATCH_MAX];
+    void add(const P& entry, int64_t blocks) {
+        p[n] = entry;
+        first[n + 1] = first[n] + (unsigned)blocks;
+        ++n;
+    }
+    unsigned blocks() const { return first[n]; }
+    // the entry that block b serves; b becomes its number inside the entry
+    __device__ const P& entry(unsigned& b) const {
+        int j = 0;
+        while (b >= first[j + 1]) ++j;
+        b -= first[j];
+        return p[j];
+    }
+};
+// one layer's part of a batched build or update
+struct BuildItem {
+    mst_layer* L;
+    const float* Wsrc;         // dense weights, read at the active positions
+    Workspace ws;
+    bool keep_dense_copy;
+};
+struct UpdateItem {
+    mst_layer* L;
+    const float* G;
+    mst_update_stats st;
+    uint64_t seed;
+    Workspace ws;
+};
+
 // ---- internal entry points implemented across the .hip files ----
-int build_views(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_t s, bool keep_dense_copy = false);
-int build_canonical(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_t s);
+int build_views(const BuildItem* items, int n, hipStream_t s);          // n up to BATCH_MAX
+int build_canonical(const BuildItem* items, int n, hipStream_t s);
 int ensure_views(const mst_layer* L, const Workspace& ws, hipStream_t s);
 bool views_wanted(const mst_layer* L);
 int ensure_fresh(const mst_layer* L, bool row, bool col, hipStream_t s);
@@ -231,8 +270,7 @@ double walk_us(const mst_layer* L, WalkJob job, int T);
 int sum_split_planes(const float* part, int64_t stride, int nsplit, float* C, int64_t n, hipStream_t s);
 int gemm_force_fp32_mfma(int on);
 int gemm_last_tile();
-int mask_update_device(mst_layer* L, const float* G, const mst_update_stats& st, uint64_t seed,
-                       const Workspace& ws, hipStream_t s);
+int mask_update_device(const UpdateItem* items, int n, hipStream_t s);   // n up to BATCH_MAX
 int dense_products_fwd(const mst_layer* L, const void* X, float* Y, int T, mst_dtype act, hipStream_t s, bool full);
 int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int T, mst_dtype act, hipStream_t s, bool full,
                              float* split_ws = nullptr, int64_t split_ws_floats = 0);
@@ -242,7 +280,7 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s);
 // heavy rows of the forward product; see heavy.hip
 int heavy_rows_enable(int on);
 int heavy_rows_mode();
-int heavy_mark(const mst_layer* L, const Workspace& ws, int Rpad, hipStream_t s);
+int heavy_mark(const mst_layer* L, const Workspace& ws, int Rpad, hipStream_t s);     // clears counts of the row view
 int heavy_fill(const mst_layer* L, hipStream_t s);
 int heavy_fwd(const mst_layer* L, const void* X, float* Y, int T, mst_dtype act, hipStream_t s);
 

@@ -223,7 +223,7 @@ int heavy_threshold(const mst_layer* L) {
 }
 
 int heavy_mark(const mst_layer* L, const Workspace& ws, int Rpad, hipStream_t s) {
-    k_mark_heavy<<<1, 1024, 0, s>>>(ws.rowcnt, L->O, heavy_threshold(L), ws.segcnt, L->row.nsub(), Rpad, L->heavy);
+    k_mark_heavy<<<1, 1024, 0, s>>>(ws.rowcnt, L->O, heavy_threshold(L), ws.segcnt[0], L->row.nsub(), Rpad, L->heavy);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }

@@ -124,6 +124,8 @@ bool use_dense_weight_grad(const mst_layer* L, mst_dtype act, int T) {
     return remembered(L, WALK_BWD_WEIGHT, act, T, [&] { return walk_us(L, WALK_BWD_WEIGHT, T) > dense_wgrad_us(L, act, T, full_precision(L, WALK_BWD_WEIGHT, act, T)); });
 }
 
+constexpr int CSEG = 2048;         // positions per wavefront of build_canonical
+
 struct LayerCarve {
     size_t mask, vals, flat, rowptr, Wd;
     size_t rptr, rent, rperm, rmap, rpos, cptr, cent, cperm, cmap, cpos, cost, heavy, Hd;
@@ -181,8 +183,10 @@ Workspace carve_workspace(void* base, int O, int I, int64_t cap, int T) {
     w.cidx = (int*)take((size_t)N * 4);
     w.sel = (uint8_t*)take((size_t)N);
     w.psel = (uint8_t*)take((size_t)(cap > 0 ? cap : 1));
-    w.segcnt = (int*)take((size_t)(std::max(cnt_r, cnt_c) + 1) * 4);
-    w.qlen = (int*)take((size_t)(std::max(r.nseg, k.nseg) + 1) * 4);
+    w.segcnt[0] = (int*)take((size_t)(std::max(cnt_r, cdiv(N, CSEG)) + 1) * 4);      // (build_canonical counts per segment of CSEG)
+    w.segcnt[1] = (int*)take((size_t)(cnt_c + 1) * 4);
+    w.qlen[0] = (int*)take((size_t)(r.nseg + 1) * 4);
+    w.qlen[1] = (int*)take((size_t)(k.nseg + 1) * 4);
     w.rowcnt = (int*)take((size_t)(O + 1) * 4);
     w.blk = (uint32_t*)take((size_t)(cdiv(N, SELECT_BLOCK) + cdiv(cap > 0 ? cap : 1, SELECT_BLOCK) + 4) * 4);
     w.sel_state = (uint64_t*)take((size_t)SEL_STATES * SEL_STATE_WORDS * 8);
@@ -198,10 +202,8 @@ Workspace carve_workspace(void* base, int O, int I, int64_t cap, int T) {
 
 // one block per row r of the mask: active count per sub-chunk of KS columns and per row; blocks past
 // the last row (the padding rows of the view) write zero counts
-__global__ void k_count_row(const uint8_t* __restrict__ mask, int O, int I, int KS, int nsub, int Rpad,
-                            int* __restrict__ segcnt, int* __restrict__ rowcnt) {
-    extern __shared__ int cnt[];   // [nsub]
-    const int r = blockIdx.x;
+__device__ inline void count_row_block(const uint8_t* __restrict__ mask, int O, int I, int KS, int nsub, int Rpad,
+                                       int* __restrict__ segcnt, int* __restrict__ rowcnt, int r, int* cnt /* [nsub] */) {
     if (r >= O) {
         for (int c = threadIdx.x; c < nsub; c += blockDim.x) segcnt[(size_t)c * Rpad + r] = 0;
         return;
@@ -241,14 +243,11 @@ __device__ inline void load_mask_tile(const uint8_t* __restrict__ mask, int O, i
     }
 }
 
-// block = (64 columns, sub-chunk c of KS rows): active count of every column inside the sub-chunk.
+// block (bx, c) = (64 columns, sub-chunk c of KS rows): active count of every column inside the sub-chunk.
 // Thread (column j, row group rg of 32 rows) counts its rows from the LDS tile.
-__global__ __launch_bounds__(256) void k_count_col(const uint8_t* __restrict__ mask, int O, int I, int KS, int Rpad,
-                                                   int* __restrict__ segcnt) {
-    __shared__ __attribute__((aligned(16))) uint8_t m[KSMAX * MT_LD];
-    __shared__ int part[4][MT_COLS];
-    const int tid = threadIdx.x, j = tid & 63, rg = tid >> 6;
-    const int i0 = blockIdx.x * MT_COLS, c = blockIdx.y;
+__device__ inline void count_col_block(const uint8_t* __restrict__ mask, int O, int I, int KS, int Rpad, int* __restrict__ segcnt,
+                                       int bx, int c, uint8_t* m, int (*part)[MT_COLS]) {
+    const int tid = threadIdx.x, j = tid & 63, rg = tid >> 6, i0 = bx * MT_COLS;
     load_mask_tile(mask, O, I, c * KS, KS, i0, m, tid);
     __syncthreads();
     int n = 0;
@@ -260,6 +259,26 @@ __global__ __launch_bounds__(256) void k_count_col(const uint8_t* __restrict__ m
     if (rg == 0 && i0 + j < Rpad) segcnt[(size_t)c * Rpad + i0 + j] = part[0][j] + part[1][j] + part[2][j] + part[3][j];
 }
 
+// The counts of both views (segcnt_c null: of the rows alone): the first row_blocks blocks of a layer take a row each
+struct CountArgs {
+    const uint8_t* mask;
+    int O, I, KS_r, nsub_r, Rpad_r, KS_c, Rpad_c, row_blocks, col_tiles;
+    int *segcnt_r, *rowcnt, *segcnt_c;
+};
+__global__ __launch_bounds__(256) void k_count(const Batch<CountArgs> batch) {
+    extern __shared__ int cnt[];
+    __shared__ __attribute__((aligned(16))) uint8_t m[KSMAX * MT_LD];
+    __shared__ int part[4][MT_COLS];
+    unsigned b = blockIdx.x;
+    const CountArgs& a = batch.entry(b);
+    if (b < (unsigned)a.row_blocks) {
+        count_row_block(a.mask, a.O, a.I, a.KS_r, a.nsub_r, a.Rpad_r, a.segcnt_r, a.rowcnt, (int)b, cnt);
+    } else {
+        b -= (unsigned)a.row_blocks;
+        count_col_block(a.mask, a.O, a.I, a.KS_c, a.Rpad_c, a.segcnt_c, (int)(b % (unsigned)a.col_tiles), (int)(b / (unsigned)a.col_tiles), m, part);
+    }
+}
+
 // One workgroup per row block (thread j = row j): orders its 128 rows by total length over all
 // chunks, longest first, lower row first on ties (the empty padding blocks keep the identity), then
 // writes the pairs of every (chunk, octet) segment of the block.  With h rows spread over whole
@@ -269,11 +288,26 @@ __global__ __launch_bounds__(256) void k_count_col(const uint8_t* __restrict__ m
 // Bound by the latency of its reads of the counts (there are only as many workgroups as row blocks), so
 // all reads of a segment are issued together (with the fill of the col view in turns of four entries: update of
 // the GPT-2-small block at density 0.05, 1024 tokens, 766 -> 742 us).
-__global__ __launch_bounds__(RB) void k_block_rank(const int* __restrict__ segcnt, int msub, int nchunk, int Rpad, int NBpad,
-                                                   int* __restrict__ rowmap, int* __restrict__ rowpos, int* __restrict__ qlen) {
+struct ViewArgs {                                     // of one view: the first nb_r blocks of k_block_rank are the row view's
+    const int* segcnt;
+    int msub, nchunk, Rpad, NBpad, NB;
+    int64_t nseg;
+    int *rowmap, *rowpos, *qlen, *ptr;
+};
+struct RankArgs {
+    ViewArgs row, col;
+};
+__global__ __launch_bounds__(RB) void k_block_rank(const Batch<RankArgs> batch) {
     __shared__ int len_s[RB], sorted[RB], row_s[RB];
     __shared__ int h_s, nzero_s;
-    const int j = threadIdx.x, b = blockIdx.x;
+    unsigned bu = blockIdx.x;
+    const RankArgs& both = batch.entry(bu);
+    const bool col = bu >= (unsigned)both.row.NBpad;
+    const ViewArgs& v = col ? both.col : both.row;
+    const int j = threadIdx.x, b = (int)bu - (col ? both.row.NBpad : 0);
+    const int msub = v.msub, nchunk = v.nchunk, Rpad = v.Rpad, NBpad = v.NBpad;
+    const int* __restrict__ segcnt = v.segcnt;
+    int *__restrict__ rowmap = v.rowmap, *__restrict__ rowpos = v.rowpos, *__restrict__ qlen = v.qlen;
     if (j == 0) { h_s = 0; nzero_s = 0; }
     int len = 0;
 #pragma unroll 8
@@ -375,9 +409,15 @@ __device__ inline void block_scan_excl(const int* in, int* out, int64_t n, int* 
     if (wave == nwave - 1 && lane == 0) out[n] = carry;            // the last segment ends at n (or is empty): the total
 }
 
-__global__ __launch_bounds__(1024) void k_scan_excl(const int* in, int* out, int64_t n) {
+struct ScanArgs {
+    const int* in;
+    int* out;
+    int64_t n;
+};
+__global__ __launch_bounds__(1024) void k_scan_excl(const Batch<ScanArgs> batch) {     // a block each
     __shared__ int wsum[16];
-    block_scan_excl(in, out, n, wsum);
+    const ScanArgs& a = batch.p[blockIdx.x];
+    block_scan_excl(a.in, a.out, a.n, wsum);
 }
 
 // One block does what follows the segment lengths of a view: (row view only) the canonical row
@@ -385,15 +425,27 @@ __global__ __launch_bounds__(1024) void k_scan_excl(const int* in, int* out, int
 // for the weight gradient, which either view can drive -- the wavefronts of a workgroup take one
 // octet of a block each and wait at every chunk for the longest, so a view costs the sum over
 // (chunk, block) of the most pairs of an octet.
-__global__ __launch_bounds__(1024) void k_view_ptr(const int* __restrict__ rowcnt, int* __restrict__ rowptr, int nrows,
-                                                   const int* __restrict__ qlen, int NBpad, int NB, int nchunk,
-                                                   int64_t nseg, int* __restrict__ ptr,
-                                                   unsigned long long* __restrict__ cost, const int* __restrict__ heavy,
-                                                   int* __restrict__ dense_live, int live) {
+struct PtrArgs {
+    const int* rowcnt;                                // counts per row
+    int* rowptr;
+    int nrows;
+    unsigned long long* cost;
+    const int* heavy;
+    int* dense_live;
+    int live;
+};
+__global__ __launch_bounds__(1024) void k_view_ptr(const Batch<RankArgs> views, const Batch<PtrArgs> batch) {    // two blocks per layer: row view, col view
     __shared__ int wsum[16];
     __shared__ unsigned long long cost_s;
-    if (rowcnt) block_scan_excl(rowcnt, rowptr, nrows, wsum);
-    block_scan_excl(qlen, ptr, nseg, wsum);
+    const int layer = blockIdx.x >> 1;
+    const bool col = (blockIdx.x & 1) != 0;
+    const ViewArgs& v = col ? views.p[layer].col : views.p[layer].row;
+    const PtrArgs& a = batch.p[layer];
+    const int* const qlen = v.qlen;
+    int* const ptr = v.ptr;
+    const int NBpad = v.NBpad, NB = v.NB, nchunk = v.nchunk;
+    if (!col) block_scan_excl(a.rowcnt, a.rowptr, a.nrows, wsum);
+    block_scan_excl(qlen, ptr, v.nseg, wsum);
     if (threadIdx.x == 0) cost_s = 0ull;
     __syncthreads();                                  // ptr[] written by this block is visible to it
     unsigned long long mine = 0ull;
@@ -408,8 +460,8 @@ __global__ __launch_bounds__(1024) void k_view_ptr(const int* __restrict__ rowcn
     __syncthreads();
     // (a row view that leaves heavy rows out cannot drive the weight gradient)
     if (threadIdx.x == 0) {
-        *cost = (heavy && heavy[0] > 0) ? (1ull << 50) : cost_s;
-        *dense_live = live;
+        a.cost[col ? 1 : 0] = (!col && a.heavy && a.heavy[0] > 0) ? (1ull << 50) : cost_s;
+        if (!col) *a.dense_live = a.live;
     }
 }
 
@@ -442,15 +494,31 @@ __device__ inline void pad_row_slots(uint2* __restrict__ ent, int* __restrict__ 
 // the 1280 rows of a 5120-wide layer on 320 workgroups); a part finds its first canonical index and
 // its place in its first chunk from the counts of the sub-chunks before it (a heavy row, whose counts
 // were cleared, from the mask itself).
-__global__ void k_fill_row(const uint8_t* __restrict__ mask, const float* __restrict__ W,
-                           int O, int I, int KS, int msub, int nsub, int NBpad, int NB,
-                           const int* __restrict__ rowptr, const int* __restrict__ ptr,
-                           const int* __restrict__ rowpos, const int* __restrict__ rowmap,
-                           float* __restrict__ vals, int* __restrict__ flat, int* __restrict__ cidx,
-                           uint2* __restrict__ ent, int* __restrict__ perm, const int* __restrict__ heavy,
-                           int nparts, int spp, const int* __restrict__ segcnt, int Rpad) {
+struct FillArgs {                                     // of one view
+    const uint8_t* mask;
+    const float* W;
+    int O, I, KS, msub, nsub, NBpad, NB, Rpad;
+    const int *rowptr, *ptr, *rowpos, *rowmap, *segcnt, *heavy;
+    float* vals;
+    int *flat, *cidx, *perm;
+    uint2* ent;
+    int nparts, spp;                                  // (row view)
+    int col_tiles;                                    // (col view)
+};
+__global__ __launch_bounds__(256) void k_fill_row(const Batch<FillArgs> batch) {
+    unsigned blk = blockIdx.x;
+    const FillArgs& a = batch.entry(blk);
+    const uint8_t* __restrict__ mask = a.mask;
+    const float* __restrict__ W = a.W;
+    const int O = a.O, I = a.I, KS = a.KS, msub = a.msub, nsub = a.nsub, NBpad = a.NBpad, NB = a.NB, Rpad = a.Rpad;
+    const int *__restrict__ rowptr = a.rowptr, *__restrict__ ptr = a.ptr, *__restrict__ rowpos = a.rowpos, *__restrict__ rowmap = a.rowmap;
+    const int *__restrict__ heavy = a.heavy, *__restrict__ segcnt = a.segcnt;
+    float* __restrict__ vals = a.vals;
+    int *__restrict__ flat = a.flat, *__restrict__ cidx = a.cidx, *__restrict__ perm = a.perm;
+    uint2* __restrict__ ent = a.ent;
+    const int nparts = a.nparts, spp = a.spp;
     const int lane = threadIdx.x & 63;
-    const int unit = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    const int unit = (int)blk * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const int r = unit / nparts, s0 = (unit % nparts) * spp, s1 = min(nsub, s0 + spp);
     if (r >= NB * RB) return;
     // a heavy row (HEAVY_MAX = 64 list entries, one per lane) fills the canonical arrays only
@@ -515,18 +583,30 @@ __global__ void k_fill_row(const uint8_t* __restrict__ mask, const float* __rest
 // the ordered compaction of the mask as ONE sequence of N positions: a wavefront owns a segment of
 // CSEG consecutive positions whatever the layer's shape is (one wavefront per row leaves a
 // layer of few long rows with a handful of workgroups).
-constexpr int CSEG = 2048;
-
 __device__ inline int nonzero_bytes(uint32_t x) {
     const uint32_t t = (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u;
     return __popc(t);
 }
 
 // active positions of every segment
-__global__ __launch_bounds__(256) void k_count_seg(const uint8_t* __restrict__ mask, int64_t N, int nseg,
-                                                   int* __restrict__ segcnt) {
+struct CanonicalArgs {
+    const uint8_t* mask;
+    const float* W;
+    int O, I;
+    int64_t N;
+    int nseg;
+    int *segcnt, *rowptr, *flat;
+    float* vals;
+};
+__global__ __launch_bounds__(256) void k_count_seg(const Batch<CanonicalArgs> batch) {
+    unsigned blk = blockIdx.x;
+    const CanonicalArgs& a = batch.entry(blk);
+    const uint8_t* __restrict__ mask = a.mask;
+    const int64_t N = a.N;
+    const int nseg = a.nseg;
+    int* __restrict__ segcnt = a.segcnt;
     const int lane = threadIdx.x & 63;
-    const int sg = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int sg = (int)blk * 4 + (threadIdx.x >> 6);
     if (sg >= nseg) return;
     const int64_t base = (int64_t)sg * CSEG;
     int c = 0;
@@ -547,12 +627,19 @@ __global__ __launch_bounds__(256) void k_count_seg(const uint8_t* __restrict__ m
 // segptr[sg] = active positions before segment sg.  A lane takes four consecutive positions of a
 // window of 256; the row pointers are written by the wavefront whose segment holds the row's
 // first position (rowptr[O] by the last one).
-__global__ __launch_bounds__(256) void k_fill_canonical(const uint8_t* __restrict__ mask, const float* __restrict__ W, int O, int I,
-                                                        int64_t N, int nseg, const int* __restrict__ segptr,
-                                                        int* __restrict__ rowptr, float* __restrict__ vals,
-                                                        int* __restrict__ flat) {
+__global__ __launch_bounds__(256) void k_fill_canonical(const Batch<CanonicalArgs> batch) {
+    unsigned blk = blockIdx.x;
+    const CanonicalArgs& a = batch.entry(blk);
+    const uint8_t* __restrict__ mask = a.mask;
+    const float* __restrict__ W = a.W;
+    const int O = a.O, I = a.I, nseg = a.nseg;
+    const int64_t N = a.N;
+    const int* __restrict__ segptr = a.segcnt;
+    int* __restrict__ rowptr = a.rowptr;
+    float* __restrict__ vals = a.vals;
+    int* __restrict__ flat = a.flat;
     const int lane = threadIdx.x & 63;
-    const int sg = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int sg = (int)blk * 4 + (threadIdx.x >> 6);
     if (sg >= nseg) return;
     const int64_t base = (int64_t)sg * CSEG, end = min(N, base + (int64_t)CSEG);
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -603,16 +690,20 @@ __global__ __launch_bounds__(256) void k_fill_canonical(const uint8_t* __restric
 // mask tile sits in LDS; thread (column j, row group rg of 32 rows) counts its rows, the
 // counts of the chunk's earlier sub-chunks and of the row groups before it give the position of its
 // first entry in the column's list, then it writes its entries in row order.
-__global__ __launch_bounds__(256) void k_fill_col(const uint8_t* __restrict__ mask, const float* __restrict__ W,
-                                                  int O, int I, int KS, int msub, int nsub, int NBpad, int NB, int Rpad,
-                                                  const int* __restrict__ segcnt, const int* __restrict__ ptr,
-                                                  const int* __restrict__ rowpos, const int* __restrict__ rowmap,
-                                                  const int* __restrict__ cidx,
-                                                  uint2* __restrict__ ent, int* __restrict__ perm) {
+__global__ __launch_bounds__(256) void k_fill_col(const Batch<FillArgs> batch) {
     __shared__ __attribute__((aligned(16))) uint8_t m[KSMAX * MT_LD];
     __shared__ int part[4][MT_COLS];
+    unsigned blk = blockIdx.x;
+    const FillArgs& a = batch.entry(blk);
+    const uint8_t* __restrict__ mask = a.mask;
+    const float* __restrict__ W = a.W;
+    const int O = a.O, I = a.I, KS = a.KS, msub = a.msub, nsub = a.nsub, NBpad = a.NBpad, NB = a.NB, Rpad = a.Rpad;
+    const int *__restrict__ segcnt = a.segcnt, *__restrict__ ptr = a.ptr, *__restrict__ rowpos = a.rowpos, *__restrict__ rowmap = a.rowmap;
+    const int* __restrict__ cidx = a.cidx;
+    uint2* __restrict__ ent = a.ent;
+    int* __restrict__ perm = a.perm;
     const int tid = threadIdx.x, j = tid & 63, rg = tid >> 6;
-    const int i0 = blockIdx.x * MT_COLS, sc = blockIdx.y, c = sc / msub, i = i0 + j;
+    const int i0 = (int)(blk % (unsigned)a.col_tiles) * MT_COLS, sc = (int)(blk / (unsigned)a.col_tiles), c = sc / msub, i = i0 + j;
     const int o0 = sc * KS, oc0 = c * msub * KS;
     load_mask_tile(mask, O, I, o0, KS, i0, m, tid);
     __syncthreads();
@@ -723,8 +814,10 @@ __global__ void k_copy_i32(const int* __restrict__ src, int* __restrict__ dst, i
 // ------------------------------------------------------------------ build
 
 // out[j] = sum of in[0 .. j), out[n] = total; in == out is allowed
-int scan_excl_i32(const int* in, int* out, int64_t n, hipStream_t s) {
-    k_scan_excl<<<1, 1024, 0, s>>>(in, out, n);
+static int scan_excl_i32(const int* in, int* out, int64_t n, hipStream_t s) {
+    Batch<ScanArgs> b;
+    b.add(ScanArgs{in, out, n}, 1);
+    k_scan_excl<<<1, 1024, 0, s>>>(b);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
@@ -737,77 +830,88 @@ int fill_u32(void* dst, uint32_t value, int64_t n_words, hipStream_t s) {
     return MST_OK;
 }
 
-// One view: count per (row, sub-chunk) -> ranking of every block's rows with the segments' lengths ->
-// pointers of the octet segments (with the view's cost for the weight gradient) -> ordered compaction.  Four launches; nothing is cleared beforehand:
-// the count kernels write the padding rows' zero counts and the fill kernels their own padding.
-static int build_one_view(View& v, bool row_view, const mst_layer* L, const float* Wsrc, const Workspace& ws, bool keep_dense_copy,
-                          hipStream_t s) {
-    const int O = L->O, I = L->I;
-    const int Rpad = v.NBpad * RB, nsub = v.nsub();
-    if (row_view) {
-        k_count_row<<<Rpad, 256, (size_t)nsub * 4, s>>>(L->mask, O, I, v.KS, nsub, Rpad, ws.segcnt, ws.rowcnt);
-        if (L->heavy_on) {
-            MST_LAUNCH_CHECK();
-            const int rc = heavy_mark(L, ws, Rpad, s);  // heavy rows leave the view
+// Rebuilds vals / flat / rowptr and both views of the layers from their masks and dense weight arrays: counts per (row, sub-chunk)
+// of both views -> ranking of every block's rows with the segments' lengths -> pointers of the octet segments (with the views'
+// costs for the weight gradient) -> ordered compaction of the row views -> of the col views, which need the canonical
+// indices that the row views' pass writes to ws.cidx.  Five launches for all layers and both views (eight per layer before);
+// nothing is cleared beforehand: the count kernel writes the padding rows' zero counts and the fill kernels their own padding.
+int build_views(const BuildItem* items, int n, hipStream_t s) {
+    Batch<CountArgs> count;
+    Batch<RankArgs> rank;
+    Batch<PtrArgs> ptr;
+    Batch<FillArgs> fill_r, fill_c;
+    int nsub_max = 1;
+    for (int x = 0; x < n; ++x) {
+        mst_layer* L = items[x].L;
+        const Workspace& ws = items[x].ws;
+        L->views_valid = false;
+        const View &r = L->row, &c = L->col;
+        const int O = L->O, I = L->I, Rpad_r = r.NBpad * RB, Rpad_c = c.NBpad * RB;
+        nsub_max = std::max(nsub_max, r.nsub());
+        const int tiles = (int)cdiv(Rpad_c, MT_COLS);
+        count.add(CountArgs{L->mask, O, I, r.KS, r.nsub(), Rpad_r, c.KS, Rpad_c, Rpad_r, tiles, ws.segcnt[0], ws.rowcnt, ws.segcnt[1]},
+                  Rpad_r + (int64_t)tiles * c.nsub());
+        auto view = [&](const View& v, int which) {
+            return ViewArgs{ws.segcnt[which], v.msub, v.nchunk, v.NBpad * RB, v.NBpad, v.NB, v.nseg, v.rowmap, v.rowpos, ws.qlen[which], v.ptr};
+        };
+        rank.add(RankArgs{view(r, 0), view(c, 1)}, r.NBpad + c.NBpad);
+        ptr.add(PtrArgs{ws.rowcnt, L->rowptr, O, L->walk_cost, L->heavy_on ? L->heavy : nullptr, L->dense_live, items[x].keep_dense_copy ? 1 : 0}, 2);
+        const int nrows = r.NB * RB, nparts = std::max(1, std::min(r.nsub(), 8192 / nrows));
+        fill_r.add(FillArgs{L->mask, items[x].Wsrc, O, I, r.KS, r.msub, r.nsub(), r.NBpad, r.NB, Rpad_r, L->rowptr, r.ptr, r.rowpos, r.rowmap,
+                            ws.segcnt[0], L->heavy_on ? L->heavy : nullptr, L->vals, L->flat, ws.cidx, r.perm, reinterpret_cast<uint2*>(r.ent),
+                            nparts, (int)cdiv(r.nsub(), nparts), 0},
+                   cdiv((int64_t)nrows * nparts, 4));
+        const int ctiles = (int)cdiv(c.NB * RB, MT_COLS);
+        fill_c.add(FillArgs{L->mask, items[x].Wsrc, O, I, c.KS, c.msub, c.nsub(), c.NBpad, c.NB, Rpad_c, nullptr, c.ptr, c.rowpos, c.rowmap,
+                            ws.segcnt[1], nullptr, nullptr, nullptr, ws.cidx, c.perm, reinterpret_cast<uint2*>(c.ent), 0, 0, ctiles},
+                   (int64_t)ctiles * c.nsub());
+    }
+    k_count<<<count.blocks(), 256, (size_t)nsub_max * 4, s>>>(count);
+    MST_LAUNCH_CHECK();
+    for (int x = 0; x < n; ++x)
+        if (items[x].L->heavy_on) {
+            const int rc = heavy_mark(items[x].L, items[x].ws, items[x].L->row.NBpad * RB, s);  // heavy rows leave the view
             if (rc != MST_OK) return rc;
         }
-    } else {
-        dim3 gcnt((unsigned)cdiv(Rpad, 64), (unsigned)nsub);
-        k_count_col<<<gcnt, 256, 0, s>>>(L->mask, O, I, v.KS, Rpad, ws.segcnt);
-    }
+    k_block_rank<<<rank.blocks(), RB, 0, s>>>(rank);
     MST_LAUNCH_CHECK();
-    k_block_rank<<<(unsigned)v.NBpad, RB, 0, s>>>(ws.segcnt, v.msub, v.nchunk, Rpad, v.NBpad, v.rowmap, v.rowpos, ws.qlen);
+    k_view_ptr<<<2 * n, 1024, 0, s>>>(rank, ptr);
     MST_LAUNCH_CHECK();
-    k_view_ptr<<<1, 1024, 0, s>>>(row_view ? ws.rowcnt : nullptr, L->rowptr, O, ws.qlen, v.NBpad, v.NB, v.nchunk, v.nseg,
-                                  v.ptr, L->walk_cost + (row_view ? 0 : 1), row_view && L->heavy_on ? L->heavy : nullptr,
-                                  L->dense_live, keep_dense_copy ? 1 : 0);
+    k_fill_row<<<fill_r.blocks(), 256, 0, s>>>(fill_r);
     MST_LAUNCH_CHECK();
-    if (row_view) {
-        const int nrows = v.NB * RB;
-        const int nparts = std::max(1, std::min(nsub, 8192 / nrows));
-        const int spp = (int)cdiv(nsub, nparts);
-        k_fill_row<<<(unsigned)cdiv((int64_t)nrows * nparts, 4), 256, 0, s>>>(
-            L->mask, Wsrc, O, I, v.KS, v.msub, nsub, v.NBpad, v.NB, L->rowptr, v.ptr, v.rowpos, v.rowmap, L->vals, L->flat,
-            ws.cidx, reinterpret_cast<uint2*>(v.ent), v.perm, L->heavy_on ? L->heavy : nullptr, nparts, spp, ws.segcnt, Rpad);
-        if (L->heavy_on) {
-            MST_LAUNCH_CHECK();
-            const int rc = heavy_fill(L, s);
+    for (int x = 0; x < n; ++x)
+        if (items[x].L->heavy_on) {
+            const int rc = heavy_fill(items[x].L, s);
             if (rc != MST_OK) return rc;
         }
-    } else {
-        dim3 gcol((unsigned)cdiv(v.NB * RB, 64), (unsigned)nsub);
-        k_fill_col<<<gcol, 256, 0, s>>>(L->mask, Wsrc, O, I, v.KS, v.msub, nsub, v.NBpad, v.NB, Rpad, ws.segcnt, v.ptr, v.rowpos,
-                                        v.rowmap, ws.cidx, reinterpret_cast<uint2*>(v.ent), v.perm);
-    }
+    k_fill_col<<<fill_c.blocks(), 256, 0, s>>>(fill_c);
     MST_LAUNCH_CHECK();
+    for (int x = 0; x < n; ++x) {
+        mst_layer* L = items[x].L;
+        L->views_valid = true;
+        L->row_stale = L->col_stale = false;
+        if (!items[x].keep_dense_copy) L->Wd_valid = L->Wd_zeros = false;
+    }
     return MST_OK;
 }
 
-// Rebuilds vals / flat / rowptr and both views from the layer's mask and a dense weight
-// array (read at the active positions only).  The col view needs the canonical indices the
-// row view pass writes to ws.cidx.
-int build_views(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_t s, bool keep_dense_copy) {
-    L->views_valid = false;
-    int rc = build_one_view(L->row, true, L, Wsrc, ws, keep_dense_copy, s);
-    if (rc != MST_OK) return rc;
-    rc = build_one_view(L->col, false, L, Wsrc, ws, keep_dense_copy, s);
-    if (rc != MST_OK) return rc;
-    L->views_valid = true;
-    L->row_stale = L->col_stale = false;
-    if (!keep_dense_copy) L->Wd_valid = L->Wd_zeros = false;
-    return MST_OK;
-}
-
-// vals / flat / rowptr alone (three launches): what a layer served by the dense contractions needs
-int build_canonical(mst_layer* L, const float* Wsrc, const Workspace& ws, hipStream_t s) {
-    L->views_valid = false;
-    const int nseg = (int)cdiv(L->N, CSEG);
-    k_count_seg<<<(unsigned)cdiv(nseg, 4), 256, 0, s>>>(L->mask, L->N, nseg, ws.segcnt);
+// vals / flat / rowptr alone (three launches): what layers served by the dense contractions need
+int build_canonical(const BuildItem* items, int n, hipStream_t s) {
+    Batch<CanonicalArgs> seg;
+    Batch<ScanArgs> scan;
+    for (int x = 0; x < n; ++x) {
+        mst_layer* L = items[x].L;
+        int* const cnt = items[x].ws.segcnt[0];
+        const int nseg = (int)cdiv(L->N, CSEG);
+        L->views_valid = false;
+        seg.add(CanonicalArgs{L->mask, items[x].Wsrc, L->O, L->I, L->N, nseg, cnt, L->rowptr, L->flat, L->vals}, cdiv(nseg, 4));
+        scan.add(ScanArgs{cnt, cnt, nseg}, 1);
+    }
+    k_count_seg<<<seg.blocks(), 256, 0, s>>>(seg);
     MST_LAUNCH_CHECK();
-    const int rc = scan_excl_i32(ws.segcnt, ws.segcnt, nseg, s);
-    if (rc != MST_OK) return rc;
-    k_fill_canonical<<<(unsigned)cdiv(nseg, 4), 256, 0, s>>>(L->mask, Wsrc, L->O, L->I, L->N, nseg, ws.segcnt, L->rowptr, L->vals,
-                                                          L->flat);
+    k_scan_excl<<<n, 1024, 0, s>>>(scan);
+    MST_LAUNCH_CHECK();
+    k_fill_canonical<<<seg.blocks(), 256, 0, s>>>(seg);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
@@ -872,7 +976,8 @@ int ensure_views(const mst_layer* Lc, const Workspace& ws, hipStream_t s) {
         const int rc = refresh_dense_copy(L, s);
         if (rc != MST_OK) return rc;
     }
-    return build_views(L, L->Wd, ws, s, true);
+    const BuildItem item{L, L->Wd, ws, true};
+    return build_views(&item, 1, s);
 }
 
 // After an update: will a sparse kernel walk the views?  Judged at the batch size and type of
@@ -953,7 +1058,9 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
     if (ws_bytes < ws.total) return MST_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     // learn the active count first so that nothing is written when it does not fit
-    k_count_row<<<L->O, 256, (size_t)L->row.nsub() * 4, s>>>(M_dev, L->O, L->I, L->row.KS, L->row.nsub(), 0, nullptr, ws.rowcnt);
+    Batch<CountArgs> count;
+    count.add(CountArgs{M_dev, L->O, L->I, L->row.KS, L->row.nsub(), 0, 0, 0, L->O, 1, nullptr, ws.rowcnt, nullptr}, L->O);
+    k_count<<<L->O, 256, (size_t)L->row.nsub() * 4, s>>>(count);
     MST_LAUNCH_CHECK();
     int rcs = scan_excl_i32(ws.rowcnt, L->rowptr, L->O, s);          // rebuilt below anyway
     if (rcs != MST_OK) return rcs;
@@ -973,7 +1080,8 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
     // only if it found rows; the forced mode of the hook keeps it for every layer.
     const int mode = heavy_rows_mode();
     L->heavy_on = mode == 2 || (mode == 1 && L->N >= ((int64_t)1 << 20));
-    const int rc = build_views(L, W_dev, ws, s);
+    const BuildItem item{L, W_dev, ws, false};
+    const int rc = build_views(&item, 1, s);
     if (rc != MST_OK) return rc;
     if (L->heavy_on && mode == 1) {
         int found = 0;

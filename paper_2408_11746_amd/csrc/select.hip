@@ -27,31 +27,27 @@ __device__ inline uint64_t splitmix64_at(uint64_t seed, uint64_t f) {
 // A key source answers get(i, key): is index i a candidate, and with which key.  get4 does the
 // same for the four indices i .. i+3 of an aligned group (i a multiple of 4, all below n) with
 // vector loads where the arrays allow it.
+// |w|, or with lambda (flat and G then given) |w| + lambda |grad|, both roundings explicit (no contraction into one fused
+// operation); a non-negative float orders like its bit pattern
 struct PruneKeys {
-    typedef uint32_t key_t;
-    const float* vals;
-    __device__ bool get(int64_t k, key_t& key) const { key = abs_bits(vals[k]); return true; }
-    __device__ void get4(int64_t k, key_t (&key)[4], bool (&ok)[4]) const {
-        const float4 v = *reinterpret_cast<const float4*>(vals + k);
-        key[0] = abs_bits(v.x); key[1] = abs_bits(v.y); key[2] = abs_bits(v.z); key[3] = abs_bits(v.w);
-        ok[0] = ok[1] = ok[2] = ok[3] = true;
-    }
-};
-// |w| + lambda |grad|, both roundings explicit (no contraction into one fused operation);
-// a non-negative float orders like its bit pattern
-struct ScoredPruneKeys {
     typedef uint32_t key_t;
     const float* vals;
     const int* flat;
     const float* G;
     float lambda;
     __device__ bool get(int64_t k, key_t& key) const {
-        key = __float_as_uint(__fadd_rn(fabsf(vals[k]), __fmul_rn(lambda, fabsf(G[flat[k]]))));
+        key = lambda == 0.f ? abs_bits(vals[k]) : __float_as_uint(__fadd_rn(fabsf(vals[k]), __fmul_rn(lambda, fabsf(G[flat[k]]))));
         return true;
     }
     __device__ void get4(int64_t k, key_t (&key)[4], bool (&ok)[4]) const {
+        if (lambda == 0.f) {
+            const float4 v = *reinterpret_cast<const float4*>(vals + k);
+            key[0] = abs_bits(v.x); key[1] = abs_bits(v.y); key[2] = abs_bits(v.z); key[3] = abs_bits(v.w);
+            ok[0] = ok[1] = ok[2] = ok[3] = true;
+        } else {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) ok[u] = get(k + u, key[u]);
+            for (int u = 0; u < 4; ++u) ok[u] = get(k + u, key[u]);
+        }
     }
 };
 struct GradKeys {
@@ -214,15 +210,42 @@ __device__ void select_digit_block(KS ks, int64_t n, uint64_t* __restrict__ stat
     }
 }
 
-// Two independent selections (the prune set and the gradient-growth set of one update) share
-// their digit passes: blocks [0, nb0) work on the first, the others on the second.
-template <typename KS0, typename KS1>
-__global__ __launch_bounds__(SEL_NT) void k_select_digit2(KS0 ks0, int64_t n0, uint64_t* __restrict__ st0, int nb0, int shift0,
-                                                          int width0, KS1 ks1, int64_t n1, uint64_t* __restrict__ st1, int nb1,
-                                                          int shift1, int width1, int first) {
+// What the flag pass of a selection does with index i beyond flags[i] = code for a selected one.
+struct FlagSink {
+    uint8_t* flags;
+    uint8_t code;
+    int full;            // 1: every index below n gets its flag (0 if not selected); 0: only the selected ones are written
+    uint8_t* grow_mask;  // not null: a selected position becomes active ...
+    float* grow_w;       // ... and its weight in the dense scratch starts at zero
+    __device__ void put(int64_t i, bool take) const {
+        if (take) {
+            flags[i] = code;
+            if (grow_mask) { grow_mask[i] = 1; grow_w[i] = 0.f; }
+        } else if (full) {
+            flags[i] = 0;
+        }
+    }
+};
+
+// Two independent selections of every layer (the prune set over its nnz active weights, the gradient-growth set over all N
+// positions) share their passes: the first nb0 blocks of a layer work on the first, the others on the second (no blocks:
+// no such selection).
+struct SelectArgs {
+    PruneKeys pk;
+    GradKeys gk;
+    int64_t nnz, N;
+    uint64_t *st_p, *st_g;
+    int *blk_p, *blk_g;
+    FlagSink sink_p, sink_g;
+    int dig0, dig1;      // blocks of a digit pass
+    int nb0;             // blocks of the tie and flag passes for the first
+};
+__global__ __launch_bounds__(SEL_NT) void k_select_digit2(const Batch<SelectArgs> batch, int shift, int width, int first) {
     __shared__ DigitShared sh;
-    if ((int)blockIdx.x < nb0) select_digit_block(ks0, n0, st0, shift0, width0, first, (int)blockIdx.x, nb0, sh);
-    else select_digit_block(ks1, n1, st1, shift1, width1, first, (int)blockIdx.x - nb0, nb1, sh);
+    unsigned b = blockIdx.x;
+    const SelectArgs& a = batch.entry(b);
+    if ((int)b < a.dig0) select_digit_block(a.pk, a.nnz, a.st_p, shift, width, first, (int)b, a.dig0, sh);
+    else select_digit_block(a.gk, a.N, a.st_g, shift, width, first, (int)b - a.dig0, a.dig1, sh);
 }
 
 // per block of SELECT_BLOCK indices: how many candidates carry exactly the threshold key
@@ -245,30 +268,13 @@ __device__ void select_ties_block(KS ks, int64_t n, const uint64_t* __restrict__
     if (threadIdx.x == 0) blk[b] = cnt;
 }
 
-template <typename KS0, typename KS1>
-__global__ void k_select_ties2(KS0 ks0, int64_t n0, const uint64_t* __restrict__ st0, int* __restrict__ blk0, int nb0,
-                               KS1 ks1, int64_t n1, const uint64_t* __restrict__ st1, int* __restrict__ blk1) {
+__global__ __launch_bounds__(256) void k_select_ties2(const Batch<SelectArgs> batch) {
     __shared__ int cnt;
-    if ((int)blockIdx.x < nb0) select_ties_block(ks0, n0, st0, blk0, (int)blockIdx.x, cnt);
-    else select_ties_block(ks1, n1, st1, blk1, (int)blockIdx.x - nb0, cnt);
+    unsigned b = blockIdx.x;
+    const SelectArgs& a = batch.entry(b);
+    if ((int)b < a.nb0) select_ties_block(a.pk, a.nnz, a.st_p, a.blk_p, (int)b, cnt);
+    else select_ties_block(a.gk, a.N, a.st_g, a.blk_g, (int)b - a.nb0, cnt);
 }
-
-// What the flag pass of a selection does with index i beyond flags[i] = code for a selected one.
-struct FlagSink {
-    uint8_t* flags;
-    uint8_t code;
-    int full;            // 1: every index below n gets its flag (0 if not selected); 0: only the selected ones are written
-    uint8_t* grow_mask;  // not null: a selected position becomes active ...
-    float* grow_w;       // ... and its weight in the dense scratch starts at zero
-    __device__ void put(int64_t i, bool take) const {
-        if (take) {
-            flags[i] = code;
-            if (grow_mask) { grow_mask[i] = 1; grow_w[i] = 0.f; }
-        } else if (full) {
-            flags[i] = 0;
-        }
-    }
-};
 
 // flags of block b; 256 threads, 8 consecutive indices each.  Keys equal to the threshold are
 // taken in index order: a key's rank is the count of such keys in the blocks before this one
@@ -337,23 +343,13 @@ __device__ void select_flag_block(KS ks, int64_t n, const uint64_t* __restrict__
     }
 }
 
-template <typename KS0, typename KS1>
-__global__ __launch_bounds__(256) void k_select_flag2(KS0 ks0, int64_t n0, const uint64_t* __restrict__ st0,
-                                                      const int* __restrict__ blk0, FlagSink sink0, int nb0, KS1 ks1, int64_t n1,
-                                                      const uint64_t* __restrict__ st1, const int* __restrict__ blk1,
-                                                      FlagSink sink1) {
+__global__ __launch_bounds__(256) void k_select_flag2(const Batch<SelectArgs> batch) {
     __shared__ int wsum[4];
     __shared__ int64_t before_s[4];
-    if ((int)blockIdx.x < nb0) select_flag_block(ks0, n0, st0, blk0, sink0, (int)blockIdx.x, wsum, before_s);
-    else select_flag_block(ks1, n1, st1, blk1, sink1, (int)blockIdx.x - nb0, wsum, before_s);
-}
-
-template <typename KS>
-__global__ __launch_bounds__(256) void k_select_flag(KS ks, int64_t n, const uint64_t* __restrict__ state,
-                                                     const int* __restrict__ blk, FlagSink sink) {
-    __shared__ int wsum[4];
-    __shared__ int64_t before_s[4];
-    select_flag_block(ks, n, state, blk, sink, (int)blockIdx.x, wsum, before_s);
+    unsigned b = blockIdx.x;
+    const SelectArgs& a = batch.entry(b);
+    if ((int)b < a.nb0) select_flag_block(a.pk, a.nnz, a.st_p, a.blk_p, a.sink_p, (int)b, wsum, before_s);
+    else select_flag_block(a.gk, a.N, a.st_g, a.blk_g, a.sink_g, (int)b - a.nb0, wsum, before_s);
 }
 
 // ---- the random selection.  Its keys are 64-bit hashes of the index: uniform, and distinct for
@@ -370,15 +366,29 @@ struct RandItem {
     int64_t f;
 };
 
-__global__ __launch_bounds__(SEL_NT) void k_rand_hist(RandKeys ks, int64_t n, uint64_t* __restrict__ state) {
+struct RandArgs {
+    RandKeys ks;
+    int64_t n;
+    uint64_t* state;
+    RandItem* list;
+    FlagSink sink;
+    int hist_blocks;
+};
+__global__ __launch_bounds__(SEL_NT) void k_rand_hist(const Batch<RandArgs> batch) {
+    unsigned blk = blockIdx.x;
+    const RandArgs& a = batch.entry(blk);
+    const RandKeys ks = a.ks;
+    const int64_t n = a.n;
+    uint64_t* __restrict__ state = a.state;
+    const int nblk = a.hist_blocks;
     __shared__ uint32_t h[RAND_BINS];
     __shared__ uint32_t part[16];
     __shared__ int is_last;
     const int tid = threadIdx.x;
     for (int i = tid; i < RAND_BINS; i += SEL_NT) h[i] = 0;
     __syncthreads();
-    const int64_t stride = (int64_t)gridDim.x * SEL_NT * 4;
-    for (int64_t i0 = ((int64_t)blockIdx.x * SEL_NT + tid) * 4; i0 < n; i0 += stride) {
+    const int64_t stride = (int64_t)nblk * SEL_NT * 4;
+    for (int64_t i0 = ((int64_t)blk * SEL_NT + tid) * 4; i0 < n; i0 += stride) {
         uint64_t key[4];
         bool ok[4];
         keys_of_group(ks, i0, n, key, ok);
@@ -397,7 +407,7 @@ __global__ __launch_bounds__(SEL_NT) void k_rand_hist(RandKeys ks, int64_t n, ui
     __syncthreads();
     if (tid == 0) {
         const unsigned long long ticket = atomicAdd(reinterpret_cast<unsigned long long*>(state + 3), 1ull);
-        is_last = ticket == (unsigned long long)gridDim.x - 1ull;
+        is_last = ticket == (unsigned long long)nblk - 1ull;
     }
     __syncthreads();
     if (!is_last) return;
@@ -439,8 +449,14 @@ __global__ __launch_bounds__(SEL_NT) void k_rand_hist(RandKeys ks, int64_t n, ui
 // the spot; those of the picked bin (about 16 per block) are gathered in LDS and appended to the
 // list with ONE add to its length (an add per hit would queue up at the counter)
 constexpr int COMPACT_PER_BLOCK = SEL_NT * 16, COMPACT_STAGE = 512;
-__global__ __launch_bounds__(SEL_NT) void k_rand_compact(RandKeys ks, int64_t n, uint64_t* __restrict__ state,
-                                                         RandItem* __restrict__ list, FlagSink sink) {
+__global__ __launch_bounds__(SEL_NT) void k_rand_compact(const Batch<RandArgs> batch) {       // COMPACT_PER_BLOCK indices per block
+    unsigned blk = blockIdx.x;
+    const RandArgs& a = batch.entry(blk);
+    const RandKeys ks = a.ks;
+    const int64_t n = a.n;
+    uint64_t* __restrict__ state = a.state;
+    RandItem* __restrict__ list = a.list;
+    const FlagSink sink = a.sink;
     __shared__ RandItem stage[COMPACT_STAGE];
     __shared__ unsigned int nstage;
     __shared__ unsigned long long base_s;
@@ -450,7 +466,7 @@ __global__ __launch_bounds__(SEL_NT) void k_rand_compact(RandKeys ks, int64_t n,
     __syncthreads();
     const uint64_t top = state[0] >> RAND_SHIFT;
     unsigned long long* len = reinterpret_cast<unsigned long long*>(state + 4);
-    const int64_t b0 = (int64_t)blockIdx.x * COMPACT_PER_BLOCK;
+    const int64_t b0 = (int64_t)blk * COMPACT_PER_BLOCK;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int64_t i4 = b0 + ((int64_t)r * SEL_NT + tid) * 4;
@@ -482,8 +498,11 @@ __global__ __launch_bounds__(SEL_NT) void k_rand_compact(RandKeys ks, int64_t n,
 // one block: the state[1]-th smallest (key, index) of the list decides the threshold.  Lists of up to
 // RAND_LDS_KEYS items (the usual case by far) are searched in LDS.
 constexpr int RAND_LDS_KEYS = 7168;
-__global__ __launch_bounds__(SEL_NT) void k_rand_finish(uint64_t* __restrict__ state, const RandItem* __restrict__ list,
-                                                        FlagSink sink) {
+__global__ __launch_bounds__(SEL_NT) void k_rand_finish(const Batch<RandArgs> batch) {        // a block per layer
+    const RandArgs& a = batch.p[blockIdx.x];
+    uint64_t* __restrict__ state = a.state;
+    const RandItem* __restrict__ list = a.list;
+    const FlagSink sink = a.sink;
     __shared__ uint64_t keys[RAND_LDS_KEYS];
     __shared__ uint32_t h[SEL_BINS];
     __shared__ uint32_t wtot[4];
@@ -570,122 +589,152 @@ __global__ __launch_bounds__(SEL_NT) void k_rand_finish(uint64_t* __restrict__ s
     }
 }
 
-// start of an update: the three selection states
-__global__ void k_update_init(uint64_t* __restrict__ state, uint64_t k0, uint64_t k1, uint64_t k2) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// start of an update: the three selection states of every layer
+struct InitArgs {
+    uint64_t *state, k[SEL_STATES];
+};
+__global__ __launch_bounds__(256) void k_update_init(const Batch<InitArgs> batch) {
+    unsigned b = blockIdx.x;
+    const InitArgs& a = batch.entry(b);
+    const int64_t i = (int64_t)b * blockDim.x + threadIdx.x;
     if (i < (int64_t)SEL_STATES * SEL_STATE_WORDS) {
         const int w = (int)(i % SEL_STATE_WORDS), which = (int)(i / SEL_STATE_WORDS);
-        state[i] = (w == 1) ? (which == 0 ? k0 : which == 1 ? k1 : k2) : 0ull;
+        a.state[i] = (w == 1) ? (which == 0 ? a.k[0] : which == 1 ? a.k[1] : a.k[2]) : 0ull;
     }
 }
 
 // kept weights go to the dense scratch, pruned positions leave the mask (psel null: nothing is pruned)
 // (zero_pruned: Wd is the layer's dense copy, whose inactive positions must read 0)
-__global__ void k_apply_prune(const float* __restrict__ vals, const int* __restrict__ flat,
-                              const uint8_t* __restrict__ psel, int64_t nnz, float* __restrict__ Wd,
-                              uint8_t* __restrict__ mask, int zero_pruned) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= nnz) return;
-    const int f = flat[k];
-    if (psel && psel[k]) {
-        mask[f] = 0;
-        if (zero_pruned) Wd[f] = 0.f;
+struct PruneArgs {
+    const float* vals;
+    const int* flat;
+    const uint8_t* psel;
+    int64_t nnz;
+    float* Wd;
+    uint8_t* mask;
+    int zero_pruned;
+};
+__global__ __launch_bounds__(256) void k_apply_prune(const Batch<PruneArgs> batch) {
+    unsigned b = blockIdx.x;
+    const PruneArgs& a = batch.entry(b);
+    const int64_t k = (int64_t)b * blockDim.x + threadIdx.x;
+    if (k >= a.nnz) return;
+    const int f = a.flat[k];
+    if (a.psel && a.psel[k]) {
+        a.mask[f] = 0;
+        if (a.zero_pruned) a.Wd[f] = 0.f;
     } else {
-        Wd[f] = vals[k];
+        a.Wd[f] = a.vals[k];
     }
 }
 
-static unsigned digit_blocks(int64_t n) { return (unsigned)std::min<int64_t>(cdiv(n, SEL_NT * 4), 256); }
+// Blocks of a digit pass over n keys: four keys per thread and round, and together no more than what the chip holds
+// at a time (two of 64 KB on a CU): a block costs the clearing and the sum of its histogram whatever it reads.
+// `total`: keys of all selections of the launch.
+static unsigned digit_blocks(int64_t n, int64_t total) {
+    const int64_t share = std::max<int64_t>(1, 512 * n / std::max<int64_t>(total, 1));
+    return (unsigned)std::min<int64_t>(std::min<int64_t>(cdiv(n, SEL_NT * 4), 256), share);
+}
 static unsigned rand_blocks(int64_t n) { return (unsigned)std::min<int64_t>(cdiv(n, SEL_NT * 8), 256); }
 
-// prune set (over the nnz active weights) and gradient-growth set (over all N positions) of one
-// update, side by side: 4 digit launches, one tie-count launch, one flag launch
-template <typename PK>
-static int select_prune_and_grad(PK pk, int64_t nnz, int64_t n_prune, GradKeys gk, int64_t N, int64_t n_grad,
-                                 uint64_t* st_prune, uint64_t* st_grad, const Workspace& ws, uint8_t* mask, float* Wnew,
-                                 hipStream_t s) {
-    const bool do_p = n_prune > 0 && nnz > 0, do_g = n_grad > 0;
-    if (!do_p && !do_g) return MST_OK;
-    const int nb0 = do_p ? (int)digit_blocks(nnz) : 0, nb1 = do_g ? (int)digit_blocks(N) : 0;
-    for (int top = 32; top > 0; top -= SEL_DIGIT_BITS) {
-        const int shift = top - SEL_DIGIT_BITS;
-        k_select_digit2<PK, GradKeys><<<(unsigned)(nb0 + nb1), SEL_NT, 0, s>>>(pk, nnz, st_prune, nb0, shift, SEL_DIGIT_BITS, gk, N,
-                                                                             st_grad, nb1, shift, SEL_DIGIT_BITS, top == 32 ? 1 : 0);
+// The updates of several layers, one launch per link of the chain for all of them (up to 11 links and those of the
+// rebuild).
+int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
+    Batch<InitArgs> init;
+    Batch<SelectArgs> digit, flag;                    // the same entries with the blocks of either pass
+    Batch<RandArgs> hist, compact;
+    Batch<PruneArgs> prune;
+    BuildItem views[BATCH_MAX], canonical[BATCH_MAX];
+    int n_views = 0, n_canonical = 0, rc;
+    int64_t keys = 0;                                 // of all selections
+    for (int x = 0; x < n; ++x)
+        keys += (items[x].st.n_prune > 0 ? items[x].L->nnz : 0) + (items[x].st.n_grad > 0 ? items[x].L->N : 0);
+    for (int x = 0; x < n; ++x) {
+        mst_layer* L = items[x].L;
+        const mst_update_stats& st = items[x].st;
+        const Workspace& ws = items[x].ws;
+        const int64_t N = L->N, nnz = L->nnz;
+        // Where the new dense weights are formed.  A layer that stays on the dense contractions after
+        // this update gets them straight into its dense copy (zero at every inactive position: kept
+        // weights are rewritten, pruned and grown positions written 0) and only vals / flat / rowptr
+        // are rebuilt; otherwise they go to the workspace and both index views are rebuilt from them.
+        L->nnz = st.nnz_after;
+        L->choice.store(0, std::memory_order_relaxed);
+        const bool with_views = views_wanted(L);
+        L->nnz = nnz;
+        L->choice.store(0, std::memory_order_relaxed);
+        float* const Wnew = with_views ? ws.Wd : L->Wd;
+        if (with_views) views[n_views++] = BuildItem{L, ws.Wd, ws, false};
+        else canonical[n_canonical++] = BuildItem{L, L->Wd, ws, false};
+        if (!with_views && !L->Wd_zeros && (rc = fill_u32(L->Wd, 0u, N, s)) != MST_OK) return rc;
+        uint64_t* const st0 = ws.sel_state;
+        init.add(InitArgs{st0, {(uint64_t)st.n_prune, (uint64_t)st.n_grad, (uint64_t)st.n_rand}}, cdiv((int64_t)SEL_STATES * SEL_STATE_WORDS, 256));
+        // During the selections the mask still means "active before this update" for every position
+        // a later selection looks at: positions grown by gradient become active at once (random
+        // growth must skip them anyway), pruned positions leave the mask only at the very end.
+        const bool do_p = st.n_prune > 0 && nnz > 0, do_g = st.n_grad > 0;
+        if (do_p || do_g) {
+            SelectArgs a;
+            a.pk = PruneKeys{L->vals, L->flat, items[x].G, L->prune_lambda};
+            a.gk = GradKeys{items[x].G, L->mask};
+            a.nnz = nnz;
+            a.N = N;
+            a.st_p = st0;
+            a.st_g = st0 + SEL_STATE_WORDS;
+            a.blk_g = reinterpret_cast<int*>(ws.blk);
+            a.blk_p = reinterpret_cast<int*>(ws.blk) + cdiv(N, SELECT_BLOCK) + 1;
+            a.sink_p = FlagSink{ws.psel, 1, 1, nullptr, nullptr};
+            a.sink_g = FlagSink{ws.sel, 2, 1, L->mask, Wnew};
+            a.dig0 = do_p ? (int)digit_blocks(nnz, keys) : 0;
+            a.dig1 = do_g ? (int)digit_blocks(N, keys) : 0;
+            a.nb0 = do_p ? (int)cdiv(nnz, SELECT_BLOCK) : 0;
+            digit.add(a, a.dig0 + a.dig1);
+            flag.add(a, a.nb0 + (do_g ? cdiv(N, SELECT_BLOCK) : 0));
+        }
+        if (st.n_rand > 0) {
+            if (st.n_grad <= 0 && (rc = fill_u32(ws.sel, 0u, cdiv(N, 4), s)) != MST_OK) return rc;   // no flag pass writes sel
+            // selected positions become active (weight 0) where they are decided: below the picked bin in the
+            // compaction pass, inside it by the finishing block; no separate flag pass
+            const RandArgs a{RandKeys{L->mask, ws.sel, items[x].seed}, N, st0 + 2 * SEL_STATE_WORDS,
+                             reinterpret_cast<RandItem*>(ws.gemm),          // 2 N items fit: more than any candidate count
+                             FlagSink{ws.sel, 3, 0, L->mask, Wnew}, (int)rand_blocks(N)};
+            hist.add(a, a.hist_blocks);
+            compact.add(a, cdiv(N, COMPACT_PER_BLOCK));
+        }
+        if (nnz > 0)
+            prune.add(PruneArgs{L->vals, L->flat, st.n_prune > 0 ? ws.psel : nullptr, nnz, Wnew, L->mask, with_views ? 0 : 1}, cdiv(nnz, 256));
+    }
+    k_update_init<<<init.blocks(), 256, 0, s>>>(init);
+    MST_LAUNCH_CHECK();
+    if (digit.n > 0) {
+        for (int shift = 32 - SEL_DIGIT_BITS; shift >= 0; shift -= SEL_DIGIT_BITS) {
+            k_select_digit2<<<digit.blocks(), SEL_NT, 0, s>>>(digit, shift, SEL_DIGIT_BITS, shift == 32 - SEL_DIGIT_BITS ? 1 : 0);
+            MST_LAUNCH_CHECK();
+        }
+        k_select_ties2<<<flag.blocks(), 256, 0, s>>>(flag);
+        MST_LAUNCH_CHECK();
+        k_select_flag2<<<flag.blocks(), 256, 0, s>>>(flag);
         MST_LAUNCH_CHECK();
     }
-    const int fb0 = do_p ? (int)cdiv(nnz, SELECT_BLOCK) : 0, fb1 = do_g ? (int)cdiv(N, SELECT_BLOCK) : 0;
-    int* blk_g = reinterpret_cast<int*>(ws.blk);
-    int* blk_p = reinterpret_cast<int*>(ws.blk) + cdiv(N, SELECT_BLOCK) + 1;
-    k_select_ties2<PK, GradKeys><<<(unsigned)(fb0 + fb1), 256, 0, s>>>(pk, nnz, st_prune, blk_p, fb0, gk, N, st_grad, blk_g);
-    MST_LAUNCH_CHECK();
-    const FlagSink sink_p{ws.psel, 1, 1, nullptr, nullptr};
-    const FlagSink sink_g{ws.sel, 2, 1, mask, Wnew};
-    k_select_flag2<PK, GradKeys><<<(unsigned)(fb0 + fb1), 256, 0, s>>>(pk, nnz, st_prune, blk_p, sink_p, fb0, gk, N, st_grad, blk_g,
-                                                                     sink_g);
-    MST_LAUNCH_CHECK();
-    return MST_OK;
-}
-
-int mask_update_device(mst_layer* L, const float* G, const mst_update_stats& st, uint64_t seed,
-                       const Workspace& ws, hipStream_t s) {
-    const int64_t N = L->N, nnz = L->nnz;
-    int rc;
-    // Where the new dense weights are formed.  A layer that stays on the dense contractions after
-    // this update gets them straight into its dense copy (zero at every inactive position: kept
-    // weights are rewritten, pruned and grown positions written 0) and only vals / flat / rowptr
-    // are rebuilt; otherwise they go to the workspace and both index views are rebuilt from them.
-    const int64_t nnz_before = L->nnz;
-    L->nnz = st.nnz_after;
-    L->choice.store(0, std::memory_order_relaxed);
-    const bool with_views = views_wanted(L);
-    L->nnz = nnz_before;
-    L->choice.store(0, std::memory_order_relaxed);
-    float* const Wnew = with_views ? ws.Wd : L->Wd;
-    if (!with_views && !L->Wd_zeros && (rc = fill_u32(L->Wd, 0u, N, s)) != MST_OK) return rc;
-    uint64_t* st0 = ws.sel_state;
-    k_update_init<<<(unsigned)cdiv((int64_t)SEL_STATES * SEL_STATE_WORDS, 256), 256, 0, s>>>(
-        st0, (uint64_t)st.n_prune, (uint64_t)st.n_grad, (uint64_t)st.n_rand);
-    MST_LAUNCH_CHECK();
-
-    // During the selections the mask still means "active before this update" for every position
-    // a later selection looks at: positions grown by gradient become active at once (random
-    // growth must skip them anyway), pruned positions leave the mask only at the very end.
-    const GradKeys gk{G, L->mask};
-    uint64_t* st_grad = st0 + SEL_STATE_WORDS;
-    if (L->prune_lambda == 0.f)
-        rc = select_prune_and_grad(PruneKeys{L->vals}, nnz, st.n_prune, gk, N, st.n_grad, st0, st_grad, ws, L->mask, Wnew, s);
-    else
-        rc = select_prune_and_grad(ScoredPruneKeys{L->vals, L->flat, G, L->prune_lambda}, nnz, st.n_prune, gk, N, st.n_grad,
-                                   st0, st_grad, ws, L->mask, Wnew, s);
-    if (rc != MST_OK) return rc;
-
-    if (st.n_rand > 0) {
-        if (st.n_grad <= 0 && (rc = fill_u32(ws.sel, 0u, cdiv(N, 4), s)) != MST_OK) return rc;   // no flag pass wrote sel
-        const RandKeys rk{L->mask, ws.sel, seed};
-        uint64_t* st_rand = st0 + 2 * SEL_STATE_WORDS;
-        RandItem* list = reinterpret_cast<RandItem*>(ws.gemm);          // 2 N items fit: more than any candidate count
-        k_rand_hist<<<rand_blocks(N), SEL_NT, 0, s>>>(rk, N, st_rand);
+    if (hist.n > 0) {
+        k_rand_hist<<<hist.blocks(), SEL_NT, 0, s>>>(hist);
         MST_LAUNCH_CHECK();
-        // selected positions become active (weight 0) where they are decided: below the picked bin in the
-        // compaction pass, inside it by the finishing block; no separate flag pass
-        const FlagSink sink_r{ws.sel, 3, 0, L->mask, Wnew};
-        k_rand_compact<<<(unsigned)cdiv(N, COMPACT_PER_BLOCK), SEL_NT, 0, s>>>(rk, N, st_rand, list, sink_r);
+        k_rand_compact<<<compact.blocks(), SEL_NT, 0, s>>>(compact);
         MST_LAUNCH_CHECK();
-        k_rand_finish<<<1, SEL_NT, 0, s>>>(st_rand, list, sink_r);
+        k_rand_finish<<<hist.n, SEL_NT, 0, s>>>(hist);
         MST_LAUNCH_CHECK();
     }
-
-    if (nnz > 0) {
-        const bool pruned = st.n_prune > 0;
-        k_apply_prune<<<(unsigned)cdiv(nnz, 256), 256, 0, s>>>(L->vals, L->flat, pruned ? ws.psel : nullptr, nnz, Wnew, L->mask,
-                                                               with_views ? 0 : 1);
+    if (prune.n > 0) {
+        k_apply_prune<<<prune.blocks(), 256, 0, s>>>(prune);
         MST_LAUNCH_CHECK();
     }
-    L->nnz = st.nnz_after;
-    L->choice.store(0, std::memory_order_relaxed);
-    if (with_views) return build_views(L, ws.Wd, ws, s);
-    L->Wd_valid = L->Wd_zeros = true;
-    return build_canonical(L, L->Wd, ws, s);
+    for (int x = 0; x < n; ++x) {
+        items[x].L->nnz = items[x].st.nnz_after;
+        items[x].L->choice.store(0, std::memory_order_relaxed);
+    }
+    if (n_views > 0 && (rc = build_views(views, n_views, s)) != MST_OK) return rc;
+    for (int x = 0; x < n_canonical; ++x) canonical[x].L->Wd_valid = canonical[x].L->Wd_zeros = true;
+    return n_canonical > 0 ? build_canonical(canonical, n_canonical, s) : MST_OK;
 }
 
 }  // namespace mst
