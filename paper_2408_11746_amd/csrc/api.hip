@@ -71,25 +71,53 @@ static int ensure_dense_copy(const mst_layer* L, hipStream_t s) {
     return refresh_dense_copy(const_cast<mst_layer*>(L), s);   // cache of vals[], not layer state
 }
 
+// The weights' planes for Y (dX) where the product reads them.  They were kept up since they were first made, or are made now:
+// then products on other streams, which are ordered after the hand-over of the values and not after this call, must find
+// them, so the call waits (once: from here on sync_values and updates make them).  A recording cannot wait and runs later or never:
+// it takes their making with it and says nothing about them.
+static int ensure_planes(const mst_layer* Lc, bool y, mst_dtype act, int M, int N, int Kdim, bool full, const uint16_t*& planes, hipStream_t s) {
+    planes = nullptr;
+    if (!gemm_wants_planes(act, M, N, Kdim, full)) return MST_OK;
+    mst_layer* L = const_cast<mst_layer*>(Lc);       // a cache of Wd, not layer state
+    planes = y ? L->planes_y : L->planes_x;
+    if (L->planes_valid) return MST_OK;
+    const bool first = !L->planes_used;
+    L->planes_used = true;
+    const int rc = make_planes(L, s);
+    if (rc != MST_OK) return rc;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    MST_HIP(hipStreamIsCapturing(s, &capture));
+    if (capture != hipStreamCaptureStatusNone) return MST_OK;
+    if (first) MST_HIP(hipStreamSynchronize(s));
+    L->planes_valid = true;
+    return MST_OK;
+}
+
 // (full: see full_precision(); split_ws: room for partial outputs of a split of the contraction range, used where the output
 // has too few tiles to fill the chip; null: one workgroup per tile whatever their number)
 int dense_products_fwd(const mst_layer* L, const void* X, float* Y, int T, mst_dtype act, hipStream_t s, bool full) {
     int rc = ensure_dense_copy(L, s);
     if (rc != MST_OK) return rc;
-    return gemm_mfma(GEMM_NT, X, act, L->Wd, MST_F32, Y, T, L->O, L->I, nullptr, 0, s, full);
+    const uint16_t* planes;
+    rc = ensure_planes(L, true, act, T, L->O, L->I, full, planes, s);
+    if (rc != MST_OK) return rc;
+    return gemm_mfma(GEMM_NT, X, act, L->Wd, MST_F32, planes, Y, T, L->O, L->I, nullptr, 0, s, full);
 }
 
 int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int T, mst_dtype act, hipStream_t s, bool full,
                              float* split_ws, int64_t split_ws_floats) {
     int rc = ensure_dense_copy(L, s);
     if (rc != MST_OK) return rc;
-    return gemm_mfma(GEMM_NN, dY, act, L->Wd, MST_F32, dX, T, L->I, L->O, split_ws, split_ws_floats, s, full);
+    const uint16_t* planes;
+    rc = ensure_planes(L, false, act, T, L->I, L->O, full, planes, s);
+    if (rc != MST_OK) return rc;
+    return gemm_mfma(GEMM_NN, dY, act, L->Wd, MST_F32, planes, dX, T, L->I, L->O, split_ws, split_ws_floats, s, full);
 }
 
 int dense_products_bwd_weight(const mst_layer* L, const void* dY, const void* X, float* dW, int T,
                               mst_dtype act, const Workspace& ws, hipStream_t s, bool full) {
     int nparts = 1;
-    int rc = gemm_mfma(GEMM_TN, dY, act, X, act, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s, full, &nparts);
+    int rc = gemm_mfma(GEMM_TN, dY, act, X, act, nullptr, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s, full, &nparts);
     if (rc != MST_OK) return rc;
     if (L->nnz > 0) {
         k_gather_flat<<<(unsigned)cdiv(L->nnz, 1024), 256, 0, s>>>(nparts > 1 ? ws.gemm : ws.G, L->N, nparts, L->flat,
@@ -268,7 +296,7 @@ int mst_dense_grad(const void* dY_dev, const void* X_dev, float* G_dev, int T, i
                    void* ws_dev, size_t ws_bytes, mst_stream_t stream) {
     if (!dY_dev || !X_dev || !G_dev || T < 1 || O < 1 || I < 1 || !act_ok(act)) return MST_ERR_ARG;
     if (!aligned16(dY_dev) || !aligned16(X_dev) || !aligned16(G_dev) || (ws_dev && !aligned16(ws_dev))) return MST_ERR_ARG;
-    return gemm_mfma(GEMM_TN, dY_dev, act, X_dev, act, G_dev, O, I, T, (float*)ws_dev,
+    return gemm_mfma(GEMM_TN, dY_dev, act, X_dev, act, nullptr, G_dev, O, I, T, (float*)ws_dev,
                      ws_dev ? (int64_t)(ws_bytes / 4) : 0, (hipStream_t)stream);
 }
 
@@ -361,7 +389,7 @@ int mst_mask_update(mst_layer_t* L, const void* dY_dev, const void* X_dev, int T
     hipStream_t s = (hipStream_t)stream;
     note_call(L, act, T);
     if (needs_gradient(L, st)) {
-        rc = gemm_mfma(GEMM_TN, dY_dev, act, X_dev, act, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s);
+        rc = gemm_mfma(GEMM_TN, dY_dev, act, X_dev, act, nullptr, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s);
         if (rc != MST_OK) return rc;
     }
     return update_common(L, ws.G, rng_seed, ws, stats_out, s, st);
@@ -385,7 +413,7 @@ int mst_sparse_fc_bwd_weight_update(mst_layer_t* L, const void* dY_dev, const vo
     if (needs_gradient(L, st)) {
         // one dense gradient serves both: the weight gradient is read from it at the positions
         // that are active now, then the update scores growth with it
-        rc = gemm_mfma(GEMM_TN, dY_dev, act, X_dev, act, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s);
+        rc = gemm_mfma(GEMM_TN, dY_dev, act, X_dev, act, nullptr, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s);
         if (rc != MST_OK) return rc;
         if (L->nnz > 0) {
             k_gather_flat<<<(unsigned)cdiv(L->nnz, 1024), 256, 0, s>>>(ws.G, L->N, 1, L->flat, L->nnz, dW_dev);

@@ -96,6 +96,12 @@ struct mst_layer {
     float* Wd = nullptr;       // [N] dense W . M, maintained only while the dense path is in use
     bool Wd_valid = false;     // Wd equals W . M
     bool Wd_zeros = false;     // Wd is zero at every inactive position (survives a change of the values)
+    // The two bfloat16 parts of Wd in the order that the products of bfloat16 activations want (gemm_planes.hip), for Y and for
+    // dX; null where no such product has whole tiles.  Made by the first product that reads them, kept up with Wd from then on:
+    // sync_values and the updates that leave Wd valid make them again.
+    uint16_t *planes_y = nullptr, *planes_x = nullptr;
+    bool planes_used = false;  // some product has read them
+    bool planes_valid = false; // they hold the parts of Wd
     // The index views are built lazily: an update of a layer that the dense contractions serve
     // (path choice at the batch size and type of the last product call) leaves them unbuilt; a
     // call that needs them and has a workspace builds them, one without runs the dense product.
@@ -250,9 +256,13 @@ int bwd_fused(const mst_layer* L, const void* dY, const void* X, float* dX, floa
 int bwd_fused_force_shape(int waves, int quads);
 // C[M x N] (fp32) = op(A) op(B) on the matrix cores; see gemm_mfma.hip.  full: fp32 operands in full whatever the shape
 enum GemmKind { GEMM_TN = 0, GEMM_NT = 1, GEMM_NN = 2 };
-int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_dtype b_dt, float* C,
+int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_dtype b_dt, const uint16_t* planes, float* C,
               int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, bool full = false,
               int* left_unsummed = nullptr);
+bool gemm_wants_planes(mst_dtype a_dt, int M, int N, int Kdim, bool full);
+// Y and dX of bfloat16 activations from the split weights' planes; see gemm_planes.hip
+int gemm_planes(const uint16_t* A, const uint16_t* P, float* C, int M, int N, int Kdim, hipStream_t s);
+int make_planes(const mst_layer* L, hipStream_t s);
 // the same at full fp32 precision for any shape (B fp32); see gemm_exact.hip
 int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,
                float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed);

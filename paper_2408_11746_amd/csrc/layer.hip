@@ -128,9 +128,12 @@ constexpr int CSEG = 2048;         // positions per wavefront of build_canonical
 
 struct LayerCarve {
     size_t mask, vals, flat, rowptr, Wd;
-    size_t rptr, rent, rperm, rmap, rpos, cptr, cent, cperm, cmap, cpos, cost, heavy, Hd;
+    size_t rptr, rent, rperm, rmap, rpos, cptr, cent, cperm, cmap, cpos, cost, heavy, Hd, py, px;
     size_t total;
 };
+
+// the tile of gemm_planes.hip divides the outputs of one product, its k step the contraction range
+static bool has_planes(int O, int I) { return O % 32 == 0 && I % 32 == 0 && (O % 256 == 0 || I % 256 == 0); }
 
 static LayerCarve carve_layer(int O, int I, int64_t cap) {
     LayerCarve c{};
@@ -156,6 +159,8 @@ static LayerCarve carve_layer(int O, int I, int64_t cap) {
     c.cost = take(16 + 4);
     c.heavy = take((size_t)(HEAVY_MAX + 2) * 4);
     c.Hd = take((size_t)HEAVY_MAX * I * 4);
+    c.py = take(has_planes(O, I) ? (size_t)N * 4 : 0);
+    c.px = take(has_planes(O, I) ? (size_t)N * 4 : 0);
     c.total = off;
     return c;
 }
@@ -890,7 +895,7 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
         mst_layer* L = items[x].L;
         L->views_valid = true;
         L->row_stale = L->col_stale = false;
-        if (!items[x].keep_dense_copy) L->Wd_valid = L->Wd_zeros = false;
+        if (!items[x].keep_dense_copy) L->Wd_valid = L->Wd_zeros = L->planes_valid = false;
     }
     return MST_OK;
 }
@@ -926,7 +931,8 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
         MST_LAUNCH_CHECK();
     }
     L->Wd_valid = L->Wd_zeros = true;
-    return MST_OK;
+    L->planes_valid = L->planes_used;                // (recorded products read them without asking)
+    return L->planes_used ? make_planes(L, s) : MST_OK;
 }
 
 // new values into the entries of the row view (and the dense rows beside it) and / or of the col view, and into
@@ -1034,6 +1040,10 @@ int mst_layer_create(mst_layer_t** out, int O, int I, int64_t nnz_capacity, void
     L->dense_live = (int*)(b + c.cost + 16);
     L->heavy = (int*)(b + c.heavy);
     L->Hd = (float*)(b + c.Hd);
+    if (has_planes(O, I)) {
+        L->planes_y = (uint16_t*)(b + c.py);
+        L->planes_x = (uint16_t*)(b + c.px);
+    }
     auto init_view = [&](View& v, int R, int K, size_t optr, size_t oent, size_t operm, size_t omap, size_t opos) {
         v = view_shape(R, K, nnz_capacity);
         v.ptr = (int*)(b + optr); v.ent = (uint4*)(b + oent); v.perm = (int*)(b + operm);
@@ -1126,21 +1136,27 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     // than at the next product, so that products recorded into a graph never see stale weights.
     const bool dense = L->Wd_zeros && L->nnz > 0, views = L->nnz > 0 && L->views_valid;   // unbuilt views take the values when they are built
     L->Wd_valid = dense;
-    bool row = views, col = views;
-    if (dense && views && !(L->row_walked && L->col_walked)) {
+    bool row = views, col = views, planes = dense && L->planes_valid;
+    L->planes_valid = planes;
+    if (dense && (L->planes_y || (views && !(L->row_walked && L->col_walked)))) {
         // Views that nothing has walked are left out, since the dense copy holds the values for their first walk.
-        // A recording refreshes every built view and changes no flag: its replays come at any time, between calls
-        // that walk a view for the first time, and it has not run yet.
+        // A recording refreshes every built view, and the planes whether they are in use or not, and changes no flag: its
+        // replays come at any time, between calls that walk a view or read the planes for the first time, and it has not run yet.
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         MST_HIP(hipStreamIsCapturing(s, &capture));
-        if (capture == hipStreamCaptureStatusNone) {
+        if (capture != hipStreamCaptureStatusNone) {
+            planes = L->planes_y != nullptr;
+        } else if (views) {
             row = L->row_walked;
             col = L->col_walked;
             L->row_stale |= !row;
             L->col_stale |= !col;
         }
     }
-    return refresh_views(L, row, col, dense, false, s);
+    const int rc = refresh_views(L, row, col, dense, false, s);
+    // (made again from the dense copy: 8.5 us at 1024 x 4096.  Scattering 5 % of the positions into them took 11, 10 % of 1280 x
+    // 5120 took 30: four stores of two bytes per value, two of them far apart.)
+    return rc == MST_OK && planes ? make_planes(L, s) : rc;
 }
 
 int mst_layer_indices(const mst_layer_t* L, int32_t* flat_dev, mst_stream_t stream) {

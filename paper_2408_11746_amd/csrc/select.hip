@@ -733,8 +733,14 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
         items[x].L->choice.store(0, std::memory_order_relaxed);
     }
     if (n_views > 0 && (rc = build_views(views, n_views, s)) != MST_OK) return rc;
-    for (int x = 0; x < n_canonical; ++x) canonical[x].L->Wd_valid = canonical[x].L->Wd_zeros = true;
-    return n_canonical > 0 ? build_canonical(canonical, n_canonical, s) : MST_OK;
+    if (n_canonical == 0) return MST_OK;
+    for (int x = 0; x < n_canonical; ++x) {
+        mst_layer* L = canonical[x].L;
+        L->Wd_valid = L->Wd_zeros = true;
+        L->planes_valid = L->planes_used;
+        if (L->planes_used && (rc = make_planes(L, s)) != MST_OK) return rc;
+    }
+    return build_canonical(canonical, n_canonical, s);
 }
 
 }  // namespace mst

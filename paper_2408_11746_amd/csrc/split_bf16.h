@@ -58,4 +58,16 @@ __device__ __forceinline__ float fp32_sum(const TA* __restrict__ A, int64_t lda,
     return sum;
 }
 
+
+// Tile number -> tile coordinates for the 256-row kernels.  Tiles are numbered in bands of four tile
+// rows, column by column inside a band: the 32 tiles an XCD works on at a time then span about
+// 4 rows x 8 columns instead of 2 x 20, so its L2 is filled with 12 operand panels instead of 22.
+constexpr int TILE_BAND = 4;
+__device__ inline void tile_coords(int tile_id, int gm, int gn, int& mi, int& ni) {
+    const int band = tile_id / (TILE_BAND * gn), rem = tile_id - band * TILE_BAND * gn;
+    const int hgt = min(TILE_BAND, gm - band * TILE_BAND);
+    ni = rem / hgt;
+    mi = band * TILE_BAND + rem - ni * hgt;
+}
+
 }  // namespace mst
