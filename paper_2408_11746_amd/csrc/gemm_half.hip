@@ -182,14 +182,22 @@ __device__ __forceinline__ void form_again(const float* __restrict__ A, int64_t 
                                            int m, int n, int kbeg, int kend) {
     if (!(__builtin_fabsf(*c) < __builtin_inff())) *c = fp32_sum<float, AK, float, BKM>(A, lda, B, ldb, m, n, kbeg, kend);
 }
-__device__ __forceinline__ void store4(float* c, int n, int N, floatx4 o) {
-    if ((N & 3) == 0) {                               // (n is a multiple of four)
-        if (n < N) *reinterpret_cast<floatx4*>(c) = o;
-    } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (n + v < N) c[v] = o[v];
+// Where N is no multiple of four a wavefront's outputs leave by way of LDS, 32 rows x COLS at a time, so that a store writes a run
+// of 256 bytes: element by element every lane of an accumulator would write to a row of its own.  2379 x 2025, k = 512,
+// 128 x 128 tiles: 49 -> 39 us (2379 x 2024, four outputs per lane and store: 35, and no less through LDS).
+// Unit u (four columns) of row r is kept at u ^ (r & 15); only this wavefront uses the area.
+template <int COLS>
+__device__ __forceinline__ uint32_t out_unit(int r, int u) { return (uint32_t)(r * (COLS * 4) + ((u ^ (r & 15)) << 4)); }
+__device__ __forceinline__ void wave_lds_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+template <int COLS>
+__device__ __forceinline__ void store_rows(const char* area, float* __restrict__ C, int m0, int n0, int M, int N, int lane) {
+    wave_lds_done();
+#pragma unroll 8
+    for (int x = 0; x < 32 * COLS / 64; ++x) {
+        const int r = x / (COLS / 64), c = x % (COLS / 64) * 64 + lane;
+        if (m0 + r < M && n0 + c < N) C[(int64_t)(m0 + r) * N + n0 + c] = *reinterpret_cast<const float*>(area + out_unit<COLS>(r, c >> 2) + 4 * (c & 3));
     }
+    wave_lds_done();
 }
 
 // Workgroup -> (tile, k range): XCD x takes a contiguous share of the tiles, one k range after the other; tiles in bands of
@@ -403,6 +411,9 @@ void k_gemm_half256(const float* __restrict__ A, int64_t lda, const float* __res
     }
     // D layout of the 16x16 MFMA: lane l, register v -> row 4*(l/16) + v (B's), column l%16 (A's)
     bool bad = false;
+    const bool rows_aligned = (N & 3) == 0;
+    char* const area = gh_lds + 16384 * (own >> 6);
+    __syncthreads();                                  // (everyone is done with the operands there)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int m = m0 + wm + 16 * i + lr, ea = expo[wm + 16 * i + lr];
@@ -415,10 +426,13 @@ void k_gemm_half256(const float* __restrict__ A, int64_t lda, const float* __res
                 bad |= !(__builtin_fabsf(acc[i][j][v]) < __builtin_inff());
                 o[v] = ldexpf(acc[i][j][v], -ea - expo[256 + wn + 16 * j + 4 * lu + v]);
             }
-            if (m < M) store4(Cz + (int64_t)m * N + n, n, N, o);
+            if (!rows_aligned) *reinterpret_cast<floatx4*>(area + out_unit<128>(16 * (i & 1) + lr, 4 * j + lu)) = o;
+            else if (m < M && n < N) *reinterpret_cast<floatx4*>(Cz + (int64_t)m * N + n) = o;
         }
+        if ((i & 1) && !rows_aligned) store_rows<128>(area, Cz, m0 + wm + 16 * (i - 1), n0 + wn, M, N, own & 63);
     }
     if (bad) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (other lanes have stored this lane's outputs)
 #pragma unroll 1
         for (int x = 0; x < 128; ++x) {
             const int m = m0 + wm + 16 * (x >> 5) + lr, n = n0 + wn + 16 * ((x >> 2) & 7) + 4 * lu + (x & 3);
@@ -590,6 +604,9 @@ void k_gemm_half128(const float* __restrict__ A, int64_t lda, const float* __res
     }
     // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4 (B's), column l%32 (A's)
     bool bad = false;
+    const bool rows_aligned = (N & 3) == 0;
+    char* const area = gh_lds + 8192 * (own >> 6);
+    __syncthreads();                                  // (everyone is done with the operands there)
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int m = m0 + wm + 32 * i + lr, ea = expo[wm + 32 * i + lr];
@@ -605,10 +622,13 @@ void k_gemm_half128(const float* __restrict__ A, int64_t lda, const float* __res
                     bad |= !(__builtin_fabsf(c) < __builtin_inff());
                     o[v] = ldexpf(c, -ea - expo[128 + nl + v]);
                 }
-                if (m < M) store4(Cz + (int64_t)m * N + n0 + nl, n0 + nl, N, o);
+                if (!rows_aligned) *reinterpret_cast<floatx4*>(area + out_unit<64>(lr, 8 * j + 2 * q + lu)) = o;
+                else if (m < M && n0 + nl < N) *reinterpret_cast<floatx4*>(Cz + (int64_t)m * N + n0 + nl) = o;
             }
+        if (!rows_aligned) store_rows<64>(area, Cz, m0 + wm + 32 * i, n0 + wn, M, N, own & 63);
     }
     if (bad) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (other lanes have stored this lane's outputs)
 #pragma unroll 1
         for (int x = 0; x < 64; ++x) {
             const int m = m0 + wm + 32 * (x >> 5) + lr, n = n0 + wn + 32 * ((x >> 4) & 1) + 8 * ((x >> 2) & 3) + 4 * lu + (x & 3);
