@@ -260,6 +260,8 @@ int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_d
               int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, bool full = false,
               int* left_unsummed = nullptr);
 bool gemm_wants_planes(mst_dtype a_dt, int M, int N, int Kdim, bool full);
+// G of bfloat16 activations, M and N multiples of 8; see gemm_wgrad.hip
+int gemm_wgrad16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int Kdim, int k_per_split, int64_t split_stride, hipStream_t s);
 // Y and dX of bfloat16 activations from the split weights' planes; see gemm_planes.hip
 int gemm_planes(const uint16_t* A, const uint16_t* P, float* C, int M, int N, int Kdim, hipStream_t s);
 int make_planes(const mst_layer* L, hipStream_t s);

@@ -29,34 +29,27 @@ constexpr int BKH = 64;            // k per LDS tile
 
 
 // A patch of 8 k x 8 m on its way from a k-major bfloat16 operand into LDS: eight 16-byte loads, an 8 x 8
-// halfword transpose (v_perm_b32), eight LDS units of eight k.  RAGGED: buffer loads from the tile's corner
+// halfword transpose (v_perm_b32), eight LDS units of eight k.  Buffer loads from the tile's corner
 // with an exact end (k rows from kend on read as zeros; what follows the end of a row is the next row and
 // lands in outputs that are not stored).  Dword alignment is all they need; where rows have an odd length
 // every other one -- the odd k of a patch, tiles start at even k -- begins in the middle of a dword, and a
 // fifth dword goes with it.  (Element by element such a layer took 780 us where an aligned one takes 170.)
 typedef uint32_t tn_u32x4 __attribute__((ext_vector_type(4)));
-template <bool RAGGED>
 struct TnPatch {
     tn_u32x4 r[8];
-    uint32_t e[RAGGED ? 4 : 1];
+    uint32_t e[4];
 
     // kcount: k rows of the tile; p's patch: rows 8 mq .., k 8 kg ..
     __device__ __forceinline__ void fetch(const uint16_t* __restrict__ src, int64_t ld, int k0, int kcount, int m0, int kend, int mq, int kg) {
         const uint32_t pitch = 2u * (uint32_t)ld, o0 = (uint32_t)(8 * kg) * pitch + (uint32_t)(16 * mq);
-        if constexpr (RAGGED) {
-            const int64_t left = (int64_t)min(kend - k0, kcount) * ld - m0;
-            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src + (int64_t)k0 * ld + m0), 0,
-                                                                                (int)((2 * left + 3) & ~3ll), 0x00020000);
+        const int64_t left = (int64_t)min(kend - k0, kcount) * ld - m0;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(src + (int64_t)k0 * ld + m0), 0,
+                                                                            (int)((2 * left + 3) & ~3ll), 0x00020000);
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk) {
-                const uint32_t o = o0 + kk * pitch;
-                r[kk] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(o & ~3u), 0, 0);
-                if (kk & 1) e[kk >> 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(o & ~3u) + 16, 0, 0);
-            }
-        } else {
-            const char* const row = reinterpret_cast<const char*>(src + (int64_t)k0 * ld + m0);
-#pragma unroll
-            for (int kk = 0; kk < 8; ++kk) r[kk] = *reinterpret_cast<const tn_u32x4*>(row + (int64_t)kk * pitch + o0);
+        for (int kk = 0; kk < 8; ++kk) {
+            const uint32_t o = o0 + kk * pitch;
+            r[kk] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(o & ~3u), 0, 0);
+            if (kk & 1) e[kk >> 1] = __builtin_amdgcn_raw_buffer_load_b32(rs, (int)(o & ~3u) + 16, 0, 0);
         }
     }
     // the LDS unit of row j of the patch; valid: k of the patch that exist (the dword that holds the last
@@ -67,11 +60,8 @@ struct TnPatch {
         tn_u32x4 o;
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
-            uint32_t odd = r[2 * d + 1][w];
-            if constexpr (RAGGED) {
-                odd = __builtin_amdgcn_alignbit(w < 3 ? r[2 * d + 1][w < 3 ? w + 1 : 0] : e[d], odd, sh);
-                if (j == 0) odd = 2 * d + 1 < valid ? odd : 0u;
-            }
+            uint32_t odd = __builtin_amdgcn_alignbit(w < 3 ? r[2 * d + 1][w < 3 ? w + 1 : 0] : e[d], r[2 * d + 1][w], sh);
+            if (j == 0) odd = 2 * d + 1 < valid ? odd : 0u;
             o[d] = __builtin_amdgcn_perm(odd, r[2 * d][w], sel);
         }
         return o;
@@ -106,7 +96,7 @@ __global__ __launch_bounds__(256) void k_gemm_tn_bf16(const uint16_t* __restrict
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-    TnPatch<true> patch;
+    TnPatch patch;
     const int mq = p & 15, kg = p >> 4;
     patch.fetch(src, ld, kbeg, BKH, o0, kend, mq, kg);
     const int lk = lane >> 5, lm = lane & 31;
@@ -772,15 +762,12 @@ void k_gemm_split_n160(const float* __restrict__ A, int64_t lda, const float* __
         }
 }
 
-// G = A^T B with BOTH operands bfloat16 and k-major (A [K x M], B [K x N]): the same 256 x 256
+// The same product for rows that are not whole 16-byte units (gemm_wgrad.hip takes the others): the 256 x 256
 // workgroup tile, eight wavefronts of 64 x 128 and two LDS stages as k_gemm_split256, k steps of
 // 64: the two planes of an operand hold its k halves (0..31, 32..63) instead of hi and lo, one
 // MFMA product per term.  A thread stages a patch of 8 k x 8 rows: eight 16-byte loads, an
 // 8 x 8 halfword transpose in registers (v_perm_b32), eight 16-byte LDS units (one per row).
 // Staging of the next tile is spread over the second half of a step's MFMAs, as there.
-// (Four wavefronts of 128 x 128 with the accumulators in the accumulation half of the
-// register file measured 15 % slower: one wavefront per SIMD leaves every wait exposed.)
-template <bool RAGGED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_tn_bf16_256(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ B, int64_t ldb,
                         float* __restrict__ C, int M, int N, int Kdim, int k_per_split, int64_t split_stride) {
@@ -814,7 +801,7 @@ void k_gemm_tn_bf16_256(const uint16_t* __restrict__ A, int64_t lda, const uint1
     const int64_t ld = h == 0 ? lda : ldb;
     const uint16_t* const src = h == 0 ? A : B;
     const int o0 = h == 0 ? m0 : n0;
-    TnPatch<RAGGED> patch;
+    TnPatch patch;
     auto fetch = [&](int k0) __attribute__((always_inline)) { patch.fetch(src, ld, k0, KS, o0, kend, mq, kg); };
     const uint32_t wr_plane = (uint32_t)((2 * h + (kg >> 2)) * PLANE);
     uint32_t wr_unit[8];                              // row 8 mq + j, unit kg & 3
@@ -879,7 +866,7 @@ void k_gemm_tn_bf16_256(const uint16_t* __restrict__ A, int64_t lda, const uint1
             for (int v = 0; v < 16; ++v) {
                 const int m = m0 + wm + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
                 const int n = n0 + wn + j * 32 + lm;
-                if (!RAGGED || (m < M && n < N)) Cz[(int64_t)m * N + n] = acc[i][j][v];
+                if (m < M && n < N) Cz[(int64_t)m * N + n] = acc[i][j][v];
             }
 }
 
@@ -939,7 +926,8 @@ double xcd_rounds(int64_t n, int places, int lone_places, double full, double lo
     return (double)(n / places) * full + last;
 }
 
-// The bfloat16 dense gradient: the two-stage 256 x 256 kernel, the 128 x 128 one or the streaming one of
+// The bfloat16 dense gradient: a 256 x 256 kernel (gemm_wgrad.hip; k_gemm_tn_bf16_256 where rows are not whole 16-byte units,
+// which costs it a quarter of the rate), the 128 x 128 one or the streaming one of
 // gemm_exact.hip (64), with the number of k ranges.  Microseconds of a 64-k step (streaming: of a k), of start-up
 // and output in steps (streaming: microseconds) and of the launch fitted to timings of 100 products on MI355X
 // (5-8 % rms error).
@@ -956,6 +944,7 @@ static SplitPlan plan_tn_bf16(int M, int N, int Kdim, int64_t max_split, bool su
             double us;
             if (tile == 64) us = 2.6 + xcd_rounds(Q * ns, 32, 0, 0.0059, 0.0054) * 64.0 * steps + (double)cdiv(Q * ns, 32) * 3.2;
             else if (tile == 128) us = xcd_rounds(Q * ns, 96, 32, 2.51, 1.36) * (steps + 4.0);
+            else if (M % 8 == 0 && N % 8 == 0) us = 2.7 + xcd_rounds(Q * ns, 32, 8, 1.44, 1.10) * (steps + 8.0);
             else us = 0.9 + xcd_rounds(Q * ns, 32, 31, 1.78, 1.44) * (steps + 5.1);
             if (ns > 1) us += 2.2 + 1.2e-6 * (double)M * (double)N * (summed ? ns + 1.0 : 0.25 * ns);
             if (best.tile == 0 || us < best.us) best = SplitPlan{tile, ns, us};
@@ -1127,10 +1116,12 @@ static int launch_tn_bf16(const void* Av, const void* Bv, float* C, int M, int N
         if (rc != MST_OK) return rc;
     } else if (plan.tile == 128) {
         k_gemm_tn_bf16<<<dim3(nsplit, (unsigned)cdiv(N, BN), (unsigned)cdiv(M, BM)), 256, 0, s>>>(A, M, B, N, dst, M, N, Kdim, kps, mn);
+    } else if (M % 8 == 0 && N % 8 == 0) {
+        const int rc = gemm_wgrad16(A, B, dst, M, N, Kdim, kps, mn, s);
+        if (rc != MST_OK) return rc;
     } else {
         const unsigned grid = (unsigned)(8 * cdiv(cdiv(M, BM2) * cdiv(N, BN2), 8) * nsplit);
-        if (M % BM2 == 0 && N % BN2 == 0 && Kdim % 64 == 0) k_gemm_tn_bf16_256<false><<<grid, 512, 0, s>>>(A, M, B, N, dst, M, N, Kdim, kps, mn);
-        else k_gemm_tn_bf16_256<true><<<grid, 512, 0, s>>>(A, M, B, N, dst, M, N, Kdim, kps, mn);
+        k_gemm_tn_bf16_256<<<grid, 512, 0, s>>>(A, M, B, N, dst, M, N, Kdim, kps, mn);
     }
     MST_LAUNCH_CHECK();
     if (left_unsummed) {

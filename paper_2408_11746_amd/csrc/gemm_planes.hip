@@ -17,7 +17,6 @@
 
 namespace mst {
 
-typedef float floatx4 __attribute__((ext_vector_type(4)));
 constexpr int PK = 32;                                // k of a step; an LDS row is 64 bytes
 constexpr int P_PLANE = 256 * 64, P_STAGE = 3 * P_PLANE;
 constexpr unsigned P_LDS = 3 * P_STAGE;               // three stages of [A, B hi, B lo]
@@ -27,18 +26,6 @@ __device__ __forceinline__ uint32_t plane_unit(int m, int u) {
     const int rho = (m & ~15) | ((m & 3) << 2) | ((m >> 2) & 3);
     return (uint32_t)(rho * 64 + (((u ^ (rho >> 2) ^ (rho >> 4)) & 3) << 4));
 }
-// 16 bytes per lane from base + voff to LDS, lane l to lds + 16 l; base and lds uniform.  The load has no register to
-// return to; whoever reads the LDS waits for it (vmcnt) and for the other wavefronts (barrier) first.
-__device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
-}
-template <int LATER>
-__device__ __forceinline__ void wait_loads() {        // until all but the LATER youngest loads of this wavefront have arrived
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LATER) : "memory");
-}
-// this wavefront's LDS accesses are done, and everyone's
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // Eight wavefronts (2 x 4) of 128 x 64; the loads of a step are issued two steps ahead, one barrier per step.
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_planes(const uint16_t* __restrict__ A, const uint16_t* __restrict__ P, float* __restrict__ C, int M, int N, int Kdim) {

@@ -8,6 +8,7 @@
 
 namespace mst {
 
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
@@ -58,6 +59,18 @@ __device__ __forceinline__ float fp32_sum(const TA* __restrict__ A, int64_t lda,
     return sum;
 }
 
+// ---- loads that go straight to LDS
+// 16 bytes per lane from base + voff to LDS, lane l to lds + 16 l; base and lds uniform.  The load has no register to
+// return to; whoever reads the LDS waits for it (vmcnt) and for the other wavefronts (barrier) first.
+__device__ __forceinline__ void load_to_lds(const void* base, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+}
+template <int LATER>
+__device__ __forceinline__ void wait_loads() {        // until all but the LATER youngest loads of this wavefront have arrived
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LATER) : "memory");
+}
+// this wavefront's LDS accesses are done, and everyone's
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // Tile number -> tile coordinates for the 256-row kernels.  Tiles are numbered in bands of four tile
 // rows, column by column inside a band: the 32 tiles an XCD works on at a time then span about
