@@ -146,8 +146,9 @@ int mst_layer_set_path(mst_layer_t* layer, mst_path path);
 /* Which path a product call with these arguments takes on the layer as it stands: 1 = masked
  * dense MFMA contraction, 0 = sparse kernel; weight_gradient = 0 asks for Y (Eq. (1)), 3 for its
  * input gradient dX (the same answer but for layers or batches that are no whole tiles and short
- * batches), 1 for the gradient of the active weights, 2 for mst_sparse_fc_bwd (both gradients from
- * the shared walk, or both from dense contractions).  Host only, no device work;
+ * batches), 1 for the gradient of the active weights, 2 for mst_sparse_fc_bwd (0: both gradients from
+ * the shared walk; 1: the weight gradient from a dense contraction, and dX from another or, with bfloat16 activations on
+ * layers or batches that are no whole tiles, from the walk where that is faster).  Host only, no device work;
  * MST_ERR_ARG on a null layer, an unknown type or T < 1. */
 int mst_layer_uses_dense(const mst_layer_t* layer, mst_dtype act, int T, int weight_gradient);
 

@@ -236,10 +236,16 @@ int mst_sparse_fc_bwd(const mst_layer_t* L, const void* dY_dev, const void* X_de
         if (rcv != MST_OK) return rcv;
         return bwd_fused(L, dY_dev, X_dev, dX_dev, dW_dev, T, act, ws, s);
     }
-    // the two dense contractions (the split area of the workspace serves dX first, then the weight
+    // the dense weight gradient (the split area of the workspace serves a dense dX first, then the weight
     // gradient: same stream)
     const bool full = full_precision(L, WALK_BWD, act, T);
-    const int rc = dense_products_bwd_input(L, dY_dev, dX_dev, T, act, s, full, ws.gemm, (int64_t)ws.gemm_floats);
+    int rc;
+    if (use_sparse_input_grad(L, act, T)) {
+        rc = ensure_views(L, ws, s);
+        if (rc == MST_OK) rc = spmm(L, L->col, dY_dev, dX_dev, T, act, s);
+    } else {
+        rc = dense_products_bwd_input(L, dY_dev, dX_dev, T, act, s, full, ws.gemm, (int64_t)ws.gemm_floats);
+    }
     if (rc != MST_OK) return rc;
     return dense_products_bwd_weight(L, dY_dev, X_dev, dW_dev, T, act, ws, s, full);
 }

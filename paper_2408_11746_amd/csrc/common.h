@@ -167,6 +167,7 @@ enum WalkJob { WALK_FWD = 0, WALK_BWD_INPUT, WALK_BWD_WEIGHT, WALK_BWD };
 bool use_dense_path(const mst_layer* L, WalkJob job, mst_dtype act, int T);
 bool use_dense_weight_grad(const mst_layer* L, mst_dtype act, int T);
 bool use_fused_backward(const mst_layer* L, mst_dtype act, int T);
+bool use_sparse_input_grad(const mst_layer* L, mst_dtype act, int T);
 // ... and the dense kernels take fp32 operands in full there
 bool full_precision(const mst_layer* L, WalkJob job, mst_dtype act, int T);
 

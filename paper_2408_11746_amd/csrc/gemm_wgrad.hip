@@ -11,8 +11,8 @@
 //   - Every step loads and waits for the same number of pieces, which keeps the loop free of branches: past the end it reads the
 //     last step again, into a stage that nobody reads.  Their number is made even (two register sets); rows past the
 //     end are cleared in LDS.
-// us, K = 16384: 4096 x 1024 in 4 ranges 158 -> 126, K = 4099 49.8 -> 42.2; 5120 x 1280, K = 8192, in 2 ranges 133 -> 112.  What bounds it
-// now: 76 % of the matrix cores' clocks at 1.6 GHz, the clock they leave, and 9 us for the 256 KB that every workgroup
+// us, K = 16384: 4096 x 1024 in 4 ranges 158 -> 125, K = 4099 49.8 -> 41; 5120 x 1280, K = 8192, in 2 ranges 133 -> 111.  What bounds it
+// now: 76 % of the matrix cores' clocks at 1.6 GHz, the clock they leave, and 8 us for the 256 KB that every workgroup
 // stores at the end, all at the same time (9 TB/s).
 #include <type_traits>
 
@@ -159,17 +159,26 @@ void k_gemm_wgrad16(const uint16_t* __restrict__ A, const uint16_t* __restrict__
     for (int i = 0; i < 8; ++i)
 #pragma unroll
         for (int j = 0; j < 8; ++j) asm volatile("" : "+a"(acc[i][j]));
-    // D layout of the 16x16 MFMA: lane l, register v -> row 4*(l/16) + v (B's), column l%16 (A's)
-    const int lm = lane & 15, ln = 4 * g;
+    // D layout of the 16x16 MFMA: lane l, register v -> row 4*(l/16) + v (B's), column l%16 (A's).  Through LDS, 64 rows at a
+    // time in this wavefront's quarter, so that a store writes two runs of 512 bytes (sixteen of 64 bytes: 16200 clocks instead of
+    // 14500); unit u (four columns) of row r is kept at u ^ (r & 15).
+    __syncthreads();
+    char* const mine = lds + 32768 * wave;
+    const int lm = lane & 15, ou = lane & 31, n = n0 + wn + 4 * ou;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int m = m0 + wm + 16 * i + lm;
-        float* const c = Cz + (int64_t)m * N;
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int n = n0 + wn + 16 * j + ln;
-            if (m < M && n < N) *reinterpret_cast<floatx4*>(c + n) = acc[i][j];
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) *reinterpret_cast<floatx4*>(mine + (16 * i + lm) * 512 + (((4 * j + g) ^ lm) << 4)) = acc[4 * h + i][j];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll 8
+        for (int r = lane >> 5; r < 64; r += 2) {
+            const int m = m0 + wm + 64 * h + r;
+            const floatx4 o = *reinterpret_cast<const floatx4*>(mine + r * 512 + ((ou ^ (r & 15)) << 4));
+            if (m < M && n < N) *reinterpret_cast<floatx4*>(Cz + (int64_t)m * N + n) = o;
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
 }
 

@@ -73,15 +73,16 @@ bool full_precision(const mst_layer* L, WalkJob job, mst_dtype act, int T) {
 }
 
 // The models take a microsecond of host time, so the answers for the last (T, type) are kept with the layer
-// until its active set changes: bits 0-3 known, 4-7 the answers (bit = WalkJob), 8 the type, 9.. T.
+// until its active set changes: bits 0-4 known, 5-9 the answers (bit = WalkJob, or SPARSE_DX), 10 the type, 11.. T.
+constexpr int SPARSE_DX = 4;
 template <typename F>
-static bool remembered(const mst_layer* L, WalkJob job, mst_dtype act, int T, F&& decide) {
+static bool remembered(const mst_layer* L, int job, mst_dtype act, int T, F&& decide) {
     std::atomic<uint64_t>& word = const_cast<mst_layer*>(L)->choice;
-    const uint64_t key = (uint64_t)T << 9 | (uint64_t)(act == MST_BF16) << 8, w = word.load(std::memory_order_relaxed);
-    const bool mine = (w & ~(uint64_t)0xFF) == key;
-    if (mine && (w >> job & 1)) return w >> (4 + job) & 1;
+    const uint64_t key = (uint64_t)T << 11 | (uint64_t)(act == MST_BF16) << 10, w = word.load(std::memory_order_relaxed);
+    const bool mine = (w & ~(uint64_t)0x3FF) == key;
+    if (mine && (w >> job & 1)) return w >> (5 + job) & 1;
     const bool yes = decide();
-    word.store((mine ? w : key) | (uint64_t)1 << job | (uint64_t)yes << (4 + job), std::memory_order_relaxed);
+    word.store((mine ? w : key) | (uint64_t)1 << job | (uint64_t)yes << (5 + job), std::memory_order_relaxed);
     return yes;
 }
 
@@ -102,18 +103,30 @@ bool use_dense_path(const mst_layer* L, WalkJob job, mst_dtype act, int T) {
     return remembered(L, job, act, T, [&] { return walk_us(L, job, T) > dense_us(L, job, act, T); });
 }
 
-// The one-call backward: one walk for both gradients, or the two dense products (a sparse dX beside a
-// dense dW is never the fastest).
+// The one-call backward: one walk for both gradients, the two dense products, or, with bfloat16 activations on other than whole
+// tiles, a sparse dX beside the dense weight gradient, whose operands need no parts (gemm_wgrad.hip: one product per
+// term where dX takes three).  A step of 4099 tokens of 1024 -> 4096, density 0.04: 206 us by one walk, 197 by dX's walk and
+// the dense gradient; 7356 tokens of 4288 -> 3170, 0.048: 1056 -> 923.  The margins are what the models are unsure of: of
+// 70 layers it is then taken at ten, nine of them 0 to 14 % faster and one (5000 tokens of 4001 -> 333, 0.05) 4 % slower; a walk of dX that was
+// ahead of two dense products by less than 15 % by the models lost up to 10 %.
+// With fp32 activations a sparse dX beside a dense dW is never the fastest.
+static double dense_backward_us(const mst_layer* L, mst_dtype act, int T) {
+    const bool full = full_precision(L, WALK_BWD, act, T);
+    return gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, GEMM_WS_SPLITS * L->N / ((int64_t)T * L->I), true, full) + dense_wgrad_us(L, act, T, full);
+}
+bool use_sparse_input_grad(const mst_layer* L, mst_dtype act, int T) {
+    if (act != MST_BF16 || L->path != MST_PATH_AUTO || whole_tiles(L, act, T) || !full_precision(L, WALK_BWD, act, T)) return false;
+    return remembered(L, SPARSE_DX, act, T, [&] {
+        const double us = walk_us(L, WALK_BWD_INPUT, T) + dense_wgrad_us(L, act, T, true) + 1.0e-6 * (double)L->N;   // (G as the gather reads it)
+        return 1.03 * us < walk_us(L, WALK_BWD, T) && 1.15 * us < dense_backward_us(L, act, T);
+    });
+}
 bool use_fused_backward(const mst_layer* L, mst_dtype act, int T) {
     if (L->path == MST_PATH_DENSE) return false;
     if (L->path == MST_PATH_SPARSE) return true;
     if (whole_tiles(L, act, T)) return (double)L->nnz <= (act == MST_F32 ? 0.085 : 0.035) * (double)L->N;
-    if (mostly_dense(L)) return false;
-    return remembered(L, WALK_BWD, act, T, [&] {
-        const bool full = full_precision(L, WALK_BWD, act, T);
-        return walk_us(L, WALK_BWD, T) <= gemm_mfma_us(GEMM_NN, act, T, L->I, L->O, GEMM_WS_SPLITS * L->N / ((int64_t)T * L->I), true, full) +
-                                              dense_wgrad_us(L, act, T, full);
-    });
+    if (mostly_dense(L) || use_sparse_input_grad(L, act, T)) return false;
+    return remembered(L, WALK_BWD, act, T, [&] { return walk_us(L, WALK_BWD, T) <= dense_backward_us(L, act, T); });
 }
 
 bool use_dense_weight_grad(const mst_layer* L, mst_dtype act, int T) {

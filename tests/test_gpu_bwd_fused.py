@@ -138,3 +138,21 @@ def test_automatic_path_of_the_one_call_backward(density, act, walk):
         np.testing.assert_array_equal(dW, sW)
     else:
         assert rel_err(dX, sX) <= TOL and rel_err(dW, sW) <= TOL
+
+
+@pytest.mark.parametrize("T,I,O,density", [(4099, 1024, 4096, 0.04), (13120, 3840, 343, 0.037)])
+def test_sparse_input_gradient_beside_the_dense_weight_gradient(T, I, O, density):
+    """bfloat16 activations, no whole tiles: the one-call backward may take dX from the walk and dW from the dense
+    contraction, also where the views are not built yet; the same bits as the separate calls give."""
+    print("case", T, I, O, density, flush=True)
+    W, M = synth.make_layer(48, 3, I, O, density)
+    X, dY, xb, yb = synth.make_activations(48, 3, T, I, O, "bf16")
+    Xd, dYd, a = dev(xb.view(np.int16)), dev(yb.view(np.int16)), mst.MST_BF16
+    rig = Rig(W, M, T)
+    L = rig.layer
+    assert L.uses_dense(a, T, 2) and L.uses_dense(a, T, 1)
+    dX, dW = _run(rig, dYd, Xd, T, I, a)
+    assert not L.uses_dense(a, T, 3)
+    assert rel_err(dX, opr.fc_bwd_input(dY, W, M)) <= TOL and rel_err(dW, opr.fc_bwd_weight(dY, X, M)) <= TOL
+    np.testing.assert_array_equal(dX, rig.bwd_input(yb.view(np.int16), a))
+    np.testing.assert_array_equal(dW, rig.bwd_weight(yb.view(np.int16), xb.view(np.int16), a))
