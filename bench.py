@@ -430,8 +430,8 @@ def run_block(args, name, mst, synth, torch, lds_peak, with_cpu_baseline):
     dp, dw = dense_prod[dL.name], dense_wgrad[dL.name]
     spmm_k = "k_walk<OUT> (launch shape chosen per call) + k_heavy_fwd after the forward (heavy rows as a dense product; returns at once without any)"
     gemm_k = "k_gemm_split256 / k_gemm_split_n160 / k_gemm_split (fp32 operands as bf16 hi + lo)" if act == "f32" else \
-        "k_gemm_a16_256 (bfloat16 activations x fp32 weights as bf16 hi + lo, 2 products per term)"
-    wgrad_dense_k = ("k_gemm_tn_bf16" if act == "bf16" else "k_gemm_split256<TN> / k_gemm_split<TN>") + " + k_gather_flat"
+        "k_gemm_planes (bfloat16 activations x fp32 weights as bf16 hi + lo, 2 products per term)"
+    wgrad_dense_k = ("k_gemm_wgrad16" if act == "bf16" else "k_gemm_split256<TN> / k_gemm_split<TN>") + " + k_gather_flat"
     kernel = {"fwd": gemm_k if dp else spmm_k,
               "bwd_input": gemm_k if dense_dx[dL.name] else spmm_k,
               "bwd_weight": wgrad_dense_k if dw else "k_walk_dw + k_walk_reduce",
