@@ -516,9 +516,9 @@ static ExactPlan plan_exact(int M, int N, int Kdim, bool a16, int64_t max_split,
     };
     static const Kind kinds[2][5] = {{{256, 256, EXACT_HALF, 32, 31, 32, 2.67, 2.04, 14.1, 0.0},
                                       {128, 128, EXACT_HALF, 64, 32, 32, 1.91, 1.23, 8.0, 3.2},
-                                      {64, 64, EXACT_LDS, 96, 32, 64, 2.62, 1.69, 0.3, 2.7},
-                                      {32, 32, EXACT_STREAM, 32, 0, 128, 0.0054, 0.0044, 3.1, 2.5},
-                                      {96, 64, EXACT_STREAM, 32, 0, 128, 0.0131, 0.0099, 3.7, 2.0}},
+                                      {64, 64, EXACT_LDS, 96, 32, 64, 2.63, 1.47, 0.5, 3.3},
+                                      {32, 32, EXACT_STREAM, 32, 0, 128, 0.0052, 0.0046, 3.1, 2.9},
+                                      {96, 64, EXACT_STREAM, 32, 0, 128, 0.0131, 0.0108, 3.7, 2.8}},
                                      {{0, 0, EXACT_HALF, 0, 0, 0, 0, 0, 0, 0},
                                       {128, 128, EXACT_LDS, 64, 32, 32, 1.64, 1.08, 1.2, 4.0},
                                       {64, 64, EXACT_LDS, 96, 32, 64, 1.65, 0.97, 0.7, 3.6},
