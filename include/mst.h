@@ -244,14 +244,13 @@ int mst_bwd_force_shape(int wavefronts_per_workgroup, int quads_per_wavefront);
  * an fp32 product by less than 2^-16 per term.  (Room to split the contraction is part of the model, so for
  * products below 2e10 multiply-adds a call with a workspace may take another kernel than one without.)
  * Every other product runs on a kernel of full fp32
- * precision: three bfloat16 values per element, exact, and six products, or, for outputs of many tiles and sums of
- * 256 terms or more, two scaled fp16 values and three products; what they leave out is below
- * 2^-24 of a term and of either sign.  So do the products that MST_PATH_AUTO moves from the sparse
+ * precision (three bfloat16 values per element, exact; six products, what they leave out is below
+ * 2^-24 of a term and of either sign).  So do the products that MST_PATH_AUTO moves from the sparse
  * to the dense kernels at low densities: up to 0.15 (short batches) or 0.035 to 0.07 (from 2048 tokens
  * on) of whole fp32 tiles, 0.03 to 0.045 of whole bfloat16 tiles from 2048 tokens on, and 0.30 of
  * everything else no product has fewer than 24 bits of its fp32 operands.  This hook pins, for all
- * later calls of the process: 1 = the full-precision kernel (1064, 1128, 1256: with a 64 x 64, 128 x 128 or
- * 256 x 256 tile, the last for fp32 operands; 1032, 1096: the streaming form for small outputs, 32 x 32 or 64 x 64); 128, 256, 160 or 192 = the split kernel with the
+ * later calls of the process: 1 = the full-precision kernel (1064, 1128: with a 64 x 64 or a
+ * 128 x 128 tile; 1256: with the largest that there is, 128 x 128; 1032, 1096: the streaming form for small outputs, 32 x 32 or 64 x 64); 128, 256, 160 or 192 = the split kernel with the
  * workgroup tile 128 x 128, 256 x 256, 256 x 160 or 256 x 192 (where the shape is a multiple of
  * it; the last two serve Y and dX only); 0 returns to the automatic choice.  The split kernel's tiles add a
  * result's terms in the same order and give identical bits.  -52 / 52 switch off / on the

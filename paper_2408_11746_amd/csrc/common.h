@@ -270,9 +270,6 @@ int make_planes(const mst_layer* L, hipStream_t s);
 int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,
                float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed);
 int gemm_exact_tile(int tile);
-// two scaled fp16 parts per value, tile 256 or 128 (k_per_split a multiple of 32); see gemm_half.hip
-int gemm_half(GemmKind kind, int tile, const float* A, int64_t lda, const float* B, int64_t ldb, float* C, int M, int N, int Kdim,
-              int k_per_split, int64_t split_stride, hipStream_t s);
 int gemm_stream_tn_bf16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int Kdim, int k_per_split, int64_t split_stride,
                         hipStream_t s);
 double xcd_rounds(int64_t n, int places, int lone_places, double full, double lone);

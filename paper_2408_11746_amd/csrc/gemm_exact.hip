@@ -18,8 +18,7 @@
 // layer of any size): they used to run on v_mfma_f32_32x32x2f32 at 100 TFLOP/s.  Six
 // v_mfma_f32_32x32x16_bf16 take the place of eight of those at a sixteenth of the time each.
 //
-// k_gemm_exact: workgroup tile TM x TM, TM = 64 or, with a bfloat16 operand, 128 (fp32 operands on larger tiles:
-// gemm_half.hip); 256 threads = four wavefronts of (TM/2) x (TM/2); k steps of
+// k_gemm_exact: workgroup tile TM x TM, TM = 128 or 64, 256 threads = four wavefronts of (TM/2) x (TM/2); k steps of
 // 4096 / TM, so that a plane of an operand's tile is 8 KB and a workgroup's LDS 48 KB (32 KB with a
 // bfloat16 operand): two (three) workgroups share a CU and one's staging runs beside another's MFMAs.
 // Loads are buffer loads from the tile's corner with exact ends: rows past the matrix read as zeros
@@ -45,6 +44,36 @@ __device__ inline uint32_t ex_unit(int m, int u) {
     if (TM == 64) return bf_unit(m, u);
     const int rho = (m & ~15) | ((m & 3) << 2) | ((m >> 2) & 3);
     return (uint32_t)(rho * 64 + (((u ^ (rho >> 2) ^ (rho >> 4)) & 3) << 4));
+}
+
+// a pair of fp32 values as three words of two bfloat16 each.  The parts are rounded to nearest, so the lower
+// ones have either sign and half the size that truncation leaves: what the dropped products lose has no direction.
+// The third part is exact: 24 bits less 8 and a sign, twice.
+__device__ inline void cut_pair(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    hi = cvt_pk_bf16(x0, x1);
+    const float b0 = x0 - __uint_as_float(hi << 16), b1 = x1 - __uint_as_float(hi & 0xFFFF0000u);
+    mid = cvt_pk_bf16(b0, b1);
+    const float c0 = b0 - __uint_as_float(mid << 16), c1 = b1 - __uint_as_float(mid & 0xFFFF0000u);
+    lo = __builtin_amdgcn_perm(__float_as_uint(c1), __float_as_uint(c0), 0x07060302u);
+}
+
+// The lower parts of an infinite value are inf - inf = NaN (those of a finite one whose first part rounds to an
+// infinity the infinity of the other sign and NaN), so a sum with such an operand comes out as NaN where fp32
+// products give a number or an infinity.  An output that is NaN is therefore formed again by fp32
+// multiply-adds, up to the first term that makes it NaN by itself; no other output pays more than a compare.
+template <typename TA, bool A_KMAJOR, typename TB, bool B_KMAJOR>
+__device__ __forceinline__ float fp32_sum(const TA* __restrict__ A, int64_t lda, const TB* __restrict__ B, int64_t ldb, int m, int n,
+                                          int kbeg, int kend) {
+    auto value = [](auto x) {
+        if constexpr (sizeof(x) == 2) return __uint_as_float((uint32_t)x << 16);
+        else return x;
+    };
+    float sum = 0.f;
+#pragma unroll 1
+    for (int k = kbeg; k < kend && sum == sum; ++k)
+        sum = fmaf(value(A[A_KMAJOR ? (int64_t)k * lda + m : (int64_t)m * lda + k]),
+                   value(B[B_KMAJOR ? (int64_t)k * ldb + n : (int64_t)n * ldb + k]), sum);
+    return sum;
 }
 
 // One operand's registers between global memory and LDS.  A thread (p = 0 .. 255) stages two pieces per
@@ -490,54 +519,42 @@ void k_gemm_stream(const void* __restrict__ Av, int64_t lda, const void* __restr
 
 // Kernel, workgroup tile and number of k ranges together, as for the split kernels: modelled time = rounds
 // one XCD needs for its share of the tiles x time of a workgroup, plus a launch and the traffic of the
-// partial outputs.  Places of an XCD: 32 workgroups of 256 x 256, 64 of 128 x 128, 96 of 64 x 64, 32 of the streaming
+// partial outputs.  Places of an XCD: 64 workgroups of 128 x 128, 96 of 64 x 64, 32 of the streaming
 // kernel; with no more workgroups than CUs each has one to itself and is faster.  Microseconds fitted to timings
-// on MI355X of 90 products (fp32, normal operands, 1 to 120 GFLOP: 8-12 % rms error; the plan loses 1.6 % on average and 22 %
-// at the worst) and 130 (bfloat16, 8-14 %).
-enum ExactKernel { EXACT_HALF, EXACT_LDS, EXACT_STREAM };            // gemm_half.hip, k_gemm_exact, k_gemm_stream
+// of 130 products, 1 to 40 GFLOP, on MI355X (8-14 % rms error).
 struct ExactPlan {
     int tile;
-    ExactKernel kernel;
+    bool stream;
     int nsplit;
     double us;
 };
-// Shortest sum that fp16 parts serve: what a part leaves out averages out over k.  At k = 100 their error is 0.28 of
-// 2^-24 sum |x w| where three bfloat16 parts have 0.21, from 256 on it is the smaller of the two.
-constexpr int HALF_MIN_K = 256;
-static int g_exact_tile = 0;                          // test hook: 0 automatic, 64, 128 or 256, streaming: 32 or 96 (64 x 64)
+static int g_exact_tile = 0;                          // test hook: 0 automatic, 64 or 128, streaming: 32 or 96 (64 x 64)
 static ExactPlan plan_exact(int M, int N, int Kdim, bool a16, int64_t max_split, bool summed) {
     struct Kind {
         int hook, tile;
-        ExactKernel kernel;
+        bool stream;
         int places, lone_places, bk;
-        // a k step with all places taken, with a CU to itself; start-up and output of a workgroup in steps
+        // fp32, bfloat16 A: a k step with all places taken, with a CU to itself; start-up and output of a workgroup
         // (streaming: a k of all steps; microseconds); launch
-        double full, lone, start, launch;
+        double full[2], lone[2], start[2], launch[2];
     };
-    static const Kind kinds[2][5] = {{{256, 256, EXACT_HALF, 32, 31, 32, 2.67, 2.04, 14.1, 0.0},
-                                      {128, 128, EXACT_HALF, 64, 32, 32, 1.91, 1.23, 8.0, 3.2},
-                                      {64, 64, EXACT_LDS, 96, 32, 64, 2.63, 1.47, 0.5, 3.3},
-                                      {32, 32, EXACT_STREAM, 32, 0, 128, 0.0052, 0.0046, 3.1, 2.9},
-                                      {96, 64, EXACT_STREAM, 32, 0, 128, 0.0131, 0.0108, 3.7, 2.8}},
-                                     {{0, 0, EXACT_HALF, 0, 0, 0, 0, 0, 0, 0},
-                                      {128, 128, EXACT_LDS, 64, 32, 32, 1.64, 1.08, 1.2, 4.0},
-                                      {64, 64, EXACT_LDS, 96, 32, 64, 1.65, 0.97, 0.7, 3.6},
-                                      {32, 32, EXACT_STREAM, 32, 0, 128, 0.0046, 0.0040, 2.6, 3.1},
-                                      {96, 64, EXACT_STREAM, 32, 0, 128, 0.0117, 0.0106, 2.6, 3.1}}};
+    static const Kind kinds[] = {{128, 128, false, 64, 32, 32, {2.71, 1.64}, {1.78, 1.08}, {1.4, 1.2}, {2.6, 4.0}},
+                                 {64, 64, false, 96, 32, 64, {2.63, 1.65}, {1.47, 0.97}, {0.5, 0.7}, {3.3, 3.6}},
+                                 {32, 32, true, 32, 0, 128, {0.0052, 0.0046}, {0.0046, 0.0040}, {3.1, 2.6}, {2.9, 3.1}},
+                                 {96, 64, true, 32, 0, 128, {0.0131, 0.0117}, {0.0108, 0.0106}, {3.7, 2.6}, {2.8, 3.1}}};
     static const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-    ExactPlan best{0, EXACT_LDS, 1, 0.0};
-    for (const Kind& kd : kinds[a16]) {
-        if (kd.tile == 0 || (g_exact_tile && kd.hook != (a16 && g_exact_tile == 256 ? 128 : g_exact_tile))) continue;
+    ExactPlan best{0, false, 1, 0.0};
+    for (const Kind& kd : kinds) {
+        if (g_exact_tile && kd.hook != g_exact_tile) continue;
         const int64_t Q = cdiv(cdiv(M, kd.tile) * cdiv(N, kd.tile), 8);
+        const double full = kd.full[a16], lone = kd.lone[a16];
         for (int ns : cand) {
             if (ns > 1 && (ns > max_split || Kdim / ns < 256)) break;
-            // fp16 parts are less exact than bfloat16 ones in a short sum (gemm_half.hip)
-            if (kd.kernel == EXACT_HALF && Kdim / ns < HALF_MIN_K && !g_exact_tile) break;
-            const double work = xcd_rounds(Q * ns, kd.places, kd.lone_places, kd.full, kd.lone);
-            double cost = kd.launch + (kd.kernel == EXACT_STREAM ? work * (double)cdiv(Kdim, ns) + (double)cdiv(Q * ns, kd.places) * kd.start
-                                                                 : work * ((double)cdiv(cdiv(Kdim, ns), kd.bk) + kd.start));
+            const double work = xcd_rounds(Q * ns, kd.places, kd.lone_places, full, lone);
+            double cost = kd.launch[a16] + (kd.stream ? work * (double)cdiv(Kdim, ns) + (double)cdiv(Q * ns, kd.places) * kd.start[a16]
+                                                      : work * ((double)cdiv(cdiv(Kdim, ns), kd.bk) + kd.start[a16]));
             if (ns > 1) cost += 3.0 + 1.0e-6 * (double)M * (double)N * (summed ? ns + 1.0 : 0.25 * ns);
-            if (best.tile == 0 || cost < best.us) best = ExactPlan{kd.tile, kd.kernel, ns, cost};
+            if (best.tile == 0 || cost < best.us) best = ExactPlan{kd.tile, kd.stream, ns, cost};
         }
     }
     return best;
@@ -562,20 +579,17 @@ static int launch_exact(const void* A, int64_t lda, const float* B, int64_t ldb,
     const unsigned grid = (unsigned)(8 * cdiv(cdiv(M, plan.tile) * cdiv(N, plan.tile), 8) * nsplit);
     float* const dst = nsplit > 1 ? split_ws : C;
     constexpr unsigned lds = (ExOperand<A16, AK, 64>::PLANES + 3) * 8192;
-    if (plan.kernel == EXACT_STREAM && plan.tile == 32) {
+    if (plan.stream && plan.tile == 32) {
         k_gemm_stream<A16, AK, false, BKM, 1><<<grid, 1024, STREAM_LDS_32, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
-    } else if (plan.kernel == EXACT_STREAM) {
+    } else if (plan.stream) {
         static uint64_t done = 0;
         const int rc = allow_lds(reinterpret_cast<const void*>(&k_gemm_stream<A16, AK, false, BKM, 2>), STREAM_LDS_64, done);
         if (rc != MST_OK) return rc;
         k_gemm_stream<A16, AK, false, BKM, 2><<<grid, 512, STREAM_LDS_64, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
-    } else if (plan.kernel == EXACT_HALF) {
-        const int rc = gemm_half(AK ? GEMM_TN : BKM ? GEMM_NN : GEMM_NT, plan.tile, (const float*)A, lda, B, ldb, dst, M, N, Kdim, kps, mn, s);
-        if (rc != MST_OK) return rc;
-    } else if (plan.tile == 64) {
-        k_gemm_exact<A16, AK, BKM, 64><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
-    } else if constexpr (A16) {
+    } else if (plan.tile == 128) {
         k_gemm_exact<A16, AK, BKM, 128><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+    } else {
+        k_gemm_exact<A16, AK, BKM, 64><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
     }
     MST_LAUNCH_CHECK();
     if (nparts) {

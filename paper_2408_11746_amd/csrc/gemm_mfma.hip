@@ -1006,14 +1006,14 @@ static int g_sched52 = 1;                 // test hook: 0 = never the five-for-t
 
 int gemm_last_tile() { return g_last_tile; }
 
-int gemm_force_fp32_mfma(int on) {       // 0 automatic; 1, 1032, 1064, 1096, 1128, 1256 the full-precision kernels; 128 / 256 / 160 / 192: split kernel with that tile; 64: streaming bf16 TN
+int gemm_force_fp32_mfma(int on) {       // 0 automatic; 1, 1032, 1064, 1096, 1128 the full-precision kernels (1256: the largest of their tiles, 1128); 128 / 256 / 160 / 192: split kernel with that tile; 64: streaming bf16 TN
     if (on == 52 || on == -52) {                    // (the other settings stay as they are)
         g_sched52 = on > 0;
         return MST_OK;
     }
     const bool exact = on == 1 || on == 1032 || on == 1064 || on == 1096 || on == 1128 || on == 1256;
     g_gemm_fp32_only = exact ? 1 : 0;
-    gemm_exact_tile(exact && on > 1 ? on - 1000 : 0);
+    gemm_exact_tile(exact && on > 1 ? std::min(on - 1000, 128) : 0);
     g_split_tile = (on == 128 || on == 256 || on == 160 || on == 192 || on == 64) ? on : 0;
     return MST_OK;
 }

@@ -21,7 +21,7 @@ constexpr int PK = 32;                                // k of a step; an LDS row
 constexpr int P_PLANE = 256 * 64, P_STAGE = 3 * P_PLANE;
 constexpr unsigned P_LDS = 3 * P_STAGE;               // three stages of [A, B hi, B lo]
 
-// LDS position of unit u (eight k) of row m inside a plane; see half_unit in gemm_half.hip
+// LDS position of unit u (eight k) of row m inside a plane; see ex_unit in gemm_exact.hip
 __device__ __forceinline__ uint32_t plane_unit(int m, int u) {
     const int rho = (m & ~15) | ((m & 3) << 2) | ((m >> 2) & 3);
     return (uint32_t)(rho * 64 + (((u ^ (rho >> 2) ^ (rho >> 4)) & 3) << 4));

@@ -1,6 +1,5 @@
 // fp32 operands on the bf16 matrix cores: the hi / lo split and the LDS layout of bf16 operand
-// tiles that the dense GEMM kernels and the heavy-row product share; the three-part cut and the fp32 sums of the
-// full-precision products.
+// tiles that the dense GEMM kernels and the heavy-row product share.
 #pragma once
 
 #include <stdint.h>
@@ -26,37 +25,6 @@ __device__ inline uint32_t cvt_pk_bf16(float a, float b) {       // {bf16(a), bf
 __device__ inline void split_pair(float x0, float x1, uint32_t& hi, uint32_t& lo) {
     hi = cvt_pk_bf16(x0, x1);
     lo = cvt_pk_bf16(x0 - __uint_as_float(hi << 16), x1 - __uint_as_float(hi & 0xFFFF0000u));
-}
-
-
-// a pair of fp32 values as three words of two bfloat16 each.  The parts are rounded to nearest, so the lower
-// ones have either sign and half the size that truncation leaves: what the dropped products lose has no direction.
-// The third part is exact: 24 bits less 8 and a sign, twice.
-__device__ inline void cut_pair(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-    hi = cvt_pk_bf16(x0, x1);
-    const float b0 = x0 - __uint_as_float(hi << 16), b1 = x1 - __uint_as_float(hi & 0xFFFF0000u);
-    mid = cvt_pk_bf16(b0, b1);
-    const float c0 = b0 - __uint_as_float(mid << 16), c1 = b1 - __uint_as_float(mid & 0xFFFF0000u);
-    lo = __builtin_amdgcn_perm(__float_as_uint(c1), __float_as_uint(c0), 0x07060302u);
-}
-
-// The lower parts of an infinite value are inf - inf = NaN (those of a finite one whose first part rounds to an
-// infinity the infinity of the other sign and NaN), so a sum with such an operand comes out as NaN where fp32
-// products give a number or an infinity.  An output that is NaN is therefore formed again by fp32
-// multiply-adds, up to the first term that makes it NaN by itself; no other output pays more than a compare.
-template <typename TA, bool A_KMAJOR, typename TB, bool B_KMAJOR>
-__device__ __forceinline__ float fp32_sum(const TA* __restrict__ A, int64_t lda, const TB* __restrict__ B, int64_t ldb, int m, int n,
-                                          int kbeg, int kend) {
-    auto value = [](auto x) {
-        if constexpr (sizeof(x) == 2) return __uint_as_float((uint32_t)x << 16);
-        else return x;
-    };
-    float sum = 0.f;
-#pragma unroll 1
-    for (int k = kbeg; k < kend && sum == sum; ++k)
-        sum = fmaf(value(A[A_KMAJOR ? (int64_t)k * lda + m : (int64_t)m * lda + k]),
-                   value(B[B_KMAJOR ? (int64_t)k * ldb + n : (int64_t)n * ldb + k]), sum);
-    return sum;
 }
 
 // ---- loads that go straight to LDS
