@@ -71,24 +71,23 @@ static int ensure_dense_copy(const mst_layer* L, hipStream_t s) {
     return refresh_dense_copy(const_cast<mst_layer*>(L), s);   // cache of vals[], not layer state
 }
 
-// The weights' planes for Y (dX) where the product reads them.  They were kept up since they were first made, or are made now:
-// then products on other streams, which are ordered after the hand-over of the values and not after this call, must find
-// them, so the call waits (once: from here on sync_values and updates make them).  A recording cannot wait and runs later or never:
-// it takes their making with it and says nothing about them.
+// The weights' planes for Y (dX) where the product reads them.  They are kept up (sync_values and updates make them), or are made now:
+// products on other streams, which are ordered after the hand-over of the values and not after this call, must then find
+// them, so the call waits before it says that they are there.  A recording cannot wait and runs later or never:
+// it takes their making with it and says nothing about them; the first eager product after it waits as well.
 static int ensure_planes(const mst_layer* Lc, bool y, mst_dtype act, int M, int N, int Kdim, bool full, const uint16_t*& planes, hipStream_t s) {
     planes = nullptr;
     if (!gemm_wants_planes(act, M, N, Kdim, full)) return MST_OK;
     mst_layer* L = const_cast<mst_layer*>(Lc);       // a cache of Wd, not layer state
     planes = y ? L->planes_y : L->planes_x;
     if (L->planes_valid) return MST_OK;
-    const bool first = !L->planes_used;
     L->planes_used = true;
     const int rc = make_planes(L, s);
     if (rc != MST_OK) return rc;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     MST_HIP(hipStreamIsCapturing(s, &capture));
     if (capture != hipStreamCaptureStatusNone) return MST_OK;
-    if (first) MST_HIP(hipStreamSynchronize(s));
+    MST_HIP(hipStreamSynchronize(s));
     L->planes_valid = true;
     return MST_OK;
 }

@@ -100,3 +100,33 @@ def test_replays_of_a_recorded_handover_reach_planes_read_between_them():
         product.replay()
         torch.cuda.synchronize()
         assert rel_err(Yg.cpu().numpy(), scale * Y1) <= PARTS, scale
+
+
+@pytest.mark.parametrize("first", ["recorded", "eager"])
+def test_products_of_two_streams_find_whole_planes(first):
+    """The planes are made by a product on a busy stream; a product on another stream, issued after that call returned and
+    ordered after the loading of the weights alone, reads them.  Also where the very first product was recorded only."""
+    T, I, O = 256, 512, 512
+    rig, X, dY, Y1, dX1, _ = _layer(T, I, O)
+    L, a, b = rig.layer, torch.cuda.Stream(), torch.cuda.Stream()
+    rig.fwd(X[:100], mst.MST_BF16)                           # the dense copy alone
+    L.buf[-8 * O * I:].fill_(0xFF)                           # the planes, two arrays at the end of the buffer: NaN until they are made
+    Xd, dYd = dev(X), dev(dY)
+    Y, dX = (torch.full((T, n), 7.0, dtype=torch.float32, device=DEV) for n in (O, I))
+    Yg, graph = torch.full((T, O), 7.0, dtype=torch.float32, device=DEV), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    if first == "recorded":
+        with torch.cuda.graph(graph, stream=a):
+            mst.mst_sparse_fc_fwd(L, Xd, Yg, T, mst.MST_BF16, a)
+    with torch.cuda.stream(a):
+        torch.cuda._sleep(100_000_000)                       # (some 50 ms)
+    mst.mst_sparse_fc_fwd(L, Xd, Y, T, mst.MST_BF16, a)
+    mst.mst_sparse_fc_bwd_input(L, dYd, dX, T, mst.MST_BF16, b)
+    torch.cuda.synchronize()
+    assert rel_err(dX.cpu().numpy(), dX1) <= PARTS
+    assert rel_err(Y.cpu().numpy(), Y1) <= PARTS
+    if first == "recorded":
+        for _ in range(2):
+            graph.replay()
+            torch.cuda.synchronize()
+            assert rel_err(Yg.cpu().numpy(), Y1) <= PARTS
