@@ -330,9 +330,10 @@ int mst_mask_update_from_scores(mst_layer_t* layer, const float* G_dev,
  * kernels that depend on one another; the chains of different layers are independent, so on
  * different streams they run side by side, and issued from one native call the host keeps up
  * with them (issued call by call from an interpreter the host is the bound).  The layers, their
- * workspaces and score buffers must be distinct; streams may repeat (those layers then follow
- * one another).  Every argument of every layer is checked before any device work; a failure of a
- * later step (MST_ERR_HIP) leaves the earlier layers updated.  stats_out (host, [n_layers]) may be
+ * workspaces and score buffers must be distinct; streams may repeat: layers of one stream share the launches
+ * of one chain, eight at a time in the order of the list.  Every argument of every layer is checked before any
+ * device work; a later failure (MST_ERR_HIP) leaves the layers of the chains before it updated and those of the chain it
+ * stopped, up to eight, undefined until they are loaded anew.  stats_out (host, [n_layers]) may be
  * NULL.  Results per layer are those of the single-layer call, bit for bit. */
 int mst_mask_update_from_scores_multi(int n_layers, mst_layer_t* const* layers, const float* const* G_dev,
                                       const double* target_density, double zeta, double rand_ratio,
