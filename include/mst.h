@@ -95,7 +95,9 @@ int mst_last_hip_error(void);           /* hipError_t of the last failing HIP ca
 /* ------------------------------------------------------------------ layers */
 
 /* Bytes of device memory a layer of shape [O x I] needs to hold up to nnz_capacity
- * active weights (mask, values, both index views).  0 on invalid arguments. */
+ * active weights: mask, values, both index views, the dense weight copy (4 bytes per position) and, if O and I are
+ * multiples of 32 and one of them of 256, room for the two split copies that products of bfloat16 activations
+ * read (8 bytes per position, whatever the activations are; untouched with fp32 ones).  0 on invalid arguments. */
 size_t mst_layer_device_bytes(int O, int I, int64_t nnz_capacity);
 
 /* Bytes of workspace sufficient for every call below on a layer of this shape with
@@ -133,7 +135,9 @@ int mst_layer_export_dense(const mst_layer_t* layer, float* W_dev, uint8_t* M_de
  * left out; the call that walks it first copies the values from there and waits for that once.)  On a
  * capturing stream the call records the refresh of every view that is built and of a dense copy in
  * use, walked or not; a view that is built, or a dense copy that comes into use, after the recording
- * is not in it.  Every
+ * is not in it.  (The split copy of the weights that products of bfloat16 activations read, see mst_sparse_fc_fwd, is
+ * recorded with it if such a product has read it or the layer's last product call had bfloat16
+ * activations; after a recording without it these products make the copy anew in every call.)  Every
  * mask update changes the set and therefore the meaning of position k of this vector. */
 int mst_layer_values(mst_layer_t* layer, float** vals_dev, int64_t* nnz);
 int mst_layer_sync_values(mst_layer_t* layer, mst_stream_t stream);

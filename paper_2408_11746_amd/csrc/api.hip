@@ -74,7 +74,8 @@ static int ensure_dense_copy(const mst_layer* L, hipStream_t s) {
 // The weights' planes for Y (dX) where the product reads them.  They are kept up (sync_values and updates make them), or are made now:
 // products on other streams, which are ordered after the hand-over of the values and not after this call, must then find
 // them, so the call waits before it says that they are there.  A recording cannot wait and runs later or never:
-// it takes their making with it and says nothing about them; the first eager product after it waits as well.
+// it takes their making with it and says nothing about them; the first eager product after it waits as well.  (Where replays may
+// leave them behind every product makes them and none waits: two that meet write the same bits.)
 static int ensure_planes(const mst_layer* Lc, bool y, mst_dtype act, int M, int N, int Kdim, bool full, const uint16_t*& planes, hipStream_t s) {
     planes = nullptr;
     if (!gemm_wants_planes(act, M, N, Kdim, full)) return MST_OK;
@@ -86,7 +87,7 @@ static int ensure_planes(const mst_layer* Lc, bool y, mst_dtype act, int M, int 
     if (rc != MST_OK) return rc;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     MST_HIP(hipStreamIsCapturing(s, &capture));
-    if (capture != hipStreamCaptureStatusNone) return MST_OK;
+    if (capture != hipStreamCaptureStatusNone || L->planes_missed) return MST_OK;
     MST_HIP(hipStreamSynchronize(s));
     L->planes_valid = true;
     return MST_OK;

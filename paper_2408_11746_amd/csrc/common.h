@@ -98,10 +98,14 @@ struct mst_layer {
     bool Wd_zeros = false;     // Wd is zero at every inactive position (survives a change of the values)
     // The two bfloat16 parts of Wd in the order that the products of bfloat16 activations want (gemm_planes.hip), for Y and for
     // dX; null where no such product has whole tiles.  Made by the first product that reads them, kept up with Wd from then on:
-    // sync_values and the updates that leave Wd valid make them again.
+    // sync_values and the updates that leave Wd valid make them again.  A hand-over that was recorded while the layer
+    // worked on fp32 activations does not carry their making, and its replays leave them behind at times
+    // that the host does not see: products of bfloat16 activations then make them each for itself.
     uint16_t *planes_y = nullptr, *planes_x = nullptr;
     bool planes_used = false;  // some product has read them
+    bool planes_missed = false;  // a hand-over without them has been recorded
     bool planes_valid = false; // they hold the parts of Wd
+    bool planes_kept() const { return planes_used && !planes_missed; }
     // The index views are built lazily: an update of a layer that the dense contractions serve
     // (path choice at the batch size and type of the last product call) leaves them unbuilt; a
     // call that needs them and has a workspace builds them, one without runs the dense product.

@@ -737,8 +737,8 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
     for (int x = 0; x < n_canonical; ++x) {
         mst_layer* L = canonical[x].L;
         L->Wd_valid = L->Wd_zeros = true;
-        L->planes_valid = L->planes_used;
-        if (L->planes_used && (rc = make_planes(L, s)) != MST_OK) return rc;
+        L->planes_valid = L->planes_kept();
+        if (L->planes_valid && (rc = make_planes(L, s)) != MST_OK) return rc;
     }
     return build_canonical(canonical, n_canonical, s);
 }

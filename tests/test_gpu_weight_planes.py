@@ -130,3 +130,44 @@ def test_products_of_two_streams_find_whole_planes(first):
             graph.replay()
             torch.cuda.synchronize()
             assert rel_err(Yg.cpu().numpy(), Y1) <= PARTS
+
+
+def test_a_handover_recorded_for_fp32_activations_leaves_the_planes_alone():
+    """A layer that works on fp32 activations records its hand-over without the planes.  Products of bfloat16 activations that
+    come after all, eager and recorded, see the values of every replay and of every eager hand-over."""
+    T, I, O = 256, 512, 512
+    rig, X, dY, Y1, dX1, (Xf, _) = _layer(T, I, O)
+    L, side = rig.layer, torch.cuda.Stream()
+    assert rel_err(rig.fwd(Xf), Y1) <= 1e-4                  # the dense copy alone
+    L.buf[-8 * O * I:].fill_(0xFF)
+    handover, product = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(handover, stream=side):
+        L.values().mul_(2.0)
+        L.sync_values(side)
+    for _ in range(2):
+        handover.replay()
+        torch.cuda.synchronize()
+    L.sync_values()
+    torch.cuda.synchronize()
+    assert bool((L.buf[-8 * O * I:] == 0xFF).all())
+    assert rel_err(rig.fwd(Xf), 4.0 * Y1) <= 1e-4
+    _check(rig, X, dY, Y1, dX1, 4.0, "first")
+    Xd, Yg = dev(X), torch.empty((T, O), dtype=torch.float32, device=DEV)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(product, stream=side):
+        mst.mst_sparse_fc_fwd(L, Xd, Yg, T, mst.MST_BF16, side)
+    for k, scale in ((3, 8.0), (4, 16.0)):
+        handover.replay()
+        product.replay()
+        torch.cuda.synchronize()
+        assert rel_err(Yg.cpu().numpy(), scale * Y1) <= PARTS, k
+        _check(rig, X, dY, Y1, dX1, scale, k)
+        L.values().mul_(0.5)
+        L.sync_values()
+        product.replay()
+        torch.cuda.synchronize()
+        assert rel_err(Yg.cpu().numpy(), 0.5 * scale * Y1) <= PARTS, k
+        _check(rig, X, dY, Y1, dX1, 0.5 * scale, k)
+        L.values().mul_(2.0)
+        L.sync_values()
