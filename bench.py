@@ -24,6 +24,7 @@ the launch stream.
 from __future__ import annotations
 
 import argparse
+import gc
 import json
 import os
 import sys
@@ -912,7 +913,12 @@ def clock_ramp(mst, torch, stream, ms=40.0):
     """The GPU's clocks take tens of milliseconds to come up after an idle period (layer set-up on the
     host); a short workload timed right after one reads 5-40 % slow.  Before the W warm-up steps of a
     timed region this runs a dense contraction on scratch buffers for `ms` milliseconds.  It touches no
-    layer state, so the W warm-up steps and the K timed steps are the same steps with or without it."""
+    layer state, so the W warm-up steps and the K timed steps are the same steps with or without it.
+    The interpreter's objects of the set-up are collected here and kept out of later collections: one over all of them takes
+    the host 35 ms, and where it fell into the 60 ms of a timed region with little work queued the GPU waited for it
+    (a headline of 3.2 or 4.4 ms per step instead of 2.95)."""
+    gc.collect()
+    gc.freeze()
     n = 4096
     a = torch.randn(n, n, device="cuda:0")
     b = torch.randn(n, n, device="cuda:0")
