@@ -195,8 +195,9 @@ int mst_heavy_rows(int on);
 /* Y_dev [T*O] = X_dev [T*I] (W.M)^T.  T >= 1.
  * (Y and dX of bfloat16 activations on whole 256 x 256 tiles read a copy of the dense weights that is split into two
  * bfloat16 values beforehand and kept in the layer's buffer.  The call that finds it missing -- the first such product of a
- * layer, also after one that was only recorded -- makes it and waits for that on `stream`, so that
- * products on other streams need an order after the hand-over of the values alone; later hand-overs and updates keep it up.
+ * layer, also after one that was only recorded, and the first product that makes the dense copy again after a loading or an
+ * update that built the views -- makes it and waits for that on `stream`, so that products on other streams need an order
+ * after the hand-over of the values alone; hand-overs and the other updates keep it up.
  * While a graph is recorded nothing waits: the recorded product then carries the making with it.) */
 int mst_sparse_fc_fwd(const mst_layer_t* layer, const void* X_dev, float* Y_dev, int T,
                       mst_dtype act, mst_stream_t stream);

@@ -71,11 +71,9 @@ static int ensure_dense_copy(const mst_layer* L, hipStream_t s) {
     return refresh_dense_copy(const_cast<mst_layer*>(L), s);   // cache of vals[], not layer state
 }
 
-// The weights' planes for Y (dX) where the product reads them.  They are kept up (sync_values and updates make them), or are made now:
-// products on other streams, which are ordered after the hand-over of the values and not after this call, must then find
-// them, so the call waits before it says that they are there.  A recording cannot wait and runs later or never:
-// it takes their making with it and says nothing about them; the first eager product after it waits as well.  (Where replays may
-// leave them behind every product makes them and none waits: two that meet write the same bits.)
+// The weights' planes for Y (dX) where the product reads them.  They are kept up (sync_values and updates make them), or are made now
+// (see planes_made; where replays may leave them behind every product makes them and none waits: two that meet write
+// the same bits).
 static int ensure_planes(const mst_layer* Lc, bool y, mst_dtype act, int M, int N, int Kdim, bool full, const uint16_t*& planes, hipStream_t s) {
     planes = nullptr;
     if (!gemm_wants_planes(act, M, N, Kdim, full)) return MST_OK;
@@ -84,13 +82,7 @@ static int ensure_planes(const mst_layer* Lc, bool y, mst_dtype act, int M, int 
     if (L->planes_valid) return MST_OK;
     L->planes_used = true;
     const int rc = make_planes(L, s);
-    if (rc != MST_OK) return rc;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    MST_HIP(hipStreamIsCapturing(s, &capture));
-    if (capture != hipStreamCaptureStatusNone || L->planes_missed) return MST_OK;
-    MST_HIP(hipStreamSynchronize(s));
-    L->planes_valid = true;
-    return MST_OK;
+    return rc == MST_OK && !L->planes_missed ? planes_made(L, s) : rc;
 }
 
 // (full: see full_precision(); split_ws: room for partial outputs of a split of the contraction range, used where the output

@@ -270,6 +270,7 @@ int gemm_wgrad16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, i
 // Y and dX of bfloat16 activations from the split weights' planes; see gemm_planes.hip
 int gemm_planes(const uint16_t* A, const uint16_t* P, float* C, int M, int N, int Kdim, hipStream_t s);
 int make_planes(const mst_layer* L, hipStream_t s);
+int planes_made(mst_layer* L, hipStream_t s);
 // the same at full fp32 precision for any shape (B fp32); see gemm_exact.hip
 int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,
                float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed);

@@ -944,8 +944,22 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
         MST_LAUNCH_CHECK();
     }
     L->Wd_valid = L->Wd_zeros = true;
-    L->planes_valid = L->planes_kept();              // (recorded products read them without asking)
-    return L->planes_valid ? make_planes(L, s) : MST_OK;
+    L->planes_valid = false;
+    if (!L->planes_kept()) return MST_OK;
+    const int rc = make_planes(L, s);                // (recorded products read them without asking)
+    return rc == MST_OK ? planes_made(L, s) : rc;
+}
+
+// The planes of Wd were made on s, by a product and not by the hand-over or the update that changed the weights.  Products on other
+// streams are ordered after those and not after this call, so it waits before it says that the planes are there.  A
+// recording cannot wait and runs later or never: it says nothing about them.
+int planes_made(mst_layer* L, hipStream_t s) {
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    MST_HIP(hipStreamIsCapturing(s, &capture));
+    if (capture != hipStreamCaptureStatusNone) return MST_OK;
+    MST_HIP(hipStreamSynchronize(s));
+    L->planes_valid = true;
+    return MST_OK;
 }
 
 // new values into the entries of the row view (and the dense rows beside it) and / or of the col view, and into

@@ -171,3 +171,24 @@ def test_a_handover_recorded_for_fp32_activations_leaves_the_planes_alone():
         _check(rig, X, dY, Y1, dX1, 0.5 * scale, k)
         L.values().mul_(2.0)
         L.sync_values()
+
+
+def test_products_of_two_streams_find_the_planes_of_weights_loaded_anew():
+    """As above for planes that products have read before: the first product after a loading makes them again together with
+    the dense copy."""
+    T, I, O = 256, 512, 512
+    rig, X, dY, Y1, dX1, _ = _layer(T, I, O)
+    L, a, b = rig.layer, torch.cuda.Stream(), torch.cuda.Stream()
+    _check(rig, X, dY, Y1, dX1, 1.0, "first")
+    W, M = rig.export()
+    L.load_dense(dev(4.0 * W), dev(M), rig.ws)
+    Xd, dYd = dev(X), dev(dY)
+    Y, dX = (torch.full((T, n), 7.0, dtype=torch.float32, device=DEV) for n in (O, I))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(a):
+        torch.cuda._sleep(100_000_000)                       # (some 50 ms)
+    mst.mst_sparse_fc_fwd(L, Xd, Y, T, mst.MST_BF16, a)
+    mst.mst_sparse_fc_bwd_input(L, dYd, dX, T, mst.MST_BF16, b)
+    torch.cuda.synchronize()
+    assert rel_err(dX.cpu().numpy(), 4.0 * dX1) <= PARTS
+    assert rel_err(Y.cpu().numpy(), 4.0 * Y1) <= PARTS
