@@ -66,42 +66,40 @@ __global__ void k_gather_flat(const float* __restrict__ G, int64_t stride, int n
     }
 }
 
-static int ensure_dense_copy(const mst_layer* L, hipStream_t s) {
-    if (L->Wd_valid) return MST_OK;
-    return refresh_dense_copy(const_cast<mst_layer*>(L), s);   // cache of vals[], not layer state
-}
-
-// The weights' planes for Y (dX) where the product reads them.  They are kept up (sync_values and updates make them), or are made now
-// (see planes_made; where replays may leave them behind every product makes them and none waits: two that meet write
-// the same bits).
-static int ensure_planes(const mst_layer* Lc, bool y, mst_dtype act, int M, int N, int Kdim, bool full, const uint16_t*& planes, hipStream_t s) {
+// What a dense product reads besides the activations, for Y (dX): the dense copy, and the weights' planes where the product takes
+// those.  They are kept up (sync_values and updates make them), or are made now: with the dense copy if a product has read
+// them before, else by themselves (see planes_made; where replays may leave them behind every product makes them and none
+// waits: two that meet write the same bits).
+static int ensure_weights(const mst_layer* Lc, bool y, mst_dtype act, int M, int N, int Kdim, bool full, const uint16_t*& planes, hipStream_t s) {
+    mst_layer* L = const_cast<mst_layer*>(Lc);       // caches of vals[], not layer state
+    int rc = MST_OK;
+    bool made = false;                                // (a recording that makes them does not say that they are there)
+    if (!L->Wd_valid) {
+        made = L->planes_kept();
+        rc = refresh_dense_copy(L, s);
+    }
     planes = nullptr;
-    if (!gemm_wants_planes(act, M, N, Kdim, full)) return MST_OK;
-    mst_layer* L = const_cast<mst_layer*>(Lc);       // a cache of Wd, not layer state
+    if (rc != MST_OK || !gemm_wants_planes(act, M, N, Kdim, full)) return rc;
     planes = y ? L->planes_y : L->planes_x;
-    if (L->planes_valid) return MST_OK;
+    if (L->planes_valid || made) return MST_OK;
     L->planes_used = true;
-    const int rc = make_planes(L, s);
+    rc = make_planes(L, s);
     return rc == MST_OK && !L->planes_missed ? planes_made(L, s) : rc;
 }
 
 // (full: see full_precision(); split_ws: room for partial outputs of a split of the contraction range, used where the output
 // has too few tiles to fill the chip; null: one workgroup per tile whatever their number)
 int dense_products_fwd(const mst_layer* L, const void* X, float* Y, int T, mst_dtype act, hipStream_t s, bool full) {
-    int rc = ensure_dense_copy(L, s);
-    if (rc != MST_OK) return rc;
     const uint16_t* planes;
-    rc = ensure_planes(L, true, act, T, L->O, L->I, full, planes, s);
+    const int rc = ensure_weights(L, true, act, T, L->O, L->I, full, planes, s);
     if (rc != MST_OK) return rc;
     return gemm_mfma(GEMM_NT, X, act, L->Wd, MST_F32, planes, Y, T, L->O, L->I, nullptr, 0, s, full);
 }
 
 int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int T, mst_dtype act, hipStream_t s, bool full,
                              float* split_ws, int64_t split_ws_floats) {
-    int rc = ensure_dense_copy(L, s);
-    if (rc != MST_OK) return rc;
     const uint16_t* planes;
-    rc = ensure_planes(L, false, act, T, L->I, L->O, full, planes, s);
+    const int rc = ensure_weights(L, false, act, T, L->I, L->O, full, planes, s);
     if (rc != MST_OK) return rc;
     return gemm_mfma(GEMM_NN, dY, act, L->Wd, MST_F32, planes, dX, T, L->I, L->O, split_ws, split_ws_floats, s, full);
 }

@@ -192,3 +192,32 @@ def test_products_of_two_streams_find_the_planes_of_weights_loaded_anew():
     torch.cuda.synchronize()
     assert rel_err(dX.cpu().numpy(), 4.0 * dX1) <= PARTS
     assert rel_err(Y.cpu().numpy(), 4.0 * Y1) <= PARTS
+
+
+def test_a_recorded_product_makes_the_planes_once():
+    """The first product after a loading makes the planes together with the dense copy where a product has read them before,
+    by themselves otherwise; recorded, it has as many nodes either way, and its replays see the values loaded."""
+    import ctypes
+    hip = ctypes.CDLL(next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line))     # (the one in use)
+    T, I, O = 256, 256, 512
+    nodes = []
+    for read_before in (False, True):
+        rig, X, dY, Y1, dX1, _ = _layer(T, I, O)
+        L, side = rig.layer, torch.cuda.Stream()
+        if read_before:
+            _check(rig, X, dY, Y1, dX1, 1.0, "first")
+            W, M = rig.export()
+            L.load_dense(dev(W), dev(M), rig.ws)
+        Xd, Y = dev(X), torch.empty((T, O), dtype=torch.float32, device=DEV)
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            mst.mst_sparse_fc_fwd(L, Xd, Y, T, mst.MST_BF16, side)
+        n = ctypes.c_size_t()
+        assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+        nodes.append(n.value)
+        for _ in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            assert rel_err(Y.cpu().numpy(), Y1) <= PARTS
+    assert nodes[0] == nodes[1]
