@@ -105,10 +105,12 @@ bool use_dense_path(const mst_layer* L, WalkJob job, mst_dtype act, int T) {
 
 // The one-call backward: one walk for both gradients, the two dense products, or, with bfloat16 activations on other than whole
 // tiles, a sparse dX beside the dense weight gradient, whose operands need no parts (gemm_wgrad.hip: one product per
-// term where dX takes three).  A step of 4099 tokens of 1024 -> 4096, density 0.04: 206 us by one walk, 197 by dX's walk and
-// the dense gradient; 7356 tokens of 4288 -> 3170, 0.048: 1056 -> 923.  The margins are what the models are unsure of: of
-// 70 layers it is then taken at ten, nine of them 0 to 14 % faster and one (5000 tokens of 4001 -> 333, 0.05) 4 % slower; a walk of dX that was
-// ahead of two dense products by less than 15 % by the models lost up to 10 %.
+// term where dX takes three).  A step of 4099 tokens of 1024 -> 4096, density 0.04: 205 us by one walk, 196 to 200 by dX's walk and
+// the dense gradient; 7356 tokens of 4288 -> 3170, 0.048: 1056 -> 923.
+// The modelled time of the dense gradient is 5 % above the measured one for rows of whole 16-byte units (sd 4 %) and 14 %
+// below it for others (sd 6 %), which is made good here; the two margins are what all three models are unsure of.
+// 630 layers of 250 to 5000, 1500 to 9000 tokens, densities 0.03 to 0.1: 3.6 % faster on average than without this choice (up to
+// 43 %), nine 3 to 9 % slower (without the correction, margins 1.03 and 1.15: 4.2 %, twenty-four 3 to 14 % slower).
 // With fp32 activations a sparse dX beside a dense dW is never the fastest.
 static double dense_backward_us(const mst_layer* L, mst_dtype act, int T) {
     const bool full = full_precision(L, WALK_BWD, act, T);
@@ -117,8 +119,9 @@ static double dense_backward_us(const mst_layer* L, mst_dtype act, int T) {
 bool use_sparse_input_grad(const mst_layer* L, mst_dtype act, int T) {
     if (act != MST_BF16 || L->path != MST_PATH_AUTO || whole_tiles(L, act, T) || !full_precision(L, WALK_BWD, act, T)) return false;
     return remembered(L, SPARSE_DX, act, T, [&] {
-        const double us = walk_us(L, WALK_BWD_INPUT, T) + dense_wgrad_us(L, act, T, true) + 1.0e-6 * (double)L->N;   // (G as the gather reads it)
-        return 1.03 * us < walk_us(L, WALK_BWD, T) && 1.15 * us < dense_backward_us(L, act, T);
+        const double modelled = dense_wgrad_us(L, act, T, true), wgrad = (L->O % 8 == 0 && L->I % 8 == 0 ? 0.95 : 1.14) * modelled;
+        const double us = walk_us(L, WALK_BWD_INPUT, T) + wgrad + 1.0e-6 * (double)L->N;   // (G as the gather reads it)
+        return 1.05 * us < walk_us(L, WALK_BWD, T) && 1.2 * us < dense_backward_us(L, act, T) - modelled + wgrad;
     });
 }
 bool use_fused_backward(const mst_layer* L, mst_dtype act, int T) {

@@ -156,3 +156,10 @@ def test_sparse_input_gradient_beside_the_dense_weight_gradient(T, I, O, density
     assert rel_err(dX, opr.fc_bwd_input(dY, W, M)) <= TOL and rel_err(dW, opr.fc_bwd_weight(dY, X, M)) <= TOL
     np.testing.assert_array_equal(dX, rig.bwd_input(yb.view(np.int16), a))
     np.testing.assert_array_equal(dW, rig.bwd_weight(yb.view(np.int16), xb.view(np.int16), a))
+
+
+@pytest.mark.parametrize("T,I,O,density", [(5948, 575, 2568, 0.071), (8194, 1197, 793, 0.062)])
+def test_rows_of_no_whole_units_stay_with_the_one_walk(T, I, O, density):
+    """There the dense weight gradient takes longer than its modelled time: beside dX's walk it lost 13 and 16 % to the walk of both."""
+    W, M = synth.make_layer(49, 3, I, O, density)
+    assert not Rig(W, M, T).layer.uses_dense(mst.MST_BF16, T, 2)
