@@ -286,17 +286,19 @@ struct CountArgs {
     int O, I, KS_r, nsub_r, Rpad_r, KS_c, Rpad_c, row_blocks, col_tiles;
     int *segcnt_r, *rowcnt, *segcnt_c;
 };
-__global__ __launch_bounds__(256) void k_count(const Batch<CountArgs> batch) {
+template <int CAP>
+__global__ __launch_bounds__(256) void k_count(const Batch<CountArgs, CAP> batch) {
     extern __shared__ int cnt[];
     __shared__ __attribute__((aligned(16))) uint8_t m[KSMAX * MT_LD];
     __shared__ int part[4][MT_COLS];
-    unsigned b = blockIdx.x;
-    const CountArgs& a = batch.entry(b);
+    if (batch.surplus()) return;
+    const unsigned b = blockIdx.x;
+    const CountArgs a = batch.entry();
     if (b < (unsigned)a.row_blocks) {
         count_row_block(a.mask, a.O, a.I, a.KS_r, a.nsub_r, a.Rpad_r, a.segcnt_r, a.rowcnt, (int)b, cnt);
     } else {
-        b -= (unsigned)a.row_blocks;
-        count_col_block(a.mask, a.O, a.I, a.KS_c, a.Rpad_c, a.segcnt_c, (int)(b % (unsigned)a.col_tiles), (int)(b / (unsigned)a.col_tiles), m, part);
+        const unsigned t = b - (unsigned)a.row_blocks;
+        count_col_block(a.mask, a.O, a.I, a.KS_c, a.Rpad_c, a.segcnt_c, (int)(t % (unsigned)a.col_tiles), (int)(t / (unsigned)a.col_tiles), m, part);
     }
 }
 
@@ -318,13 +320,15 @@ struct ViewArgs {                                     // of one view: the first 
 struct RankArgs {
     ViewArgs row, col;
 };
-__global__ __launch_bounds__(RB) void k_block_rank(const Batch<RankArgs> batch) {
+template <int CAP>
+__global__ __launch_bounds__(RB) void k_block_rank(const Batch<RankArgs, CAP> batch) {
     __shared__ int len_s[RB], sorted[RB], row_s[RB];
     __shared__ int h_s, nzero_s;
-    unsigned bu = blockIdx.x;
-    const RankArgs& both = batch.entry(bu);
+    if (batch.surplus()) return;
+    const unsigned bu = blockIdx.x;
+    const RankArgs both = batch.entry();
     const bool col = bu >= (unsigned)both.row.NBpad;
-    const ViewArgs& v = col ? both.col : both.row;
+    const ViewArgs v = col ? both.col : both.row;
     const int j = threadIdx.x, b = (int)bu - (col ? both.row.NBpad : 0);
     const int msub = v.msub, nchunk = v.nchunk, Rpad = v.Rpad, NBpad = v.NBpad;
     const int* __restrict__ segcnt = v.segcnt;
@@ -435,9 +439,10 @@ struct ScanArgs {
     int* out;
     int64_t n;
 };
-__global__ __launch_bounds__(1024) void k_scan_excl(const Batch<ScanArgs> batch) {     // a block each
+template <int CAP>
+__global__ __launch_bounds__(1024) void k_scan_excl(const Batch<ScanArgs, CAP> batch) {     // a block each
     __shared__ int wsum[16];
-    const ScanArgs& a = batch.p[blockIdx.x];
+    const ScanArgs a = batch.entry();
     block_scan_excl(a.in, a.out, a.n, wsum);
 }
 
@@ -447,6 +452,7 @@ __global__ __launch_bounds__(1024) void k_scan_excl(const Batch<ScanArgs> batch)
 // octet of a block each and wait at every chunk for the longest, so a view costs the sum over
 // (chunk, block) of the most pairs of an octet.
 struct PtrArgs {
+    RankArgs views;
     const int* rowcnt;                                // counts per row
     int* rowptr;
     int nrows;
@@ -455,13 +461,13 @@ struct PtrArgs {
     int* dense_live;
     int live;
 };
-__global__ __launch_bounds__(1024) void k_view_ptr(const Batch<RankArgs> views, const Batch<PtrArgs> batch) {    // two blocks per layer: row view, col view
+template <int CAP>
+__global__ __launch_bounds__(1024) void k_view_ptr(const Batch<PtrArgs, CAP> batch) {    // two blocks per layer: row view, col view
     __shared__ int wsum[16];
     __shared__ unsigned long long cost_s;
-    const int layer = blockIdx.x >> 1;
-    const bool col = (blockIdx.x & 1) != 0;
-    const ViewArgs& v = col ? views.p[layer].col : views.p[layer].row;
-    const PtrArgs& a = batch.p[layer];
+    const bool col = blockIdx.x != 0;
+    const PtrArgs a = batch.entry();
+    const ViewArgs v = col ? a.views.col : a.views.row;
     const int* const qlen = v.qlen;
     int* const ptr = v.ptr;
     const int NBpad = v.NBpad, NB = v.NB, nchunk = v.nchunk;
@@ -526,9 +532,11 @@ struct FillArgs {                                     // of one view
     int nparts, spp;                                  // (row view)
     int col_tiles;                                    // (col view)
 };
-__global__ __launch_bounds__(256) void k_fill_row(const Batch<FillArgs> batch) {
-    unsigned blk = blockIdx.x;
-    const FillArgs& a = batch.entry(blk);
+template <int CAP>
+__global__ __launch_bounds__(256) void k_fill_row(const Batch<FillArgs, CAP> batch) {
+    if (batch.surplus()) return;
+    const unsigned blk = blockIdx.x;
+    const FillArgs a = batch.entry();
     const uint8_t* __restrict__ mask = a.mask;
     const float* __restrict__ W = a.W;
     const int O = a.O, I = a.I, KS = a.KS, msub = a.msub, nsub = a.nsub, NBpad = a.NBpad, NB = a.NB, Rpad = a.Rpad;
@@ -619,9 +627,11 @@ struct CanonicalArgs {
     int *segcnt, *rowptr, *flat;
     float* vals;
 };
-__global__ __launch_bounds__(256) void k_count_seg(const Batch<CanonicalArgs> batch) {
-    unsigned blk = blockIdx.x;
-    const CanonicalArgs& a = batch.entry(blk);
+template <int CAP>
+__global__ __launch_bounds__(256) void k_count_seg(const Batch<CanonicalArgs, CAP> batch) {
+    if (batch.surplus()) return;
+    const unsigned blk = blockIdx.x;
+    const CanonicalArgs a = batch.entry();
     const uint8_t* __restrict__ mask = a.mask;
     const int64_t N = a.N;
     const int nseg = a.nseg;
@@ -648,9 +658,11 @@ __global__ __launch_bounds__(256) void k_count_seg(const Batch<CanonicalArgs> ba
 // segptr[sg] = active positions before segment sg.  A lane takes four consecutive positions of a
 // window of 256; the row pointers are written by the wavefront whose segment holds the row's
 // first position (rowptr[O] by the last one).
-__global__ __launch_bounds__(256) void k_fill_canonical(const Batch<CanonicalArgs> batch) {
-    unsigned blk = blockIdx.x;
-    const CanonicalArgs& a = batch.entry(blk);
+template <int CAP>
+__global__ __launch_bounds__(256) void k_fill_canonical(const Batch<CanonicalArgs, CAP> batch) {
+    if (batch.surplus()) return;
+    const unsigned blk = blockIdx.x;
+    const CanonicalArgs a = batch.entry();
     const uint8_t* __restrict__ mask = a.mask;
     const float* __restrict__ W = a.W;
     const int O = a.O, I = a.I, nseg = a.nseg;
@@ -711,11 +723,13 @@ __global__ __launch_bounds__(256) void k_fill_canonical(const Batch<CanonicalArg
 // mask tile sits in LDS; thread (column j, row group rg of 32 rows) counts its rows, the
 // counts of the chunk's earlier sub-chunks and of the row groups before it give the position of its
 // first entry in the column's list, then it writes its entries in row order.
-__global__ __launch_bounds__(256) void k_fill_col(const Batch<FillArgs> batch) {
+template <int CAP>
+__global__ __launch_bounds__(256) void k_fill_col(const Batch<FillArgs, CAP> batch) {
     __shared__ __attribute__((aligned(16))) uint8_t m[KSMAX * MT_LD];
     __shared__ int part[4][MT_COLS];
-    unsigned blk = blockIdx.x;
-    const FillArgs& a = batch.entry(blk);
+    if (batch.surplus()) return;
+    const unsigned blk = blockIdx.x;
+    const FillArgs a = batch.entry();
     const uint8_t* __restrict__ mask = a.mask;
     const float* __restrict__ W = a.W;
     const int O = a.O, I = a.I, KS = a.KS, msub = a.msub, nsub = a.nsub, NBpad = a.NBpad, NB = a.NB, Rpad = a.Rpad;
@@ -836,9 +850,9 @@ __global__ void k_copy_i32(const int* __restrict__ src, int* __restrict__ dst, i
 
 // out[j] = sum of in[0 .. j), out[n] = total; in == out is allowed
 static int scan_excl_i32(const int* in, int* out, int64_t n, hipStream_t s) {
-    Batch<ScanArgs> b;
+    Batch<ScanArgs, 1> b;
     b.add(ScanArgs{in, out, n}, 1);
-    k_scan_excl<<<1, 1024, 0, s>>>(b);
+    k_scan_excl<<<b.grid(), 1024, 0, s>>>(b);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
@@ -875,8 +889,9 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
         auto view = [&](const View& v, int which) {
             return ViewArgs{ws.segcnt[which], v.msub, v.nchunk, v.NBpad * RB, v.NBpad, v.NB, v.nseg, v.rowmap, v.rowpos, ws.qlen[which], v.ptr};
         };
-        rank.add(RankArgs{view(r, 0), view(c, 1)}, r.NBpad + c.NBpad);
-        ptr.add(PtrArgs{ws.rowcnt, L->rowptr, O, L->walk_cost, L->heavy_on ? L->heavy : nullptr, L->dense_live, items[x].keep_dense_copy ? 1 : 0}, 2);
+        const RankArgs views{view(r, 0), view(c, 1)};
+        rank.add(views, r.NBpad + c.NBpad);
+        ptr.add(PtrArgs{views, ws.rowcnt, L->rowptr, O, L->walk_cost, L->heavy_on ? L->heavy : nullptr, L->dense_live, items[x].keep_dense_copy ? 1 : 0}, 2);
         const int nrows = r.NB * RB, nparts = std::max(1, std::min(r.nsub(), 8192 / nrows));
         fill_r.add(FillArgs{L->mask, items[x].Wsrc, O, I, r.KS, r.msub, r.nsub(), r.NBpad, r.NB, Rpad_r, L->rowptr, r.ptr, r.rowpos, r.rowmap,
                             ws.segcnt[0], L->heavy_on ? L->heavy : nullptr, L->vals, L->flat, ws.cidx, r.perm, reinterpret_cast<uint2*>(r.ent),
@@ -887,25 +902,25 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
                             ws.segcnt[1], nullptr, nullptr, nullptr, ws.cidx, c.perm, reinterpret_cast<uint2*>(c.ent), 0, 0, ctiles},
                    (int64_t)ctiles * c.nsub());
     }
-    k_count<<<count.blocks(), 256, (size_t)nsub_max * 4, s>>>(count);
+    launch_batch(count, [&](const auto& b) { k_count<<<b.grid(), 256, (size_t)nsub_max * 4, s>>>(b); });
     MST_LAUNCH_CHECK();
     for (int x = 0; x < n; ++x)
         if (items[x].L->heavy_on) {
             const int rc = heavy_mark(items[x].L, items[x].ws, items[x].L->row.NBpad * RB, s);  // heavy rows leave the view
             if (rc != MST_OK) return rc;
         }
-    k_block_rank<<<rank.blocks(), RB, 0, s>>>(rank);
+    launch_batch(rank, [&](const auto& b) { k_block_rank<<<b.grid(), RB, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
-    k_view_ptr<<<2 * n, 1024, 0, s>>>(rank, ptr);
+    launch_batch(ptr, [&](const auto& b) { k_view_ptr<<<b.grid(), 1024, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
-    k_fill_row<<<fill_r.blocks(), 256, 0, s>>>(fill_r);
+    launch_batch(fill_r, [&](const auto& b) { k_fill_row<<<b.grid(), 256, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
     for (int x = 0; x < n; ++x)
         if (items[x].L->heavy_on) {
             const int rc = heavy_fill(items[x].L, s);
             if (rc != MST_OK) return rc;
         }
-    k_fill_col<<<fill_c.blocks(), 256, 0, s>>>(fill_c);
+    launch_batch(fill_c, [&](const auto& b) { k_fill_col<<<b.grid(), 256, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
     for (int x = 0; x < n; ++x) {
         mst_layer* L = items[x].L;
@@ -928,11 +943,11 @@ int build_canonical(const BuildItem* items, int n, hipStream_t s) {
         seg.add(CanonicalArgs{L->mask, items[x].Wsrc, L->O, L->I, L->N, nseg, cnt, L->rowptr, L->flat, L->vals}, cdiv(nseg, 4));
         scan.add(ScanArgs{cnt, cnt, nseg}, 1);
     }
-    k_count_seg<<<seg.blocks(), 256, 0, s>>>(seg);
+    launch_batch(seg, [&](const auto& b) { k_count_seg<<<b.grid(), 256, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
-    k_scan_excl<<<n, 1024, 0, s>>>(scan);
+    launch_batch(scan, [&](const auto& b) { k_scan_excl<<<b.grid(), 1024, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
-    k_fill_canonical<<<seg.blocks(), 256, 0, s>>>(seg);
+    launch_batch(seg, [&](const auto& b) { k_fill_canonical<<<b.grid(), 256, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
@@ -1100,7 +1115,7 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
     // learn the active count first so that nothing is written when it does not fit
     Batch<CountArgs> count;
     count.add(CountArgs{M_dev, L->O, L->I, L->row.KS, L->row.nsub(), 0, 0, 0, L->O, 1, nullptr, ws.rowcnt, nullptr}, L->O);
-    k_count<<<L->O, 256, (size_t)L->row.nsub() * 4, s>>>(count);
+    launch_batch(count, [&](const auto& b) { k_count<<<b.grid(), 256, (size_t)L->row.nsub() * 4, s>>>(b); });
     MST_LAUNCH_CHECK();
     int rcs = scan_excl_i32(ws.rowcnt, L->rowptr, L->O, s);          // rebuilt below anyway
     if (rcs != MST_OK) return rcs;

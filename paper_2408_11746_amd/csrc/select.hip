@@ -240,10 +240,12 @@ struct SelectArgs {
     int dig0, dig1;      // blocks of a digit pass
     int nb0;             // blocks of the tie and flag passes for the first
 };
-__global__ __launch_bounds__(SEL_NT) void k_select_digit2(const Batch<SelectArgs> batch, int shift, int width, int first) {
+template <int CAP>
+__global__ __launch_bounds__(SEL_NT) void k_select_digit2(const Batch<SelectArgs, CAP> batch, int shift, int width, int first) {
     __shared__ DigitShared sh;
-    unsigned b = blockIdx.x;
-    const SelectArgs& a = batch.entry(b);
+    if (batch.surplus()) return;
+    const unsigned b = blockIdx.x;
+    const SelectArgs a = batch.entry();
     if ((int)b < a.dig0) select_digit_block(a.pk, a.nnz, a.st_p, shift, width, first, (int)b, a.dig0, sh);
     else select_digit_block(a.gk, a.N, a.st_g, shift, width, first, (int)b - a.dig0, a.dig1, sh);
 }
@@ -268,10 +270,12 @@ __device__ void select_ties_block(KS ks, int64_t n, const uint64_t* __restrict__
     if (threadIdx.x == 0) blk[b] = cnt;
 }
 
-__global__ __launch_bounds__(256) void k_select_ties2(const Batch<SelectArgs> batch) {
+template <int CAP>
+__global__ __launch_bounds__(256) void k_select_ties2(const Batch<SelectArgs, CAP> batch) {
     __shared__ int cnt;
-    unsigned b = blockIdx.x;
-    const SelectArgs& a = batch.entry(b);
+    if (batch.surplus()) return;
+    const unsigned b = blockIdx.x;
+    const SelectArgs a = batch.entry();
     if ((int)b < a.nb0) select_ties_block(a.pk, a.nnz, a.st_p, a.blk_p, (int)b, cnt);
     else select_ties_block(a.gk, a.N, a.st_g, a.blk_g, (int)b - a.nb0, cnt);
 }
@@ -343,11 +347,13 @@ __device__ void select_flag_block(KS ks, int64_t n, const uint64_t* __restrict__
     }
 }
 
-__global__ __launch_bounds__(256) void k_select_flag2(const Batch<SelectArgs> batch) {
+template <int CAP>
+__global__ __launch_bounds__(256) void k_select_flag2(const Batch<SelectArgs, CAP> batch) {
     __shared__ int wsum[4];
     __shared__ int64_t before_s[4];
-    unsigned b = blockIdx.x;
-    const SelectArgs& a = batch.entry(b);
+    if (batch.surplus()) return;
+    const unsigned b = blockIdx.x;
+    const SelectArgs a = batch.entry();
     if ((int)b < a.nb0) select_flag_block(a.pk, a.nnz, a.st_p, a.blk_p, a.sink_p, (int)b, wsum, before_s);
     else select_flag_block(a.gk, a.N, a.st_g, a.blk_g, a.sink_g, (int)b - a.nb0, wsum, before_s);
 }
@@ -374,9 +380,11 @@ struct RandArgs {
     FlagSink sink;
     int hist_blocks;
 };
-__global__ __launch_bounds__(SEL_NT) void k_rand_hist(const Batch<RandArgs> batch) {
-    unsigned blk = blockIdx.x;
-    const RandArgs& a = batch.entry(blk);
+template <int CAP>
+__global__ __launch_bounds__(SEL_NT) void k_rand_hist(const Batch<RandArgs, CAP> batch) {
+    if (batch.surplus()) return;
+    const unsigned blk = blockIdx.x;
+    const RandArgs a = batch.entry();
     const RandKeys ks = a.ks;
     const int64_t n = a.n;
     uint64_t* __restrict__ state = a.state;
@@ -449,9 +457,11 @@ __global__ __launch_bounds__(SEL_NT) void k_rand_hist(const Batch<RandArgs> batc
 // the spot; those of the picked bin (about 16 per block) are gathered in LDS and appended to the
 // list with ONE add to its length (an add per hit would queue up at the counter)
 constexpr int COMPACT_PER_BLOCK = SEL_NT * 16, COMPACT_STAGE = 512;
-__global__ __launch_bounds__(SEL_NT) void k_rand_compact(const Batch<RandArgs> batch) {       // COMPACT_PER_BLOCK indices per block
-    unsigned blk = blockIdx.x;
-    const RandArgs& a = batch.entry(blk);
+template <int CAP>
+__global__ __launch_bounds__(SEL_NT) void k_rand_compact(const Batch<RandArgs, CAP> batch) {       // COMPACT_PER_BLOCK indices per block
+    if (batch.surplus()) return;
+    const unsigned blk = blockIdx.x;
+    const RandArgs a = batch.entry();
     const RandKeys ks = a.ks;
     const int64_t n = a.n;
     uint64_t* __restrict__ state = a.state;
@@ -498,8 +508,9 @@ __global__ __launch_bounds__(SEL_NT) void k_rand_compact(const Batch<RandArgs> b
 // one block: the state[1]-th smallest (key, index) of the list decides the threshold.  Lists of up to
 // RAND_LDS_KEYS items (the usual case by far) are searched in LDS.
 constexpr int RAND_LDS_KEYS = 7168;
-__global__ __launch_bounds__(SEL_NT) void k_rand_finish(const Batch<RandArgs> batch) {        // a block per layer
-    const RandArgs& a = batch.p[blockIdx.x];
+template <int CAP>
+__global__ __launch_bounds__(SEL_NT) void k_rand_finish(const Batch<RandArgs, CAP> batch) {        // a block per layer
+    const RandArgs a = batch.entry();
     uint64_t* __restrict__ state = a.state;
     const RandItem* __restrict__ list = a.list;
     const FlagSink sink = a.sink;
@@ -593,9 +604,11 @@ __global__ __launch_bounds__(SEL_NT) void k_rand_finish(const Batch<RandArgs> ba
 struct InitArgs {
     uint64_t *state, k[SEL_STATES];
 };
-__global__ __launch_bounds__(256) void k_update_init(const Batch<InitArgs> batch) {
-    unsigned b = blockIdx.x;
-    const InitArgs& a = batch.entry(b);
+template <int CAP>
+__global__ __launch_bounds__(256) void k_update_init(const Batch<InitArgs, CAP> batch) {
+    if (batch.surplus()) return;
+    const unsigned b = blockIdx.x;
+    const InitArgs a = batch.entry();
     const int64_t i = (int64_t)b * blockDim.x + threadIdx.x;
     if (i < (int64_t)SEL_STATES * SEL_STATE_WORDS) {
         const int w = (int)(i % SEL_STATE_WORDS), which = (int)(i / SEL_STATE_WORDS);
@@ -614,9 +627,11 @@ struct PruneArgs {
     uint8_t* mask;
     int zero_pruned;
 };
-__global__ __launch_bounds__(256) void k_apply_prune(const Batch<PruneArgs> batch) {
-    unsigned b = blockIdx.x;
-    const PruneArgs& a = batch.entry(b);
+template <int CAP>
+__global__ __launch_bounds__(256) void k_apply_prune(const Batch<PruneArgs, CAP> batch) {
+    if (batch.surplus()) return;
+    const unsigned b = blockIdx.x;
+    const PruneArgs a = batch.entry();
     const int64_t k = (int64_t)b * blockDim.x + threadIdx.x;
     if (k >= a.nnz) return;
     const int f = a.flat[k];
@@ -704,28 +719,28 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
         if (nnz > 0)
             prune.add(PruneArgs{L->vals, L->flat, st.n_prune > 0 ? ws.psel : nullptr, nnz, Wnew, L->mask, with_views ? 0 : 1}, cdiv(nnz, 256));
     }
-    k_update_init<<<init.blocks(), 256, 0, s>>>(init);
+    launch_batch(init, [&](const auto& b) { k_update_init<<<b.grid(), 256, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
     if (digit.n > 0) {
         for (int shift = 32 - SEL_DIGIT_BITS; shift >= 0; shift -= SEL_DIGIT_BITS) {
-            k_select_digit2<<<digit.blocks(), SEL_NT, 0, s>>>(digit, shift, SEL_DIGIT_BITS, shift == 32 - SEL_DIGIT_BITS ? 1 : 0);
+            launch_batch(digit, [&](const auto& b) { k_select_digit2<<<b.grid(), SEL_NT, 0, s>>>(b, shift, SEL_DIGIT_BITS, shift == 32 - SEL_DIGIT_BITS ? 1 : 0); });
             MST_LAUNCH_CHECK();
         }
-        k_select_ties2<<<flag.blocks(), 256, 0, s>>>(flag);
+        launch_batch(flag, [&](const auto& b) { k_select_ties2<<<b.grid(), 256, 0, s>>>(b); });
         MST_LAUNCH_CHECK();
-        k_select_flag2<<<flag.blocks(), 256, 0, s>>>(flag);
+        launch_batch(flag, [&](const auto& b) { k_select_flag2<<<b.grid(), 256, 0, s>>>(b); });
         MST_LAUNCH_CHECK();
     }
     if (hist.n > 0) {
-        k_rand_hist<<<hist.blocks(), SEL_NT, 0, s>>>(hist);
+        launch_batch(hist, [&](const auto& b) { k_rand_hist<<<b.grid(), SEL_NT, 0, s>>>(b); });
         MST_LAUNCH_CHECK();
-        k_rand_compact<<<compact.blocks(), SEL_NT, 0, s>>>(compact);
+        launch_batch(compact, [&](const auto& b) { k_rand_compact<<<b.grid(), SEL_NT, 0, s>>>(b); });
         MST_LAUNCH_CHECK();
-        k_rand_finish<<<hist.n, SEL_NT, 0, s>>>(hist);
+        launch_batch(hist, [&](const auto& b) { k_rand_finish<<<dim3(1, (unsigned)b.n), SEL_NT, 0, s>>>(b); });
         MST_LAUNCH_CHECK();
     }
     if (prune.n > 0) {
-        k_apply_prune<<<prune.blocks(), 256, 0, s>>>(prune);
+        launch_batch(prune, [&](const auto& b) { k_apply_prune<<<b.grid(), 256, 0, s>>>(b); });
         MST_LAUNCH_CHECK();
     }
     for (int x = 0; x < n; ++x) {
