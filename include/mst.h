@@ -266,11 +266,12 @@ int mst_bwd_force_shape(int wavefronts_per_workgroup, int quads_per_wavefront);
  * result's terms in the same order and give identical bits.  -52 / 52 switch off / on the
  * schedule that gives two 256 x 256 tiles five workgroups (used where plain k ranges would
  * leave a fifth of the CUs idle; other cut points of the k range, so another order of
- * additions); these two leave the other settings as they are.  Test and measurement aid,
+ * additions); these two leave the other settings as they are.  24 = Y and dX of the dense path on the sparse matrix
+ * instructions at any density where O and I are multiples of 64 (the same two parts per fp32 operand).  Test and measurement aid,
  * not thread-safe. */
 int mst_gemm_force_fp32_mfma(int on);
 /* Workgroup tile (128, 256, 160 or 192 as above) of the last dense product that ran on a split
- * kernel in this process, 0 if it ran on another kernel.  Test aid, not thread-safe. */
+ * kernel in this process, 24 if it ran on the sparse matrix instructions, 0 if it ran on another kernel.  Test aid, not thread-safe. */
 int mst_gemm_last_tile(void);
 
 /* G_dev [O*I] = dY^T X at every position (the score of gradient-based growth: the dense

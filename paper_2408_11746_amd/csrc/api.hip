@@ -66,9 +66,42 @@ __global__ void k_gather_flat(const float* __restrict__ G, int64_t stride, int n
     }
 }
 
+// Y (dX) on the sparse matrix instructions where that is ahead: *done says whether it ran.  The packed weights are kept
+// up as the planes are (see ensure_weights); the first product of a layer that makes them learns how even the mask is
+// and may leave the work to the dense kernels after all.
+static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, int T, mst_dtype act, int64_t split_floats, hipStream_t s, bool* done) {
+    mst_layer* L = const_cast<mst_layer*>(Lc);       // caches of vals[], not layer state
+    *done = false;
+    int tokens = pairs_tokens(L, y, act, T, split_floats);
+    if (tokens == 0) return MST_OK;
+    bool made = false;
+    if (!L->Wd_valid) {
+        made = pairs_kept(L, L->nnz);
+        const int rc = refresh_dense_copy(L, s);
+        if (rc != MST_OK) return rc;
+    }
+    if (L->pairs_valid && !L->pairs_recorded) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        MST_HIP(hipStreamIsCapturing(s, &capture));
+        L->pairs_recorded = capture != hipStreamCaptureStatusNone;
+    }
+    if (!L->pairs_valid && !made) {
+        const bool first = !L->pairs_used;
+        L->pairs_used = true;
+        const int rc = make_pairs(L, s);
+        const int rcm = rc == MST_OK ? weights_made(L, false, true, first, s) : rc;
+        if (rcm != MST_OK) return rcm;
+        tokens = pairs_tokens(L, y, act, T, split_floats);
+        if (tokens == 0) return MST_OK;
+    }
+    *done = true;
+    gemm_note_tile(24);
+    return gemm_pairs(A, act, y ? L->pairs_y : L->pairs_x, C, T, tokens, s);
+}
+
 // What a dense product reads besides the activations, for Y (dX): the dense copy, and the weights' planes where the product takes
 // those.  They are kept up (sync_values and updates make them), or are made now: with the dense copy if a product has read
-// them before, else by themselves (see planes_made; where replays may leave them behind every product makes them and none
+// them before, else by themselves (see weights_made; where replays may leave them behind every product makes them and none
 // waits: two that meet write the same bits).
 static int ensure_weights(const mst_layer* Lc, bool y, mst_dtype act, int M, int N, int Kdim, bool full, const uint16_t*& planes, hipStream_t s) {
     mst_layer* L = const_cast<mst_layer*>(Lc);       // caches of vals[], not layer state
@@ -84,22 +117,28 @@ static int ensure_weights(const mst_layer* Lc, bool y, mst_dtype act, int M, int
     if (L->planes_valid || made) return MST_OK;
     L->planes_used = true;
     rc = make_planes(L, s);
-    return rc == MST_OK && !L->planes_missed ? planes_made(L, s) : rc;
+    return rc == MST_OK && !L->planes_missed ? weights_made(L, true, false, false, s) : rc;
 }
 
 // (full: see full_precision(); split_ws: room for partial outputs of a split of the contraction range, used where the output
 // has too few tiles to fill the chip; null: one workgroup per tile whatever their number)
 int dense_products_fwd(const mst_layer* L, const void* X, float* Y, int T, mst_dtype act, hipStream_t s, bool full) {
+    bool done = false;
+    int rc = full ? MST_OK : pairs_product(L, true, X, Y, T, act, 0, s, &done);
+    if (rc != MST_OK || done) return rc;
     const uint16_t* planes;
-    const int rc = ensure_weights(L, true, act, T, L->O, L->I, full, planes, s);
+    rc = ensure_weights(L, true, act, T, L->O, L->I, full, planes, s);
     if (rc != MST_OK) return rc;
     return gemm_mfma(GEMM_NT, X, act, L->Wd, MST_F32, planes, Y, T, L->O, L->I, nullptr, 0, s, full);
 }
 
 int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int T, mst_dtype act, hipStream_t s, bool full,
                              float* split_ws, int64_t split_ws_floats) {
+    bool done = false;
+    int rc = full ? MST_OK : pairs_product(L, false, dY, dX, T, act, split_ws ? split_ws_floats : 0, s, &done);
+    if (rc != MST_OK || done) return rc;
     const uint16_t* planes;
-    const int rc = ensure_weights(L, false, act, T, L->I, L->O, full, planes, s);
+    rc = ensure_weights(L, false, act, T, L->I, L->O, full, planes, s);
     if (rc != MST_OK) return rc;
     return gemm_mfma(GEMM_NN, dY, act, L->Wd, MST_F32, planes, dX, T, L->I, L->O, split_ws, split_ws_floats, s, full);
 }

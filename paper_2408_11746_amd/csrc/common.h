@@ -66,6 +66,15 @@ struct View {
     int nsub() const { return nchunk * msub; }
 };
 
+// S [R x K] as the products on the sparse matrix instructions read it (gemm_pairs.hip): bands of 256 rows, steps of 64 k
+struct PairsView {
+    int R = 0, K = 0, nk = 0, bands = 0;
+    uint8_t* slots = nullptr;  // [band][step][32] where the k pairs (2 p, 2 p + 1) of a step go in an LDS row
+    uint32_t* flags = nullptr; // [band][step] a byte per two tiles of 32 rows: 1 if one of them needs a second step
+    uint32_t* count = nullptr; // how many of those bytes are 1 (of both views: the row view's)
+    char* blocks = nullptr;    // [band][2 nk] packed tiles of the steps, then those of the second steps
+    size_t bytes = 0;
+};
 // Hd row j = row heavy[1 + j] of W . M, from the canonical arrays, by one block (heavy rows, heavy.hip);
 // value(k) = the k-th active weight.  Every thread of the block must call it; j at or past the count does nothing.
 template <typename F>
@@ -107,6 +116,14 @@ struct mst_layer {
     bool planes_missed = false;  // a hand-over without them has been recorded
     bool planes_valid = false; // they hold the parts of Wd
     bool planes_kept() const { return planes_used && !planes_missed; }
+    // The packed weights of Y and dX on the sparse matrix instructions, with the life of the planes: made by the first product that
+    // reads them, kept up with Wd from then on while the density is one at which they are used.  (No layer of another
+    // shape has them: blocks null.)
+    mst::PairsView pairs_y, pairs_x;
+    bool pairs_used = false, pairs_missed = false, pairs_valid = false;      // as those of the planes
+    bool pairs_recorded = false;   // a recorded product reads them without making them: kept up at any density
+    bool pairs_matched = false;    // their slots were chosen for the present active set
+    float pairs_skew = 0.f;        // share of the steps with a second one, beyond what a uniform mask would have (measured when they are first made)
     // The index views are built lazily: an update of a layer that the dense contractions serve
     // (path choice at the batch size and type of the last product call) leaves them unbuilt; a
     // call that needs them and has a workspace builds them, one without runs the dense product.
@@ -283,7 +300,17 @@ int gemm_wgrad16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, i
 // Y and dX of bfloat16 activations from the split weights' planes; see gemm_planes.hip
 int gemm_planes(const uint16_t* A, const uint16_t* P, float* C, int M, int N, int Kdim, hipStream_t s);
 int make_planes(const mst_layer* L, hipStream_t s);
-int planes_made(mst_layer* L, hipStream_t s);
+int weights_made(mst_layer* L, bool planes, bool pairs, bool measure, hipStream_t s);
+// the same at densities of a tenth and below, for both activation types; see gemm_pairs.hip
+PairsView pairs_view(void* mem, int R, int K);
+bool pairs_kept(const mst_layer* L, int64_t nnz);
+int make_pairs(mst_layer* L, hipStream_t s);
+int measure_pairs(mst_layer* L, hipStream_t s);
+int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split_floats);
+int gemm_pairs(const void* A, mst_dtype act, const PairsView& v, float* C, int T, int tokens, hipStream_t s);
+double gemm_two_parts_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split);
+bool gemm_pairs_forced();
+void gemm_note_tile(int tile);
 // the same at full fp32 precision for any shape (B fp32); see gemm_exact.hip
 int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,
                float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed);

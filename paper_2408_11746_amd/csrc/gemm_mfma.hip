@@ -1005,8 +1005,10 @@ static int g_last_tile = 0;               // workgroup tile of the last split-ke
 static int g_sched52 = 1;                 // test hook: 0 = never the five-for-two schedule
 
 int gemm_last_tile() { return g_last_tile; }
+void gemm_note_tile(int tile) { g_last_tile = tile; }
+bool gemm_pairs_forced() { return g_split_tile == 24; }
 
-int gemm_force_fp32_mfma(int on) {       // 0 automatic; 1, 1032, 1064, 1096, 1128 the full-precision kernels (1256: the largest of their tiles, 1128); 128 / 256 / 160 / 192: split kernel with that tile; 64: streaming bf16 TN
+int gemm_force_fp32_mfma(int on) {       // 0 automatic; 1, 1032, 1064, 1096, 1128 the full-precision kernels (1256: the largest of their tiles, 1128); 128 / 256 / 160 / 192: split kernel with that tile; 64: streaming bf16 TN; 24: gemm_pairs.hip
     if (on == 52 || on == -52) {                    // (the other settings stay as they are)
         g_sched52 = on > 0;
         return MST_OK;
@@ -1014,7 +1016,7 @@ int gemm_force_fp32_mfma(int on) {       // 0 automatic; 1, 1032, 1064, 1096, 11
     const bool exact = on == 1 || on == 1032 || on == 1064 || on == 1096 || on == 1128 || on == 1256;
     g_gemm_fp32_only = exact ? 1 : 0;
     gemm_exact_tile(exact && on > 1 ? std::min(on - 1000, 128) : 0);
-    g_split_tile = (on == 128 || on == 256 || on == 160 || on == 192 || on == 64) ? on : 0;
+    g_split_tile = (on == 128 || on == 256 || on == 160 || on == 192 || on == 64 || on == 24) ? on : 0;
     return MST_OK;
 }
 
@@ -1029,7 +1031,7 @@ static bool split_ok(int M, int N, int Kdim, int64_t lda, int64_t ldb, bool a_km
 static SplitPlan plan_fp32(GemmKind kind, int M, int N, int Kdim, int64_t max_split, bool summed) {
     const bool ak = kind == GEMM_TN;
     if (!split_ok(M, N, Kdim, ak ? M : Kdim, kind == GEMM_NT ? Kdim : N, ak)) return SplitPlan{0, 1, 0.0};
-    const int pin = g_split_tile;
+    const int pin = g_split_tile == 24 ? 0 : g_split_tile;
     SplitPlan plan = plan_split(M, N, Kdim, max_split, summed, pin == 0 || pin == 128, pin == 0 || pin == 256,
                                 !ak && (pin == 0 || pin == 160), !ak && (pin == 0 || pin == 192));
     if (plan.tile == 0)                               // the pinned tile does not fit this shape: any that does
@@ -1160,6 +1162,15 @@ int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_d
     if (kind == GEMM_TN) return launch_split<true, true>(plan, A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
     if (kind == GEMM_NT) return launch_split<false, false>(plan, A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
     return launch_split<false, true>(plan, A, Kdim, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+}
+
+// Modelled time of a product Y or dX that the kernels of two bfloat16 parts per fp32 operand run, 0 where others do (or one
+// of their tiles is pinned).
+double gemm_two_parts_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split) {
+    if (g_gemm_fp32_only || g_split_tile != 0) return 0.0;
+    if (a_dt == MST_BF16) return use_a16(M, N, Kdim) ? a16_us(M, N, Kdim) : 0.0;
+    const SplitPlan plan = plan_fp32(kind, M, N, Kdim, max_split, true);
+    return plan.tile != 0 ? plan.us : 0.0;
 }
 
 // Modelled time of a product in microseconds, as the kernel choice above would run it.

@@ -144,12 +144,15 @@ constexpr int CSEG = 2048;         // positions per wavefront of build_canonical
 
 struct LayerCarve {
     size_t mask, vals, flat, rowptr, Wd;
-    size_t rptr, rent, rperm, rmap, rpos, cptr, cent, cperm, cmap, cpos, cost, heavy, Hd, py, px;
+    size_t rptr, rent, rperm, rmap, rpos, cptr, cent, cperm, cmap, cpos, cost, heavy, Hd, sy, sx, py, px;
     size_t total;
 };
 
 // the tile of gemm_planes.hip divides the outputs of one product, its k step the contraction range
 static bool has_planes(int O, int I) { return O % 32 == 0 && I % 32 == 0 && (O % 256 == 0 || I % 256 == 0); }
+
+// whole steps of gemm_pairs.hip in both directions
+static bool has_pairs(int O, int I) { return O % 64 == 0 && I % 64 == 0; }
 
 static LayerCarve carve_layer(int O, int I, int64_t cap) {
     LayerCarve c{};
@@ -175,6 +178,8 @@ static LayerCarve carve_layer(int O, int I, int64_t cap) {
     c.cost = take(16 + 4);
     c.heavy = take((size_t)(HEAVY_MAX + 2) * 4);
     c.Hd = take((size_t)HEAVY_MAX * I * 4);
+    c.sy = take(has_pairs(O, I) ? pairs_view(nullptr, O, I).bytes : 0);
+    c.sx = take(has_pairs(O, I) ? pairs_view(nullptr, I, O).bytes : 0);
     c.py = take(has_planes(O, I) ? (size_t)N * 4 : 0);
     c.px = take(has_planes(O, I) ? (size_t)N * 4 : 0);
     c.total = off;
@@ -926,7 +931,7 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
         mst_layer* L = items[x].L;
         L->views_valid = true;
         L->row_stale = L->col_stale = false;
-        if (!items[x].keep_dense_copy) L->Wd_valid = L->Wd_zeros = L->planes_valid = false;
+        if (!items[x].keep_dense_copy) L->Wd_valid = L->Wd_zeros = L->planes_valid = L->pairs_valid = L->pairs_matched = false;
     }
     return MST_OK;
 }
@@ -962,21 +967,30 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
         MST_LAUNCH_CHECK();
     }
     L->Wd_valid = L->Wd_zeros = true;
-    L->planes_valid = false;
-    if (!L->planes_kept()) return MST_OK;
-    const int rc = make_planes(L, s);                // (recorded products read them without asking)
-    return rc == MST_OK ? planes_made(L, s) : rc;
+    L->planes_valid = L->pairs_valid = false;
+    const bool planes = L->planes_kept(), pairs = pairs_kept(L, L->nnz);
+    if (!planes && !pairs) return MST_OK;
+    int rc = planes ? make_planes(L, s) : MST_OK;    // (recorded products read them without asking)
+    if (rc == MST_OK && pairs) rc = make_pairs(L, s);
+    return rc == MST_OK ? weights_made(L, planes, pairs, false, s) : rc;
 }
 
-// The planes of Wd were made on s, by a product and not by the hand-over or the update that changed the weights.  Products on other
-// streams are ordered after those and not after this call, so it waits before it says that the planes are there.  A
-// recording cannot wait and runs later or never: it says nothing about them.
-int planes_made(mst_layer* L, hipStream_t s) {
+// The planes of Wd (its packed pairs) were made on s, by a product and not by the hand-over or the update that changed the
+// weights.  Products on other streams are ordered after those and not after this call, so it waits before it says that they are
+// there.  A recording cannot wait and runs later or never: it says nothing about them.
+int weights_made(mst_layer* L, bool planes, bool pairs, bool measure, hipStream_t s) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     MST_HIP(hipStreamIsCapturing(s, &capture));
     if (capture != hipStreamCaptureStatusNone) return MST_OK;
-    MST_HIP(hipStreamSynchronize(s));
-    L->planes_valid = true;
+    if (measure) {
+        const int rc = measure_pairs(L, s);
+        if (rc != MST_OK) return rc;
+    } else {
+        MST_HIP(hipStreamSynchronize(s));
+    }
+    L->planes_valid |= planes;
+    L->pairs_valid |= pairs;
+    L->pairs_matched |= pairs;
     return MST_OK;
 }
 
@@ -1085,6 +1099,10 @@ int mst_layer_create(mst_layer_t** out, int O, int I, int64_t nnz_capacity, void
     L->dense_live = (int*)(b + c.cost + 16);
     L->heavy = (int*)(b + c.heavy);
     L->Hd = (float*)(b + c.Hd);
+    if (has_pairs(O, I)) {
+        L->pairs_y = pairs_view(b + c.sy, O, I);
+        L->pairs_x = pairs_view(b + c.sx, I, O);
+    }
     if (has_planes(O, I)) {
         L->planes_y = (uint16_t*)(b + c.py);
         L->planes_x = (uint16_t*)(b + c.px);
@@ -1125,6 +1143,7 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
     if ((int64_t)total > L->cap) return MST_ERR_STATE;
     MST_HIP(hipMemcpyAsync(L->mask, M_dev, (size_t)L->N, hipMemcpyDeviceToDevice, s));
     L->nnz = total;
+    L->pairs_skew = 0.f;
     L->choice.store(0, std::memory_order_relaxed);
     L->built = false;                                   // a failed rebuild leaves no usable layer
     // Heavy rows (heavy.hip).  The dense pass costs a launch after every sparse forward, a read of
@@ -1181,9 +1200,10 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     // than at the next product, so that products recorded into a graph never see stale weights.
     const bool dense = L->Wd_zeros && L->nnz > 0, views = L->nnz > 0 && L->views_valid;   // unbuilt views take the values when they are built
     L->Wd_valid = dense;
-    bool row = views, col = views, planes = dense && L->planes_valid;
+    bool row = views, col = views, planes = dense && L->planes_valid, pairs = dense && L->pairs_valid && pairs_kept(L, L->nnz);
     L->planes_valid = planes;
-    if (dense && (L->planes_y || (views && !(L->row_walked && L->col_walked)))) {
+    L->pairs_valid = pairs;
+    if (dense && (L->planes_y || L->pairs_y.blocks || (views && !(L->row_walked && L->col_walked)))) {
         // Views that nothing has walked are left out, since the dense copy holds the values for their first walk.
         // A recording refreshes every built view and changes no flag of theirs: its replays come at any time, between
         // calls that walk a view for the first time, and it has not run yet.  It takes the planes along if a product has read them
@@ -1194,6 +1214,9 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
         if (capture != hipStreamCaptureStatusNone) {
             planes = !L->planes_missed && (L->planes_used || (L->planes_y && L->hint_act == MST_BF16));
             L->planes_missed |= L->planes_y && !planes;
+            // (the packed pairs likewise; products that would read them go to the dense kernels once they are missed)
+            pairs = pairs_kept(L, L->nnz);
+            L->pairs_missed |= L->pairs_y.blocks && !pairs;
         } else if (views) {
             row = L->row_walked;
             col = L->col_walked;
@@ -1204,7 +1227,9 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     const int rc = refresh_views(L, row, col, dense, false, s);
     // (made again from the dense copy: 8.5 us at 1024 x 4096.  Scattering 5 % of the positions into them took 11, 10 % of 1280 x
     // 5120 took 30: four stores of two bytes per value, two of them far apart.)
-    return rc == MST_OK && planes ? make_planes(L, s) : rc;
+    if (rc != MST_OK) return rc;
+    const int rcp = planes ? make_planes(L, s) : MST_OK;
+    return rcp == MST_OK && pairs ? make_pairs(L, s) : rcp;
 }
 
 int mst_layer_indices(const mst_layer_t* L, int32_t* flat_dev, mst_stream_t stream) {
