@@ -33,7 +33,12 @@
 //   - the weight goes through one v_mov_b32_dpp: a plain v_fmac_f32 issues in 3.4 clocks, one with a
 //     DPP operand in 5.2;
 //   - the wavefronts' octets are dealt in a snake over the blocks of the slab, so that the longest
-//     octets of different blocks (rows are ranked by length in a block) meet in no wavefront.
+//     octets of different blocks (rows are ranked by length in a block) meet in no wavefront;
+//   - a wavefront's priority falls with the octets it has left.  With equal ones the oldest wavefront of a SIMD unit is
+//     served first: of a chunk's 7 us at 1280 -> 5120, density 0.02, the last wavefront walked 2.6 us longer than the mean
+//     one, alone on its unit and waiting for its own reads, with the priorities 0.9 us.  Y there 118 -> 113, at density 0.05
+//     183 -> 172, dX 168 -> 158.  Where an octet is twice as long (both gradients) the last two octets count in halves:
+//     199 -> 190 and 374 -> 361 (in whole octets 192 and 363);
 // Measured (us; before = 128-token tiles over 128-index chunks, 8192 tokens, density 0.02):
 //   Y of 1280 -> 5120: 168 -> 118;  dX of it: 210 -> 104;  both gradients of it: 300 -> 190.
 #pragma once
@@ -241,7 +246,10 @@ __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(std::make_integer_sequence<int, N>{}, f); }
 
-// lds: at least max(KC * 256, 2 * STAGE_BYTES) bytes
+// row blocks of B that pass through LDS between two barriers of the prologue
+constexpr int walk_areas(int q) { return q <= 5 ? q : 3; }
+
+// lds: at least max(KC * 256, 2 * STAGE_BYTES) bytes, with DW max(KC * 256, walk_areas(Q) * STAGE_BYTES)
 template <typename TIn, int Q, bool OUT, bool DW>
 __device__ __forceinline__ void walk_body(const WalkSide& sd, const WalkArgs& wa, char* lds) {
     constexpr int NI = (KCMAX / 4 + 63) / 64;        // items of 4 tokens x 4 indices a thread stages per chunk
@@ -315,33 +323,49 @@ __device__ __forceinline__ void walk_body(const WalkSide& sd, const WalkArgs& wa
     const std::integral_constant<int, NI> i_all;
 
     // ---- DW: B of this lane's tokens for the row of each of its octets, through LDS so that the global
-    // reads are contiguous runs (two staging areas used in turn); all lane groups of a spread octet
-    // work on the row of lane group 0
+    // reads are contiguous runs; all lane groups of a spread octet work on the row of lane group 0.  The loads
+    // of all blocks go out together and as many blocks as the LDS holds pass between two barriers: block by block
+    // the prologue waited for memory Q times (dW of 1024 -> 4096, 4099 tokens, density 0.04, bf16: 94 -> 84 us).
     float xr[DW ? Q : 1][8];
     if constexpr (DW) {
+        constexpr int AREAS = walk_areas(Q), NB4 = WT * RB / 4 / WALK_NT;
         const TIn* __restrict__ B = static_cast<const TIn*>(sd.B);
         const uint32_t ldb = (uint32_t)R * (uint32_t)sizeof(TIn);
+        int rm[Q];
+        float4 bq[Q][NB4];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) rm[q] = sd.rowmap[((b0 + q) * OPB + octet_of(wave, q)) * OCT + g];
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
             const int row0 = (b0 + q) * RB;
-            char* half = lds + (q & 1) * STAGE_BYTES;
-            if (row0 < R) {
-                const uint32_t end = rows * ldb - (uint32_t)row0 * (uint32_t)sizeof(TIn);
-                const __amdgpu_buffer_rsrc_t rs = buffer_of(B + (int64_t)t0 * R + row0, end);
+            // (a block past the last row: no accesses, zeros)
+            const uint32_t end = row0 < R ? rows * ldb - (uint32_t)row0 * (uint32_t)sizeof(TIn) : 0u;
+            const __amdgpu_buffer_rsrc_t rs = buffer_of(B + (int64_t)t0 * R + (row0 < R ? row0 : 0), end);
 #pragma unroll
-                for (int it = 0; it < WT * RB / 4 / WALK_NT; ++it) {
-                    const int item = it * WALK_NT + tid, tl = item / (RB / 4), j = item % (RB / 4);
-                    *reinterpret_cast<float4*>(half + stage_unit(tl, j)) =
-                        buffer_quad<TIn>(rs, (uint32_t)tl * ldb + (uint32_t)(4 * j) * (uint32_t)sizeof(TIn), end, (R & 1) == 0);
-                }
+            for (int it = 0; it < NB4; ++it) {
+                const int item = it * WALK_NT + tid, tl = item / (RB / 4), j = item % (RB / 4);
+                bq[q][it] = buffer_quad<TIn>(rs, (uint32_t)tl * ldb + (uint32_t)(4 * j) * (uint32_t)sizeof(TIn), end, (R & 1) == 0);
             }
-            __syncthreads();
-            const int* rmq = sd.rowmap + (int64_t)((b0 + q) * OPB + octet_of(wave, q)) * OCT;
-            const int rm = rmq[g], rm0 = rmq[0];
-            const int rl = (((rm & SPREAD_FLAG) ? rm0 : rm) & ~SPREAD_FLAG) - row0;
+        }
 #pragma unroll
-            for (int e = 0; e < 8; ++e)
-                xr[q][e] = row0 < R ? *reinterpret_cast<const float*>(half + stage_byte(lane_token(s, g, e), rl)) : 0.f;
+        for (int q0 = 0; q0 < Q; q0 += AREAS) {
+            if (q0 > 0) __syncthreads();
+#pragma unroll
+            for (int q = q0; q < min(Q, q0 + AREAS); ++q)
+#pragma unroll
+                for (int it = 0; it < NB4; ++it) {
+                    const int item = it * WALK_NT + tid, tl = item / (RB / 4), j = item % (RB / 4);
+                    *reinterpret_cast<float4*>(lds + (q - q0) * STAGE_BYTES + stage_unit(tl, j)) = bq[q][it];
+                }
+            __syncthreads();
+#pragma unroll
+            for (int q = q0; q < min(Q, q0 + AREAS); ++q) {
+                const int row = (rm[q] & SPREAD_FLAG) ? __builtin_amdgcn_readfirstlane(rm[q]) : rm[q];
+                const int rl = (row & ~SPREAD_FLAG) - (b0 + q) * RB;
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    xr[q][e] = *reinterpret_cast<const float*>(lds + (q - q0) * STAGE_BYTES + stage_byte(lane_token(s, g, e), rl & (RB - 1)));
+            }
         }
     }
     float acc[OUT ? Q : 1][8];
@@ -381,6 +405,12 @@ __device__ __forceinline__ void walk_body(const WalkSide& sd, const WalkArgs& wa
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < Q; ++q) {
+            // (see the head: the fewer octets are left, the less priority a wavefront has)
+            constexpr bool HALVES = OUT && DW;
+            if (HALVES ? q < Q - 1 : q < Q - 3) __builtin_amdgcn_s_setprio(3);
+            else if (!HALVES && q == Q - 3) __builtin_amdgcn_s_setprio(2);
+            else if (HALVES || q == Q - 2) __builtin_amdgcn_s_setprio(1);
+            else __builtin_amdgcn_s_setprio(0);
             int p = pb[q];
             const int pend = pe[q];
             const int after = from[q + 1];                    // first batch of what is walked next
@@ -437,7 +467,10 @@ __device__ __forceinline__ void walk_body(const WalkSide& sd, const WalkArgs& wa
                     }
                 });
             };
+            const int mid = (p + pend) >> 1;
             while (p + 4 <= pend) {
+                if (HALVES && q == Q - 2 && p >= mid) __builtin_amdgcn_s_setprio(2);
+                if (HALVES && q == Q - 1 && p >= mid) __builtin_amdgcn_s_setprio(0);
                 batch(std::integral_constant<int, 4>{}, p + 4 < pend ? p + 4 : after);
                 p += 4;
             }

@@ -35,7 +35,7 @@ __global__ __launch_bounds__(WALK_NT) void k_walk_dw(const WalkSide row, const W
     walk_body<TIn, Q, false, true>(sd, wa, walk_lds);
 }
 
-inline unsigned walk_lds_bytes(int KC) { return (unsigned)std::max(KC * WT * 4, 2 * STAGE_BYTES); }
+inline unsigned walk_lds_bytes(int KC, int areas) { return (unsigned)std::max(KC * WT * 4, areas * STAGE_BYTES); }
 inline unsigned walk_grid(int ntile, int nslab) { return 8u * (unsigned)cdiv((int64_t)ntile * nslab, 8); }
 
 template <typename TIn, int Q, bool OUT, bool DW>
@@ -44,7 +44,7 @@ static int launch_q(const WalkSide& sd, const WalkArgs& wa, int nsplit, hipStrea
     static uint64_t done = 0;
     const int rc = allow_lds(reinterpret_cast<const void*>(&k_walk<TIn, Q, OUT, DW>), KCMAX * WT * 4, done);
     if (rc != MST_OK) return rc;
-    k_walk<TIn, Q, OUT, DW><<<dim3(walk_grid(wa.ntile, sd.nslab), (unsigned)nsplit), WALK_NT, walk_lds_bytes(sd.KC), s>>>(WalkParams{sd, wa});
+    k_walk<TIn, Q, OUT, DW><<<dim3(walk_grid(wa.ntile, sd.nslab), (unsigned)nsplit), WALK_NT, walk_lds_bytes(sd.KC, DW ? std::max(2, walk_areas(Q)) : 2), s>>>(WalkParams{sd, wa});
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
@@ -77,7 +77,7 @@ static int launch_dw_q(const WalkSide& row, const WalkSide& col, const WalkArgs&
     static uint64_t done = 0;
     const int rc = allow_lds(reinterpret_cast<const void*>(&k_walk_dw<TIn, Q>), KCMAX * WT * 4, done);
     if (rc != MST_OK) return rc;
-    k_walk_dw<TIn, Q><<<walk_grid(wa.ntile, std::max(row.nslab, col.nslab)), WALK_NT, walk_lds_bytes(std::max(row.KC, col.KC)), s>>>(
+    k_walk_dw<TIn, Q><<<walk_grid(wa.ntile, std::max(row.nslab, col.nslab)), WALK_NT, walk_lds_bytes(std::max(row.KC, col.KC), walk_areas(Q)), s>>>(
         row, col, wa, drive);
     MST_LAUNCH_CHECK();
     return MST_OK;
