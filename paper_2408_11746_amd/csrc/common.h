@@ -203,7 +203,7 @@ struct Workspace {
     int* segcnt[2] = {nullptr, nullptr};   // active count per (sub-chunk, row) of the row view and of the col view
     int* qlen[2] = {nullptr, nullptr};     // pairs per octet segment of either
     int* rowcnt = nullptr;     // [O + 1]
-    uint32_t* blk = nullptr;   // per-block tie counts: [blocks(N) + 1] of the growth selections, then [blocks(cap) + 1] of the prune selection
+    uint32_t* blk = nullptr;   // tie counts of the flag pass's blocks: [blocks(N) + 1] of the gradient growth, then [blocks(cap) + 1] of the prune selection
     uint64_t* sel_state = nullptr;   // [SEL_STATES][SEL_STATE_WORDS] radix-select state + histogram
     float* gemm = nullptr;     // [GEMM_WS_SPLITS * N] split-k partial outputs of the dense GEMM
     size_t gemm_floats = 0;
@@ -214,10 +214,11 @@ struct Workspace {
 Workspace carve_workspace(void* base, int O, int I, int64_t cap, int T);
 
 constexpr int GEMM_WS_SPLITS = 8;
-constexpr int SELECT_BLOCK = 2048;   // elements per block in the ordered tie pass
-constexpr int SEL_DIGIT_BITS = 8;                        // radix-select digit
+constexpr int SELECT_BLOCK = 2048;   // a block of the flag pass has more elements than this
+constexpr int SEL_DIGIT_BITS = 8;                        // digit of the end of the random selection
 constexpr int SEL_BINS = 1 << SEL_DIGIT_BITS;
-constexpr int SEL_STATE_WORDS = 8 + 4096 / 2;            // one selection: 8 control words + up to 4096 uint32 histogram bins
+constexpr int SEL_CTRL = 16;
+constexpr int SEL_STATE_WORDS = SEL_CTRL + 7168 / 2;     // one selection: control words + the uint32 histograms of its digits
 constexpr int SEL_STATES = 3;                            // prune, gradient growth, random growth
 
 View view_shape(int R, int K, int64_t cap);
