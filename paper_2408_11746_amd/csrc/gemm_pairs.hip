@@ -300,19 +300,12 @@ __device__ __forceinline__ void static_for(F&& f) { static_for_impl(std::make_in
 
 // NTK: tiles of 32 tokens of a wavefront; AHEAD: steps between the load of an operand and its way to LDS, a register set each
 template <bool BF, int NTK, int AHEAD>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_gemm_pairs(const char* __restrict__ A, const PairsView v, float* __restrict__ C, int T) {
+__device__ __forceinline__ void pairs_tile(const char* __restrict__ A, const PairsView& v, float* __restrict__ C, int T, int t0, int band, char* const lds) {
     constexpr int TOK = 64 * NTK, PLANE = TOK * 64, XST = (BF ? 2 : 4) * PLANE, STAGE = XST + PK_BLOCK;
     constexpr int LINES = BF ? 1 : 2, NX = NTK * LINES;           // 128-byte lines of a row in a step; 16-byte pieces of a thread
-    extern __shared__ __attribute__((aligned(16))) char lds[];
     uint16_t* const list = reinterpret_cast<uint16_t*>(lds + 2 * STAGE);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int gm = (T + TOK - 1) / TOK, gn = v.bands, ntiles = gm * gn, Q = (ntiles + 7) >> 3;
-    const int tile_id = (int)(blockIdx.x & 7) * Q + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= Q || tile_id >= ntiles) return;
-    int mi, band;
-    tile_coords(tile_id, gm, gn, mi, band);
-    const int t0 = mi * TOK, nk = v.nk;
+    const int nk = v.nk;
     // steps of the second kind, in ascending order
     const uint32_t* const flags = v.flags + (int64_t)band * nk;
     int nsec = 0;
@@ -552,24 +545,69 @@ void k_gemm_pairs(const char* __restrict__ A, const PairsView v, float* __restri
     }
 }
 
-template <bool BF, int NTK, int AHEAD>
-static int launch_pairs(const void* A, const PairsView& v, float* C, int T, hipStream_t s) {
+// `full` token tiles of 64 NTK tokens, the tokens behind them in tiles of 64 (TAIL)
+template <bool BF, int NTK, int AHEAD, bool TAIL>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_gemm_pairs(const char* __restrict__ A, const PairsView v, float* __restrict__ C, int T, int full) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int xcd = (int)(blockIdx.x & 7), at = (int)(blockIdx.x >> 3);
+    const int nfull = full * v.bands, Q = (nfull + 7) >> 3;
+    int mi, band;
+    if (at < Q) {
+        const int id = xcd * Q + at;
+        if (id >= nfull) return;
+        tile_coords(id, full, v.bands, mi, band);
+        pairs_tile<BF, NTK, AHEAD>(A, v, C, T, mi * 64 * NTK, band, lds);
+    } else if constexpr (TAIL) {
+        const int t1 = full * 64 * NTK, rest = (T - t1 + 63) / 64, ntail = rest * v.bands, QT = (ntail + 7) >> 3;
+        const int id = xcd * QT + at - Q;
+        if (at - Q >= QT || id >= ntail) return;
+        tile_coords(id, rest, v.bands, mi, band);
+        pairs_tile<BF, 1, AHEAD>(A, v, C, T, t1 + mi * 64, band, lds);
+    }
+}
+
+template <bool BF, int NTK, int AHEAD, bool TAIL>
+static int launch_pairs(const void* A, const PairsView& v, float* C, int T, int full, hipStream_t s) {
     constexpr int STAGE = 64 * NTK * 64 * (BF ? 2 : 4) + PK_BLOCK;
     const unsigned bytes = 2 * STAGE + (unsigned)align_up(2 * (size_t)v.nk, 16);
     static uint64_t done = 0;
-    const int rc = allow_lds(reinterpret_cast<const void*>(&k_gemm_pairs<BF, NTK, AHEAD>), 2 * STAGE + 4096, done);
+    const int rc = allow_lds(reinterpret_cast<const void*>(&k_gemm_pairs<BF, NTK, AHEAD, TAIL>), 2 * STAGE + 4096, done);
     if (rc != MST_OK) return rc;
-    const int64_t tiles = cdiv(T, 64 * NTK) * v.bands;
-    k_gemm_pairs<BF, NTK, AHEAD><<<(unsigned)(8 * cdiv(tiles, 8)), 512, bytes, s>>>(static_cast<const char*>(A), v, C, T);
+    const int64_t tail = full * 64 * NTK < T ? cdiv(T - full * 64 * NTK, 64) : 0;
+    const int64_t per_xcd = cdiv((int64_t)full * v.bands, 8) + cdiv(tail * v.bands, 8);
+    k_gemm_pairs<BF, NTK, AHEAD, TAIL><<<(unsigned)(8 * per_xcd), 512, bytes, s>>>(static_cast<const char*>(A), v, C, T, full);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
 
-// C [T x R] = A [T x K] S^T, S given by its packed pairs; tokens: of a workgroup's tile
+// Microseconds of an fp32 product with `full` token tiles of 128, the rest in tiles of 64.  (Per step of 64 k: 1.52 with 128 tokens
+// on every CU, 1.0 on a few, 0.87 and 0.75 with 64: the weights of a step cost the same for either.)
+static double pairs_f32_us(int T, int R, int K, int full, double second) {
+    const int64_t bands = cdiv(R, PB_ROWS), rest = std::max(0, T - 128 * full);
+    const int64_t Q = cdiv(full * bands, 8), QT = cdiv(cdiv(rest, 64) * bands, 8);
+    return (xcd_rounds(Q, 32, 8, 1.52, 1.0) + xcd_rounds(QT, 32, 8, 0.87, 0.75)) * (K / PK_STEP) * (1.0 + 0.8 * second) +
+           (double)cdiv(Q, 32) * 8.0 + (double)cdiv(QT, 32) * 5.0;
+}
+
+// Token tiles of 128 of an fp32 product.  A CU holds one workgroup, so 320 tiles are two rounds, the second one a quarter full:
+// the tokens behind the last full round go in tiles of 64, twice as many CUs for them, where that is the shorter way (5120
+// -> 1280, 8192 tokens: 212 -> 186 us; 3840 -> 1280: 161 -> 141; all of them where 128 would leave half of the CUs idle: 3072 -> 768,
+// 2048 tokens: 57 -> 41).
+static int pairs_full_tiles(int T, int R, int K) {
+    const int all = (int)cdiv(T, 128);
+    if (gemm_pairs_forced()) return T % 3 == 0 ? all : T % 3 == 1 ? 0 : all / 2;      // (pinned: every kind)
+    const int bands = (int)cdiv(R, PB_ROWS), whole = (int)((int64_t)all * bands / 256 * 256 / bands);
+    return pairs_f32_us(T, R, K, whole, 0.0) < pairs_f32_us(T, R, K, all, 0.0) ? whole : all;
+}
+
+// C [T x R] = A [T x K] S^T, S given by its packed pairs; tokens: of a workgroup's tile (fp32: pairs_full_tiles)
 int gemm_pairs(const void* A, mst_dtype act, const PairsView& v, float* C, int T, int tokens, hipStream_t s) {
     if (v.R % 4 || v.K % PK_STEP) return MST_ERR_ARG;
-    if (act == MST_F32) return launch_pairs<false, 2, 2>(A, v, C, T, s);
-    return tokens == 128 ? launch_pairs<true, 2, 2>(A, v, C, T, s) : tokens == 192 ? launch_pairs<true, 3, 2>(A, v, C, T, s) : launch_pairs<true, 4, 1>(A, v, C, T, s);
+    if (act == MST_F32) return launch_pairs<false, 2, 2, true>(A, v, C, T, pairs_full_tiles(T, v.R, v.K), s);
+    const int full = (int)cdiv(T, tokens);
+    return tokens == 128 ? launch_pairs<true, 2, 2, false>(A, v, C, T, full, s) : tokens == 192 ? launch_pairs<true, 3, 2, false>(A, v, C, T, full, s)
+                                                                                : launch_pairs<true, 4, 1, false>(A, v, C, T, full, s);
 }
 
 // ------------------------------------------------------------------ choice
@@ -598,10 +636,10 @@ int measure_pairs(mst_layer* L, hipStream_t s) {
 }
 
 static double pairs_us(mst_dtype act, int T, int R, int K, int tokens, double second) {
+    if (act == MST_F32) return pairs_f32_us(T, R, K, pairs_full_tiles(T, R, K), second);
     const int64_t Q = cdiv(cdiv(T, tokens) * cdiv(R, PB_ROWS), 8);
     double full, lone, ends;
-    if (act == MST_F32) full = 1.52, lone = 1.0, ends = 8.0;
-    else if (tokens == 256) full = 1.95, lone = 1.3, ends = 9.0;
+    if (tokens == 256) full = 1.95, lone = 1.3, ends = 9.0;
     else if (tokens == 192) full = 1.5, lone = 0.95, ends = 7.0;
     else full = 1.2, lone = 0.8, ends = 5.0;
     return xcd_rounds(Q, 32, 8, full, lone) * (K / PK_STEP) * (1.0 + 0.8 * second) + (double)cdiv(Q, 32) * ends;
