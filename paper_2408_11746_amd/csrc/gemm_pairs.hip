@@ -109,9 +109,11 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
         }
     }
     // rows past the end: no weights (whatever is there reaches outputs that are not stored), selectors as of empty quads, no flags
-    if (tid == 0) v.flags[at] = 0;
-    if (tid == 0 && blockIdx.x == 0) *y.count = 0;
+    // (nothing else of the flags: a product that reads the same layer on another stream may be under way, and the packing behind this
+    // launch writes what is there already)
     const int missing = (band + 1) * PB_ROWS - v.R;
+    if (tid < 4 && 64 * tid >= PB_ROWS - missing) reinterpret_cast<uint8_t*>(v.flags + at)[tid] = 0;
+    if (tid == 0 && blockIdx.x == 0) *y.count = 0;
     if (missing > 0)
         for (int e = tid; e < 4 * missing; e += 256) {       // [first, second step][32 k][missing rows]
             const int row = PB_ROWS - missing + e % missing, ss = e / missing;

@@ -841,25 +841,26 @@ __global__ void k_scatter_dense(const float* __restrict__ vals, const int* __res
     if (k == 0 && dense_live) *dense_live = 1;
 }
 
-// W . M as a dense array and the mask beside it (either may be null), one launch.  The first blocks own up to EXPORT_COLS
-// columns of a row each: the row's active values go to their places in a zeroed run of LDS and the run is written once,
-// where a fill of the array with a scatter of single values behind it wrote every line twice.  The other blocks copy 4 KB of
+// W . M as a dense array and the mask beside it (either may be null), one launch.  The first blocks own up to EXPORT_RUN
+// positions each, `rows` whole rows or a part of one: the active values go to their places in a zeroed run of LDS and the run is written
+// once, where a fill of the array with a scatter of single values behind it wrote every line twice.  The other blocks copy 4 KB of
 // the mask each.  (Four layers of a GPT-2-small block, W and M: 72 us with a fill, a scatter and a copy for each, 30 like this; GPT-2-large: 91, 45.)
-constexpr int EXPORT_COLS = 4096;
+constexpr int EXPORT_RUN = 4096;
 __global__ __launch_bounds__(256) void k_export_dense(const float* __restrict__ vals, const int* __restrict__ flat,
                                                       const int* __restrict__ rowptr, const uint8_t* __restrict__ mask,
-                                                      int64_t nnz, int64_t N, int I, int parts, unsigned row_blocks,
+                                                      int64_t nnz, int64_t N, int O, int I, int rows, int parts, unsigned run_blocks,
                                                       float* __restrict__ W, uint8_t* __restrict__ M, int* __restrict__ dense_live) {
-    __shared__ __attribute__((aligned(16))) float run[EXPORT_COLS];
+    __shared__ __attribute__((aligned(16))) float run[EXPORT_RUN];
     const int tid = threadIdx.x;
-    if (blockIdx.x >= row_blocks) {
-        const int64_t p = ((int64_t)(blockIdx.x - row_blocks) * 256 + tid) * 16;
+    if (blockIdx.x >= run_blocks) {
+        const int64_t p = ((int64_t)(blockIdx.x - run_blocks) * 256 + tid) * 16;
         if (p + 16 <= N) *reinterpret_cast<uint4*>(M + p) = *reinterpret_cast<const uint4*>(mask + p);
         else for (int64_t i = p; i < N; ++i) M[i] = mask[i];
         return;
     }
-    const int r = (int)(blockIdx.x / (unsigned)parts), c0 = (int)(blockIdx.x % (unsigned)parts) * EXPORT_COLS, n = min(I - c0, EXPORT_COLS);
-    const int k0 = nnz > 0 ? rowptr[r] : 0, k1 = nnz > 0 ? rowptr[r + 1] : 0;
+    const int r = (int)(blockIdx.x / (unsigned)parts) * rows, r1 = min(r + rows, O), c0 = (int)(blockIdx.x % (unsigned)parts) * EXPORT_RUN;
+    const int n = min((r1 - r) * I - c0, EXPORT_RUN);
+    const int k0 = nnz > 0 ? rowptr[r] : 0, k1 = nnz > 0 ? rowptr[r1] : 0;
     for (int i = 4 * tid; i < n; i += 1024) *reinterpret_cast<float4*>(run + i) = make_float4(0.f, 0.f, 0.f, 0.f);
     __syncthreads();
     const int64_t base = (int64_t)r * I + c0;
@@ -868,11 +869,9 @@ __global__ __launch_bounds__(256) void k_export_dense(const float* __restrict__ 
         if (at >= 0 && at < n) run[at] = vals[k];
     }
     __syncthreads();
-    if ((I & 3) == 0) {
-        for (int i = 4 * tid; i < n; i += 1024) *reinterpret_cast<float4*>(W + base + i) = *reinterpret_cast<const float4*>(run + i);
-    } else {
-        for (int i = tid; i < n; i += 256) W[base + i] = run[i];
-    }
+    const int n4 = (base & 3) == 0 ? n & ~3 : 0;
+    for (int i = 4 * tid; i < n4; i += 1024) *reinterpret_cast<float4*>(W + base + i) = *reinterpret_cast<const float4*>(run + i);
+    for (int i = n4 + tid; i < n; i += 256) W[base + i] = run[i];
     if (blockIdx.x == 0 && tid == 0 && dense_live) *dense_live = 1;
 }
 
@@ -994,11 +993,14 @@ int build_canonical(const BuildItem* items, int n, hipStream_t s) {
 
 // W . M to W and / or the mask to M (dense_live: null where W is not the layer's own dense copy)
 static int export_dense(const mst_layer* L, float* W, uint8_t* M, int* dense_live, hipStream_t s) {
-    const int parts = (int)cdiv(L->I, EXPORT_COLS);
-    const unsigned row_blocks = W ? (unsigned)(L->O * parts) : 0u, mask_blocks = M ? (unsigned)cdiv(L->N, 4096) : 0u;
-    if (row_blocks + mask_blocks == 0) return MST_OK;
-    k_export_dense<<<row_blocks + mask_blocks, 256, 0, s>>>(L->vals, L->flat, L->rowptr, L->mask, L->nnz, L->N, L->I, parts, row_blocks,
-                                                            W, M, dense_live);
+    // Rows of a run: one, several where a layer has far more rows than the chip holds blocks, then whole fours so that runs begin on 16 bytes
+    const int parts = (int)cdiv(L->I, EXPORT_RUN);
+    int rows = std::max(1, std::min(EXPORT_RUN / L->I, L->O / 1024));
+    if (rows >= 4) rows &= ~3;
+    const unsigned run_blocks = W ? (unsigned)(cdiv(L->O, rows) * parts) : 0u, mask_blocks = M ? (unsigned)cdiv(L->N, 4096) : 0u;
+    if (run_blocks + mask_blocks == 0) return MST_OK;
+    k_export_dense<<<run_blocks + mask_blocks, 256, 0, s>>>(L->vals, L->flat, L->rowptr, L->mask, L->nnz, L->N, L->O, L->I, rows, parts,
+                                                            run_blocks, W, M, dense_live);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }

@@ -1,5 +1,5 @@
-"""mst_layer_export_dense against the arrays that the layer was loaded from: rows shorter and longer than the run of columns a
-workgroup owns (4096), row lengths that are no multiple of four, empty and full rows, either output alone."""
+"""mst_layer_export_dense against the arrays that the layer was loaded from: rows shorter and longer than the run of positions a
+workgroup owns (4096), layers of so many rows that it owns several, row lengths that are no multiple of four, empty and full rows, either output alone."""
 import pytest
 import torch
 
@@ -8,7 +8,8 @@ from paper_2408_11746_amd import binding as mst
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("O,I", [(1, 1), (5, 7), (64, 64), (3, 4095), (3, 4096), (3, 4097), (2, 8201), (1283, 515), (4, 12288)])
+@pytest.mark.parametrize("O,I", [(1, 1), (5, 7), (64, 64), (3, 4095), (3, 4096), (3, 4097), (2, 8201), (1283, 515), (4, 12288), (3073, 515), (2051, 768),
+                                 (9000, 7), (65535, 1)])
 @pytest.mark.parametrize("density", [0.0, 0.03, 1.0])
 def test_export(O, I, density):
     gen = torch.Generator().manual_seed(O * 131 + I)
