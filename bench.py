@@ -207,19 +207,31 @@ def split_gemm_applies(M, N, K):
     return M % 128 == 0 and N % 128 == 0 and K % 64 == 0
 
 
-def dense_gemm_roofline(flops, ms, act, M, N, K, bf16_products=1.0):
+PAIRS_DENSITY = 0.12     # dense-path Y and dX up to here run on the 2-of-4 sparse matrix instructions (gemm_pairs.hip)
+
+
+def on_pairs(density, O, I):
+    return density <= PAIRS_DENSITY and O % 64 == 0 and I % 64 == 0
+
+
+def dense_gemm_roofline(flops, ms, act, M, N, K, bf16_products=1.0, executed=1.0):
     """A dense contraction: the matrix cores' peak for the dtype of the MFMA instructions that
     run.  fp32 operands on whole tiles run as 3 bf16 MFMA products per term: executed flops =
     3 x the product's 2 M N K, against the bf16 peak.  With bfloat16 activations the weight
-    gradient is one product per term, Y and dX (fp32 weights split hi + lo) two."""
+    gradient is one product per term, Y and dX (fp32 weights split hi + lo) two.  `executed`: share of
+    those flops that is multiplied at all, one half on the 2-of-4 sparse matrix instructions."""
     tf = flops / ms / 1e9
+    half = "" if executed == 1.0 else ", %.2g of it multiplied: 2-of-4 sparse MFMA" % executed
     if act == "bf16":
-        return dict(bound="mfma", achieved=round(bf16_products * tf, 2), peak=MFMA_BF16_PEAK_TFLOPS, unit="TFLOP/s",
-                    frac=round(bf16_products * tf / MFMA_BF16_PEAK_TFLOPS, 4),
-                    mfma_dtype="bf16 (%.3g MFMA products per term)" % bf16_products)
+        run = executed * bf16_products * tf
+        return dict(bound="mfma", achieved=round(run, 2), peak=MFMA_BF16_PEAK_TFLOPS, unit="TFLOP/s",
+                    frac=round(run / MFMA_BF16_PEAK_TFLOPS, 4),
+                    mfma_dtype="bf16 (%.3g MFMA products per term%s)" % (bf16_products, half))
     if split_gemm_applies(M, N, K):
-        return dict(bound="mfma", achieved=round(3 * tf, 2), peak=MFMA_BF16_PEAK_TFLOPS, unit="TFLOP/s",
-                    frac=round(3 * tf / MFMA_BF16_PEAK_TFLOPS, 4), mfma_dtype="bf16 (fp32 operands split hi + lo, 3 products)",
+        run = executed * 3 * tf
+        return dict(bound="mfma", achieved=round(run, 2), peak=MFMA_BF16_PEAK_TFLOPS, unit="TFLOP/s",
+                    frac=round(run / MFMA_BF16_PEAK_TFLOPS, 4),
+                    mfma_dtype="bf16 (fp32 operands split hi + lo, 3 products%s)" % half,
                     fp32_equivalent_tflops=round(tf, 2), frac_of_fp32_mfma_peak=round(tf / MFMA_FP32_PEAK_TFLOPS, 4))
     return dict(bound="mfma", achieved=round(tf, 2), peak=MFMA_FP32_PEAK_TFLOPS, unit="TFLOP/s",
                 frac=round(tf / MFMA_FP32_PEAK_TFLOPS, 4), mfma_dtype="fp32")
@@ -235,7 +247,7 @@ def roofline_of(row, L, act, kernel, traffic_cfg):
         if row.get("path") == "dense-mfma":
             mnk = row.get("dense_mnk") or ((L.T, L.O, L.I) if row["call"] == "fwd" else (L.T, L.I, L.O))
             roof = dense_gemm_roofline(row["dense_flops"], row["avg_ms"], act, *mnk,
-                                       bf16_products=row.get("bf16_products", 1.0))
+                                       bf16_products=row.get("bf16_products", 1.0), executed=row.get("executed", 1.0))
         elif t_hbm >= t_alu:
             roof = dict(bound="hbm", achieved=row["hbm_gbs"], peak=HBM_PEAK_GBS, unit="GB/s",
                         frac=round(row["hbm_gbs"] / HBM_PEAK_GBS, 4))
@@ -432,6 +444,7 @@ def run_block(args, name, mst, synth, torch, lds_peak, with_cpu_baseline):
     spmm_k = "k_walk<OUT> (launch shape chosen per call) + k_heavy_fwd after the forward (heavy rows as a dense product; returns at once without any)"
     gemm_k = "k_gemm_split256 / k_gemm_split_n160 / k_gemm_split (fp32 operands as bf16 hi + lo)" if act == "f32" else \
         "k_gemm_planes (bfloat16 activations x fp32 weights as bf16 hi + lo, 2 products per term)"
+    gemm_k += ", up to a density of about a tenth k_gemm_pairs (the same parts on v_smfmac_f32_32x32x32_bf16)"
     wgrad_dense_k = ("k_gemm_wgrad16" if act == "bf16" else "k_gemm_split256<TN> / k_gemm_split<TN>") + " + k_gather_flat"
     kernel = {"fwd": gemm_k if dp else spmm_k,
               "bwd_input": gemm_k if dense_dx[dL.name] else spmm_k,
@@ -445,6 +458,10 @@ def run_block(args, name, mst, synth, torch, lds_peak, with_cpu_baseline):
         drow["dense_mnk"] = {"fwd": (T, dL.O, dL.I), "bwd_input": (T, dL.I, dL.O)}.get(drow["call"], (dL.O, dL.I, T))
         # bfloat16 activations: Y, dX = 2 MFMA products per term, weight gradient 1, the one-call backward both
         drow["bf16_products"] = {"fwd": 2.0, "bwd_input": 2.0, "bwd_weight": 1.0, "bwd": 1.5}[drow["call"]]
+        if on_pairs(density, dL.O, dL.I):
+            # the weight gradient multiplies everything: of the one-call backward's products one (bf16) or three (fp32) per term
+            drow["executed"] = {"fwd": 0.5, "bwd_input": 0.5, "bwd_weight": 1.0,
+                                "bwd": 2.0 / 3.0 if act == "bf16" else 0.75}[drow["call"]]
     roof = roofline_of(drow, dL, act, kernel, name)
 
     out = {
@@ -782,7 +799,8 @@ def run_sweep(args, mst, synth, torch, lds_peak, with_cpu_baseline):
                 product_row_numbers(row, ms, by, L.flops_product(nnz), lds_bytes, lds_peak)
                 if dense_path:
                     mnk = (T, L.O, L.I) if call == "fwd" else (T, L.I, L.O)
-                    r = dense_gemm_roofline(L.flops_dense_grad(), ms, "f32", *mnk)
+                    r = dense_gemm_roofline(L.flops_dense_grad(), ms, "f32", *mnk,
+                                            executed=0.5 if on_pairs(nnz / (L.O * L.I), L.O, L.I) else 1.0)
                     row.update(dense_flops=L.flops_dense_grad(), mfma_tflops=r["achieved"], mfma_frac=r["frac"],
                                mfma_dtype=r["mfma_dtype"])
                 calls.append(row)
@@ -826,7 +844,7 @@ def run_sweep(args, mst, synth, torch, lds_peak, with_cpu_baseline):
                   "v_mfma_f32_32x32x16_bf16 per term) + k_splitk_reduce4 (ordered sum of its split partial outputs)")
     elif drow.get("path") == "dense-mfma":
         kernel = ("k_gemm_split256 (masked dense product, bf16 hi + lo split on v_mfma_f32_32x32x16_bf16; preceded by the "
-                  "scatter of the dense weight copy after an update)")
+                  "scatter of the dense weight copy after an update) or, at a density of about a tenth, k_gemm_pairs")
     else:
         kernel = "k_walk<OUT> (launch shape chosen per call)"
     roof = roofline_of(drow, dL, "f32", kernel, "C5")
