@@ -70,7 +70,8 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t x) {
     return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
 }
 
-// Block = (view, band, step); y first.
+// Block = (view, band, step); y first.  Bound by latencies: the mask's lines (all of a thread's loads go out together; eight pairs of them at a
+// time and counts looked up lane by lane: 28 us at 5120 x 1280, so 21), then the search of one wavefront.
 __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__ mask, int I, const PairsView y, const PairsView x) {
     constexpr int NP = PK_PAIRS, NQ = NP / 2;
     __shared__ unsigned long long g1[NP][4], g2[NP][4];
@@ -102,11 +103,12 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
         }
     } else {
         const uint8_t* m = mask + (int64_t)k0 * I + (in ? r : 0);
-#pragma unroll 8
-        for (int p = 0; p < NP; ++p) {
-            const uint8_t a = m[(int64_t)(2 * p) * I], b = m[(int64_t)(2 * p + 1) * I];
-            pair(p, in && a != 0, in && b != 0);
-        }
+        uint8_t e[PK_STEP];                           // (all loads in flight before the first is looked at)
+#pragma unroll
+        for (int k = 0; k < PK_STEP; ++k) e[k] = m[(int64_t)k * I];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int p = 0; p < NP; ++p) pair(p, in && e[2 * p] != 0, in && e[2 * p + 1] != 0);
     }
     // rows past the end: no weights (whatever is there reaches outputs that are not stored), selectors as of empty quads, no flags
     // (nothing else of the flags: a product that reads the same layer on another stream may be under way, and the packing behind this
@@ -174,33 +176,31 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
     }
     // Where the quads go.  Four dwords that 32 lanes of the product's staging store together meet in no LDS bank if they are the four
     // dwords of 16 bytes, each of another such unit (see row0 there); which four go together differs with the activations' type.  So
-    // each quad in turn takes the half of a unit, and its two dwords the order, that meet the fewest so far.  Lane (g, l): dwords of
-    // group g at place l of a unit; 0 <= g < 8 fp32 (line, half of its chunks, dword of a chunk), then bfloat16.  (Quads in the order
+    // each quad in turn takes the half of a unit, and its two dwords the order, that meet the fewest so far.  Lane g: dwords of
+    // group g at each place of a unit; 0 <= g < 8 fp32 (line, half of its chunks, dword of a chunk), then bfloat16.  (Quads in the order
     // in which they were found, and rows that shared banks: 500 clocks of conflicts in a step of fp32, 815 of bfloat16; the products of
     // 1024 <-> 4096, 16384 tokens, bfloat16, 0.05: Y 150 -> 148.5 and dX 123 -> 120 us, fp32 within 1 %.)
-    uint32_t met = 0;
+    const int mine1 = first_s[lane & (NQ - 1)], mine2 = second_s[lane & (NQ - 1)];
+    uint32_t met = 0;                                 // lane g: four counts of eight bits
     int taken[2] = {0, 0}, place = 0;                 // lane m: place of quad m's first dword
-    auto group_f32 = [](int p) { return (p >> 4) * 4 + (p >> 3 & 1) * 2 + (p & 1); };
-    auto group_bf16 = [](int p) { return 8 + (p >> 4) * 4 + (p & 3); };
     for (int m = 0; m < NQ; ++m) {
-        const int p = __builtin_amdgcn_readfirstlane(first_s[m]), q = __builtin_amdgcn_readfirstlane(second_s[m]);
-        const int g[4] = {group_f32(p), group_bf16(p), group_f32(q), group_bf16(q)};
-        int best = 0, least = 1 << 20;
+        const int p = __builtin_amdgcn_readlane(mine1, m), q = __builtin_amdgcn_readlane(mine2, m);
+        const int pf = (p >> 4) * 4 + (p >> 3 & 1) * 2 + (p & 1), pb = 8 + (p >> 4) * 4 + (p & 3);
+        const int qf = (q >> 4) * 4 + (q >> 3 & 1) * 2 + (q & 1), qb = 8 + (q >> 4) * 4 + (q & 3);
+        const uint32_t of_p = (uint32_t)(__builtin_amdgcn_readlane((int)met, pf) + __builtin_amdgcn_readlane((int)met, pb));
+        const uint32_t of_q = (uint32_t)(__builtin_amdgcn_readlane((int)met, qf) + __builtin_amdgcn_readlane((int)met, qb));
+        const uint32_t sum = of_p + ((of_q & 0x00FF00FFu) << 8 | (of_q >> 8 & 0x00FF00FFu));       // (q takes the place beside p's)
+        uint32_t least = 0xFFFFFFFFu;
 #pragma unroll
-        for (int l = 0; l < 4; ++l) {
-            int sum = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) sum += __builtin_amdgcn_readlane((int)met, 4 * g[e] + (e < 2 ? l : l ^ 1));
-            if (taken[l >> 1] < NQ / 2 && sum < least) least = sum, best = l;
-        }
-        const int half = best >> 1, unit = half ? taken[1]++ : taken[0]++;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) met += lane == 4 * g[e] + (e < 2 ? best : best ^ 1) ? 1u : 0u;
+        for (uint32_t l = 0; l < 4; ++l)
+            if (taken[l >> 1] < NQ / 2) least = min(least, (sum >> (8 * l) & 255u) << 2 | l);
+        const int best = (int)(least & 3u), half = best >> 1, unit = half ? taken[1]++ : taken[0]++;
+        met += (lane == pf || lane == pb ? 1u << (8 * best) : 0u) + (lane == qf || lane == qb ? 1u << (8 * (best ^ 1)) : 0u);
         if (lane == m) place = 4 * unit + best;
     }
     if (lane < NQ) {
-        v.slots[(int64_t)at * NP + first_s[lane]] = (uint8_t)(4 * place);
-        v.slots[(int64_t)at * NP + second_s[lane]] = (uint8_t)(4 * (place ^ 1));
+        v.slots[(int64_t)at * NP + mine1] = (uint8_t)(4 * place);
+        v.slots[(int64_t)at * NP + mine2] = (uint8_t)(4 * (place ^ 1));
     }
 }
 
