@@ -143,3 +143,37 @@ def test_automatic_choice(dtype):
         assert want is None or (mst.mst_gemm_last_tile() == PAIRS) == want, (density, mask)
         ref = x[:64].double() @ torch.from_numpy((W * M).astype(np.float64)).to(DEV).T
         assert rel_err(Y[:64].cpu().numpy(), ref.cpu().numpy()) <= PARTS, (density, mask)
+
+
+def test_recordings_side_by_side():
+    """Two recordings that each make the packed weights, replayed on two streams at once: what one makes again the other may be
+    reading (masks of second steps included), so it has to stay what it is throughout."""
+    T, I, O = 1024, 512, 832
+    rig, W, M, X, dY, ops, act = _layer(T, I, O, 0.3, "f32")
+    mst.mst_gemm_force_fp32_mfma(0)
+    rig.fwd(ops[0], act)                                     # the dense copy, and no packed weights
+    mst.mst_gemm_force_fp32_mfma(PAIRS)
+    L, Xd, dYd = rig.layer, dev(X), dev(dY)
+    sides = [torch.cuda.Stream() for _ in range(2)]
+    outs = [(torch.zeros((T, O), dtype=torch.float32, device=DEV), torch.zeros((T, I), dtype=torch.float32, device=DEV)) for _ in sides]
+    graphs = []
+    for side, (Y, dX) in zip(sides, outs):
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            for _ in range(4):
+                mst.mst_sparse_fc_fwd(L, Xd, Y, T, act, side)
+                mst.mst_sparse_fc_bwd_input(L, dYd, dX, T, act, side)
+        graphs.append(graph)
+    Yr, dXr = opr.fc_fwd(X, W, M), opr.fc_bwd_input(dY, W, M)
+    for k in range(4):
+        torch.cuda.synchronize()
+        for graph, side, (Y, dX) in zip(graphs, sides, outs):
+            with torch.cuda.stream(side):
+                Y.zero_()
+                dX.zero_()
+                graph.replay()
+        torch.cuda.synchronize()
+        for Y, dX in outs:
+            assert rel_err(Y.cpu().numpy(), Yr) <= PARTS, k
+            assert rel_err(dX.cpu().numpy(), dXr) <= PARTS, k
