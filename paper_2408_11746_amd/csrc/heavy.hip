@@ -66,9 +66,12 @@ template <> struct HeavyRegs<float> { float4 a[2]; float4 b[2][2]; };
 template <> struct HeavyRegs<uint16_t> { uint4 a; float4 b[2][2]; };
 
 // Workgroup = 32 tokens x up to 64 heavy rows (T / 32 workgroups: two per CU at T = 16384, which
-// is what keeps the memory side busy -- a workgroup has one fetch in flight at a time).  Wavefronts
-// 0 and 1 own one 32 x 32 MFMA tile each (rows 0..31 and 32..63 of the heavy list; the second idles
-// when the list is short), all four stage.  k steps of 128 through one LDS stage, per half of
+// is what keeps the memory side busy -- a workgroup has one fetch in flight at a time).  All
+// four wavefronts stage and multiply: with up to 32 rows each a quarter of a step's k, with more two of them half of it for one of
+// the two row tiles; their sums meet in LDS at the end, and rows 33..64 are staged only where there are any (with one
+// wavefront a row tile, 16 rows of 3072 -> 768 at 16384 tokens took 51 us, now 43; 201 MB of activations pass in that
+// time, at the rate of a large copy.  With 54 rows of 768 -> 3072 the scattered stores are the larger part: 33 us either way).
+// k steps of 128 through one LDS stage, per half of
 // 64 k: A hi, A lo (32 rows of 128 bytes), B hi, B lo (64 rows); the next step's operands travel in
 // registers while this one is multiplied.  A: thread tid stages unit tid & 7 of row tid >> 3; B:
 // unit idx & 7 of row idx >> 3, idx = it * 256 + tid: eight threads read 256 consecutive bytes.
@@ -87,11 +90,12 @@ __global__ __launch_bounds__(256) void k_heavy_fwd(const TA* __restrict__ X, con
     char* const Bh = lds + 2 * PA;
     char* const Bl = lds + 2 * PA + PB;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wn = (wave & 1) * 32;
+    // row tiles; wavefronts that share one, each with its part of a step's eight 16 k
+    const int tiles = nh > 32 ? 2 : 1, parts = 4 / tiles, part = wave / tiles, per = 8 / parts;
+    const int wn = (wave & (tiles - 1)) * 32;
     const int lk = lane >> 5, lm = lane & 31;
     const int m0 = blockIdx.x * HT;
     if (tid < HEAVY_MAX) col_s[tid] = tid < nh ? heavy[1 + tid] : 0;
-    const bool active = wave < 2 && wn < nh;
 
     const int ua = tid & 7, ra = tid >> 3;
     const uint32_t addr_a = bf_unit(ra, ua);
@@ -112,7 +116,8 @@ __global__ __launch_bounds__(256) void k_heavy_fwd(const TA* __restrict__ X, con
             if constexpr (std::is_same<TA, float>::value) heavy_load8(arow, k, I, vec_x != 0, rg[hf].a[0], rg[hf].a[1]);
             else rg[hf].a = heavy_load8(arow, k, I, vec_x != 0);
 #pragma unroll
-            for (int it = 0; it < 2; ++it) heavy_load8(brow[it], k, I, vec_h != 0, rg[hf].b[it][0], rg[hf].b[it][1]);
+            for (int it = 0; it < 2; ++it)
+                if (it < tiles) heavy_load8(brow[it], k, I, vec_h != 0, rg[hf].b[it][0], rg[hf].b[it][1]);
         }
     };
     floatx16 acc;
@@ -127,36 +132,43 @@ __global__ __launch_bounds__(256) void k_heavy_fwd(const TA* __restrict__ X, con
             if constexpr (std::is_same<TA, float>::value) heavy_stage_f32(Ah, Al, hf * HALF + addr_a, rg[hf].a[0], rg[hf].a[1]);
             else *reinterpret_cast<uint4*>(Ah + hf * HALF + addr_a) = rg[hf].a;
 #pragma unroll
-            for (int it = 0; it < 2; ++it) heavy_stage_f32(Bh, Bl, hf * HALF + addr_b[it], rg[hf].b[it][0], rg[hf].b[it][1]);
+            for (int it = 0; it < 2; ++it)
+                if (it < tiles) heavy_stage_f32(Bh, Bl, hf * HALF + addr_b[it], rg[hf].b[it][0], rg[hf].b[it][1]);
         }
         __syncthreads();
         if (k0 + HK < I) fetch(k0 + HK);
-        if (active) {
 #pragma unroll
-            for (int ks = 0; ks < 16; ks += 2) {          // 16 k per MFMA: units ks + lk of half ks >> 3
-                const uint32_t hoff = (ks >> 3) * HALF;
-                const uint32_t oa = hoff + bf_unit(lm, (ks & 7) + lk), ob = hoff + bf_unit(wn + lm, (ks & 7) + lk);
-                const bf16x8 ah = *reinterpret_cast<const bf16x8*>(Ah + oa);
-                const bf16x8 bh = *reinterpret_cast<const bf16x8*>(Bh + ob);
-                const bf16x8 bl = *reinterpret_cast<const bf16x8*>(Bl + ob);
-                if constexpr (std::is_same<TA, float>::value) {
-                    const bf16x8 al = *reinterpret_cast<const bf16x8*>(Al + oa);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
-                }
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
+        for (int j = 0; j < 4; ++j) {                     // 16 k per MFMA: units ks + lk of half ks >> 3
+            if (j >= per) break;
+            const int ks = 2 * (part * per + j);
+            const uint32_t hoff = (uint32_t)(ks >> 3) * HALF;
+            const uint32_t oa = hoff + bf_unit(lm, (ks & 7) + lk), ob = hoff + bf_unit(wn + lm, (ks & 7) + lk);
+            const bf16x8 ah = *reinterpret_cast<const bf16x8*>(Ah + oa);
+            const bf16x8 bh = *reinterpret_cast<const bf16x8*>(Bh + ob);
+            const bf16x8 bl = *reinterpret_cast<const bf16x8*>(Bl + ob);
+            if constexpr (std::is_same<TA, float>::value) {
+                const bf16x8 al = *reinterpret_cast<const bf16x8*>(Al + oa);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
             }
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
         }
     }
-    if (!active) return;
+    // The parts of a tile are added in their order; each of its wavefronts adds and stores its share of the 16 registers.
     // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
+    __syncthreads();
+    float* const sums = reinterpret_cast<float*>(lds);   // [wavefront][register][lane]
+#pragma unroll
+    for (int v = 0; v < 16; ++v) sums[(wave * 16 + v) * 64 + lane] = acc[v];
+    __syncthreads();
     const int n = wn + lm;
     if (n >= nh) return;
     const int col = col_s[n];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
+    for (int v = part * 16 / parts; v < (part + 1) * 16 / parts; ++v) {
+        float sum = 0.f;
+        for (int p = 0; p < parts; ++p) sum += sums[((p * tiles + (wave & (tiles - 1))) * 16 + v) * 64 + lane];
         const int m = m0 + 8 * (v >> 2) + 4 * lk + (v & 3);
-        if (m < T) Y[(int64_t)m * O + col] = acc[v];
+        if (m < T) Y[(int64_t)m * O + col] = sum;
     }
 }
 
