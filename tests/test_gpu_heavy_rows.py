@@ -168,3 +168,27 @@ def test_the_default_takes_layers_of_a_million_positions_only():
             if mode == 1:
                 assert rel_err(rig.fwd(X[:, :I]), opr.fc_fwd(X[:, :I], W, M)) <= TOL
     assert slots[(1024, 1)] < slots[(1024, 0)] and slots[(768, 1)] == slots[(768, 0)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("rows,I", [(1, 264), (31, 130), (32, 128), (33, 256), (64, 1001)])
+def test_row_tiles_and_shares_of_a_step(rows, I, dtype):
+    """One and two row tiles of 32, full and partly filled; k steps of 128 with a remainder that leaves some of the wavefronts'
+    shares empty; a last token tile of 6.  Two bfloat16 parts leave at most 3 * 2^-18 of a term."""
+    O, T = 1100, 70
+    rng = np.random.default_rng(rows)
+    M = (rng.random((O, I)) < 0.005).astype(np.uint8)
+    heavy = rng.choice(O, rows, replace=False)
+    M[heavy] = 1
+    assert set(heavy_rule(M)) == set(heavy)
+    W = (rng.standard_normal((O, I)) * 0.02).astype(np.float32)
+    if dtype == "bf16":
+        X, dY, xb, _ = synth.make_activations(9, 1, T, I, O, "bf16")
+        x, act = xb.view(np.int16), mst.MST_BF16
+    else:
+        X, dY = synth.make_activations(9, 1, T, I, O)
+        x, act = X, mst.MST_F32
+    rig = Rig(W, M, T)
+    rig.layer.set_path(mst.MST_PATH_SPARSE)
+    assert rig.layer.format_stats()["heavy_rows"] == rows
+    assert rel_err(rig.fwd(x, act), opr.fc_fwd(X, W, M)) <= 2e-5
