@@ -76,7 +76,6 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
     constexpr int NP = PK_PAIRS, NQ = NP / 2;
     __shared__ unsigned long long g1[NP][4], g2[NP][4];
     __shared__ uint16_t cost[NP][NP];
-    __shared__ uint8_t first_s[NQ], second_s[NQ];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const bool rows = blockIdx.x < (unsigned)(y.bands * y.nk);
     const PairsView& v = rows ? y : x;
@@ -140,7 +139,7 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
         const int p = 2 * j + (lane >> 5), q = lane & 31;
         key[j] = p < q ? (uint32_t)cost[p][q] << 16 | (uint32_t)p << 8 | (uint32_t)q : 0xFFFFFFFFu;
     }
-    int total = 0;
+    int total = 0, first = 0, second = 0;             // lane m (mod 16): quad m
     uint32_t used = 0;
     for (int m = 0; m < NQ; ++m) {
         uint32_t best = 0xFFFFFFFFu;
@@ -151,27 +150,25 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
         const uint32_t p = best >> 8 & 31u, q = best & 31u;
         total += (int)(best >> 16);
         used |= 1u << p | 1u << q;
-        if (lane == 0) { first_s[m] = (uint8_t)p; second_s[m] = (uint8_t)q; }
+        if ((lane & (NQ - 1)) == m) first = (int)p, second = (int)q;
     }
     // exchanges between two quads while one gains
     for (int round = 0; round < NQ && total > 0; ++round) {
         uint32_t best = 0xFFFFFFFFu;
+        const int u = __shfl(first, lane >> 1 & (NQ - 1)), w = __shfl(second, lane >> 1 & (NQ - 1));
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
             const int e = 64 * j + lane, how = e & 1, a = (e >> 1) / NQ, b = (e >> 1) % NQ;
-            const int p = first_s[a], q = second_s[a], u = first_s[b], w = second_s[b];
+            const int p = __shfl(first, a), q = __shfl(second, a);
             const int gain = (int)cost[p][q] + cost[u][w] - (how ? (int)cost[p][w] + cost[q][u] : (int)cost[p][u] + cost[q][w]);
             if (a < b && gain > 0) best = min(best, (uint32_t)(0x7FFF - gain) << 16 | (uint32_t)e);
         }
         best = wave_min(best);
         if (best == 0xFFFFFFFFu) break;
-        const int e = (int)(best & 0xFFFFu), how = e & 1, a = (e >> 1) / NQ, b = (e >> 1) % NQ;
-        const uint8_t q = second_s[a], u = first_s[b], w = second_s[b];
-        if (lane == 0) {
-            second_s[a] = how ? w : u;
-            first_s[b] = q;
-            second_s[b] = how ? u : w;
-        }
+        const int e = (int)(best & 0xFFFFu), how = e & 1, a = (e >> 1) / NQ, b = (e >> 1) % NQ, m = lane & (NQ - 1);
+        const int qa = __builtin_amdgcn_readlane(second, a), ub = __builtin_amdgcn_readlane(first, b), wb = __builtin_amdgcn_readlane(second, b);
+        if (m == a) second = how ? wb : ub;
+        if (m == b) first = qa, second = how ? ub : wb;
         total -= 0x7FFF - (int)(best >> 16);
     }
     // Where the quads go.  Four dwords that 32 lanes of the product's staging store together meet in no LDS bank if they are the four
@@ -180,11 +177,10 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
     // group g at each place of a unit; 0 <= g < 8 fp32 (line, half of its chunks, dword of a chunk), then bfloat16.  (Quads in the order
     // in which they were found, and rows that shared banks: 500 clocks of conflicts in a step of fp32, 815 of bfloat16; the products of
     // 1024 <-> 4096, 16384 tokens, bfloat16, 0.05: Y 150 -> 148.5 and dX 123 -> 120 us, fp32 within 1 %.)
-    const int mine1 = first_s[lane & (NQ - 1)], mine2 = second_s[lane & (NQ - 1)];
     uint32_t met = 0;                                 // lane g: four counts of eight bits
     int taken[2] = {0, 0}, place = 0;                 // lane m: place of quad m's first dword
     for (int m = 0; m < NQ; ++m) {
-        const int p = __builtin_amdgcn_readlane(mine1, m), q = __builtin_amdgcn_readlane(mine2, m);
+        const int p = __builtin_amdgcn_readlane(first, m), q = __builtin_amdgcn_readlane(second, m);
         const int pf = (p >> 4) * 4 + (p >> 3 & 1) * 2 + (p & 1), pb = 8 + (p >> 4) * 4 + (p & 3);
         const int qf = (q >> 4) * 4 + (q >> 3 & 1) * 2 + (q & 1), qb = 8 + (q >> 4) * 4 + (q & 3);
         const uint32_t of_p = (uint32_t)(__builtin_amdgcn_readlane((int)met, pf) + __builtin_amdgcn_readlane((int)met, pb));
@@ -199,8 +195,8 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
         if (lane == m) place = 4 * unit + best;
     }
     if (lane < NQ) {
-        v.slots[(int64_t)at * NP + mine1] = (uint8_t)(4 * place);
-        v.slots[(int64_t)at * NP + mine2] = (uint8_t)(4 * (place ^ 1));
+        v.slots[(int64_t)at * NP + first] = (uint8_t)(4 * place);
+        v.slots[(int64_t)at * NP + second] = (uint8_t)(4 * (place ^ 1));
     }
 }
 
