@@ -67,30 +67,39 @@ __global__ void k_gather_flat(const float* __restrict__ G, int64_t stride, int n
 }
 
 // Y (dX) on the sparse matrix instructions where that is ahead: *done says whether it ran.  The packed weights are kept
-// up as the planes are (see ensure_weights); the first product of a layer that makes them learns how even the mask is
-// and may leave the work to the dense kernels after all.
+// up as the planes are (see ensure_weights); the first product on a mask learns how even it is and may leave the work to the
+// dense kernels after all.
 static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, int T, mst_dtype act, int64_t split_floats, hipStream_t s, bool* done) {
     mst_layer* L = const_cast<mst_layer*>(Lc);       // caches of vals[], not layer state
     *done = false;
+    if (!L->pairs_y.blocks) return MST_OK;
+    L->pairs_calls = std::min(L->pairs_calls + 1, PAIRS_CALLS);
     int tokens = pairs_tokens(L, y, act, T, split_floats);
     if (tokens == 0) return MST_OK;
+    const bool measured = L->pairs_measured;
     bool made = false;
     if (!L->Wd_valid) {
         made = pairs_kept(L, L->nnz);
         const int rc = refresh_dense_copy(L, s);
         if (rc != MST_OK) return rc;
     }
-    if (L->pairs_valid && !L->pairs_recorded) {
+    if (L->pairs_valid && !(L->pairs_recorded && L->pairs_measured)) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         MST_HIP(hipStreamIsCapturing(s, &capture));
-        L->pairs_recorded = capture != hipStreamCaptureStatusNone;
+        if (capture != hipStreamCaptureStatusNone) {
+            L->pairs_recorded = true;
+        } else if (!L->pairs_measured) {              // (an update made them)
+            const int rc = measure_pairs(L, s);
+            if (rc != MST_OK) return rc;
+        }
     }
     if (!L->pairs_valid && !made) {
-        const bool first = !L->pairs_used;
         L->pairs_used = true;
         const int rc = make_pairs(L, s);
-        const int rcm = rc == MST_OK ? weights_made(L, false, true, first, s) : rc;
+        const int rcm = rc == MST_OK ? weights_made(L, false, true, s) : rc;
         if (rcm != MST_OK) return rcm;
+    }
+    if (!measured && L->pairs_measured) {
         tokens = pairs_tokens(L, y, act, T, split_floats);
         if (tokens == 0) return MST_OK;
     }
@@ -117,7 +126,7 @@ static int ensure_weights(const mst_layer* Lc, bool y, mst_dtype act, int M, int
     if (L->planes_valid || made) return MST_OK;
     L->planes_used = true;
     rc = make_planes(L, s);
-    return rc == MST_OK && !L->planes_missed ? weights_made(L, true, false, false, s) : rc;
+    return rc == MST_OK && !L->planes_missed ? weights_made(L, true, false, s) : rc;
 }
 
 // (full: see full_precision(); split_ws: room for partial outputs of a split of the contraction range, used where the output

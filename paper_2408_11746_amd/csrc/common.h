@@ -71,7 +71,8 @@ struct PairsView {
     int R = 0, K = 0, nk = 0, bands = 0;
     uint8_t* slots = nullptr;  // [band][step][32] where the k pairs (2 p, 2 p + 1) of a step go in an LDS row
     uint32_t* flags = nullptr; // [band][step] a byte per two tiles of 32 rows: 1 if one of them needs a second step
-    uint32_t* count = nullptr; // how many of those bytes are 1 (of both views: the row view's)
+    uint8_t* over = nullptr;   // [band][step] 1: by the mask some row needs a second one
+    uint32_t* count = nullptr; // [2] (the row view's) how many of those there are in either view
     char* blocks = nullptr;    // [band][2 nk] packed tiles of the steps, then those of the second steps
     size_t bytes = 0;
 };
@@ -123,7 +124,12 @@ struct mst_layer {
     bool pairs_used = false, pairs_missed = false, pairs_valid = false;      // as those of the planes
     bool pairs_recorded = false;   // a recorded product reads them without making them: kept up at any density
     bool pairs_matched = false;    // their slots were chosen for the present active set
-    float pairs_skew = 0.f;        // share of the steps with a second one, beyond what a uniform mask would have (measured when they are first made)
+    // Y, dX: share of the steps with a second one, against that of a uniform mask, and whether it was measured on the present mask.  A loading
+    // makes it unknown, so does an update behind PAIRS_CALLS products (pairs_calls: those since the last measurement).
+    float pairs_skew[2] = {0.f, 0.f};
+    bool pairs_measured = false;
+    int pairs_calls = 0;
+    void pairs_unknown() { pairs_skew[0] = pairs_skew[1] = 0.f; pairs_measured = false; }
     // The index views are built lazily: an update of a layer that the dense contractions serve
     // (path choice at the batch size and type of the last product call) leaves them unbuilt; a
     // call that needs them and has a workspace builds them, one without runs the dense product.
@@ -301,12 +307,15 @@ int gemm_wgrad16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, i
 // Y and dX of bfloat16 activations from the split weights' planes; see gemm_planes.hip
 int gemm_planes(const uint16_t* A, const uint16_t* P, float* C, int M, int N, int Kdim, hipStream_t s);
 int make_planes(const mst_layer* L, hipStream_t s);
-int weights_made(mst_layer* L, bool planes, bool pairs, bool measure, hipStream_t s);
+int weights_made(mst_layer* L, bool planes, bool pairs, hipStream_t s);
 // the same at densities of a tenth and below, for both activation types; see gemm_pairs.hip
 PairsView pairs_view(void* mem, int R, int K);
 bool pairs_kept(const mst_layer* L, int64_t nnz);
 int make_pairs(mst_layer* L, hipStream_t s);
 int measure_pairs(mst_layer* L, hipStream_t s);
+// A measurement waits for its stream: an update behind fewer products than these leaves the last one standing.  (Updates are hundreds of
+// steps apart in earnest; a loop that updates after every step would wait in every step.)
+constexpr int PAIRS_CALLS = 64;
 int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split_floats);
 int gemm_pairs(const void* A, mst_dtype act, const PairsView& v, float* C, int T, int tokens, hipStream_t s);
 double gemm_two_parts_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split);

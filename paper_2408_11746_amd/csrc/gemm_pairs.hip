@@ -50,7 +50,8 @@ PairsView pairs_view(void* mem, int R, int K) {
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return b ? b + o : nullptr; };
     v.slots = (uint8_t*)take((size_t)n * PK_PAIRS);
     v.flags = (uint32_t*)take((size_t)n * 4);
-    v.count = (uint32_t*)take(4);
+    v.over = (uint8_t*)take((size_t)n);
+    v.count = (uint32_t*)take(8);
     v.blocks = take((size_t)n * 2 * PK_BLOCK);
     v.bytes = off;
     return v;
@@ -114,7 +115,6 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
     // launch writes what is there already)
     const int missing = (band + 1) * PB_ROWS - v.R;
     if (tid < 4 && 64 * tid >= PB_ROWS - missing) reinterpret_cast<uint8_t*>(v.flags + at)[tid] = 0;
-    if (tid == 0 && blockIdx.x == 0) *y.count = 0;
     if (missing > 0)
         for (int e = tid; e < 4 * missing; e += 256) {       // [first, second step][32 k][missing rows]
             const int row = PB_ROWS - missing + e % missing, ss = e / missing;
@@ -171,6 +171,7 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
         if (m == b) first = qa, second = how ? ub : wb;
         total -= 0x7FFF - (int)(best >> 16);
     }
+    if (lane == 0) v.over[at] = total > 0 ? 1 : 0;
     // Where the quads go.  Four dwords that 32 lanes of the product's staging store together meet in no LDS bank if they are the four
     // dwords of 16 bytes, each of another such unit (see row0 there); which four go together differs with the activations' type.  So
     // each quad in turn takes the half of a unit, and its two dwords the order, that meet the fewest so far.  Lane g: dwords of
@@ -286,10 +287,7 @@ __global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W,
     __syncthreads();
     // the two tiles go together
     const bool on = (over_s[wave] | over_s[wave ^ 1]) != 0;
-    if (lane == 0 && (wave & 1) == 0) {
-        reinterpret_cast<uint8_t*>(v.flags + bk)[t >> 1] = on ? 1 : 0;
-        if (on) atomicAdd(y.count, 1u);               // (read once, by the packing that follows the first choice of slots)
-    }
+    if (lane == 0 && (wave & 1) == 0) reinterpret_cast<uint8_t*>(v.flags + bk)[t >> 1] = on ? 1 : 0;
     if (!on) return;
 #pragma unroll
     for (int ss = 0; ss < 2; ++ss) store(blk + (int64_t)v.nk * PK_BLOCK + ss * PW_SUB, hi2[ss], lo2[ss], ix2[ss]);
@@ -650,14 +648,33 @@ bool pairs_kept(const mst_layer* L, int64_t nnz) {
     return L->pairs_used && !L->pairs_missed && (L->pairs_recorded || (double)nnz <= PAIRS_LINE * (double)L->N);
 }
 
-// How uneven a layer's first mask is, read back where the product that packs the weights waits anyway: the share of the units of
-// two tiles x one step that go a second time, against that of a uniformly random mask (a quarter of its steps).
+// How uneven the present mask is: the share of the steps of a band that go a second time, against that of a uniformly random mask.
+// By the mask and not by the weights: those that an update has grown are zero until the next step.  Read back by the first
+// product that reads the packed weights of a mask, which waits for it.
+__global__ __launch_bounds__(256) void k_count_second(const PairsView y, const PairsView x) {
+    __shared__ uint32_t sum;
+    const PairsView& v = blockIdx.x == 0 ? y : x;
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
+    uint32_t n = 0;
+    for (int e = threadIdx.x; e < v.bands * v.nk; e += 256) n += v.over[e];
+    if (n) atomicAdd(&sum, n);
+    __syncthreads();
+    if (threadIdx.x == 0) y.count[blockIdx.x] = sum;
+}
 int measure_pairs(mst_layer* L, hipStream_t s) {
-    uint32_t second = 0;
-    MST_HIP(hipMemcpyAsync(&second, L->pairs_y.count, 4, hipMemcpyDeviceToHost, s));
+    k_count_second<<<2, 256, 0, s>>>(L->pairs_y, L->pairs_x);
+    MST_LAUNCH_CHECK();
+    uint32_t second[2] = {0, 0};
+    MST_HIP(hipMemcpyAsync(second, L->pairs_y.count, 8, hipMemcpyDeviceToHost, s));
     MST_HIP(hipStreamSynchronize(s));
-    const double share = (double)second / (2.0 * (double)(L->O / 64) * (double)(L->I / 64));
-    L->pairs_skew = (float)std::min(1.0, std::max(0.0, 4.0 * (share - 0.03) - second_steps((double)L->nnz / (double)L->N)));
+    const double uniform = second_steps((double)L->nnz / (double)L->N);
+    for (int v = 0; v < 2; ++v) {
+        const PairsView& view = v == 0 ? L->pairs_y : L->pairs_x;
+        L->pairs_skew[v] = (float)((double)second[v] / ((double)view.bands * view.nk) - uniform);
+    }
+    L->pairs_measured = true;
+    L->pairs_calls = 0;
     return MST_OK;
 }
 
@@ -679,7 +696,7 @@ int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split
     const int R = y ? L->O : L->I, K = y ? L->I : L->O;
     const double dense = gemm_two_parts_us(y ? GEMM_NT : GEMM_NN, act, T, R, K, std::max<int64_t>(1, split_floats / ((int64_t)T * R)));
     if (dense == 0.0) return 0;
-    const double second = std::min(1.0, second_steps(d) + (double)L->pairs_skew);
+    const double second = std::min(1.0, std::max(0.0, second_steps(d) + (double)L->pairs_skew[y ? 0 : 1]));
     double best = dense;
     int tokens = 0;
     for (int t : {128, 192, 256}) {

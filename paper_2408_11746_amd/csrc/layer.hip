@@ -1019,17 +1019,18 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
     if (!planes && !pairs) return MST_OK;
     int rc = planes ? make_planes(L, s) : MST_OK;    // (recorded products read them without asking)
     if (rc == MST_OK && pairs) rc = make_pairs(L, s);
-    return rc == MST_OK ? weights_made(L, planes, pairs, false, s) : rc;
+    return rc == MST_OK ? weights_made(L, planes, pairs, s) : rc;
 }
 
 // The planes of Wd (its packed pairs) were made on s, by a product and not by the hand-over or the update that changed the
 // weights.  Products on other streams are ordered after those and not after this call, so it waits before it says that they are
-// there.  A recording cannot wait and runs later or never: it says nothing about them.
-int weights_made(mst_layer* L, bool planes, bool pairs, bool measure, hipStream_t s) {
+// there (and where the pairs are of a mask that nothing is known of, it learns how even that is).  A recording cannot wait and
+// runs later or never: it says nothing about them.
+int weights_made(mst_layer* L, bool planes, bool pairs, hipStream_t s) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     MST_HIP(hipStreamIsCapturing(s, &capture));
     if (capture != hipStreamCaptureStatusNone) return MST_OK;
-    if (measure) {
+    if (pairs && !L->pairs_measured) {
         const int rc = measure_pairs(L, s);
         if (rc != MST_OK) return rc;
     } else {
@@ -1190,7 +1191,7 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
     if ((int64_t)total > L->cap) return MST_ERR_STATE;
     MST_HIP(hipMemcpyAsync(L->mask, M_dev, (size_t)L->N, hipMemcpyDeviceToDevice, s));
     L->nnz = total;
-    L->pairs_skew = 0.f;
+    L->pairs_unknown();
     L->choice.store(0, std::memory_order_relaxed);
     L->built = false;                                   // a failed rebuild leaves no usable layer
     // Heavy rows (heavy.hip).  The dense pass costs a launch after every sparse forward, a read of

@@ -801,6 +801,7 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
     for (int x = 0; x < n; ++x) {
         items[x].L->nnz = items[x].st.nnz_after;
         items[x].L->choice.store(0, std::memory_order_relaxed);
+        if (items[x].L->pairs_calls >= PAIRS_CALLS) items[x].L->pairs_unknown();
     }
     if (n_views > 0 && (rc = build_views(views, n_views, s)) != MST_OK) return rc;
     if (n_canonical == 0) return MST_OK;

@@ -1,0 +1,106 @@
+"""Which products go to the sparse matrix instructions, and when their packed weights are made again: the choice follows the mask
+that the layer has now, the packing follows what products read.  Nothing is pinned but where a test says so; every product is compared with
+the double-precision product of the exported weights (two bfloat16 parts per fp32 operand: see test_gpu_pairs.py)."""
+import pytest
+
+import paper_2408_11746_amd as mst
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from gpu_util import DEV, rel_err  # noqa: E402
+
+PARTS = 2e-5
+PAIRS = 24
+T, I, O = 8192, 1024, 4096
+
+
+def _mask(density, kind, gen):
+    """uniform: every position alike.  rows: a twentieth of the rows full, so that most of the steps of Y go a second time.  crossed: full rows and
+    full columns, so that those of dX do as well."""
+    M = torch.rand((O, I), generator=gen, device=DEV) < (density if kind == "uniform" else density - 0.05)
+    if kind != "uniform":
+        M[torch.randperm(O, generator=gen, device=DEV)[:O // (20 if kind == "rows" else 40)]] = True
+    if kind == "crossed":
+        M[:, torch.randperm(I, generator=gen, device=DEV)[:I // 40]] = True
+    return M.to(torch.uint8)
+
+
+class Layer:
+    def __init__(self, density, mask="uniform", dtype="f32"):
+        self.act = mst.MST_BF16 if dtype == "bf16" else mst.MST_F32
+        self.gen = torch.Generator(device=DEV).manual_seed(9)
+        self.L = mst.Layer(O, I, O * I, DEV)
+        self.ws = torch.empty(mst.mst_workspace_bytes(O, I, O * I, T), dtype=torch.uint8, device=DEV)
+        self.load(density, mask)
+        kind = torch.bfloat16 if dtype == "bf16" else torch.float32
+        self.X = torch.randn((T, I), generator=self.gen, device=DEV).to(kind)
+        self.dY = torch.randn((T, O), generator=self.gen, device=DEV).to(kind)
+        self.Y = torch.empty((T, O), dtype=torch.float32, device=DEV)
+        self.dX = torch.empty((T, I), dtype=torch.float32, device=DEV)
+
+    def load(self, density, mask):
+        W = 0.02 * torch.randn((O, I), generator=self.gen, device=DEV)
+        self.L.load_dense(W, _mask(density, mask, self.gen), self.ws)
+
+    def weights(self):
+        W = torch.empty((O, I), dtype=torch.float32, device=DEV)
+        self.L.export_dense(W, None)
+        return W.double()
+
+    def update(self, density, zeta=0.3, rand_ratio=0.25):
+        G = torch.randn((O, I), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV)
+        mst.mst_mask_update_from_scores(self.L, G, density, zeta, rand_ratio, 7, self.ws)
+        self.L.values().add_(0.01)
+        self.L.sync_values()
+        torch.cuda.synchronize()
+
+    def fwd(self, tokens=T, stream=None):
+        self.Y.fill_(float("nan"))
+        mst.mst_sparse_fc_fwd(self.L, self.X, self.Y, tokens, self.act, stream)
+        return mst.mst_gemm_last_tile() == PAIRS
+
+    def right(self, scale=1.0, tokens=T):
+        """the last Y, of the weights handed over last (scale: theirs against the values now)"""
+        torch.cuda.synchronize()
+        W = self.weights() * scale
+        at = torch.arange(0, tokens, max(1, tokens // 64), device=DEV)
+        assert rel_err(self.Y[at].cpu().numpy(), (self.X[at].double() @ W.T).cpu().numpy()) <= PARTS
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_the_choice_follows_the_loaded_mask(dtype):
+    l = Layer(0.1, "uniform", dtype)
+    assert l.fwd()
+    l.right()
+    for mask, want in (("rows", False), ("uniform", True), ("rows", False)):
+        l.load(0.1, mask)
+        assert l.fwd() == want, mask
+        l.right()
+
+
+def test_a_recorded_first_product_leaves_the_measurement_to_an_eager_one():
+    l, side, graph = Layer(0.1, "rows"), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    l.L.set_path(mst.MST_PATH_DENSE)
+    mst.mst_gemm_force_fp32_mfma(128)
+    try:
+        l.fwd()                                              # the dense copy alone
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        l.fwd(stream=side)
+    graph.replay()
+    l.right()
+    assert not l.fwd()
+    l.right()
+
+
+def test_the_choice_follows_updates():
+    """An uneven mask that an update replaces by a random one: measured again where products have come between."""
+    l = Layer(0.1, "rows")
+    for _ in range(70):
+        assert not l.fwd()
+    l.update(0.1, zeta=1.0, rand_ratio=1.0)
+    assert l.fwd()
+    l.right()
