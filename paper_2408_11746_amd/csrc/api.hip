@@ -67,7 +67,7 @@ __global__ void k_gather_flat(const float* __restrict__ G, int64_t stride, int n
 }
 
 // Y (dX) on the sparse matrix instructions where that is ahead: *done says whether it ran.  The packed weights are kept
-// up as the planes are (see ensure_weights); the first product on a mask learns how even it is and may leave the work to the
+// up while products read them (see common.h); the first product on a mask learns how even it is and may leave the work to the
 // dense kernels after all.
 static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, int T, mst_dtype act, int64_t split_floats, hipStream_t s, bool* done) {
     mst_layer* L = const_cast<mst_layer*>(Lc);       // caches of vals[], not layer state
@@ -79,7 +79,7 @@ static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, i
     const bool measured = L->pairs_measured;
     bool made = false;
     if (!L->Wd_valid) {
-        made = pairs_kept(L, L->nnz);
+        made = L->pairs_recorded;                     // (then the dense copy brings them along)
         const int rc = refresh_dense_copy(L, s);
         if (rc != MST_OK) return rc;
     }
@@ -94,15 +94,18 @@ static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, i
         }
     }
     if (!L->pairs_valid && !made) {
-        L->pairs_used = true;
         const int rc = make_pairs(L, s);
         const int rcm = rc == MST_OK ? weights_made(L, false, true, s) : rc;
         if (rcm != MST_OK) return rcm;
     }
     if (!measured && L->pairs_measured) {
         tokens = pairs_tokens(L, y, act, T, split_floats);
-        if (tokens == 0) return MST_OK;
+        if (tokens == 0) {
+            L->pairs_unread = mst_layer::PAIRS_UNREAD;
+            return MST_OK;
+        }
     }
+    L->pairs_unread = 0;
     *done = true;
     gemm_note_tile(24);
     return gemm_pairs(A, act, y ? L->pairs_y : L->pairs_x, C, T, tokens, s);

@@ -117,12 +117,16 @@ struct mst_layer {
     bool planes_missed = false;  // a hand-over without them has been recorded
     bool planes_valid = false; // they hold the parts of Wd
     bool planes_kept() const { return planes_used && !planes_missed; }
-    // The packed weights of Y and dX on the sparse matrix instructions, with the life of the planes: made by the first product that
-    // reads them, kept up with Wd from then on while the density is one at which they are used.  (No layer of another
-    // shape has them: blocks null.)
+    // The packed weights of Y and dX on the sparse matrix instructions: made by the first product that reads them, kept up with Wd while
+    // products do.  A hand-over makes them again unless the last PAIRS_UNREAD of them did so for nobody (another batch size, a mask
+    // that turned out uneven), an update where the products that came last would read them at its density.  (No layer of
+    // another shape has them: blocks null.)
     mst::PairsView pairs_y, pairs_x;
-    bool pairs_used = false, pairs_missed = false, pairs_valid = false;      // as those of the planes
-    bool pairs_recorded = false;   // a recorded product reads them without making them: kept up at any density
+    static constexpr int PAIRS_UNREAD = 8;
+    int pairs_unread = PAIRS_UNREAD;             // hand-overs since a product read them
+    bool pairs_missed = false, pairs_valid = false;      // as those of the planes
+    // A recorded product reads them without making them.  Its replays come when they like, so they are made whenever Wd changes, at any density.
+    bool pairs_recorded = false;
     bool pairs_matched = false;    // their slots were chosen for the present active set
     // Y, dX: share of the steps with a second one, against that of a uniform mask, and whether it was measured on the present mask.  A loading
     // makes it unknown, so does an update behind PAIRS_CALLS products (pairs_calls: those since the last measurement).
@@ -310,7 +314,8 @@ int make_planes(const mst_layer* L, hipStream_t s);
 int weights_made(mst_layer* L, bool planes, bool pairs, hipStream_t s);
 // the same at densities of a tenth and below, for both activation types; see gemm_pairs.hip
 PairsView pairs_view(void* mem, int R, int K);
-bool pairs_kept(const mst_layer* L, int64_t nnz);
+bool pairs_kept(const mst_layer* L);
+bool pairs_wanted(const mst_layer* L);
 int make_pairs(mst_layer* L, hipStream_t s);
 int measure_pairs(mst_layer* L, hipStream_t s);
 // A measurement waits for its stream: an update behind fewer products than these leaves the last one standing.  (Updates are hundreds of

@@ -644,9 +644,7 @@ static double second_steps(double d) {
     return std::min(1.0, 0.10 + 38.0 * (d - 0.10));
 }
 
-bool pairs_kept(const mst_layer* L, int64_t nnz) {
-    return L->pairs_used && !L->pairs_missed && (L->pairs_recorded || (double)nnz <= PAIRS_LINE * (double)L->N);
-}
+bool pairs_kept(const mst_layer* L) { return !L->pairs_missed && (L->pairs_recorded || L->pairs_unread < mst_layer::PAIRS_UNREAD); }
 
 // How uneven the present mask is: the share of the steps of a band that go a second time, against that of a uniformly random mask.
 // By the mask and not by the weights: those that an update has grown are zero until the next step.  Read back by the first
@@ -705,6 +703,17 @@ int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split
         if (us < best) best = us, tokens = t;
     }
     return tokens;
+}
+
+// Would Y or dX of a batch like the last one read them?
+bool pairs_wanted(const mst_layer* L) {
+    if (L->hint_T <= 0) return false;
+    const mst_dtype act = (mst_dtype)L->hint_act;
+    auto reads = [&](bool y) {
+        const WalkJob job = y ? WALK_FWD : WALK_BWD_INPUT;
+        return use_dense_path(L, job, act, L->hint_T) && !full_precision(L, job, act, L->hint_T) && pairs_tokens(L, y, act, L->hint_T, 0) != 0;
+    };
+    return reads(true) || reads(false);
 }
 
 }  // namespace mst

@@ -1015,7 +1015,7 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
     }
     L->Wd_valid = L->Wd_zeros = true;
     L->planes_valid = L->pairs_valid = false;
-    const bool planes = L->planes_kept(), pairs = pairs_kept(L, L->nnz);
+    const bool planes = L->planes_kept(), pairs = L->pairs_recorded;
     if (!planes && !pairs) return MST_OK;
     int rc = planes ? make_planes(L, s) : MST_OK;    // (recorded products read them without asking)
     if (rc == MST_OK && pairs) rc = make_pairs(L, s);
@@ -1238,7 +1238,7 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     // than at the next product, so that products recorded into a graph never see stale weights.
     const bool dense = L->Wd_zeros && L->nnz > 0, views = L->nnz > 0 && L->views_valid;   // unbuilt views take the values when they are built
     L->Wd_valid = dense;
-    bool row = views, col = views, planes = dense && L->planes_valid, pairs = dense && L->pairs_valid && pairs_kept(L, L->nnz);
+    bool row = views, col = views, planes = dense && L->planes_valid, pairs = dense && L->pairs_valid && pairs_kept(L);
     L->planes_valid = planes;
     L->pairs_valid = pairs;
     if (dense && (L->planes_y || L->pairs_y.blocks || (views && !(L->row_walked && L->col_walked)))) {
@@ -1253,13 +1253,16 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
             planes = !L->planes_missed && (L->planes_used || (L->planes_y && L->hint_act == MST_BF16));
             L->planes_missed |= L->planes_y && !planes;
             // (the packed pairs likewise; products that would read them go to the dense kernels once they are missed)
-            pairs = pairs_kept(L, L->nnz);
+            pairs = pairs_kept(L);
             L->pairs_missed |= L->pairs_y.blocks && !pairs;
-        } else if (views) {
-            row = L->row_walked;
-            col = L->col_walked;
-            L->row_stale |= !row;
-            L->col_stale |= !col;
+        } else {
+            if (views) {
+                row = L->row_walked;
+                col = L->col_walked;
+                L->row_stale |= !row;
+                L->col_stale |= !col;
+            }
+            L->pairs_unread += pairs && L->pairs_unread < mst_layer::PAIRS_UNREAD;
         }
     }
     const int rc = refresh_views(L, row, col, dense, false, s);

@@ -12,7 +12,7 @@ from gpu_util import DEV, rel_err  # noqa: E402
 
 PARTS = 2e-5
 PAIRS = 24
-T, I, O = 8192, 1024, 4096
+T, I, O = 16384, 1024, 4096
 
 
 def _mask(density, kind, gen):
@@ -60,12 +60,28 @@ class Layer:
         mst.mst_sparse_fc_fwd(self.L, self.X, self.Y, tokens, self.act, stream)
         return mst.mst_gemm_last_tile() == PAIRS
 
+    def bwd(self, stream=None):
+        self.dX.fill_(float("nan"))
+        mst.mst_sparse_fc_bwd_input(self.L, self.dY, self.dX, T, self.act, stream)
+        return mst.mst_gemm_last_tile() == PAIRS
+
     def right(self, scale=1.0, tokens=T):
         """the last Y, of the weights handed over last (scale: theirs against the values now)"""
         torch.cuda.synchronize()
         W = self.weights() * scale
         at = torch.arange(0, tokens, max(1, tokens // 64), device=DEV)
         assert rel_err(self.Y[at].cpu().numpy(), (self.X[at].double() @ W.T).cpu().numpy()) <= PARTS
+
+    def right_dx(self, scale=1.0):
+        torch.cuda.synchronize()
+        W = self.weights() * scale
+        at = torch.arange(0, T, T // 64, device=DEV)
+        assert rel_err(self.dX[at].cpu().numpy(), (self.dY[at].double() @ W).cpu().numpy()) <= PARTS
+
+    def packed(self):
+        """the packed weights of dX, in front of the two planes at the end of the layer's buffer"""
+        end = self.L.buf.numel() - 8 * O * I
+        return self.L.buf[end - -(-I // 256) * (O // 64) * 2 * 34816:end]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -104,3 +120,76 @@ def test_the_choice_follows_updates():
     l.update(0.1, zeta=1.0, rand_ratio=1.0)
     assert l.fwd()
     l.right()
+
+
+def _untouched(l, what):
+    torch.cuda.synchronize()
+    assert bool((l.packed() == 0xFF).all()), what
+
+
+def test_nothing_is_packed_for_a_mask_that_was_turned_down():
+    l = Layer(0.1, "crossed")
+    assert not l.fwd()
+    assert not l.bwd()
+    torch.cuda.synchronize()
+    l.packed().fill_(0xFF)
+    l.L.values().mul_(2.0)
+    l.L.sync_values()
+    _untouched(l, "handed over")
+    assert not l.fwd()
+    l.right()
+    l.update(0.1)
+    _untouched(l, "updated")
+    assert not l.fwd()
+    l.right()
+
+
+def test_nothing_is_packed_at_a_density_at_which_the_dense_kernels_are_ahead():
+    l = Layer(0.1)
+    assert l.fwd() and l.bwd()
+    l.update(0.09)
+    assert l.fwd() and l.bwd()
+    l.right()
+    l.right_dx()
+    torch.cuda.synchronize()
+    l.packed().fill_(0xFF)
+    l.update(0.119)
+    _untouched(l, "updated")
+    assert not l.fwd()
+    l.right()
+    l.update(0.1)
+    assert l.fwd() and l.bwd()
+    l.right()
+    l.right_dx()
+
+
+def test_the_packing_stops_where_no_product_reads_it():
+    l = Layer(0.1)
+    assert l.fwd()
+    for k in range(12):                                      # (short batches: other kernels)
+        l.L.values().mul_(1.1)
+        l.L.sync_values()
+        l.fwd(tokens=100)
+        if k == 9:
+            torch.cuda.synchronize()
+            l.packed().fill_(0xFF)
+    _untouched(l, "twelve hand-overs")
+    assert l.fwd()
+    l.right()
+
+
+def test_a_recorded_product_outlives_the_densities_of_the_packed_pairs():
+    l, side, graph = Layer(0.1), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    assert l.fwd()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        assert l.fwd(stream=side)
+    for density in (0.2, 0.5, 0.1):
+        l.update(density)                                    # (keeps the dense copy)
+        graph.replay()
+        l.right()
+        for _ in range(12):                                  # hand-overs that nothing but the recording reads
+            l.L.values().mul_(1.1)
+            l.L.sync_values()
+        graph.replay()
+        l.right()
