@@ -74,7 +74,7 @@ static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, i
     *done = false;
     if (!L->pairs_y.blocks) return MST_OK;
     L->pairs_calls = std::min(L->pairs_calls + 1, PAIRS_CALLS);
-    int tokens = pairs_tokens(L, y, act, T, split_floats);
+    int tokens = pairs_tokens(L, y, act, T, split_floats, 0.0);
     if (tokens == 0) return MST_OK;
     const bool measured = L->pairs_measured;
     bool made = false;
@@ -83,23 +83,33 @@ static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, i
         const int rc = refresh_dense_copy(L, s);
         if (rc != MST_OK) return rc;
     }
-    if (L->pairs_valid && !(L->pairs_recorded && L->pairs_measured)) {
+    bool recording = false;
+    if (!(L->pairs_valid && L->pairs_recorded && measured)) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         MST_HIP(hipStreamIsCapturing(s, &capture));
-        if (capture != hipStreamCaptureStatusNone) {
-            L->pairs_recorded = true;
-        } else if (!L->pairs_measured) {              // (an update made them)
+        recording = capture != hipStreamCaptureStatusNone;
+    }
+    if (L->pairs_valid) {
+        L->pairs_recorded |= recording;
+        if (!recording && !L->pairs_measured) {       // (an update made them)
             const int rc = measure_pairs(L, s);
             if (rc != MST_OK) return rc;
         }
-    }
-    if (!L->pairs_valid && !made) {
-        const int rc = make_pairs(L, s);
-        const int rcm = rc == MST_OK ? weights_made(L, false, true, s) : rc;
-        if (rcm != MST_OK) return rcm;
+    } else if (!made) {
+        // A recording makes them in every replay, and where replays of a hand-over may leave them behind every product does.  It
+        // then waits for the choice of the pairs alone, once on every mask.
+        if (recording || L->pairs_missed) {
+            tokens = pairs_tokens(L, y, act, T, split_floats, making_pairs_us(L, recording && !L->pairs_matched));
+            if (tokens == 0) return MST_OK;
+        }
+        const bool wait = !(L->pairs_missed && L->pairs_matched && L->pairs_measured);
+        int rc = make_pairs(L, s);
+        if (rc == MST_OK && wait) rc = weights_made(L, false, true, s);
+        if (rc != MST_OK) return rc;
     }
     if (!measured && L->pairs_measured) {
-        tokens = pairs_tokens(L, y, act, T, split_floats);
+        const double making_us = L->pairs_missed ? making_pairs_us(L, false) : 0.0;
+        tokens = pairs_tokens(L, y, act, T, split_floats, making_us);
         if (tokens == 0) {
             L->pairs_unread = mst_layer::PAIRS_UNREAD;
             return MST_OK;

@@ -124,7 +124,7 @@ struct mst_layer {
     mst::PairsView pairs_y, pairs_x;
     static constexpr int PAIRS_UNREAD = 8;
     int pairs_unread = PAIRS_UNREAD;             // hand-overs since a product read them
-    bool pairs_missed = false, pairs_valid = false;      // as those of the planes
+    bool pairs_missed = false, pairs_valid = false;      // as those of the planes (missed: products make them each for itself)
     // A recorded product reads them without making them.  Its replays come when they like, so they are made whenever Wd changes, at any density.
     bool pairs_recorded = false;
     bool pairs_matched = false;    // their slots were chosen for the present active set
@@ -321,7 +321,8 @@ int measure_pairs(mst_layer* L, hipStream_t s);
 // A measurement waits for its stream: an update behind fewer products than these leaves the last one standing.  (Updates are hundreds of
 // steps apart in earnest; a loop that updates after every step would wait in every step.)
 constexpr int PAIRS_CALLS = 64;
-int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split_floats);
+int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split_floats, double making_us);
+double making_pairs_us(const mst_layer* L, bool match);
 int gemm_pairs(const void* A, mst_dtype act, const PairsView& v, float* C, int T, int tokens, hipStream_t s);
 double gemm_two_parts_us(GemmKind kind, mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split);
 bool gemm_pairs_forced();

@@ -686,9 +686,13 @@ static double pairs_us(mst_dtype act, int T, int R, int K, int tokens, double se
     return xcd_rounds(Q, 32, 8, full, lone) * (K / PK_STEP) * (1.0 + 0.8 * second) + (double)cdiv(Q, 32) * ends;
 }
 
-int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split_floats) {
+// Of the packing, with the choice of the pairs or without (measured 64 x 64 to 5120 x 5120, within 2 us).
+double making_pairs_us(const mst_layer* L, bool match) { return 5.0 + 1.5e-6 * (double)L->N + (match ? 14.0 + 1.6e-6 * (double)L->N : 0.0); }
+
+// Tokens of a tile, 0 where the dense kernels are ahead.  making_us: what this product spends on the packed weights before it reads them
+int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split_floats, double making_us) {
     const double d = (double)L->nnz / (double)L->N;
-    if (!L->pairs_y.blocks || L->pairs_missed) return 0;
+    if (!L->pairs_y.blocks) return 0;
     if (gemm_pairs_forced()) return act == MST_F32 ? 128 : 64 * (2 + T % 3);
     if (d > PAIRS_LINE) return 0;
     const int R = y ? L->O : L->I, K = y ? L->I : L->O;
@@ -699,7 +703,7 @@ int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split
     int tokens = 0;
     for (int t : {128, 192, 256}) {
         if (act == MST_F32 && t != 128) break;
-        const double us = pairs_us(act, T, R, K, t, second);
+        const double us = pairs_us(act, T, R, K, t, second) + making_us;
         if (us < best) best = us, tokens = t;
     }
     return tokens;
@@ -711,7 +715,7 @@ bool pairs_wanted(const mst_layer* L) {
     const mst_dtype act = (mst_dtype)L->hint_act;
     auto reads = [&](bool y) {
         const WalkJob job = y ? WALK_FWD : WALK_BWD_INPUT;
-        return use_dense_path(L, job, act, L->hint_T) && !full_precision(L, job, act, L->hint_T) && pairs_tokens(L, y, act, L->hint_T, 0) != 0;
+        return use_dense_path(L, job, act, L->hint_T) && !full_precision(L, job, act, L->hint_T) && pairs_tokens(L, y, act, L->hint_T, 0, 0.0) != 0;
     };
     return reads(true) || reads(false);
 }

@@ -1037,7 +1037,7 @@ int weights_made(mst_layer* L, bool planes, bool pairs, hipStream_t s) {
         MST_HIP(hipStreamSynchronize(s));
     }
     L->planes_valid |= planes;
-    L->pairs_valid |= pairs;
+    L->pairs_valid |= pairs && !L->pairs_missed;
     L->pairs_matched |= pairs;
     return MST_OK;
 }
@@ -1252,7 +1252,7 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
         if (capture != hipStreamCaptureStatusNone) {
             planes = !L->planes_missed && (L->planes_used || (L->planes_y && L->hint_act == MST_BF16));
             L->planes_missed |= L->planes_y && !planes;
-            // (the packed pairs likewise; products that would read them go to the dense kernels once they are missed)
+            // (the packed pairs likewise, if products read them)
             pairs = pairs_kept(L);
             L->pairs_missed |= L->pairs_y.blocks && !pairs;
         } else {

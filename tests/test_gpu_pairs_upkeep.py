@@ -178,6 +178,66 @@ def test_the_packing_stops_where_no_product_reads_it():
     l.right()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_handover_recorded_at_half_density_does_not_bar_the_packed_pairs(dtype):
+    l, side, graph = Layer(0.5, "uniform", dtype), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    assert not l.fwd()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        l.L.sync_values(side)
+    l.update(0.1)
+    for _ in range(3):
+        assert l.fwd() and l.bwd()
+        l.right()
+        l.right_dx()
+        l.L.values().mul_(2.0)
+        l.L.sync_values()
+    torch.cuda.synchronize()
+    step = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(step, stream=side):
+        assert l.fwd(stream=side) and l.bwd(stream=side)
+        l.L.values().mul_(2.0)
+        l.L.sync_values(side)
+    for _ in range(3):
+        step.replay()
+        l.right(0.5)
+        l.right_dx(0.5)
+        assert l.fwd() and l.bwd()
+        l.right()
+        l.right_dx()
+        l.L.values().mul_(0.25)
+        l.L.sync_values()
+
+
+def test_a_handover_recorded_before_the_first_packed_product():
+    """Its replays leave packed weights behind that products read between them."""
+    l, side, graph, product = Layer(0.1), torch.cuda.Stream(), torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    mst.mst_gemm_force_fp32_mfma(128)
+    try:
+        assert not l.fwd()                                   # the dense copy alone
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        l.L.values().mul_(2.0)
+        l.L.sync_values(side)
+    assert l.fwd()
+    l.right()
+    with torch.cuda.graph(product, stream=side):
+        l.fwd(stream=side)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert l.fwd()
+        l.right()
+        graph.replay()
+        torch.cuda.synchronize()
+        product.replay()
+        l.right()
+        assert l.bwd()
+        l.right_dx()
+
+
 def test_a_recorded_product_outlives_the_densities_of_the_packed_pairs():
     l, side, graph = Layer(0.1), torch.cuda.Stream(), torch.cuda.CUDAGraph()
     assert l.fwd()
