@@ -315,7 +315,7 @@ int weights_made(mst_layer* L, bool planes, bool pairs, hipStream_t s);
 // the same at densities of a tenth and below, for both activation types; see gemm_pairs.hip
 PairsView pairs_view(void* mem, int R, int K);
 bool pairs_kept(const mst_layer* L);
-bool pairs_wanted(const mst_layer* L);
+bool pairs_wanted(const mst_layer* L, bool both);
 int make_pairs(mst_layer* L, hipStream_t s);
 int measure_pairs(mst_layer* L, hipStream_t s);
 // A measurement waits for its stream: an update behind fewer products than these leaves the last one standing.  (Updates are hundreds of

@@ -709,15 +709,15 @@ int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split
     return tokens;
 }
 
-// Would Y or dX of a batch like the last one read them?
-bool pairs_wanted(const mst_layer* L) {
+// Would Y or dX (both of them) of a batch like the last one read them?
+bool pairs_wanted(const mst_layer* L, bool both) {
     if (L->hint_T <= 0) return false;
     const mst_dtype act = (mst_dtype)L->hint_act;
     auto reads = [&](bool y) {
         const WalkJob job = y ? WALK_FWD : WALK_BWD_INPUT;
         return use_dense_path(L, job, act, L->hint_T) && !full_precision(L, job, act, L->hint_T) && pairs_tokens(L, y, act, L->hint_T, 0, 0.0) != 0;
     };
-    return reads(true) || reads(false);
+    return both ? reads(true) && reads(false) : reads(true) || reads(false);
 }
 
 }  // namespace mst

@@ -1245,16 +1245,16 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
         // Views that nothing has walked are left out, since the dense copy holds the values for their first walk.
         // A recording refreshes every built view and changes no flag of theirs: its replays come at any time, between
         // calls that walk a view for the first time, and it has not run yet.  It takes the planes along if a product has read them
-        // or the last product call had bfloat16 activations; otherwise they count as missed.
+        // or the last product call had bfloat16 activations that did not go to the packed pairs, in both directions; otherwise they count as missed.
         // (Recorded regardless, a replayed fp32 step of the GPT-2-small block took 1.217 ms instead of 1.194.)
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
         MST_HIP(hipStreamIsCapturing(s, &capture));
         if (capture != hipStreamCaptureStatusNone) {
-            planes = !L->planes_missed && (L->planes_used || (L->planes_y && L->hint_act == MST_BF16));
-            L->planes_missed |= L->planes_y && !planes;
-            // (the packed pairs likewise, if products read them)
+            // (the packed pairs if products read them)
             pairs = pairs_kept(L);
             L->pairs_missed |= L->pairs_y.blocks && !pairs;
+            planes = !L->planes_missed && (L->planes_used || (L->planes_y && L->hint_act == MST_BF16 && !(pairs && pairs_wanted(L, true))));
+            L->planes_missed |= L->planes_y && !planes;
         } else {
             if (views) {
                 row = L->row_walked;

@@ -810,7 +810,7 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
         L->Wd_valid = L->Wd_zeros = true;
         L->planes_valid = L->planes_kept();
         if (L->planes_valid && (rc = make_planes(L, s)) != MST_OK) return rc;
-        L->pairs_valid = pairs_kept(L) && (L->pairs_recorded || pairs_wanted(L));
+        L->pairs_valid = pairs_kept(L) && (L->pairs_recorded || pairs_wanted(L, false));
         L->pairs_matched = false;
         if (L->pairs_valid && (rc = make_pairs(L, s)) != MST_OK) return rc;
         L->pairs_matched = L->pairs_valid;

@@ -253,3 +253,31 @@ def test_a_recorded_product_outlives_the_densities_of_the_packed_pairs():
             l.L.sync_values()
         graph.replay()
         l.right()
+
+
+def test_a_recorded_handover_leaves_out_planes_that_the_packed_pairs_stand_for():
+    l, side, graph = Layer(0.1, "uniform", "bf16"), torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    assert l.fwd() and l.bwd()
+    planes = l.L.buf[-8 * O * I:]
+    torch.cuda.synchronize()
+    planes.fill_(0xFF)
+    with torch.cuda.graph(graph, stream=side):
+        l.L.values().mul_(2.0)
+        l.L.sync_values(side)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert bool((planes == 0xFF).all())
+        assert l.fwd() and l.bwd()
+        l.right()
+        l.right_dx()
+    mst.mst_gemm_force_fp32_mfma(256)                        # products that read the planes after all
+    try:
+        for _ in range(2):
+            graph.replay()
+            torch.cuda.synchronize()
+            l.fwd()
+            assert mst.mst_gemm_last_tile() == 256
+            l.right()
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
