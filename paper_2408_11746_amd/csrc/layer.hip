@@ -845,10 +845,13 @@ __global__ void k_scatter_dense(const float* __restrict__ vals, const int* __res
 // positions each, `rows` whole rows or a part of one: the active values go to their places in a zeroed run of LDS and the run is written
 // once, where a fill of the array with a scatter of single values behind it wrote every line twice.  The other blocks copy 4 KB of
 // the mask each.  (Four layers of a GPT-2-small block, W and M: 72 us with a fill, a scatter and a copy for each, 30 like this; GPT-2-large: 91, 45.)
+// A part of a long row finds its active positions by 256 samples of the row's, and a thread's next four are loaded together.  (Every
+// part read all of its row's, one after the other, each value behind its position: 256 x 65535 full 204 us, now 44, a scatter 67; 32 x
+// 65535 84, 8.4, 10.4; 4000 x 8193 full 175, 110, 125; 1280 x 5120 full 30, 21, 26; 3072 x 768 full 8.2, 5.6, 11.)
 constexpr int EXPORT_RUN = 4096;
 __global__ __launch_bounds__(256) void k_export_dense(const float* __restrict__ vals, const int* __restrict__ flat,
                                                       const int* __restrict__ rowptr, const uint8_t* __restrict__ mask,
-                                                      int64_t nnz, int64_t N, int O, int I, int rows, int parts, unsigned run_blocks,
+                                                      int64_t nnz, int64_t N, int O, int I, int rows, int parts, int part, unsigned run_blocks,
                                                       float* __restrict__ W, uint8_t* __restrict__ M, int* __restrict__ dense_live) {
     __shared__ __attribute__((aligned(16))) float run[EXPORT_RUN];
     const int tid = threadIdx.x;
@@ -858,15 +861,32 @@ __global__ __launch_bounds__(256) void k_export_dense(const float* __restrict__ 
         else for (int64_t i = p; i < N; ++i) M[i] = mask[i];
         return;
     }
-    const int r = (int)(blockIdx.x / (unsigned)parts) * rows, r1 = min(r + rows, O), c0 = (int)(blockIdx.x % (unsigned)parts) * EXPORT_RUN;
-    const int n = min((r1 - r) * I - c0, EXPORT_RUN);
-    const int k0 = nnz > 0 ? rowptr[r] : 0, k1 = nnz > 0 ? rowptr[r1] : 0;
+    const int r = (int)(blockIdx.x / (unsigned)parts) * rows, r1 = min(r + rows, O), c0 = (int)(blockIdx.x % (unsigned)parts) * part;
+    const int n = min((r1 - r) * I - c0, part);
+    int k0 = nnz > 0 ? rowptr[r] : 0, k1 = nnz > 0 ? rowptr[r1] : 0;
     for (int i = 4 * tid; i < n; i += 1024) *reinterpret_cast<float4*>(run + i) = make_float4(0.f, 0.f, 0.f, 0.f);
-    __syncthreads();
     const int64_t base = (int64_t)r * I + c0;
-    for (int k = k0 + tid; k < k1; k += 256) {
-        const int64_t at = (int64_t)flat[k] - base;
-        if (at >= 0 && at < n) run[at] = vals[k];
+    if (parts > 1 && k1 - k0 > 1024) {
+        const int step = (k1 - k0 + 255) / 256, at = k0 + tid * step;
+        const int64_t f = at < k1 ? (int64_t)flat[at] : (int64_t)1 << 32;
+        const int before = __syncthreads_count(f < base), within = __syncthreads_count(f < base + n);
+        k1 = min(k1, k0 + within * step);             // (sample `within` is the first one past the part, `before` the first one in it)
+        k0 += max(before - 1, 0) * step;
+    } else {
+        __syncthreads();
+    }
+    for (int k = k0 + tid; k < k1; k += 1024) {
+        int64_t at[4];
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = min(k + 256 * u, k1 - 1);
+            at[u] = (int64_t)flat[j] - base;
+            v[u] = vals[j];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (at[u] >= 0 && at[u] < n) run[at[u]] = v[u];        // (the last one up to four times, the same value)
     }
     __syncthreads();
     const int n4 = (base & 3) == 0 ? n & ~3 : 0;
@@ -997,9 +1017,10 @@ static int export_dense(const mst_layer* L, float* W, uint8_t* M, int* dense_liv
     const int parts = (int)cdiv(L->I, EXPORT_RUN);
     int rows = std::max(1, std::min(EXPORT_RUN / L->I, L->O / 1024));
     if (rows >= 4) rows &= ~3;
+    const int part = parts > 1 ? (int)(cdiv(cdiv(L->I, parts), 4) * 4) : EXPORT_RUN;
     const unsigned run_blocks = W ? (unsigned)(cdiv(L->O, rows) * parts) : 0u, mask_blocks = M ? (unsigned)cdiv(L->N, 4096) : 0u;
     if (run_blocks + mask_blocks == 0) return MST_OK;
-    k_export_dense<<<run_blocks + mask_blocks, 256, 0, s>>>(L->vals, L->flat, L->rowptr, L->mask, L->nnz, L->N, L->O, L->I, rows, parts,
+    k_export_dense<<<run_blocks + mask_blocks, 256, 0, s>>>(L->vals, L->flat, L->rowptr, L->mask, L->nnz, L->N, L->O, L->I, rows, parts, part,
                                                             run_blocks, W, M, dense_live);
     MST_LAUNCH_CHECK();
     return MST_OK;

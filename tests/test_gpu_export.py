@@ -32,3 +32,24 @@ def test_export(O, I, density):
         if with_M:
             assert torch.equal(oM[:O * I].view(O, I), expect_M)
         assert (oW[O * I if with_W else 0:] == 7.0).all() and (oM[O * I if with_M else 0:] == 9).all()   # nothing past the end
+
+
+@pytest.mark.parametrize("O,I,density", [(2, 4100, 0.26), (3, 8193, 0.2), (2, 16381, 0.5), (1, 65535, 1.0), (2, 65533, 0.016), (2, 65534, 0.9)])
+def test_parts_of_long_rows(O, I, density):
+    """Rows of several parts with more than 1024 active positions, whose parts find theirs by samples: even ones, and rows whose
+    positions all lie at one end."""
+    gen = torch.Generator().manual_seed(I)
+    W = torch.randn(O, I, generator=gen)
+    M = torch.rand(O, I, generator=gen) < density
+    if O > 1:
+        at = I - int(density * I) if I % 2 else 0
+        M[1] = False
+        M[1, at:at + int(density * I)] = True
+    count = int(M.sum())
+    layer = mst.Layer(O, I, count, "cuda")
+    ws = torch.empty(mst.mst_workspace_bytes(O, I, count, 64), dtype=torch.uint8, device="cuda")
+    layer.load_dense(W.cuda(), M.to(torch.uint8).cuda(), ws)
+    out = torch.full((O * I + 64,), 7.0, device="cuda")
+    layer.export_dense(out, None)
+    out = out.cpu()
+    assert torch.equal(out[:O * I].view(O, I), torch.where(M, W, torch.zeros(()))) and (out[O * I:] == 7.0).all()
