@@ -281,3 +281,14 @@ def test_a_recorded_handover_leaves_out_planes_that_the_packed_pairs_stand_for()
             l.right()
     finally:
         mst.mst_gemm_force_fp32_mfma(0)
+
+
+@pytest.mark.parametrize("tokens", [2048, 5120, 9216])
+def test_full_rows_go_to_the_dense_kernels(tokens):
+    """Where every step goes a second time and the dense kernel takes 1.85 to 2.1 times as long as the steps of the first kind."""
+    l = Layer(0.1, "rows")
+    assert not l.fwd(tokens)
+    l.right(tokens=tokens)
+    l.load(0.1, "uniform")
+    assert l.fwd(tokens)
+    l.right(tokens=tokens)
