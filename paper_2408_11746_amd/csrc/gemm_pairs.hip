@@ -607,15 +607,15 @@ static int launch_pairs(const void* A, const PairsView& v, float* C, int T, int 
 
 // What a step of the second kind takes against one of the first: nothing goes to LDS beside its products, and a wavefront without any
 // waits for the others.
-constexpr double SECOND_STEP = 1.2;
+constexpr double SECOND_STEP_F32 = 1.4, SECOND_STEP_BF16 = 1.3;
 
-// Microseconds of an fp32 product with `full` token tiles of 128, the rest in tiles of 64.  (Per step of 64 k: 1.52 with 128 tokens
-// on every CU, 1.0 on a few, 0.87 and 0.75 with 64: the weights of a step cost the same for either.)
+// Microseconds of an fp32 product with `full` token tiles of 128, the rest in tiles of 64.  (Per step of 64 k: 1.41 with 128 tokens
+// on every CU, 0.93 on a few, 0.81 and 0.70 with 64: the weights of a step cost the same for either.)
 static double pairs_f32_us(int T, int R, int K, int full, double second) {
     const int64_t bands = cdiv(R, PB_ROWS), rest = std::max(0, T - 128 * full);
     const int64_t Q = cdiv(full * bands, 8), QT = cdiv(cdiv(rest, 64) * bands, 8);
-    return (xcd_rounds(Q, 32, 8, 1.52, 1.0) + xcd_rounds(QT, 32, 8, 0.87, 0.75)) * (K / PK_STEP) * (1.0 + SECOND_STEP * second) +
-           (double)cdiv(Q, 32) * 8.0 + (double)cdiv(QT, 32) * 5.0;
+    return (xcd_rounds(Q, 32, 8, 1.41, 0.93) + xcd_rounds(QT, 32, 8, 0.81, 0.70)) * (K / PK_STEP) * (1.0 + SECOND_STEP_F32 * second) +
+           (double)cdiv(Q, 32) * 7.4 + (double)cdiv(QT, 32) * 4.6;
 }
 
 // Token tiles of 128 of an fp32 product.  A CU holds one workgroup, so 320 tiles are two rounds, the second one a quarter full:
@@ -687,18 +687,18 @@ static double pairs_us(mst_dtype act, int T, int R, int K, int tokens, double se
     if (tokens == 256) full = 1.95, lone = 1.3, ends = 9.0;
     else if (tokens == 192) full = 1.5, lone = 0.95, ends = 7.0;
     else full = 1.2, lone = 0.8, ends = 5.0;
-    return xcd_rounds(Q, 32, 8, full, lone) * (K / PK_STEP) * (1.0 + SECOND_STEP * second) + (double)cdiv(Q, 32) * ends;
+    return xcd_rounds(Q, 32, 8, full, lone) * (K / PK_STEP) * (1.0 + SECOND_STEP_BF16 * second) + (double)cdiv(Q, 32) * ends;
 }
 
 // Of the packing, with the choice of the pairs or without (measured 64 x 64 to 5120 x 5120, within 2 us).
 double making_pairs_us(const mst_layer* L, bool match) { return 5.0 + 1.5e-6 * (double)L->N + (match ? 14.0 + 1.6e-6 * (double)L->N : 0.0); }
 
 // Tokens of a tile, 0 where the dense kernels are ahead.  making_us: what this product spends on the packed weights before it reads them
-// The modelled times of 1040 products (layers of 256 to 6000, 1024 to 16384 tokens, densities 0.03 to 0.12, a quarter of them with full rows) are, of
-// the measured ones: fp32 1.05 (sd 0.06) where few steps go a second time, the dense kernels there 1.02 (0.10); bfloat16 1.17, 1.10 and 1.18
-// (0.05) for 128, 192 and 256 tokens, dense 1.23 (0.06).  The choice loses 0.4 % (fp32) and 0.25 % against the best of all kernels, 31
-// and 12 % at the worst, and leaves 4 of 670 and 3 of 370 products slower than the dense kernels by more than 3 % (9 % at the
-// worst); with second steps at 0.8 of a first one 34 and 11 were, up to 23 %.  On 302 and 98 others: loss 0.6 and 0.3 %, none and 2 slower.
+// 3040 products on three cards (layers of 256 to 6000, 1024 to 16384 tokens, densities 0.03 to 0.12, a quarter with full rows): the modelled times
+// are, of the measured ones, 0.93 to 1.02 by card in fp32 (sd 0.06, where few steps go a second time), of the dense kernels there 0.96 to
+// 1.04 (0.10); in bfloat16 1.12 to 1.21, 1.05 to 1.13 and 1.13 to 1.21 (0.05) for 128, 192 and 256 tokens, dense 1.18 to 1.25 (0.07).  The choice
+// loses 0.3 % against the best of all kernels, 21 % at the worst, and leaves 9 of 2062 fp32 and 2 of 978 bfloat16 products slower than the
+// dense kernels by more than 3 % (12 % at the worst).  With second steps at 0.8 of a first one and first ones 7 % dearer in fp32: 94 and 33, 23 %.
 int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split_floats, double making_us) {
     const double d = (double)L->nnz / (double)L->N;
     if (!L->pairs_y.blocks) return 0;
