@@ -204,7 +204,9 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
 // ------------------------------------------------------------------ packing
 // Block = 64 o x 64 i of the dense weights, read once for both views: two tiles of 32 rows of either, one step.  A wavefront
 // packs a tile; lane = row and 16 k of every 32.  Bound by the 8.5 bytes per position that it reads and writes.
-__global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W, int I, const PairsView y, const PairsView x) {
+// first: the packing behind a choice of slots; block 0 counts the steps that go a second time (a launch of its own: four layers of a
+// GPT-2-small block 19 us longer in the first pass on new masks).
+__global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W, int I, const PairsView y, const PairsView x, bool first) {
     constexpr int LD = PK_STEP + 1;
     __shared__ float tile[64 * LD];
     __shared__ uint8_t pair_s[2][PK_PAIRS];           // dword in a slot
@@ -288,6 +290,15 @@ __global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W,
     // the two tiles go together
     const bool on = (over_s[wave] | over_s[wave ^ 1]) != 0;
     if (lane == 0 && (wave & 1) == 0) reinterpret_cast<uint8_t*>(v.flags + bk)[t >> 1] = on ? 1 : 0;
+    if (first && blockIdx.x == 0 && blockIdx.y == 0) {            // (a wavefront each)
+        const PairsView& of = wave == 0 ? y : x;
+        if (wave < 2) {
+            uint32_t c = 0;
+            for (int e = lane; e < of.bands * of.nk; e += 64) c += of.over[e];
+            for (int d = 32; d >= 1; d >>= 1) c += (uint32_t)__shfl_xor((int)c, d, 64);
+            if (lane == 0) y.count[wave] = c;
+        }
+    }
     if (!on) return;
 #pragma unroll
     for (int ss = 0; ss < 2; ++ss) store(blk + (int64_t)v.nk * PK_BLOCK + ss * PW_SUB, hi2[ss], lo2[ss], ix2[ss]);
@@ -300,7 +311,7 @@ int make_pairs(mst_layer* L, hipStream_t s) {
         k_match_pairs<<<(unsigned)(y.bands * y.nk + x.bands * x.nk), 256, 0, s>>>(L->mask, L->I, y, x);
         MST_LAUNCH_CHECK();
     }
-    k_pack_pairs<<<dim3((unsigned)(L->I / 64), (unsigned)(L->O / 64)), 256, 0, s>>>(L->Wd, L->I, y, x);
+    k_pack_pairs<<<dim3((unsigned)(L->I / 64), (unsigned)(L->O / 64)), 256, 0, s>>>(L->Wd, L->I, y, x, !L->pairs_matched);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
@@ -653,20 +664,7 @@ bool pairs_kept(const mst_layer* L) { return !L->pairs_missed && (L->pairs_recor
 // How uneven the present mask is: the share of the steps of a band that go a second time, against that of a uniformly random mask.
 // By the mask and not by the weights: those that an update has grown are zero until the next step.  Read back by the first
 // product that reads the packed weights of a mask, which waits for it.
-__global__ __launch_bounds__(256) void k_count_second(const PairsView y, const PairsView x) {
-    __shared__ uint32_t sum;
-    const PairsView& v = blockIdx.x == 0 ? y : x;
-    if (threadIdx.x == 0) sum = 0;
-    __syncthreads();
-    uint32_t n = 0;
-    for (int e = threadIdx.x; e < v.bands * v.nk; e += 256) n += v.over[e];
-    if (n) atomicAdd(&sum, n);
-    __syncthreads();
-    if (threadIdx.x == 0) y.count[blockIdx.x] = sum;
-}
 int measure_pairs(mst_layer* L, hipStream_t s) {
-    k_count_second<<<2, 256, 0, s>>>(L->pairs_y, L->pairs_x);
-    MST_LAUNCH_CHECK();
     uint32_t second[2] = {0, 0};
     MST_HIP(hipMemcpyAsync(second, L->pairs_y.count, 8, hipMemcpyDeviceToHost, s));
     MST_HIP(hipStreamSynchronize(s));
