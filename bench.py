@@ -207,11 +207,19 @@ def split_gemm_applies(M, N, K):
     return M % 128 == 0 and N % 128 == 0 and K % 64 == 0
 
 
-PAIRS_DENSITY = 0.12     # dense-path Y and dX up to here run on the 2-of-4 sparse matrix instructions (gemm_pairs.hip)
+PAIRS_TILE = 24     # what mst_gemm_last_tile says of a product on the 2-of-4 sparse matrix instructions (gemm_pairs.hip)
 
 
-def on_pairs(density, O, I):
-    return density <= PAIRS_DENSITY and O % 64 == 0 and I % 64 == 0
+def on_pairs(mst, L, call, stream):
+    """Did the library run Y (dX: of the one-call backward too, whose dense product may split its contraction besides) of this dense-path layer
+    there?  One untimed call."""
+    if call == "fwd":
+        mst.mst_sparse_fc_fwd(L.layer, L.X, L.Y, L.T, L.act, stream)
+    elif call in ("bwd_input", "bwd"):
+        mst.mst_sparse_fc_bwd_input(L.layer, L.dY, L.dX, L.T, L.act, stream)
+    else:
+        return False
+    return mst.mst_gemm_last_tile() == PAIRS_TILE
 
 
 def dense_gemm_roofline(flops, ms, act, M, N, K, bf16_products=1.0, executed=1.0):
@@ -458,7 +466,7 @@ def run_block(args, name, mst, synth, torch, lds_peak, with_cpu_baseline):
         drow["dense_mnk"] = {"fwd": (T, dL.O, dL.I), "bwd_input": (T, dL.I, dL.O)}.get(drow["call"], (dL.O, dL.I, T))
         # bfloat16 activations: Y, dX = 2 MFMA products per term, weight gradient 1, the one-call backward both
         drow["bf16_products"] = {"fwd": 2.0, "bwd_input": 2.0, "bwd_weight": 1.0, "bwd": 1.5}[drow["call"]]
-        if on_pairs(density, dL.O, dL.I):
+        if on_pairs(mst, dL, drow["call"], stream):
             # the weight gradient multiplies everything: of the one-call backward's products one (bf16) or three (fp32) per term
             drow["executed"] = {"fwd": 0.5, "bwd_input": 0.5, "bwd_weight": 1.0,
                                 "bwd": 2.0 / 3.0 if act == "bf16" else 0.75}[drow["call"]]
@@ -646,6 +654,7 @@ def run_sweep(args, mst, synth, torch, lds_peak, with_cpu_baseline):
     ev = []            # (position, layer index, call, start event, end event)
     nnz_at = {}        # position -> per-layer active counts (host arithmetic of the update, no read-back)
     dense_at = {}      # position -> per layer: does the library route Y and dX to the masked dense contraction
+    tile_at = {}       # (position, layer index, call) -> which dense kernel ran it (of the untimed steps)
 
     def run_step(t, record):
         pos = t % ncyc
@@ -669,6 +678,8 @@ def run_sweep(args, mst, synth, torch, lds_peak, with_cpu_baseline):
                     nxt = mark(stream)
                     ev.append((pos, li, call, last, nxt))
                     last = nxt
+                else:
+                    tile_at[pos, li, call] = mst.mst_gemm_last_tile()
         fork = None
         grads_first = args.update_streams >= 2 and not args.fused_update
         multi = args.update_streams == 3 and not args.fused_update
@@ -800,7 +811,7 @@ def run_sweep(args, mst, synth, torch, lds_peak, with_cpu_baseline):
                 if dense_path:
                     mnk = (T, L.O, L.I) if call == "fwd" else (T, L.I, L.O)
                     r = dense_gemm_roofline(L.flops_dense_grad(), ms, "f32", *mnk,
-                                            executed=0.5 if on_pairs(nnz / (L.O * L.I), L.O, L.I) else 1.0)
+                                            executed=0.5 if tile_at[p, li, call] == PAIRS_TILE else 1.0)
                     row.update(dense_flops=L.flops_dense_grad(), mfma_tflops=r["achieved"], mfma_frac=r["frac"],
                                mfma_dtype=r["mfma_dtype"])
                 calls.append(row)
