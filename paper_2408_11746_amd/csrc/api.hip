@@ -78,11 +78,9 @@ static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, i
     if (tokens == 0) return MST_OK;
     const bool measured = L->pairs_measured;
     bool made = false;
-    if (!L->Wd_valid) {
-        made = L->pairs_recorded;                     // (then the dense copy brings them along)
-        const int rc = refresh_dense_copy(L, s);
-        if (rc != MST_OK) return rc;
-    }
+    const int rcd = ensure_dense_copy(L, s, &made);
+    if (rcd != MST_OK) return rcd;
+    made &= L->pairs_recorded;                        // (then the dense copy brings them along)
     bool recording = false;
     if (!(L->pairs_valid && L->pairs_recorded && measured)) {
         hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -127,12 +125,9 @@ static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, i
 // waits: two that meet write the same bits).
 static int ensure_weights(const mst_layer* Lc, bool y, mst_dtype act, int M, int N, int Kdim, bool full, const uint16_t*& planes, hipStream_t s) {
     mst_layer* L = const_cast<mst_layer*>(Lc);       // caches of vals[], not layer state
-    int rc = MST_OK;
-    bool made = false;                                // (a recording that makes them does not say that they are there)
-    if (!L->Wd_valid) {
-        made = L->planes_kept();
-        rc = refresh_dense_copy(L, s);
-    }
+    bool made = false;
+    int rc = ensure_dense_copy(L, s, &made);
+    made &= L->planes_kept();                         // (a recording that makes them does not say that they are there)
     planes = nullptr;
     if (rc != MST_OK || !gemm_wants_planes(act, M, N, Kdim, full)) return rc;
     planes = y ? L->planes_y : L->planes_x;

@@ -107,6 +107,7 @@ struct mst_layer {
     float* Wd = nullptr;       // [N] dense W . M, maintained only while the dense path is in use
     bool Wd_valid = false;     // Wd equals W . M
     bool Wd_zeros = false;     // Wd is zero at every inactive position (survives a change of the values)
+    bool Wd_pending = false;   // ... but it was formed by a recording, which may not have run yet: eager calls form it anew
     // The two bfloat16 parts of Wd in the order that the products of bfloat16 activations want (gemm_planes.hip), for Y and for
     // dX; null where no such product has whole tiles.  Made by the first product that reads them, kept up with Wd from then on:
     // sync_values and the updates that leave Wd valid make them again.  A hand-over that was recorded while the layer
@@ -347,7 +348,7 @@ int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int 
                              float* split_ws = nullptr, int64_t split_ws_floats = 0);
 int dense_products_bwd_weight(const mst_layer* L, const void* dY, const void* X, float* dW, int T,
                               mst_dtype act, const Workspace& ws, hipStream_t s, bool full);
-int refresh_dense_copy(mst_layer* L, hipStream_t s);
+int ensure_dense_copy(mst_layer* L, hipStream_t s, bool* refreshed);
 // heavy rows of the forward product; see heavy.hip
 int heavy_rows_enable(int on);
 int heavy_rows_mode();

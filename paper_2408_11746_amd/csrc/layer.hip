@@ -985,7 +985,7 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
         mst_layer* L = items[x].L;
         L->views_valid = true;
         L->row_stale = L->col_stale = false;
-        if (!items[x].keep_dense_copy) L->Wd_valid = L->Wd_zeros = L->planes_valid = L->pairs_valid = L->pairs_matched = false;
+        if (!items[x].keep_dense_copy) L->Wd_valid = L->Wd_zeros = L->Wd_pending = L->planes_valid = L->pairs_valid = L->pairs_matched = false;
     }
     return MST_OK;
 }
@@ -1026,8 +1026,8 @@ static int export_dense(const mst_layer* L, float* W, uint8_t* M, int* dense_liv
     return MST_OK;
 }
 
-int refresh_dense_copy(mst_layer* L, hipStream_t s) {
-    if (!L->Wd_zeros) {
+static int refresh_dense_copy(mst_layer* L, bool recording, hipStream_t s) {
+    if (!L->Wd_zeros || L->Wd_pending) {
         const int rc = export_dense(L, L->Wd, nullptr, L->dense_live, s);
         if (rc != MST_OK) return rc;
     } else if (L->nnz > 0) {                         // the active set is unchanged since the last time: only values move
@@ -1035,12 +1035,25 @@ int refresh_dense_copy(mst_layer* L, hipStream_t s) {
         MST_LAUNCH_CHECK();
     }
     L->Wd_valid = L->Wd_zeros = true;
+    L->Wd_pending = recording;
     L->planes_valid = L->pairs_valid = false;
     const bool planes = L->planes_kept(), pairs = L->pairs_recorded;
     if (!planes && !pairs) return MST_OK;
     int rc = planes ? make_planes(L, s) : MST_OK;    // (recorded products read them without asking)
     if (rc == MST_OK && pairs) rc = make_pairs(L, s);
     return rc == MST_OK ? weights_made(L, planes, pairs, s) : rc;
+}
+
+// refreshed: it was out of date, or formed by a recording
+int ensure_dense_copy(mst_layer* L, hipStream_t s, bool* refreshed) {
+    *refreshed = false;
+    if (L->Wd_valid && !L->Wd_pending) return MST_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    MST_HIP(hipStreamIsCapturing(s, &capture));
+    const bool recording = capture != hipStreamCaptureStatusNone;
+    if (L->Wd_valid && recording) return MST_OK;
+    *refreshed = true;
+    return refresh_dense_copy(L, recording, s);
 }
 
 // The planes of Wd (its packed pairs) were made on s, by a product and not by the hand-over or the update that changed the
@@ -1106,10 +1119,9 @@ int ensure_fresh(const mst_layer* Lc, bool row, bool col, hipStream_t s) {
 int ensure_views(const mst_layer* Lc, const Workspace& ws, hipStream_t s) {
     if (Lc->views_valid) return MST_OK;
     mst_layer* L = const_cast<mst_layer*>(Lc);       // a cache of (mask, vals), not layer state
-    if (!L->Wd_valid) {
-        const int rc = refresh_dense_copy(L, s);
-        if (rc != MST_OK) return rc;
-    }
+    bool refreshed;
+    const int rc = ensure_dense_copy(L, s, &refreshed);
+    if (rc != MST_OK) return rc;
     const BuildItem item{L, L->Wd, ws, true};
     return build_views(&item, 1, s);
 }

@@ -743,7 +743,7 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
         float* const Wnew = with_views ? ws.Wd : L->Wd;
         if (with_views) views[n_views++] = BuildItem{L, ws.Wd, ws, false};
         else canonical[n_canonical++] = BuildItem{L, L->Wd, ws, false};
-        if (!with_views && !L->Wd_zeros && (rc = fill_u32(L->Wd, 0u, N, s)) != MST_OK) return rc;
+        if (!with_views && (!L->Wd_zeros || L->Wd_pending) && (rc = fill_u32(L->Wd, 0u, N, s)) != MST_OK) return rc;
         uint64_t* const st0 = ws.sel_state;
         // During the selections the mask still means "active before this update" for every position
         // a later selection looks at: positions grown by gradient become active at once (random
@@ -808,6 +808,7 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
     for (int x = 0; x < n_canonical; ++x) {
         mst_layer* L = canonical[x].L;
         L->Wd_valid = L->Wd_zeros = true;
+        L->Wd_pending = false;
         L->planes_valid = L->planes_kept();
         if (L->planes_valid && (rc = make_planes(L, s)) != MST_OK) return rc;
         L->pairs_valid = pairs_kept(L) && (L->pairs_recorded || pairs_wanted(L, false));
