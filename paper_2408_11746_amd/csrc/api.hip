@@ -209,9 +209,12 @@ int mst_sparse_fc_fwd(const mst_layer_t* L, const void* X_dev, float* Y_dev, int
     hipStream_t s = (hipStream_t)stream;
     note_call(L, act, T);
     // (unbuilt views and no workspace to build them with: the dense product, same result within tolerance)
-    if (use_dense_path(L, WALK_FWD, act, T) || !L->views_valid)
+    bool views;
+    int rc = views_there(L, s, &views);
+    if (rc != MST_OK) return rc;
+    if (use_dense_path(L, WALK_FWD, act, T) || !views)
         return dense_products_fwd(L, X_dev, Y_dev, T, act, s, full_precision(L, WALK_FWD, act, T));
-    const int rc = spmm(L, L->row, X_dev, Y_dev, T, act, s);
+    rc = spmm(L, L->row, X_dev, Y_dev, T, act, s);
     if (rc != MST_OK || !L->heavy_on) return rc;
     return heavy_fwd(L, X_dev, Y_dev, T, act, s);        // the rows the view leaves out (returns at once without any)
 }
@@ -222,7 +225,10 @@ int mst_sparse_fc_bwd_input(const mst_layer_t* L, const void* dY_dev, float* dX_
     if (!L->built) return MST_ERR_STATE;
     hipStream_t s = (hipStream_t)stream;
     note_call(L, act, T);
-    if (use_dense_path(L, WALK_BWD_INPUT, act, T) || !L->views_valid)
+    bool views;
+    const int rc = views_there(L, s, &views);
+    if (rc != MST_OK) return rc;
+    if (use_dense_path(L, WALK_BWD_INPUT, act, T) || !views)
         return dense_products_bwd_input(L, dY_dev, dX_dev, T, act, s, full_precision(L, WALK_BWD_INPUT, act, T));
     return spmm(L, L->col, dY_dev, dX_dev, T, act, s);
 }
@@ -301,7 +307,7 @@ int mst_layer_uses_dense(const mst_layer_t* L, mst_dtype act, int T, int weight_
     // Y and dX have no workspace to build unbuilt views with: they then run dense whatever the density
     if (weight_gradient == 2) return use_fused_backward(L, act, T) ? 0 : 1;
     if (weight_gradient == 0 || weight_gradient == 3)
-        return use_dense_path(L, weight_gradient == 0 ? WALK_FWD : WALK_BWD_INPUT, act, T) || !L->views_valid ? 1 : 0;
+        return use_dense_path(L, weight_gradient == 0 ? WALK_FWD : WALK_BWD_INPUT, act, T) || !L->views_valid || L->views_pending ? 1 : 0;
     return use_dense_weight_grad(L, act, T) ? 1 : 0;
 }
 

@@ -139,6 +139,7 @@ struct mst_layer {
     // (path choice at the batch size and type of the last product call) leaves them unbuilt; a
     // call that needs them and has a workspace builds them, one without runs the dense product.
     bool views_valid = false;
+    bool views_pending = false;    // ... but they were built by a recording, which may not have run yet: eager calls treat them as unbuilt
     // While a dense copy is in use mst_layer_sync_values refreshes the entries of a built view only if a product
     // has ever walked that view of the layer (recorded products included: recording is a call, and its replays
     // outlive rebuilt views); the entries of the others are stale and take the dense copy's values before their
@@ -290,6 +291,7 @@ struct UpdateItem {
 int build_views(const BuildItem* items, int n, hipStream_t s);          // n up to BATCH_MAX
 int build_canonical(const BuildItem* items, int n, hipStream_t s);
 int ensure_views(const mst_layer* L, const Workspace& ws, hipStream_t s);
+int views_there(const mst_layer* L, hipStream_t s, bool* there);
 bool views_wanted(const mst_layer* L);
 int ensure_fresh(const mst_layer* L, bool row, bool col, hipStream_t s);
 // the products of the sparse path; see walk.hip

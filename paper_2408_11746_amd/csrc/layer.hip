@@ -984,7 +984,7 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
     for (int x = 0; x < n; ++x) {
         mst_layer* L = items[x].L;
         L->views_valid = true;
-        L->row_stale = L->col_stale = false;
+        L->views_pending = L->row_stale = L->col_stale = false;
         if (!items[x].keep_dense_copy) L->Wd_valid = L->Wd_zeros = L->Wd_pending = L->planes_valid = L->pairs_valid = L->pairs_matched = false;
     }
     return MST_OK;
@@ -1117,13 +1117,29 @@ int ensure_fresh(const mst_layer* Lc, bool row, bool col, hipStream_t s) {
 
 // The views of a layer whose last update left them unbuilt, from the mask and the dense copy.
 int ensure_views(const mst_layer* Lc, const Workspace& ws, hipStream_t s) {
-    if (Lc->views_valid) return MST_OK;
+    bool there, refreshed;
+    int rc = views_there(Lc, s, &there);
+    if (rc != MST_OK || there) return rc;
     mst_layer* L = const_cast<mst_layer*>(Lc);       // a cache of (mask, vals), not layer state
-    bool refreshed;
-    const int rc = ensure_dense_copy(L, s, &refreshed);
+    rc = ensure_dense_copy(L, s, &refreshed);
     if (rc != MST_OK) return rc;
     const BuildItem item{L, L->Wd, ws, true};
-    return build_views(&item, 1, s);
+    rc = build_views(&item, 1, s);
+    if (rc != MST_OK) return rc;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    MST_HIP(hipStreamIsCapturing(s, &capture));
+    L->views_pending = capture != hipStreamCaptureStatusNone;
+    return MST_OK;
+}
+
+// Can a call on s walk the views?
+int views_there(const mst_layer* L, hipStream_t s, bool* there) {
+    *there = L->views_valid;
+    if (!L->views_valid || !L->views_pending) return MST_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    MST_HIP(hipStreamIsCapturing(s, &capture));
+    *there = capture != hipStreamCaptureStatusNone;
+    return MST_OK;
 }
 
 // After an update: will a sparse kernel walk the views?  Judged at the batch size and type of
