@@ -70,7 +70,8 @@ typedef enum { MST_PATH_AUTO = 0, MST_PATH_SPARSE = 1, MST_PATH_DENSE = 2 } mst_
  * mst_sparse_fc_bwd_weight, mst_sparse_fc_bwd_weight_update) build them first whenever a sparse
  * kernel is due; mst_sparse_fc_fwd and mst_sparse_fc_bwd_input, which carry none, compute the
  * same product with the dense contraction whatever the density; mst_sparse_fc_bwd_weight_static
- * returns MST_ERR_STATE; mst_layer_format_stats reports zero stored entries. */
+ * returns MST_ERR_STATE; mst_layer_format_stats reports zero stored entries.  (Where the call that builds them is
+ * recorded into a graph the last two read them as they are, so replay it first; products that are not recorded treat them as unbuilt.) */
 
 /* Hyper-parameters of Sec. 3.1 / 3.2 (Table "Private hyperparameters of MST"). */
 typedef struct {
@@ -95,9 +96,11 @@ int mst_last_hip_error(void);           /* hipError_t of the last failing HIP ca
 /* ------------------------------------------------------------------ layers */
 
 /* Bytes of device memory a layer of shape [O x I] needs to hold up to nnz_capacity
- * active weights: mask, values, both index views, the dense weight copy (4 bytes per position) and, if O and I are
- * multiples of 32 and one of them of 256, room for the two split copies that products of bfloat16 activations
- * read (8 bytes per position, whatever the activations are; untouched with fp32 ones).  0 on invalid arguments. */
+ * active weights: mask, values, both index views, the dense weight copy (4 bytes per position), if O and I are
+ * multiples of 32 and one of them of 256 room for the two split copies that products of bfloat16 activations
+ * read (8 bytes per position, whatever the activations are; untouched with fp32 ones), and if O and I are multiples of
+ * 64 room for the packed copies that products on the sparse matrix instructions read (8.5 bytes per position, more where
+ * O or I is no multiple of 256; untouched until such a product runs).  0 on invalid arguments. */
 size_t mst_layer_device_bytes(int O, int I, int64_t nnz_capacity);
 
 /* Bytes of workspace sufficient for every call below on a layer of this shape with
@@ -129,7 +132,8 @@ int mst_layer_export_dense(const mst_layer_t* layer, float* W_dev, uint8_t* M_de
 /* The active weights as one fp32 vector in ascending flat-index order, for the caller's
  * optimiser to update in place.  After changing them call mst_layer_sync_values: it copies
  * the values into whatever the products read (the entries of the index views, a dense weight copy
- * that is in use) with one kernel on `stream`, nothing else; products recorded into a HIP graph
+ * that is in use) with one kernel on `stream`, and makes the split and the packed copies of the weights
+ * again that products read (one kernel each); products recorded into a HIP graph
  * therefore see the new values on their next replay, and no product sees values that have not been
  * handed over.  (While a dense copy is in use, a view that no product of the layer has walked yet is
  * left out; the call that walks it first copies the values from there and waits for that once.)  On a
@@ -137,7 +141,9 @@ int mst_layer_export_dense(const mst_layer_t* layer, float* W_dev, uint8_t* M_de
  * use, walked or not; a view that is built, or a dense copy that comes into use, after the recording
  * is not in it.  (The split copy of the weights that products of bfloat16 activations read, see mst_sparse_fc_fwd, is
  * recorded with it if such a product has read it or the layer's last product call had bfloat16
- * activations; after a recording without it these products make the copy anew in every call.)  Every
+ * activations that do not read the packed copies for both Y and dX; the packed copies are recorded with it if one of the last eight
+ * hand-overs was read by a product on them.  After a recording without one of them the products that read it make it anew in
+ * every call, for the rest of the layer's life: record behind a step or two at the density at which the replays will run.)  Every
  * mask update changes the set and therefore the meaning of position k of this vector. */
 int mst_layer_values(mst_layer_t* layer, float** vals_dev, int64_t* nnz);
 int mst_layer_sync_values(mst_layer_t* layer, mst_stream_t stream);
@@ -198,6 +204,10 @@ int mst_heavy_rows(int on);
  * layer, also after one that was only recorded, and the first product that makes the dense copy again after a loading or an
  * update that built the views -- makes it and waits for that on `stream`, so that products on other streams need an order
  * after the hand-over of the values alone; hand-overs and the other updates keep it up.
+ * Up to a density of 0.12, Y and dX of either type that would take the dense kernels with two bfloat16 values per fp32 operand read packed
+ * copies of the weights instead where that is faster (O and I multiples of 64; mst_gemm_force_fp32_mfma, 24).  They are made and waited for in the same way, and
+ * the first eager product on a mask reads back how evenly its rows fill them, which decides whether that mask uses them: it waits too.
+ * A mask is a new one after mst_layer_load_dense, and after an update with 64 or more products of the layer before it.
  * While a graph is recorded nothing waits: the recorded product then carries the making with it.) */
 int mst_sparse_fc_fwd(const mst_layer_t* layer, const void* X_dev, float* Y_dev, int T,
                       mst_dtype act, mst_stream_t stream);
