@@ -129,10 +129,10 @@ def test_recorded_products_and_handovers(warm):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_automatic_choice(dtype):
-    """Whole tiles at a density of a tenth go there, half-dense ones do not; an uneven mask goes where it was measured to belong."""
+    """Whole tiles at a density of a tenth go there, half-dense ones do not, nor Y of a mask with full rows, whose every step goes a second time."""
     mst.mst_gemm_force_fp32_mfma(0)
     T, I, O = 8192, 768, 3072
-    for density, mask, want in ((0.1, "uniform", True), (0.5, "uniform", False), (0.1, "powerlaw", None)):
+    for density, mask, want in ((0.1, "uniform", True), (0.5, "uniform", False), (0.1, "powerlaw", False)):
         W, M = synth.make_layer(5, 1, I, O, density, mask)
         rig = Rig(W, M, T)
         X = torch.randn((T, I), dtype=torch.float32, device=DEV)
@@ -140,7 +140,7 @@ def test_automatic_choice(dtype):
         Y = torch.empty((T, O), dtype=torch.float32, device=DEV)
         mst.mst_sparse_fc_fwd(rig.layer, x, Y, T, mst.MST_BF16 if dtype == "bf16" else mst.MST_F32)
         torch.cuda.synchronize()
-        assert want is None or (mst.mst_gemm_last_tile() == PAIRS) == want, (density, mask)
+        assert (mst.mst_gemm_last_tile() == PAIRS) == want, (density, mask)
         ref = x[:64].double() @ torch.from_numpy((W * M).astype(np.float64)).to(DEV).T
         assert rel_err(Y[:64].cpu().numpy(), ref.cpu().numpy()) <= PARTS, (density, mask)
 
