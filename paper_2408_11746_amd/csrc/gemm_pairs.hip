@@ -18,11 +18,11 @@
 //     cold activations 270 us, so 248).
 //   - The operands of a step's last products are in registers when the wavefronts meet, so the first ones of the next step are
 //     read beside them (Y of 1280 -> 5120, 0.05: 203 -> 189 us).
-// Measured (us, before = the dense kernels; 8192 tokens, fp32, 0.10): Y of 1280 -> 5120 281 -> 197, dX of it 304 -> 243; Y of 768 ->
-// 3072 114 -> 90, dX of it 123 -> 92.  16384 tokens, bfloat16, 0.05: Y of 1024 -> 4096 234 -> 164, dX 198 -> 135.
+// Measured (us, before = the dense kernels; 8192 tokens, fp32, 0.10): Y of 1280 -> 5120 281 -> 196, dX of it 304 -> 223; Y of 768 ->
+// 3072 114 -> 90, dX of it 123 -> 92.  16384 tokens, bfloat16, 0.05: Y of 1024 -> 4096 234 -> 144, dX 198 -> 118.
 // What bounds it: the matrix cores take 18 ns an instruction with the whole chip on them (1.75 GHz), 0.86 of the 1.4 us of a
 // step of fp32 and 1.15 of the 1.95 of bfloat16; the conversions and stores of the activations between the products (10 %), and the
-// outputs of all workgroups at once (8 us a round) are the most of the rest.
+// outputs of all workgroups at once (7 to 9 us a round) are the most of the rest.
 #include <type_traits>
 #include <utility>
 
@@ -72,7 +72,7 @@ __device__ __forceinline__ uint32_t wave_min(uint32_t x) {
 }
 
 // Block = (view, band, step); y first.  Bound by latencies: the mask's lines (all of a thread's loads go out together; eight pairs of them at a
-// time and counts looked up lane by lane: 28 us at 5120 x 1280, so 21), then the search of one wavefront.
+// time and counts looked up lane by lane: 28 us at 5120 x 1280, so 22), then the search of one wavefront.
 __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__ mask, int I, const PairsView y, const PairsView x) {
     constexpr int NP = PK_PAIRS, NQ = NP / 2;
     __shared__ unsigned long long g1[NP][4], g2[NP][4];
