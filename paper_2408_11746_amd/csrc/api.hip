@@ -83,9 +83,8 @@ static int pairs_product(const mst_layer* Lc, bool y, const void* A, float* C, i
     made &= L->pairs_recorded;                        // (then the dense copy brings them along)
     bool recording = false;
     if (!(L->pairs_valid && L->pairs_recorded && measured)) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        MST_HIP(hipStreamIsCapturing(s, &capture));
-        recording = capture != hipStreamCaptureStatusNone;
+        const int rc = stream_recording(s, &recording);
+        if (rc != MST_OK) return rc;
     }
     if (L->pairs_valid) {
         L->pairs_recorded |= recording;

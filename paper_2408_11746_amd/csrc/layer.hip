@@ -1048,10 +1048,9 @@ static int refresh_dense_copy(mst_layer* L, bool recording, hipStream_t s) {
 int ensure_dense_copy(mst_layer* L, hipStream_t s, bool* refreshed) {
     *refreshed = false;
     if (L->Wd_valid && !L->Wd_pending) return MST_OK;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    MST_HIP(hipStreamIsCapturing(s, &capture));
-    const bool recording = capture != hipStreamCaptureStatusNone;
-    if (L->Wd_valid && recording) return MST_OK;
+    bool recording;
+    const int rc = stream_recording(s, &recording);
+    if (rc != MST_OK || (L->Wd_valid && recording)) return rc;
     *refreshed = true;
     return refresh_dense_copy(L, recording, s);
 }
@@ -1061,11 +1060,11 @@ int ensure_dense_copy(mst_layer* L, hipStream_t s, bool* refreshed) {
 // there (and where the pairs are of a mask that nothing is known of, it learns how even that is).  A recording cannot wait and
 // runs later or never: it says nothing about them.
 int weights_made(mst_layer* L, bool planes, bool pairs, hipStream_t s) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    MST_HIP(hipStreamIsCapturing(s, &capture));
-    if (capture != hipStreamCaptureStatusNone) return MST_OK;
+    bool recording;
+    int rc = stream_recording(s, &recording);
+    if (rc != MST_OK || recording) return rc;
     if (pairs && !L->pairs_measured) {
-        const int rc = measure_pairs(L, s);
+        rc = measure_pairs(L, s);
         if (rc != MST_OK) return rc;
     } else {
         MST_HIP(hipStreamSynchronize(s));
@@ -1104,11 +1103,10 @@ int ensure_fresh(const mst_layer* Lc, bool row, bool col, hipStream_t s) {
     row = row && L->row_stale;
     col = col && L->col_stale;
     if (!row && !col) return MST_OK;
-    const int rc = refresh_views(L, row, col, false, true, s);
-    if (rc != MST_OK) return rc;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    MST_HIP(hipStreamIsCapturing(s, &capture));
-    if (capture != hipStreamCaptureStatusNone) return MST_OK;
+    int rc = refresh_views(L, row, col, false, true, s);
+    bool recording = false;
+    if (rc == MST_OK) rc = stream_recording(s, &recording);
+    if (rc != MST_OK || recording) return rc;
     MST_HIP(hipStreamSynchronize(s));
     if (row) L->row_stale = false;
     if (col) L->col_stale = false;
@@ -1126,20 +1124,14 @@ int ensure_views(const mst_layer* Lc, const Workspace& ws, hipStream_t s) {
     const BuildItem item{L, L->Wd, ws, true};
     rc = build_views(&item, 1, s);
     if (rc != MST_OK) return rc;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    MST_HIP(hipStreamIsCapturing(s, &capture));
-    L->views_pending = capture != hipStreamCaptureStatusNone;
-    return MST_OK;
+    return stream_recording(s, &L->views_pending);
 }
 
 // Can a call on s walk the views?
 int views_there(const mst_layer* L, hipStream_t s, bool* there) {
     *there = L->views_valid;
     if (!L->views_valid || !L->views_pending) return MST_OK;
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    MST_HIP(hipStreamIsCapturing(s, &capture));
-    *there = capture != hipStreamCaptureStatusNone;
-    return MST_OK;
+    return stream_recording(s, there);
 }
 
 // After an update: will a sparse kernel walk the views?  Judged at the batch size and type of
@@ -1296,9 +1288,10 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
         // calls that walk a view for the first time, and it has not run yet.  It takes the planes along if a product has read them
         // or the last product call had bfloat16 activations that did not go to the packed pairs, in both directions; otherwise they count as missed.
         // (Recorded regardless, a replayed fp32 step of the GPT-2-small block took 1.217 ms instead of 1.194.)
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        MST_HIP(hipStreamIsCapturing(s, &capture));
-        if (capture != hipStreamCaptureStatusNone) {
+        bool recording;
+        const int rcr = stream_recording(s, &recording);
+        if (rcr != MST_OK) return rcr;
+        if (recording) {
             // (the packed pairs if products read them)
             pairs = pairs_kept(L);
             L->pairs_missed |= L->pairs_y.blocks && !pairs;
