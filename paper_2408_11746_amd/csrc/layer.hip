@@ -875,6 +875,14 @@ __global__ __launch_bounds__(256) void k_export_dense(const float* __restrict__ 
     } else {
         __syncthreads();
     }
+    if (k1 - k0 <= 256) {                             // (four each would be the same one four times: 3072 x 768 at 0.04 4.0 us, so 3.9)
+        if (tid < k1 - k0) {
+            const int64_t at = (int64_t)flat[k0 + tid] - base;
+            const float v = vals[k0 + tid];
+            if (at >= 0 && at < n) run[at] = v;
+        }
+        k0 = k1;
+    }
     for (int k = k0 + tid; k < k1; k += 1024) {
         int64_t at[4];
         float v[4];
