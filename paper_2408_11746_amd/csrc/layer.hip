@@ -307,15 +307,21 @@ __global__ __launch_bounds__(256) void k_count(const Batch<CountArgs, CAP> batch
     }
 }
 
-// One workgroup per row block (thread j = row j): orders its 128 rows by total length over all
-// chunks, longest first, lower row first on ties (the empty padding blocks keep the identity), then
-// writes the pairs of every (chunk, octet) segment of the block.  With h rows spread over whole
-// octets (h <= #empty rows / 7) the octets cost about
-//   sum_{j<h} ceil(len_j / 8)  +  sum over the octets of the other rows of their longest row,
-// h is the value that minimises it (0 for every mask without empty rows).
+// One workgroup per row block (thread j = row j): decides which rows share an octet, then writes the pairs of every
+// (chunk, octet) segment of the block.  A segment is as long as the longest of its eight rows in that chunk, so rows should share
+// an octet that are long in the same chunks.
+//   - By total length, longest first, lower row first on ties (the empty padding blocks keep the identity).  With h rows
+//     spread over whole octets (h <= #empty rows / 7) the octets cost about
+//       sum_{j<h} ceil(len_j / 8)  +  sum over the octets of the other rows of their longest row,
+//     h is the value that minimises it (0 for every mask without empty rows).
+//   - By halves: the longer and the shorter half of the rows in the first part of the chunks, each of those by the next
+//     part, four times (with two chunks: quarters by the first, then by the second).  Of rows of equal density the total says
+//     little about a chunk, and every split narrows one of them: real entries of all steps at 12.8 a row and chunk 0.75 -> 0.85
+//     with two chunks, 0.73 -> 0.81 with three, 0.71 -> 0.76 with five, 0.71 -> 0.73 with eight.  Octets that lie four
+//     apart, and so meet on a SIMD unit of the walk, hold both halves of every split.
+// No row spread: whichever takes fewer pairs.
 // Bound by the latency of its reads of the counts (there are only as many workgroups as row blocks), so
-// all reads of a segment are issued together (with the fill of the col view in turns of four entries: update of
-// the GPT-2-small block at density 0.05, 1024 tokens, 766 -> 742 us).
+// all of them are issued together, once, and kept by chunk in LDS.
 struct ViewArgs {                                     // of one view: the first nb_r blocks of k_block_rank are the row view's
     const int* segcnt;
     int msub, nchunk, Rpad, NBpad, NB;
@@ -327,8 +333,10 @@ struct RankArgs {
 };
 template <int CAP>
 __global__ __launch_bounds__(RB) void k_block_rank(const Batch<RankArgs, CAP> batch) {
-    __shared__ int len_s[RB], sorted[RB], row_s[RB];
-    __shared__ int h_s, nzero_s;
+    extern __shared__ uint16_t cnt_s[];               // [nchunk][RB] entries of a row in a chunk
+    __shared__ __attribute__((aligned(16))) uint32_t code_s[RB];
+    __shared__ int sorted[RB], row_s[2][RB];          // row_s: rows by place, ranked and halved
+    __shared__ int h_s, nzero_s, gain_s;
     if (batch.surplus()) return;
     const unsigned bu = blockIdx.x;
     const RankArgs both = batch.entry();
@@ -338,17 +346,45 @@ __global__ __launch_bounds__(RB) void k_block_rank(const Batch<RankArgs, CAP> ba
     const int msub = v.msub, nchunk = v.nchunk, Rpad = v.Rpad, NBpad = v.NBpad;
     const int* __restrict__ segcnt = v.segcnt;
     int *__restrict__ rowmap = v.rowmap, *__restrict__ rowpos = v.rowpos, *__restrict__ qlen = v.qlen;
-    if (j == 0) { h_s = 0; nzero_s = 0; }
-    int len = 0;
-#pragma unroll 8
-    for (int c = 0; c < nchunk * msub; ++c) len += segcnt[(size_t)c * Rpad + b * RB + j];
-    len_s[j] = len;
-    __syncthreads();
-    int rank = 0;
-    for (int u = 0; u < RB; ++u) {
-        const int lu = len_s[u];
-        rank += (lu > len) || (lu == len && u < j);
+    if (j == 0) h_s = nzero_s = gain_s = 0;
+    // the row's entries by chunk; keys: in all, and in the parts of the chunks that the splits go by
+    const int nkey = nchunk >= 3 ? 4 : nchunk == 2 ? 2 : 0;
+    int len = 0, key[4] = {0, 0, 0, 0};
+    constexpr int MSUB = KCMAX / KSMAX, AT_ONCE = 4;
+    for (int c0 = 0; c0 < nchunk; c0 += AT_ONCE) {
+        int x[AT_ONCE][MSUB];
+#pragma unroll
+        for (int d = 0; d < AT_ONCE; ++d)
+#pragma unroll
+            for (int u = 0; u < MSUB; ++u) x[d][u] = segcnt[(size_t)(min(c0 + d, nchunk - 1) * msub + min(u, msub - 1)) * Rpad + b * RB + j];
+#pragma unroll
+        for (int d = 0; d < AT_ONCE; ++d) {
+            const int c = c0 + d;
+            if (c >= nchunk) break;
+            int n = 0;
+#pragma unroll
+            for (int u = 0; u < MSUB; ++u) n += u < msub ? x[d][u] : 0;
+            cnt_s[c * RB + j] = (uint16_t)n;
+            len += n;
+            const int part = nchunk <= 4 ? c : 4 * c / nchunk;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) key[q] += part == q ? n : 0;
+        }
     }
+    if (nchunk == 3) key[3] = len;
+    // this row's place among the block's by ascending codes, which differ
+    auto place = [&](uint32_t code) {
+        code_s[j] = code;
+        __syncthreads();
+        int at = 0;
+#pragma unroll 8
+        for (int u = 0; u < RB; u += 4) {
+            const uint4 x = *reinterpret_cast<const uint4*>(code_s + u);
+            at += (x.x < code) + (x.y < code) + (x.z < code) + (x.w < code);
+        }
+        return at;
+    };
+    const int rank = place((uint32_t)(0xFFFF - len) << 7 | (uint32_t)j);
     sorted[rank] = len;
     if (len == 0) atomicAdd(&nzero_s, 1);
     __syncthreads();
@@ -372,33 +408,55 @@ __global__ __launch_bounds__(RB) void k_block_rank(const Batch<RankArgs, CAP> ba
     if (p < h) { slot = OCT * p; flag_row = SPREAD_FLAG; }               // spread row: lane group 0 of octet p
     else if (p < RB - 7 * h) slot = OCT * h + (p - h);                   // ordinary rows fill the other octets
     else { const int e = p - (RB - 7 * h); slot = OCT * (e / 7) + 1 + e % 7; }   // empty rows own the rest
-    const int flag_oct = slot / OCT < h ? SPREAD_FLAG : 0;
-    rowmap[b * RB + slot] = (b * RB + j) | flag_oct;
-    rowpos[b * RB + j] = slot | flag_row;
-    row_s[slot] = j;
+    row_s[0][slot] = j;
+    int halved = 0;
+    const bool split = h == 0 && nkey > 0 && sorted[0] > 0;
+    if (split) {
+        // splits: place among the rows by (group so far, key, row), the group's next bits from it
+        int group = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q >= nkey) break;
+            if (q > 0) __syncthreads();
+            halved = place((uint32_t)group << 23 | (uint32_t)(0xFFFF - key[q]) << 7 | (uint32_t)j);
+            group = nkey == 4 ? halved >> (6 - q) : halved >> (q == 0 ? 5 : 3);
+        }
+        // group: the splits' results, the first one highest; octets four apart differ in each of them
+        const int octet = nkey == 4 ? ((group >> 3) & 1) << 3 | ((group >> 1) & 1) << 2 | ((group >> 3 ^ group >> 2) & 1) << 1 | ((group >> 1 ^ group) & 1)
+                                    : (group & 12) | (((group >> 2) + group) & 3);
+        halved = OCT * octet + (halved & (OCT - 1));
+        row_s[1][halved] = j;
+    }
     __syncthreads();
     // pairs of a segment: longest of its eight rows (a spread row: an eighth of it), rounded up to even, halved
-    for (int idx = j; idx < nchunk * OPB; idx += RB) {
-        const int c = idx / OPB, o = idx % OPB;
-        const int* cnt = segcnt + (size_t)c * msub * Rpad + b * RB;
-        int n[OCT];
-#pragma unroll
-        for (int g = 0; g < OCT; ++g) {
-            n[g] = 0;
-#pragma unroll
-            for (int u = 0; u < KCMAX / KSMAX; ++u) {
-                const int v = cnt[(size_t)min(u, msub - 1) * Rpad + row_s[o * OCT + g]];
-                n[g] += u < msub ? v : 0;
-            }
-        }
-        int L = n[0];
+    auto pairs = [&](int how, int c, int o) {
+        const uint16_t* cnt = cnt_s + c * RB;
+        const int* rows = row_s[how] + o * OCT;
+        int L = cnt[rows[0]];
         if (o < h) {
             L = (L + 7) >> 3;
         } else {
 #pragma unroll
-            for (int g = 1; g < OCT; ++g) L = max(L, n[g]);
+            for (int g = 1; g < OCT; ++g) L = max(L, (int)cnt[rows[g]]);
         }
-        qlen[((size_t)c * NBpad + b) * OPB + o] = (L + 1) >> 1;
+        return (L + 1) >> 1;
+    };
+    int how = 0;
+    if (split) {
+        int gain = 0;
+        for (int idx = j; idx < nchunk * OPB; idx += RB) gain += pairs(0, idx / OPB, idx % OPB) - pairs(1, idx / OPB, idx % OPB);
+        for (int d = 32; d >= 1; d >>= 1) gain += __shfl_xor(gain, d, 64);
+        if ((j & 63) == 0) atomicAdd(&gain_s, gain);
+        __syncthreads();
+        how = gain_s > 0 ? 1 : 0;
+    }
+    if (how) slot = halved;
+    const int flag_oct = slot / OCT < h ? SPREAD_FLAG : 0;
+    rowmap[b * RB + slot] = (b * RB + j) | flag_oct;
+    rowpos[b * RB + j] = slot | flag_row;
+    for (int idx = j; idx < nchunk * OPB; idx += RB) {
+        const int c = idx / OPB, o = idx % OPB;
+        qlen[((size_t)c * NBpad + b) * OPB + o] = pairs(how, c, o);
     }
 }
 
@@ -942,7 +1000,7 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
     Batch<RankArgs> rank;
     Batch<PtrArgs> ptr;
     Batch<FillArgs> fill_r, fill_c;
-    int nsub_max = 1;
+    int nsub_max = 1, nchunk_max = 1;
     for (int x = 0; x < n; ++x) {
         mst_layer* L = items[x].L;
         const Workspace& ws = items[x].ws;
@@ -950,6 +1008,7 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
         const View &r = L->row, &c = L->col;
         const int O = L->O, I = L->I, Rpad_r = r.NBpad * RB, Rpad_c = c.NBpad * RB;
         nsub_max = std::max(nsub_max, r.nsub());
+        nchunk_max = std::max({nchunk_max, r.nchunk, c.nchunk});
         const int tiles = (int)cdiv(Rpad_c, MT_COLS);
         count.add(CountArgs{L->mask, O, I, r.KS, r.nsub(), Rpad_r, c.KS, Rpad_c, Rpad_r, tiles, ws.segcnt[0], ws.rowcnt, ws.segcnt[1]},
                   Rpad_r + (int64_t)tiles * c.nsub());
@@ -976,7 +1035,7 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
             const int rc = heavy_mark(items[x].L, items[x].ws, items[x].L->row.NBpad * RB, s);  // heavy rows leave the view
             if (rc != MST_OK) return rc;
         }
-    launch_batch(rank, [&](const auto& b) { k_block_rank<<<b.grid(), RB, 0, s>>>(b); });
+    launch_batch(rank, [&](const auto& b) { k_block_rank<<<b.grid(), RB, (size_t)nchunk_max * RB * 2, s>>>(b); });
     MST_LAUNCH_CHECK();
     launch_batch(ptr, [&](const auto& b) { k_view_ptr<<<b.grid(), 1024, 0, s>>>(b); });
     MST_LAUNCH_CHECK();

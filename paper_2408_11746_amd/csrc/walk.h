@@ -26,6 +26,9 @@
 //   - chunks of 640 instead of 128 indices: an ELL slice pads to the longest of its rows per chunk, and
 //     25.6 instead of 2.6 entries a row and chunk at density 0.02 waste 0.25-0.30 instead of 0.44 of
 //     the steps, and there are five times fewer barriers, over slabs of up to 768 rows;
+//   - rows that are long in the same chunks share an octet (k_block_rank): 0.15 of the steps wasted with two
+//     chunks, 0.24 with five, 0.27 with eight (8192 tokens, density 0.02: Y of 1280 -> 5120 100.5 -> 95, of 5120 -> 1280
+//     88 -> 86, both gradients of the two 188 -> 184 and 204 -> 193);
 //   - eight tokens a lane: the address, weight and row-sum instructions are shared by eight tokens;
 //   - odd lane groups read the upper token half of a row first, even ones the lower: with the swizzle
 //     of lds_off the reads are then free of bank conflicts (1.5 M conflict cycles instead of 26 M in
