@@ -113,9 +113,9 @@ static const WalkCost kOut = {0.0060, 1.7}, kBoth = {0.0105, 2.9}, kDw = {0.0090
 
 static double octet_steps(const View& v, double density) {
     const double m = density * v.KC;                                  // entries per row and chunk
-    // the longest of eight binomial rows, even; rows share an octet by their lengths in the chunks, which tell the less the
-    // more chunks there are (counted on views of two to eight chunks, within 2 %)
-    return m + (v.nchunk > 1 ? 1.42 - 1.3 / v.nchunk : 1.42) * std::sqrt(m) + 0.5;
+    // the longest of eight binomial rows, even.  (Rows share an octet by their lengths in the chunks, which takes 3 to 12 % off
+    // that; in the time of a call it is within what the models are unsure of, and the lines drawn with them stay where they are.)
+    return m + 1.42 * std::sqrt(m) + 0.5;
 }
 static double walk_units(const View& v, double density) { return octet_steps(v, density) * v.nchunk * v.NB; }   // see k_view_ptr
 static double walk_round(const View& v, double density, int q, int chunks, const WalkCost& wc) {
