@@ -204,7 +204,7 @@ int mst_heavy_rows(int on);
  * layer, also after one that was only recorded, and the first product that makes the dense copy again after a loading or an
  * update that built the views -- makes it and waits for that on `stream`, so that products on other streams need an order
  * after the hand-over of the values alone; hand-overs and the other updates keep it up.
- * Up to a density of 0.12, Y and dX of either type that would take the dense kernels with two bfloat16 values per fp32 operand read packed
+ * Up to a density of 0.118, Y and dX of either type that would take the dense kernels with two bfloat16 values per fp32 operand read packed
  * copies of the weights instead where that is faster (O and I multiples of 64; mst_gemm_force_fp32_mfma, 24).  They are made and waited for in the same way, and
  * the first eager product on a mask reads back how evenly its rows fill them, which decides whether that mask uses them: it waits too.
  * A mask is a new one after mst_layer_load_dense, and after an update with 64 or more products of the layer before it.

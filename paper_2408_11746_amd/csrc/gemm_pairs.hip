@@ -7,22 +7,33 @@
 // of 32 rows x 32 k, and a second pass over those would take back most of the gain.  So the quads are chosen:  the
 // activations go to LDS by dwords (two k, as bfloat16) anyway, and for every band of 256 rows and step of 64 k the 32 dwords are
 // paired up so that the fewest rows overflow (k_match_pairs: greedy, then exchanges between two quads).  Up to density 0.08 that
-// leaves nothing, at 0.10 one step in ten with a few overflowing rows, at 0.12 five in six.  What is left goes to a second step of the
-// same 64 k with the third and fourth entries, walked after the others by the wavefronts that have any: every mask is exact.
+// leaves nothing, at 0.10 one step in ten with a few overflowing rows, at 0.12 five in six.  What is left, the third and fourth entries, is
+// packed by itself ("second weights") and multiplied in the same step by the wavefronts that have any, over the activations that are in LDS
+// anyway: every mask is exact.
 //
-// A workgroup: one band x 128 tokens (fp32) or 256, 192, 128 tokens (bfloat16), eight wavefronts of 64 rows x half the tokens;
-// two LDS stages of 64 k, one barrier per step.
-//   - Everything passes through registers, packed weights too: an operand is loaded one or two steps before its way to LDS,
-//     each piece right behind the store that freed its registers, between the products (loads in front of the step held the
-//     matrix cores up for 1000 clocks; straight to LDS, all loads of a step had to arrive within it: 1280 <- 5120, 0.1, 8192 tokens,
-//     cold activations 270 us, so 248).
-//   - The operands of a step's last products are in registers when the wavefronts meet, so the first ones of the next step are
-//     read beside them (Y of 1280 -> 5120, 0.05: 203 -> 189 us).
-// Measured (us, before = the dense kernels; 8192 tokens, fp32, 0.10): Y of 1280 -> 5120 281 -> 196, dX of it 304 -> 223; Y of 768 ->
-// 3072 114 -> 90, dX of it 123 -> 92.  16384 tokens, bfloat16, 0.05: Y of 1024 -> 4096 234 -> 144, dX 198 -> 118.
-// What bounds it: the matrix cores take 18 ns an instruction with the whole chip on them (1.75 GHz), 0.86 of the 1.4 us of a
-// step of fp32 and 1.15 of the 1.95 of bfloat16; the conversions and stores of the activations between the products (10 %), and the
-// outputs of all workgroups at once (7 to 9 us a round) are the most of the rest.
+// A tile: one band x 128 tokens (fp32; the tokens behind the last full round in tiles of 64) or 256, 192, 128 tokens (bfloat16), eight
+// wavefronts of 64 rows x half the tokens.  A CU holds one workgroup, which forms tile after tile (numbers 32 apart on its XCD).
+//   - The steps of a tile follow those of the one before: what is on its way belongs to the next tile already while the outputs
+//     leave, so a tile has no start of its own (as workgroups of one tile each, loads, conversion and the place of the
+//     next workgroup took 5 us of 29 at 768 -> 3072).
+//   - The weights go straight to LDS, three stages of 32 KB: loaded while the step before the last one runs.  Through registers they
+//     cost 34 of those and 250 clocks of a step; with two stages they had to arrive within a step.
+//   - The activations are loaded two steps before their way to LDS, each piece right behind the store that freed its registers, converted
+//     and stored between the products.  A slot of the table is what the address differs by, so an address costs one instruction.  Two
+//     stages of 32 KB: with the weights' all of a CU's LDS; the selectors stay in registers, and the outputs leave through the stage of
+//     weights that is free then, every wavefront's through the part of it that its own loads fill next.
+//   - The operands of the last two blocks of products of a step are in registers when the wavefronts meet, so the reads for the next step
+//     stand beside 12 products and the reads of a step are spread evenly over it.
+//   - One barrier per step.  The loop has one way out: with a second one in the middle the compiler counted a step's loads
+//     less in every wait, and the step took 4000 clocks.
+// Measured (us; before = one workgroup per tile, weights through registers, second weights as steps of their own behind the others; 8192
+// tokens, fp32, 0.10): Y of 1280 -> 5120 199 -> 172, dX of it 210 -> 197; Y of 768 -> 3072 78 -> 69, dX of it 80 -> 70.  16384 tokens,
+// bfloat16, 0.05: Y of 1024 -> 4096 143 -> 138, dX 113.5 -> 113.
+// What bounds it: a step of fp32 takes 2000 to 2600 clocks, 1536 of them matrix instructions (before 2600), but at 1.55 GHz where it was
+// 1.65 to 1.97: the chip lowers its clock for what it does per clock.  bfloat16: 2700 clocks of which 2048 are products, and 9000 to 12000
+// for the 256 KB of outputs of a tile, all workgroups at once.  Workgroups that start at different times (up to 10 us apart) gained nothing
+// in fp32 and 2 % in bfloat16, outputs past the L2 or through it are the same.
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -35,8 +46,9 @@ typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t pk_u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int PB_ROWS = 256, PB_TILES = PB_ROWS / 32;          // rows of a band, MFMA tiles of them
-constexpr int PW_TILE = 2048, PW_SUB = PB_TILES * PW_TILE + PB_TILES * 128;   // [tile][hi 1 KB, lo 1 KB], [tile][64 lanes] selectors
-constexpr int PK_STEP = 64, PK_PAIRS = PK_STEP / 2, PK_BLOCK = 2 * PW_SUB;    // k of a step, packed bytes of a step
+constexpr int PK_STEP = 64, PK_PAIRS = PK_STEP / 2;            // k of a step
+constexpr int PW_TILE = 2048, PW_SUB = PB_TILES * PW_TILE, PW_STEP = 2 * PW_SUB;   // packed bytes: [32 k][tile][hi 1 KB, lo 1 KB]
+constexpr int PW_SEL = PB_TILES / 2 * 64 * 8;                   // selectors of a step: [two tiles][lane][tile], first 32 k in the low half
 
 PairsView pairs_view(void* mem, int R, int K) {
     PairsView v;
@@ -48,11 +60,12 @@ PairsView pairs_view(void* mem, int R, int K) {
     char* b = static_cast<char*>(mem);
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes); return b ? b + o : nullptr; };
-    v.slots = (uint8_t*)take((size_t)n * PK_PAIRS);
+    v.slots = (uint16_t*)take((size_t)n * PK_PAIRS * 2);
     v.flags = (uint32_t*)take((size_t)n * 4);
     v.over = (uint8_t*)take((size_t)n);
     v.count = (uint32_t*)take(8);
-    v.blocks = take((size_t)n * 2 * PK_BLOCK);
+    v.blocks = take((size_t)n * 2 * PW_STEP);
+    v.sel = (uint32_t*)take((size_t)n * 2 * PW_SEL);
     v.bytes = off;
     return v;
 }
@@ -116,11 +129,10 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
     const int missing = (band + 1) * PB_ROWS - v.R;
     if (tid < 4 && 64 * tid >= PB_ROWS - missing) reinterpret_cast<uint8_t*>(v.flags + at)[tid] = 0;
     if (missing > 0)
-        for (int e = tid; e < 4 * missing; e += 256) {       // [first, second step][32 k][missing rows]
+        for (int e = tid; e < 4 * missing; e += 256) {       // [first, second step][half of a lane's k][missing rows]
             const int row = PB_ROWS - missing + e % missing, ss = e / missing;
-            char* b = v.blocks + ((int64_t)band * 2 * v.nk + kb + (ss >> 1) * v.nk) * PK_BLOCK + (ss & 1) * PW_SUB + PB_TILES * PW_TILE;
-            reinterpret_cast<uint16_t*>(b)[(row >> 5) * 64 + (row & 31)] = 0x4444u;
-            reinterpret_cast<uint16_t*>(b)[(row >> 5) * 64 + 32 + (row & 31)] = 0x4444u;
+            uint32_t* const sel = v.sel + ((int64_t)band * 2 * v.nk + kb + (ss >> 1) * v.nk) * (PW_SEL / 4);
+            sel[(row >> 6) * 128 + ((ss & 1) * 32 + (row & 31)) * 2 + (row >> 5 & 1)] = 0x44444444u;
         }
     __syncthreads();
     for (int e = tid; e < NP * NP; e += 256) {
@@ -196,8 +208,10 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
         if (lane == m) place = 4 * unit + best;
     }
     if (lane < NQ) {
-        v.slots[(int64_t)at * NP + first] = (uint8_t)(4 * place);
-        v.slots[(int64_t)at * NP + second] = (uint8_t)(4 * (place ^ 1));
+        // (as the product's staging store wants it, see there)
+        auto slot = [](int pl) { return (uint16_t)((pl & 15) << 2 | (pl >> 4) << 14); };
+        v.slots[(int64_t)at * NP + first] = slot(place);
+        v.slots[(int64_t)at * NP + second] = slot(place ^ 1);
     }
 }
 
@@ -224,7 +238,10 @@ __global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W,
         float* p = tile + o * LD + c;
         p[0] = w.x; p[1] = w.y; p[2] = w.z; p[3] = w.w;
     }
-    if ((wave & 1) == 0 && lane < PK_PAIRS) pair_s[wave >> 1][v.slots[bk * PK_PAIRS + lane] >> 2] = (uint8_t)lane;
+    if ((wave & 1) == 0 && lane < PK_PAIRS) {
+        const uint32_t f = v.slots[bk * PK_PAIRS + lane];
+        pair_s[wave >> 1][(f >> 2 & 15) | (f >> 14) << 4] = (uint8_t)lane;
+    }
     __syncthreads();
     const int row = 32 * (wave & 1) + (lane & 31), h = lane >> 5;
     // element (row, k) of this wavefront's view
@@ -232,14 +249,15 @@ __global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W,
     const int step = of_x ? LD : 1;
     const uint8_t* const ps = pair_s[wave >> 1];
     pk_u32x4 hi2[2], lo2[2];
-    uint32_t ix2[2];
+    uint32_t ix1 = 0, ix2 = 0;                        // of both halves of the step
     bool over = false;
-    char* const blk = v.blocks + ((int64_t)band * 2 * v.nk + kb) * PK_BLOCK;
-    auto store = [&](char* b, pk_u32x4 hi, pk_u32x4 lo, uint32_t ix) {
-        *reinterpret_cast<pk_u32x4*>(b + t * PW_TILE + lane * 16) = hi;
-        *reinterpret_cast<pk_u32x4*>(b + t * PW_TILE + 1024 + lane * 16) = lo;
-        *reinterpret_cast<uint16_t*>(b + PB_TILES * PW_TILE + t * 128 + lane * 2) = (uint16_t)ix;
+    const int64_t first_step = (int64_t)band * 2 * v.nk + kb;
+    auto store = [&](int64_t at_step, int ss, pk_u32x4 hi, pk_u32x4 lo) {
+        char* const b = v.blocks + at_step * PW_STEP + ss * PW_SUB + t * PW_TILE + lane * 16;
+        *reinterpret_cast<pk_u32x4*>(b) = hi;
+        *reinterpret_cast<pk_u32x4*>(b + 1024) = lo;
     };
+    auto store_sel = [&](int64_t at_step, uint32_t ix) { v.sel[at_step * (PW_SEL / 4) + (t >> 1) * 128 + lane * 2 + (t & 1)] = ix; };
 #pragma unroll
     for (int ss = 0; ss < 2; ++ss) {
         float f[16];
@@ -250,8 +268,6 @@ __global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W,
             f[2 * i + 1] = p[step];
         }
         pk_u32x4 hi, lo;
-        uint32_t ix = 0;
-        ix2[ss] = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const float* g = f + 4 * q;
@@ -270,20 +286,21 @@ __global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W,
             };
             float a, b;
             uint32_t hh, ll;
-            ix |= two(m, a, b) << (4 * q);
+            ix1 |= two(m, a, b) << (4 * q + 16 * ss);
             split_pair(a, b, hh, ll);
             hi[q] = hh;
             lo[q] = ll;
             uint32_t m2 = m & (m - 1u);
             m2 &= m2 - 1u;
             over |= m2 != 0;
-            ix2[ss] |= two(m2, a, b) << (4 * q);
+            ix2 |= two(m2, a, b) << (4 * q + 16 * ss);
             split_pair(a, b, hh, ll);
             hi2[ss][q] = hh;
             lo2[ss][q] = ll;
         }
-        store(blk + ss * PW_SUB, hi, lo, ix);
+        store(first_step, ss, hi, lo);
     }
+    store_sel(first_step, ix1);
     const unsigned long long any = __ballot(over);
     if (lane == 0) over_s[wave] = any != 0ull;
     __syncthreads();
@@ -301,7 +318,8 @@ __global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W,
     }
     if (!on) return;
 #pragma unroll
-    for (int ss = 0; ss < 2; ++ss) store(blk + (int64_t)v.nk * PK_BLOCK + ss * PW_SUB, hi2[ss], lo2[ss], ix2[ss]);
+    for (int ss = 0; ss < 2; ++ss) store(first_step + v.nk, ss, hi2[ss], lo2[ss]);
+    store_sel(first_step + v.nk, ix2);
 }
 
 // From the mask and the dense copy: the slots where the active set is a new one, and the blocks
@@ -331,97 +349,109 @@ __device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>
 template <int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(std::make_integer_sequence<int, N>{}, f); }
 
-// NTK: tiles of 32 tokens of a wavefront; AHEAD: steps between the load of an operand and its way to LDS, a register set each
-template <bool BF, int NTK, int AHEAD>
-__device__ __forceinline__ void pairs_tile(const char* __restrict__ A, const PairsView& v, float* __restrict__ C, int T, int t0, int band, char* const lds) {
-    constexpr int TOK = 64 * NTK, PLANE = TOK * 64, XST = (BF ? 2 : 4) * PLANE, STAGE = XST + PK_BLOCK;
-    constexpr int LINES = BF ? 1 : 2, NX = NTK * LINES;           // 128-byte lines of a row in a step; 16-byte pieces of a thread
-    uint16_t* const list = reinterpret_cast<uint16_t*>(lds + 2 * STAGE);
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nk = v.nk;
-    // steps of the second kind, in ascending order
-    const uint32_t* const flags = v.flags + (int64_t)band * nk;
-    int nsec = 0;
-    for (int base = 0; base < nk; base += 64) {
-        const bool on = base + lane < nk && flags[base + lane] != 0;
-        const unsigned long long bal = __ballot(on);
-        if (wave == 0 && on) list[nsec + __popcll(bal & ((1ull << lane) - 1ull))] = (uint16_t)(base + lane);
-        nsec += __popcll(bal);
-    }
-    nsec = __builtin_amdgcn_readfirstlane(nsec);
-    __syncthreads();
-    const int nv = nk + nsec;
-    auto kblock = [&](int t) { return t < nk ? t : __builtin_amdgcn_readfirstlane((int)list[t - nk]); };
+// LDS: two stages of the activations, three of the weights
+constexpr int PX_STAGE = 32768, PX_SUB = 16384, PW_RING = 2 * PX_STAGE, PAIRS_LDS = PW_RING + 3 * PW_STEP;
 
-    // ---- staging: chunk of 16 bytes of row r0 + 64 it
+// All of a workgroup's tiles of 64 NTK tokens x one band: numbers xcd Q + at, at = at0, at0 + 32, ...  The steps of one tile follow
+// those of the one before without a break; between two of them the wavefronts store their outputs.
+// NTK: tiles of 32 tokens of a wavefront
+template <bool BF, int NTK>
+__device__ __forceinline__ void pairs_tiles(const char* __restrict__ A, const PairsView& v, float* __restrict__ C, int T, int t_begin, int n_tok, int xcd, int Q, int at0,
+                                            char* const lds) {
+    constexpr int TOK = 64 * NTK, PLANE = TOK * 64;
+    constexpr int LINES = BF ? 1 : 2, NX = NTK * LINES;           // 128-byte lines of a row in a step; 16-byte pieces of a thread
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nk = v.nk, ntiles = n_tok * v.bands;
+    auto is_tile = [&](int at) { return at < Q && xcd * Q + at < ntiles; };
+    if (!is_tile(at0)) return;
+    const uint32_t pitch = (uint32_t)v.K * (BF ? 2u : 4u);
+
+    // ---- where a step's operands are
+    struct Source {
+        int at, kb, t0, band;
+        const char* w;                                // packed tiles of the step
+        __amdgpu_buffer_rsrc_t rs;                    // the token tile's activations
+    };
+    auto tile_of = [&](int at, int& t0, int& band) {
+        int mi;
+        tile_coords(xcd * Q + at, n_tok, v.bands, mi, band);
+        t0 = t_begin + mi * TOK;
+    };
+    auto aim = [&](Source& s, int at) {
+        s.at = at;
+        s.kb = 0;
+        tile_of(at, s.t0, s.band);
+        s.w = v.blocks + (int64_t)s.band * 2 * nk * PW_STEP;
+        s.rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(A + (int64_t)s.t0 * pitch), 0, (int)((uint32_t)min(T - s.t0, TOK) * pitch), 0x00020000);
+    };
+    auto advance = [&](Source& s) {                   // (past the last step: that step again, into stages that nobody reads)
+        if (s.kb + 1 < nk) { ++s.kb; s.w += PW_STEP; }
+        else if (is_tile(s.at + 32)) aim(s, s.at + 32);
+    };
+
+    // ---- staging: chunk of 16 bytes of row row0 + 64 it
     // (32 lanes: four chunks of eight rows whose positions in LDS, two in 128 bytes times four swizzles, put any dword of a
     // 64-byte row in eight different banks)
     const int chunk = (lane & 3) | (lane >> 5) << 2;
     const int row0 = (lane >> 2 & 7) + 8 * wave;
-    const uint32_t pitch = (uint32_t)v.K * (BF ? 2u : 4u);
-    const uint32_t rows = (uint32_t)min(T - t0, TOK);
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(A + (int64_t)t0 * pitch), 0, (int)(rows * pitch), 0x00020000);
     const uint32_t xoff = (uint32_t)row0 * pitch + 16u * chunk;
-    const uint32_t wbase = (uint32_t)pr_rho(row0) * 64u, wswz = (((uint32_t)pr_rho(row0) >> 2 ^ (uint32_t)pr_rho(row0) >> 4) & 3u) << 4;
-    const char* const slots = reinterpret_cast<const char*>(v.slots) + (int64_t)band * nk * PK_PAIRS;
-    const char* const wblk = v.blocks + (int64_t)band * 2 * nk * PK_BLOCK;
+    // a slot is the dword's place in a row (64 bytes of 32 k) and, 16 KB on, which 32 k: it and the row's address have no bits in
+    // common but those of the swizzle
+    const uint32_t wbase = (uint32_t)pr_rho(row0) * 64u | (((uint32_t)pr_rho(row0) >> 2 ^ (uint32_t)pr_rho(row0) >> 4) & 3u) << 4;
+    const uint32_t slot_off = BF ? 8u * chunk : 4u * chunk, sel_off = (uint32_t)(wave >> 1) * 512u + 8u * lane, w_off = 4096u * wave + 16u * lane;
+    uint32_t no_lane;                                 // zero that the compiler takes for a lane's own (a scalar load would share the LDS reads' counter)
+    asm("v_mov_b32 %0, 0" : "=v"(no_lane));
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
 
-    // What a thread carries of a step: NX pieces of 16 bytes of the activations with the slots of their dwords, four pieces of
-    // the packed weights and a dword of their selectors.  Operation n of a step: something goes to LDS, and what its
-    // registers held is loaded AHEAD steps on.
+    // What a thread carries of a step: NX pieces of 16 bytes of the activations with the slots of their dwords, its selectors and the flags of
+    // the 64-row groups.  Operation n of a step: something goes to LDS, and what its registers held is loaded two steps on.
     struct Carried {
-        pk_u32x4 x[NX], w[4];
-        uint32_t slot[LINES], sel;
-    };
-    struct Source {
-        const char* w;
-        int kb;
-    };
-    auto source = [&](int t) {
-        t = min(t, nv - 1);                           // (past the end the last step again, into a stage that nobody reads)
-        const int kb = kblock(t);
-        return Source{wblk + (int64_t)(t < nk ? t : nk + kb) * PK_BLOCK, kb};
+        pk_u32x4 x[NX];
+        uint32_t slot[2], sel[2], flag;
     };
     auto load_x = [&](Carried& f, const Source& src, int n) __attribute__((always_inline)) {
-        f.x[n] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)(xoff + (uint32_t)(64 * (n % NTK)) * pitch + 128u * (uint32_t)(src.kb * LINES + n / NTK)), 0, 0);
+        f.x[n] = __builtin_amdgcn_raw_buffer_load_b128(src.rs, (int)(xoff + (uint32_t)(64 * (n % NTK)) * pitch + 128u * (uint32_t)(src.kb * LINES + n / NTK)), 0, 0);
     };
     auto load_slot = [&](Carried& f, const Source& src, int line) __attribute__((always_inline)) {
-        // (fp32: those of two chunks; a load of 16 bits would be widened, and waited for, where the loop closes)
-        f.slot[line] = *reinterpret_cast<const uint32_t*>(slots + (int64_t)src.kb * PK_PAIRS + 16 * line + (BF ? 4 * chunk : 2 * (chunk & ~1)));
+        const char* p = reinterpret_cast<const char*>(v.slots) + ((int64_t)src.band * nk + src.kb) * (2 * PK_PAIRS) + 32 * line + slot_off;
+        if constexpr (BF) {
+            const uint2 u = *reinterpret_cast<const uint2*>(p);
+            f.slot[0] = u.x;
+            f.slot[1] = u.y;
+        } else {
+            f.slot[line] = *reinterpret_cast<const uint32_t*>(p);
+        }
     };
-    // (of a block [2][tiles, selectors]: 16 bytes at 1 KB (wave + 8 n) of the tiles, a dword of the selectors)
-    const uint32_t wsel = (uint32_t)(PB_TILES * PW_TILE + (tid >> 8) * PW_SUB + 4 * (tid & 255));
-    auto wpiece = [&](int n) { return (uint32_t)((n >> 1) * PW_SUB + 16 * (512 * (n & 1) + tid)); };
-    auto load_w = [&](Carried& f, const Source& src, int n) __attribute__((always_inline)) {
-        if (n < 4) f.w[n] = *reinterpret_cast<const pk_u32x4*>(src.w + wpiece(n));
-        else f.sel = *reinterpret_cast<const uint32_t*>(src.w + wsel);
+    auto load_sel = [&](Carried& f, const Source& src) __attribute__((always_inline)) {
+        const uint2 u = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(v.sel) + ((int64_t)src.band * 2 * nk + src.kb) * PW_SEL + sel_off);
+        f.sel[0] = u.x;
+        f.sel[1] = u.y;
+        f.flag = v.flags[(int64_t)src.band * nk + src.kb + no_lane];
     };
-    constexpr int HALF = (NTK + 1) / 2, NPUT = BF ? 4 * HALF : 4 * NTK, NOPS = NPUT + 5;
-    auto operation = [&](Carried& f, uint32_t stage, const Source& next, auto nc) __attribute__((always_inline)) {
+    auto load_w = [&](const char* w, uint32_t ring, int n) __attribute__((always_inline)) { load_to_lds(w + 1024 * n, w_off, lds0 + PW_RING + ring + 4096u * wave + 1024u * n); };
+    constexpr int NPUT = BF ? 4 * ((NTK + 1) / 2) : 4 * NTK;
+    constexpr int LOADS = NX + LINES + 2, VM = LOADS + 4;         // of a step, and with the weights' four
+    auto put = [&](Carried& f, uint32_t stage, const Source& next, auto nc) __attribute__((always_inline)) {
         constexpr int n = decltype(nc)::value;
-        if constexpr (n >= NPUT) {
-            constexpr int m = n - NPUT;
-            if constexpr (m < 4) *reinterpret_cast<pk_u32x4*>(lds + stage + XST + wpiece(m)) = f.w[m];
-            else *reinterpret_cast<uint32_t*>(lds + stage + XST + wsel) = f.sel;
-            load_w(f, next, m);
-        } else if constexpr (BF) {
+        if constexpr (BF) {
             constexpr int e = n % 4, h = n / 4;               // dword e of pieces 2 h and 2 h + 1
-            const uint32_t b = f.slot[0] >> (8 * e) & 255u;
-            char* const p = lds + stage + wbase + 8192u * h + (b >> 6) * PLANE + ((b & 63u) ^ wswz);
+            const uint32_t b = e & 1 ? f.slot[e >> 1] >> 16 : f.slot[e >> 1] & 0xFFFFu;
+            char* const p = lds + ((wbase ^ b) + stage + 8192u * h);
             *reinterpret_cast<uint32_t*>(p) = f.x[2 * h][e];
             if (2 * h + 1 < NTK) *reinterpret_cast<uint32_t*>(p + 4096) = f.x[2 * h + 1 < NTK ? 2 * h + 1 : 0][e];
             if constexpr (e == 3) {
                 load_x(f, next, 2 * h);
                 if (2 * h + 1 < NTK) load_x(f, next, 2 * h + 1);
-                if constexpr (h == HALF - 1) load_slot(f, next, 0);
+                if constexpr (h == (NTK + 1) / 2 - 1) load_slot(f, next, 0);
             }
         } else {
             constexpr int e = n % 2, it = n / 2 % NTK, line = n / (2 * NTK);
-            const uint32_t b = f.slot[line] >> (8 * e + 16 * (chunk & 1)) & 255u;
+            const uint32_t b = e ? f.slot[line] >> 16 : f.slot[line] & 0xFFFFu;
             const pk_u32x4& x = f.x[line * NTK + it];
             uint32_t hi, lo;
             split_pair(__uint_as_float(x[2 * e]), __uint_as_float(x[2 * e + 1]), hi, lo);
-            char* const p = lds + stage + wbase + 4096u * it + (b >> 6) * (2 * PLANE) + ((b & 63u) ^ wswz);
+            asm volatile("" : "+v"(hi), "+v"(lo));    // (in front of the load: one register for what is loaded and what was)
+            char* const p = lds + ((wbase ^ b) + stage + 4096u * it);
             *reinterpret_cast<uint32_t*>(p) = hi;
             *reinterpret_cast<uint32_t*>(p + PLANE) = lo;
             if constexpr (e == 1) {
@@ -435,204 +465,310 @@ __device__ __forceinline__ void pairs_tile(const char* __restrict__ A, const Pai
         for (int n = 0; n < NX; ++n) load_x(f, src, n);
 #pragma unroll
         for (int n = 0; n < LINES; ++n) load_slot(f, src, n);
-#pragma unroll
-        for (int n = 0; n < 5; ++n) load_w(f, src, n);
+        load_sel(f, src);
     };
 
-    // ---- products: wavefront = 64 rows of the band x 32 NTK tokens
-    const int wr = wave >> 1, wt = (wave & 1) * 32 * NTK;
+    // ---- products: wavefront = 64 rows of the band x 32 NTK tokens.  A block: the NZ products of 32 k with one token tile, for two row
+    // tiles.  The operands of block b + LEAD are read in front of block b, so the last LEAD blocks of a step stand behind the
+    // barrier that its reads end at, beside the reads for the next one.
+    const int wr = wave >> 1, wt = (wave & 1) * NTK;
     const int ln = lane & 31, lh = lane >> 5;
+    constexpr int NZ = BF ? 2 : 3, NB = 2 * NTK, LEAD = NTK == 1 || NTK == 4 ? 1 : 2, S = LEAD == 1 ? 2 : NTK == 3 ? 3 : 4;
     uint32_t fx[2][2];                                // [unit 0 + lh, 2 + lh][parity of the tile]
 #pragma unroll
     for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int par = 0; par < 2; ++par) fx[u][par] = pr_unit(32 * par + ln, 2 * u + lh) - 2048u * par;
+        for (int par = 0; par < 2; ++par) fx[u][par] = pr_unit(32 * par + ln, 2 * u + lh) - 2048u * par + 2048u * wt;
+    const bool odd_wt = NTK % 2 != 0 && (wt & 1) != 0;       // (NTK odd: the parity of the wavefront's first tile differs)
+    const uint32_t wlane = PW_RING + 2u * wr * PW_TILE + 16u * lane;
     floatx16 acc[2][NTK];
+    bf16x8 w[2][2][2];                                // [32 k][part][row tile]
+    bf16x16 x[S][BF ? 1 : 2];
+    uint32_t sel[2][2], flag[2];                      // [parity of the step][row tile]
+    auto zero_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < NTK; ++j)
+            for (int j = 0; j < NTK; ++j)
 #pragma unroll
-            for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-
-    auto frag_x = [&](uint32_t stage, int plane, int j) __attribute__((always_inline)) {
-        const int tile = (wt >> 5) + j;
-        const char* p = lds + stage + plane * PLANE + 2048 * tile;
-        // (NTK odd: the parity of the wavefront's first tile differs)
-        const bf16x8 lo = *reinterpret_cast<const bf16x8*>(p + ((tile & 1) ? fx[0][1] : fx[0][0]));
-        const bf16x8 hi = *reinterpret_cast<const bf16x8*>(p + ((tile & 1) ? fx[1][1] : fx[1][0]));
+                for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+    };
+    auto frag_x = [&](uint32_t at, int j) __attribute__((always_inline)) {
+        const uint32_t a = ((j & 1) != 0) != odd_wt ? fx[0][1] : fx[0][0], b = ((j & 1) != 0) != odd_wt ? fx[1][1] : fx[1][0];
+        const bf16x8 lo = *reinterpret_cast<const bf16x8*>(lds + (a + at + 2048u * j));
+        const bf16x8 hi = *reinterpret_cast<const bf16x8*>(lds + (b + at + 2048u * j));
         return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15);
     };
-    constexpr int NZ = BF ? 2 : 3, NB = 2 * NTK;      // a block: the NZ products of 32 k with one token tile, for two row tiles
-    bf16x8 w[2][2][2];                                // [set][part][row tile]
-    int ix[2][2];
-    bf16x16 x[2][BF ? 1 : 2];
-    auto read_w = [&](auto set, uint32_t stage, int ss) __attribute__((always_inline)) {
-        constexpr int S = decltype(set)::value;
-        const char* wp = lds + stage + XST + ss * PW_SUB;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-#pragma unroll
-            for (int z = 0; z < 2; ++z) w[S][z][i] = *reinterpret_cast<const bf16x8*>(wp + (2 * wr + i) * PW_TILE + 1024 * z + 16 * lane);
-            ix[S][i] = *reinterpret_cast<const uint16_t*>(wp + PB_TILES * PW_TILE + (2 * wr + i) * 128 + 2 * lane);
-        }
+    auto fragments = [&](bf16x16 (&x)[BF ? 1 : 2], auto bc, uint32_t stage) __attribute__((always_inline)) {         // operands of block b
+        constexpr int b = decltype(bc)::value;
+        x[0] = frag_x(stage + PX_SUB * (b / NTK), b % NTK);
+        if constexpr (!BF) x[1] = frag_x(stage + PX_SUB * (b / NTK) + PLANE, b % NTK);
     };
-    auto read_x = [&](auto set, uint32_t stage, int b) __attribute__((always_inline)) {
-        constexpr int S = decltype(set)::value;
-        if (BF) {
-            x[S][0] = frag_x(stage, b / NTK, b % NTK);
-        } else {
-            x[S][0] = frag_x(stage, 2 * (b / NTK), b % NTK);
-            x[S][BF ? 0 : 1] = frag_x(stage, 2 * (b / NTK) + 1, b % NTK);
-        }
+    auto read_x = [&](auto bc, uint32_t stage) __attribute__((always_inline)) { fragments(x[decltype(bc)::value % S], bc, stage); };
+    auto read_w = [&](auto ssc, uint32_t ring) __attribute__((always_inline)) {
+        constexpr int ss = decltype(ssc)::value;
+        const char* const p = lds + (wlane + ring);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int z = 0; z < 2; ++z) w[ss][z][i] = *reinterpret_cast<const bf16x8*>(p + ss * PW_SUB + i * PW_TILE + 1024 * z);
     };
-    // block b of a step (weights in set b / NTK, activations in set b % 2; NB is even): `between` its products something else
-    auto block = [&](auto bc, auto between) __attribute__((always_inline)) {
-        constexpr int b = decltype(bc)::value, j = b % NTK, W = b / NTK, X = b & 1;
+    // the products of block b; `between` them something else
+    auto products = [&](auto bc, const bf16x8 (&w)[2][2][2], const bf16x16 (&x)[BF ? 1 : 2], const uint32_t (&ix)[2], auto between) __attribute__((always_inline)) {
+        constexpr int b = decltype(bc)::value, j = b % NTK, W = b / NTK;
         static_for<2 * NZ>([&](auto mc) __attribute__((always_inline)) {
             constexpr int m = decltype(mc)::value, z = m >> 1, i = m & 1;
-            if constexpr (BF) acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(w[W][1 - z][i], x[X][0], acc[i][j], ix[W][i], 0, 0);
-            else acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(w[W][z == 0 ? 1 : 0][i], x[X][z == 1 ? 1 : 0], acc[i][j], ix[W][i], 0, 0);
+            const int s = (int)(W ? ix[i] >> 16 : ix[i]);
+            if constexpr (BF) acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(w[W][1 - z][i], x[0], acc[i][j], s, 0, 0);
+            else acc[i][j] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(w[W][z == 0 ? 1 : 0][i], x[z == 1 ? 1 : 0], acc[i][j], s, 0, 0);
             between(mc);
             __builtin_amdgcn_sched_barrier(0x124);
         });
     };
+    auto block = [&](auto bc, const uint32_t (&ix)[2], auto between) __attribute__((always_inline)) { products(bc, w, x[decltype(bc)::value % S], ix, between); };
     using zero = std::integral_constant<int, 0>;
     using one_ = std::integral_constant<int, 1>;
 
-    Carried carried[AHEAD];
-    load_all(carried[0], source(0));
-    static_for<NOPS>([&](auto nc) __attribute__((always_inline)) { operation(carried[0], 0, source(1), nc); });
-    if constexpr (AHEAD == 2) load_all(carried[AHEAD - 1], source(2));
-    lds_barrier();
-    read_w(zero{}, 0, 0);
-    read_x(zero{}, 0, 0);
-    // step t on stage cur, whose first operands are in registers: f holds step t + 1.  The operands of the last block are in
-    // registers when everyone meets, so the first ones of the next step are read beside its products.
-    // SECOND: the steps of the second kind (and a last odd one of the first), few, some of them without products for this
-    // wavefront's rows.
-    auto step = [&](int t, Carried& f, uint32_t cur, auto odd, auto second) __attribute__((always_inline)) {
-        constexpr int ODD = decltype(odd)::value, SECOND = decltype(second)::value, NM = (NB - 1) * 2 * NZ;
-        const uint32_t nxt = STAGE - cur;
-        const bool mul = !SECOND || t < nk || (t < nv && (__builtin_amdgcn_readfirstlane((int)flags[kblock(t)]) >> (8 * wr) & 255) != 0);
-        const Source next = source(t + 1 + AHEAD);
-        if constexpr (SECOND) static_for<NOPS>([&](auto nc) __attribute__((always_inline)) { operation(f, nxt, next, nc); });
-        if (mul) {
-            static_for<NB - 1>([&](auto bc) __attribute__((always_inline)) {
-                constexpr int b = decltype(bc)::value;
-                __builtin_amdgcn_sched_barrier(0);
-                read_x(std::integral_constant<int, (b + 1) & 1>{}, cur, b + 1);
-                if constexpr (b == NTK - 1) read_w(one_{}, cur, 1);
-                block(bc, [&](auto mc) __attribute__((always_inline)) {
-                    constexpr int at = b * 2 * NZ + decltype(mc)::value;
-                    if constexpr (!SECOND)
-                        static_for<(at + 1) * NOPS / NM - at * NOPS / NM>([&](auto pc) __attribute__((always_inline)) {
-                            operation(f, nxt, next, std::integral_constant<int, at * NOPS / NM + decltype(pc)::value>{});
-                        });
-                });
-            });
-        }
-        lds_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        read_w(zero{}, nxt, 0);
-        read_x(zero{}, nxt, 0);
-        if (mul) block(std::integral_constant<int, NB - 1>{}, [](auto) {});
-    };
-    int t = 0;
-#pragma unroll 1
-    for (; t + 2 <= nk; t += 2) {
-        step(t, carried[0], 0, zero{}, zero{});
-        step(t + 1, carried[AHEAD - 1], STAGE, one_{}, zero{});
-    }
-#pragma unroll 1
-    for (; t < nv; t += 2) {
-        step(t, carried[0], 0, zero{}, one_{});
-        step(t + 1, carried[AHEAD - 1], STAGE, one_{}, one_{});
-    }
-    // D: lane l, register q -> row 8 (q / 4) + 4 (l / 32) + q % 4 of the band's tile, token l % 32.  The outputs leave through this
-    // wavefront's part of LDS, 32 tokens x 64 rows at a time, in runs of 256 bytes past the L2 (768 -> 768, 8192 tokens: 30.2
-    // us with stores of 16 bytes from the registers, 28.5 in runs, 26.4 in runs past the L2; from the registers past it 43).
-    lds_barrier();
-    const int R = v.R;
-    char* const mine = lds + wave * 8192;
-    const int r0 = band * PB_ROWS + 64 * wr;
+    // ---- the tile whose products are formed
+    int c_at = at0, c_kb = 0, c_t0, c_band;
+    tile_of(at0, c_t0, c_band);
+
+    // D: lane l, register q -> row 8 (q / 4) + 4 (l / 32) + q % 4 of the band's tile, token l % 32.  The outputs leave through the
+    // wavefront's own part of the weights' stage that is free, 16 tokens x 64 rows at a time, in runs of 256 bytes past the L2 (768 -> 768,
+    // 8192 tokens: 30.2 us with stores of 16 bytes from the registers, 28.5 in runs, 26.4 in runs past the L2; from the registers past it 43).
+    auto store_tile = [&](uint32_t ring) __attribute__((always_inline)) {
+        const int R = v.R, r0 = c_band * PB_ROWS;
+        uint32_t le = threadIdx.x & 63;               // (lane constants worked out again)
+        asm volatile("" : "+v"(le));
+        const uint32_t me = PW_RING + ring + 4096u * wave, tok = le & 15, half = le >> 5;
+        const uint32_t row = 64u * wr + 4u * tok;     // of the band, as this lane stores it
+        const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(C + (int64_t)c_t0 * R + r0, 0, (min(T - c_t0, TOK) * R - r0) * 4, 0x00020000);
+        const uint32_t off = (int)row < R - r0 ? ((le >> 4) * (uint32_t)R + row) * 4u : 0x80000000u;       // (past the end: no access)
 #pragma unroll
-    for (int j = 0; j < NTK; ++j) {
+        for (int j = 0; j < NTK; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if ((le >> 4 & 1) == (uint32_t)h) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            floatx4 o;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) o[e] = acc[i][j][4 * q + e];
+                            *reinterpret_cast<floatx4*>(lds + (me + tok * 256u + (((8u * i + 2u * q + half) ^ tok) << 4))) = o;
+                        }
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const uint32_t tl = 4u * g + (le >> 4);
+                    const pk_u32x4 o = *reinterpret_cast<const pk_u32x4*>(lds + (me + tl * 256u + ((tok ^ tl) << 4)));
+                    __builtin_amdgcn_raw_buffer_store_b128(o, out, (int)(off + (uint32_t)(32 * (wt + j) + 16 * h + 4 * g) * (uint32_t)R * 4u), 0, 2);
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            }
+    };
+
+    // ---- step t on stage P = t % 2 and ring place t % 3.  In front of its barrier: its first NB - LEAD blocks, the second part of what brings
+    // step t + 1 to LDS, the loads of step t + 2's weights.  Behind: its last blocks, the first reads of step t + 1 and
+    // the first part of what brings step t + 2 to LDS.
+    constexpr int PUT_BEHIND = NPUT * LEAD / NB, NFRONT = NPUT - PUT_BEHIND + 5;
+    Carried carried[2];
+    Source far, near;                                 // of the activations (two steps on) and the weights (one step on) of the step that goes to LDS
+    uint32_t ring = 0;                                // place of step t
+    auto next_place = [](uint32_t r) { return r == 2u * PW_STEP ? 0u : r + PW_STEP; };
+    auto second_weights = [&](auto ssc, bf16x8 (&w)[2][2][2], uint32_t (&ix)[2]) __attribute__((always_inline)) {
+        constexpr int ss = decltype(ssc)::value;
+        uint32_t le = threadIdx.x & 63;
+        asm volatile("" : "+v"(le));
+        const int64_t at = (int64_t)c_band * 2 * nk + nk + c_kb;
+        const char* const p = v.blocks + at * PW_STEP + 2 * wr * PW_TILE + 16 * le;
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                floatx4 o;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = acc[i][j][4 * q + e];
-                const int u = 8 * i + 2 * q + lh;
-                *reinterpret_cast<floatx4*>(mine + ln * 256 + ((u ^ (ln & 15)) << 4)) = o;
-            }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int g = 0; g < 8; ++g) {
-            const int tl = 4 * g + (lane >> 4), u = lane & 15;
-            const floatx4 o = *reinterpret_cast<const floatx4*>(mine + tl * 256 + ((u ^ (tl & 15)) << 4));
-            const int tt = t0 + wt + 32 * j + tl;
-            if (tt < T && r0 + 4 * u < R) __builtin_nontemporal_store(o, reinterpret_cast<floatx4*>(C + (int64_t)tt * R + r0 + 4 * u));
+            for (int z = 0; z < 2; ++z) w[ss][z][i] = *reinterpret_cast<const bf16x8*>(p + ss * PW_SUB + i * PW_TILE + 1024 * z);
+        if constexpr (ss == 0) {
+            const uint2 u = *reinterpret_cast<const uint2*>(reinterpret_cast<const char*>(v.sel) + at * PW_SEL + 512 * wr + 8 * le);
+            ix[0] = u.x;
+            ix[1] = u.y;
         }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    }
+    };
+    auto keep_sel = [&](Carried& f, int p) __attribute__((always_inline)) {
+        asm volatile("v_mov_b32 %0, %3\n\tv_mov_b32 %1, %4\n\tv_readfirstlane_b32 %2, %5" : "=&v"(sel[p][0]), "=&v"(sel[p][1]), "=&s"(flag[p]) : "v"(f.sel[0]), "v"(f.sel[1]), "v"(f.flag));
+    };
+    auto step = [&](auto pc) __attribute__((always_inline)) {
+        constexpr int P = decltype(pc)::value;
+        constexpr uint32_t cur = P * PX_STAGE, nxt = PX_STAGE - cur;
+        const uint32_t ring1 = next_place(ring), ring2 = next_place(ring1);
+        constexpr int MF = (NB - LEAD) * 2 * NZ, MB = LEAD * 2 * NZ;
+        Carried& f1 = carried[1 - P];
+        Carried& f2 = carried[P];
+        auto front = [&](auto nc) __attribute__((always_inline)) {
+            constexpr int n = decltype(nc)::value + PUT_BEHIND;
+            if constexpr (n < NPUT) {
+                put(f1, nxt, far, std::integral_constant<int, n>{});
+            } else if constexpr (n < NPUT + 4) {
+                load_w(near.w, ring2, n - NPUT);
+            } else {
+                keep_sel(f1, 1 - P);
+                load_sel(f1, far);
+            }
+        };
+        static_for<NB - LEAD>([&](auto bc) __attribute__((always_inline)) {
+            constexpr int b = decltype(bc)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            read_x(std::integral_constant<int, b + LEAD>{}, cur);
+            if constexpr (b == NTK - LEAD) read_w(one_{}, ring);
+            block(bc, sel[P], [&](auto mc) __attribute__((always_inline)) {
+                constexpr int at = b * 2 * NZ + decltype(mc)::value;
+                static_for<(at + 1) * NFRONT / MF - at * NFRONT / MF>([&](auto oc) __attribute__((always_inline)) {
+                    front(std::integral_constant<int, at * NFRONT / MF + decltype(oc)::value>{});
+                });
+            });
+        });
+        near = far;
+        advance(far);
+        // rows with a third or fourth weight among four k: those weights over the same activations, by the wavefronts that have any
+        if ((flag[P] >> (8 * wr) & 255u) != 0) {
+            bf16x8 w2[2][2][2];
+            uint32_t ix[2];
+            __builtin_amdgcn_sched_barrier(0);
+            second_weights(zero{}, w2, ix);
+            if constexpr (NTK < 3) second_weights(one_{}, w2, ix);
+            static_for<NB>([&](auto bc) __attribute__((always_inline)) {
+                constexpr int b = decltype(bc)::value;
+                if constexpr (NTK >= 3 && b == NTK) {         // (no room for both)
+                    __builtin_amdgcn_sched_barrier(0);
+                    second_weights(one_{}, w2, ix);
+                }
+                bf16x16 x2[BF ? 1 : 2];
+                fragments(x2, bc, cur);
+                products(bc, w2, x2, ix, [](auto) {});
+            });
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        wait_loads<VM>();                             // the weights of step t + 1 (loaded in step t - 1) are in LDS
+        lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        auto behind = [&](auto nc) __attribute__((always_inline)) { put(f2, cur, far, nc); };
+        auto reads = [&](auto dc) __attribute__((always_inline)) {
+            constexpr int d = decltype(dc)::value;
+            if constexpr (d == 0) read_w(zero{}, ring1);
+            read_x(dc, nxt);
+        };
+        static_for<LEAD>([&](auto dc) __attribute__((always_inline)) {
+            constexpr int d = decltype(dc)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            reads(dc);
+            block(std::integral_constant<int, NB - LEAD + d>{}, sel[P], [&](auto mc) __attribute__((always_inline)) {
+                constexpr int at = d * 2 * NZ + decltype(mc)::value;
+                static_for<(at + 1) * PUT_BEHIND / MB - at * PUT_BEHIND / MB>([&](auto oc) __attribute__((always_inline)) {
+                    behind(std::integral_constant<int, at * PUT_BEHIND / MB + decltype(oc)::value>{});
+                });
+            });
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // behind the last step of a tile: its outputs
+    bool live = true;
+    auto finish = [&]() __attribute__((always_inline)) {
+        const uint32_t place = ring;
+        ring = next_place(ring);
+        if (++c_kb < nk) return;
+        if (live) store_tile(place);
+        live = live && is_tile(c_at + 32);
+        c_kb = 0;
+        if (live) {
+            c_at += 32;
+            tile_of(c_at, c_t0, c_band);
+        }
+        zero_sums();
+    };
+
+    aim(far, at0);
+    load_all(carried[0], far);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) load_w(far.w, 0, n);
+    advance(far);
+    load_all(carried[1], far);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) load_w(far.w, PW_STEP, n);
+    advance(far);
+    zero_sums();
+    static_for<NPUT>([&](auto nc) __attribute__((always_inline)) { put(carried[0], 0, far, nc); __builtin_amdgcn_sched_barrier(0); });
+    keep_sel(carried[0], 0);
+    load_sel(carried[0], far);
+    near = far;                                       // (the weights of step 2)
+    advance(far);
+    static_for<PUT_BEHIND>([&](auto nc) __attribute__((always_inline)) { put(carried[1], PX_STAGE, far, nc); __builtin_amdgcn_sched_barrier(0); });
+    wait_loads<LOADS>();                              // (what came behind the weights of step 1)
+    lds_barrier();
+    read_w(zero{}, 0);
+    static_for<LEAD>([&](auto dc) __attribute__((always_inline)) { read_x(dc, 0); });
+    // (one way out of the loop, so that the waits for what is carried round it count all of the loads between: an odd number of steps is
+    // followed by one for nobody)
+#pragma unroll 1
+    do {
+        step(zero{});
+        finish();
+        step(one_{});
+        finish();
+    } while (live);
+    // nothing may arrive in LDS that is not ours any more
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    lds_barrier();
 }
 
-// `full` token tiles of 64 NTK tokens, the tokens behind them in tiles of 64 (TAIL)
-template <bool BF, int NTK, int AHEAD, bool TAIL>
+// `full` token tiles of 64 NTK tokens, the tokens behind them in tiles of 64 (TAIL).  Workgroup = (XCD, one of its 32 CUs).
+template <bool BF, int NTK, bool TAIL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_pairs(const char* __restrict__ A, const PairsView v, float* __restrict__ C, int T, int full) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int xcd = (int)(blockIdx.x & 7), at = (int)(blockIdx.x >> 3);
-    const int nfull = full * v.bands, Q = (nfull + 7) >> 3;
-    int mi, band;
-    if (at < Q) {
-        const int id = xcd * Q + at;
-        if (id >= nfull) return;
-        tile_coords(id, full, v.bands, mi, band);
-        pairs_tile<BF, NTK, AHEAD>(A, v, C, T, mi * 64 * NTK, band, lds);
-    } else if constexpr (TAIL) {
-        const int t1 = full * 64 * NTK, rest = (T - t1 + 63) / 64, ntail = rest * v.bands, QT = (ntail + 7) >> 3;
-        const int id = xcd * QT + at - Q;
-        if (at - Q >= QT || id >= ntail) return;
-        tile_coords(id, rest, v.bands, mi, band);
-        pairs_tile<BF, 1, AHEAD>(A, v, C, T, t1 + mi * 64, band, lds);
+    const int xcd = (int)(blockIdx.x & 7), first = (int)(blockIdx.x >> 3);
+    const int Q = (full * v.bands + 7) >> 3;
+    pairs_tiles<BF, NTK>(A, v, C, T, 0, full, xcd, Q, first, lds);
+    if constexpr (TAIL) {
+        const int t1 = full * 64 * NTK, rest = (T - t1 + 63) / 64, QT = (rest * v.bands + 7) >> 3;
+        // (the CUs that have a tile less begin)
+        pairs_tiles<BF, 1>(A, v, C, T, t1, rest, xcd, QT, first >= Q % 32 ? first - Q % 32 : first - Q % 32 + 32, lds);
     }
 }
 
-template <bool BF, int NTK, int AHEAD, bool TAIL>
+template <bool BF, int NTK, bool TAIL>
 static int launch_pairs(const void* A, const PairsView& v, float* C, int T, int full, hipStream_t s) {
-    constexpr int STAGE = 64 * NTK * 64 * (BF ? 2 : 4) + PK_BLOCK;
-    const unsigned bytes = 2 * STAGE + (unsigned)align_up(2 * (size_t)v.nk, 16);
     static uint64_t done = 0;
-    const int rc = allow_lds(reinterpret_cast<const void*>(&k_gemm_pairs<BF, NTK, AHEAD, TAIL>), 2 * STAGE + 4096, done);
+    const int rc = allow_lds(reinterpret_cast<const void*>(&k_gemm_pairs<BF, NTK, TAIL>), PAIRS_LDS, done);
     if (rc != MST_OK) return rc;
     const int64_t tail = full * 64 * NTK < T ? cdiv(T - full * 64 * NTK, 64) : 0;
     const int64_t per_xcd = cdiv((int64_t)full * v.bands, 8) + cdiv(tail * v.bands, 8);
-    k_gemm_pairs<BF, NTK, AHEAD, TAIL><<<(unsigned)(8 * per_xcd), 512, bytes, s>>>(static_cast<const char*>(A), v, C, T, full);
+    k_gemm_pairs<BF, NTK, TAIL><<<(unsigned)(8 * std::min<int64_t>(32, per_xcd)), 512, PAIRS_LDS, s>>>(static_cast<const char*>(A), v, C, T, full);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }
 
-// What a step of the second kind takes against one of the first: nothing goes to LDS beside its products, and a wavefront without any
-// waits for the others.
-constexpr double SECOND_STEP_F32 = 1.4, SECOND_STEP_BF16 = 1.3;
-
-// Microseconds of an fp32 product with `full` token tiles of 128, the rest in tiles of 64.  (Per step of 64 k: 1.41 with 128 tokens
-// on every CU, 0.93 on a few, 0.81 and 0.70 with 64: the weights of a step cost the same for either.)
-static double pairs_f32_us(int T, int R, int K, int full, double second) {
-    const int64_t bands = cdiv(R, PB_ROWS), rest = std::max(0, T - 128 * full);
-    const int64_t Q = cdiv(full * bands, 8), QT = cdiv(cdiv(rest, 64) * bands, 8);
-    return (xcd_rounds(Q, 32, 8, 1.41, 0.93) + xcd_rounds(QT, 32, 8, 0.81, 0.70)) * (K / PK_STEP) * (1.0 + SECOND_STEP_F32 * second) +
-           (double)cdiv(Q, 32) * 7.4 + (double)cdiv(QT, 32) * 4.6;
+// What the second weights add to the steps' time where a share `second` of them has any: the wavefronts of the 64-row groups without wait
+// for the others, so a step with one such group costs a third of a step and one with four of them a whole one (taken as
+// 1.5: such masks have full rows, and stay with the dense kernels where those are as fast).  (Y of 768 -> 3072, 8190
+// tokens, fp32, densities 0.07, 0.10, 0.11, 0.12, 0.25: 71, 73, 81, 100, 133 us; bfloat16, 256 tokens: 55, 57, 64, 75, 89.)
+static double second_part(double second, bool bf16) {
+    const double group = 1.0 - std::sqrt(std::sqrt(1.0 - second));        // share of the steps in which a group has some
+    return (bf16 ? 0.40 : 0.35) * second + 1.15 * group * group;
 }
 
-// Token tiles of 128 of an fp32 product.  A CU holds one workgroup, so 320 tiles are two rounds, the second one a quarter full:
+// Microseconds of an fp32 product with `full` token tiles of 128, the rest in tiles of 64.  (Per step of 64 k: 1.36 with 128 tokens
+// on every CU, 0.92 on a few, 0.89 and 0.68 with 64: the weights of a step cost the same for either.  222 products of whole tiles, sd 5 %.)
+static double pairs_f32_us(int T, int R, int K, int full, double second) {
+    const int64_t bands = cdiv(R, PB_ROWS), rest = std::max(0, T - 128 * full), steps = K / PK_STEP;
+    const int64_t Q = cdiv(full * bands, 8), QT = cdiv(cdiv(rest, 64) * bands, 8);
+    return xcd_rounds(Q, 32, 8, 1.36, 0.92) * steps * (1.0 + second_part(second, false)) + xcd_rounds(QT, 32, 8, 0.89, 0.68) * steps * (1.0 + 2.0 * second_part(second, false)) +
+           (Q > 0 ? 2.6 + cdiv(Q, 32) * 4.7 : 0.0) + (QT > 0 ? 3.4 + cdiv(QT, 32) * 1.5 : 0.0);
+}
+
+// Token tiles of 128 of an fp32 product.  320 tiles are two rounds of the CUs, the second one a quarter full:
 // the tokens behind the last full round go in tiles of 64, twice as many CUs for them, where that is the shorter way (5120
 // -> 1280, 8192 tokens: 212 -> 186 us; 3840 -> 1280: 161 -> 141; all of them where 128 would leave half of the CUs idle: 3072 -> 768,
-// 2048 tokens: 57 -> 41).
+// 2048 tokens: 57 -> 41, before a workgroup's tiles followed each other without a break).
 static int pairs_full_tiles(int T, int R, int K) {
     const int all = (int)cdiv(T, 128);
     if (gemm_pairs_forced()) return T % 3 == 0 ? all : T % 3 == 1 ? 0 : all / 2;      // (pinned: every kind)
@@ -643,14 +779,16 @@ static int pairs_full_tiles(int T, int R, int K) {
 // C [T x R] = A [T x K] S^T, S given by its packed pairs; tokens: of a workgroup's tile (fp32: pairs_full_tiles)
 int gemm_pairs(const void* A, mst_dtype act, const PairsView& v, float* C, int T, int tokens, hipStream_t s) {
     if (v.R % 4 || v.K % PK_STEP) return MST_ERR_ARG;
-    if (act == MST_F32) return launch_pairs<false, 2, 2, true>(A, v, C, T, pairs_full_tiles(T, v.R, v.K), s);
+    if (act == MST_F32) return launch_pairs<false, 2, true>(A, v, C, T, pairs_full_tiles(T, v.R, v.K), s);
     const int full = (int)cdiv(T, tokens);
-    return tokens == 128 ? launch_pairs<true, 2, 2, false>(A, v, C, T, full, s) : tokens == 192 ? launch_pairs<true, 3, 2, false>(A, v, C, T, full, s)
-                                                                                : launch_pairs<true, 4, 1, false>(A, v, C, T, full, s);
+    return tokens == 128 ? launch_pairs<true, 2, false>(A, v, C, T, full, s) : tokens == 192 ? launch_pairs<true, 3, false>(A, v, C, T, full, s)
+                                                                                : launch_pairs<true, 4, false>(A, v, C, T, full, s);
 }
 
 // ------------------------------------------------------------------ choice
-constexpr double PAIRS_LINE = 0.12;
+// Above, four steps in five have second weights and the products are within 10 % of the dense kernels on either side (Y of 1024 -> 4096, 16384
+// tokens, fp32: 268 of 313 us at 0.11, 306 of 307 at 0.119).
+constexpr double PAIRS_LINE = 0.118;
 
 // share of the steps of a uniformly random mask that need a second one
 static double second_steps(double d) {
@@ -682,21 +820,18 @@ static double pairs_us(mst_dtype act, int T, int R, int K, int tokens, double se
     if (act == MST_F32) return pairs_f32_us(T, R, K, pairs_full_tiles(T, R, K), second);
     const int64_t Q = cdiv(cdiv(T, tokens) * cdiv(R, PB_ROWS), 8);
     double full, lone, ends;
-    if (tokens == 256) full = 1.95, lone = 1.3, ends = 9.0;
-    else if (tokens == 192) full = 1.5, lone = 0.95, ends = 7.0;
-    else full = 1.2, lone = 0.8, ends = 5.0;
-    return xcd_rounds(Q, 32, 8, full, lone) * (K / PK_STEP) * (1.0 + SECOND_STEP_BF16 * second) + (double)cdiv(Q, 32) * ends;
+    if (tokens == 256) full = 1.78, lone = 1.25, ends = 11.5;
+    else if (tokens == 192) full = 1.40, lone = 1.08, ends = 8.0;
+    else full = 1.13, lone = 0.90, ends = 4.7;
+    return 3.0 + xcd_rounds(Q, 32, 8, full, lone) * (K / PK_STEP) * (1.0 + second_part(second, true)) + (double)cdiv(Q, 32) * ends;
 }
 
 // Of the packing, with the choice of the pairs or without (measured 64 x 64 to 5120 x 5120, within 2 us).
 double making_pairs_us(const mst_layer* L, bool match) { return 5.0 + 1.5e-6 * (double)L->N + (match ? 14.0 + 1.6e-6 * (double)L->N : 0.0); }
 
 // Tokens of a tile, 0 where the dense kernels are ahead.  making_us: what this product spends on the packed weights before it reads them
-// 3040 products on three cards (layers of 256 to 6000, 1024 to 16384 tokens, densities 0.03 to 0.12, a quarter with full rows): the modelled times
-// are, of the measured ones, 0.93 to 1.02 by card in fp32 (sd 0.06, where few steps go a second time), of the dense kernels there 0.96 to
-// 1.04 (0.10); in bfloat16 1.12 to 1.21, 1.05 to 1.13 and 1.13 to 1.21 (0.05) for 128, 192 and 256 tokens, dense 1.18 to 1.25 (0.07).  The choice
-// loses 0.3 % against the best of all kernels, 21 % at the worst, and leaves 9 of 2062 fp32 and 2 of 978 bfloat16 products slower than the
-// dense kernels by more than 3 % (12 % at the worst).  With second steps at 0.8 of a first one and first ones 7 % dearer in fp32: 94 and 33, 23 %.
+// 468 products of whole tiles (layers of 256 to 5120, 2048 to 16384 tokens, densities 0.03 to 0.11): the modelled times are the measured ones
+// in fp32 (sd 0.05) and 1.2 of them in bfloat16 (sd 0.03 to 0.04), as those of the dense kernels are there (0.96 to 1.04 and 1.18 to 1.25).
 int pairs_tokens(const mst_layer* L, bool y, mst_dtype act, int T, int64_t split_floats, double making_us) {
     const double d = (double)L->nnz / (double)L->N;
     if (!L->pairs_y.blocks) return 0;

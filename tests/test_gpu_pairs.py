@@ -177,3 +177,29 @@ def test_recordings_side_by_side():
         for Y, dX in outs:
             assert rel_err(Y.cpu().numpy(), Yr) <= PARTS, k
             assert rel_err(dX.cpu().numpy(), dXr) <= PARTS, k
+
+
+# Workgroups that form more tiles than one, whose steps follow each other without a break: one, two and odd numbers of steps a tile, three
+# kinds of token tiles (by T mod 3), a cut-off last band and last token tile, tiles for some workgroups of an XCD only.
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("density", [0.07, 0.13])
+@pytest.mark.parametrize("T,I,O", [(16385, 64, 1280), (16386, 128, 960), (16384, 192, 1024), (20000, 320, 832), (10020, 64, 2880), (9001, 448, 1856)])
+def test_tiles_in_a_row(T, I, O, density, dtype):
+    print("case", T, I, O, density, dtype, flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T + I)
+    act, td = (mst.MST_BF16, torch.bfloat16) if dtype == "bf16" else (mst.MST_F32, torch.float32)
+    W, M = synth.make_layer(5, 1, I, O, density)
+    X = torch.randn(T, I, generator=g, device=DEV).to(td)
+    dY = torch.randn(T, O, generator=g, device=DEV).to(td)
+    rig = Rig(W, M, 64, cap=O * I)
+    rig.layer.set_path(mst.MST_PATH_DENSE)
+    Wd = dev(W).double() * dev(M)
+    Y = torch.full((T, O), float("nan"), device=DEV)
+    dX = torch.full((T, I), float("nan"), device=DEV)
+    mst.mst_sparse_fc_fwd(rig.layer, X, Y, T, act)
+    assert mst.mst_gemm_last_tile() == PAIRS
+    mst.mst_sparse_fc_bwd_input(rig.layer, dY, dX, T, act)
+    assert mst.mst_gemm_last_tile() == PAIRS
+    for got, ref in ((Y, X.double() @ Wd.t()), (dX, dY.double() @ Wd)):
+        assert float((got.double() - ref).abs().max()) <= PARTS * float(ref.abs().max())
