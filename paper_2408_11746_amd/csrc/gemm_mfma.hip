@@ -288,13 +288,16 @@ void k_gemm_split(const float* __restrict__ A, int64_t lda, const float* __restr
 // Threads 0..255 stage A, 256..511 stage B.  LDS rows are 32 k = 64 bytes = four 16-byte
 // units; row m sits at position rho(m) (the two low bit pairs of m swapped inside its group of
 // 16) and its unit u at (u ^ (rho >> 2) ^ (rho >> 4)) & 3: the MFMA operand reads of 16
-// consecutive rows, the k-major stores (rows four apart) and the m-major stores (four rows x
-// four units) each cover all banks once.
+// consecutive rows and the m-major stores (four rows x four units) each cover all banks once.  A store takes eight lanes at
+// a time, 128 bytes a clock: where they go to rows four or two apart (APART, k-major operands) a term more keeps them apart
+// (two of the eight met: 12 % of the kernel's cycles in the dense gradient of 1280 x 5120).
 constexpr int BM2 = 256, BN2 = 256, SPK2 = 32;
 
+template <int APART = 0>
 __device__ inline uint32_t bf_unit32(int m, int u) {
     const int rho = (m & ~15) | ((m & 3) << 2) | ((m >> 2) & 3);
-    return (uint32_t)(rho * 64 + (((u ^ (rho >> 2) ^ (rho >> 4)) & 3) << 4));
+    const int other = APART == 4 ? rho & 2 : APART == 2 ? rho >> 1 & 1 : 0;
+    return (uint32_t)(rho * 64 + (((u ^ (rho >> 2) ^ (rho >> 4) ^ other) & 3) << 4));
 }
 
 // Staging roles.  A thread stages four "pieces" per step; a piece is one 16-byte LDS unit in each
@@ -326,10 +329,10 @@ __device__ inline void split256_pair(const float4 (&r)[8], int piece, int q, uin
 // byte offset of that piece inside one half of its operand's tile
 template <int LAYOUT>
 __device__ inline uint32_t split256_unit(int p, int h, int piece) {
-    if (LAYOUT == 0) return bf_unit32(4 * (p & 63) + piece, p >> 6);
+    if (LAYOUT == 0) return bf_unit32<4>(4 * (p & 63) + piece, p >> 6);
     if (LAYOUT == 1) return bf_unit32(mmajor_row(p, piece), p & 3);
     if (piece < 2) return bf_unit32(mmajor_row(p, 2 * h + piece), p & 3);
-    return bf_unit32(4 * (p & 63) + 2 * h + piece - 2, p >> 6);
+    return bf_unit32<4>(4 * (p & 63) + 2 * h + piece - 2, p >> 6);
 }
 
 template <bool A_KMAJOR, bool B_KMAJOR>
@@ -482,7 +485,7 @@ void k_gemm_split256(const float* __restrict__ A, int64_t lda, const float* __re
             bf16x8 ah[2], al[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                const uint32_t ua = bf_unit32(wm + 32 * i + lm, 2 * ks + lk);
+                const uint32_t ua = bf_unit32<A_KMAJOR ? 4 : 0>(wm + 32 * i + lm, 2 * ks + lk);
                 ah[i] = *reinterpret_cast<const bf16x8*>(Ah + ua);
                 al[i] = *reinterpret_cast<const bf16x8*>(Al + ua);
             }
@@ -491,7 +494,7 @@ void k_gemm_split256(const float* __restrict__ A, int64_t lda, const float* __re
                 bf16x8 bh[2], bl[2];
 #pragma unroll
                 for (int jj = 0; jj < 2; ++jj) {
-                    const uint32_t ub = bf_unit32(wn + 32 * (2 * jp + jj) + lm, 2 * ks + lk);
+                    const uint32_t ub = bf_unit32<B_KMAJOR ? 4 : 0>(wn + 32 * (2 * jp + jj) + lm, 2 * ks + lk);
                     bh[jj] = *reinterpret_cast<const bf16x8*>(Bh + ub);
                     bl[jj] = *reinterpret_cast<const bf16x8*>(Bl + ub);
                 }
@@ -651,8 +654,8 @@ void k_gemm_split_n160(const float* __restrict__ A, int64_t lda, const float* __
         const int q = tid < 2 * BNW ? tid : tid - 2 * BNW, nq = q % (BNW / 2), kg = q / (BNW / 2);
         voff[2] = (uint32_t)(8 * kg * pb + 8 * nq);
         voff[3] = 0;
-        wr_unit[2] = 2 * PLANE + bf_unit32(2 * nq, kg);
-        wr_unit[3] = 2 * PLANE + bf_unit32(2 * nq + 1, kg);
+        wr_unit[2] = 2 * PLANE + bf_unit32<2>(2 * nq, kg);
+        wr_unit[3] = 2 * PLANE + bf_unit32<2>(2 * nq + 1, kg);
     }
     float4 r[8];
     auto fetch = [&](int k0) __attribute__((always_inline)) {
@@ -707,7 +710,7 @@ void k_gemm_split_n160(const float* __restrict__ A, int64_t lda, const float* __
             bf16x8 bh[NJ], bl[NJ];
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
-                const uint32_t ub = bf_unit32(32 * j + lm, 2 * ks + lk);
+                const uint32_t ub = bf_unit32<B_KMAJOR ? 2 : 0>(32 * j + lm, 2 * ks + lk);
                 bh[j] = *reinterpret_cast<const bf16x8*>(Bh + ub);
                 bl[j] = *reinterpret_cast<const bf16x8*>(Bl + ub);
             }

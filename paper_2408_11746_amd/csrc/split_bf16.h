@@ -12,9 +12,10 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // An LDS row is 64 k of bf16 = 128 bytes = eight 16-byte units; unit u of row m is kept at
-// position u ^ ((m >> 1) & 7): the MFMA operand reads of 16 consecutive rows then cover all
-// banks once.
-__device__ inline uint32_t bf_unit(int m, int u) { return (uint32_t)(m * 128 + ((u ^ ((m >> 1) & 7)) << 4)); }
+// position u ^ ((m >> 1 ^ m >> 4) & 7): the MFMA operand reads of 16 consecutive rows then cover all
+// banks once, and so do the stores of eight lanes to rows two, four or eight apart (a store takes 128 bytes a clock, a
+// read 256).
+__device__ inline uint32_t bf_unit(int m, int u) { return (uint32_t)(m * 128 + ((u ^ ((m >> 1 ^ m >> 4) & 7)) << 4)); }
 
 __device__ inline uint32_t cvt_pk_bf16(float a, float b) {       // {bf16(a), bf16(b)}, round to nearest even
     uint32_t r;
