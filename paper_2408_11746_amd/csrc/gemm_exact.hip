@@ -38,12 +38,15 @@ namespace mst {
 typedef uint32_t ex_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t ex_u32x2 __attribute__((ext_vector_type(2)));
 
-// LDS position of unit u (eight k) of row m in a plane of rows of 32 k (64 bytes) or 64 k (128 bytes)
+// LDS position of unit u (eight k) of row m in a plane of rows of 32 k (64 bytes) or 64 k (128 bytes).  Sixteen lanes read, and eight lanes
+// store, without meeting in a bank: rows 0, 4, 8, 12 lie side by side, and the units of rows that are a multiple of 128 bytes apart
+// are exchanged differently for each of them (k-major stores take every other row; before the last term of the exchange, and with
+// m-major stores of consecutive rows, a third of the LDS cycles were conflicts).
 template <int TM>
 __device__ inline uint32_t ex_unit(int m, int u) {
     if (TM == 64) return bf_unit(m, u);
     const int rho = (m & ~15) | ((m & 3) << 2) | ((m >> 2) & 3);
-    return (uint32_t)(rho * 64 + (((u ^ (rho >> 2) ^ (rho >> 4)) & 3) << 4));
+    return (uint32_t)(rho * 64 + (((u ^ (rho >> 2) ^ (rho >> 4) ^ (rho >> 1 & 1)) & 3) << 4));
 }
 
 // a pair of fp32 values as three words of two bfloat16 each.  The parts are rounded to nearest, so the lower
@@ -86,6 +89,15 @@ struct ExOperand {
     float f[BF16 ? 1 : 16];      // piece j, k kk: k-major f[2 kk + j], m-major f[8 j + kk]
     ex_u32x4 h[BF16 ? 2 : 1];
 
+    // Which row and unit thread p stages as its piece j.  (m-major, 128 tile: eight lanes store 128 consecutive bytes, the four units of two
+    // rows that lie together.)
+    __device__ static __forceinline__ int row(int p, int j) {
+        if constexpr (KMAJOR) return 2 * (p % (TM / 2)) + j;
+        else if constexpr (TM == 64) return (j * 256 + p) / UNITS;
+        else return 64 * j + 16 * (p >> 6) + 4 * (p >> 2 & 3) + (p >> 4 & 3);
+    }
+    __device__ static __forceinline__ int unit(int p) { return KMAJOR ? p / (TM / 2) : p % UNITS; }
+
     // rows (k-major: k, m-major: m) of the tile past the end are cut off by the descriptor
     __device__ __forceinline__ void fetch(const T* __restrict__ src, int64_t ld, int k0, int m0, int kend, int Mdim, int p) {
         const int64_t corner = KMAJOR ? (int64_t)k0 * ld + m0 : (int64_t)m0 * ld + k0;
@@ -95,7 +107,7 @@ struct ExOperand {
         const uint32_t pitch = (uint32_t)ld * (uint32_t)sizeof(T);
         if constexpr (KMAJOR) {
             static_assert(!BF16, "a bfloat16 operand is m-major");
-            const uint32_t o = (uint32_t)(8 * (p / (TM / 2))) * pitch + (uint32_t)(8 * (p % (TM / 2)));
+            const uint32_t o = (uint32_t)(8 * unit(p)) * pitch + (uint32_t)(4 * row(p, 0));
 #pragma unroll
             for (int kk = 0; kk < 8; ++kk) {
                 const ex_u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(o + kk * pitch), 0, 0);
@@ -105,8 +117,7 @@ struct ExOperand {
         } else {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int idx = j * 256 + p, m = idx / UNITS, u = idx % UNITS;
-                const uint32_t o = (uint32_t)m * pitch + (uint32_t)(8 * u) * (uint32_t)sizeof(T);
+                const uint32_t o = (uint32_t)row(p, j) * pitch + (uint32_t)(8 * unit(p)) * (uint32_t)sizeof(T);
                 if constexpr (BF16) {
                     if ((ld & 1) == 0) {
                         h[j] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)o, 0, 0);
@@ -135,7 +146,7 @@ struct ExOperand {
         if constexpr (!KMAJOR) {
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int valid = kend - (k0 + 8 * ((j * 256 + p) % UNITS));      // k of this unit that exist
+                const int valid = kend - (k0 + 8 * unit(p));      // k of this unit that exist
                 if constexpr (BF16) {
 #pragma unroll
                     for (int d = 0; d < 4; ++d)
@@ -151,9 +162,7 @@ struct ExOperand {
         constexpr int PLANE = TM * BK * 2;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            uint32_t a;
-            if constexpr (KMAJOR) a = ex_unit<TM>(2 * (p % (TM / 2)) + j, p / (TM / 2));
-            else a = ex_unit<TM>((j * 256 + p) / UNITS, (j * 256 + p) % UNITS);
+            const uint32_t a = ex_unit<TM>(row(p, j), unit(p));
             if constexpr (BF16) {
                 *reinterpret_cast<ex_u32x4*>(lds + a) = h[j];
             } else {
@@ -173,10 +182,9 @@ struct ExOperand {
 
 // Tile numbers run in bands of eight tile rows, column by column inside a band (the tiles an XCD works on
 // at a time share operand panels in its L2); XCD x takes a contiguous share, one k range after the other.
-// (TN has the fewest registers: left to itself the compiler takes two more than three workgroups on a CU can have; dense
-// gradient of 5001 x 1000 -> 4000 with two 220 us, with three 218.4.)
-template <bool A16, bool A_KMAJOR, bool B_KMAJOR, int TM>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(A_KMAJOR ? 3 : 2, 3)))
+// PER_CU: workgroups on a CU that the registers are for (plan_exact's choice; 0: as many as the LDS holds).
+template <bool A16, bool A_KMAJOR, bool B_KMAJOR, int TM, int PER_CU>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PER_CU ? PER_CU : 2, PER_CU ? PER_CU : 3)))
 void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
                   int M, int N, int Kdim, int k_per_split, int64_t split_stride) {
     typedef ExOperand<A16, A_KMAJOR, TM> OpA;
@@ -519,17 +527,21 @@ void k_gemm_stream(const void* __restrict__ Av, int64_t lda, const void* __restr
 
 // Kernel, workgroup tile and number of k ranges together, as for the split kernels: modelled time = rounds
 // one XCD needs for its share of the tiles x time of a workgroup, plus a launch and the traffic of the
-// partial outputs.  Places of an XCD: 64 workgroups of 128 x 128, 96 of 64 x 64, 32 of the streaming
+// partial outputs.  Places of an XCD: 64 or 96 workgroups of 128 x 128, 96 of 64 x 64, 32 of the streaming
 // kernel; with no more workgroups than CUs each has one to itself and is faster.  Microseconds fitted to timings
 // of 130 products, 1 to 40 GFLOP, on MI355X (8-14 % rms error).
+// Three 128 x 128 workgroups of fp32 operands on a CU take 1.45 times as long as two (1.56 with both operands k-major; 115 shapes, sd 4 to
+// 7 %), so which of the two is ahead is a matter of how the tiles fill the rounds: Y of 1000 -> 4000, 5001 tokens (1280 tiles), 240 us with
+// two and 212 with three, of 1203 -> 801, 16001 tokens (882 tiles), 191 and 212.  (bfloat16 A: three always, as its constants were fitted.)
 struct ExactPlan {
     int tile;
     bool stream;
     int nsplit;
     double us;
+    int places;
 };
 static int g_exact_tile = 0;                          // test hook: 0 automatic, 64 or 128, streaming: 32 or 96 (64 x 64)
-static ExactPlan plan_exact(int M, int N, int Kdim, bool a16, int64_t max_split, bool summed) {
+static ExactPlan plan_exact(bool three, bool tn, int M, int N, int Kdim, bool a16, int64_t max_split, bool summed) {
     struct Kind {
         int hook, tile;
         bool stream;
@@ -539,29 +551,32 @@ static ExactPlan plan_exact(int M, int N, int Kdim, bool a16, int64_t max_split,
         double full[2], lone[2], start[2], launch[2];
     };
     static const Kind kinds[] = {{128, 128, false, 64, 32, 32, {2.71, 1.64}, {1.78, 1.08}, {1.4, 1.2}, {2.6, 4.0}},
+                                 {128, 128, false, 96, 32, 32, {3.92, 0.0}, {1.78, 0.0}, {1.4, 0.0}, {2.6, 0.0}},
                                  {64, 64, false, 96, 32, 64, {2.63, 1.65}, {1.47, 0.97}, {0.5, 0.7}, {3.3, 3.6}},
                                  {32, 32, true, 32, 0, 128, {0.0052, 0.0046}, {0.0046, 0.0040}, {3.1, 2.6}, {2.9, 3.1}},
                                  {96, 64, true, 32, 0, 128, {0.0131, 0.0117}, {0.0108, 0.0106}, {3.7, 2.6}, {2.8, 3.1}}};
     static const int cand[] = {1, 2, 3, 4, 5, 6, 8, 10, 12, 16};
-    ExactPlan best{0, false, 1, 0.0};
+    ExactPlan best{0, false, 1, 0.0, 0};
     for (const Kind& kd : kinds) {
         if (g_exact_tile && kd.hook != g_exact_tile) continue;
         const int64_t Q = cdiv(cdiv(M, kd.tile) * cdiv(N, kd.tile), 8);
-        const double full = kd.full[a16], lone = kd.lone[a16];
+        if ((a16 || !three) && kd.full[1] == 0.0) continue;
+        const double full = kd.full[a16] * (tn && kd.tile == 128 && kd.places == 96 ? 1.07 : 1.0), lone = kd.lone[a16];
         for (int ns : cand) {
             if (ns > 1 && (ns > max_split || Kdim / ns < 256)) break;
             const double work = xcd_rounds(Q * ns, kd.places, kd.lone_places, full, lone);
             double cost = kd.launch[a16] + (kd.stream ? work * (double)cdiv(Kdim, ns) + (double)cdiv(Q * ns, kd.places) * kd.start[a16]
                                                       : work * ((double)cdiv(cdiv(Kdim, ns), kd.bk) + kd.start[a16]));
             if (ns > 1) cost += 3.0 + 1.0e-6 * (double)M * (double)N * (summed ? ns + 1.0 : 0.25 * ns);
-            if (best.tile == 0 || cost < best.us) best = ExactPlan{kd.tile, kd.stream, ns, cost};
+            if (best.tile == 0 || cost < best.us) best = ExactPlan{kd.tile, kd.stream, ns, cost, kd.places};
         }
     }
     return best;
 }
 
+// (with two 128 x 128 workgroups on a CU: the lines between the kernels were drawn with these times)
 double gemm_exact_us(mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed) {
-    return plan_exact(M, N, Kdim, a_dt == MST_BF16, max_split, summed).us;
+    return plan_exact(false, false, M, N, Kdim, a_dt == MST_BF16, max_split, summed).us;
 }
 
 int gemm_exact_tile(int tile) {
@@ -573,7 +588,7 @@ template <bool A16, bool AK, bool BKM>
 static int launch_exact(const void* A, int64_t lda, const float* B, int64_t ldb, float* C, int M, int N, int Kdim,
                         float* split_ws, int64_t split_ws_floats, int* nparts, hipStream_t s) {
     const int64_t mn = (int64_t)M * N;
-    const ExactPlan plan = plan_exact(M, N, Kdim, A16, split_ws ? split_ws_floats / mn : 1, nparts == nullptr);
+    const ExactPlan plan = plan_exact(true, AK, M, N, Kdim, A16, split_ws ? split_ws_floats / mn : 1, nparts == nullptr);
     const int kps = (int)(cdiv(cdiv(Kdim, plan.nsplit), 128) * 128);
     const int nsplit = (int)cdiv(Kdim, kps);
     const unsigned grid = (unsigned)(8 * cdiv(cdiv(M, plan.tile) * cdiv(N, plan.tile), 8) * nsplit);
@@ -587,9 +602,11 @@ static int launch_exact(const void* A, int64_t lda, const float* B, int64_t ldb,
         if (rc != MST_OK) return rc;
         k_gemm_stream<A16, AK, false, BKM, 2><<<grid, 512, STREAM_LDS_64, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
     } else if (plan.tile == 128) {
-        k_gemm_exact<A16, AK, BKM, 128><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+        if constexpr (A16) k_gemm_exact<A16, AK, BKM, 128, 0><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+        else if (plan.places == 96) k_gemm_exact<A16, AK, BKM, 128, 3><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+        else k_gemm_exact<A16, AK, BKM, 128, 2><<<grid, 256, 56u << 10, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);     // (the LDS of three)
     } else {
-        k_gemm_exact<A16, AK, BKM, 64><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+        k_gemm_exact<A16, AK, BKM, 64, 0><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
     }
     MST_LAUNCH_CHECK();
     if (nparts) {

@@ -201,3 +201,28 @@ def test_values_next_to_the_largest_finite_one(mode):
     ref = X.astype(np.float64) @ W.T.astype(np.float64)
     for rows in ([3, 64], [t for t in range(T) if t not in (3, 64)]):
         assert rel_err(Y[rows], ref[rows]) <= FP32
+
+
+@pytest.mark.parametrize("M,N,K", [(5000, 2040, 37), (5000, 2500, 37), (2561, 3970, 70), (12700, 1025, 33)])
+def test_two_and_three_workgroups_on_a_cu(M, N, K):
+    """128 x 128 tiles: 80, 100, 84 and 113 of them an XCD, in rounds of 96 or of 64, whichever is the shorter way; Y, dX and the dense
+    gradient as M x N products over K."""
+    g = torch.Generator(device=DEV).manual_seed(M)
+    A, B = torch.randn(M, K, generator=g, device=DEV), torch.randn(N, K, generator=g, device=DEV)
+    ref = A.double() @ B.double().t()
+    new = lambda: torch.full((M, N), float("nan"), device=DEV)  # noqa: E731
+    Y, dX, G = new(), new(), new()
+    try:
+        mst.mst_gemm_force_fp32_mfma(1128)
+        for O, I, W, out, call in ((N, K, B, Y, mst.mst_sparse_fc_fwd), (K, N, B.t().contiguous(), dX, mst.mst_sparse_fc_bwd_input)):
+            L = mst.Layer(O, I, O * I, DEV)
+            ws = torch.empty(mst.mst_workspace_bytes(O, I, O * I, 1), dtype=torch.uint8, device=DEV)
+            L.load_dense(W, torch.ones((O, I), dtype=torch.uint8, device=DEV), ws)
+            L.set_path(mst.MST_PATH_DENSE)
+            call(L, A, out, M, mst.MST_F32)
+        mst.mst_dense_grad(A.t().contiguous(), B.t().contiguous(), G, K, M, N, mst.MST_F32, None)
+        torch.cuda.synchronize()
+    finally:
+        mst.mst_gemm_force_fp32_mfma(0)
+    for got in (Y, dX, G):
+        assert float((got.double() - ref).abs().max()) <= FP32 * float(ref.abs().max())
