@@ -37,7 +37,7 @@ static int static_scratch(void** out) {
 
 // out[k] = sum over the nparts partial outputs (stride apart, added in ascending order) at
 // the k-th active position: the split sum of the dense gradient is only formed where the
-// weight gradient is wanted
+// weight gradient is wanted.  (For a whole dense gradient, and for kernels that write no active positions alone.)
 // (a thread takes four consecutive active positions: one 16-byte read of their indices, the four
 // gathers of a part in flight together, one 16-byte store; flat and out are 16-byte aligned)
 __global__ void k_gather_flat(const float* __restrict__ G, int64_t stride, int nparts, const int* __restrict__ flat,
@@ -162,8 +162,10 @@ int dense_products_bwd_input(const mst_layer* L, const void* dY, float* dX, int 
 int dense_products_bwd_weight(const mst_layer* L, const void* dY, const void* X, float* dW, int T,
                               mst_dtype act, const Workspace& ws, hipStream_t s, bool full) {
     int nparts = 1;
-    int rc = gemm_mfma(GEMM_TN, dY, act, X, act, nullptr, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s, full, &nparts);
+    ActiveOut active{L, dW};
+    int rc = gemm_mfma(GEMM_TN, dY, act, X, act, nullptr, ws.G, L->O, L->I, T, ws.gemm, (int64_t)ws.gemm_floats, s, full, &nparts, &active);
     if (rc != MST_OK) return rc;
+    if (active.done) return nparts > 1 ? sum_split_planes(ws.gemm, active.stride, nparts, dW, L->nnz, s) : MST_OK;
     if (L->nnz > 0) {
         k_gather_flat<<<(unsigned)cdiv(L->nnz, 1024), 256, 0, s>>>(nparts > 1 ? ws.gemm : ws.G, L->N, nparts, L->flat,
                                                                   L->nnz, dW);

@@ -151,6 +151,12 @@ struct mst_layer {
     int* dense_live = nullptr; // device: Wd holds the values handed over last (0: every built view holds them)
     int hint_T = 0;            // batch size and activation type of the last product call (0: none yet)
     int hint_act = 0;
+    // Which of every 32 columns are active and where they lie in vals (see active.h), for layers with rows of whole 16 bytes (null: none).  Made when
+    // the layer is loaded; an update makes them again if a product has read them, recorded products included, since their replays read them
+    // without asking.  Otherwise the next product does.
+    uint2* runs = nullptr;
+    bool runs_valid = false, runs_used = false;
+    bool runs_missed = false;  // an update without them has been recorded: its replays leave them behind, products do without
     std::atomic<uint64_t> choice{0};   // sparse-or-dense choices at the last batch size and type (see remembered(); 0: none)
     mst::View row;             // S = W   [O x I], used by fwd (and bwd_weight)
     mst::View col;             // S = W^T [I x O], used by bwd_input
@@ -317,12 +323,24 @@ int bwd_fused(const mst_layer* L, const void* dY, const void* X, float* dX, floa
 int bwd_fused_force_shape(int waves, int quads);
 // C[M x N] (fp32) = op(A) op(B) on the matrix cores; see gemm_mfma.hip.  full: fp32 operands in full whatever the shape
 enum GemmKind { GEMM_TN = 0, GEMM_NT = 1, GEMM_NN = 2 };
+// (active: a GEMM_TN product of which only L's active outputs are wanted; where its kernel can leave the others out, the active ones
+// go to dW, or to the partial outputs `stride` apart, and done says so)
+struct ActiveRuns;
+struct ActiveOut {
+    const mst_layer* L;
+    float* dW;
+    int64_t stride = 0;
+    bool done = false;
+};
+int active_runs(ActiveOut* active, hipStream_t s, ActiveRuns& runs, int64_t& stride);
+int make_runs(mst_layer* const* layers, int n, hipStream_t s);           // n up to BATCH_MAX
 int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_dtype b_dt, const uint16_t* planes, float* C,
               int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, bool full = false,
-              int* left_unsummed = nullptr);
+              int* left_unsummed = nullptr, ActiveOut* active = nullptr);
 bool gemm_wants_planes(mst_dtype a_dt, int M, int N, int Kdim, bool full);
 // G of bfloat16 activations, M and N multiples of 8; see gemm_wgrad.hip
-int gemm_wgrad16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int Kdim, int k_per_split, int64_t split_stride, hipStream_t s);
+int gemm_wgrad16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int Kdim, int k_per_split, int64_t split_stride,
+                 const ActiveRuns& runs, hipStream_t s);
 // Y and dX of bfloat16 activations from the split weights' planes; see gemm_planes.hip
 int gemm_planes(const uint16_t* A, const uint16_t* P, float* C, int M, int N, int Kdim, hipStream_t s);
 int make_planes(const mst_layer* L, hipStream_t s);

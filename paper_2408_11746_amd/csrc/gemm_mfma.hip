@@ -11,6 +11,7 @@
 // into separate partial outputs that a second kernel adds in a fixed order.
 #include <type_traits>
 #include "common.h"
+#include "active.h"
 #include "split_bf16.h"
 
 namespace mst {
@@ -167,6 +168,44 @@ __device__ inline void split_fetch(const float* __restrict__ src, int64_t ld, in
 __device__ inline float f4_at(const float4& v, int j) { return j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w; }
 __device__ inline uint32_t u4_at(const uint4& v, int j) { return j == 0 ? v.x : j == 1 ? v.y : j == 2 ? v.z : v.w; }
 
+// The active outputs of 2 x JT MFMA tiles at (m, n), which whole words cover.  A lane loads the words of a row into the wavefront's
+// own JT * 512 bytes of LDS ahead of the loop (behind the last product their way from memory took 3.5 us); from there each goes to the
+// lanes of its row and column block.  Whole planes and a gather -> this: 3072 x 768, 8192 tokens, density 0.1, three parts 116.5 + 9.5
+// us, so 114 + 4.9; 5120 x 1280 at 0.5 204 + 16.8, so 198.5 + 9.1.
+template <int JT>
+__device__ __forceinline__ void load_words(const ActiveRuns& runs, int m, int n, char* lds, int lane) {
+    const uint2* p = runs.words + (int64_t)(m + lane) * runs.per_row + (n >> 5);
+#pragma unroll
+    for (int j = 0; j < JT; j += 2) *reinterpret_cast<uint4*>(lds + lane * JT * 8 + 8 * j) = *reinterpret_cast<const uint4*>(p + j);
+}
+template <int JT>
+__device__ __forceinline__ void store_tiles(float* C, const ActiveRuns& runs, const char* lds, int lane, const floatx16 (&acc)[2][JT]) {
+    const __amdgpu_buffer_rsrc_t out = active_buffer(C, runs);
+    const char* const mine = lds + (lane >> 5) * 4 * JT * 8;
+    // (four rows of either half at a time; the next ones are on their way while these are stored)
+    uint4 w[2][4][JT / 2];
+    auto read = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < JT / 2; ++j) w[g & 1][r][j] = *reinterpret_cast<const uint4*>(mine + (8 * g + r) * JT * 8 + 16 * j);
+    };
+    const uint32_t below = (1u << (lane & 31)) - 1u;
+    read(0);
+#pragma unroll
+    for (int g = 0; g < 8; ++g) {
+        if (g < 7) read(g + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < JT; ++j) {
+                const uint4 q = w[g & 1][r][j >> 1];
+                store_active(out, j & 1 ? make_uint2(q.z, q.w) : make_uint2(q.x, q.y), lane, below, acc[g >> 2][j][4 * (g & 3) + r]);
+            }
+    }
+}
+
 template <bool KMAJOR>
 __device__ inline void split_stage(char* hi_lds, char* lo_lds, int p, const float4 (&r)[8]) {
     if (KMAJOR) {
@@ -198,11 +237,11 @@ __device__ inline void split_stage(char* hi_lds, char* lo_lds, int p, const floa
     }
 }
 
-template <bool A_KMAJOR, bool B_KMAJOR>
+template <bool A_KMAJOR, bool B_KMAJOR, bool ACTIVE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_split(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
-                  float* __restrict__ C, int M, int N, int Kdim, int k_per_split, int64_t split_stride) {
-    __shared__ __attribute__((aligned(16))) char lds[4 * BM * 128];      // A hi, A lo, B hi, B lo
+                  float* __restrict__ C, int M, int N, int Kdim, int k_per_split, int64_t split_stride, const ActiveRuns runs) {
+    __shared__ __attribute__((aligned(16))) char lds[4 * BM * 128 + (ACTIVE ? 4 * 1024 : 0)];      // A hi, A lo, B hi, B lo
     char* const Ah = lds;
     char* const Al = lds + BM * 128;
     char* const Bh = lds + 2 * BM * 128;
@@ -232,6 +271,7 @@ void k_gemm_split(const float* __restrict__ A, int64_t lda, const float* __restr
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
+    if constexpr (ACTIVE) load_words<2>(runs, m0 + wm, n0 + wn, lds + 4 * BM * 128 + 1024 * wave, lane);
     float4 ra[8], rb[8];
     split_fetch<A_KMAJOR>(A, lda, kbeg, m0, tid, ra);
     split_fetch<B_KMAJOR>(B, ldb, kbeg, n0, tid, rb);
@@ -266,6 +306,10 @@ void k_gemm_split(const float* __restrict__ A, int64_t lda, const float* __restr
             acc[1][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1h, b0h, acc[1][0], 0, 0, 0);
             acc[1][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1h, b1h, acc[1][1], 0, 0, 0);
         }
+    }
+    if constexpr (ACTIVE) {
+        store_tiles(Cz, runs, lds + 4 * BM * 128 + 1024 * wave, lane, acc);
+        return;
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -335,12 +379,13 @@ __device__ inline uint32_t split256_unit(int p, int h, int piece) {
     return bf_unit32<4>(4 * (p & 63) + 2 * h + piece - 2, p >> 6);
 }
 
-template <bool A_KMAJOR, bool B_KMAJOR>
+// ACTIVE (k_gemm_split too): only the active outputs, side by side (C and split_stride are of them)
+template <bool A_KMAJOR, bool B_KMAJOR, bool ACTIVE>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_split256(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
-                     float* __restrict__ C, int M, int N, int Kdim, int k_per_split, int64_t split_stride, int sched) {
+                     float* __restrict__ C, int M, int N, int Kdim, int k_per_split, int64_t split_stride, int sched, const ActiveRuns runs) {
     constexpr int PLANE = BM2 * 64;                                       // one half (hi or lo) of one operand tile
-    __shared__ __attribute__((aligned(16))) char lds[2 * 4 * PLANE];     // [stage][A hi, A lo, B hi, B lo]
+    __shared__ __attribute__((aligned(16))) char lds[2 * 4 * PLANE + (ACTIVE ? 8 * 2048 : 0)];     // [stage][A hi, A lo, B hi, B lo]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = (wave >> 1) * 64, wn = (wave & 1) * 128;
     const int gn = N / BN2, ntiles = (M / BM2) * gn;
@@ -543,6 +588,7 @@ void k_gemm_split256(const float* __restrict__ A, int64_t lda, const float* __re
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
+        if constexpr (ACTIVE) load_words<4>(runs, m0 + wm, n0 + wn, lds + 8 * PLANE + 2048 * wave, lane);
         fetch(kbeg, r);
         stage(0, r);
         if (kbeg + SPK2 < kend) fetch(kbeg + SPK2, r);
@@ -559,16 +605,20 @@ void k_gemm_split256(const float* __restrict__ A, int64_t lda, const float* __re
         }
         step(buf, false_type{}, false_type{}, 0);     // last step
 
+        if constexpr (ACTIVE) {
+            store_tiles(Cz, runs, lds + 8 * PLANE + 2048 * wave, lane, acc);
+        } else {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+                for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int m = m0 + wm + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
-                    const int n = n0 + wn + j * 32 + lm;
-                    Cz[(int64_t)m * N + n] = acc[i][j][v];
-                }
+                    for (int v = 0; v < 16; ++v) {
+                        const int m = m0 + wm + i * 32 + 8 * (v >> 2) + 4 * lk + (v & 3);
+                        const int n = n0 + wn + j * 32 + lm;
+                        Cz[(int64_t)m * N + n] = acc[i][j][v];
+                    }
+        }
         if (sg + 1 < nseg) __syncthreads();           // the next segment reuses the LDS stages
     }
 }
@@ -882,12 +932,20 @@ __global__ void k_splitk_reduce(const float* __restrict__ part, int64_t stride, 
     for (int z = 0; z < nsplit; ++z) s += part[(int64_t)z * stride + i];
     C[i] = s;
 }
-// the same with four consecutive outputs per thread (n and stride multiples of 4, 16-byte aligned
+// the same with four consecutive outputs per thread (stride a multiple of 4, 16-byte aligned
 // bases): 16-byte loads, a quarter of the threads
 __global__ void k_splitk_reduce4(const float* __restrict__ part, int64_t stride, int nsplit,
-                                 float* __restrict__ C, int64_t n4) {
+                                 float* __restrict__ C, int64_t n) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n4) return;
+    if (4 * i >= n) return;
+    if (4 * i + 4 > n) {
+        for (int64_t e = 4 * i; e < n; ++e) {
+            float s = 0.f;
+            for (int z = 0; z < nsplit; ++z) s += part[(int64_t)z * stride + e];
+            C[e] = s;
+        }
+        return;
+    }
     const float4* p = reinterpret_cast<const float4*>(part) + i;
     const int64_t s4 = stride >> 2;
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -906,8 +964,8 @@ __global__ void k_splitk_reduce4(const float* __restrict__ part, int64_t stride,
     reinterpret_cast<float4*>(C)[i] = s;
 }
 int sum_split_planes(const float* part, int64_t stride, int nsplit, float* C, int64_t n, hipStream_t s) {
-    if (n % 4 == 0 && stride % 4 == 0 && aligned16(part) && aligned16(C))
-        k_splitk_reduce4<<<(unsigned)cdiv(n / 4, 256), 256, 0, s>>>(part, stride, nsplit, C, n / 4);
+    if (stride % 4 == 0 && aligned16(part) && aligned16(C))
+        k_splitk_reduce4<<<(unsigned)cdiv(n, 1024), 256, 0, s>>>(part, stride, nsplit, C, n);
     else
         k_splitk_reduce<<<(unsigned)cdiv(n, 256), 256, 0, s>>>(part, stride, nsplit, C, n);
     MST_LAUNCH_CHECK();
@@ -1047,8 +1105,15 @@ static SplitPlan plan_fp32(GemmKind kind, int M, int N, int Kdim, int64_t max_sp
 
 template <bool AK, bool BKM>
 static int launch_split(const SplitPlan& plan, const void* A, int64_t lda, const void* B, int64_t ldb, float* C, int M, int N,
-                        int Kdim, float* split_ws, int64_t split_ws_floats, int* left_unsummed, hipStream_t s) {
+                        int Kdim, float* split_ws, int64_t split_ws_floats, int* left_unsummed, hipStream_t s, ActiveOut* active = nullptr) {
     const int64_t mn = (int64_t)M * N;
+    int64_t stride = mn;
+    ActiveRuns runs{};
+    if constexpr (AK) {
+        const int rc = active_runs(active, s, runs, stride);
+        if (rc != MST_OK) return rc;
+    }
+    const bool only = runs.words != nullptr;
     const int tile = plan.tile, nsplit0 = plan.nsplit;
     g_last_tile = tile;
     const int kstep = tile == 128 ? SPK : SPK2;
@@ -1056,15 +1121,15 @@ static int launch_split(const SplitPlan& plan, const void* A, int64_t lda, const
     const int nsplit = (int)cdiv(Kdim, kps);
     const int tm = tile == 128 ? 128 : 256;
     const unsigned grid = (unsigned)(8 * cdiv((int64_t)(M / tm) * (N / tile), 8) * nsplit);
-    float* dst = nsplit > 1 ? split_ws : C;
+    float* dst = nsplit > 1 ? split_ws : only ? active->dW : C;
     // About 100 tiles of 256 x 256 with two k ranges each leave a fifth of the CUs idle: five
     // workgroups per two tiles instead (k_gemm_split256, sched = 1), three partial planes per tile.
     const int64_t tiles256 = (int64_t)(M / BM2) * (N / BN2);
     const int S = Kdim / SPK2, x_steps = (int)cdiv(2 * S + 13, 5);
     if (tile == 256 && nsplit == 2 && g_sched52 && split_ws && split_ws_floats / mn >= 3 && tiles256 % 2 == 0 &&
         tiles256 * 5 / 2 <= 256 && tiles256 * 2 <= 218 && S - 2 * x_steps >= 8) {
-        k_gemm_split256<AK, BKM><<<256u, 512, 0, s>>>((const float*)A, lda, (const float*)B, ldb, split_ws,
-                                                                              M, N, Kdim, x_steps * SPK2, mn, 1);
+        const auto kernel = only ? k_gemm_split256<AK, BKM, AK> : k_gemm_split256<AK, BKM, false>;
+        kernel<<<256u, 512, 0, s>>>((const float*)A, lda, (const float*)B, ldb, split_ws, M, N, Kdim, x_steps * SPK2, stride, 1, runs);
         MST_LAUNCH_CHECK();
         if (left_unsummed) {
             *left_unsummed = 3;
@@ -1080,10 +1145,13 @@ static int launch_split(const SplitPlan& plan, const void* A, int64_t lda, const
     } else if (tile == 192) {
         if constexpr (!AK)
             k_gemm_split_n160<192, BKM><<<grid, 512, 0, s>>>((const float*)A, lda, (const float*)B, ldb, dst, M, N, Kdim, kps, mn);
-    } else if (tile == 256)
-        k_gemm_split256<AK, BKM><<<grid, 512, 0, s>>>((const float*)A, lda, (const float*)B, ldb, dst, M, N, Kdim, kps, mn, 0);
-    else
-        k_gemm_split<AK, BKM><<<grid, 256, 0, s>>>((const float*)A, lda, (const float*)B, ldb, dst, M, N, Kdim, kps, mn);
+    } else if (tile == 256) {
+        const auto kernel = only ? k_gemm_split256<AK, BKM, AK> : k_gemm_split256<AK, BKM, false>;
+        kernel<<<grid, 512, 0, s>>>((const float*)A, lda, (const float*)B, ldb, dst, M, N, Kdim, kps, stride, 0, runs);
+    } else {
+        const auto kernel = only ? k_gemm_split<AK, BKM, AK> : k_gemm_split<AK, BKM, false>;
+        kernel<<<grid, 256, 0, s>>>((const float*)A, lda, (const float*)B, ldb, dst, M, N, Kdim, kps, stride, runs);
+    }
     MST_LAUNCH_CHECK();
     if (left_unsummed) {
         *left_unsummed = nsplit;
@@ -1110,7 +1178,7 @@ static bool use_a16(int M, int N, int Kdim) {
            (g_split_tile == 256 || (double)M * N * Kdim >= 2.0e10 || a16_us(M, N, Kdim) <= gemm_exact_us(MST_BF16, M, N, Kdim, 1, true));
 }
 static int launch_tn_bf16(const void* Av, const void* Bv, float* C, int M, int N, int Kdim, float* split_ws,
-                          int64_t split_ws_floats, int* left_unsummed, hipStream_t s) {
+                          int64_t split_ws_floats, int* left_unsummed, hipStream_t s, ActiveOut* active) {
     const int64_t mn = (int64_t)M * N;
     const uint16_t *A = (const uint16_t*)Av, *B = (const uint16_t*)Bv;
     const SplitPlan plan = plan_tn_bf16(M, N, Kdim, split_ws ? split_ws_floats / mn : 1, left_unsummed == nullptr);
@@ -1122,7 +1190,11 @@ static int launch_tn_bf16(const void* Av, const void* Bv, float* C, int M, int N
     } else if (plan.tile == 128) {
         k_gemm_tn_bf16<<<dim3(nsplit, (unsigned)cdiv(N, BN), (unsigned)cdiv(M, BM)), 256, 0, s>>>(A, M, B, N, dst, M, N, Kdim, kps, mn);
     } else if (M % 8 == 0 && N % 8 == 0) {
-        const int rc = gemm_wgrad16(A, B, dst, M, N, Kdim, kps, mn, s);
+        int64_t stride = mn;
+        ActiveRuns runs{};
+        int rc = active_runs(active, s, runs, stride);
+        if (rc != MST_OK) return rc;
+        rc = gemm_wgrad16(A, B, nsplit == 1 && runs.words ? active->dW : dst, M, N, Kdim, kps, stride, runs, s);
         if (rc != MST_OK) return rc;
     } else {
         const unsigned grid = (unsigned)(8 * cdiv(cdiv(M, BM2) * cdiv(N, BN2), 8) * nsplit);
@@ -1144,12 +1216,12 @@ bool gemm_wants_planes(mst_dtype a_dt, int M, int N, int Kdim, bool full) { retu
 // NN: C[M x N] = A B,   A [M x K], B [K x N] (fp32)   (dX = dY Wd)
 // planes: of B for this product, where gemm_wants_planes says so
 int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_dtype b_dt, const uint16_t* planes, float* C,
-              int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, bool full, int* left_unsummed) {
+              int M, int N, int Kdim, float* split_ws, int64_t split_ws_floats, hipStream_t s, bool full, int* left_unsummed, ActiveOut* active) {
     const bool ab = a_dt == MST_BF16, bb = b_dt == MST_BF16;
     g_last_tile = 0;
     if (kind == GEMM_TN ? ab != bb : bb) return MST_ERR_ARG;
     if (ab) {
-        if (kind == GEMM_TN) return launch_tn_bf16(A, B, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+        if (kind == GEMM_TN) return launch_tn_bf16(A, B, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s, active);
         if (gemm_wants_planes(a_dt, M, N, Kdim, full)) {
             const int rc = gemm_planes((const uint16_t*)A, planes, C, M, N, Kdim, s);
             if (rc != MST_OK) return rc;
@@ -1162,7 +1234,7 @@ int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_d
     const int64_t max_split = split_ws ? split_ws_floats / ((int64_t)M * N) : 1;
     const SplitPlan plan = full ? SplitPlan{0, 1, 0.0} : plan_fp32(kind, M, N, Kdim, max_split, left_unsummed == nullptr);
     if (plan.tile == 0) return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
-    if (kind == GEMM_TN) return launch_split<true, true>(plan, A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
+    if (kind == GEMM_TN) return launch_split<true, true>(plan, A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s, active);
     if (kind == GEMM_NT) return launch_split<false, false>(plan, A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
     return launch_split<false, true>(plan, A, Kdim, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
 }

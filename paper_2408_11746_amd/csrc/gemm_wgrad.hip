@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "active.h"
 #include "split_bf16.h"
 
 namespace mst {
@@ -24,15 +25,19 @@ namespace mst {
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef short shortx8 __attribute__((ext_vector_type(8)));
 constexpr int GK = 32, G_OP = GK * 512, G_STAGE = 2 * G_OP;      // a row of LDS is one k and 256 columns
-constexpr unsigned G_LDS = 4 * G_STAGE;
+constexpr unsigned G_LDS = 4 * G_STAGE, G_WORDS = 4096;         // (words of a wavefront's 128 rows and columns)
 
 // The 32-byte units (16 columns) of row k are kept at unit ^ swizzle(k): the eight rows that half a wavefront reads
 // (four and, eight further, four) lie in different banks.
 __device__ __forceinline__ int wgrad_swizzle(int k) { return (k & 3) | ((k >> 1) & 4); }
 
+// ACTIVE: only the active outputs, side by side (C and split_stride are of them).  Whole planes and a gather -> this, at a density of
+// 0.05: 1024 <-> 4096, 16384 tokens 108 + 10.2 us, so 104 + 4.9; 4096 x 1024, 4099 tokens 39 + 8.5, so 37.7 + 4.9, and the products
+// behind it, which find their operands in the caches: both products of the backward 10 us.
+template <bool ACTIVE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void k_gemm_wgrad16(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, float* __restrict__ C, int M, int N, int Kdim,
-                    int k_per_split, int64_t split_stride) {
+                    int k_per_split, int64_t split_stride, const ActiveRuns runs) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = (wave >> 1) * 128, wn = (wave & 1) * 128;
@@ -136,6 +141,19 @@ void k_gemm_wgrad16(const uint16_t* __restrict__ A, const uint16_t* __restrict__
     };
 
     offsets(GK);
+    if constexpr (ACTIVE) {
+        // The words of this wavefront's outputs (past the end: no active ones), now: loaded behind the last step, their way from memory
+        // was 3.5 us of the kernel's time.
+        uint2 w[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int at = 64 * e + lane, m = m0 + wm + (at >> 2), word = ((n0 + wn) >> 5) + (at & 3);
+            w[e] = make_uint2(0xFFFFFFFFu, 0u);
+            if (m < M && word < runs.per_row) w[e] = runs.words[(int64_t)m * runs.per_row + word];
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) *reinterpret_cast<uint2*>(lds + G_LDS + G_WORDS * wave + 8 * (64 * e + lane)) = w[e];
+    }
     load(0);
     load(1);
     arrive(0);
@@ -172,6 +190,39 @@ void k_gemm_wgrad16(const uint16_t* __restrict__ A, const uint16_t* __restrict__
 #pragma unroll
             for (int j = 0; j < 8; ++j) *reinterpret_cast<floatx4*>(mine + (16 * i + lm) * 512 + (((4 * j + g) ^ lm) << 4)) = acc[4 * h + i][j];
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        if constexpr (ACTIVE) {
+            // a lane has a column, so that a store writes what is active among 64 columns in one run
+            const __amdgpu_buffer_rsrc_t out = active_buffer(Cz, runs);
+            const uint32_t below = (1u << (lane & 31)) - 1u;
+            const char* const words = lds + G_LDS + G_WORDS * wave + (64 * h) * 32 + 8 * (lane >> 5);
+            // (four rows at a time, the next ones on their way while these are stored: there is one wavefront on a SIMD)
+            uint2 w[2][8];
+            float o[2][8];
+            auto get = [&](int set, int r0) __attribute__((always_inline)) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int r = r0 + (e >> 1), c = 64 * (e & 1) + lane;
+                    w[set][e] = *reinterpret_cast<const uint2*>(words + 32 * r + 16 * (e & 1));
+                    o[set][e] = *reinterpret_cast<const float*>(mine + r * 512 + (((c >> 2) ^ (r & 15)) << 4) + 4 * (c & 3));
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto put = [&](int set) __attribute__((always_inline)) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) store_active(out, w[set][e], lane, below, o[set][e]);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            get(0, 0);
+#pragma unroll 2
+            for (int r = 0; r < 64; r += 8) {
+                get(1, r + 4);
+                put(0);
+                get(0, min(r + 8, 60));
+                put(1);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            continue;
+        }
 #pragma unroll 8
         for (int r = lane >> 5; r < 64; r += 2) {
             const int m = m0 + wm + 64 * h + r;
@@ -183,13 +234,17 @@ void k_gemm_wgrad16(const uint16_t* __restrict__ A, const uint16_t* __restrict__
 }
 
 // ranges of k_per_split (a multiple of 32) rows, each into its own M x N floats, split_stride (a multiple of 4) apart
-int gemm_wgrad16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int Kdim, int k_per_split, int64_t split_stride, hipStream_t s) {
+int gemm_wgrad16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int Kdim, int k_per_split, int64_t split_stride,
+                 const ActiveRuns& runs, hipStream_t s) {
     if (M % 8 || N % 8 || k_per_split % GK) return MST_ERR_ARG;
-    static uint64_t done = 0;
-    const int rc = allow_lds(reinterpret_cast<const void*>(&k_gemm_wgrad16), G_LDS, done);
+    static uint64_t done[2] = {0, 0};
+    const bool active = runs.words != nullptr;
+    const auto kernel = active ? k_gemm_wgrad16<true> : k_gemm_wgrad16<false>;
+    const unsigned bytes = G_LDS + (active ? 4 * G_WORDS : 0u);
+    const int rc = allow_lds(reinterpret_cast<const void*>(kernel), (int)bytes, done[active]);
     if (rc != MST_OK) return rc;
     const unsigned grid = (unsigned)(8 * cdiv(cdiv(M, 256) * cdiv(N, 256), 8) * cdiv(Kdim, k_per_split));
-    k_gemm_wgrad16<<<grid, 256, G_LDS, s>>>(A, B, C, M, N, Kdim, k_per_split, split_stride);
+    kernel<<<grid, 256, bytes, s>>>(A, B, C, M, N, Kdim, k_per_split, split_stride, runs);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }

@@ -13,6 +13,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "active.h"
 
 namespace mst {
 
@@ -144,12 +145,15 @@ constexpr int CSEG = 2048;         // positions per wavefront of build_canonical
 
 struct LayerCarve {
     size_t mask, vals, flat, rowptr, Wd;
-    size_t rptr, rent, rperm, rmap, rpos, cptr, cent, cperm, cmap, cpos, cost, heavy, Hd, sy, sx, py, px;
+    size_t rptr, rent, rperm, rmap, rpos, cptr, cent, cperm, cmap, cpos, cost, heavy, Hd, runs, sy, sx, py, px;
     size_t total;
 };
 
 // the tile of gemm_planes.hip divides the outputs of one product, its k step the contraction range
 static bool has_planes(int O, int I) { return O % 32 == 0 && I % 32 == 0 && (O % 256 == 0 || I % 256 == 0); }
+
+// rows of whole 16 bytes of the mask, and outputs whose bytes an unsigned holds
+static bool has_runs(int O, int I) { return I % 16 == 0 && (int64_t)O * I < (int64_t)1 << 30; }
 
 // whole steps of gemm_pairs.hip in both directions
 static bool has_pairs(int O, int I) { return O % 64 == 0 && I % 64 == 0; }
@@ -178,6 +182,7 @@ static LayerCarve carve_layer(int O, int I, int64_t cap) {
     c.cost = take(16 + 4);
     c.heavy = take((size_t)(HEAVY_MAX + 2) * 4);
     c.Hd = take((size_t)HEAVY_MAX * I * 4);
+    c.runs = take(has_runs(O, I) ? (size_t)O * (size_t)cdiv(I, 32) * sizeof(uint2) : 0);
     c.sy = take(has_pairs(O, I) ? pairs_view(nullptr, O, I).bytes : 0);
     c.sx = take(has_pairs(O, I) ? pairs_view(nullptr, I, O).bytes : 0);
     c.py = take(has_planes(O, I) ? (size_t)N * 4 : 0);
@@ -1078,6 +1083,82 @@ int build_canonical(const BuildItem* items, int n, hipStream_t s) {
     return MST_OK;
 }
 
+// Which of each 32 columns of a row are inactive, and the canonical index of the first active one: a wavefront per row, a lane per 32 positions.
+struct RunArgs {
+    const uint8_t* mask;
+    const int* rowptr;
+    uint2* runs;
+    int O, I;
+};
+template <int CAP>
+__global__ __launch_bounds__(256) void k_active_runs(const Batch<RunArgs, CAP> batch) {
+    if (batch.surplus()) return;
+    const RunArgs a = batch.entry();
+    const int row = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (row >= a.O) return;
+    const uint8_t* const m = a.mask + (int64_t)row * a.I;
+    const int words = (a.I + 31) / 32;
+    int first = a.rowptr[row];
+    for (int w0 = 0; w0 < words; w0 += 64) {
+        const int w = w0 + lane;
+        uint32_t bits = 0;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            if (32 * w + 16 * h >= a.I) continue;
+            const uint4 u = *reinterpret_cast<const uint4*>(m + 32 * w + 16 * h);
+            const uint32_t d[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+            for (int e = 0; e < 16; ++e) bits |= ((d[e >> 2] >> (8 * (e & 3)) & 0xFFu) != 0u ? 1u : 0u) << (16 * h + e);
+        }
+        const int n = __popc(bits);
+        int upto = n;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int below = __shfl_up(upto, d, 64);
+            if (lane >= d) upto += below;
+        }
+        if (w < words) a.runs[(int64_t)row * words + w] = make_uint2(~bits, (uint32_t)(first + upto - n));
+        first += __shfl(upto, 63, 64);
+    }
+}
+int make_runs(mst_layer* const* layers, int n, hipStream_t s) {
+    Batch<RunArgs> batch;
+    for (int x = 0; x < n; ++x) {
+        mst_layer* L = layers[x];
+        if (!L->runs) continue;
+        batch.add(RunArgs{L->mask, L->rowptr, L->runs, L->O, L->I}, cdiv(L->O, 4));
+        L->runs_valid = true;
+    }
+    if (batch.n == 0) return MST_OK;
+    launch_batch(batch, [&](const auto& b) { k_active_runs<<<b.grid(), 256, 0, s>>>(b); });
+    MST_LAUNCH_CHECK();
+    return MST_OK;
+}
+
+// For a product that reads them.  Made by the product itself they are not there for other streams before it has waited for them,
+// once behind an update that found them unread; a recording cannot wait and leaves them.
+int active_runs(ActiveOut* active, hipStream_t s, ActiveRuns& runs, int64_t& stride) {
+    if (!active) return MST_OK;
+    mst_layer* L = const_cast<mst_layer*>(active->L);        // a cache of the mask, not layer state
+    if (!L->runs || L->runs_missed || L->nnz == 0) return MST_OK;
+    // Small layers with many active weights stay on whole outputs: their planes stay in the caches, and the gather of them takes what the stores
+    // of single values take more (bfloat16, 1288 x 1040, 3000 tokens: 30.1 us at a density of 0.5 and 31.0 at 0.9, so 31.4 and 32.5; at
+    // 0.2 30.3, so 29.6.  5120 x 1280, 512 tokens: 28.8 and 31.6, so 27.6 and 30.2).
+    if (4 * L->nnz > L->N && L->N < (int64_t)1 << 21) return MST_OK;
+    if (!L->runs_valid) {
+        bool recording;
+        int rc = stream_recording(s, &recording);
+        if (rc != MST_OK || recording) return rc;
+        rc = make_runs(&L, 1, s);
+        if (rc != MST_OK) return rc;
+        MST_HIP(hipStreamSynchronize(s));
+    }
+    L->runs_used = true;
+    runs = ActiveRuns{L->runs, (int)cdiv(L->I, 32), (uint32_t)(4 * L->nnz)};
+    active->stride = stride = (int64_t)align_up((size_t)L->nnz, 4);
+    active->done = true;
+    return MST_OK;
+}
+
 // W . M to W and / or the mask to M (dense_live: null where W is not the layer's own dense copy)
 static int export_dense(const mst_layer* L, float* W, uint8_t* M, int* dense_live, hipStream_t s) {
     // Rows of a run: one, several where a layer has far more rows than the chip holds blocks, then whole fours so that runs begin on 16 bytes
@@ -1255,6 +1336,7 @@ int mst_layer_create(mst_layer_t** out, int O, int I, int64_t nnz_capacity, void
     L->dense_live = (int*)(b + c.cost + 16);
     L->heavy = (int*)(b + c.heavy);
     L->Hd = (float*)(b + c.Hd);
+    if (has_runs(O, I)) L->runs = (uint2*)(b + c.runs);
     if (has_pairs(O, I)) {
         L->pairs_y = pairs_view(b + c.sy, O, I);
         L->pairs_x = pairs_view(b + c.sx, I, O);
@@ -1302,6 +1384,7 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
     L->pairs_unknown();
     L->choice.store(0, std::memory_order_relaxed);
     L->built = false;                                   // a failed rebuild leaves no usable layer
+    L->runs_valid = false;
     // Heavy rows (heavy.hip).  The dense pass costs a launch after every sparse forward, a read of
     // X and T scattered stores per heavy row: a layer of less than 2^20 positions does not earn
     // that back (measured: 768 x 768 at T = 16384 loses 10 us, 768 x 2304 gains 19 us), and a layer
@@ -1319,6 +1402,8 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
         MST_HIP(hipStreamSynchronize(s));
         L->heavy_on = found > 0;
     }
+    const int rcr = make_runs(&L, 1, s);
+    if (rcr != MST_OK) return rcr;
     L->built = true;
     return MST_OK;
 }

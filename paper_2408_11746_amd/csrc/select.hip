@@ -722,7 +722,10 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
     Batch<RandArgs> compact;
     Batch<EndArgs> end;
     BuildItem views[BATCH_MAX], canonical[BATCH_MAX];
-    int n_views = 0, n_canonical = 0, rc;
+    mst_layer* runs[BATCH_MAX];
+    int n_views = 0, n_canonical = 0, n_runs = 0, rc;
+    bool recording;
+    if ((rc = stream_recording(s, &recording)) != MST_OK) return rc;
     int64_t keys = 0;                                 // of all selections
     for (int x = 0; x < n; ++x)
         keys += (items[x].st.n_prune > 0 ? items[x].L->nnz : 0) + (items[x].st.n_grad > 0 ? items[x].L->N : 0);
@@ -802,9 +805,11 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
         items[x].L->nnz = items[x].st.nnz_after;
         items[x].L->choice.store(0, std::memory_order_relaxed);
         if (items[x].L->pairs_calls >= PAIRS_CALLS) items[x].L->pairs_unknown();
+        items[x].L->runs_valid = false;
+        if (items[x].L->runs_used) runs[n_runs++] = items[x].L;
+        else items[x].L->runs_missed |= recording;
     }
     if (n_views > 0 && (rc = build_views(views, n_views, s)) != MST_OK) return rc;
-    if (n_canonical == 0) return MST_OK;
     for (int x = 0; x < n_canonical; ++x) {
         mst_layer* L = canonical[x].L;
         L->Wd_valid = L->Wd_zeros = true;
@@ -816,7 +821,8 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
         if (L->pairs_valid && (rc = make_pairs(L, s)) != MST_OK) return rc;
         L->pairs_matched = L->pairs_valid;
     }
-    return build_canonical(canonical, n_canonical, s);
+    if (n_canonical > 0 && (rc = build_canonical(canonical, n_canonical, s)) != MST_OK) return rc;
+    return n_runs > 0 ? make_runs(runs, n_runs, s) : MST_OK;
 }
 
 }  // namespace mst

@@ -1,0 +1,123 @@
+"""The weight gradient on the dense matrix cores that writes the active positions alone (dW of App. Eq. (1)'s gradients): every tile, one
+and several partial outputs, rows that end inside a word of 32 columns, tiles past the last row and column, empty and full rows, few and
+all positions.  Small whole numbers, whose products and sums are exact in every kernel: the result has to be the exact one."""
+import numpy as np
+import pytest
+
+import paper_2408_11746_amd as mst
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+from gpu_util import Rig, DEV  # noqa: E402
+
+
+@pytest.fixture(autouse=True)
+def automatic():
+    yield
+    mst.mst_gemm_force_fp32_mfma(0)
+
+
+def _numbers(T, n, act, seed):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(seed)
+    return torch.randint(-3, 4, (T, n), generator=gen, device=DEV).to(torch.bfloat16 if act == mst.MST_BF16 else torch.float32).contiguous()
+
+
+def _mask(O, I, density, seed):
+    M = (np.random.default_rng(seed).random((O, I)) < density).astype(np.uint8)
+    M[O // 2] = 0
+    M[O - 1] = 0
+    M[0] = 1
+    M[1, :33] = 1
+    M[2, I - 1] = 1
+    return M
+
+
+def _check(rig, dY, X, act, dW=None):
+    if dW is None:
+        dW = torch.full((rig.layer.nnz + 64,), 7.0, device=DEV)
+        mst.mst_sparse_fc_bwd_weight(rig.layer, dY, X, dW, X.shape[0], rig.ws, act)
+    G = dY.double().cpu().numpy().T @ X.double().cpu().numpy()
+    dW = dW.cpu().numpy()
+    n = rig.layer.nnz
+    assert np.array_equal(dW[:n], G.ravel()[rig.indices()])
+    assert np.all(dW[n:] == 7.0)
+
+
+def _rig(O, I, T, density, seed=5):
+    M = _mask(O, I, density, seed)
+    rig = Rig(M * np.float32(0.5), M, T, cap=O * I)
+    rig.layer.set_path(mst.MST_PATH_DENSE)
+    return rig
+
+
+@pytest.mark.parametrize("density", [0.01, 0.2, 1.0])
+@pytest.mark.parametrize("O,I,T,act,tile", [
+    (256, 256, 64, "f32", 256), (512, 256, 2048, "f32", 256), (3072, 768, 1024, "f32", 256), (2560, 2560, 1024, "f32", 256),
+    (128, 128, 64, "f32", 128), (256, 384, 96, "f32", 128), (384, 1152, 2048, "f32", 128),
+    (8, 16, 1, "bf16", 256), (264, 272, 33, "bf16", 256), (520, 48, 2049, "bf16", 256), (1288, 1040, 3000, "bf16", 256), (2048, 1040, 97, "bf16", 256),
+    (264, 264, 96, "bf16", 256), (300, 270, 64, "f32", 0), (96, 80, 64, "bf16", 64)])
+def test_exact_gradient(O, I, T, act, tile, density):
+    print("case", O, I, T, act, tile, density, flush=True)
+    kind = mst.MST_BF16 if act == "bf16" else mst.MST_F32
+    mst.mst_gemm_force_fp32_mfma(tile)
+    rig = _rig(O, I, T, density)
+    X, dY = _numbers(T, I, kind, 1), _numbers(T, O, kind, 2)
+    _check(rig, dY, X, kind)
+
+
+@pytest.mark.parametrize("read_before", [True, False])
+def test_updates_take_the_words_along(read_before):
+    """Eager and recorded products before and behind eager and recorded updates of the active set."""
+    O, I, T, act = 1024, 256, 512, mst.MST_F32
+    mst.mst_gemm_force_fp32_mfma(256)
+    rig = _rig(O, I, T, 0.1)
+    L, side = rig.layer, torch.cuda.Stream()
+    X, dY = _numbers(T, I, act, 1), _numbers(T, O, act, 2)
+    score = torch.randn(O, I, device=DEV)
+    density = L.nnz / (O * I)
+    if read_before:
+        _check(rig, dY, X, act)
+    mst.mst_mask_update_from_scores(L, score, density, 0.3, 0.25, 11, rig.ws)
+    if read_before:
+        _check(rig, dY, X, act)
+    update, product = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+    dW = torch.full((L.nnz + 64,), 7.0, device=DEV)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(update, stream=side):
+        mst.mst_mask_update_from_scores(L, score, density, 0.3, 0.25, 12, rig.ws, side)
+    with torch.cuda.graph(product, stream=side):
+        mst.mst_sparse_fc_bwd_weight(L, dY, X, dW, T, rig.ws, act, side)
+    for _ in range(3):
+        update.replay()
+        torch.cuda.synchronize()
+        _check(rig, dY, X, act)
+        dW.fill_(7.0)
+        product.replay()
+        torch.cuda.synchronize()
+        _check(rig, dY, X, act, dW)
+    mst.mst_mask_update_from_scores(L, score, density, 0.3, 0.25, 13, rig.ws)
+    _check(rig, dY, X, act)
+    product.replay()
+    torch.cuda.synchronize()
+    _check(rig, dY, X, act, dW)
+
+
+def test_two_streams_behind_an_update_that_left_the_words():
+    O, I, T, act = 1024, 256, 512, mst.MST_F32
+    mst.mst_gemm_force_fp32_mfma(256)
+    rig = _rig(O, I, T, 0.1)
+    L, a, b = rig.layer, torch.cuda.Stream(), torch.cuda.Stream()
+    X, dY = _numbers(T, I, act, 1), _numbers(T, O, act, 2)
+    mst.mst_mask_update_from_scores(L, torch.randn(O, I, device=DEV), L.nnz / (O * I), 0.3, 0.25, 11, rig.ws)
+    out = [torch.full((L.nnz + 64,), 7.0, device=DEV) for _ in range(2)]
+    ws = torch.empty_like(rig.ws)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(a):
+        torch.cuda._sleep(10_000_000)
+    mst.mst_sparse_fc_bwd_weight(L, dY, X, out[0], T, rig.ws, act, a)
+    mst.mst_sparse_fc_bwd_weight(L, dY, X, out[1], T, ws, act, b)
+    torch.cuda.synchronize()
+    for dW in out:
+        _check(rig, dY, X, act, dW)
