@@ -349,7 +349,8 @@ int weights_made(mst_layer* L, bool planes, bool pairs, hipStream_t s);
 PairsView pairs_view(void* mem, int R, int K);
 bool pairs_kept(const mst_layer* L);
 bool pairs_wanted(const mst_layer* L, bool both);
-int make_pairs(mst_layer* L, hipStream_t s);
+struct ActiveRuns;
+int make_pairs(mst_layer* L, hipStream_t s, const ActiveRuns* words = nullptr);
 int measure_pairs(mst_layer* L, hipStream_t s);
 // A measurement waits for its stream: an update behind fewer products than these leaves the last one standing.  (Updates are hundreds of
 // steps apart in earnest; a loop that updates after every step would wait in every step.)

@@ -38,6 +38,7 @@
 #include <utility>
 
 #include "common.h"
+#include "active.h"
 #include "split_bf16.h"
 
 namespace mst {
@@ -220,7 +221,12 @@ __global__ __launch_bounds__(256) void k_match_pairs(const uint8_t* __restrict__
 // packs a tile; lane = row and 16 k of every 32.  Bound by the 8.5 bytes per position that it reads and writes.
 // first: the packing behind a choice of slots; block 0 counts the steps that go a second time (a launch of its own: four layers of a
 // GPT-2-small block 19 us longer in the first pass on new masks).
-__global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W, int I, const PairsView y, const PairsView x, bool first) {
+// HANDED_OVER: the dense weights are out of date and are written as well, from the active values and the words that lead to them (a
+// launch that writes them and this kernel behind it: 3072 x 768 at a density of 0.1 5.9 + 9.1 us, so 10.6; 1024 x 4096 at 0.05 6.3 + 11.1,
+// so 12.4).
+template <bool HANDED_OVER>
+__global__ __launch_bounds__(256) void k_pack_pairs(float* __restrict__ W, int I, const PairsView y, const PairsView x, bool first,
+                                                    float* __restrict__ vals, const ActiveRuns runs, int* __restrict__ dense_live) {
     constexpr int LD = PK_STEP + 1;
     __shared__ float tile[64 * LD];
     __shared__ uint8_t pair_s[2][PK_PAIRS];           // dword in a slot
@@ -231,10 +237,28 @@ __global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W,
     const PairsView& v = of_x ? x : y;
     const int r0 = of_x ? i0 : o0, band = r0 / PB_ROWS, kb = (of_x ? o0 : i0) / PK_STEP, t = (r0 % PB_ROWS) / 32 + (wave & 1);
     const int64_t bk = (int64_t)band * v.nk + kb;
+    float4 handed[4];
+    if constexpr (HANDED_OVER) {
+        const __amdgpu_buffer_rsrc_t from = active_buffer(vals, runs);
+        const int c = 4 * (tid & 15);
+        uint2 word[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) word[e] = runs.words[(int64_t)(o0 + 16 * e + (tid >> 4)) * runs.per_row + ((i0 + c) >> 5)];
+        auto value = [&](int e, int q) __attribute__((always_inline)) {
+            const uint32_t col = (uint32_t)(c & 31) + (uint32_t)q;
+            return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(from, (int)active_offset(word[e], col, (1u << col) - 1u), 0, 0));
+        };
+#pragma unroll
+        for (int e = 0; e < 4; ++e) handed[e] = make_float4(value(e, 0), value(e, 1), value(e, 2), value(e, 3));
+        if (blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *dense_live = 1;
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int o = 16 * e + (tid >> 4), c = 4 * (tid & 15);
-        const float4 w = *reinterpret_cast<const float4*>(W + (int64_t)(o0 + o) * I + i0 + c);
+        float4* const at = reinterpret_cast<float4*>(W + (int64_t)(o0 + o) * I + i0 + c);
+        float4 w;
+        if constexpr (HANDED_OVER) *at = w = handed[e];
+        else w = *at;
         float* p = tile + o * LD + c;
         p[0] = w.x; p[1] = w.y; p[2] = w.z; p[3] = w.w;
     }
@@ -322,14 +346,16 @@ __global__ __launch_bounds__(256) void k_pack_pairs(const float* __restrict__ W,
     store_sel(first_step + v.nk, ix2);
 }
 
-// From the mask and the dense copy: the slots where the active set is a new one, and the blocks
-int make_pairs(mst_layer* L, hipStream_t s) {
+// From the mask and the dense copy: the slots where the active set is a new one, and the blocks.  words: of the active set, where the
+// dense copy has to take the values first
+int make_pairs(mst_layer* L, hipStream_t s, const ActiveRuns* words) {
     const PairsView &y = L->pairs_y, &x = L->pairs_x;
     if (!L->pairs_matched) {
         k_match_pairs<<<(unsigned)(y.bands * y.nk + x.bands * x.nk), 256, 0, s>>>(L->mask, L->I, y, x);
         MST_LAUNCH_CHECK();
     }
-    k_pack_pairs<<<dim3((unsigned)(L->I / 64), (unsigned)(L->O / 64)), 256, 0, s>>>(L->Wd, L->I, y, x, !L->pairs_matched);
+    const auto pack = words ? k_pack_pairs<true> : k_pack_pairs<false>;
+    pack<<<dim3((unsigned)(L->I / 64), (unsigned)(L->O / 64)), 256, 0, s>>>(L->Wd, L->I, y, x, !L->pairs_matched, L->vals, words ? *words : ActiveRuns{}, L->dense_live);
     MST_LAUNCH_CHECK();
     return MST_OK;
 }

@@ -1134,6 +1134,8 @@ int make_runs(mst_layer* const* layers, int n, hipStream_t s) {
     return MST_OK;
 }
 
+static ActiveRuns runs_of(const mst_layer* L) { return ActiveRuns{L->runs, (int)cdiv(L->I, 32), (uint32_t)(4 * L->nnz)}; }
+
 // For a product that reads them.  Made by the product itself they are not there for other streams before it has waited for them,
 // once behind an update that found them unread; a recording cannot wait and leaves them.
 int active_runs(ActiveOut* active, hipStream_t s, ActiveRuns& runs, int64_t& stride) {
@@ -1153,7 +1155,7 @@ int active_runs(ActiveOut* active, hipStream_t s, ActiveRuns& runs, int64_t& str
         MST_HIP(hipStreamSynchronize(s));
     }
     L->runs_used = true;
-    runs = ActiveRuns{L->runs, (int)cdiv(L->I, 32), (uint32_t)(4 * L->nnz)};
+    runs = runs_of(L);
     active->stride = stride = (int64_t)align_up((size_t)L->nnz, 4);
     active->done = true;
     return MST_OK;
@@ -1459,10 +1461,19 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
             L->pairs_unread += pairs && L->pairs_unread < mst_layer::PAIRS_UNREAD;
         }
     }
-    const int rc = refresh_views(L, row, col, dense, false, s);
+    // (the packing brings the values to the dense copy itself where it can; a view's entries before it, since they say that the dense copy is out of use)
+    const bool with_pairs = pairs && L->runs_valid && !L->runs_missed;
+    const int rc = refresh_views(L, row, col, dense && !with_pairs, false, s);
     // (made again from the dense copy: 8.5 us at 1024 x 4096.  Scattering 5 % of the positions into them took 11, 10 % of 1280 x
     // 5120 took 30: four stores of two bytes per value, two of them far apart.)
     if (rc != MST_OK) return rc;
+    if (with_pairs) {
+        L->runs_used = true;
+        const ActiveRuns words = runs_of(L);
+        const int rcw = make_pairs(L, s, &words);
+        if (rcw != MST_OK) return rcw;
+        pairs = false;
+    }
     const int rcp = planes ? make_planes(L, s) : MST_OK;
     return rcp == MST_OK && pairs ? make_pairs(L, s) : rcp;
 }

@@ -121,3 +121,63 @@ def test_two_streams_behind_an_update_that_left_the_words():
     torch.cuda.synchronize()
     for dW in out:
         _check(rig, dY, X, act, dW)
+
+
+@pytest.mark.parametrize("O,I", [(512, 512), (1280, 320), (64, 2048)])
+def test_a_handover_that_packs(O, I):
+    """Values handed over, eagerly and by a recording, before and behind an update, while products read the packed weights: those, the
+    dense copy (products pinned to a kernel that reads it) and a view that is walked for the first time later all hold them."""
+    T, act, side = 4096, mst.MST_F32, torch.cuda.Stream()
+    rig = _rig(O, I, T, 0.08)
+    L = rig.layer
+    X = _numbers(T, I, act, 1)
+    Y = torch.empty((T, O), device=DEV)
+    fill = torch.empty(O * I, device=DEV)                     # whole numbers that three and two bfloat16 parts hold
+
+    def product(tile, path=mst.MST_PATH_DENSE):
+        L.set_path(path)
+        mst.mst_gemm_force_fp32_mfma(tile)
+        Y.fill_(7.0)
+        mst.mst_sparse_fc_fwd(L, X, Y, T, act)
+        torch.cuda.synchronize()
+        return Y.double()
+
+    def check(values):
+        W = torch.zeros(O * I, dtype=torch.float64, device=DEV)
+        W[torch.from_numpy(rig.indices()).to(DEV).long()] = values.double()
+        want = X.double() @ W.view(O, I).T
+        assert torch.equal(product(24), want)
+        assert mst.mst_gemm_last_tile() == 24
+        assert torch.equal(product(128 if O % 128 == 0 and I % 128 == 0 else 1032), want)
+        return want
+
+    def hand_over(scale):
+        n = L.nnz
+        L.values().copy_((torch.arange(n, device=DEV) % 15 - 7) * scale)
+        L.sync_values()
+        return L.values().clone()
+
+    hand_over(1.0)
+    product(24)                                               # packed from now on
+    check(hand_over(2.0))
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        L.values().copy_(fill[:L.nnz])
+        L.sync_values(side)
+    for k in range(3):
+        fill.copy_((torch.arange(O * I, device=DEV) + k) % 13 - 6)
+        graph.replay()
+        torch.cuda.synchronize()
+        check(fill[:L.nnz])
+        check(hand_over(1.0 + k))
+    mst.mst_mask_update_from_scores(L, torch.randn(O, I, device=DEV), L.nnz / (O * I), 0.3, 0.25, 11, rig.ws)
+    product(24)
+    check(hand_over(4.0))
+    fill.copy_(torch.arange(O * I, device=DEV) % 11 - 5)
+    graph.replay()
+    torch.cuda.synchronize()
+    check(fill[:L.nnz])
+    want = check(hand_over(3.0))
+    L.values().zero_()                                        # (not handed over)
+    assert torch.equal(product(0, mst.MST_PATH_SPARSE), want)
