@@ -694,6 +694,7 @@ struct CanonicalArgs {
     int nseg;
     int *segcnt, *rowptr, *flat;
     float* vals;
+    uint2* runs;               // null: not wanted, or rows that end inside a word
 };
 template <int CAP>
 __global__ __launch_bounds__(256) void k_count_seg(const Batch<CanonicalArgs, CAP> batch) {
@@ -725,7 +726,8 @@ __global__ __launch_bounds__(256) void k_count_seg(const Batch<CanonicalArgs, CA
 
 // segptr[sg] = active positions before segment sg.  A lane takes four consecutive positions of a
 // window of 256; the row pointers are written by the wavefront whose segment holds the row's
-// first position (rowptr[O] by the last one).
+// first position (rowptr[O] by the last one).  Eight lanes have a word of active.h (a launch of its own: 4 to 8 us per layer of an
+// update, of a GPT-2-large block).
 template <int CAP>
 __global__ __launch_bounds__(256) void k_fill_canonical(const Batch<CanonicalArgs, CAP> batch) {
     if (batch.surplus()) return;
@@ -770,6 +772,14 @@ __global__ __launch_bounds__(256) void k_fill_canonical(const Batch<CanonicalArg
             total += __popcll(bal[u]);
         }
         int k = canon + before;
+        if (a.runs) {
+            uint32_t bits = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) bits |= (on[u] ? 1u : 0u) << (4 * (lane & 7) + u);
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) bits |= (uint32_t)__shfl_xor((int)bits, d, 64);
+            if ((lane & 7) == 0 && p < end) a.runs[p >> 5] = make_uint2(~bits, (uint32_t)k);
+        }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             if (on[u]) { vals[k] = w[u]; flat[k] = (int)(p + u); ++k; }
@@ -1071,7 +1081,9 @@ int build_canonical(const BuildItem* items, int n, hipStream_t s) {
         int* const cnt = items[x].ws.segcnt[0];
         const int nseg = (int)cdiv(L->N, CSEG);
         L->views_valid = false;
-        seg.add(CanonicalArgs{L->mask, items[x].Wsrc, L->O, L->I, L->N, nseg, cnt, L->rowptr, L->flat, L->vals}, cdiv(nseg, 4));
+        uint2* const runs = L->runs_used && L->I % 32 == 0 ? L->runs : nullptr;
+        L->runs_valid |= runs != nullptr;
+        seg.add(CanonicalArgs{L->mask, items[x].Wsrc, L->O, L->I, L->N, nseg, cnt, L->rowptr, L->flat, L->vals, runs}, cdiv(nseg, 4));
         scan.add(ScanArgs{cnt, cnt, nseg}, 1);
     }
     launch_batch(seg, [&](const auto& b) { k_count_seg<<<b.grid(), 256, 0, s>>>(b); });
@@ -1124,7 +1136,7 @@ int make_runs(mst_layer* const* layers, int n, hipStream_t s) {
     Batch<RunArgs> batch;
     for (int x = 0; x < n; ++x) {
         mst_layer* L = layers[x];
-        if (!L->runs) continue;
+        if (!L->runs || L->runs_valid) continue;
         batch.add(RunArgs{L->mask, L->rowptr, L->runs, L->O, L->I}, cdiv(L->O, 4));
         L->runs_valid = true;
     }

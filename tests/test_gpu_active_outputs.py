@@ -67,12 +67,16 @@ def test_exact_gradient(O, I, T, act, tile, density):
     _check(rig, dY, X, kind)
 
 
+@pytest.mark.parametrize("path", [mst.MST_PATH_DENSE, mst.MST_PATH_AUTO])
+@pytest.mark.parametrize("O,I,kind", [(1024, 256, "f32"), (776, 272, "bf16"), (1048, 224, "bf16")])
 @pytest.mark.parametrize("read_before", [True, False])
-def test_updates_take_the_words_along(read_before):
-    """Eager and recorded products before and behind eager and recorded updates of the active set."""
-    O, I, T, act = 1024, 256, 512, mst.MST_F32
+def test_updates_take_the_words_along(read_before, O, I, kind, path):
+    """Eager and recorded products before and behind eager and recorded updates of the active set, updates that rebuild the views and
+    updates that do not."""
+    T, act = 512, mst.MST_BF16 if kind == "bf16" else mst.MST_F32
     mst.mst_gemm_force_fp32_mfma(256)
     rig = _rig(O, I, T, 0.1)
+    rig.layer.set_path(path)
     L, side = rig.layer, torch.cuda.Stream()
     X, dY = _numbers(T, I, act, 1), _numbers(T, O, act, 2)
     score = torch.randn(O, I, device=DEV)
