@@ -151,7 +151,7 @@ struct mst_layer {
     int* dense_live = nullptr; // device: Wd holds the values handed over last (0: every built view holds them)
     int hint_T = 0;            // batch size and activation type of the last product call (0: none yet)
     int hint_act = 0;
-    // Which of every 32 columns are active and where they lie in vals (see active.h), for layers with rows of whole 16 bytes (null: none).  Made when
+    // Which of every 32 columns are active and where they lie in vals (see active.h), for layers with rows of whole eights (null: none).  Made when
     // the layer is loaded; an update makes them again if a product has read them, recorded products included, since their replays read them
     // without asking.  Otherwise the next product does.
     uint2* runs = nullptr;
@@ -363,7 +363,7 @@ bool gemm_pairs_forced();
 void gemm_note_tile(int tile);
 // the same at full fp32 precision for any shape (B fp32); see gemm_exact.hip
 int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,
-               float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed);
+               float* split_ws, int64_t split_ws_floats, hipStream_t s, int* left_unsummed, ActiveOut* active = nullptr);
 int gemm_exact_tile(int tile);
 int gemm_stream_tn_bf16(const uint16_t* A, const uint16_t* B, float* C, int M, int N, int Kdim, int k_per_split, int64_t split_stride,
                         hipStream_t s);

@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "active.h"
 #include "split_bf16.h"
 
 namespace mst {
@@ -183,10 +184,13 @@ struct ExOperand {
 // Tile numbers run in bands of eight tile rows, column by column inside a band (the tiles an XCD works on
 // at a time share operand panels in its L2); XCD x takes a contiguous share, one k range after the other.
 // PER_CU: workgroups on a CU that the registers are for (plan_exact's choice; 0: as many as the LDS holds).
-template <bool A16, bool A_KMAJOR, bool B_KMAJOR, int TM, int PER_CU>
+// ACTIVE: only the active outputs, side by side (C and split_stride are of them).  Whole outputs and a gather -> this: 4000 x 1000 at a density of
+// 0.2, 5001 tokens 215 us, so 208, 1000 tokens 54.2, so 49.4; 5000 x 4000 at 0.9, 700 tokens 180, so 149.
+template <bool A16, bool A_KMAJOR, bool B_KMAJOR, int TM, int PER_CU, bool ACTIVE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PER_CU ? PER_CU : 2, PER_CU ? PER_CU : 3)))
 void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
-                  int M, int N, int Kdim, int k_per_split, int64_t split_stride) {
+                  int M, int N, int Kdim, int k_per_split, int64_t split_stride, const ActiveRuns runs) {
+    static_assert(!ACTIVE || TM == 128);
     typedef ExOperand<A16, A_KMAJOR, TM> OpA;
     typedef ExOperand<false, B_KMAJOR, TM> OpB;
     constexpr int BK = 4096 / TM, PLANE = 8192, MI = TM / 64;
@@ -257,6 +261,15 @@ void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restr
         rb.stage(lb, tid);
     };
     int k0 = kbeg;
+    char* const words = lb + OpB::PLANES * PLANE + 1024 * wave;      // of this wavefront's 64 rows and columns; past the end: no active ones
+    if constexpr (ACTIVE) {
+        const int m = m0 + wm + lane, word = (n0 + wn) >> 5;
+        uint2 w[2] = {make_uint2(0xFFFFFFFFu, 0u), make_uint2(0xFFFFFFFFu, 0u)};
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (m < M && word + j < runs.per_row) w[j] = runs.words[(int64_t)m * runs.per_row + word + j];
+        *reinterpret_cast<uint4*>(words + 16 * lane) = make_uint4(w[0].x, w[0].y, w[1].x, w[1].y);
+    }
     fetch(k0);
     for (; k0 + BK < kend; k0 += BK) {
         __syncthreads();
@@ -276,6 +289,31 @@ void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restr
         for (int v = 0; v < 16; ++v) acc[0][0][v] += other[v];
     // D layout of the 32x32 MFMA: lane l, register v -> row 8*(v/4) + 4*(l/32) + v%4, column l%32
     bool nan = false;
+    if constexpr (ACTIVE) {
+        const __amdgpu_buffer_rsrc_t out = active_buffer(Cz, runs);
+        const uint32_t below = (1u << lm) - 1u;
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const uint4 w = *reinterpret_cast<const uint4*>(words + 16 * (32 * i + 8 * (v >> 2) + 4 * lk + (v & 3)));
+                store_active(out, make_uint2(w.x, w.y), lane, below, acc[i][0][v]);
+                store_active(out, make_uint2(w.z, w.w), lane, below, acc[i][MI - 1][v]);
+                nan |= acc[i][0][v] != acc[i][0][v] || acc[i][MI - 1][v] != acc[i][MI - 1][v];
+            }
+        if (nan) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll 1
+            for (int x = 0; x < MI * MI * 16; ++x) {
+                const int r = (x / (16 * MI)) * 32 + 8 * ((x >> 2) & 3) + 4 * lk + (x & 3), j = (x >> 4) % MI;
+                const uint32_t at = active_offset(*reinterpret_cast<const uint2*>(words + 16 * r + 8 * j), (uint32_t)lm, below);
+                if (at >= runs.bytes) continue;
+                float* const c = Cz + (at >> 2);
+                if (*c != *c) *c = fp32_sum<typename OpA::T, A_KMAJOR, float, B_KMAJOR>(A, lda, B, ldb, m0 + wm + r, n0 + wn + 32 * j + lm, kbeg, kend);
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -586,7 +624,7 @@ int gemm_exact_tile(int tile) {
 
 template <bool A16, bool AK, bool BKM>
 static int launch_exact(const void* A, int64_t lda, const float* B, int64_t ldb, float* C, int M, int N, int Kdim,
-                        float* split_ws, int64_t split_ws_floats, int* nparts, hipStream_t s) {
+                        float* split_ws, int64_t split_ws_floats, int* nparts, hipStream_t s, ActiveOut* active = nullptr) {
     const int64_t mn = (int64_t)M * N;
     const ExactPlan plan = plan_exact(true, AK, M, N, Kdim, A16, split_ws ? split_ws_floats / mn : 1, nparts == nullptr);
     const int kps = (int)(cdiv(cdiv(Kdim, plan.nsplit), 128) * 128);
@@ -602,11 +640,25 @@ static int launch_exact(const void* A, int64_t lda, const float* B, int64_t ldb,
         if (rc != MST_OK) return rc;
         k_gemm_stream<A16, AK, false, BKM, 2><<<grid, 512, STREAM_LDS_64, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
     } else if (plan.tile == 128) {
-        if constexpr (A16) k_gemm_exact<A16, AK, BKM, 128, 0><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
-        else if (plan.places == 96) k_gemm_exact<A16, AK, BKM, 128, 3><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
-        else k_gemm_exact<A16, AK, BKM, 128, 2><<<grid, 256, 56u << 10, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);     // (the LDS of three)
+        constexpr bool CAN = AK && BKM && !A16;
+        int64_t stride = mn;
+        ActiveRuns runs{};
+        if constexpr (CAN) {
+            const int rc = active_runs(active, s, runs, stride);
+            if (rc != MST_OK) return rc;
+        }
+        const bool only = runs.words != nullptr;
+        float* const to = only && nsplit == 1 ? active->dW : dst;
+        if constexpr (A16) {
+            k_gemm_exact<A16, AK, BKM, 128, 0, false><<<grid, 256, lds, s>>>(A, lda, B, ldb, to, M, N, Kdim, kps, stride, runs);
+        } else {
+            const auto three = only ? k_gemm_exact<A16, AK, BKM, 128, 3, CAN> : k_gemm_exact<A16, AK, BKM, 128, 3, false>;
+            const auto two = only ? k_gemm_exact<A16, AK, BKM, 128, 2, CAN> : k_gemm_exact<A16, AK, BKM, 128, 2, false>;
+            if (plan.places == 96) three<<<grid, 256, lds + (only ? 4096u : 0u), s>>>(A, lda, B, ldb, to, M, N, Kdim, kps, stride, runs);
+            else two<<<grid, 256, 56u << 10, s>>>(A, lda, B, ldb, to, M, N, Kdim, kps, stride, runs);     // (the LDS of three)
+        }
     } else {
-        k_gemm_exact<A16, AK, BKM, 64, 0><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn);
+        k_gemm_exact<A16, AK, BKM, 64, 0, false><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn, ActiveRuns{});
     }
     MST_LAUNCH_CHECK();
     if (nparts) {
@@ -629,9 +681,9 @@ int gemm_stream_tn_bf16(const uint16_t* A, const uint16_t* B, float* C, int M, i
 }
 
 int gemm_exact(GemmKind kind, const void* A, mst_dtype a_dt, const float* B, float* C, int M, int N, int Kdim,
-               float* split_ws, int64_t split_ws_floats, hipStream_t s, int* nparts) {
+               float* split_ws, int64_t split_ws_floats, hipStream_t s, int* nparts, ActiveOut* active) {
     const bool a16 = a_dt == MST_BF16;
-    if (kind == GEMM_TN) return a16 ? MST_ERR_ARG : launch_exact<false, true, true>(A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, nparts, s);
+    if (kind == GEMM_TN) return a16 ? MST_ERR_ARG : launch_exact<false, true, true>(A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, nparts, s, active);
     if (kind == GEMM_NT)
         return a16 ? launch_exact<true, false, false>(A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, nparts, s)
                    : launch_exact<false, false, false>(A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, nparts, s);

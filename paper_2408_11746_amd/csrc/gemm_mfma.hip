@@ -1233,7 +1233,7 @@ int gemm_mfma(GemmKind kind, const void* A, mst_dtype a_dt, const void* B, mst_d
     }
     const int64_t max_split = split_ws ? split_ws_floats / ((int64_t)M * N) : 1;
     const SplitPlan plan = full ? SplitPlan{0, 1, 0.0} : plan_fp32(kind, M, N, Kdim, max_split, left_unsummed == nullptr);
-    if (plan.tile == 0) return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed);
+    if (plan.tile == 0) return gemm_exact(kind, A, a_dt, (const float*)B, C, M, N, Kdim, split_ws, split_ws_floats, s, left_unsummed, active);
     if (kind == GEMM_TN) return launch_split<true, true>(plan, A, M, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s, active);
     if (kind == GEMM_NT) return launch_split<false, false>(plan, A, Kdim, B, Kdim, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);
     return launch_split<false, true>(plan, A, Kdim, B, N, C, M, N, Kdim, split_ws, split_ws_floats, left_unsummed, s);

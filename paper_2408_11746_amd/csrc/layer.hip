@@ -152,8 +152,8 @@ struct LayerCarve {
 // the tile of gemm_planes.hip divides the outputs of one product, its k step the contraction range
 static bool has_planes(int O, int I) { return O % 32 == 0 && I % 32 == 0 && (O % 256 == 0 || I % 256 == 0); }
 
-// rows of whole 16 bytes of the mask, and outputs whose bytes an unsigned holds
-static bool has_runs(int O, int I) { return I % 16 == 0 && (int64_t)O * I < (int64_t)1 << 30; }
+// rows of whole eights of the mask, and outputs whose bytes an unsigned holds
+static bool has_runs(int O, int I) { return I % 8 == 0 && (int64_t)O * I < (int64_t)1 << 30; }
 
 // whole steps of gemm_pairs.hip in both directions
 static bool has_pairs(int O, int I) { return O % 64 == 0 && I % 64 == 0; }
@@ -1115,12 +1115,12 @@ __global__ __launch_bounds__(256) void k_active_runs(const Batch<RunArgs, CAP> b
         const int w = w0 + lane;
         uint32_t bits = 0;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (32 * w + 16 * h >= a.I) continue;
-            const uint4 u = *reinterpret_cast<const uint4*>(m + 32 * w + 16 * h);
-            const uint32_t d[4] = {u.x, u.y, u.z, u.w};
+        for (int h = 0; h < 4; ++h) {
+            if (32 * w + 8 * h >= a.I) continue;
+            const uint2 u = *reinterpret_cast<const uint2*>(m + 32 * w + 8 * h);
+            const uint32_t d[2] = {u.x, u.y};
 #pragma unroll
-            for (int e = 0; e < 16; ++e) bits |= ((d[e >> 2] >> (8 * (e & 3)) & 0xFFu) != 0u ? 1u : 0u) << (16 * h + e);
+            for (int e = 0; e < 8; ++e) bits |= ((d[e >> 2] >> (8 * (e & 3)) & 0xFFu) != 0u ? 1u : 0u) << (8 * h + e);
         }
         const int n = __popc(bits);
         int upto = n;

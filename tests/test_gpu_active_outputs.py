@@ -57,7 +57,8 @@ def _rig(O, I, T, density, seed=5):
     (256, 256, 64, "f32", 256), (512, 256, 2048, "f32", 256), (3072, 768, 1024, "f32", 256), (2560, 2560, 1024, "f32", 256),
     (128, 128, 64, "f32", 128), (256, 384, 96, "f32", 128), (384, 1152, 2048, "f32", 128),
     (8, 16, 1, "bf16", 256), (264, 272, 33, "bf16", 256), (520, 48, 2049, "bf16", 256), (1288, 1040, 3000, "bf16", 256), (2048, 1040, 97, "bf16", 256),
-    (264, 264, 96, "bf16", 256), (300, 270, 64, "f32", 0), (96, 80, 64, "bf16", 64)])
+    (264, 264, 96, "bf16", 256), (264, 264, 33, "f32", 1128), (130, 40, 1, "f32", 1128), (1300, 520, 2048, "f32", 1128), (2500, 1000, 3001, "f32", 1128),
+    (2500, 1000, 130, "f32", 1128), (300, 270, 64, "f32", 0), (96, 80, 64, "bf16", 64)])
 def test_exact_gradient(O, I, T, act, tile, density):
     print("case", O, I, T, act, tile, density, flush=True)
     kind = mst.MST_BF16 if act == "bf16" else mst.MST_F32
@@ -65,6 +66,21 @@ def test_exact_gradient(O, I, T, act, tile, density):
     rig = _rig(O, I, T, density)
     X, dY = _numbers(T, I, kind, 1), _numbers(T, O, kind, 2)
     _check(rig, dY, X, kind)
+
+
+def test_infinite_operands_of_the_full_precision_kernel():
+    """the positions that full fp32 sums make infinite or no number, and the others as the whole dense gradient has them"""
+    O, I, T, act = 264, 264, 64, mst.MST_F32
+    mst.mst_gemm_force_fp32_mfma(1128)
+    rig = _rig(O, I, T, 0.2)
+    X, dY = _numbers(T, I, act, 1), _numbers(T, O, act, 2)
+    X[5, 0], X[6, 0], X[7, 33], dY[9, 2] = float("inf"), float("-inf"), float("inf"), float("nan")
+    dW, G = torch.full((rig.layer.nnz + 64,), 7.0, device=DEV), torch.empty((O, I), device=DEV)
+    mst.mst_sparse_fc_bwd_weight(rig.layer, dY, X, dW, T, rig.ws, act)
+    mst.mst_dense_grad(dY, X, G, T, O, I, act, rig.ws)
+    want, dW = G.cpu().numpy().ravel()[rig.indices()], dW.cpu().numpy()
+    assert np.isnan(want).any() and np.isinf(want).any()
+    assert np.array_equal(dW[:-64], want, equal_nan=True) and np.all(dW[-64:] == 7.0)
 
 
 @pytest.mark.parametrize("path", [mst.MST_PATH_DENSE, mst.MST_PATH_AUTO])
