@@ -453,7 +453,7 @@ def run_block(args, name, mst, synth, torch, lds_peak, with_cpu_baseline):
     gemm_k = "k_gemm_split256 / k_gemm_split_n160 / k_gemm_split (fp32 operands as bf16 hi + lo)" if act == "f32" else \
         "k_gemm_planes (bfloat16 activations x fp32 weights as bf16 hi + lo, 2 products per term)"
     gemm_k += ", up to a density of about a tenth k_gemm_pairs (the same parts on v_smfmac_f32_32x32x32_bf16)"
-    wgrad_dense_k = ("k_gemm_wgrad16" if act == "bf16" else "k_gemm_split256<TN> / k_gemm_split<TN>") + " + k_gather_flat"
+    wgrad_dense_k = ("k_gemm_wgrad16" if act == "bf16" else "k_gemm_split256<TN> / k_gemm_split<TN>") + " of the active positions + k_splitk_reduce4 (small, mostly active layers: whole, + k_gather_flat)"
     kernel = {"fwd": gemm_k if dp else spmm_k,
               "bwd_input": gemm_k if dense_dx[dL.name] else spmm_k,
               "bwd_weight": wgrad_dense_k if dw else "k_walk_dw + k_walk_reduce",

@@ -70,8 +70,8 @@ struct View {
 struct PairsView {
     int R = 0, K = 0, nk = 0, bands = 0;
     uint16_t* slots = nullptr; // [band][step][32] where the k pairs (2 p, 2 p + 1) of a step go in LDS
-    uint32_t* flags = nullptr; // [band][step] a byte per two tiles of 32 rows: 1 if one of them needs a second step
-    uint8_t* over = nullptr;   // [band][step] 1: by the mask some row needs a second one
+    uint32_t* flags = nullptr; // [band][step] a byte per two tiles of 32 rows: 1 if one of them has second weights
+    uint8_t* over = nullptr;   // [band][step] 1: by the mask some row has second weights
     uint32_t* count = nullptr; // [2] (the row view's) how many of those there are in either view
     char* blocks = nullptr;    // [band][2 nk] packed tiles of the steps, then those of the third and fourth weights among four k
     uint32_t* sel = nullptr;   // [band][2 nk] their selectors
