@@ -1082,7 +1082,6 @@ int build_canonical(const BuildItem* items, int n, hipStream_t s) {
         const int nseg = (int)cdiv(L->N, CSEG);
         L->views_valid = false;
         uint2* const runs = L->runs_used && L->I % 32 == 0 ? L->runs : nullptr;
-        L->runs_valid |= runs != nullptr;
         seg.add(CanonicalArgs{L->mask, items[x].Wsrc, L->O, L->I, L->N, nseg, cnt, L->rowptr, L->flat, L->vals, runs}, cdiv(nseg, 4));
         scan.add(ScanArgs{cnt, cnt, nseg}, 1);
     }
@@ -1092,6 +1091,8 @@ int build_canonical(const BuildItem* items, int n, hipStream_t s) {
     MST_LAUNCH_CHECK();
     launch_batch(seg, [&](const auto& b) { k_fill_canonical<<<b.grid(), 256, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
+    for (int x = 0; x < n; ++x)
+        if (items[x].L->runs_used && items[x].L->I % 32 == 0) items[x].L->runs_valid = items[x].L->runs != nullptr;
     return MST_OK;
 }
 
@@ -1132,13 +1133,14 @@ __global__ __launch_bounds__(256) void k_active_runs(const Batch<RunArgs, CAP> b
         first += __shfl(upto, 63, 64);
     }
 }
+// (those that have them are left out; whether they are there is for the caller to say: behind the launch where it changes the mask, behind a wait
+// where it is a product)
 int make_runs(mst_layer* const* layers, int n, hipStream_t s) {
     Batch<RunArgs> batch;
     for (int x = 0; x < n; ++x) {
-        mst_layer* L = layers[x];
+        const mst_layer* L = layers[x];
         if (!L->runs || L->runs_valid) continue;
         batch.add(RunArgs{L->mask, L->rowptr, L->runs, L->O, L->I}, cdiv(L->O, 4));
-        L->runs_valid = true;
     }
     if (batch.n == 0) return MST_OK;
     launch_batch(batch, [&](const auto& b) { k_active_runs<<<b.grid(), 256, 0, s>>>(b); });
@@ -1149,7 +1151,8 @@ int make_runs(mst_layer* const* layers, int n, hipStream_t s) {
 static ActiveRuns runs_of(const mst_layer* L) { return ActiveRuns{L->runs, (int)cdiv(L->I, 32), (uint32_t)(4 * L->nnz)}; }
 
 // For a product that reads them.  Made by the product itself they are not there for other streams before it has waited for them,
-// once behind an update that found them unread; a recording cannot wait and leaves them.
+// once behind an update that found them unread, and it says that they are there after the wait (two that meet, from two threads, each make
+// them: the same bits); a recording cannot wait and leaves them.
 int active_runs(ActiveOut* active, hipStream_t s, ActiveRuns& runs, int64_t& stride) {
     if (!active) return MST_OK;
     mst_layer* L = const_cast<mst_layer*>(active->L);        // a cache of the mask, not layer state
@@ -1165,6 +1168,7 @@ int active_runs(ActiveOut* active, hipStream_t s, ActiveRuns& runs, int64_t& str
         rc = make_runs(&L, 1, s);
         if (rc != MST_OK) return rc;
         MST_HIP(hipStreamSynchronize(s));
+        L->runs_valid = true;
     }
     L->runs_used = true;
     runs = runs_of(L);
@@ -1418,6 +1422,7 @@ int mst_layer_load_dense(mst_layer_t* L, const float* W_dev, const uint8_t* M_de
     }
     const int rcr = make_runs(&L, 1, s);
     if (rcr != MST_OK) return rcr;
+    L->runs_valid = L->runs != nullptr;
     L->built = true;
     return MST_OK;
 }

@@ -822,7 +822,10 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
         L->pairs_matched = L->pairs_valid;
     }
     if (n_canonical > 0 && (rc = build_canonical(canonical, n_canonical, s)) != MST_OK) return rc;
-    return n_runs > 0 ? make_runs(runs, n_runs, s) : MST_OK;
+    if (n_runs == 0) return MST_OK;
+    rc = make_runs(runs, n_runs, s);
+    for (int x = 0; rc == MST_OK && x < n_runs; ++x) runs[x]->runs_valid = true;
+    return rc;
 }
 
 }  // namespace mst

@@ -1,6 +1,8 @@
 """The weight gradient on the dense matrix cores that writes the active positions alone (dW of App. Eq. (1)'s gradients): every tile, one
 and several partial outputs, rows that end inside a word of 32 columns, tiles past the last row and column, empty and full rows, few and
 all positions.  Small whole numbers, whose products and sums are exact in every kernel: the result has to be the exact one."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -138,6 +140,33 @@ def test_two_streams_behind_an_update_that_left_the_words():
         torch.cuda._sleep(10_000_000)
     mst.mst_sparse_fc_bwd_weight(L, dY, X, out[0], T, rig.ws, act, a)
     mst.mst_sparse_fc_bwd_weight(L, dY, X, out[1], T, ws, act, b)
+    torch.cuda.synchronize()
+    for dW in out:
+        _check(rig, dY, X, act, dW)
+
+
+def test_two_threads_behind_an_update_that_left_the_words():
+    """The words are said to be there once they are: a product of another thread that comes while the first one waits for them does not read
+    those of the mask before."""
+    O, I, T, act = 1024, 256, 512, mst.MST_F32
+    mst.mst_gemm_force_fp32_mfma(256)
+    rig = _rig(O, I, T, 0.1)
+    L, a, b = rig.layer, torch.cuda.Stream(), torch.cuda.Stream()
+    X, dY = _numbers(T, I, act, 1), _numbers(T, O, act, 2)
+    mst.mst_mask_update_from_scores(L, torch.randn(O, I, device=DEV), L.nnz / (O * I), 0.3, 0.25, 11, rig.ws)
+    out = [torch.full((L.nnz + 64,), 7.0, device=DEV) for _ in range(2)]
+    ws = torch.empty_like(rig.ws)
+    begun = torch.cuda.Event()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(a):
+        torch.cuda._sleep(1_000_000_000)                 # (0.4 s)
+        begun.record()
+    first = threading.Thread(target=mst.mst_sparse_fc_bwd_weight, args=(L, dY, X, out[0], T, rig.ws, act, a))
+    first.start()
+    first.join(0.02)
+    assert not begun.query()                                  # (the first thread's words are still to be made)
+    mst.mst_sparse_fc_bwd_weight(L, dY, X, out[1], T, ws, act, b)
+    first.join()
     torch.cuda.synchronize()
     for dW in out:
         _check(rig, dY, X, act, dW)
