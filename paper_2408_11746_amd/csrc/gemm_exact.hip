@@ -183,7 +183,9 @@ struct ExOperand {
 
 // Tile numbers run in bands of eight tile rows, column by column inside a band (the tiles an XCD works on
 // at a time share operand panels in its L2); XCD x takes a contiguous share, one k range after the other.
-// PER_CU: workgroups on a CU that the registers are for (plan_exact's choice; 0: as many as the LDS holds).
+// PER_CU: workgroups on a CU that the registers are for (plan_exact's choice; 0: as many as the LDS holds).  With both operands k-major always
+// three, two of them held apart by their LDS: the code for two needs no more registers (170), and alone on its CU it is 9 % slower (dense
+// gradients of 1048 x 792, 385 tokens, to 5000 x 4000, one k range; half of the 80 shapes are 10 % slower with it).
 // ACTIVE: only the active outputs, side by side (C and split_stride are of them).  Whole outputs and a gather -> this: 4000 x 1000 at a density of
 // 0.2, 5001 tokens 215 us, so 208, 1000 tokens 54.2, so 49.4; 5000 x 4000 at 0.9, 700 tokens 180, so 149.
 template <bool A16, bool A_KMAJOR, bool B_KMAJOR, int TM, int PER_CU, bool ACTIVE>
@@ -653,9 +655,9 @@ static int launch_exact(const void* A, int64_t lda, const float* B, int64_t ldb,
             k_gemm_exact<A16, AK, BKM, 128, 0, false><<<grid, 256, lds, s>>>(A, lda, B, ldb, to, M, N, Kdim, kps, stride, runs);
         } else {
             const auto three = only ? k_gemm_exact<A16, AK, BKM, 128, 3, CAN> : k_gemm_exact<A16, AK, BKM, 128, 3, false>;
-            const auto two = only ? k_gemm_exact<A16, AK, BKM, 128, 2, CAN> : k_gemm_exact<A16, AK, BKM, 128, 2, false>;
             if (plan.places == 96) three<<<grid, 256, lds + (only ? 4096u : 0u), s>>>(A, lda, B, ldb, to, M, N, Kdim, kps, stride, runs);
-            else two<<<grid, 256, 56u << 10, s>>>(A, lda, B, ldb, to, M, N, Kdim, kps, stride, runs);     // (the LDS of three)
+            else if constexpr (AK) three<<<grid, 256, 56u << 10, s>>>(A, lda, B, ldb, to, M, N, Kdim, kps, stride, runs);     // (the LDS of three)
+            else k_gemm_exact<A16, AK, BKM, 128, 2, false><<<grid, 256, 56u << 10, s>>>(A, lda, B, ldb, to, M, N, Kdim, kps, stride, runs);
         }
     } else {
         k_gemm_exact<A16, AK, BKM, 64, 0, false><<<grid, 256, lds, s>>>(A, lda, B, ldb, dst, M, N, Kdim, kps, mn, ActiveRuns{});
