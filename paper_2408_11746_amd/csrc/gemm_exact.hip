@@ -45,7 +45,7 @@ typedef uint32_t ex_u32x2 __attribute__((ext_vector_type(2)));
 // m-major stores of consecutive rows, a third of the LDS cycles were conflicts).
 template <int TM>
 __device__ inline uint32_t ex_unit(int m, int u) {
-    if (TM == 64) return bf_unit(m, u);
+    if (TM == 64) return (uint32_t)(m * 128 + ((u ^ ((m >> 1) & 7)) << 4));      // (stores of rows two apart, or of one row)
     const int rho = (m & ~15) | ((m & 3) << 2) | ((m >> 2) & 3);
     return (uint32_t)(rho * 64 + (((u ^ (rho >> 2) ^ (rho >> 4) ^ (rho >> 1 & 1)) & 3) << 4));
 }
@@ -189,7 +189,7 @@ struct ExOperand {
 // ACTIVE: only the active outputs, side by side (C and split_stride are of them).  Whole outputs and a gather -> this: 4000 x 1000 at a density of
 // 0.2, 5001 tokens 215 us, so 208, 1000 tokens 54.2, so 49.4; 5000 x 4000 at 0.9, 700 tokens 180, so 149.
 template <bool A16, bool A_KMAJOR, bool B_KMAJOR, int TM, int PER_CU, bool ACTIVE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PER_CU ? PER_CU : 2, PER_CU ? PER_CU : 3)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PER_CU ? PER_CU : A_KMAJOR ? 3 : 2, PER_CU ? PER_CU : 3)))
 void k_gemm_exact(const void* __restrict__ Av, int64_t lda, const float* __restrict__ B, int64_t ldb, float* __restrict__ C,
                   int M, int N, int Kdim, int k_per_split, int64_t split_stride, const ActiveRuns runs) {
     static_assert(!ACTIVE || TM == 128);
