@@ -570,9 +570,12 @@ void k_gemm_stream(const void* __restrict__ Av, int64_t lda, const void* __restr
 // partial outputs.  Places of an XCD: 64 or 96 workgroups of 128 x 128, 96 of 64 x 64, 32 of the streaming
 // kernel; with no more workgroups than CUs each has one to itself and is faster.  Microseconds fitted to timings
 // of 130 products, 1 to 40 GFLOP, on MI355X (8-14 % rms error).
-// Three 128 x 128 workgroups of fp32 operands on a CU take 1.45 times as long as two (1.56 with both operands k-major; 115 shapes, sd 4 to
-// 7 %), so which of the two is ahead is a matter of how the tiles fill the rounds: Y of 1000 -> 4000, 5001 tokens (1280 tiles), 240 us with
+// Three 128 x 128 workgroups of fp32 operands on a CU take 1.45 times as long as two (115 shapes, sd 4 to 7 %), so which of the two is
+// ahead is a matter of how the tiles fill the rounds: Y of 1000 -> 4000, 5001 tokens (1280 tiles), 240 us with
 // two and 212 with three, of 1203 -> 801, 16001 tokens (882 tiles), 191 and 212.  (bfloat16 A: three always, as its constants were fitted.)
+// With both operands k-major 1.51 times, and less by a twentieth where a second round follows the first, whose workgroups do not
+// end together (104 outputs of 10^6 and more, one to eight ranges; 1.56 and nothing off took one range where several with a second round were
+// ahead: 2304 x 3840, 3001 tokens, density 0.5, 336 us with one range, 283 with five, 309 before three were a choice).
 struct ExactPlan {
     int tile;
     bool stream;
@@ -601,10 +604,11 @@ static ExactPlan plan_exact(bool three, bool tn, int M, int N, int Kdim, bool a1
         if (g_exact_tile && kd.hook != g_exact_tile) continue;
         const int64_t Q = cdiv(cdiv(M, kd.tile) * cdiv(N, kd.tile), 8);
         if ((a16 || !three) && kd.full[1] == 0.0) continue;
-        const double full = kd.full[a16] * (tn && kd.tile == 128 && kd.places == 96 ? 1.07 : 1.0), lone = kd.lone[a16];
+        const bool tn_three = tn && kd.tile == 128 && kd.places == 96;
+        const double full = kd.full[a16] * (tn_three ? 1.045 : 1.0), lone = kd.lone[a16];
         for (int ns : cand) {
             if (ns > 1 && (ns > max_split || Kdim / ns < 256)) break;
-            const double work = xcd_rounds(Q * ns, kd.places, kd.lone_places, full, lone);
+            const double work = xcd_rounds(Q * ns, kd.places, kd.lone_places, full, lone) * (tn_three && Q * ns > kd.places ? 0.944 : 1.0);
             double cost = kd.launch[a16] + (kd.stream ? work * (double)cdiv(Kdim, ns) + (double)cdiv(Q * ns, kd.places) * kd.start[a16]
                                                       : work * ((double)cdiv(cdiv(Kdim, ns), kd.bk) + kd.start[a16]));
             if (ns > 1) cost += 3.0 + 1.0e-6 * (double)M * (double)N * (summed ? ns + 1.0 : 0.25 * ns);
