@@ -152,11 +152,15 @@ struct mst_layer {
     int hint_T = 0;            // batch size and activation type of the last product call (0: none yet)
     int hint_act = 0;
     // Which of every 32 columns are active and where they lie in vals (see active.h), for layers with rows of whole eights (null: none).  Made when
-    // the layer is loaded; an update makes them again if a product has read them, recorded products included, since their replays read them
-    // without asking.  Otherwise the next product does.
+    // the layer is loaded; an update makes them again if a product or a hand-over has read them, unless the last RUNS_UNREAD updates did so for
+    // nobody (the ultra-sparse phase walks; they are 2 us of an update of the four layers of a GPT-2-small block, 7 to 10 of a
+    // GPT-2-large one), and always once a recording has read them, since its replays do so without asking.  Otherwise the next product does.
     uint2* runs = nullptr;
-    bool runs_valid = false, runs_used = false;
+    bool runs_valid = false, runs_recorded = false;
     bool runs_missed = false;  // an update without them has been recorded: its replays leave them behind, products do without
+    static constexpr int RUNS_UNREAD = 8;
+    int runs_unread = -1;                        // updates since something read them (-1: nothing has)
+    bool runs_kept(bool recording) const { return runs_recorded || (runs_unread >= 0 && (recording || runs_unread < RUNS_UNREAD)); }
     std::atomic<uint64_t> choice{0};   // sparse-or-dense choices at the last batch size and type (see remembered(); 0: none)
     mst::View row;             // S = W   [O x I], used by fwd (and bwd_weight)
     mst::View col;             // S = W^T [I x O], used by bwd_input
@@ -307,7 +311,7 @@ struct UpdateItem {
 
 // ---- internal entry points implemented across the .hip files ----
 int build_views(const BuildItem* items, int n, hipStream_t s);          // n up to BATCH_MAX
-int build_canonical(const BuildItem* items, int n, hipStream_t s);
+int build_canonical(const BuildItem* items, int n, bool recording, hipStream_t s);
 int ensure_views(const mst_layer* L, const Workspace& ws, hipStream_t s);
 int views_there(const mst_layer* L, hipStream_t s, bool* there);
 bool views_wanted(const mst_layer* L);

@@ -1073,7 +1073,7 @@ int build_views(const BuildItem* items, int n, hipStream_t s) {
 }
 
 // vals / flat / rowptr alone (three launches): what layers served by the dense contractions need
-int build_canonical(const BuildItem* items, int n, hipStream_t s) {
+int build_canonical(const BuildItem* items, int n, bool recording, hipStream_t s) {
     Batch<CanonicalArgs> seg;
     Batch<ScanArgs> scan;
     for (int x = 0; x < n; ++x) {
@@ -1081,7 +1081,7 @@ int build_canonical(const BuildItem* items, int n, hipStream_t s) {
         int* const cnt = items[x].ws.segcnt[0];
         const int nseg = (int)cdiv(L->N, CSEG);
         L->views_valid = false;
-        uint2* const runs = L->runs_used && L->I % 32 == 0 ? L->runs : nullptr;
+        uint2* const runs = L->runs_kept(recording) && L->I % 32 == 0 ? L->runs : nullptr;
         seg.add(CanonicalArgs{L->mask, items[x].Wsrc, L->O, L->I, L->N, nseg, cnt, L->rowptr, L->flat, L->vals, runs}, cdiv(nseg, 4));
         scan.add(ScanArgs{cnt, cnt, nseg}, 1);
     }
@@ -1092,7 +1092,7 @@ int build_canonical(const BuildItem* items, int n, hipStream_t s) {
     launch_batch(seg, [&](const auto& b) { k_fill_canonical<<<b.grid(), 256, 0, s>>>(b); });
     MST_LAUNCH_CHECK();
     for (int x = 0; x < n; ++x)
-        if (items[x].L->runs_used && items[x].L->I % 32 == 0) items[x].L->runs_valid = items[x].L->runs != nullptr;
+        if (items[x].L->runs_kept(recording) && items[x].L->I % 32 == 0) items[x].L->runs_valid = items[x].L->runs != nullptr;
     return MST_OK;
 }
 
@@ -1161,16 +1161,20 @@ int active_runs(ActiveOut* active, hipStream_t s, ActiveRuns& runs, int64_t& str
     // of single values take more (bfloat16, 1288 x 1040, 3000 tokens: 30.1 us at a density of 0.5 and 31.0 at 0.9, so 31.4 and 32.5; at
     // 0.2 30.3, so 29.6.  5120 x 1280, 512 tokens: 28.8 and 31.6, so 27.6 and 30.2).
     if (4 * L->nnz > L->N && L->N < (int64_t)1 << 21) return MST_OK;
+    bool recording = false;
+    if (!L->runs_valid || !L->runs_recorded) {
+        const int rc = stream_recording(s, &recording);
+        if (rc != MST_OK) return rc;
+    }
     if (!L->runs_valid) {
-        bool recording;
-        int rc = stream_recording(s, &recording);
-        if (rc != MST_OK || recording) return rc;
-        rc = make_runs(&L, 1, s);
+        if (recording) return MST_OK;
+        const int rc = make_runs(&L, 1, s);
         if (rc != MST_OK) return rc;
         MST_HIP(hipStreamSynchronize(s));
         L->runs_valid = true;
     }
-    L->runs_used = true;
+    L->runs_recorded |= recording;
+    L->runs_unread = 0;
     runs = runs_of(L);
     active->stride = stride = (int64_t)align_up((size_t)L->nnz, 4);
     active->done = true;
@@ -1453,13 +1457,13 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     bool row = views, col = views, planes = dense && L->planes_valid, pairs = dense && L->pairs_valid && pairs_kept(L);
     L->planes_valid = planes;
     L->pairs_valid = pairs;
+    bool recording = false;
     if (dense && (L->planes_y || L->pairs_y.blocks || (views && !(L->row_walked && L->col_walked)))) {
         // Views that nothing has walked are left out, since the dense copy holds the values for their first walk.
         // A recording refreshes every built view and changes no flag of theirs: its replays come at any time, between
         // calls that walk a view for the first time, and it has not run yet.  It takes the planes along if a product has read them
         // or the last product call had bfloat16 activations that did not go to the packed pairs, in both directions; otherwise they count as missed.
         // (Recorded regardless, a replayed fp32 step of the GPT-2-small block took 1.217 ms instead of 1.194.)
-        bool recording;
         const int rcr = stream_recording(s, &recording);
         if (rcr != MST_OK) return rcr;
         if (recording) {
@@ -1485,7 +1489,8 @@ int mst_layer_sync_values(mst_layer_t* L, mst_stream_t stream) {
     // 5120 took 30: four stores of two bytes per value, two of them far apart.)
     if (rc != MST_OK) return rc;
     if (with_pairs) {
-        L->runs_used = true;
+        L->runs_recorded |= recording;
+        L->runs_unread = 0;
         const ActiveRuns words = runs_of(L);
         const int rcw = make_pairs(L, s, &words);
         if (rcw != MST_OK) return rcw;

@@ -806,7 +806,7 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
         items[x].L->choice.store(0, std::memory_order_relaxed);
         if (items[x].L->pairs_calls >= PAIRS_CALLS) items[x].L->pairs_unknown();
         items[x].L->runs_valid = false;
-        if (items[x].L->runs_used) runs[n_runs++] = items[x].L;
+        if (items[x].L->runs_kept(recording)) runs[n_runs++] = items[x].L;
         else items[x].L->runs_missed |= recording;
     }
     if (n_views > 0 && (rc = build_views(views, n_views, s)) != MST_OK) return rc;
@@ -821,10 +821,13 @@ int mask_update_device(const UpdateItem* items, int n, hipStream_t s) {
         if (L->pairs_valid && (rc = make_pairs(L, s)) != MST_OK) return rc;
         L->pairs_matched = L->pairs_valid;
     }
-    if (n_canonical > 0 && (rc = build_canonical(canonical, n_canonical, s)) != MST_OK) return rc;
+    if (n_canonical > 0 && (rc = build_canonical(canonical, n_canonical, recording, s)) != MST_OK) return rc;
     if (n_runs == 0) return MST_OK;
     rc = make_runs(runs, n_runs, s);
-    for (int x = 0; rc == MST_OK && x < n_runs; ++x) runs[x]->runs_valid = true;
+    for (int x = 0; x < n_runs; ++x) {
+        runs[x]->runs_valid = rc == MST_OK;
+        runs[x]->runs_unread += runs[x]->runs_unread >= 0 && runs[x]->runs_unread < mst_layer::RUNS_UNREAD;
+    }
     return rc;
 }
 

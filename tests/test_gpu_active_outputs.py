@@ -203,6 +203,51 @@ def test_two_threads_behind_an_update_that_left_the_words():
         _check(rig, dY, X, act, dW)
 
 
+@pytest.mark.parametrize("O,I", [(1024, 256), (776, 272)])
+@pytest.mark.parametrize("updates", [1, 8, 9, 20])
+def test_updates_that_make_the_words_for_nobody(updates, O, I):
+    """Behind eight updates that nothing read the words of, an update leaves them to the next product.  A recorded product, which cannot make
+    them, shows which: it writes active positions alone where they are there.  Then it is read by its replays, and every update makes them."""
+    T, act, side = 512, mst.MST_BF16, torch.cuda.Stream()
+    mst.mst_gemm_force_fp32_mfma(256)
+    rig = _rig(O, I, T, 0.1)
+    L = rig.layer
+    X, dY = _numbers(T, I, act, 1), _numbers(T, O, act, 2)
+    score = torch.randn(O, I, device=DEV)
+    density = L.nnz / (O * I)
+    assert _writes_active(rig, dY, X, act)
+    for k in range(updates):
+        mst.mst_mask_update_from_scores(L, score, density, 0.3, 0.25, 20 + k, rig.ws)
+    dW = torch.full((L.nnz + 64,), 7.0, device=DEV)
+    ws = rig.ws[:rig.ws.numel() & ~3].view(torch.int32)
+
+    def record():
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph, stream=side):
+            mst.mst_sparse_fc_bwd_weight(L, dY, X, dW, T, rig.ws, act, side)
+        return graph
+
+    def replay(graph):
+        ws.fill_(0x5A5A5A5A)
+        dW.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        _check(rig, dY, X, act, dW)
+        written = int((ws != 0x5A5A5A5A).sum())
+        return written == 0 or written % (O * I) != 0
+
+    graph = record()
+    for _ in range(3):
+        assert replay(graph) == (updates <= 8)
+    assert _writes_active(rig, dY, X, act)                    # (an eager one makes them)
+    graph = record()
+    for k in range(12):                                       # (the recorded product has read them)
+        assert replay(graph)
+        mst.mst_mask_update_from_scores(L, score, density, 0.3, 0.25, 50 + k, rig.ws)
+    assert replay(graph) and _writes_active(rig, dY, X, act)
+
+
 @pytest.mark.parametrize("O,I", [(512, 512), (1280, 320), (64, 2048)])
 def test_a_handover_that_packs(O, I):
     """Values handed over, eagerly and by a recording, before and behind an update, while products read the packed weights: those, the
