@@ -35,10 +35,12 @@ constexpr int PAIR_TAIL = 16;    // readable step pairs past the last one (a who
 __host__ __device__ inline uint32_t lds_off(uint32_t k) { return (k << 8) | (((k >> 2) & 3u) << 4); }
 
 // Sparse matrix S [R x K] as the product kernels walk it.  Rows are grouped in blocks of
-// RB = 128 consecutive rows.  Inside a block the rows are ranked by their total length
-// (longest first, lower index first on ties); the row of rank 8o + g belongs to octet o and
-// lane group g, so the eight rows of an octet have similar lengths (little ELL padding even
-// when row lengths are very uneven).  rowmap[128b + rank] is that row.  For every
+// RB = 128 consecutive rows.  Inside a block every row has a place; the row of place 8o + g
+// belongs to octet o and lane group g.  The places are ranks by the rows' total length (longest
+// first, lower index first on ties), or, where that takes fewer pairs, come from halving the block
+// by the lengths in parts of the chunks (k_block_rank): the eight rows of an octet have similar
+// lengths, in every chunk (little ELL padding even when row lengths are very uneven).
+// rowmap[128b + place] is that row.  For every
 // (chunk c of K, block b, octet o) the eight rows' entries inside the chunk are stored side
 // by side, padded with zero-weight entries to the longest of the eight and to an even
 // count (an ELL slice of height 8): step j of the octet holds one entry per lane group.
@@ -61,8 +63,8 @@ struct View {
     int* ptr = nullptr;    // [nseg + 1] first pair of segment (c*NBpad + b)*16 + o
     uint4* ent = nullptr;  // [cap_pairs * 8]
     int* perm = nullptr;   // [cap_pairs * 16] canonical index of entry slot (pair*8 + g)*2 + half, -1 = padding
-    int* rowmap = nullptr; // [NBpad * 128] rank inside the block -> row (identity in the empty blocks)
-    int* rowpos = nullptr; // [NBpad * 128] row -> rank inside its block
+    int* rowmap = nullptr; // [NBpad * 128] place inside the block -> row (identity in the empty blocks)
+    int* rowpos = nullptr; // [NBpad * 128] row -> place inside its block
     int nsub() const { return nchunk * msub; }
 };
 

@@ -618,7 +618,8 @@ static ExactPlan plan_exact(bool three, bool tn, int M, int N, int Kdim, bool a1
     return best;
 }
 
-// (with two 128 x 128 workgroups on a CU: the lines between the kernels were drawn with these times)
+// For the choice between these kernels and others, whose lines were drawn with these times: as if two 128 x 128 workgroups on a CU were the only
+// way.  (Of 8000 products 128 to 8192 wide 6 % are modelled more than 5 % too long by that, one 40 %.)
 double gemm_exact_us(mst_dtype a_dt, int M, int N, int Kdim, int64_t max_split, bool summed) {
     return plan_exact(false, false, M, N, Kdim, a_dt == MST_BF16, max_split, summed).us;
 }

@@ -24,8 +24,8 @@ constexpr int BM = 128, BN = 128;      // bf16 kernel tile
 // [8 k x 8 m] patch with eight 16-byte loads (threads 0..127 the A tile, 128..255 the B
 // tile; a wavefront reads four 256-byte row pieces per load), transposes it in registers
 // and stores eight 16-byte rows [m][8 k].  Workgroup tile 128 x 128 x 64; an LDS row is 64 k
-// = 128 bytes = eight 16-byte units, unit u of row m is kept at position u ^ ((m >> 1) & 7):
-// the MFMA operand reads of 16 consecutive rows then cover all banks once.
+// = 128 bytes = eight 16-byte units, unit u of row m is kept where bf_unit says: the MFMA operand reads of
+// 16 consecutive rows then cover all banks once.
 constexpr int BKH = 64;            // k per LDS tile
 
 

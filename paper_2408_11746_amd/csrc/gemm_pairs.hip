@@ -773,10 +773,12 @@ static int launch_pairs(const void* A, const PairsView& v, float* C, int T, int 
     return MST_OK;
 }
 
-// What the second weights add to the steps' time where a share `second` of them has any: the wavefronts of the 64-row groups without wait
-// for the others, so a step with one such group costs a third of a step and one with four of them a whole one (taken as
-// 1.5: such masks have full rows, and stay with the dense kernels where those are as fast).  (Y of 768 -> 3072, 8190
+// What the second weights add to the steps' time where a share `second` of them has any.  The groups of 64 rows are taken to be alike; the
+// wavefronts of those without wait for the others, so a step with one such group is long by a third.  (Uniform masks, Y of 768 -> 3072, 8190
 // tokens, fp32, densities 0.07, 0.10, 0.11, 0.12, 0.25: 71, 73, 81, 100, 133 us; bfloat16, 256 tokens: 55, 57, 64, 75, 89.)
+// Every step with some is modelled as 2.5 steps, and more than it takes: with a full row in every 64 Y of 1280 -> 5120 takes 285 us (without
+// 167), of 768 -> 3072 108 (75), of 1280 -> 1280 106 (62); the dense kernels 256, 96 and 69, which are right there.  With one in every 256 it
+// takes 213, 82 and 84, and the first two of these stay on the dense kernels all the same.
 static double second_part(double second, bool bf16) {
     const double group = 1.0 - std::sqrt(std::sqrt(1.0 - second));        // share of the steps in which a group has some
     return (bf16 ? 0.40 : 0.35) * second + 1.15 * group * group;

@@ -53,7 +53,9 @@ static bool whole_tiles(const mst_layer* L, mst_dtype act, int T) {
     return T >= 2048 && T % tile == 0 && L->O % tile == 0 && L->I % tile == 0;
 }
 static bool mostly_dense(const mst_layer* L) { return (double)L->nnz > 0.30 * (double)L->N; }
-static double dense_wgrad_us(const mst_layer* L, mst_dtype act, int T, bool full) {      // the sum of the k ranges is part of the gather
+// (The sum of the k ranges as part of a gather from whole partial outputs.  Rows of whole eights have had neither since their kernels write
+// the active positions alone, up to a quarter sooner; the lines drawn with this model stay where they are, on the side of the walk.)
+static double dense_wgrad_us(const mst_layer* L, mst_dtype act, int T, bool full) {
     return 3.0 + gemm_mfma_us(GEMM_TN, act, L->O, L->I, T, GEMM_WS_SPLITS, false, full);
 }
 
@@ -121,7 +123,7 @@ bool use_sparse_input_grad(const mst_layer* L, mst_dtype act, int T) {
     if (act != MST_BF16 || L->path != MST_PATH_AUTO || whole_tiles(L, act, T) || !full_precision(L, WALK_BWD, act, T)) return false;
     return remembered(L, SPARSE_DX, act, T, [&] {
         const double modelled = dense_wgrad_us(L, act, T, true), wgrad = (L->O % 8 == 0 && L->I % 8 == 0 ? 0.95 : 1.14) * modelled;
-        const double us = walk_us(L, WALK_BWD_INPUT, T) + wgrad + 1.0e-6 * (double)L->N;   // (G as the gather reads it)
+        const double us = walk_us(L, WALK_BWD_INPUT, T) + wgrad + 1.0e-6 * (double)L->N;   // (a read of G by the gather, also where there is none: see dense_wgrad_us)
         return 1.05 * us < walk_us(L, WALK_BWD, T) && 1.2 * us < dense_backward_us(L, act, T) - modelled + wgrad;
     });
 }
@@ -1158,8 +1160,10 @@ int active_runs(ActiveOut* active, hipStream_t s, ActiveRuns& runs, int64_t& str
     mst_layer* L = const_cast<mst_layer*>(active->L);        // a cache of the mask, not layer state
     if (!L->runs || L->runs_missed || L->nnz == 0) return MST_OK;
     // Small layers with many active weights stay on whole outputs: their planes stay in the caches, and the gather of them takes what the stores
-    // of single values take more (bfloat16, 1288 x 1040, 3000 tokens: 30.1 us at a density of 0.5 and 31.0 at 0.9, so 31.4 and 32.5; at
-    // 0.2 30.3, so 29.6.  5120 x 1280, 512 tokens: 28.8 and 31.6, so 27.6 and 30.2).
+    // of single values take more.  Whole and a gather, active positions alone (us): bfloat16, 1288 x 1040, 3000 tokens, densities 0.2, 0.5, 0.9:
+    // 30.7 and 30.4, 31.1 and 32.6, 32.0 and 34.1; 768 x 2304, 4096 tokens: 36.9 and 31.5, 37.7 and 34.0, 39.1 and 38.0.  fp32 loses less by it:
+    // the first 67.0 and 63.6, 66.6 and 64.7, 67.1 and 65.8; 768 x 768, 8192 tokens, at 0.9: 53.2 and 53.8.  Above the line 4096 x 1024, 4096
+    // tokens, at 0.5 and 0.9: bfloat16 51.1 and 46.2, 53.4 and 51.4, fp32 103 and 97, 106 and 104.
     if (4 * L->nnz > L->N && L->N < (int64_t)1 << 21) return MST_OK;
     bool recording = false;
     if (!L->runs_valid || !L->runs_recorded) {

@@ -35,8 +35,9 @@
 //     the case above, 150 -> 135 us);
 //   - the weight goes through one v_mov_b32_dpp: a plain v_fmac_f32 issues in 3.4 clocks, one with a
 //     DPP operand in 5.2;
-//   - the wavefronts' octets are dealt in a snake over the blocks of the slab, so that the longest
-//     octets of different blocks (rows are ranked by length in a block) meet in no wavefront;
+//   - the wavefronts' octets are dealt in a snake over the blocks of the slab (octet w, then 15 - w), so that the longest
+//     octets of blocks whose rows are ranked by length meet in no wavefront.  In blocks whose rows are halved by the lengths in parts of
+//     the chunks no octet is the longest: 15 - w is of the other half in the first and the third split and of the same in the others;
 //   - a wavefront's priority falls with the octets it has left.  With equal ones the oldest wavefront of a SIMD unit is
 //     served first: of a chunk's 7 us at 1280 -> 5120, density 0.02, the last wavefront walked 2.6 us longer than the mean
 //     one, alone on its unit and waiting for its own reads, with the priorities 0.9 us.  Y there 118 -> 113, at density 0.05
