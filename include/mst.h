@@ -100,7 +100,9 @@ int mst_last_hip_error(void);           /* hipError_t of the last failing HIP ca
  * multiples of 32 and one of them of 256 room for the two split copies that products of bfloat16 activations
  * read (8 bytes per position, whatever the activations are; untouched with fp32 ones), and if O and I are multiples of
  * 64 room for the packed copies that products on the sparse matrix instructions read (8.5 bytes per position, more where
- * O or I is no multiple of 256; untouched until such a product runs).  0 on invalid arguments. */
+ * O or I is no multiple of 256; untouched until such a product runs).  If I is a multiple of 8 also the active words that
+ * weight gradients read (see mst_sparse_fc_bwd_weight; 8 bytes per 32 columns of a row, made when the layer is loaded).
+ * 0 on invalid arguments. */
 size_t mst_layer_device_bytes(int O, int I, int64_t nnz_capacity);
 
 /* Bytes of workspace sufficient for every call below on a layer of this shape with
@@ -143,7 +145,8 @@ int mst_layer_export_dense(const mst_layer_t* layer, float* W_dev, uint8_t* M_de
  * recorded with it if such a product has read it or the layer's last product call had bfloat16
  * activations that do not read the packed copies for both Y and dX; the packed copies are recorded with it if one of the last eight
  * hand-overs was read by a product on them.  After a recording without one of them the products that read it make it anew in
- * every call, for the rest of the layer's life: record behind a step or two at the density at which the replays will run.)  Every
+ * every call, for the rest of the layer's life: record behind a step or two at the density at which the replays will run.
+ * Where the active words are there the packed copies and the dense one take the values in one launch instead of two.)  Every
  * mask update changes the set and therefore the meaning of position k of this vector. */
 int mst_layer_values(mst_layer_t* layer, float** vals_dev, int64_t* nnz);
 int mst_layer_sync_values(mst_layer_t* layer, mst_stream_t stream);
@@ -216,7 +219,14 @@ int mst_sparse_fc_fwd(const mst_layer_t* layer, const void* X_dev, float* Y_dev,
 int mst_sparse_fc_bwd_input(const mst_layer_t* layer, const void* dY_dev, float* dX_dev, int T,
                             mst_dtype act, mst_stream_t stream);
 
-/* dW_dev [nnz] = sum_t dY[t, o] X[t, i] for the active (o, i), ascending flat index. */
+/* dW_dev [nnz] = sum_t dY[t, o] X[t, i] for the active (o, i), ascending flat index.
+ * (On the dense kernels of layers with rows of whole eights the active words of the mask say where each result goes.  mst_layer_load_dense makes
+ * them; an update makes them again if a product or a hand-over has read them, unless the eight updates before it did so for
+ * nobody, and always once a recorded call has read them.  Otherwise the next weight gradient that reads them -- this call or mst_sparse_fc_bwd -- makes
+ * them and waits for that on `stream`, once, so that products on other streams need an order after the update alone.  While a graph is
+ * recorded nothing waits: without them the recorded product forms the whole gradient and gathers from it.  An update that is recorded
+ * before anything has read them does not carry them, and its replays come when they like: for the rest of the layer's life, a
+ * reload included, its products gather and its hand-overs take two launches.  So let one step run before an update is recorded.) */
 int mst_sparse_fc_bwd_weight(const mst_layer_t* layer, const void* dY_dev, const void* X_dev,
                              float* dW_dev, int T, mst_dtype act,
                              void* ws_dev, size_t ws_bytes, mst_stream_t stream);
@@ -334,7 +344,8 @@ int mst_update_counts(int64_t n_total, int64_t nnz, double target_density, doubl
  *   apply  pruned and grown weights are 0; kept weights keep their value; the index
  *          views are rebuilt.  |.| compares fp32 bit patterns with the sign cleared.
  * The new active count is known on return (host arithmetic); the device work is
- * asynchronous.  stats_out (host) may be NULL. */
+ * asynchronous.  stats_out (host) may be NULL.  (mst_sparse_fc_bwd_weight says what an update that is recorded
+ * before the layer's first step leaves out for good.) */
 int mst_mask_update_from_scores(mst_layer_t* layer, const float* G_dev,
                                 double target_density, double zeta, double rand_ratio,
                                 uint64_t rng_seed, void* ws_dev, size_t ws_bytes,
