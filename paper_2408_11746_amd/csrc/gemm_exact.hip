@@ -575,7 +575,7 @@ void k_gemm_stream(const void* __restrict__ Av, int64_t lda, const void* __restr
 // two and 212 with three, of 1203 -> 801, 16001 tokens (882 tiles), 191 and 212.  (bfloat16 A: three always, as its constants were fitted.)
 // With both operands k-major 1.51 times, and less by a twentieth where a second round follows the first, whose workgroups do not
 // end together (104 outputs of 10^6 and more, one to eight ranges; 1.56 and nothing off took one range where several with a second round were
-// ahead: 2304 x 3840, 3001 tokens, density 0.5, 336 us with one range, 283 with five, 309 before three were a choice).
+// ahead: 2304 x 3840, 3001 tokens, 342 us with one range, 283 with five).
 struct ExactPlan {
     int tile;
     bool stream;

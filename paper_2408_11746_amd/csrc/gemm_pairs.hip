@@ -29,9 +29,10 @@
 // Measured (us; before = one workgroup per tile, weights through registers, second weights as steps of their own behind the others; 8192
 // tokens, fp32, 0.10): Y of 1280 -> 5120 199 -> 172, dX of it 210 -> 197; Y of 768 -> 3072 78 -> 69, dX of it 80 -> 70.  16384 tokens,
 // bfloat16, 0.05: Y of 1024 -> 4096 143 -> 138, dX 113.5 -> 113.
-// What bounds it: a step of fp32 takes 2000 to 2600 clocks, 1536 of them matrix instructions (before 2600), but at 1.55 GHz where it was
-// 1.65 to 1.97: the chip lowers its clock for what it does per clock.  bfloat16: 2700 clocks of which 2048 are products, and 9000 to 12000
-// for the 256 KB of outputs of a tile, all workgroups at once.  Workgroups that start at different times (up to 10 us apart) gained nothing
+// What bounds it: Y of 1280 -> 5120 keeps the CUs busy for 75 million clocks (before 90), 54 % of them matrix instructions (45), dX for 78 (92),
+// 52 % (44); the bfloat16 products for 62 (69) and 50 (52), 54 % (49) and 67 % (64), what is left mostly the 256 KB of outputs of a tile, all
+// workgroups at once.  One product at a time runs at 1.8 to 2.0 GHz; one behind the other the same clocks take up to a quarter
+// longer (176 to 217 us in one trace).  Workgroups that start at different times (up to 10 us apart) gained nothing
 // in fp32 and 2 % in bfloat16, outputs past the L2 or through it are the same.
 #include <cmath>
 #include <type_traits>
