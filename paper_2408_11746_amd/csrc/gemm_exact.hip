@@ -184,7 +184,7 @@ struct ExOperand {
 // Tile numbers run in bands of eight tile rows, column by column inside a band (the tiles an XCD works on
 // at a time share operand panels in its L2); XCD x takes a contiguous share, one k range after the other.
 // PER_CU: workgroups on a CU that the registers are for (plan_exact's choice; 0: as many as the LDS holds).  With both operands k-major always
-// three, two of them held apart by their LDS: the code for two needs no more registers (170), and alone on its CU it is 9 % slower (dense
+// three, two of them held apart by their LDS: the code for two takes three registers more (170) and is, alone on its CU, 9 % slower (dense
 // gradients of 1048 x 792, 385 tokens, to 5000 x 4000, one k range; half of the 80 shapes are 10 % slower with it).
 // ACTIVE: only the active outputs, side by side (C and split_stride are of them).  Whole outputs and a gather -> this: 4000 x 1000 at a density of
 // 0.2, 5001 tokens 215 us, so 208, 1000 tokens 54.2, so 49.4; 5000 x 4000 at 0.9, 700 tokens 180, so 149.
